@@ -60,6 +60,16 @@ static int get_masked_stream(spd_ctx* ctx, int phase, const std::vector<uint32_t
   return SPD_OK;
 }
 
+static int stage_alloc(spd_stage* st, size_t cap) {
+  char *h = nullptr, *d = nullptr;
+  SPD_HIP(hipHostMalloc((void**)&h, cap, hipHostMallocDefault));
+  hipError_t e = hipHostGetDevicePointer((void**)&d, h, 0);
+  if (e != hipSuccess) { (void)hipHostFree(h); return hip_fail(e); }
+  if (st->host) (void)hipHostFree(st->host);
+  st->host = h; st->dev = d; st->cap = cap;
+  return SPD_OK;
+}
+
 extern "C" int spd_ctx_create(int device, spd_ctx** out) {
   if (!out || device < -1) return SPD_EINVAL;
   spd_ctx* c = new (std::nothrow) spd_ctx();
@@ -99,18 +109,25 @@ extern "C" int spd_ctx_create(int device, spd_ctx** out) {
       if (rc == SPD_OK && e == hipSuccess) e = hipEventCreate(&s.ev_end);
       if (rc == SPD_OK && e == hipSuccess) e = hipEventCreateWithFlags(&s.ev_switch, hipEventDisableTiming);
       if (rc == SPD_OK && e == hipSuccess) e = hipEventCreateWithFlags(&s.ev_cross, hipEventDisableTiming);
-      // The decode phase's staging ring exists from the start, with the capacity the entry point that
-      // allocates nothing works with; each slot has a device twin of its own and one in the scratch array.
+      for (spd_seal& seal : s.seals)
+        if (rc == SPD_OK && e == hipSuccess) e = hipEventCreateWithFlags(&seal.ev, hipEventDisableTiming);
+      if (rc == SPD_OK && e == hipSuccess) e = hipHostMalloc((void**)&s.flag, sizeof(uint64_t), hipHostMallocDefault);
+      if (rc == SPD_OK && e == hipSuccess) {
+        *s.flag = 0;
+        e = hipHostGetDevicePointer((void**)&s.flag_dev, s.flag, 0);
+      }
+      if (rc == SPD_OK && e == hipSuccess) e = hipMalloc((void**)&s.rope_dev, sizeof(double) * ROPE_TABLE_DIM / 2);
+      if (rc == SPD_OK && e == hipSuccess && ph == SPD_PHASE_DECODE) {
+        e = hipMalloc((void**)&s.merge_counters, sizeof(uint32_t) * MERGE_COUNTERS);
+        if (e == hipSuccess) e = hipMemset(s.merge_counters, 0, sizeof(uint32_t) * MERGE_COUNTERS);
+        if (e == hipSuccess) e = hipDeviceSynchronize();
+      }
+      // The decode phase's staging ring exists from the start, with room for everything the entry point that
+      // allocates nothing takes.
       if (rc == SPD_OK && e == hipSuccess && ph == SPD_PHASE_DECODE) {
         rc = scratch_resolve(device, &c->scratch);
-        for (int i = 0; rc == SPD_OK && e == hipSuccess && i < 4; ++i) {
-          spd_stage& st = s.ring[i];
-          e = hipHostMalloc((void**)&st.host, NOALLOC_STAGE_BYTES, hipHostMallocDefault);
-          if (e == hipSuccess) e = hipMalloc((void**)&st.dev, NOALLOC_STAGE_BYTES);
-          if (e == hipSuccess) e = hipEventCreateWithFlags(&st.done, hipEventDisableTiming);
-          st.cap = NOALLOC_STAGE_BYTES;
-          st.dev_static = c->scratch + (size_t)i * NOALLOC_STAGE_BYTES;
-        }
+        for (spd_stage& st : s.ring)
+          if (rc == SPD_OK) rc = stage_alloc(&st, NOALLOC_RING_BYTES);
       }
       if (rc != SPD_OK || e != hipSuccess) {
         if (e != hipSuccess) hip_fail(e);
@@ -130,11 +147,13 @@ extern "C" int spd_ctx_destroy(spd_ctx* ctx) {
     for (auto& kv : ctx->stream_cache) (void)hipStreamSynchronize(kv.second);
     for (int ph = 0; ph < 2; ++ph) {
       spd_phase_state& s = ctx->phase[ph];
-      for (spd_stage& st : s.ring) {
+      for (spd_stage& st : s.ring)
         if (st.host) (void)hipHostFree(st.host);
-        if (st.dev) (void)hipFree(st.dev);
-        if (st.done) (void)hipEventDestroy(st.done);
-      }
+      for (spd_seal& seal : s.seals)
+        if (seal.ev) (void)hipEventDestroy(seal.ev);
+      if (s.flag) (void)hipHostFree(s.flag);
+      if (s.rope_dev) (void)hipFree(s.rope_dev);
+      if (s.merge_counters) (void)hipFree(s.merge_counters);
       if (s.workspace) (void)hipFree(s.workspace);
       for (auto& r : s.ws_retired) (void)hipFree(r.first);
       for (hipEvent_t e : {s.ev_start, s.ev_end, s.ev_switch, s.ev_cross})
@@ -212,6 +231,8 @@ int phase_enter(spd_ctx* ctx, int phase, hipStream_t* stream_out) {
   spd_phase_state& s = ctx->phase[phase];
   if (s.has_pending) {
     if (s.pending_stream != s.stream) {
+      int rc = phase_seal(ctx, phase, s.stream);
+      if (rc != SPD_OK) return rc;
       SPD_HIP(hipEventRecord(s.ev_switch, s.stream));
       SPD_HIP(hipStreamWaitEvent(s.pending_stream, s.ev_switch, 0));
       s.stream = s.pending_stream;
@@ -230,80 +251,92 @@ static void raise_done_seq(spd_phase_state& s, uint64_t seq) {
   }
 }
 
+// Has step `seq` finished, as far as the phase's word in pinned memory says?  No runtime call.
+static bool flag_says_done(spd_phase_state& s, uint64_t seq) {
+  if (s.done_seq.load(std::memory_order_acquire) >= seq) return true;
+  const uint64_t f = __atomic_load_n(s.flag, __ATOMIC_ACQUIRE);
+  if (f < seq) return false;
+  raise_done_seq(s, f);
+  return true;
+}
+
 int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool may_alloc) {
   spd_phase_state& s = ctx->phase[phase];
   spd_stage& st = s.ring[s.ring_pos];
-  if (st.in_flight) {
-    // Poll, with pauses, instead of hipEventSynchronize: a blocking wait inside the runtime (and a
-    // tight polling loop as well) keeps the other phase's thread from launching meanwhile.
-    hipError_t e;
-    while ((e = hipEventQuery(st.done)) == hipErrorNotReady) std::this_thread::sleep_for(std::chrono::microseconds(20));
-    if (e != hipSuccess) return hip_fail(e);
-    st.in_flight = false;
-    raise_done_seq(s, st.seq.load(std::memory_order_relaxed));
+  // The slot's last step is STAGE_SLOTS steps back: the step after it reports its end.  The word is polled, first in a
+  // spin, then with pauses; the runtime is asked now and then only, because its calls keep the other phase's thread
+  // from launching (and to notice a device error).
+  for (int spins = 0; st.seq && !flag_says_done(s, st.seq); ++spins) {
+    if (spins < 4096) {
+      __builtin_ia32_pause();
+      continue;
+    }
+    std::this_thread::sleep_for(std::chrono::microseconds(20));
+    if (spins % 64 == 0) {
+      const hipError_t e = hipStreamQuery(s.stream);
+      if (e == hipSuccess) raise_done_seq(s, s.issue_seq.load(std::memory_order_relaxed));
+      else if (e != hipErrorNotReady) return hip_fail(e);
+    }
   }
-  if (!may_alloc && (!st.done || st.cap < bytes || !st.dev_static)) return SPD_ETOOBIG;
-  if (!st.done) SPD_HIP(hipEventCreateWithFlags(&st.done, hipEventDisableTiming));
+  st.seq = 0;
   if (st.cap < bytes) {
+    if (!may_alloc) return SPD_ETOOBIG;
     size_t cap = std::max<size_t>(256 * 1024, st.cap);
     while (cap < bytes) cap *= 2;
-    char *h = nullptr, *d = nullptr;
-    SPD_HIP(hipHostMalloc((void**)&h, cap, hipHostMallocDefault));
-    hipError_t e = hipMalloc((void**)&d, cap);
-    if (e != hipSuccess) { (void)hipHostFree(h); return hip_fail(e); }
-    if (st.host) (void)hipHostFree(st.host);
-    if (st.dev) (void)hipFree(st.dev);
-    st.host = h; st.dev = d; st.cap = cap;
+    int rc = stage_alloc(&st, cap);
+    if (rc != SPD_OK) return rc;
   }
   *out = &st;
   return SPD_OK;
 }
 
-int stage_host_as_device(spd_stage* st, void** out) {
-  SPD_HIP(hipHostGetDevicePointer(out, st->host, 0));
-  return SPD_OK;
-}
-
-int stage_copy(spd_stage* st, size_t bytes, hipStream_t stream, char* dev) {
-  // The step's metadata crosses to the device with a small copy kernel on the phase's own stream
-  // (pinned host memory is device-readable).  hipMemcpyAsync would put it on a copy path that the
-  // two phases share: with each phase driven by its own thread the copies then wait for each
-  // other's predecessors and one phase starves the other.
-  void* host_dev = nullptr;
-  SPD_HIP(hipHostGetDevicePointer(&host_dev, st->host, 0));
-  SPD_HIP(launch_copy(dev ? dev : st->dev, host_dev, (bytes + 15) & ~(size_t)15, 1, stream));
-  return SPD_OK;
-}
-
-// Called behind the step's last kernel: the slot's event then also says that the step has finished, which is
-// what spd_kv_free asks about.
-int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, size_t bytes, hipStream_t stream, bool copy, char* dev) {
+int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, hipStream_t stream) {
   spd_phase_state& s = ctx->phase[phase];
-  if (copy) {
-    int rc = stage_copy(st, bytes, stream, dev);
-    if (rc != SPD_OK) return rc;
-  }
-  SPD_HIP(hipEventRecord(st->done, stream));
-  st->seq.store(s.issue_seq.load(std::memory_order_relaxed) + 1, std::memory_order_release);   // after the record
-  s.issue_seq.fetch_add(1, std::memory_order_release);
-  st->in_flight = true;
-  s.ring_pos = (s.ring_pos + 1) % 4;
+  st->seq = s.issue_seq.fetch_add(1, std::memory_order_release) + 1;
+  s.ring_pos = (s.ring_pos + 1) % STAGE_SLOTS;
+  return s.stream_lent.load(std::memory_order_relaxed) ? phase_seal(ctx, phase, stream) : SPD_OK;
+}
+
+StepMark step_mark(spd_ctx* ctx, int phase) {
+  spd_phase_state& s = ctx->phase[phase];
+  return StepMark{s.flag_dev, s.issue_seq.load(std::memory_order_relaxed)};
+}
+
+int phase_seal(spd_ctx* ctx, int phase, hipStream_t stream) {
+  spd_phase_state& s = ctx->phase[phase];
+  std::lock_guard<std::mutex> lk(s.seal_mu);            // spd_phase_stream may be asked from any thread
+  const uint64_t seq = s.issue_seq.load(std::memory_order_acquire);
+  if (seq == 0 || s.sealed_seq >= seq || flag_says_done(s, seq)) return SPD_OK;
+  spd_seal& seal = s.seals[s.seal_pos];
+  SPD_HIP(hipEventRecord(seal.ev, stream));
+  seal.seq.store(seq, std::memory_order_release);       // after the record
+  s.seal_pos = (s.seal_pos + 1) % STAGE_SLOTS;
+  s.sealed_seq = seq;
   return SPD_OK;
 }
 
 bool phase_step_done(spd_ctx* ctx, int phase, uint64_t seq) {
   if (seq == 0 || ctx->device < 0) return true;
   spd_phase_state& s = ctx->phase[phase];
-  if (s.done_seq.load(std::memory_order_acquire) >= seq) return true;
+  if (flag_says_done(s, seq)) return true;
   (void)hipSetDevice(ctx->device);
-  // A slot whose number is `seq` or later carries an event recorded behind that step's last kernel (the number is
+  // A seal whose number is `seq` or later carries an event recorded behind that step's last kernel (the number is
   // stored after the record, so reading it first means the event is at least that recent).
-  for (spd_stage& st : s.ring) {
-    const uint64_t q = st.seq.load(std::memory_order_acquire);
-    if (q >= seq && st.done && hipEventQuery(st.done) == hipSuccess) {
+  for (spd_seal& seal : s.seals) {
+    const uint64_t q = seal.seq.load(std::memory_order_acquire);
+    if (q >= seq && hipEventQuery(seal.ev) == hipSuccess) {
       raise_done_seq(s, q);
       return true;
     }
+  }
+  // The last step of the phase has no later one to report it: it has finished if the stream is idle.
+  // (The count is read before the stream: whichever stream is current after that waits for the one before it.)
+  const uint64_t issued = s.issue_seq.load(std::memory_order_acquire);
+  hipStream_t stream;
+  { std::lock_guard<std::mutex> lk(ctx->part_mu); stream = s.stream; }
+  if (issued >= seq && hipStreamQuery(stream) == hipSuccess) {
+    raise_done_seq(s, issued);
+    return true;
   }
   (void)hipGetLastError();      // hipErrorNotReady is not an error to keep
   return false;
@@ -405,6 +438,8 @@ extern "C" int spd_phase_wait_for(spd_ctx* ctx, int phase, int other) {
   if (ctx->device < 0) return SPD_ESTATE;
   std::lock_guard<std::mutex> lk(ctx->part_mu);
   spd_phase_state& me = ctx->phase[phase];
+  int rc = phase_seal(ctx, phase, me.stream);
+  if (rc != SPD_OK) return rc;
   SPD_HIP(hipEventRecord(me.ev_cross, ctx->phase[other].stream));
   SPD_HIP(hipStreamWaitEvent(me.stream, me.ev_cross, 0));
   return SPD_OK;
@@ -415,7 +450,8 @@ extern "C" int spd_phase_stream(spd_ctx* ctx, int phase, void** hip_stream_out) 
   if (ctx->device < 0) return SPD_ESTATE;
   std::lock_guard<std::mutex> lk(ctx->part_mu);
   *hip_stream_out = (void*)ctx->phase[phase].stream;
-  return SPD_OK;
+  ctx->phase[phase].stream_lent = true;                 // from here on every step gets its seal at once
+  return phase_seal(ctx, phase, ctx->phase[phase].stream);
 }
 
 extern "C" int spd_phase_last_ms(spd_ctx* ctx, int phase, float* ms) {
@@ -432,6 +468,7 @@ extern "C" int spd_phase_copy(spd_ctx* ctx, int phase, void* dst, const void* sr
   hipStream_t stream;
   int rc = phase_enter(ctx, phase, &stream);
   if (rc != SPD_OK) return rc;
+  if ((rc = phase_seal(ctx, phase, stream)) != SPD_OK) return rc;
   SPD_HIP(launch_copy(dst, src, bytes, ctx->phase[phase].active_cus, stream));
   return SPD_OK;
 }
@@ -442,6 +479,7 @@ extern "C" int spd_phase_read(spd_ctx* ctx, int phase, const void* src, uint64_t
   hipStream_t stream;
   int rc = phase_enter(ctx, phase, &stream);
   if (rc != SPD_OK) return rc;
+  if ((rc = phase_seal(ctx, phase, stream)) != SPD_OK) return rc;
   SPD_HIP(launch_read(src, bytes, ctx->phase[phase].active_cus, nullptr, stream));
   return SPD_OK;
 }
@@ -452,6 +490,7 @@ extern "C" int spd_phase_read_lds(spd_ctx* ctx, int phase, const void* src, uint
   hipStream_t stream;
   int rc = phase_enter(ctx, phase, &stream);
   if (rc != SPD_OK) return rc;
+  if ((rc = phase_seal(ctx, phase, stream)) != SPD_OK) return rc;
   SPD_HIP(launch_read_lds(src, bytes, ctx->phase[phase].active_cus, nullptr, stream));
   return SPD_OK;
 }
@@ -482,6 +521,7 @@ extern "C" int spd_phase_probe_cus(spd_ctx* ctx, int phase, int32_t n_blocks, in
   if (rc != SPD_OK) return rc;
   char* ws = nullptr;
   if ((rc = workspace_reserve(ctx, phase, sizeof(int32_t) * (size_t)n_blocks, &ws)) != SPD_OK) return rc;
+  if ((rc = phase_seal(ctx, phase, stream)) != SPD_OK) return rc;
   SPD_HIP(launch_probe((int32_t*)ws, n_blocks, stream));
   std::vector<int32_t> host((size_t)n_blocks);
   SPD_HIP(hipMemcpyAsync(host.data(), ws, sizeof(int32_t) * (size_t)n_blocks, hipMemcpyDeviceToHost, stream));

@@ -22,6 +22,7 @@ extern "C" int spd_ffn_pack_gate_up(spd_ctx* ctx, int phase, const void* w_gate,
   if (ctx->device < 0) return SPD_ESTATE;
   hipStream_t stream;
   if ((rc = phase_enter(ctx, phase, &stream)) != SPD_OK) return rc;
+  if ((rc = phase_seal(ctx, phase, stream)) != SPD_OK) return rc;
   SPD_HIP(launch_ffn_pack(w_gate, w_up, w_gu, hidden, inter, stream));
   return SPD_OK;
 }
@@ -38,6 +39,7 @@ extern "C" int spd_ffn_gate_up(spd_ctx* ctx, int phase, const void* x, const voi
   hipStream_t stream;
   if ((rc = phase_enter(ctx, phase, &stream)) != SPD_OK) return rc;
   if ((rc = kernel_timing_mark(ctx, phase, 0, stream)) != SPD_OK) return rc;
-  SPD_HIP(launch_ffn_gate_up(x, w_gu, out, n_tokens, hidden, inter, ctx->xcds, std::max(1, ctx->phase[phase].active_cus), stream));
+  SPD_HIP(launch_ffn_gate_up(x, w_gu, out, n_tokens, hidden, inter, ctx->xcds, std::max(1, ctx->phase[phase].active_cus),
+                             step_mark(ctx, phase), stream));
   return kernel_timing_mark(ctx, phase, 1, stream);
 }

@@ -71,6 +71,42 @@ struct TileDesc {
   int32_t pad[3];    // pad[0]: logical position of the tile's token slot 0 in its request
 };
 
+// A step's first kernel stores `seq`, the number of the phase's step before it, at `flag`: that step has finished.
+struct StepMark {
+  uint64_t* flag;
+  uint64_t seq;
+};
+#if defined(__HIPCC__)
+__device__ inline void store_mark(const StepMark& m) {
+  if (m.flag) __hip_atomic_store(m.flag, m.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+#endif
+
+// Decode work item = one chunk of one request's context: this header, then the ids of the pages the chunk touches (the
+// first one is the page of the chunk's first token), the last id repeated up to the record's end.  Everything a
+// workgroup needs sits at an address it knows from its own number, so that it is had in one round trip, which counts
+// where the records are read over PCIe out of the staging buffer.
+struct DecodeItem {
+  int32_t req, chunk, n_chunks;
+  int32_t n;         // attended tokens of the request
+};
+
+// What a decode attention launch is given.
+struct DecodeLaunch {
+  const void *q, *k_new, *v_new;      // k_new: null without append
+  void* out;
+  const char* items;                  // n_items records of item_stride bytes
+  const int32_t* n_chunks;            // [B]
+  const double* w;                    // rot / 2 frequencies
+  int item_stride, n_items, B, H;
+  float scale;
+  int chunk_units, max_chunks;
+  int rot, off, interleaved;          // rot = 0: no rotation
+  float *ws_o, *ws_ml;
+  uint32_t* counters;                 // [B * Hkv] zeros: the chunks are merged by the last workgroup; null: by a launch of its own
+  StepMark mark;
+};
+
 // Prefill work item = one workgroup: one tile of query rows of one request, for a group of query
 // heads that share a KV head.  len == 0 marks a padding item (the workgroup exits at once).
 struct PrefillWork {
@@ -87,6 +123,11 @@ struct PrefillWork {
 // split-K partials and the rotated queries.
 constexpr size_t NOALLOC_STAGE_BYTES = 256u << 10;
 constexpr size_t NOALLOC_WS_BYTES = 32u << 20;
+// pinned bytes of a staging slot of the decode phase: the metadata of any batch within NOALLOC_STAGE_BYTES (which
+// counts one block table row per request) in the form the kernels read, one record per work item
+constexpr size_t NOALLOC_RING_BYTES = 1u << 20;
+constexpr size_t MERGE_COUNTERS = 4096;
+constexpr int STAGE_SLOTS = 8;             // steps of a phase in flight before a new one waits for the oldest
 constexpr size_t SCRATCH_BYTES = 4 * NOALLOC_STAGE_BYTES + NOALLOC_WS_BYTES;
 
 extern thread_local int g_last_hip_error;
@@ -115,14 +156,17 @@ struct spd_pool {
   std::unordered_map<uint64_t, spd_req_table> tables;
 };
 
-struct spd_stage {          // pinned host buffer + device twin, reused round-robin per phase
+struct spd_stage {          // pinned host buffer a step's metadata is read from, reused round-robin per phase
   char* host = nullptr;
-  char* dev = nullptr;
+  char* dev = nullptr;      // the same buffer as the device addresses it
   size_t cap = 0;
-  char* dev_static = nullptr;   // this slot's metadata twin inside the static scratch array (decode phase)
-  hipEvent_t done = nullptr;          // recorded behind the last kernel of the step that used the slot
-  bool in_flight = false;
-  std::atomic<uint64_t> seq{0};       // number of that step (stored after the event has been recorded)
+  uint64_t seq = 0;         // number of the last step that used the slot (0: none)
+};
+
+// An event recorded behind a step, for the steps whose end no later step of the phase reports (see phase_seal).
+struct spd_seal {
+  hipEvent_t ev = nullptr;
+  std::atomic<uint64_t> seq{0};       // that step's number (stored after the event has been recorded)
 };
 
 struct spd_phase_state {
@@ -132,12 +176,32 @@ struct spd_phase_state {
   int pending_cus = 0;
   bool has_pending = false;
   std::vector<uint32_t> active_mask, pending_mask;
-  spd_stage ring[4];
+  spd_stage ring[spd::STAGE_SLOTS];
   int ring_pos = 0;
+  // One word of pinned memory per phase: the first kernel of every step stores the number of the step before it, which
+  // the stream has finished by then.  Steps cost no event this way (an event record is 2 us of host time and 4 to 6 us
+  // of the stream's).
+  uint64_t* flag = nullptr;            // host address
+  uint64_t* flag_dev = nullptr;        // the same word as the device addresses it
+  spd_seal seals[spd::STAGE_SLOTS];
+  int seal_pos = 0;
+  std::mutex seal_mu;
+  uint64_t sealed_seq = 0;             // latest step with a seal of its own
+  std::atomic<bool> stream_lent{false};            // spd_phase_stream has handed the stream out: the caller's own work may follow any step
   std::atomic<uint64_t> issue_seq{0};  // steps (ring commits) of this phase so far; the next step's number is this + 1
   std::atomic<uint64_t> done_seq{0};   // a step number known to have finished on the GPU (steps of a phase finish in order)
   hipEvent_t ev_start = nullptr, ev_end = nullptr, ev_switch = nullptr, ev_cross = nullptr;
   bool timed = false;
+  // RoPE frequencies of the configuration the phase's steps used last, in device memory (rope_table)
+  double* rope_dev = nullptr;
+  spd_rope_config rope_key{};
+  bool rope_valid = false;
+  uint32_t* merge_counters = nullptr;  // decode phase: MERGE_COUNTERS zeros (split_merge.h), zero again after every step
+  // a step's working lists, kept from step to step (one thread drives a phase)
+  std::vector<uint64_t> tmp_set, tmp_items;
+  std::vector<spd_req_table*> tmp_tables;
+  std::vector<int32_t> tmp_sizes;
+  std::vector<int64_t> tmp_heap;
   char* workspace = nullptr;           // split-K partials (decode)
   size_t ws_cap = 0;
   // workspaces outgrown, with the number of the last step that may still read them: freed once that step has
@@ -169,12 +233,12 @@ int phase_enter(spd_ctx* ctx, int phase, hipStream_t* stream_out);   // adopt pe
 // may_alloc = false: SPD_ETOOBIG instead of growing the slot's buffers
 int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool may_alloc = true);
 int scratch_resolve(int device, char** out);   // noalloc.hip: address of `device`'s copy of the scratch array
-// copy = false: the caller has already launched a kernel that copies host -> dev (see launch_kv_write)
-// dev: the device twin to copy to (null: the slot's own st->dev)
-int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, size_t bytes, hipStream_t stream, bool copy = true,
-                 char* dev = nullptr);
-int stage_host_as_device(spd_stage* st, void** out);   // device-readable address of the pinned host buffer
-int stage_copy(spd_stage* st, size_t bytes, hipStream_t stream, char* dev = nullptr);   // host buffer -> device twin
+int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, hipStream_t stream);   // behind the step's last launch: the step has its number
+// what the first kernel enqueued behind the phase's last step stores (see spd_phase_state::flag)
+StepMark step_mark(spd_ctx* ctx, int phase);
+// Before anything but a step's first kernel goes onto the phase's stream: an event behind the last step, unless that
+// step is known to have finished or has one.
+int phase_seal(spd_ctx* ctx, int phase, hipStream_t stream);
 // true if step number `seq` of `phase` has finished on the GPU (any thread may ask)
 bool phase_step_done(spd_ctx* ctx, int phase, uint64_t seq);
 int workspace_reserve(spd_ctx* ctx, int phase, size_t bytes, char** out);
@@ -182,34 +246,36 @@ int kernel_timing_mark(spd_ctx* ctx, int phase, int which, hipStream_t stream); 
 // rope.cpp: SPD_OK if the configuration is well-formed; the frequency table (rotary_dim / 2 doubles)
 int rope_config_check(const spd_rope_config* c);
 void rope_frequencies(const spd_rope_config* c, double* out);
+// The frequency table of `c` in device memory, valid for the phase's work enqueued from here on.  A configuration the
+// phase has not just used is written to a staging slot and copied by a launch of its own (rotary_dim <= ROPE_TABLE_DIM).
+constexpr int ROPE_TABLE_DIM = 1024;
+int rope_table(spd_ctx* ctx, int phase, const spd_rope_config* c, char* host, const char* host_dev, hipStream_t stream, StepMark* mark,
+               const double** out);
 
-// kernel launchers (kernels_*.hip); all enqueue on `stream` and return the launch status
+// kernel launchers (kernels_*.hip); all enqueue on `stream` and return the launch status; `mark` is stored by the launch
+// where it is the first one behind a step (flag null: it is not)
 // d_tiles may be device-readable pinned host memory.  With copy_dst non-null the same launch also
 // copies copy_bytes (rounded up to 16) from copy_src to copy_dst.
 // With rope_w non-null (device or device-readable pinned: rot / 2 frequencies) the key rows are rotated on the way
 // (position = TileDesc.pad[0] + token slot), into the pages and in place in k; only where kv_write_can_rotate.
 hipError_t launch_kv_write(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles,
-                           const void* k, const void* v, hipStream_t stream, void* copy_dst = nullptr,
+                           const void* k, const void* v, const StepMark& mark, hipStream_t stream, void* copy_dst = nullptr,
                            const void* copy_src = nullptr, uint64_t copy_bytes = 0, const double* rope_w = nullptr,
                            int rot = 0, int rot_off = 0, bool interleaved = false);
 bool kv_write_can_rotate(const PoolGeom& g);
 hipError_t launch_kv_gather(const PoolGeom& g, const char* pool_base, const TileDesc* d_tiles, int n_tiles,
-                            void* k_out, void* v_out, hipStream_t stream);
+                            void* k_out, void* v_out, const StepMark& mark, hipStream_t stream);
 // FP8 latent pools (kernels_kv_fp8.hip): quantising page write of dense [rows, 576] bf16 latent rows (with the same
 // optional metadata copy as launch_kv_write), and the gather that hands back the dequantised rows
 hipError_t launch_kv_write_fp8(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* latent,
-                               hipStream_t stream, void* copy_dst = nullptr, const void* copy_src = nullptr,
+                               const StepMark& mark, hipStream_t stream, void* copy_dst = nullptr, const void* copy_src = nullptr,
                                uint64_t copy_bytes = 0);
 hipError_t launch_kv_gather_fp8(const PoolGeom& g, const char* pool_base, const TileDesc* d_tiles, int n_tiles, void* out,
-                                hipStream_t stream);
-hipError_t launch_decode_gqa(const PoolGeom& g, const char* pool_base, const void* q, void* out,
-                             const int32_t* d_ctx_lens, const int32_t* d_block_tables, int bt_stride,
-                             const void* d_items, int n_items, int B, int H, float scale, int chunk_tiles,
-                             int max_chunks, float* ws_o, float* ws_ml, hipStream_t stream);
-hipError_t launch_decode_mla(const PoolGeom& g, const char* pool_base, const void* q, void* out,
-                             const int32_t* d_ctx_lens, const int32_t* d_block_tables, int bt_stride,
-                             const void* d_items, int n_items, int B, int H, float scale, int chunk_steps,
-                             int max_chunks, float* ws_o, float* ws_ml, hipStream_t stream, bool fp8 = false);
+                                const StepMark& mark, hipStream_t stream);
+hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const StepMark& mark, hipStream_t stream);
+hipError_t launch_decode_gqa(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream);
+// the new latent row is in its page already and q is rotated (launch_rope_append / launch_kv_write before it)
+hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream);
 int decode_mla_step_tokens();
 // one workgroup per chain: workgroup b computes the items d_work[d_chain[b]] .. d_work[d_chain[b + 1] - 1]
 hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillWork* d_work,
@@ -218,15 +284,15 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out
 // x [T, K], w_gu [2 I, K] (joint gate/up rows in blocks of 32 + 32), out [T, I], all bf16 in device memory;
 // K a multiple of 32, I a multiple of 128
 hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int cus,
-                              hipStream_t stream);
+                              const StepMark& mark, hipStream_t stream);
 hipError_t launch_ffn_pack(const void* w_gate, const void* w_up, void* w_gu, int K, int I, hipStream_t stream);
 // d_pos, d_w may be device-readable pinned host memory
 hipError_t launch_rope(void* q, int n_q_heads, void* k, int n_kv_heads, int dim, int rot, int off, bool interleaved,
-                       int n_tokens, const int32_t* d_pos, const double* d_w, hipStream_t stream);
+                       int n_tokens, const int32_t* d_pos, const double* d_w, const StepMark& mark, hipStream_t stream);
 // decode step with RoPE: rotated query copy + rotated key (and value) appended to the page, one launch
 hipError_t launch_rope_append(const PoolGeom& g, char* pool_base, const TileDesc* d_descs, const int32_t* d_ctx_lens, int B,
                               const void* q, void* q_out, int Hq, int dq, const void* k_new, const void* v_new, int rot,
-                              int off, bool interleaved, const double* d_w, hipStream_t stream);
+                              int off, bool interleaved, const double* d_w, const StepMark& mark, hipStream_t stream);
 hipError_t launch_probe(int32_t* d_ids, int n_blocks, hipStream_t stream);
 hipError_t launch_copy(void* dst, const void* src, uint64_t bytes, int cus, hipStream_t stream);
 hipError_t launch_read(const void* src, uint64_t bytes, int cus, uint32_t* sink, hipStream_t stream);

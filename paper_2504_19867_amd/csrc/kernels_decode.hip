@@ -18,6 +18,7 @@
 // Long contexts are split into chunks (split-K); partial (max, sum, O) triples go to a
 // workspace and a small second kernel merges them.
 #include "internal.h"
+#include "split_merge.h"
 
 namespace spd {
 
@@ -50,22 +51,49 @@ __device__ inline uint4 load_once(const uint4* p) {
   return uint4{r.x, r.y, r.z, r.w};
 }
 
+// LDS written above by lanes of this wave is read below by other lanes of it (a wave's LDS accesses are served in order)
+__device__ inline void lds_visible_in_wave() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Page ids of the tiles one wave streams, in its lanes: lane 2 i + u holds where tile u of the wave's i-th step lies.
+struct TileWindow { uint32_t lo, hi; };
+
 template <int D>
-__device__ inline void load_step(TileFrag<D>& f, const char* __restrict__ pool, uint64_t page_bytes,
-                                 uint32_t tile_bytes, int tiles_per_page, const int32_t* __restrict__ bt_row,
-                                 uint64_t head_off, int tile, int n_tiles, int lane) {
+__device__ inline void load_step(TileFrag<D>& f, const char* __restrict__ base, const TileWindow& w, int i, int lane) {
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    int t = tile + u;
-    t = t < n_tiles ? t : n_tiles - 1;            // an out-of-range tile re-reads the last one; it is masked later
-    const int page = bt_row[t / tiles_per_page];
-    const char* p = pool + (uint64_t)page * page_bytes + head_off + (uint64_t)(t % tiles_per_page) * tile_bytes;
+    const uint64_t off = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)w.hi, 2 * i + u) << 32) |
+                         (uint32_t)__builtin_amdgcn_readlane((int)w.lo, 2 * i + u);
+    const char* p = base + off;
     const uint4* kp = (const uint4*)p + lane;
     const uint4* vp = (const uint4*)(p + TILE_T * D * 2) + lane;
 #pragma unroll
     for (int s = 0; s < D / 32; ++s) f.k[u][s] = load_once(kp + s * 64);
 #pragma unroll
     for (int s = 0; s < D / 32; ++s) f.v[u][s] = load_once(vp + s * 64);
+  }
+}
+
+// The token that this step appends is on its way to its page while its tile is on its way here: its key and value are
+// put into the operand registers instead (krow, vrow: D entries each in LDS).
+template <int D>
+__device__ inline void patch_tile(TileFrag<D>& f, int u, int slot, const bf16_t* krow, const bf16_t* vrow, int col, int c4) {
+#pragma unroll
+  for (int s = 0; s < D / 32; ++s) {
+    const uint4 kk = *(const uint4*)(krow + 8 * (4 * s + c4));
+    if (col == slot) f.k[u][s] = kk;
+    if (c4 == (slot >> 2)) {
+      // 16 bytes = [(d / 16) % 2][token % 4] for d = 32 s + col and 32 s + 16 + col
+      uint32_t w[4] = {f.v[u][s].x, f.v[u][s].y, f.v[u][s].z, f.v[u][s].w};
+      const int t = slot & 3, sh = 16 * (t & 1);
+      const uint32_t keep = ~(0xffffu << sh);
+      const uint32_t v0 = (uint32_t)vrow[32 * s + col] << sh, v1 = (uint32_t)vrow[32 * s + 16 + col] << sh;
+      if (t < 2) { w[0] = (w[0] & keep) | v0; w[2] = (w[2] & keep) | v1; }
+      else       { w[1] = (w[1] & keep) | v0; w[3] = (w[3] & keep) | v1; }
+      f.v[u][s] = uint4{w[0], w[1], w[2], w[3]};
+    }
   }
 }
 
@@ -136,35 +164,169 @@ __device__ inline void compute_step(const TileFrag<D>& f, const bf16x8 (&qf)[D /
   }
 }
 
+// The attention launch is the whole step: it rotates its query heads (RoPE), rotates the new token's key and puts key
+// and value into their page (the workgroup of the request's last chunk, per KV head), and attends to the context with
+// that token included.  As launches of their own the append and the rotation cost 5.6 us per step, and more than the
+// attention itself in a batch of a few short contexts.
+struct GqaArgs {
+  char* pool;
+  uint64_t page_bytes;
+  uint32_t head_bytes, tile_bytes;
+  int tiles_per_page;
+  const bf16_t *q, *k_new, *v_new;
+  bf16_t* out;
+  const char* items;
+  int item_stride, Hkv, H, G;
+  float c;                      // scale * log2(e)
+  int chunk_tiles, max_chunks;
+  const double* w;
+  int rot, off, interleaved;
+  float *ws_o, *ws_ml;
+  uint32_t* counters;
+  StepMark mark;
+};
+
+__device__ inline float bf_lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
+__device__ inline float bf_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
+
+// The 16-byte piece `own` (entries e0 .. e0 + 7 of a head) rotated; `oth` is the piece with the other halves of its
+// pairs (half layout).  Same arithmetic as the RoPE step.
+__device__ inline uint4 rotate_piece(uint4 own, uint4 oth, int e0, int off, int rot, bool interleaved, const float* cs, const float* sn) {
+  if (e0 < off || e0 >= off + rot) return own;
+  uint32_t ow[4] = {own.x, own.y, own.z, own.w};
+  const uint32_t tw[4] = {oth.x, oth.y, oth.z, oth.w};
+  if (interleaved) {
+    const int p0 = (e0 - off) >> 1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float xa = bf_lo(ow[j]), xb = bf_hi(ow[j]);
+      ow[j] = pack_bf16_rne(xa * cs[p0 + j] - xb * sn[p0 + j], xb * cs[p0 + j] + xa * sn[p0 + j]);
+    }
+  } else {
+    const int half = rot >> 1;
+    const bool first = e0 < off + half;           // this piece holds the a side of its 8 pairs
+    const int p0 = first ? e0 - off : e0 - off - half;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float m0 = bf_lo(ow[j]), m1 = bf_hi(ow[j]), o0 = bf_lo(tw[j]), o1 = bf_hi(tw[j]);
+      const float c0 = cs[p0 + 2 * j], s0 = sn[p0 + 2 * j], c1 = cs[p0 + 2 * j + 1], s1 = sn[p0 + 2 * j + 1];
+      ow[j] = first ? pack_bf16_rne(m0 * c0 - o0 * s0, m1 * c1 - o1 * s1) : pack_bf16_rne(m0 * c0 + o0 * s0, m1 * c1 + o1 * s1);
+    }
+  }
+  return uint4{ow[0], ow[1], ow[2], ow[3]};
+}
+// first entry of the piece that holds the other halves of the pairs of the piece at e0 (e0 itself where there is none)
+__device__ inline int partner_piece(int e0, int off, int rot, bool interleaved) {
+  if (interleaved || e0 < off || e0 >= off + rot) return e0;
+  return e0 < off + (rot >> 1) ? e0 + (rot >> 1) : e0 - (rot >> 1);
+}
+
 // grid (n_items * n_kv_heads), block 256; workgroup i serves KV head i % n_kv_heads of work item
-// i / n_kv_heads = (request, chunk).  Heads vary fastest so that the round-robin placement of
+// i / n_kv_heads.  Heads vary fastest so that the round-robin placement of
 // workgroups on the 8 XCDs gives every XCD the same mix of long and short chunks.
 template <int D>
-__global__ __launch_bounds__(256, 2) void decode_gqa_kernel(
-    const char* __restrict__ pool, uint64_t page_bytes, uint32_t head_bytes, uint32_t tile_bytes, int tiles_per_page,
-    const bf16_t* __restrict__ q, bf16_t* __restrict__ out, const int32_t* __restrict__ ctx_lens,
-    const int32_t* __restrict__ bt, int bt_stride, const int2* __restrict__ items, int Hkv, int H, int G,
-    float c /* scale * log2(e) */, int chunk_tiles, int max_chunks, float* __restrict__ ws_o,
-    float* __restrict__ ws_ml) {
-  const int2 item = items[blockIdx.x / Hkv];
-  const int b = item.x, chunk = item.y, g = blockIdx.x % Hkv;
-  const int n = ctx_lens[b];
-  const int n_tiles = (n + TILE_T - 1) / TILE_T;
-  const int tile0 = chunk * chunk_tiles;
-  if (tile0 >= n_tiles) return;
-  const int tile1 = min(n_tiles, tile0 + chunk_tiles);
-  const int n_steps = (tile1 - tile0 + 1) >> 1;
-  const int n_chunks = (n_tiles + chunk_tiles - 1) / chunk_tiles;
+__global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(a.mark);
+  const int g = blockIdx.x % a.Hkv;
+  const char* rec = a.items + (size_t)(blockIdx.x / a.Hkv) * a.item_stride;
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: page ids become scalar loads
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
   const int col = lane & 15, c4 = lane >> 4;
+  __shared__ __attribute__((aligned(16))) float sm_o[4][16][D + 4];
+  __shared__ float sm_m[4][16], sm_l[4][16];
+  __shared__ int32_t sm_rec[256];
+  __shared__ uint32_t sm_last;
+  // The record (header, page ids) is fetched once per workgroup: it may lie in pinned host memory.
+  const int words = a.item_stride >> 2;
+  if ((int)threadIdx.x < words) sm_rec[threadIdx.x] = ((const int32_t*)rec)[threadIdx.x];
+  const double w_lane = a.rot ? a.w[min(lane, (a.rot >> 1) - 1)] : 0.0;
+  __syncthreads();
+  const int b = __builtin_amdgcn_readfirstlane(sm_rec[0]), chunk = __builtin_amdgcn_readfirstlane(sm_rec[1]);
+  const int n_chunks = __builtin_amdgcn_readfirstlane(sm_rec[2]), n = __builtin_amdgcn_readfirstlane(sm_rec[3]);
+  auto page_id = [&](int i) -> int {               // i-th page of the chunk
+    const int wd = min(i + 4, words - 1);
+    return wd < 256 ? sm_rec[wd] : ((const int32_t*)rec)[wd];
+  };
+  const int n_tiles = (n + TILE_T - 1) / TILE_T;
+  const int tile0 = chunk * a.chunk_tiles;
+  const int tile1 = min(n_tiles, tile0 + a.chunk_tiles);
+  const int n_steps = (tile1 - tile0 + 1) >> 1;
+  const int my_steps = (n_steps - wave + 3) >> 2;                      // this wave's steps: wave, wave + 4, ...
+  const bool interleaved = a.interleaved != 0;
 
+  // Each wave has a piece of LDS of its own, later used for its part of the merge: nothing in it needs a barrier.
+  float* cs = &sm_o[wave][0][0];                   // [D / 2] cosines, sines, then the new token's key and value
+  float* sn = cs + D / 2;
+  bf16_t* krow = (bf16_t*)(sn + D / 2);
+  bf16_t* vrow = krow + D;
+
+  // where tile u of step i (of the 32 the window holds) lies: lane 2 i + u
+  char* pool_g = a.pool + (uint64_t)g * a.head_bytes;
+  const int page0 = tile0 / a.tiles_per_page;
+  auto fill_window = [&](int s0) -> TileWindow {
+    const int t = min(tile0 + 2 * (wave + 4 * (s0 + (lane >> 1))) + (lane & 1), n_tiles - 1);   // out of range: the last tile, masked later
+    const int pg = t / a.tiles_per_page;
+    const uint64_t off = (uint64_t)(uint32_t)page_id(pg - page0) * a.page_bytes + (uint64_t)(t - pg * a.tiles_per_page) * a.tile_bytes;
+    return TileWindow{(uint32_t)off, (uint32_t)(off >> 32)};
+  };
+
+  // ---- the loads that everything waits for first: query pieces, and in one wave the new token's key and value
+  uint4 own[D / 32], oth[D / 32];
+  const bf16_t* qrow = a.q + ((size_t)b * a.H + g * a.G + min(col, a.G - 1)) * D;
+#pragma unroll
+  for (int s = 0; s < D / 32; ++s) {
+    const int e0 = 8 * (4 * s + c4);
+    own[s] = *(const uint4*)(qrow + e0);
+    if (a.rot) oth[s] = *(const uint4*)(qrow + partner_piece(e0, a.off, a.rot, interleaved));
+  }
+  // the new token's tile is the last one of the request: the wave whose step holds it does the append
+  const bool appends = a.k_new != nullptr && tile1 == n_tiles && ((n_steps - 1) & 3) == wave;
+  const int patch = appends ? n_tiles - 1 : -1;
+  constexpr int PCS = D / 8;                       // 16-byte pieces of a head
+  uint4 kv_own = uint4{0, 0, 0, 0}, kv_oth = uint4{0, 0, 0, 0};
+  if (appends) {                                   // lanes 0 .. PCS - 1: pieces of the key, the next PCS: of the value
+    const int pc = lane % PCS, e0 = 8 * pc;
+    const bf16_t* src = (lane / PCS & 1) ? a.v_new : a.k_new;
+    src += ((size_t)b * a.Hkv + g) * D;
+    kv_own = *(const uint4*)(src + e0);
+    if (a.rot && lane < PCS) kv_oth = *(const uint4*)(src + partner_piece(e0, a.off, a.rot, interleaved));
+  }
+
+  TileFrag<D> fa, fb;
+  TileWindow win = TileWindow{0, 0};
+  if (my_steps > 0) {
+    win = fill_window(0);
+    load_step<D>(fa, pool_g, win, 0, lane);
+  }
+  if (a.rot) {
+    if (lane < (a.rot >> 1)) {
+      const double turns = (double)(n - 1) * w_lane * 0.15915494309189535;
+      const float ang = (float)((turns - __builtin_rint(turns)) * 6.283185307179586);
+      sincosf(ang, &sn[lane], &cs[lane]);
+    }
+    lds_visible_in_wave();
+  }
   bf16x8 qf[D / 32];
 #pragma unroll
   for (int s = 0; s < D / 32; ++s) {
-    uint4 raw = uint4{0, 0, 0, 0};
-    if (col < G) raw = *(const uint4*)(q + ((size_t)b * H + g * G + col) * D + 8 * (4 * s + c4));
-    qf[s] = __builtin_bit_cast(bf16x8, raw);
+    uint4 piece = own[s];
+    if (a.rot) piece = rotate_piece(own[s], oth[s], 8 * (4 * s + c4), a.off, a.rot, interleaved, cs, sn);
+    if (col >= a.G) piece = uint4{0, 0, 0, 0};
+    qf[s] = __builtin_bit_cast(bf16x8, piece);
+  }
+  if (appends) {
+    const int pc = lane % PCS, t = (n - 1) % TILE_T;
+    const int pg = (n_tiles - 1) / a.tiles_per_page;
+    char* tile = pool_g + (uint64_t)(uint32_t)page_id(pg - page0) * a.page_bytes + (uint64_t)(n_tiles - 1 - pg * a.tiles_per_page) * a.tile_bytes;
+    if (lane < PCS) {
+      const uint4 piece = a.rot ? rotate_piece(kv_own, kv_oth, 8 * pc, a.off, a.rot, interleaved, cs, sn) : kv_own;
+      *(uint4*)(krow + 8 * pc) = piece;
+      *(uint4*)(tile + ((size_t)(pc * TILE_T + t) << 4)) = piece;
+    } else if (lane < 2 * PCS) {
+      *(uint4*)(vrow + 8 * pc) = kv_own;
+    }
+    lds_visible_in_wave();
+    for (int d = lane; d < D; d += 64) ((bf16_t*)(tile + TILE_T * D * 2))[v_elem_offset(t, d)] = vrow[d];
   }
 
   f32x4 O[D / 16];
@@ -172,77 +334,98 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(
   for (int i = 0; i < D / 16; ++i) O[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
 
-  const int32_t* bt_row = bt + (size_t)b * bt_stride;
-  const uint64_t head_off = (uint64_t)g * head_bytes;
   // Software pipeline over this wave's steps j = wave, wave + 4, ...: the loads of the next step
   // are in flight while the current one is consumed.  The steady-state loop body has no branch,
   // so the compiler can wait for exactly the older buffer (vmcnt = loads of the newer one).
-#define SPD_LOAD(F, J) load_step<D>(F, pool, page_bytes, tile_bytes, tiles_per_page, bt_row, head_off, tile0 + 2 * (J), n_tiles, lane)
-#define SPD_COMP(F, J) compute_step<D>(F, qf, O, m, l, tile0 + 2 * (J), n_tiles, n, c, c4)
-  TileFrag<D> fa, fb;
-  int j = wave;
-  if (j < n_steps) {
-    SPD_LOAD(fa, j);
-    while (j + 8 < n_steps) {
-      SPD_LOAD(fb, j + 4);
-      SPD_COMP(fa, j);
-      SPD_LOAD(fa, j + 8);
-      SPD_COMP(fb, j + 4);
-      j += 8;
+  // Only a request's last step can hold the appended token, so the patch sits behind the steady state.
+#define SPD_TILE(I) (tile0 + 2 * (wave + 4 * (I)))
+#define SPD_LOAD(F, I) load_step<D>(F, pool_g, win, (I) - s0, lane)
+#define SPD_COMP(F, I) compute_step<D>(F, qf, O, m, l, SPD_TILE(I), n_tiles, n, a.c, c4)
+#define SPD_LAST(F, I)                                                                                              \
+  do {                                                                                                              \
+    if (patch >= 0) {                                                                                               \
+      if (min(SPD_TILE(I), n_tiles - 1) == patch) patch_tile<D>(F, 0, (n - 1) % TILE_T, krow, vrow, col, c4);       \
+      if (min(SPD_TILE(I) + 1, n_tiles - 1) == patch) patch_tile<D>(F, 1, (n - 1) % TILE_T, krow, vrow, col, c4);   \
+    }                                                                                                               \
+    SPD_COMP(F, I);                                                                                                 \
+  } while (0)
+  for (int s0 = 0; s0 < my_steps; s0 += 32) {      // 32 steps (of 128 tokens over the four waves) per window
+    const int s1 = min(my_steps, s0 + 32);
+    if (s0) {
+      win = fill_window(s0);
+      SPD_LOAD(fa, s0);
     }
-    if (j + 4 < n_steps) {
-      SPD_LOAD(fb, j + 4);
-      SPD_COMP(fa, j);
-      SPD_COMP(fb, j + 4);
+    int i = s0;
+    while (i + 2 < s1) {
+      SPD_LOAD(fb, i + 1);
+      SPD_COMP(fa, i);
+      SPD_LOAD(fa, i + 2);
+      SPD_COMP(fb, i + 1);
+      i += 2;
+    }
+    if (i + 1 < s1) {
+      SPD_LOAD(fb, i + 1);
+      SPD_COMP(fa, i);
+      SPD_LAST(fb, i + 1);
     } else {
-      SPD_COMP(fa, j);
+      SPD_LAST(fa, i);
     }
   }
+#undef SPD_TILE
 #undef SPD_LOAD
 #undef SPD_COMP
+#undef SPD_LAST
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
 
   // merge the four waves' (m, l, O) through LDS
-  __shared__ float sm_o[4][16][D + 4];
-  __shared__ float sm_m[4][16], sm_l[4][16];
 #pragma unroll
   for (int blk = 0; blk < D / 16; ++blk)
     *(f32x4*)&sm_o[wave][col][16 * blk + 4 * c4] = O[blk];
   if (c4 == 0) { sm_m[wave][col] = m; sm_l[wave][col] = l; }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < G * D; idx += 256) {
-    const int qh = idx / D, d = idx % D;
+  const size_t head0 = (size_t)b * a.H + g * a.G;
+  // two output dims per thread
+  for (int idx = threadIdx.x; idx < a.G * (D / 2); idx += 256) {
+    const int qh = idx / (D / 2), d = 2 * (idx % (D / 2));
     const float m_tot = fmaxf(fmaxf(sm_m[0][qh], sm_m[1][qh]), fmaxf(sm_m[2][qh], sm_m[3][qh]));
-    float l_tot = 0.f, o = 0.f;
+    float l_tot = 0.f, o0 = 0.f, o1 = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float wgt = __builtin_amdgcn_exp2f((sm_m[w][qh] - m_tot) * c);
+      const float wgt = __builtin_amdgcn_exp2f((sm_m[w][qh] - m_tot) * a.c);
       l_tot += sm_l[w][qh] * wgt;
-      o += sm_o[w][qh][d] * wgt;
+      o0 += sm_o[w][qh][d] * wgt;
+      o1 += sm_o[w][qh][d + 1] * wgt;
     }
-    const size_t head = (size_t)b * H + g * G + qh;
+    const size_t head = head0 + qh;
     if (n_chunks == 1) {
-      out[head * D + d] = to_bf16_rne(o / l_tot);
+      *(uint32_t*)(a.out + head * D + d) = pack_bf16_rne(o0 / l_tot, o1 / l_tot);
     } else {
-      const size_t slot = head * max_chunks + chunk;
-      ws_o[slot * D + d] = o;
-      if (d == 0) { ws_ml[slot * 2] = m_tot * c; ws_ml[slot * 2 + 1] = l_tot; }
+      const size_t slot = head * a.max_chunks + chunk;
+      store_partial(a.ws_o + slot * D + d, o0, o1, a.counters != nullptr);
+      if (d == 0) store_partial(a.ws_ml + slot * 2, m_tot * a.c, l_tot, a.counters != nullptr);
     }
+  }
+  if (n_chunks == 1 || a.counters == nullptr) return;
+  // ---- small launches: the workgroup that finds itself to be the last of its (request, KV head) merges the chunks
+  if (!last_of(a.counters + (size_t)b * a.Hkv + g, (uint32_t)n_chunks, &sm_last)) return;
+  for (int idx = threadIdx.x; idx < a.G * (D / 2); idx += 256) {
+    const int qh = idx / (D / 2), d = 2 * (idx % (D / 2));
+    const size_t head = head0 + qh, slot0 = head * a.max_chunks;
+    const f32x2 r = merge_chunks(a.ws_o + slot0 * D + d, D, a.ws_ml + slot0 * 2, n_chunks);
+    *(uint32_t*)(a.out + head * D + d) = pack_bf16_rne(r[0], r[1]);
   }
 }
 
 // grid (ceil(H / (512 / D)), B), block 128: merge the chunks of (request, head) pairs; D / 4 threads per head, four
 // output dims each.
 template <int D>
-__global__ __launch_bounds__(128) void decode_combine_kernel(bf16_t* __restrict__ out, const int32_t* __restrict__ ctx_lens,
-                                                            int H, int chunk_tiles, int max_chunks,
-                                                            const float* __restrict__ ws_o,
+__global__ __launch_bounds__(128) void decode_combine_kernel(bf16_t* __restrict__ out, const int32_t* __restrict__ chunks,
+                                                            int H, int max_chunks, const float* __restrict__ ws_o,
                                                             const float* __restrict__ ws_ml) {
   constexpr int TPH = D / 4;                       // threads per head
   const int h = blockIdx.x * (128 / TPH) + threadIdx.x / TPH, b = blockIdx.y, d = 4 * (threadIdx.x % TPH);
-  const int n_tiles = (ctx_lens[b] + TILE_T - 1) / TILE_T;
-  const int n_chunks = (n_tiles + chunk_tiles - 1) / chunk_tiles;
+  const int n_chunks = chunks[b];
   if (n_chunks <= 1 || h >= H) return;            // one chunk: written directly by the attention kernel
   const size_t slot0 = ((size_t)b * H + h) * max_chunks;
   float m_tot = -INFINITY;
@@ -261,31 +444,28 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(bf16_t* __restrict_
 }
 
 template <int D>
-static hipError_t launch_decode_gqa_t(const PoolGeom& g, const char* pool_base, const void* q, void* out,
-                                      const int32_t* d_ctx_lens, const int32_t* d_bt, int bt_stride,
-                                      const int2* d_items, int n_items, int B, int H, float scale, int chunk_tiles,
-                                      int max_chunks, float* ws_o, float* ws_ml, hipStream_t stream) {
-  const float c = scale * 1.4426950408889634f;
-  hipLaunchKernelGGL(decode_gqa_kernel<D>, dim3((unsigned)n_items * g.Hkv), dim3(256), 0, stream, pool_base,
-                     g.page_bytes, g.head_bytes, g.tile_bytes, g.tiles_per_page, (const bf16_t*)q, (bf16_t*)out, d_ctx_lens,
-                     d_bt, bt_stride, d_items, g.Hkv, H, H / g.Hkv, c, chunk_tiles, max_chunks, ws_o, ws_ml);
+static hipError_t launch_decode_gqa_t(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream) {
+  GqaArgs a;
+  a.pool = pool_base;
+  a.page_bytes = g.page_bytes; a.head_bytes = g.head_bytes; a.tile_bytes = g.tile_bytes; a.tiles_per_page = g.tiles_per_page;
+  a.q = (const bf16_t*)d.q; a.k_new = (const bf16_t*)d.k_new; a.v_new = (const bf16_t*)d.v_new; a.out = (bf16_t*)d.out;
+  a.items = d.items; a.item_stride = d.item_stride;
+  a.Hkv = g.Hkv; a.H = d.H; a.G = d.H / g.Hkv;
+  a.c = d.scale * 1.4426950408889634f;
+  a.chunk_tiles = d.chunk_units; a.max_chunks = d.max_chunks;
+  a.w = d.w; a.rot = d.rot; a.off = d.off; a.interleaved = d.interleaved;
+  a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.counters = d.counters; a.mark = d.mark;
+  hipLaunchKernelGGL(decode_gqa_kernel<D>, dim3((unsigned)d.n_items * g.Hkv), dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || max_chunks <= 1) return e;
-  hipLaunchKernelGGL(decode_combine_kernel<D>, dim3((unsigned)(H + 512 / D - 1) / (512 / D), B), dim3(128), 0, stream, (bf16_t*)out, d_ctx_lens, H, chunk_tiles,
-                     max_chunks, ws_o, ws_ml);
+  if (e != hipSuccess || d.max_chunks <= 1 || d.counters) return e;
+  hipLaunchKernelGGL(decode_combine_kernel<D>, dim3((unsigned)(d.H + 512 / D - 1) / (512 / D), d.B), dim3(128), 0, stream, (bf16_t*)d.out,
+                     d.n_chunks, d.H, d.max_chunks, d.ws_o, d.ws_ml);
   return hipGetLastError();
 }
 
-hipError_t launch_decode_gqa(const PoolGeom& g, const char* pool_base, const void* q, void* out,
-                             const int32_t* d_ctx_lens, const int32_t* d_block_tables, int bt_stride,
-                             const void* d_items, int n_items, int B, int H, float scale, int chunk_tiles,
-                             int max_chunks, float* ws_o, float* ws_ml, hipStream_t stream) {
-  if (g.dk == 128)
-    return launch_decode_gqa_t<128>(g, pool_base, q, out, d_ctx_lens, d_block_tables, bt_stride, (const int2*)d_items,
-                                    n_items, B, H, scale, chunk_tiles, max_chunks, ws_o, ws_ml, stream);
-  if (g.dk == 64)
-    return launch_decode_gqa_t<64>(g, pool_base, q, out, d_ctx_lens, d_block_tables, bt_stride, (const int2*)d_items,
-                                   n_items, B, H, scale, chunk_tiles, max_chunks, ws_o, ws_ml, stream);
+hipError_t launch_decode_gqa(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream) {
+  if (g.dk == 128) return launch_decode_gqa_t<128>(g, pool_base, d, stream);
+  if (g.dk == 64) return launch_decode_gqa_t<64>(g, pool_base, d, stream);
   return hipErrorInvalidValue;
 }
 

@@ -88,23 +88,23 @@ __device__ inline float mla_max_over_rows(float x) {
 template <bool FP8>
 __global__ __launch_bounds__(256, 2) void decode_mla_kernel(
     const char* __restrict__ pool, uint64_t page_bytes, int steps_per_page, const bf16_t* __restrict__ q,
-    bf16_t* __restrict__ out, const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ bt, int bt_stride,
-    const int2* __restrict__ items, int H, float c /* scale * log2(e) */, int chunk_steps, int max_chunks, float* __restrict__ ws_o,
-    float* __restrict__ ws_ml) {
+    bf16_t* __restrict__ out, const char* __restrict__ items, int item_stride, int H, float c /* scale * log2(e) */, int chunk_steps,
+    int max_chunks, float* __restrict__ ws_o, float* __restrict__ ws_ml, StepMark mark) {
   using namespace mla;
   __shared__ __attribute__((aligned(1024))) char smem[NSTAGE * STAGE_BYTES];
-  const int2 item = items[blockIdx.x];
-  const int b = item.x, chunk = item.y;
-  const int n = ctx_lens[b];
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
+  const char* rec = items + (size_t)blockIdx.x * item_stride;
+  const DecodeItem item = *(const DecodeItem*)rec;
+  const int b = item.req, chunk = item.chunk, n = item.n;
   const int n_steps_all = (n + STEP_T - 1) / STEP_T;
   const int step0 = chunk * chunk_steps;
-  if (step0 >= n_steps_all) return;
   const int n_steps = min(n_steps_all - step0, chunk_steps);
-  const int n_chunks = (n_steps_all + chunk_steps - 1) / chunk_steps;
+  const int n_chunks = item.n_chunks;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, c4 = lane >> 4;       // col: head (B operand / accumulator column) or token (A operand row)
-  const int32_t* bt_row = bt + (size_t)b * bt_stride;
+  const int page_first = step0 / steps_per_page;
+  const int32_t* rec_pages = (const int32_t*)(rec + sizeof(DecodeItem));     // the chunk's pages
   const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
 
   // absorbed-query fragments: B operand, column = head, dims 8 (4 s + c4) .. + 7 for k-step s
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256, 2) void decode_mla_kernel(
   // stalls meanwhile: in the loop they are handed out one at a time between MFMAs.
   auto load_src = [&](int st) -> const char* {
     const int gs = step0 + st;
-    const int page = bt_row[gs / steps_per_page];
+    const int page = rec_pages[gs / steps_per_page - page_first];
     return pool + (uint64_t)page * page_bytes + (size_t)(gs % steps_per_page) * STAGE_BYTES;
   };
   auto load_one = [&](const char* src, int st, int j) {
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void decode_mla_kernel(
   };
   auto fp8_src = [&](int st) -> const char* {
     const int gs = step0 + st;
-    const int page = bt_row[gs / steps_per_page];
+    const int page = rec_pages[gs / steps_per_page - page_first];
     return pool + (uint64_t)page * page_bytes + (size_t)(gs % steps_per_page) * FP8_STEP_BYTES;
   };
   // Two register sets that swap roles from step to step: iteration st stores step st + 1 out of one set and loads
@@ -227,9 +227,8 @@ __global__ __launch_bounds__(256, 2) void decode_mla_kernel(
   }
   // The loop itself touches neither the block table in memory nor a division: lane i of `pages` holds the id of
   // the chunk's i-th page, the step to load next is tracked as (page, step inside the page).
-  const int page_first = step0 / steps_per_page;
-  const int n_pages_all = (n_steps_all + steps_per_page - 1) / steps_per_page;
-  const int pages = bt_row[min(page_first + lane, n_pages_all - 1)];   // a chunk spans at most 64 pages (the host sees to it)
+  const int n_pages = (step0 + n_steps - 1) / steps_per_page - page_first + 1;
+  const int pages = rec_pages[min(lane, n_pages - 1)];   // a chunk spans at most 64 pages (the host sees to it)
   int nl_page = (step0 + PD) / steps_per_page - page_first, nl_sub = (step0 + PD) % steps_per_page;
   // Draw the compiler's wait for the query loads (and the page ids) to this point, after the first steps are on
   // their way: left to itself it waits at their first use inside the loop, with a count that knows
@@ -388,14 +387,12 @@ __global__ __launch_bounds__(256, 2) void decode_mla_kernel(
 // grid (H, B), block 128: merge the chunks of one (request, head); four output dims per thread, so that all
 // workgroups of a batch are resident at once and the launch is one round of loads deep.
 __global__ __launch_bounds__(128) void decode_mla_combine_kernel(bf16_t* __restrict__ out,
-                                                                const int32_t* __restrict__ ctx_lens, int H,
-                                                                int chunk_steps, int max_chunks,
+                                                                const int32_t* __restrict__ chunks, int H, int max_chunks,
                                                                 const float* __restrict__ ws_o,
                                                                 const float* __restrict__ ws_ml) {
   static_assert(mla::DV == 4 * 128, "one thread per four output dims");
   const int h = blockIdx.x, b = blockIdx.y, d = 4 * threadIdx.x;
-  const int n_steps = (ctx_lens[b] + mla::STEP_T - 1) / mla::STEP_T;
-  const int n_chunks = (n_steps + chunk_steps - 1) / chunk_steps;
+  const int n_chunks = chunks[b];
   if (n_chunks <= 1) return;
   const size_t slot0 = ((size_t)b * H + h) * max_chunks;
   float m_tot = -INFINITY;
@@ -415,25 +412,21 @@ __global__ __launch_bounds__(128) void decode_mla_combine_kernel(bf16_t* __restr
 
 int decode_mla_step_tokens() { return mla::STEP_T; }
 
-hipError_t launch_decode_mla(const PoolGeom& g, const char* pool_base, const void* q, void* out,
-                             const int32_t* d_ctx_lens, const int32_t* d_block_tables, int bt_stride,
-                             const void* d_items, int n_items, int B, int H, float scale, int chunk_steps,
-                             int max_chunks, float* ws_o, float* ws_ml, hipStream_t stream, bool fp8) {
-  const float c = scale * 1.4426950408889634f;
+hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream) {
+  const float c = d.scale * 1.4426950408889634f;
+  const int spp = g.P / mla::STEP_T;
   // the kernel keeps a chunk's page ids in the 64 lanes of one register
-  if (chunk_steps <= 0 || (chunk_steps + g.P / mla::STEP_T - 1) / (g.P / mla::STEP_T) + 1 > 64) return hipErrorInvalidValue;
-  if (fp8)
-    hipLaunchKernelGGL(decode_mla_kernel<true>, dim3((unsigned)n_items), dim3(256), 0, stream, pool_base, g.page_bytes,
-                       g.P / mla::STEP_T, (const bf16_t*)q, (bf16_t*)out, d_ctx_lens, d_block_tables, bt_stride,
-                       (const int2*)d_items, H, c, chunk_steps, max_chunks, ws_o, ws_ml);
+  if (d.chunk_units <= 0 || (d.chunk_units + spp - 1) / spp + 1 > 64) return hipErrorInvalidValue;
+  if (g.kind == SPD_KV_MLA_LATENT_FP8)
+    hipLaunchKernelGGL(decode_mla_kernel<true>, dim3((unsigned)d.n_items), dim3(256), 0, stream, pool_base, g.page_bytes, spp,
+                       (const bf16_t*)d.q, (bf16_t*)d.out, d.items, d.item_stride, d.H, c, d.chunk_units, d.max_chunks, d.ws_o, d.ws_ml, d.mark);
   else
-    hipLaunchKernelGGL(decode_mla_kernel<false>, dim3((unsigned)n_items), dim3(256), 0, stream, pool_base, g.page_bytes,
-                       g.P / mla::STEP_T, (const bf16_t*)q, (bf16_t*)out, d_ctx_lens, d_block_tables, bt_stride,
-                       (const int2*)d_items, H, c, chunk_steps, max_chunks, ws_o, ws_ml);
+    hipLaunchKernelGGL(decode_mla_kernel<false>, dim3((unsigned)d.n_items), dim3(256), 0, stream, pool_base, g.page_bytes, spp,
+                       (const bf16_t*)d.q, (bf16_t*)d.out, d.items, d.item_stride, d.H, c, d.chunk_units, d.max_chunks, d.ws_o, d.ws_ml, d.mark);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || max_chunks <= 1) return e;
-  hipLaunchKernelGGL(decode_mla_combine_kernel, dim3(H, B), dim3(128), 0, stream, (bf16_t*)out, d_ctx_lens, H,
-                     chunk_steps, max_chunks, ws_o, ws_ml);
+  if (e != hipSuccess || d.max_chunks <= 1) return e;
+  hipLaunchKernelGGL(decode_mla_combine_kernel, dim3(d.H, d.B), dim3(128), 0, stream, (bf16_t*)d.out, d.n_chunks, d.H, d.max_chunks, d.ws_o,
+                     d.ws_ml);
   return hipGetLastError();
 }
 

@@ -60,7 +60,8 @@ __device__ inline void dma16s(const void* sbase, uint32_t voff, uint32_t lds_byt
 template <int MB, int WNW, int NSTAGE>
 __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                                    bf16_t* __restrict__ out, int T, int K, int I, int tiles_m,
-                                                                   int tiles_n, int xcds) {
+                                                                   int tiles_n, int xcds, StepMark mark) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
   constexpr int WAVES = 2 * WNW, BM = 64 * MB, BNP = 64 * WNW, PD = NSTAGE - 1;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BNP * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
   // 1 KiB load instructions per wave per slice.  Where x has fewer pieces than there are waves (a 64-token tile under
@@ -262,18 +263,18 @@ __global__ __launch_bounds__(256) void ffn_pack_kernel(const uint4* __restrict__
 }  // namespace
 
 template <int MB, int WNW, int NSTAGE>
-static hipError_t launch_tiles(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, hipStream_t stream) {
+static hipError_t launch_tiles(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, const StepMark& mark, hipStream_t stream) {
   constexpr int BM = 64 * MB, BNP = 64 * WNW;
   const int tiles_m = (T + BM - 1) / BM, tiles_n = 2 * I / BNP;
   if (tiles_n < xcds) xcds = 1;
   const int per = xcds > 1 ? ((tiles_n + xcds - 1) / xcds) * tiles_m : tiles_m * tiles_n;
   hipLaunchKernelGGL((ffn_gate_up_kernel<MB, WNW, NSTAGE>), dim3((unsigned)(per * xcds)), dim3(128 * WNW), 0, stream, (const bf16_t*)x,
-                     (const bf16_t*)w_gu, (bf16_t*)out, T, K, I, tiles_m, tiles_n, xcds);
+                     (const bf16_t*)w_gu, (bf16_t*)out, T, K, I, tiles_m, tiles_n, xcds, mark);
   return hipGetLastError();
 }
 
 hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int cus,
-                              hipStream_t stream) {
+                              const StepMark& mark, hipStream_t stream) {
   // small batches are bound by reading the weights: the small tile where the large one would leave
   // half of the share's compute units without a workgroup
   const int large_tiles = ((T + 255) / 256) * (2 * I / 256);
@@ -281,11 +282,11 @@ hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T,
     // 64 x 256 tiles (one workgroup per CU, 96 KiB of weights in flight) where they give nearly every compute
     // unit of the share a workgroup; 64 x 128 tiles (two per CU, 80 KiB in flight) otherwise
     const int wide_tiles = 2 * I / 256;
-    if (8 * wide_tiles >= 7 * cus) return launch_tiles<1, 4, 7>(x, w_gu, out, T, K, I, xcds, stream);
-    return launch_tiles<1, 2, 6>(x, w_gu, out, T, K, I, xcds, stream);
+    if (8 * wide_tiles >= 7 * cus) return launch_tiles<1, 4, 7>(x, w_gu, out, T, K, I, xcds, mark, stream);
+    return launch_tiles<1, 2, 6>(x, w_gu, out, T, K, I, xcds, mark, stream);
   }
-  if (T <= 128 || (T <= 256 && 2 * large_tiles <= cus)) return launch_tiles<2, 2, 4>(x, w_gu, out, T, K, I, xcds, stream);
-  return launch_tiles<4, 4, 4>(x, w_gu, out, T, K, I, xcds, stream);
+  if (T <= 128 || (T <= 256 && 2 * large_tiles <= cus)) return launch_tiles<2, 2, 4>(x, w_gu, out, T, K, I, xcds, mark, stream);
+  return launch_tiles<4, 4, 4>(x, w_gu, out, T, K, I, xcds, mark, stream);
 }
 
 hipError_t launch_ffn_pack(const void* w_gate, const void* w_up, void* w_gu, int K, int I, hipStream_t stream) {

@@ -31,7 +31,8 @@ __global__ __launch_bounds__(256) void kv_write_kernel(char* __restrict__ base, 
                                                        const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
                                                        int Hkv, int dk, int dv, int natural, int n_tiles,
                                                        uint4* __restrict__ copy_dst, const uint4* __restrict__ copy_src,
-                                                       uint64_t copy_n16) {
+                                                       uint64_t copy_n16, StepMark mark) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) store_mark(mark);
   if ((int)blockIdx.x >= n_tiles) {
     const uint64_t blk = (uint64_t)(blockIdx.x - n_tiles) * gridDim.y + blockIdx.y;
     const uint64_t stride = (uint64_t)(gridDim.x - n_tiles) * gridDim.y * blockDim.x;
@@ -141,7 +142,8 @@ __global__ __launch_bounds__(256) void kv_write_heads_kernel(char* __restrict__ 
                                                              const TileDesc* __restrict__ descs, const bf16_t* __restrict__ k,
                                                              const bf16_t* __restrict__ v, int Hkv, int dk, int dv, int n_tiles,
                                                              uint4* __restrict__ copy_dst, const uint4* __restrict__ copy_src,
-                                                             uint64_t copy_n16, RopeFuse rp) {
+                                                             uint64_t copy_n16, RopeFuse rp, StepMark mark) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) store_mark(mark);
   if ((int)blockIdx.x >= n_tiles) {
     const uint64_t blk = (uint64_t)(blockIdx.x - n_tiles) * gridDim.y + blockIdx.y;
     const uint64_t stride = (uint64_t)(gridDim.x - n_tiles) * gridDim.y * blockDim.x;
@@ -266,7 +268,8 @@ __global__ __launch_bounds__(256) void kv_gather_kernel(const char* __restrict__
                                                         uint32_t head_bytes, uint32_t tile_bytes,
                                                         uint32_t tile_k_bytes, const TileDesc* __restrict__ descs,
                                                         bf16_t* __restrict__ k_out, bf16_t* __restrict__ v_out,
-                                                        int Hkv, int dk, int dv, int natural) {
+                                                        int Hkv, int dk, int dv, int natural, StepMark mark) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) store_mark(mark);
   const TileDesc d = descs[blockIdx.x];
   const int g = blockIdx.y;
   const char* tile = base + (uint64_t)d.page * page_bytes + (uint64_t)g * head_bytes + (uint64_t)d.sub * tile_bytes;
@@ -481,12 +484,25 @@ hipError_t launch_copy(void* dst, const void* src, uint64_t bytes, int cus, hipS
   return hipGetLastError();
 }
 
+// The metadata of a step, out of pinned host memory to its device twin.
+__global__ __launch_bounds__(256) void meta_copy_kernel(uint4* __restrict__ dst, const uint4* __restrict__ src, uint32_t n16, StepMark mark) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
+  const uint32_t stride = gridDim.x * blockDim.x;
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += stride) dst[i] = src[i];
+}
+
+hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const StepMark& mark, hipStream_t stream) {
+  const uint32_t n16 = (uint32_t)((bytes + 15) / 16);
+  hipLaunchKernelGGL(meta_copy_kernel, dim3(std::min<uint32_t>(64, (n16 + 255) / 256)), dim3(256), 0, stream, (uint4*)dst, (const uint4*)src, n16, mark);
+  return hipGetLastError();
+}
+
 bool kv_write_can_rotate(const PoolGeom& g) {
   return g.kind == SPD_KV_GQA && g.dk <= 128 && g.dv <= 128 && g.Hkv >= 2;
 }
 
 hipError_t launch_kv_write(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k,
-                           const void* v, hipStream_t stream, void* copy_dst, const void* copy_src, uint64_t copy_bytes,
+                           const void* v, const StepMark& mark, hipStream_t stream, void* copy_dst, const void* copy_src, uint64_t copy_bytes,
                            const double* rope_w, int rot, int rot_off, bool interleaved) {
   const uint64_t n16 = copy_dst ? (copy_bytes + 15) / 16 : 0;
   const int copy_cols = n16 ? (int)std::min<uint64_t>(16, (n16 + 256ull * g.Hkv - 1) / (256ull * g.Hkv)) : 0;
@@ -500,26 +516,26 @@ hipError_t launch_kv_write(const PoolGeom& g, char* pool_base, const TileDesc* d
     if (rope_w)
       hipLaunchKernelGGL((kv_write_heads_kernel<HG, true>), dim3(n_tiles + cols, groups), dim3(256), 0, stream, pool_base,
                          g.page_bytes, g.head_bytes, g.tile_bytes, g.tile_k_bytes, d_tiles, (const bf16_t*)k, (const bf16_t*)v,
-                         g.Hkv, g.dk, g.dv, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, rp);
+                         g.Hkv, g.dk, g.dv, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, rp, mark);
     else
       hipLaunchKernelGGL((kv_write_heads_kernel<HG, false>), dim3(n_tiles + cols, groups), dim3(256), 0, stream, pool_base,
                          g.page_bytes, g.head_bytes, g.tile_bytes, g.tile_k_bytes, d_tiles, (const bf16_t*)k, (const bf16_t*)v,
-                         g.Hkv, g.dk, g.dv, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, rp);
+                         g.Hkv, g.dk, g.dv, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, rp, mark);
     return hipGetLastError();
   }
   if (rope_w) return hipErrorInvalidValue;          // callers ask kv_write_can_rotate first
   hipLaunchKernelGGL(kv_write_kernel, dim3(n_tiles + copy_cols, g.Hkv), dim3(256), 0, stream, pool_base, g.page_bytes,
                      g.head_bytes, g.tile_bytes, g.tile_k_bytes, d_tiles, (const bf16_t*)k, (const bf16_t*)v, g.Hkv, g.dk,
-                     g.dv, g.kind == SPD_KV_MLA_LATENT ? 1 : 0, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16);
+                     g.dv, g.kind == SPD_KV_MLA_LATENT ? 1 : 0, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, mark);
   return hipGetLastError();
 }
 
 hipError_t launch_kv_gather(const PoolGeom& g, const char* pool_base, const TileDesc* d_tiles, int n_tiles, void* k_out,
-                            void* v_out, hipStream_t stream) {
+                            void* v_out, const StepMark& mark, hipStream_t stream) {
   if (n_tiles <= 0) return hipSuccess;
   hipLaunchKernelGGL(kv_gather_kernel, dim3(n_tiles, g.Hkv), dim3(256), 0, stream, pool_base, g.page_bytes,
                      g.head_bytes, g.tile_bytes, g.tile_k_bytes, d_tiles, (bf16_t*)k_out, (bf16_t*)v_out, g.Hkv, g.dk,
-                     g.dv, g.kind == SPD_KV_MLA_LATENT ? 1 : 0);
+                     g.dv, g.kind == SPD_KV_MLA_LATENT ? 1 : 0, mark);
   return hipGetLastError();
 }
 

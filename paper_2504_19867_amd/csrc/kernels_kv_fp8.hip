@@ -37,7 +37,8 @@ __global__ __launch_bounds__(256) void kv_write_latent_fp8_kernel(char* __restri
                                                                   uint32_t tile_bytes, const TileDesc* __restrict__ descs,
                                                                   const bf16_t* __restrict__ latent, int n_tiles,
                                                                   uint4* __restrict__ copy_dst, const uint4* __restrict__ copy_src,
-                                                                  uint64_t copy_n16) {
+                                                                  uint64_t copy_n16, StepMark mark) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
   if ((int)blockIdx.x >= n_tiles) {
     const uint64_t blk = blockIdx.x - n_tiles;
     const uint64_t stride = (uint64_t)(gridDim.x - n_tiles) * blockDim.x;
@@ -80,7 +81,8 @@ __global__ __launch_bounds__(256) void kv_write_latent_fp8_kernel(char* __restri
 // grid (n_tiles), block 256.  out: dense [rows, 576] bf16 = decode(code) * scale rounded to bf16, rope as stored.
 __global__ __launch_bounds__(256) void kv_gather_latent_fp8_kernel(const char* __restrict__ base, uint64_t page_bytes,
                                                                    uint32_t tile_bytes, const TileDesc* __restrict__ descs,
-                                                                   bf16_t* __restrict__ out) {
+                                                                   bf16_t* __restrict__ out, StepMark mark) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
   const TileDesc d = descs[blockIdx.x];
   const int t = threadIdx.x >> 4, l = threadIdx.x & 15;
   if (t < d.t_begin || t >= d.t_end) return;
@@ -105,20 +107,20 @@ __global__ __launch_bounds__(256) void kv_gather_latent_fp8_kernel(const char* _
 }
 
 hipError_t launch_kv_write_fp8(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* latent,
-                               hipStream_t stream, void* copy_dst, const void* copy_src, uint64_t copy_bytes) {
+                               const StepMark& mark, hipStream_t stream, void* copy_dst, const void* copy_src, uint64_t copy_bytes) {
   const uint64_t n16 = copy_dst ? (copy_bytes + 15) / 16 : 0;
   const int copy_cols = n16 ? (int)std::min<uint64_t>(16, (n16 + 255) / 256) : 0;
   if (n_tiles <= 0 && copy_cols == 0) return hipSuccess;
   hipLaunchKernelGGL(kv_write_latent_fp8_kernel, dim3(n_tiles + copy_cols), dim3(256), 0, stream, pool_base, g.page_bytes,
-                     g.tile_bytes, d_tiles, (const bf16_t*)latent, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16);
+                     g.tile_bytes, d_tiles, (const bf16_t*)latent, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, mark);
   return hipGetLastError();
 }
 
 hipError_t launch_kv_gather_fp8(const PoolGeom& g, const char* pool_base, const TileDesc* d_tiles, int n_tiles, void* out,
-                                hipStream_t stream) {
+                                const StepMark& mark, hipStream_t stream) {
   if (n_tiles <= 0) return hipSuccess;
   hipLaunchKernelGGL(kv_gather_latent_fp8_kernel, dim3(n_tiles), dim3(256), 0, stream, pool_base, g.page_bytes, g.tile_bytes,
-                     d_tiles, (bf16_t*)out);
+                     d_tiles, (bf16_t*)out, mark);
   return hipGetLastError();
 }
 

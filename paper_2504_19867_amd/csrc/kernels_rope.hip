@@ -35,10 +35,12 @@ struct RopeArgs {
   int chunks[2];          // head chunks of q, of k
   const int32_t* pos;     // [n_tokens]
   const double* w;        // [rot / 2]
+  StepMark mark;
 };
 
 template <bool INTERLEAVED>
 __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(a.mark);
   const long long tid = (long long)blockIdx.x * 256 + threadIdx.x;
   const int per_token = (a.chunks[0] + a.chunks[1]) * a.groups;
   const long long t = tid / per_token;
@@ -90,8 +92,9 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
 }
 
 hipError_t launch_rope(void* q, int n_q_heads, void* k, int n_kv_heads, int dim, int rot, int off, bool interleaved,
-                       int n_tokens, const int32_t* d_pos, const double* d_w, hipStream_t stream) {
+                       int n_tokens, const int32_t* d_pos, const double* d_w, const StepMark& mark, hipStream_t stream) {
   RopeArgs a;
+  a.mark = mark;
   a.x[0] = (unsigned short*)q;
   a.x[1] = (unsigned short*)k;
   a.heads[0] = n_q_heads;
@@ -139,6 +142,7 @@ struct RopeAppendArgs {
   uint64_t page_bytes;
   uint32_t head_bytes, tile_bytes, tile_k_bytes;
   int natural;
+  StepMark mark;
 };
 
 // the 8 entries starting at entry e0 of a head vector `row`, rotated
@@ -172,6 +176,7 @@ __device__ inline uint4 rope_piece(const unsigned short* row, int e0, int off, i
 }
 
 __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(a.mark);
   __shared__ float cs[128], sn[128];              // rotary_dim <= 256
   const int r = blockIdx.x;
   const int npairs = a.rot >> 1;
@@ -211,9 +216,10 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a) {
 
 hipError_t launch_rope_append(const PoolGeom& g, char* pool_base, const TileDesc* d_descs, const int32_t* d_ctx_lens, int B,
                               const void* q, void* q_out, int Hq, int dq, const void* k_new, const void* v_new, int rot,
-                              int off, bool interleaved, const double* d_w, hipStream_t stream) {
+                              int off, bool interleaved, const double* d_w, const StepMark& mark, hipStream_t stream) {
   if (B <= 0) return hipSuccess;
   RopeAppendArgs a;
+  a.mark = mark;
   a.q = (const unsigned short*)q; a.q_out = (unsigned short*)q_out;
   a.k = (const unsigned short*)k_new; a.v = (const unsigned short*)v_new;
   a.Hq = Hq; a.Hkv = g.Hkv; a.dq = dq; a.dk = g.dk; a.dv = g.dv;

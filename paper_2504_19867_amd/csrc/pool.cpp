@@ -82,15 +82,17 @@ int64_t blocks_missing_locked(spd_pool* pool, uint64_t req, int64_t n_tokens) {
 }
 
 // Caller holds pool->mu and has checked that enough blocks are free.
-uint64_t reserve_locked(spd_pool* pool, uint64_t req, int64_t n_tokens) {
-  int64_t need = blocks_missing_locked(pool, req, n_tokens);
-  std::vector<int32_t>& t = pool->tables[req];
-  for (int64_t i = 0; i < need; ++i) {
+uint64_t reserve_entry_locked(spd_pool* pool, spd_req_table& t, int64_t n_tokens) {
+  const int64_t want = (n_tokens + pool->desc.page_tokens - 1) / pool->desc.page_tokens;
+  while ((int64_t)t.size() < want) {
     t.push_back(pool->free_stack.back());
     pool->free_stack.pop_back();
+    ++pool->used;
   }
-  pool->used += need;
   return ++pool->op_seq;
+}
+uint64_t reserve_locked(spd_pool* pool, uint64_t req, int64_t n_tokens) {
+  return reserve_entry_locked(pool, pool->tables[req], n_tokens);
 }
 }  // namespace spd
 

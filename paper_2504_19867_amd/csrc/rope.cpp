@@ -41,6 +41,23 @@ void rope_frequencies(const spd_rope_config* c, double* out) {
     out[i] = w;
   }
 }
+
+// `host` (device address `host_dev`): room for the table in the step's staging slot.  `mark` goes with the copy where
+// there is one, and is cleared then.
+int rope_table(spd_ctx* ctx, int phase, const spd_rope_config* c, char* host, const char* host_dev, hipStream_t stream, StepMark* mark,
+               const double** out) {
+  spd_phase_state& s = ctx->phase[phase];
+  *out = s.rope_dev;
+  static_assert(sizeof(spd_rope_config) == 4 * sizeof(double) + 4 * sizeof(int32_t), "compared byte by byte");
+  if (s.rope_valid && std::memcmp(&s.rope_key, c, sizeof *c) == 0) return SPD_OK;
+  s.rope_valid = false;
+  rope_frequencies(c, (double*)host);
+  SPD_HIP(launch_meta_copy(s.rope_dev, host_dev, sizeof(double) * (size_t)(c->rotary_dim / 2), *mark, stream));
+  mark->flag = nullptr;
+  s.rope_key = *c;
+  s.rope_valid = true;
+  return SPD_OK;
+}
 }  // namespace spd
 
 extern "C" int spd_rope_inv_freq(const spd_rope_config* cfg, double* out, int32_t cap) {
@@ -77,17 +94,14 @@ extern "C" int spd_rope_qk(spd_ctx* ctx, int phase, const spd_rope_config* cfg, 
   if (st_rc != SPD_OK) return st_rc;
   rope_frequencies(cfg, (double*)st->host);
   std::memcpy(st->host + w_bytes, positions, p_bytes);
-  void* host_dev = nullptr;
-  st_rc = stage_host_as_device(st, &host_dev);
-  if (st_rc != SPD_OK) return st_rc;
   // the kernel reads the table and the positions straight out of the pinned buffer
   const void* qq = q ? q : k;
   const int hq = q ? n_q_heads : n_kv_heads;
   st_rc = kernel_timing_mark(ctx, phase, 0, stream);
   if (st_rc != SPD_OK) return st_rc;
   SPD_HIP(launch_rope((void*)qq, hq, q ? k : nullptr, n_kv_heads, dim, cfg->rotary_dim, cfg->rotary_offset, cfg->interleaved != 0,
-                      n_tokens, (const int32_t*)((const char*)host_dev + w_bytes), (const double*)host_dev, stream));
+                      n_tokens, (const int32_t*)(st->dev + w_bytes), (const double*)st->dev, step_mark(ctx, phase), stream));
   st_rc = kernel_timing_mark(ctx, phase, 1, stream);
   if (st_rc != SPD_OK) return st_rc;
-  return stage_commit(ctx, phase, st, w_bytes + p_bytes, stream, false);
+  return stage_commit(ctx, phase, st, stream);
 }

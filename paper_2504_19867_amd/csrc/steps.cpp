@@ -19,28 +19,50 @@ using namespace spd;
 namespace spd {
 int64_t blocks_missing_locked(spd_pool* pool, uint64_t req, int64_t n_tokens);
 uint64_t reserve_locked(spd_pool* pool, uint64_t req, int64_t n_tokens);
+uint64_t reserve_entry_locked(spd_pool* pool, spd_req_table& table, int64_t n_tokens);
 }  // namespace spd
 
 static inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
+static inline size_t align64(size_t x) { return (x + 63) & ~(size_t)63; }
+static inline size_t align4k(size_t x) { return (x + 4095) & ~(size_t)4095; }
 
 // Tile descriptors covering logical positions [start, start + n) of a request whose block
-// table is `bt`; dense row src_row0 maps to position `start`.
-static void build_tile_descs(const PoolGeom& g, const int32_t* bt, int32_t start, int32_t n, int32_t src_row0,
-                             std::vector<TileDesc>& out) {
-  int32_t pos = start, end = start + n;
-  while (pos < end) {
-    int32_t tile = pos / TILE_T, t_begin = pos % TILE_T;
-    int32_t t_end = std::min<int32_t>(TILE_T, t_begin + (end - pos));
-    TileDesc d{};
-    d.src_row = src_row0 + (pos - start);
-    d.page = bt[tile / g.tiles_per_page];
-    d.sub = tile % g.tiles_per_page;
-    d.t_begin = t_begin;
-    d.t_end = t_end;
-    d.pad[0] = tile * TILE_T;
-    out.push_back(d);
-    pos += t_end - t_begin;
+// table is `bt`, written at `out`; dense row src_row0 maps to position `start`.  Returns how many.
+static int build_tile_descs(const PoolGeom& g, const int32_t* bt, int32_t start, int32_t n, int32_t src_row0, TileDesc* out) {
+  int32_t tile = start / TILE_T, t_begin = start % TILE_T, row = src_row0, left = n;
+  int32_t page = tile / g.tiles_per_page, sub = tile % g.tiles_per_page;
+  int count = 0;
+  for (; left > 0; ++count) {
+    const int32_t t_end = std::min<int32_t>(TILE_T, t_begin + left);
+    out[count] = TileDesc{row, bt[page], sub, t_begin, t_end, {tile * TILE_T, 0, 0}};
+    row += t_end - t_begin;
+    left -= t_end - t_begin;
+    t_begin = 0;
+    ++tile;
+    if (++sub == g.tiles_per_page) { sub = 0; ++page; }
   }
+  return count;
+}
+static size_t tile_desc_count(int32_t start, int32_t n) { return (size_t)((start % TILE_T) + n + TILE_T - 1) / TILE_T; }
+
+// Does a request id occur twice?  Small batches pair by pair, larger ones through an open-addressing table.
+static bool has_duplicates(const uint64_t* ids, int n, std::vector<uint64_t>& set) {
+  if (n <= 24) {
+    for (int i = 1; i < n; ++i)
+      for (int j = 0; j < i; ++j)
+        if (ids[i] == ids[j]) return true;
+    return false;
+  }
+  size_t cap = 64;
+  while (cap < (size_t)n * 2) cap *= 2;
+  set.assign(cap, 0);                       // holds index + 1
+  for (int i = 0; i < n; ++i) {
+    size_t h = (size_t)((ids[i] * 0x9e3779b97f4a7c15ull) >> 20) & (cap - 1);
+    for (; set[h]; h = (h + 1) & (cap - 1))
+      if (ids[set[h] - 1] == ids[i]) return true;
+    set[h] = (uint64_t)i + 1;
+  }
+  return false;
 }
 
 // The kernels move 16 bytes per lane: every tensor a step is given must start on a 16-byte boundary.
@@ -62,34 +84,28 @@ static int kv_copy(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t req_id, int
   if ((g.kind == SPD_KV_GQA) != (v != nullptr)) return SPD_EINVAL;
   if (misaligned16(k, v)) return SPD_EINVAL;
   if (ctx->device < 0) return SPD_ESTATE;
-  std::vector<TileDesc> descs;
+  spd_stage* st;
+  int rc, n_descs;
+  if ((rc = stage_acquire(ctx, phase, tile_desc_count(start_pos, n_tokens) * sizeof(TileDesc), &st)) != SPD_OK) return rc;
   {
     std::lock_guard<std::mutex> lk(pool->mu);
     auto it = pool->tables.find(req_id);
     if (it == pool->tables.end()) return SPD_ENOENT;
-    int64_t need = ((int64_t)start_pos + n_tokens + g.P - 1) / g.P;
+    const int64_t need = ((int64_t)start_pos + n_tokens + g.P - 1) / g.P;
     if ((int64_t)it->second.size() < need) return SPD_EINVAL;
-    build_tile_descs(g, it->second.data(), start_pos, n_tokens, 0, descs);
+    n_descs = build_tile_descs(g, it->second.data(), start_pos, n_tokens, 0, (TileDesc*)st->host);
     it->second.last_use[phase] = next_step_number(ctx, phase);
   }
   hipStream_t stream;
-  int rc = phase_enter(ctx, phase, &stream);
-  if (rc != SPD_OK) return rc;
-  size_t bytes = descs.size() * sizeof(TileDesc);
-  spd_stage* st;
-  if ((rc = stage_acquire(ctx, phase, bytes, &st)) != SPD_OK) return rc;
-  memcpy(st->host, descs.data(), bytes);
-  if ((rc = stage_copy(st, bytes, stream)) != SPD_OK) return rc;
+  if ((rc = phase_enter(ctx, phase, &stream)) != SPD_OK) return rc;
+  const TileDesc* descs = (const TileDesc*)st->dev;              // read over PCIe, once per workgroup
+  const StepMark mark = step_mark(ctx, phase);
   const bool fp8 = g.kind == SPD_KV_MLA_LATENT_FP8;
-  if (write && fp8)
-    SPD_HIP(launch_kv_write_fp8(g, pool->base, (const TileDesc*)st->dev, (int)descs.size(), k, stream));
-  else if (write)
-    SPD_HIP(launch_kv_write(g, pool->base, (const TileDesc*)st->dev, (int)descs.size(), k, v, stream));
-  else if (fp8)
-    SPD_HIP(launch_kv_gather_fp8(g, pool->base, (const TileDesc*)st->dev, (int)descs.size(), (void*)k, stream));
-  else
-    SPD_HIP(launch_kv_gather(g, pool->base, (const TileDesc*)st->dev, (int)descs.size(), (void*)k, (void*)v, stream));
-  return stage_commit(ctx, phase, st, bytes, stream, false);
+  if (write && fp8) SPD_HIP(launch_kv_write_fp8(g, pool->base, descs, n_descs, k, mark, stream));
+  else if (write) SPD_HIP(launch_kv_write(g, pool->base, descs, n_descs, k, v, mark, stream));
+  else if (fp8) SPD_HIP(launch_kv_gather_fp8(g, pool->base, descs, n_descs, (void*)k, mark, stream));
+  else SPD_HIP(launch_kv_gather(g, pool->base, descs, n_descs, (void*)k, (void*)v, mark, stream));
+  return stage_commit(ctx, phase, st, stream);
 }
 
 extern "C" int spd_kv_write(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t req_id, int32_t start_pos,
@@ -123,11 +139,10 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
     if (b->rope->rotary_dim % 16 || b->rope->rotary_offset % 8 || b->rope->rotary_offset + b->rope->rotary_dim > b->dim_qk)
       return SPD_EINVAL;
   }
-  for (int r = 0; r < b->n_req; ++r) {
+  spd_phase_state& ps = ctx->phase[SPD_PHASE_PREFILL];
+  for (int r = 0; r < b->n_req; ++r)
     if (b->cu_seqlens[r + 1] <= b->cu_seqlens[r]) return SPD_EINVAL;     // zero-length prompt
-    for (int r2 = 0; r2 < r; ++r2)
-      if (b->req_ids[r2] == b->req_ids[r]) return SPD_EINVAL;
-  }
+  if (has_duplicates(b->req_ids, b->n_req, ps.tmp_set)) return SPD_EINVAL;
   if (ctx->device < 0) return SPD_ESTATE;
 
   // chunked prefill: some request continues a prompt whose first prefix_lens[r] tokens are cached
@@ -187,29 +202,26 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   size_t n_descs = 0, n_gather = 0;
   for (int r = 0; r < b->n_req; ++r) {
     const int32_t len = b->cu_seqlens[r + 1] - b->cu_seqlens[r], pre = chunked ? b->prefix_lens[r] : 0;
-    n_descs += (size_t)((pre % TILE_T) + len + TILE_T - 1) / TILE_T;
-    if (chunked) n_gather += (size_t)(pre + len + TILE_T - 1) / TILE_T;
+    n_descs += tile_desc_count(pre, len);
+    if (chunked) n_gather += tile_desc_count(0, pre + len);
   }
   size_t off_chain = align16(work.size() * sizeof(PrefillWork));
   size_t off_desc = align16(off_chain + chain.size() * sizeof(int32_t));
   size_t off_gather = align16(off_desc + n_descs * sizeof(TileDesc));
-  // RoPE inside the step: the frequency table, and every row's position for the rotation of q
+  // RoPE inside the step: every row's position for the rotation of q, and room for the frequency table
   const int32_t n_rows = b->cu_seqlens[b->n_req];
-  size_t off_w = align16(off_gather + n_gather * sizeof(TileDesc));
-  size_t off_pos = align16(off_w + (b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0));
-  size_t bytes = off_pos + (b->rope ? sizeof(int32_t) * (size_t)n_rows : 0);
+  size_t off_pos = align16(off_gather + n_gather * sizeof(TileDesc));
+  size_t bytes = align16(off_pos + (b->rope ? sizeof(int32_t) * (size_t)n_rows : 0));
+  const size_t off_w = bytes, w_bytes = b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0;
   spd_stage* st;
-  if ((rc = stage_acquire(ctx, SPD_PHASE_PREFILL, bytes, &st)) != SPD_OK) return rc;
+  if ((rc = stage_acquire(ctx, SPD_PHASE_PREFILL, bytes + w_bytes, &st)) != SPD_OK) return rc;
+  // workspace: the metadata's device twin, then the gathered K and V of a chunked step
   char* ws = nullptr;
-  size_t ws_k_bytes = 0;
-  if (chunked) {
-    ws_k_bytes = align16((size_t)kv_cu.back() * g.Hkv * g.dk * 2);
-    const size_t ws_v_bytes = (size_t)kv_cu.back() * g.Hkv * g.dv * 2;
-    if ((rc = workspace_reserve(ctx, SPD_PHASE_PREFILL, ws_k_bytes + ws_v_bytes, &ws)) != SPD_OK) return rc;
-  }
-  std::vector<TileDesc> descs, gdescs;
-  descs.reserve(n_descs);
-  gdescs.reserve(n_gather);
+  // (whole pages of 4 KiB: the attention kernel loads rows in 1 KiB pieces, which should not straddle cache lines)
+  const size_t ws_k = align4k(bytes), ws_v = ws_k + (chunked ? align4k((size_t)kv_cu.back() * g.Hkv * g.dk * 2) : 0);
+  const size_t ws_bytes = ws_v + (chunked ? (size_t)kv_cu.back() * g.Hkv * g.dv * 2 : 0);
+  if ((rc = workspace_reserve(ctx, SPD_PHASE_PREFILL, ws_bytes, &ws)) != SPD_OK) return rc;
+  TileDesc *h_desc = (TileDesc*)(st->host + off_desc), *h_gather = (TileDesc*)(st->host + off_gather);
   {
     std::lock_guard<std::mutex> lk(pool->mu);                       // atomic: query, get, update
     int64_t need = 0;
@@ -228,66 +240,58 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
       reserve_locked(pool, b->req_ids[r], pre + len);
       spd_req_table& entry = pool->tables[b->req_ids[r]];
       entry.last_use[SPD_PHASE_PREFILL] = next_step_number(ctx, SPD_PHASE_PREFILL);
-      const int32_t* table = entry.data();
-      build_tile_descs(g, table, pre, len, row0, descs);
-      if (chunked) build_tile_descs(g, table, 0, pre + len, kv_cu[(size_t)r], gdescs);
+      h_desc += build_tile_descs(g, entry.data(), pre, len, row0, h_desc);
+      if (chunked) h_gather += build_tile_descs(g, entry.data(), 0, pre + len, kv_cu[(size_t)r], h_gather);
     }
   }
   hipStream_t stream;
   if ((rc = phase_enter(ctx, SPD_PHASE_PREFILL, &stream)) != SPD_OK) return rc;
   memcpy(st->host, work.data(), work.size() * sizeof(PrefillWork));
   memcpy(st->host + off_chain, chain.data(), chain.size() * sizeof(int32_t));
-  memcpy(st->host + off_desc, descs.data(), descs.size() * sizeof(TileDesc));
-  if (chunked) memcpy(st->host + off_gather, gdescs.data(), gdescs.size() * sizeof(TileDesc));
+  StepMark mark = step_mark(ctx, SPD_PHASE_PREFILL);
+  const double* rope_w = nullptr;
+  if (ctx->kernel_timing) SPD_HIP(hipEventRecord(ps.ev_start, stream));
   if (b->rope) {
-    rope_frequencies(b->rope, (double*)(st->host + off_w));
     int32_t* pos = (int32_t*)(st->host + off_pos);
     for (int r = 0; r < b->n_req; ++r)
       for (int32_t i = b->cu_seqlens[r]; i < b->cu_seqlens[r + 1]; ++i)
         pos[i] = (chunked ? b->prefix_lens[r] : 0) + (i - b->cu_seqlens[r]);
+    if ((rc = rope_table(ctx, SPD_PHASE_PREFILL, b->rope, st->host + off_w, st->dev + off_w, stream, &mark, &rope_w)) != SPD_OK) return rc;
   }
-  spd_phase_state& ps = ctx->phase[SPD_PHASE_PREFILL];
-  if (ctx->kernel_timing) SPD_HIP(hipEventRecord(ps.ev_start, stream));
   const void* page_src_k = g.kind == SPD_KV_GQA ? b->k : b->latent;
   const void* page_src_v = g.kind == SPD_KV_GQA ? b->v : nullptr;
   // one launch: the page write reads its descriptors straight out of the pinned staging buffer,
   // and extra workgroups of the same kernel copy the whole staging buffer to its device twin,
   // where the attention kernel (and the gather of a chunked step) find their lists
-  void* host_dev = nullptr;
-  if ((rc = stage_host_as_device(st, &host_dev)) != SPD_OK) return rc;
   const spd_rope_config* rc_ = b->rope;
   const bool fused = rc_ && kv_write_can_rotate(g);
-  if (rc_ && !fused)        // no fused form for this pool shape: q and k in one pass of their own, before the page write
+  if (rc_ && !fused) {      // no fused form for this pool shape: q and k in one pass of their own, before the page write
     SPD_HIP(launch_rope((void*)b->q, b->n_q_heads, (void*)b->k, b->n_kv_heads, b->dim_qk, rc_->rotary_dim, rc_->rotary_offset,
-                        rc_->interleaved != 0, n_rows, (const int32_t*)((const char*)host_dev + off_pos),
-                        (const double*)((const char*)host_dev + off_w), stream));
+                        rc_->interleaved != 0, n_rows, (const int32_t*)(st->dev + off_pos), rope_w, mark, stream));
+    mark.flag = nullptr;
+  }
+  const TileDesc* d_desc = (const TileDesc*)(st->dev + off_desc);
   if (g.kind == SPD_KV_MLA_LATENT_FP8)
-    SPD_HIP(launch_kv_write_fp8(g, pool->base, (const TileDesc*)((const char*)host_dev + off_desc), (int)descs.size(), page_src_k,
-                                stream, st->dev, host_dev, bytes));
+    SPD_HIP(launch_kv_write_fp8(g, pool->base, d_desc, (int)n_descs, page_src_k, mark, stream, ws, st->dev, bytes));
   else
-    SPD_HIP(launch_kv_write(g, pool->base, (const TileDesc*)((const char*)host_dev + off_desc), (int)descs.size(), page_src_k,
-                            page_src_v, stream, st->dev, host_dev, bytes,
-                            fused ? (const double*)((const char*)host_dev + off_w) : nullptr, fused ? rc_->rotary_dim : 0,
-                            fused ? rc_->rotary_offset : 0, fused && rc_->interleaved != 0));
+    SPD_HIP(launch_kv_write(g, pool->base, d_desc, (int)n_descs, page_src_k, page_src_v, mark, stream, ws, st->dev, bytes,
+                            fused ? rope_w : nullptr, fused ? rc_->rotary_dim : 0, fused ? rc_->rotary_offset : 0,
+                            fused && rc_->interleaved != 0));
   if (fused)                // the keys were rotated on their way into the pages (and in place); the queries here
     SPD_HIP(launch_rope((void*)b->q, b->n_q_heads, nullptr, 0, b->dim_qk, rc_->rotary_dim, rc_->rotary_offset,
-                        rc_->interleaved != 0, n_rows, (const int32_t*)(st->dev + off_pos), (const double*)(st->dev + off_w),
-                        stream));
+                        rc_->interleaved != 0, n_rows, (const int32_t*)(ws + off_pos), rope_w, StepMark{}, stream));
   const void *att_k = b->k, *att_v = b->v;
   if (chunked) {
     // every request's rows 0 .. prefix+len-1, the new ones included, back out of the pages
-    SPD_HIP(launch_kv_gather(g, pool->base, (const TileDesc*)(st->dev + off_gather), (int)gdescs.size(), ws,
-                             ws + ws_k_bytes, stream));
-    att_k = ws;
-    att_v = ws + ws_k_bytes;
+    SPD_HIP(launch_kv_gather(g, pool->base, (const TileDesc*)(ws + off_gather), (int)n_gather, ws + ws_k, ws + ws_v, StepMark{}, stream));
+    att_k = ws + ws_k;
+    att_v = ws + ws_v;
   }
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 0, stream)) != SPD_OK) return rc;
-  SPD_HIP(launch_prefill(b->q, att_k, att_v, b->out, (const PrefillWork*)st->dev, (const int32_t*)(st->dev + off_chain),
+  SPD_HIP(launch_prefill(b->q, att_k, att_v, b->out, (const PrefillWork*)ws, (const int32_t*)(ws + off_chain),
                          n_blocks, b->n_q_heads, b->n_kv_heads, b->dim_qk, b->dim_v, b->scale, stream));
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 1, stream)) != SPD_OK) return rc;
-  // the staging buffer is free again once the kernels above have run; its event goes behind the
-  // attention kernel so that nothing sits between the page write and the attention launch
-  if ((rc = stage_commit(ctx, SPD_PHASE_PREFILL, st, bytes, stream, false)) != SPD_OK) return rc;
+  if ((rc = stage_commit(ctx, SPD_PHASE_PREFILL, st, stream)) != SPD_OK) return rc;
   if (ctx->kernel_timing) {
     SPD_HIP(hipEventRecord(ps.ev_end, stream));
     ps.timed = true;
@@ -345,7 +349,7 @@ static int decode_chunk_units(spd_phase_state& ps, const int32_t* ctx_lens, int 
   return (int)std::min<int64_t>(std::max<int64_t>(c, 16), 1 << 20);
 }
 
-// noalloc: the variant that allocates nothing.  Metadata twins and workspace lie in the static scratch
+// noalloc: the variant that allocates nothing.  The metadata's device twin and the workspace lie in the static scratch
 // array, the staging ring is used as spd_ctx_create made it, no timing events are recorded.
 static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch* b, bool noalloc) {
   if (!ctx || !pool || pool->ctx != ctx || !b || b->n_req <= 0 || !b->req_ids || !b->ctx_lens) return SPD_EINVAL;
@@ -357,12 +361,10 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   if (append && (g.kind == SPD_KV_GQA) != (b->v_new != nullptr)) return SPD_EINVAL;
   if (!append && b->v_new) return SPD_EINVAL;
   if (misaligned16(b->q, b->out, b->k_new, b->v_new)) return SPD_EINVAL;
-  for (int r = 0; r < b->n_req; ++r) {
+  spd_phase_state& ds = ctx->phase[SPD_PHASE_DECODE];
+  for (int r = 0; r < b->n_req; ++r)
     if (b->ctx_lens[r] <= 0) return SPD_EINVAL;                            // empty context
-    if (append)
-      for (int r2 = 0; r2 < r; ++r2)
-        if (b->req_ids[r2] == b->req_ids[r]) return SPD_EINVAL;
-  }
+  if (append && has_duplicates(b->req_ids, b->n_req, ds.tmp_set)) return SPD_EINVAL;
   if (b->rope) {
     if (g.kind == SPD_KV_MLA_LATENT_FP8) return SPD_EINVAL;
     int rrc = rope_config_check(b->rope);
@@ -374,136 +376,170 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   if (ctx->device < 0) return SPD_ESTATE;
 
   const int B = b->n_req;
-  const bool fp8 = g.kind == SPD_KV_MLA_LATENT_FP8;
-  const bool mla = g.kind == SPD_KV_MLA_LATENT || fp8;
+  const bool mla = g.kind != SPD_KV_GQA;
   const int unit_t = mla ? decode_mla_step_tokens() : TILE_T;     // tokens per split-K unit
-  int64_t sum_tiles = 0;
-  int32_t max_tiles = 0, max_pages = 0;
+  const int units_per_page = g.P / unit_t;
+  int64_t sum_units = 0;
+  int32_t max_units = 0, max_pages = 0;
   for (int r = 0; r < B; ++r) {
-    int32_t tiles = (b->ctx_lens[r] + unit_t - 1) / unit_t;
-    sum_tiles += tiles;
-    max_tiles = std::max(max_tiles, tiles);
+    int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t;
+    sum_units += units;
+    max_units = std::max(max_units, units);
     max_pages = std::max(max_pages, (b->ctx_lens[r] + g.P - 1) / g.P);
   }
-  const int bt_stride = max_pages;
 
   // the share this step will run on: a staged partition is adopted further down, once nothing but a HIP call can
   // fail any more, so a step that returns an error of its own leaves the partition as it was
   int rc;
-  spd_phase_state& ds = ctx->phase[SPD_PHASE_DECODE];
   int share;
   {
     std::lock_guard<std::mutex> lk(ctx->part_mu);
     share = ds.has_pending ? ds.pending_cus : ds.active_cus;
   }
-  int chunk_tiles = decode_chunk_units(ds, b->ctx_lens, B, unit_t, sum_tiles, g.Hkv, share, mla,
-                                       ctx->env_decode_chunk_tiles);
+  int chunk_units = decode_chunk_units(ds, b->ctx_lens, B, unit_t, sum_units, g.Hkv, share, mla, ctx->env_decode_chunk_tiles);
   // the MLA kernel keeps the page ids of a chunk in the 64 lanes of one register: at most 63 pages per chunk
   // (a chunk that starts inside a page touches one more than it holds)
-  if (mla) chunk_tiles = std::min(chunk_tiles, 62 * (g.P / unit_t));
-  const int max_chunks = (max_tiles + chunk_tiles - 1) / chunk_tiles;
+  if (mla) chunk_units = std::min(chunk_units, 62 * units_per_page);
+  chunk_units = std::min(chunk_units, std::max(8, (max_units + 7) / 8 * 8));
+  const int max_chunks = (max_units + chunk_units - 1) / chunk_units;
 
-  // work items (request, chunk), longest first: only chunks that exist are launched
-  struct Item { int32_t req, chunk, units; };
-  std::vector<Item> items;
+  // work items (request, chunk), longest first: only chunks that exist are launched.  The full chunks come first, request
+  // by request, then the requests' remainders by length.
+  std::vector<uint64_t>& items = ds.tmp_items;                    // (units << 32 | request) of the remainders
+  items.clear();
+  int n_full = 0;
   for (int r = 0; r < B; ++r) {
-    const int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t;
-    for (int32_t ck = 0; ck * chunk_tiles < units; ++ck)
-      items.push_back(Item{r, ck, std::min<int32_t>(chunk_tiles, units - ck * chunk_tiles)});
+    const int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t, rest = units % chunk_units;
+    n_full += units / chunk_units;
+    if (rest) items.push_back((uint64_t)(uint32_t)rest << 32 | (uint32_t)(B - 1 - r));   // equal lengths: request order
   }
-  std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& c) { return a.units > c.units; });
-  const int n_items = (int)items.size();
+  std::sort(items.begin(), items.end(), std::greater<uint64_t>());
+  const int n_items = n_full + (int)items.size();
 
-  size_t off_bt = align16(sizeof(int32_t) * (size_t)B);
-  size_t off_items = align16(off_bt + sizeof(int32_t) * (size_t)B * bt_stride);
-  size_t off_desc = align16(off_items + sizeof(int32_t) * 2 * (size_t)n_items);
-  size_t off_w = align16(off_desc + (append ? sizeof(TileDesc) * (size_t)B : 0));
-  size_t bytes = off_w + (b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0);
+  // a record per item: header and page ids (a chunk that starts inside a page touches one more than it holds)
+  const int chunk_pages = std::min<int64_t>(max_pages, ((int64_t)chunk_units + units_per_page - 1) / units_per_page + (chunk_units % units_per_page ? 1 : 0));
+  const size_t stride = (sizeof(DecodeItem) + sizeof(int32_t) * (size_t)chunk_pages + 63) & ~(size_t)63;
+  if (stride > INT32_MAX) return SPD_EINVAL;
+  const size_t off_chunks = align64(stride * (size_t)n_items);
+  const size_t off_ctx = align16(off_chunks + sizeof(int32_t) * (size_t)B);
+  const bool old_append = mla && (append || b->rope);             // rotation and append in a launch of their own
+  const size_t off_desc = align16(off_ctx + (old_append ? sizeof(int32_t) * (size_t)B : 0));
+  const size_t bytes = align16(off_desc + (old_append && append ? sizeof(TileDesc) * (size_t)B : 0));
+  const size_t w_bytes = b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0;
+  // what the limit of the entry point that allocates nothing counts: one block table row per request, the items, the appends
+  if (noalloc && sizeof(int32_t) * (size_t)B * (1 + (size_t)max_pages) + 8 * (size_t)n_items + (append ? sizeof(TileDesc) * (size_t)B : 0) + w_bytes >
+                     NOALLOC_STAGE_BYTES)
+    return SPD_ETOOBIG;
   spd_stage* st;
-  if (noalloc && bytes > NOALLOC_STAGE_BYTES) return SPD_ETOOBIG;
-  if ((rc = stage_acquire(ctx, SPD_PHASE_DECODE, bytes, &st, !noalloc)) != SPD_OK) return rc;
-  char* const sdev = noalloc ? st->dev_static : st->dev;          // device twin of the step's metadata
+  if ((rc = stage_acquire(ctx, SPD_PHASE_DECODE, bytes + w_bytes, &st, !noalloc)) != SPD_OK) return rc;
   const bool timing = ctx->kernel_timing && !noalloc;
+  const int n_wgs = n_items * g.Hkv;
+  // Few workgroups read their records straight out of the pinned staging buffer: a launch less.  Above 1024 records of
+  // 64 bytes that takes longer than the launch that copies them to the device (PCIe, 1.3 us per round trip).
+  const bool twin = (size_t)n_wgs * stride > 65536;
+  // Split-K partials: merged by the attention launch itself where it has few workgroups, else by a launch of its own
+  const bool inline_merge = !mla && n_wgs <= 512 && (size_t)B * g.Hkv <= MERGE_COUNTERS;
   char* ws = nullptr;
-  size_t ws_o_bytes = max_chunks > 1 ? align16(sizeof(float) * (size_t)B * b->n_q_heads * max_chunks * g.dv) : 0;
-  size_t ws_ml_bytes = max_chunks > 1 ? align16(sizeof(float) * (size_t)B * b->n_q_heads * max_chunks * 2) : 0;
-  size_t ws_q_bytes = b->rope ? (size_t)B * b->n_q_heads * g.dk * 2 : 0;      // the rotated query
+  const size_t ws_o_bytes = max_chunks > 1 ? align16(sizeof(float) * (size_t)B * b->n_q_heads * max_chunks * g.dv) : 0;
+  const size_t ws_ml_bytes = max_chunks > 1 ? align16(sizeof(float) * (size_t)B * b->n_q_heads * max_chunks * 2) : 0;
+  const size_t ws_q_bytes = mla && b->rope ? (size_t)B * b->n_q_heads * g.dk * 2 : 0;      // the rotated query
+  const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + ws_q_bytes + (twin && !noalloc ? bytes : 0);
   if (noalloc) {
-    if (ws_o_bytes + ws_ml_bytes + ws_q_bytes > NOALLOC_WS_BYTES) return SPD_ETOOBIG;
+    if (ws_bytes > NOALLOC_WS_BYTES) return SPD_ETOOBIG;
     ws = ctx->scratch + 4 * NOALLOC_STAGE_BYTES;
-  } else if (ws_o_bytes + ws_ml_bytes + ws_q_bytes > 0 &&
-             (rc = workspace_reserve(ctx, SPD_PHASE_DECODE, ws_o_bytes + ws_ml_bytes + ws_q_bytes, &ws)) != SPD_OK) {
+  } else if (ws_bytes > 0 && (rc = workspace_reserve(ctx, SPD_PHASE_DECODE, ws_bytes, &ws)) != SPD_OK) {
     return rc;
   }
-  char* ws_q = b->rope ? ws + ws_o_bytes + ws_ml_bytes : nullptr;
-  if (b->rope) rope_frequencies(b->rope, (double*)(st->host + off_w));
+  char* const ws_q = ws + ws_o_bytes + ws_ml_bytes;
 
-  int32_t* h_ctx = (int32_t*)st->host;
-  int32_t* h_bt = (int32_t*)(st->host + off_bt);
-  int32_t* h_items = (int32_t*)(st->host + off_items);
-  for (int i = 0; i < n_items; ++i) {
-    h_items[2 * i] = items[(size_t)i].req;
-    h_items[2 * i + 1] = items[(size_t)i].chunk;
-  }
+  int32_t* h_chunks = (int32_t*)(st->host + off_chunks);
+  int32_t* h_ctx = (int32_t*)(st->host + off_ctx);
   TileDesc* h_desc = (TileDesc*)(st->host + off_desc);
+  std::vector<spd_req_table*>& tables = ds.tmp_tables;
+  tables.assign((size_t)B, nullptr);
+  auto put_item = [&](char* rec, int r, int32_t chunk) {
+    const int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t, u0 = chunk * chunk_units, u1 = std::min(units, u0 + chunk_units);
+    *(DecodeItem*)rec = DecodeItem{r, chunk, (units + chunk_units - 1) / chunk_units, b->ctx_lens[r]};
+    const int32_t p0 = u0 / units_per_page, p1 = (u1 - 1) / units_per_page + 1;
+    int32_t* dst = (int32_t*)(rec + sizeof(DecodeItem));
+    const int32_t* src = tables[(size_t)r]->data();
+    memcpy(dst, src + p0, sizeof(int32_t) * (size_t)(p1 - p0));
+    const int words = (int)((stride - sizeof(DecodeItem)) / sizeof(int32_t));
+    for (int32_t i = p1 - p0; i < words; ++i) dst[i] = src[p1 - 1];
+  };
   {
     std::lock_guard<std::mutex> lk(pool->mu);                       // atomic: query, get, update
-    if (append) {
-      int64_t need = 0;
-      for (int r = 0; r < B; ++r) need += blocks_missing_locked(pool, b->req_ids[r], b->ctx_lens[r]);
-      if (need > (int64_t)pool->free_stack.size()) return SPD_ENOMEM;
-    } else {
-      for (int r = 0; r < B; ++r) {
-        auto it = pool->tables.find(b->req_ids[r]);
+    int64_t need = 0;
+    for (int r = 0; r < B; ++r) {
+      auto it = pool->tables.find(b->req_ids[r]);
+      if (it != pool->tables.end()) tables[(size_t)r] = &it->second;
+      const int64_t have = it == pool->tables.end() ? 0 : (int64_t)it->second.size();
+      if (append) {
+        need += std::max<int64_t>(0, (b->ctx_lens[r] + (int64_t)g.P - 1) / g.P - have);
+      } else {
         if (it == pool->tables.end()) return SPD_ENOENT;
-        if ((int64_t)it->second.size() * g.P < b->ctx_lens[r]) return SPD_EINVAL;
+        if (have * g.P < b->ctx_lens[r]) return SPD_EINVAL;
       }
     }
+    if (need > (int64_t)pool->free_stack.size()) return SPD_ENOMEM;
+    const uint64_t number = next_step_number(ctx, SPD_PHASE_DECODE);
     for (int r = 0; r < B; ++r) {
-      if (append) reserve_locked(pool, b->req_ids[r], b->ctx_lens[r]);
-      spd_req_table& t = pool->tables[b->req_ids[r]];
-      t.last_use[SPD_PHASE_DECODE] = next_step_number(ctx, SPD_PHASE_DECODE);
-      int32_t pages = (b->ctx_lens[r] + g.P - 1) / g.P;
-      h_ctx[r] = b->ctx_lens[r];
-      memcpy(h_bt + (size_t)r * bt_stride, t.data(), sizeof(int32_t) * pages);
-      for (int32_t p = pages; p < bt_stride; ++p) h_bt[(size_t)r * bt_stride + p] = t[0];
       if (append) {
-        std::vector<TileDesc> one;
-        build_tile_descs(g, t.data(), b->ctx_lens[r] - 1, 1, r, one);
-        h_desc[r] = one[0];
+        if (!tables[(size_t)r]) tables[(size_t)r] = &pool->tables[b->req_ids[r]];
+        reserve_entry_locked(pool, *tables[(size_t)r], b->ctx_lens[r]);
       }
+      tables[(size_t)r]->last_use[SPD_PHASE_DECODE] = number;
+    }
+    char* rec = st->host;
+    for (int r = 0; r < B; ++r) {
+      const int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t;
+      h_chunks[r] = (units + chunk_units - 1) / chunk_units;
+      for (int32_t ck = 0; ck < units / chunk_units; ++ck, rec += stride) put_item(rec, r, ck);
+      if (old_append) h_ctx[r] = b->ctx_lens[r];
+      if (old_append && append) build_tile_descs(g, tables[(size_t)r]->data(), b->ctx_lens[r] - 1, 1, r, h_desc + r);
+    }
+    for (size_t i = 0; i < items.size(); ++i, rec += stride) {
+      const int r = B - 1 - (int)(uint32_t)items[i];
+      put_item(rec, r, h_chunks[r] - 1);
     }
   }
   hipStream_t stream;
   if ((rc = phase_enter(ctx, SPD_PHASE_DECODE, &stream)) != SPD_OK) return rc;
   if (timing) SPD_HIP(hipEventRecord(ds.ev_start, stream));
-  if ((rc = stage_copy(st, bytes, stream, sdev)) != SPD_OK) return rc;
-  const void* att_q = b->q;
-  if (b->rope) {
-    SPD_HIP(launch_rope_append(g, pool->base, (const TileDesc*)(sdev + off_desc), (const int32_t*)sdev, B, b->q, ws_q,
-                               b->n_q_heads, g.dk, append ? b->k_new : nullptr, append ? b->v_new : nullptr,
-                               b->rope->rotary_dim, b->rope->rotary_offset, b->rope->interleaved != 0,
-                               (const double*)(sdev + off_w), stream));
-    att_q = ws_q;
-  } else if (append && fp8) {
-    SPD_HIP(launch_kv_write_fp8(g, pool->base, (const TileDesc*)(sdev + off_desc), B, b->k_new, stream));
-  } else if (append) {
-    SPD_HIP(launch_kv_write(g, pool->base, (const TileDesc*)(sdev + off_desc), B, b->k_new, b->v_new, stream));
+  StepMark mark = step_mark(ctx, SPD_PHASE_DECODE);
+  DecodeLaunch d{};
+  if (b->rope && (rc = rope_table(ctx, SPD_PHASE_DECODE, b->rope, st->host + bytes, st->dev + bytes, stream, &mark, &d.w)) != SPD_OK) return rc;
+  const char* meta = st->dev;
+  if (twin && (!noalloc || bytes <= 4 * NOALLOC_STAGE_BYTES)) {
+    char* to = noalloc ? ctx->scratch : ws + ws_o_bytes + ws_ml_bytes + ws_q_bytes;
+    SPD_HIP(launch_meta_copy(to, st->dev, bytes, mark, stream));
+    mark.flag = nullptr;
+    meta = to;
   }
+  d.q = b->q; d.k_new = b->k_new; d.v_new = b->v_new; d.out = b->out;
+  d.items = meta; d.n_chunks = (const int32_t*)(meta + off_chunks);
+  d.item_stride = (int)stride; d.n_items = n_items; d.B = B; d.H = b->n_q_heads; d.scale = b->scale;
+  d.chunk_units = chunk_units; d.max_chunks = max_chunks;
+  if (b->rope) { d.rot = b->rope->rotary_dim; d.off = b->rope->rotary_offset; d.interleaved = b->rope->interleaved != 0; }
+  d.ws_o = (float*)ws; d.ws_ml = (float*)(ws + ws_o_bytes);
+  d.counters = inline_merge ? ds.merge_counters : nullptr;
+  if (mla && b->rope) {
+    SPD_HIP(launch_rope_append(g, pool->base, (const TileDesc*)(meta + off_desc), (const int32_t*)(meta + off_ctx), B, b->q, ws_q,
+                               b->n_q_heads, g.dk, b->k_new, b->v_new, d.rot, d.off, d.interleaved, d.w, mark, stream));
+    mark.flag = nullptr;
+    d.q = ws_q;
+  } else if (mla && append) {
+    const TileDesc* descs = (const TileDesc*)(meta + off_desc);
+    if (g.kind == SPD_KV_MLA_LATENT_FP8) SPD_HIP(launch_kv_write_fp8(g, pool->base, descs, B, b->k_new, mark, stream));
+    else SPD_HIP(launch_kv_write(g, pool->base, descs, B, b->k_new, b->v_new, mark, stream));
+    mark.flag = nullptr;
+  }
+  d.mark = mark;
   if (timing && (rc = kernel_timing_mark(ctx, SPD_PHASE_DECODE, 0, stream)) != SPD_OK) return rc;
-  if (mla)
-    SPD_HIP(launch_decode_mla(g, pool->base, att_q, b->out, (const int32_t*)sdev, (const int32_t*)(sdev + off_bt),
-                              bt_stride, sdev + off_items, n_items, B, b->n_q_heads, b->scale, chunk_tiles, max_chunks,
-                              (float*)(max_chunks > 1 ? ws : nullptr), (float*)(max_chunks > 1 ? ws + ws_o_bytes : nullptr), stream,
-                              fp8));
-  else
-    SPD_HIP(launch_decode_gqa(g, pool->base, att_q, b->out, (const int32_t*)sdev, (const int32_t*)(sdev + off_bt),
-                              bt_stride, sdev + off_items, n_items, B, b->n_q_heads, b->scale, chunk_tiles, max_chunks,
-                              (float*)(max_chunks > 1 ? ws : nullptr), (float*)(max_chunks > 1 ? ws + ws_o_bytes : nullptr), stream));
+  if (mla) SPD_HIP(launch_decode_mla(g, pool->base, d, stream));
+  else SPD_HIP(launch_decode_gqa(g, pool->base, d, stream));
   if (timing && (rc = kernel_timing_mark(ctx, SPD_PHASE_DECODE, 1, stream)) != SPD_OK) return rc;
-  // the slot's event goes behind the attention kernels: it frees the staging slot and tells spd_kv_free that
-  // the step no longer reads its requests' pages
-  if ((rc = stage_commit(ctx, SPD_PHASE_DECODE, st, bytes, stream, false)) != SPD_OK) return rc;
+  if ((rc = stage_commit(ctx, SPD_PHASE_DECODE, st, stream)) != SPD_OK) return rc;
   if (timing) {
     SPD_HIP(hipEventRecord(ds.ev_end, stream));
     ds.timed = true;

@@ -12,6 +12,8 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
+from array import array
 from typing import List, Optional, Sequence, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -156,6 +158,30 @@ def _load() -> C.CDLL:
 
 
 lib = _load()
+
+
+# The two steps are called once per layer and iteration, with request lists that change from call to call: their argument
+# structures are packed straight into bytes (the layout of spd_prefill_batch / spd_decode_batch; ctypes structures and
+# arrays of the same content take two to three times as long to make).
+def _entry(name: str):
+    fn = lib[name]                      # a function object of its own, beside the typed lib.<name>
+    fn.argtypes = [C.c_void_p, C.c_void_p, C.c_char_p]
+    fn.restype = C.c_int
+    return fn
+
+
+_pack_prefill = struct.Struct("@iPPPPPPPiiiifPP").pack
+_pack_decode = struct.Struct("@iPPPPPPifP").pack
+_prefill_entry, _decode_entry = _entry("spd_prefill_step"), _entry("spd_decode_step")
+
+
+def _numbers(code: str, values) -> array:
+    """A C array of `values` (array typecode Q or i)."""
+    try:
+        return array(code, values)
+    except (TypeError, OverflowError):  # floats and the like, as int() takes them; out of range, as ctypes wraps them
+        kind = C.c_uint64 if code == "Q" else C.c_int32
+        return array(code, bytes((kind * len(values))(*[int(x) for x in values])))
 
 
 def strerror(status: int) -> str:
@@ -465,8 +491,18 @@ class Pool:
     def prefill_step(self, req_ids: Sequence[int], cu_seqlens: Sequence[int], q, k, v, out, n_q_heads: int,
                      n_kv_heads: int, dim_qk: int, dim_v: int, scale: float, latent=None, prefix_lens=None,
                      rope: Optional[spd_rope_config] = None) -> None:
-        self.prefill_step_batch(self.make_prefill_batch(req_ids, cu_seqlens, q, k, v, out, n_q_heads, n_kv_heads,
-                                                        dim_qk, dim_v, scale, latent, prefix_lens, rope))
+        ids, cu = _numbers("Q", req_ids), _numbers("i", cu_seqlens)
+        n = len(ids)
+        if len(cu) != n + 1 or (prefix_lens is not None and len(prefix_lens) != n):
+            return self.prefill_step_batch(self.make_prefill_batch(req_ids, cu_seqlens, q, k, v, out, n_q_heads, n_kv_heads,
+                                                                   dim_qk, dim_v, scale, latent, prefix_lens, rope))
+        pre = _numbers("i", prefix_lens) if prefix_lens is not None else None
+        args = _pack_prefill(n, ids.buffer_info()[0], cu.buffer_info()[0], _ptr(q) or 0, _ptr(k) or 0, _ptr(v) or 0, _ptr(latent) or 0,
+                             _ptr(out) or 0, n_q_heads, n_kv_heads, dim_qk, dim_v, scale, pre.buffer_info()[0] if pre is not None else 0,
+                             C.addressof(rope) if rope is not None else 0)
+        status = _prefill_entry(self.ctx.h, self.h, args)
+        if status != SPD_OK:
+            _check(status, "spd_prefill_step")
 
     def make_prefill_batch(self, req_ids: Sequence[int], cu_seqlens: Sequence[int], q, k, v, out, n_q_heads: int,
                            n_kv_heads: int, dim_qk: int, dim_v: int, scale: float, latent=None, prefix_lens=None,
@@ -524,4 +560,11 @@ class Pool:
         _check(lib.spd_decode_step_noalloc(self.ctx.h, self.h, C.byref(batch)), "spd_decode_step_noalloc")
 
     def decode_step(self, req_ids, ctx_lens, q, out, n_q_heads: int, scale: float, k_new=None, v_new=None, rope=None) -> None:
-        self.decode_step_batch(self.make_decode_batch(req_ids, ctx_lens, q, out, n_q_heads, scale, k_new, v_new, rope))
+        ids, lens = _numbers("Q", req_ids), _numbers("i", ctx_lens)
+        if len(ids) != len(lens):
+            return self.decode_step_batch(self.make_decode_batch(req_ids, ctx_lens, q, out, n_q_heads, scale, k_new, v_new, rope))
+        args = _pack_decode(len(ids), ids.buffer_info()[0], lens.buffer_info()[0], _ptr(q) or 0, _ptr(k_new) or 0, _ptr(v_new) or 0,
+                            _ptr(out) or 0, n_q_heads, scale, C.addressof(rope) if rope is not None else 0)
+        status = _decode_entry(self.ctx.h, self.h, args)
+        if status != SPD_OK:
+            _check(status, "spd_decode_step")
