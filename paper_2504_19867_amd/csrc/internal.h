@@ -89,7 +89,11 @@ __device__ inline void store_mark(const StepMark& m) {
 struct DecodeItem {
   int32_t req, chunk, n_chunks;
   int32_t n;         // attended tokens of the request
+  int32_t unit0, n_units;   // the chunk, in units of 16 tokens
+  int32_t next;      // the record the workgroup goes on with, or -1 (latent decode)
+  int32_t pad;
 };
+constexpr int DECODE_ITEM_WORDS = sizeof(DecodeItem) / 4;
 
 // What a decode attention launch is given.
 struct DecodeLaunch {
@@ -98,9 +102,9 @@ struct DecodeLaunch {
   const char* items;                  // n_items records of item_stride bytes
   const int32_t* n_chunks;            // [B]
   const double* w;                    // rot / 2 frequencies
-  int item_stride, n_items, B, H;
+  int item_stride, n_wgs, B, H;       // n_wgs: workgroups (GQA: per KV head), each starts with the record of its number
   float scale;
-  int chunk_units, max_chunks;
+  int max_chunks;
   int rot, off, interleaved;          // rot = 0: no rotation
   float *ws_o, *ws_ml;
   uint32_t* counters;                 // [B * Hkv] zeros: the chunks are merged by the last workgroup; null: by a launch of its own
@@ -198,19 +202,16 @@ struct spd_phase_state {
   bool rope_valid = false;
   uint32_t* merge_counters = nullptr;  // decode phase: MERGE_COUNTERS zeros (split_merge.h), zero again after every step
   // a step's working lists, kept from step to step (one thread drives a phase)
-  std::vector<uint64_t> tmp_set, tmp_items;
+  std::vector<uint64_t> tmp_set;
+  std::vector<spd::DecodeItem> tmp_items, tmp_items2;
   std::vector<spd_req_table*> tmp_tables;
-  std::vector<int32_t> tmp_sizes;
-  std::vector<int64_t> tmp_heap;
+  std::vector<int32_t> tmp_sizes, tmp_chunks;
   char* workspace = nullptr;           // split-K partials (decode)
   size_t ws_cap = 0;
   // workspaces outgrown, with the number of the last step that may still read them: freed once that step has
   // finished (looked at when the workspace grows again, in spd_phase_sync and when the context goes)
   std::vector<std::pair<char*, uint64_t>> ws_retired;
   std::mutex ws_mu;                    // the list above (a step's thread against another thread's spd_phase_sync)
-  // last split-K chunk choice of the MLA decode (re-derived when the batch has changed by more than a little)
-  int ck_B = 0, ck_cus = 0, ck_chunk = 0;
-  int64_t ck_sum = 0;
   hipEvent_t kev[256][2] = {};         // kernel timing ring (measurement aid)
   uint64_t kev_count = 0, kev_read = 0;
 };
@@ -274,9 +275,8 @@ hipError_t launch_kv_gather_fp8(const PoolGeom& g, const char* pool_base, const 
                                 const StepMark& mark, hipStream_t stream);
 hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const StepMark& mark, hipStream_t stream);
 hipError_t launch_decode_gqa(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream);
-// the new latent row is in its page already and q is rotated (launch_rope_append / launch_kv_write before it)
 hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream);
-int decode_mla_step_tokens();
+constexpr int MLA_CHUNK_PAGES = 252;      // pages a chunk of the latent decode may touch (the workgroup keeps their ids in LDS)
 // one workgroup per chain: workgroup b computes the items d_work[d_chain[b]] .. d_work[d_chain[b + 1] - 1]
 hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillWork* d_work,
                           const int32_t* d_chain, int n_blocks, int H, int Hkv, int dqk, int dv, float scale,
@@ -289,10 +289,6 @@ hipError_t launch_ffn_pack(const void* w_gate, const void* w_up, void* w_gu, int
 // d_pos, d_w may be device-readable pinned host memory
 hipError_t launch_rope(void* q, int n_q_heads, void* k, int n_kv_heads, int dim, int rot, int off, bool interleaved,
                        int n_tokens, const int32_t* d_pos, const double* d_w, const StepMark& mark, hipStream_t stream);
-// decode step with RoPE: rotated query copy + rotated key (and value) appended to the page, one launch
-hipError_t launch_rope_append(const PoolGeom& g, char* pool_base, const TileDesc* d_descs, const int32_t* d_ctx_lens, int B,
-                              const void* q, void* q_out, int Hq, int dq, const void* k_new, const void* v_new, int rot,
-                              int off, bool interleaved, const double* d_w, const StepMark& mark, hipStream_t stream);
 hipError_t launch_probe(int32_t* d_ids, int n_blocks, hipStream_t stream);
 hipError_t launch_copy(void* dst, const void* src, uint64_t bytes, int cus, hipStream_t stream);
 hipError_t launch_read(const void* src, uint64_t bytes, int cus, uint32_t* sink, hipStream_t stream);

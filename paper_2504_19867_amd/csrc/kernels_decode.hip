@@ -18,6 +18,7 @@
 // Long contexts are split into chunks (split-K); partial (max, sum, O) triples go to a
 // workspace and a small second kernel merges them.
 #include "internal.h"
+#include "rope_device.h"
 #include "split_merge.h"
 
 namespace spd {
@@ -178,48 +179,13 @@ struct GqaArgs {
   const char* items;
   int item_stride, Hkv, H, G;
   float c;                      // scale * log2(e)
-  int chunk_tiles, max_chunks;
+  int max_chunks;
   const double* w;
   int rot, off, interleaved;
   float *ws_o, *ws_ml;
   uint32_t* counters;
   StepMark mark;
 };
-
-__device__ inline float bf_lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
-__device__ inline float bf_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
-
-// The 16-byte piece `own` (entries e0 .. e0 + 7 of a head) rotated; `oth` is the piece with the other halves of its
-// pairs (half layout).  Same arithmetic as the RoPE step.
-__device__ inline uint4 rotate_piece(uint4 own, uint4 oth, int e0, int off, int rot, bool interleaved, const float* cs, const float* sn) {
-  if (e0 < off || e0 >= off + rot) return own;
-  uint32_t ow[4] = {own.x, own.y, own.z, own.w};
-  const uint32_t tw[4] = {oth.x, oth.y, oth.z, oth.w};
-  if (interleaved) {
-    const int p0 = (e0 - off) >> 1;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float xa = bf_lo(ow[j]), xb = bf_hi(ow[j]);
-      ow[j] = pack_bf16_rne(xa * cs[p0 + j] - xb * sn[p0 + j], xb * cs[p0 + j] + xa * sn[p0 + j]);
-    }
-  } else {
-    const int half = rot >> 1;
-    const bool first = e0 < off + half;           // this piece holds the a side of its 8 pairs
-    const int p0 = first ? e0 - off : e0 - off - half;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float m0 = bf_lo(ow[j]), m1 = bf_hi(ow[j]), o0 = bf_lo(tw[j]), o1 = bf_hi(tw[j]);
-      const float c0 = cs[p0 + 2 * j], s0 = sn[p0 + 2 * j], c1 = cs[p0 + 2 * j + 1], s1 = sn[p0 + 2 * j + 1];
-      ow[j] = first ? pack_bf16_rne(m0 * c0 - o0 * s0, m1 * c1 - o1 * s1) : pack_bf16_rne(m0 * c0 + o0 * s0, m1 * c1 + o1 * s1);
-    }
-  }
-  return uint4{ow[0], ow[1], ow[2], ow[3]};
-}
-// first entry of the piece that holds the other halves of the pairs of the piece at e0 (e0 itself where there is none)
-__device__ inline int partner_piece(int e0, int off, int rot, bool interleaved) {
-  if (interleaved || e0 < off || e0 >= off + rot) return e0;
-  return e0 < off + (rot >> 1) ? e0 + (rot >> 1) : e0 - (rot >> 1);
-}
 
 // grid (n_items * n_kv_heads), block 256; workgroup i serves KV head i % n_kv_heads of work item
 // i / n_kv_heads.  Heads vary fastest so that the round-robin placement of
@@ -244,12 +210,13 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
   const int b = __builtin_amdgcn_readfirstlane(sm_rec[0]), chunk = __builtin_amdgcn_readfirstlane(sm_rec[1]);
   const int n_chunks = __builtin_amdgcn_readfirstlane(sm_rec[2]), n = __builtin_amdgcn_readfirstlane(sm_rec[3]);
   auto page_id = [&](int i) -> int {               // i-th page of the chunk
-    const int wd = min(i + 4, words - 1);
-    return wd < 256 ? sm_rec[wd] : ((const int32_t*)rec)[wd];
+    const int wd = min(i + DECODE_ITEM_WORDS, words - 1);
+    int id = sm_rec[min(wd, 255)];
+    if (words > 256 && wd > 255) id = ((const int32_t*)rec)[wd];
+    return id;
   };
   const int n_tiles = (n + TILE_T - 1) / TILE_T;
-  const int tile0 = chunk * a.chunk_tiles;
-  const int tile1 = min(n_tiles, tile0 + a.chunk_tiles);
+  const int tile0 = __builtin_amdgcn_readfirstlane(sm_rec[4]), tile1 = tile0 + __builtin_amdgcn_readfirstlane(sm_rec[5]);
   const int n_steps = (tile1 - tile0 + 1) >> 1;
   const int my_steps = (n_steps - wave + 3) >> 2;                      // this wave's steps: wave, wave + 4, ...
   const bool interleaved = a.interleaved != 0;
@@ -277,7 +244,7 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
   for (int s = 0; s < D / 32; ++s) {
     const int e0 = 8 * (4 * s + c4);
     own[s] = *(const uint4*)(qrow + e0);
-    if (a.rot) oth[s] = *(const uint4*)(qrow + partner_piece(e0, a.off, a.rot, interleaved));
+    if (a.rot) oth[s] = *(const uint4*)(qrow + rope_partner(e0, a.off, a.rot, interleaved));
   }
   // the new token's tile is the last one of the request: the wave whose step holds it does the append
   const bool appends = a.k_new != nullptr && tile1 == n_tiles && ((n_steps - 1) & 3) == wave;
@@ -289,7 +256,7 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
     const bf16_t* src = (lane / PCS & 1) ? a.v_new : a.k_new;
     src += ((size_t)b * a.Hkv + g) * D;
     kv_own = *(const uint4*)(src + e0);
-    if (a.rot && lane < PCS) kv_oth = *(const uint4*)(src + partner_piece(e0, a.off, a.rot, interleaved));
+    if (a.rot && lane < PCS) kv_oth = *(const uint4*)(src + rope_partner(e0, a.off, a.rot, interleaved));
   }
 
   TileFrag<D> fa, fb;
@@ -310,7 +277,7 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
 #pragma unroll
   for (int s = 0; s < D / 32; ++s) {
     uint4 piece = own[s];
-    if (a.rot) piece = rotate_piece(own[s], oth[s], 8 * (4 * s + c4), a.off, a.rot, interleaved, cs, sn);
+    if (a.rot) piece = rope_rotate(own[s], oth[s], 8 * (4 * s + c4), a.off, a.rot, interleaved, cs, sn);
     if (col >= a.G) piece = uint4{0, 0, 0, 0};
     qf[s] = __builtin_bit_cast(bf16x8, piece);
   }
@@ -319,7 +286,7 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
     const int pg = (n_tiles - 1) / a.tiles_per_page;
     char* tile = pool_g + (uint64_t)(uint32_t)page_id(pg - page0) * a.page_bytes + (uint64_t)(n_tiles - 1 - pg * a.tiles_per_page) * a.tile_bytes;
     if (lane < PCS) {
-      const uint4 piece = a.rot ? rotate_piece(kv_own, kv_oth, 8 * pc, a.off, a.rot, interleaved, cs, sn) : kv_own;
+      const uint4 piece = a.rot ? rope_rotate(kv_own, kv_oth, 8 * pc, a.off, a.rot, interleaved, cs, sn) : kv_own;
       *(uint4*)(krow + 8 * pc) = piece;
       *(uint4*)(tile + ((size_t)(pc * TILE_T + t) << 4)) = piece;
     } else if (lane < 2 * PCS) {
@@ -407,40 +374,10 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
     }
   }
   if (n_chunks == 1 || a.counters == nullptr) return;
-  // ---- small launches: the workgroup that finds itself to be the last of its (request, KV head) merges the chunks
+  // ---- few chunks: the workgroup that finds itself to be the last of its (request, KV head) merges them
   if (!last_of(a.counters + (size_t)b * a.Hkv + g, (uint32_t)n_chunks, &sm_last)) return;
-  for (int idx = threadIdx.x; idx < a.G * (D / 2); idx += 256) {
-    const int qh = idx / (D / 2), d = 2 * (idx % (D / 2));
-    const size_t head = head0 + qh, slot0 = head * a.max_chunks;
-    const f32x2 r = merge_chunks(a.ws_o + slot0 * D + d, D, a.ws_ml + slot0 * 2, n_chunks);
-    *(uint32_t*)(a.out + head * D + d) = pack_bf16_rne(r[0], r[1]);
-  }
-}
-
-// grid (ceil(H / (512 / D)), B), block 128: merge the chunks of (request, head) pairs; D / 4 threads per head, four
-// output dims each.
-template <int D>
-__global__ __launch_bounds__(128) void decode_combine_kernel(bf16_t* __restrict__ out, const int32_t* __restrict__ chunks,
-                                                            int H, int max_chunks, const float* __restrict__ ws_o,
-                                                            const float* __restrict__ ws_ml) {
-  constexpr int TPH = D / 4;                       // threads per head
-  const int h = blockIdx.x * (128 / TPH) + threadIdx.x / TPH, b = blockIdx.y, d = 4 * (threadIdx.x % TPH);
-  const int n_chunks = chunks[b];
-  if (n_chunks <= 1 || h >= H) return;            // one chunk: written directly by the attention kernel
-  const size_t slot0 = ((size_t)b * H + h) * max_chunks;
-  float m_tot = -INFINITY;
-  for (int ck = 0; ck < n_chunks; ++ck) m_tot = fmaxf(m_tot, ws_ml[(slot0 + ck) * 2]);
-  float l_tot = 0.f;
-  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int ck = 0; ck < n_chunks; ++ck) {
-    const float wgt = __builtin_amdgcn_exp2f(ws_ml[(slot0 + ck) * 2] - m_tot);
-    l_tot += ws_ml[(slot0 + ck) * 2 + 1] * wgt;
-    o += *(const f32x4*)(ws_o + (slot0 + ck) * D + d) * wgt;
-  }
-  uint2 pk;
-  pk.x = pack_bf16_rne(o[0] / l_tot, o[1] / l_tot);
-  pk.y = pack_bf16_rne(o[2] / l_tot, o[3] / l_tot);
-  *(uint2*)(out + ((size_t)b * H + h) * D + d) = pk;
+  const size_t slot0 = head0 * a.max_chunks;
+  merge_in_launch<D, 256>(a.ws_o + slot0 * D, a.ws_ml + slot0 * 2, a.G, a.max_chunks, n_chunks, &sm_o[0][0][0], a.out + head0 * D);
 }
 
 template <int D>
@@ -452,15 +389,13 @@ static hipError_t launch_decode_gqa_t(const PoolGeom& g, char* pool_base, const 
   a.items = d.items; a.item_stride = d.item_stride;
   a.Hkv = g.Hkv; a.H = d.H; a.G = d.H / g.Hkv;
   a.c = d.scale * 1.4426950408889634f;
-  a.chunk_tiles = d.chunk_units; a.max_chunks = d.max_chunks;
+  a.max_chunks = d.max_chunks;
   a.w = d.w; a.rot = d.rot; a.off = d.off; a.interleaved = d.interleaved;
   a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.counters = d.counters; a.mark = d.mark;
-  hipLaunchKernelGGL(decode_gqa_kernel<D>, dim3((unsigned)d.n_items * g.Hkv), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(decode_gqa_kernel<D>, dim3((unsigned)d.n_wgs * g.Hkv), dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || d.max_chunks <= 1 || d.counters) return e;
-  hipLaunchKernelGGL(decode_combine_kernel<D>, dim3((unsigned)(d.H + 512 / D - 1) / (512 / D), d.B), dim3(128), 0, stream, (bf16_t*)d.out,
-                     d.n_chunks, d.H, d.max_chunks, d.ws_o, d.ws_ml);
-  return hipGetLastError();
+  return launch_merge_chunks<D>(d, stream);
 }
 
 hipError_t launch_decode_gqa(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream) {

@@ -12,6 +12,7 @@
 //
 // Both kernels: one workgroup per 16-token tile, 16 lanes per token; a lane owns 32 consecutive ckv entries (a
 // quarter of a scale block: the block's maximum is formed over 4 neighbouring lanes).
+#include "fp8_row.h"
 #include "internal.h"
 
 namespace spd {
@@ -22,14 +23,10 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int ROW = FP8_ROW_BYTES;   // 656
-constexpr float E4M3_MAX = 448.f;
 
-__device__ inline float bf_lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
-__device__ inline float bf_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
 __device__ inline uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
-__device__ inline float clamp448(float y) { return fminf(fmaxf(y, -E4M3_MAX), E4M3_MAX); }
 }  // namespace
 
 // grid (n_tiles + copy_cols), block 256.  latent: dense [rows, 576] bf16.
@@ -50,32 +47,9 @@ __global__ __launch_bounds__(256) void kv_write_latent_fp8_kernel(char* __restri
   if (t < d.t_begin || t >= d.t_end) return;        // whole groups of 16 lanes leave together: the shuffles below stay inside a group of 4
   const bf16_t* src = latent + (size_t)(d.src_row + t - d.t_begin) * 576;
   char* row = base + (uint64_t)d.page * page_bytes + (uint64_t)d.sub * tile_bytes + (size_t)t * ROW;
-  // 32 entries of this lane: four 16-byte pieces
-  uint32_t w[16];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const uint4 p = *(const uint4*)(src + 32 * l + 8 * j);
-    w[4 * j] = p.x; w[4 * j + 1] = p.y; w[4 * j + 2] = p.z; w[4 * j + 3] = p.w;
-  }
-  float amax = 0.f;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) amax = fmaxf(amax, fmaxf(fabsf(bf_lo(w[j])), fabsf(bf_hi(w[j]))));
-  amax = fmaxf(amax, __shfl_xor(amax, 1));
-  amax = fmaxf(amax, __shfl_xor(amax, 2));
-  const float scale = amax > 0.f ? amax / E4M3_MAX : 1.f;
-  uint32_t codes[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    // four entries per word: entries 4 j .. 4 j + 3 = the two halves of w[2 j] and w[2 j + 1]
-    int pk = 0;
-    pk = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(bf_lo(w[2 * j]) / scale), clamp448(bf_hi(w[2 * j]) / scale), pk, false);
-    pk = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(bf_lo(w[2 * j + 1]) / scale), clamp448(bf_hi(w[2 * j + 1]) / scale), pk, true);
-    codes[j] = (uint32_t)pk;
-  }
-  *(uint4*)(row + 32 * l) = uint4{codes[0], codes[1], codes[2], codes[3]};
-  *(uint4*)(row + 32 * l + 16) = uint4{codes[4], codes[5], codes[6], codes[7]};
-  if ((l & 3) == 0) *(float*)(row + 512 + 4 * (l >> 2)) = scale;
-  if (l < 8) *(uint4*)(row + 528 + 16 * l) = *(const uint4*)(src + 512 + 8 * l);
+  Fp8Piece p;
+  fp8_quantise(src, l, p);
+  fp8_store_row(row, src, l, p);
 }
 
 // grid (n_tiles), block 256.  out: dense [rows, 576] bf16 = decode(code) * scale rounded to bf16, rope as stored.

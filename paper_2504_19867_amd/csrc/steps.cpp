@@ -3,6 +3,7 @@
 // the kernels (kernels_*.hip).
 #include "internal.h"
 #include "prefill_work.h"
+#include "split_merge.h"
 
 #include <stdlib.h>
 #include <string.h>
@@ -300,53 +301,109 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
 }
 
 // ------------------------------------------------------------------------------------------ decode
-// Split-K chunk length in units (16-token tiles for GQA, 16-token steps for MLA).
-static int decode_chunk_units(spd_phase_state& ps, const int32_t* ctx_lens, int B, int unit_t, int64_t sum_units, int Hkv,
-                              int cus, bool mla, int override_tiles) {
-  const int64_t round = mla ? 1 : 8;              // GQA: 4 waves x 2 tiles per step
-  if (override_tiles > 0) return (int)((override_tiles + round - 1) / round * round);   // tuning override
-  if (mla) {
-    // Two workgroups are resident per CU (slots); items are issued longest first and a slot takes
-    // the next item when it is done, so a chunk length is judged by replaying exactly that: the
-    // candidate with the shortest finish time wins.  An item costs its steps plus a pipeline
-    // fill.  The choice is kept while the batch stays about the same.
-    if (ps.ck_chunk > 0 && ps.ck_B == B && ps.ck_cus == cus && llabs(sum_units - ps.ck_sum) * 32 <= ps.ck_sum)
-      return ps.ck_chunk;
-    const int slots = std::max(1, 2 * cus);
-    const int64_t fill = 6;
-    const int64_t c_min = std::max<int64_t>(8, (sum_units + slots - 1) / slots);
-    int64_t best_c = c_min, best_t = INT64_MAX;
-    std::vector<int32_t> sizes;
-    std::vector<int64_t> heap;
-    for (int k = 0; k < 16; ++k) {
-      const int64_t c = c_min + c_min * k / 6;    // c_min .. 3.5 c_min
-      sizes.clear();
-      for (int r = 0; r < B; ++r) {
-        int32_t u = (ctx_lens[r] + unit_t - 1) / unit_t;
-        for (; u > 0; u -= (int32_t)c) sizes.push_back((int32_t)std::min<int64_t>(u, c));
-      }
-      std::sort(sizes.begin(), sizes.end(), std::greater<int32_t>());
-      heap.assign((size_t)slots, 0);              // min-heap of slot finish times
-      auto cmp = std::greater<int64_t>();
-      int64_t finish = 0;
-      for (int32_t sz : sizes) {
-        std::pop_heap(heap.begin(), heap.end(), cmp);
-        heap.back() += sz + fill;
-        finish = std::max(finish, heap.back());
-        std::push_heap(heap.begin(), heap.end(), cmp);
-      }
-      if (finish < best_t) { best_t = finish; best_c = c; }
-    }
-    ps.ck_B = B; ps.ck_cus = cus; ps.ck_sum = sum_units; ps.ck_chunk = (int)std::min<int64_t>(best_c, 1 << 20);
-    return ps.ck_chunk;
+// How the step's contexts are split over workgroups, in units of 16 tokens.
+struct DecodeSplit {
+  int n_wgs = 0, max_chunks = 1;
+  int32_t chunk_units = 0;       // largest chunk
+};
+
+static inline void push_chunk(std::vector<DecodeItem>& items, int r, int32_t chunk, int32_t n, int32_t u0, int32_t nu) {
+  items.push_back(DecodeItem{r, chunk, 0, n, u0, nu, -1, 0});
+}
+
+// Chunks of c units, handed out longest first: the full chunks, request by request, then the requests' remainders by length.
+static void cut_chunks(spd_phase_state& ps, const int32_t* ctx_lens, int B, int max_units, int64_t c, int32_t* n_chunks, DecodeSplit& out) {
+  out.chunk_units = (int32_t)c;
+  out.max_chunks = (int)((max_units + c - 1) / c);
+  std::vector<DecodeItem>& items = ps.tmp_items;
+  std::vector<uint64_t>& rest = ps.tmp_set;                      // (units << 32 | request)
+  items.clear();
+  rest.clear();
+  for (int r = 0; r < B; ++r) {
+    const int32_t units = (ctx_lens[r] + TILE_T - 1) / TILE_T, full = units / (int32_t)c;
+    n_chunks[r] = (int32_t)((units + c - 1) / c);
+    for (int32_t ck = 0; ck < full; ++ck) push_chunk(items, r, ck, ctx_lens[r], ck * (int32_t)c, (int32_t)c);
+    if (units % c) rest.push_back((uint64_t)(units % c) << 32 | (uint32_t)(B - 1 - r));   // equal lengths: request order
   }
-  // GQA: aim at ~6 workgroups per CU of the decode share: enough to balance unequal contexts
-  // (items are issued longest first), few enough to keep the split-K partials small
-  int64_t target_wgs = (int64_t)cus * 6;
-  int64_t per_head_chunks = std::max<int64_t>(1, target_wgs / std::max(1, Hkv));
-  int64_t c = (sum_units + per_head_chunks - 1) / per_head_chunks;
-  c = (c + round - 1) / round * round;
-  return (int)std::min<int64_t>(std::max<int64_t>(c, 16), 1 << 20);
+  std::sort(rest.begin(), rest.end(), std::greater<uint64_t>());
+  for (uint64_t k : rest) {
+    const int r = B - 1 - (int)(uint32_t)k;
+    push_chunk(items, r, n_chunks[r] - 1, ctx_lens[r], (n_chunks[r] - 1) * (int32_t)c, (int32_t)(k >> 32));
+  }
+  out.n_wgs = (int)items.size();
+}
+
+// GQA: about 6 workgroups per CU of the decode share: enough to balance unequal contexts, few enough to keep the split-K
+// partials small.
+static void split_gqa(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t sum_units, int max_units, int Hkv, int cus, int override_tiles,
+                      int32_t* n_chunks, DecodeSplit& out) {
+  const int64_t round = 8;                       // 4 waves x 2 tiles per step
+  int64_t c;
+  if (override_tiles > 0) {                      // tuning override
+    c = (override_tiles + round - 1) / round * round;
+  } else {
+    const int64_t per_head_chunks = std::max<int64_t>(1, (int64_t)cus * 6 / std::max(1, Hkv));
+    c = (sum_units + per_head_chunks - 1) / per_head_chunks;
+    c = std::min<int64_t>(std::max<int64_t>((c + round - 1) / round * round, 16), 1 << 20);
+  }
+  cut_chunks(ps, ctx_lens, B, max_units, std::min<int64_t>(c, (max_units + round - 1) / round * round), n_chunks, out);
+}
+
+// Latent decode: two workgroups per CU are resident, and the batch's units are dealt to them evenly, in request order, a
+// workgroup going on from one request's end to the next one's beginning.  (Chunks of one length, handed out longest first, left
+// a quarter of the slots idle at the end.)  A chunk costs its pipeline fill and its merge beside its tiles, about as
+// much as CHUNK_COST tiles; chunks are whole rounds of the four waves, except at a request's end.
+static void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t sum_units, int cus, int units_per_page, int override_units,
+                         int32_t* n_chunks, DecodeSplit& out) {
+  constexpr int64_t CHUNK_COST = 20, ROUND = 4;
+  const int64_t slots = std::max(1, 2 * cus), most = (int64_t)(MLA_CHUNK_PAGES - 1) * units_per_page / ROUND * ROUND;
+  std::vector<DecodeItem>& items = ps.tmp_items;
+  std::vector<int32_t>& owner = ps.tmp_sizes;                    // workgroup of each chunk
+  // at least two tiles per wave
+  int64_t quota = CHUNK_COST + (override_units > 0 ? override_units : std::max<int64_t>(2 * ROUND, (sum_units + B * CHUNK_COST) / slots));
+  for (;; quota += std::max<int64_t>(1, quota / 64)) {
+    const int64_t sliver = std::min<int64_t>((quota - CHUNK_COST) / 4, 4);
+    items.clear();
+    owner.clear();
+    int wg = 0;
+    int64_t room = quota;
+    out.chunk_units = 0;
+    out.max_chunks = 1;
+    for (int r = 0; r < B; ++r) {
+      const int32_t units = (ctx_lens[r] + TILE_T - 1) / TILE_T;
+      int32_t u0 = 0, chunk = 0;
+      while (u0 < units) {
+        const int64_t left = units - u0;
+        if (room < quota && room - CHUNK_COST <= sliver && left > room - CHUNK_COST) { ++wg; room = quota; }   // too little room to start here
+        int64_t take = std::min<int64_t>(left, std::max<int64_t>(ROUND, (room - CHUNK_COST) / ROUND * ROUND));
+        if (left > take && left - take <= sliver) take = left;                  // too little left to start elsewhere
+        take = std::min(take, most);
+        push_chunk(items, r, chunk++, ctx_lens[r], u0, (int32_t)take);
+        owner.push_back(wg);
+        out.chunk_units = std::max(out.chunk_units, (int32_t)take);
+        u0 += (int32_t)take;
+        room -= CHUNK_COST + take;
+        if (room < CHUNK_COST + ROUND) { ++wg; room = quota; }
+      }
+      n_chunks[r] = chunk;
+      out.max_chunks = std::max(out.max_chunks, (int)chunk);
+    }
+    out.n_wgs = owner.back() + 1;
+    if (out.n_wgs <= slots || override_units > 0) break;
+  }
+  // workgroup i starts with record i: first chunks to the front, the others behind them, linked
+  const int n = (int)items.size();
+  std::vector<DecodeItem>& sorted = ps.tmp_items2;
+  sorted.resize((size_t)n);
+  int behind = out.n_wgs, prev = 0;
+  for (int i = 0; i < n; ++i) {
+    const bool first = i == 0 || owner[(size_t)i] != owner[(size_t)i - 1];
+    const int at = first ? owner[(size_t)i] : behind++;
+    sorted[(size_t)at] = items[(size_t)i];
+    if (!first) sorted[(size_t)prev].next = at;
+    prev = at;
+  }
+  items.swap(sorted);
 }
 
 // noalloc: the variant that allocates nothing.  The metadata's device twin and the workspace lie in the static scratch
@@ -377,12 +434,11 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
 
   const int B = b->n_req;
   const bool mla = g.kind != SPD_KV_GQA;
-  const int unit_t = mla ? decode_mla_step_tokens() : TILE_T;     // tokens per split-K unit
-  const int units_per_page = g.P / unit_t;
+  const int units_per_page = g.P / TILE_T;
   int64_t sum_units = 0;
   int32_t max_units = 0, max_pages = 0;
   for (int r = 0; r < B; ++r) {
-    int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t;
+    const int32_t units = (b->ctx_lens[r] + TILE_T - 1) / TILE_T;
     sum_units += units;
     max_units = std::max(max_units, units);
     max_pages = std::max(max_pages, (b->ctx_lens[r] + g.P - 1) / g.P);
@@ -396,35 +452,20 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
     std::lock_guard<std::mutex> lk(ctx->part_mu);
     share = ds.has_pending ? ds.pending_cus : ds.active_cus;
   }
-  int chunk_units = decode_chunk_units(ds, b->ctx_lens, B, unit_t, sum_units, g.Hkv, share, mla, ctx->env_decode_chunk_tiles);
-  // the MLA kernel keeps the page ids of a chunk in the 64 lanes of one register: at most 63 pages per chunk
-  // (a chunk that starts inside a page touches one more than it holds)
-  if (mla) chunk_units = std::min(chunk_units, 62 * units_per_page);
-  chunk_units = std::min(chunk_units, std::max(8, (max_units + 7) / 8 * 8));
-  const int max_chunks = (max_units + chunk_units - 1) / chunk_units;
-
-  // work items (request, chunk), longest first: only chunks that exist are launched.  The full chunks come first, request
-  // by request, then the requests' remainders by length.
-  std::vector<uint64_t>& items = ds.tmp_items;                    // (units << 32 | request) of the remainders
-  items.clear();
-  int n_full = 0;
-  for (int r = 0; r < B; ++r) {
-    const int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t, rest = units % chunk_units;
-    n_full += units / chunk_units;
-    if (rest) items.push_back((uint64_t)(uint32_t)rest << 32 | (uint32_t)(B - 1 - r));   // equal lengths: request order
-  }
-  std::sort(items.begin(), items.end(), std::greater<uint64_t>());
-  const int n_items = n_full + (int)items.size();
+  std::vector<int32_t>& n_chunks = ds.tmp_chunks;
+  n_chunks.resize((size_t)B);
+  DecodeSplit sp;
+  if (mla) split_latent(ds, b->ctx_lens, B, sum_units, share, units_per_page, ctx->env_decode_chunk_tiles, n_chunks.data(), sp);
+  else split_gqa(ds, b->ctx_lens, B, sum_units, max_units, g.Hkv, share, ctx->env_decode_chunk_tiles, n_chunks.data(), sp);
+  const std::vector<DecodeItem>& items = ds.tmp_items;
+  const int n_items = (int)items.size(), max_chunks = sp.max_chunks;
 
   // a record per item: header and page ids (a chunk that starts inside a page touches one more than it holds)
-  const int chunk_pages = std::min<int64_t>(max_pages, ((int64_t)chunk_units + units_per_page - 1) / units_per_page + (chunk_units % units_per_page ? 1 : 0));
+  const int chunk_pages = (int)std::min<int64_t>(max_pages, ((int64_t)sp.chunk_units + units_per_page - 2) / units_per_page + 1);
   const size_t stride = (sizeof(DecodeItem) + sizeof(int32_t) * (size_t)chunk_pages + 63) & ~(size_t)63;
   if (stride > INT32_MAX) return SPD_EINVAL;
   const size_t off_chunks = align64(stride * (size_t)n_items);
-  const size_t off_ctx = align16(off_chunks + sizeof(int32_t) * (size_t)B);
-  const bool old_append = mla && (append || b->rope);             // rotation and append in a launch of their own
-  const size_t off_desc = align16(off_ctx + (old_append ? sizeof(int32_t) * (size_t)B : 0));
-  const size_t bytes = align16(off_desc + (old_append && append ? sizeof(TileDesc) * (size_t)B : 0));
+  const size_t bytes = align16(off_chunks + sizeof(int32_t) * (size_t)B);
   const size_t w_bytes = b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0;
   // what the limit of the entry point that allocates nothing counts: one block table row per request, the items, the appends
   if (noalloc && sizeof(int32_t) * (size_t)B * (1 + (size_t)max_pages) + 8 * (size_t)n_items + (append ? sizeof(TileDesc) * (size_t)B : 0) + w_bytes >
@@ -433,40 +474,27 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   spd_stage* st;
   if ((rc = stage_acquire(ctx, SPD_PHASE_DECODE, bytes + w_bytes, &st, !noalloc)) != SPD_OK) return rc;
   const bool timing = ctx->kernel_timing && !noalloc;
-  const int n_wgs = n_items * g.Hkv;
+  const int n_wgs = sp.n_wgs * g.Hkv;
   // Few workgroups read their records straight out of the pinned staging buffer: a launch less.  Above 1024 records of
   // 64 bytes that takes longer than the launch that copies them to the device (PCIe, 1.3 us per round trip).
-  const bool twin = (size_t)n_wgs * stride > 65536;
-  // Split-K partials: merged by the attention launch itself where it has few workgroups, else by a launch of its own
-  const bool inline_merge = !mla && n_wgs <= 512 && (size_t)B * g.Hkv <= MERGE_COUNTERS;
+  const bool twin = (size_t)n_items * g.Hkv * stride > 131072;
+  // Split-K partials are merged by the attention launch itself where a request has few chunks and the launch few workgroups
+  // (each pays for going past the L2), else by a launch of its own
+  const bool inline_merge = n_wgs <= (mla ? 128 : 512) && max_chunks <= MERGE_IN_LAUNCH_CHUNKS && (size_t)B * g.Hkv <= MERGE_COUNTERS;
   char* ws = nullptr;
   const size_t ws_o_bytes = max_chunks > 1 ? align16(sizeof(float) * (size_t)B * b->n_q_heads * max_chunks * g.dv) : 0;
   const size_t ws_ml_bytes = max_chunks > 1 ? align16(sizeof(float) * (size_t)B * b->n_q_heads * max_chunks * 2) : 0;
-  const size_t ws_q_bytes = mla && b->rope ? (size_t)B * b->n_q_heads * g.dk * 2 : 0;      // the rotated query
-  const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + ws_q_bytes + (twin && !noalloc ? bytes : 0);
+  const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + (twin && !noalloc ? bytes : 0);
   if (noalloc) {
     if (ws_bytes > NOALLOC_WS_BYTES) return SPD_ETOOBIG;
     ws = ctx->scratch + 4 * NOALLOC_STAGE_BYTES;
   } else if (ws_bytes > 0 && (rc = workspace_reserve(ctx, SPD_PHASE_DECODE, ws_bytes, &ws)) != SPD_OK) {
     return rc;
   }
-  char* const ws_q = ws + ws_o_bytes + ws_ml_bytes;
 
   int32_t* h_chunks = (int32_t*)(st->host + off_chunks);
-  int32_t* h_ctx = (int32_t*)(st->host + off_ctx);
-  TileDesc* h_desc = (TileDesc*)(st->host + off_desc);
   std::vector<spd_req_table*>& tables = ds.tmp_tables;
   tables.assign((size_t)B, nullptr);
-  auto put_item = [&](char* rec, int r, int32_t chunk) {
-    const int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t, u0 = chunk * chunk_units, u1 = std::min(units, u0 + chunk_units);
-    *(DecodeItem*)rec = DecodeItem{r, chunk, (units + chunk_units - 1) / chunk_units, b->ctx_lens[r]};
-    const int32_t p0 = u0 / units_per_page, p1 = (u1 - 1) / units_per_page + 1;
-    int32_t* dst = (int32_t*)(rec + sizeof(DecodeItem));
-    const int32_t* src = tables[(size_t)r]->data();
-    memcpy(dst, src + p0, sizeof(int32_t) * (size_t)(p1 - p0));
-    const int words = (int)((stride - sizeof(DecodeItem)) / sizeof(int32_t));
-    for (int32_t i = p1 - p0; i < words; ++i) dst[i] = src[p1 - 1];
-  };
   {
     std::lock_guard<std::mutex> lk(pool->mu);                       // atomic: query, get, update
     int64_t need = 0;
@@ -490,18 +518,19 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
       }
       tables[(size_t)r]->last_use[SPD_PHASE_DECODE] = number;
     }
+    const int words = (int)((stride - sizeof(DecodeItem)) / sizeof(int32_t));
     char* rec = st->host;
-    for (int r = 0; r < B; ++r) {
-      const int32_t units = (b->ctx_lens[r] + unit_t - 1) / unit_t;
-      h_chunks[r] = (units + chunk_units - 1) / chunk_units;
-      for (int32_t ck = 0; ck < units / chunk_units; ++ck, rec += stride) put_item(rec, r, ck);
-      if (old_append) h_ctx[r] = b->ctx_lens[r];
-      if (old_append && append) build_tile_descs(g, tables[(size_t)r]->data(), b->ctx_lens[r] - 1, 1, r, h_desc + r);
+    for (int i = 0; i < n_items; ++i, rec += stride) {
+      DecodeItem it = items[(size_t)i];
+      it.n_chunks = n_chunks[(size_t)it.req];
+      *(DecodeItem*)rec = it;
+      const int32_t p0 = it.unit0 / units_per_page, p1 = (it.unit0 + it.n_units - 1) / units_per_page + 1;
+      const int32_t* src = tables[(size_t)it.req]->data();
+      int32_t* dst = (int32_t*)(rec + sizeof(DecodeItem));
+      memcpy(dst, src + p0, sizeof(int32_t) * (size_t)(p1 - p0));
+      for (int32_t j = p1 - p0; j < words; ++j) dst[j] = src[p1 - 1];
     }
-    for (size_t i = 0; i < items.size(); ++i, rec += stride) {
-      const int r = B - 1 - (int)(uint32_t)items[i];
-      put_item(rec, r, h_chunks[r] - 1);
-    }
+    memcpy(h_chunks, n_chunks.data(), sizeof(int32_t) * (size_t)B);
   }
   hipStream_t stream;
   if ((rc = phase_enter(ctx, SPD_PHASE_DECODE, &stream)) != SPD_OK) return rc;
@@ -511,29 +540,18 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   if (b->rope && (rc = rope_table(ctx, SPD_PHASE_DECODE, b->rope, st->host + bytes, st->dev + bytes, stream, &mark, &d.w)) != SPD_OK) return rc;
   const char* meta = st->dev;
   if (twin && (!noalloc || bytes <= 4 * NOALLOC_STAGE_BYTES)) {
-    char* to = noalloc ? ctx->scratch : ws + ws_o_bytes + ws_ml_bytes + ws_q_bytes;
+    char* to = noalloc ? ctx->scratch : ws + ws_o_bytes + ws_ml_bytes;
     SPD_HIP(launch_meta_copy(to, st->dev, bytes, mark, stream));
     mark.flag = nullptr;
     meta = to;
   }
   d.q = b->q; d.k_new = b->k_new; d.v_new = b->v_new; d.out = b->out;
   d.items = meta; d.n_chunks = (const int32_t*)(meta + off_chunks);
-  d.item_stride = (int)stride; d.n_items = n_items; d.B = B; d.H = b->n_q_heads; d.scale = b->scale;
-  d.chunk_units = chunk_units; d.max_chunks = max_chunks;
+  d.item_stride = (int)stride; d.n_wgs = sp.n_wgs; d.B = B; d.H = b->n_q_heads; d.scale = b->scale;
+  d.max_chunks = max_chunks;
   if (b->rope) { d.rot = b->rope->rotary_dim; d.off = b->rope->rotary_offset; d.interleaved = b->rope->interleaved != 0; }
   d.ws_o = (float*)ws; d.ws_ml = (float*)(ws + ws_o_bytes);
   d.counters = inline_merge ? ds.merge_counters : nullptr;
-  if (mla && b->rope) {
-    SPD_HIP(launch_rope_append(g, pool->base, (const TileDesc*)(meta + off_desc), (const int32_t*)(meta + off_ctx), B, b->q, ws_q,
-                               b->n_q_heads, g.dk, b->k_new, b->v_new, d.rot, d.off, d.interleaved, d.w, mark, stream));
-    mark.flag = nullptr;
-    d.q = ws_q;
-  } else if (mla && append) {
-    const TileDesc* descs = (const TileDesc*)(meta + off_desc);
-    if (g.kind == SPD_KV_MLA_LATENT_FP8) SPD_HIP(launch_kv_write_fp8(g, pool->base, descs, B, b->k_new, mark, stream));
-    else SPD_HIP(launch_kv_write(g, pool->base, descs, B, b->k_new, b->v_new, mark, stream));
-    mark.flag = nullptr;
-  }
   d.mark = mark;
   if (timing && (rc = kernel_timing_mark(ctx, SPD_PHASE_DECODE, 0, stream)) != SPD_OK) return rc;
   if (mla) SPD_HIP(launch_decode_mla(g, pool->base, d, stream));
