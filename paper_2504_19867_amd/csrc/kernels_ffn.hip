@@ -20,11 +20,12 @@
 // LDS; the four 16-byte chunks of a row are XOR-swizzled with bits 2..3 of the row number, which
 // spreads 16 consecutive rows over all banks.
 //
-// Decode batches (up to 256 tokens) are bound by reading the weights once: the same kernel with smaller
-// tiles (128 x 128 with four waves, 64 x 128 with a ring of six stages, two workgroups per compute unit; 64 x 256
-// with eight waves and a ring of seven stages where that still gives every unit a workgroup),
-// so that every compute unit of the share has a workgroup and more weight bytes are in flight per unit.
+// Decode batches of up to 128 tokens are bound by reading the weights once and have a kernel of their own
+// (ffn_gate_up_stream_kernel); between 128 and 256 tokens the tile kernel runs with 128 x 128 tiles (four waves, two workgroups
+// per compute unit), so that every compute unit of the share has a workgroup.
 #include "internal.h"
+
+#include <type_traits>
 
 namespace spd {
 
@@ -48,28 +49,18 @@ __device__ inline void dma16s(const void* sbase, uint32_t voff, uint32_t lds_byt
 }
 #define SPD_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))
 
-// MB: 32-token blocks per wave; WNW: waves along the joint columns; NSTAGE: LDS ring.  The waves form a
-// 2 x WNW grid, each with 32 MB tokens x 64 joint columns; the workgroup's tile is 64 MB tokens x 64 WNW
-// joint columns.
-// <4, 4, 4>: 256 x 256 for prompt batches.  For small batches the product is bound by reading the
-// weights once, and what counts is how many weight bytes a CU keeps in flight: <2, 2, 4>: 128 x 128,
-// four waves, two workgroups per CU, for up to 128 tokens; <1, 2, 6>: 64 x 128 with a ring of six
-// 12 KiB stages, of which 8 KiB are weights, two workgroups per CU, for up to 64 tokens; <1, 4, 7>: 64 x 256,
-// eight waves, a ring of seven 20 KiB stages of which 16 KiB are weights (x is a fifth of what a workgroup
-// loads instead of a third), one workgroup per CU.
-template <int MB, int WNW, int NSTAGE>
+// MB: 32-token blocks per wave; WNW: waves along the joint columns.  The waves form a 2 x WNW grid, each with
+// 32 MB tokens x 64 joint columns; the workgroup's tile is 64 MB tokens x 64 WNW joint columns: <4, 4>: 256 x 256 for
+// prompt batches, <2, 2>: 128 x 128, four waves, two workgroups per CU.
+template <int MB, int WNW>
 __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                                    bf16_t* __restrict__ out, int T, int K, int I, int tiles_m,
                                                                    int tiles_n, int xcds, StepMark mark) {
   if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
-  constexpr int WAVES = 2 * WNW, BM = 64 * MB, BNP = 64 * WNW, PD = NSTAGE - 1;
+  constexpr int NSTAGE = 4, WAVES = 2 * WNW, BM = 64 * MB, BNP = 64 * WNW, PD = NSTAGE - 1;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BNP * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
-  // 1 KiB load instructions per wave per slice.  Where x has fewer pieces than there are waves (a 64-token tile under
-  // eight waves), every wave loads one: piece wave % A_LOADS, so two waves write the same bytes to the same place.
-  constexpr int A_LOADS = A_BYTES / 1024, B_LOADS = B_BYTES / 1024;
-  constexpr bool A_SHARED = A_LOADS < WAVES;
-  constexpr int LPW = A_SHARED ? 1 + B_LOADS / WAVES : (A_LOADS + B_LOADS) / WAVES;
-  static_assert(B_LOADS % WAVES == 0 && (A_SHARED ? WAVES % A_LOADS == 0 : A_LOADS % WAVES == 0), "loads divide evenly over the waves");
+  constexpr int A_LOADS = A_BYTES / 1024, B_LOADS = B_BYTES / 1024, LPW = (A_LOADS + B_LOADS) / WAVES;   // 1 KiB load instructions (per wave)
+  static_assert(B_LOADS % WAVES == 0 && A_LOADS % WAVES == 0, "loads divide evenly over the waves");
   __shared__ __attribute__((aligned(1024))) char smem[NSTAGE * STAGE_BYTES];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -111,10 +102,7 @@ __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t*
   // [64 ii, 64 ii + 64) of the stage: x rows first (row = slot / 4), then weight rows; slot s of a
   // row holds the row's chunk s ^ ((row >> 2) & 3).  Token rows past T re-read row T - 1.
   // piece number of this wave's load j: below A_LOADS a piece of x, from there on pieces of the weights
-  auto piece_of = [&](int j) __attribute__((always_inline)) -> int {
-    if constexpr (A_SHARED) return j == 0 ? wave % A_LOADS : A_LOADS + wave + WAVES * (j - 1);
-    else return wave + WAVES * j;
-  };
+  auto piece_of = [&](int j) __attribute__((always_inline)) -> int { return wave + WAVES * j; };
   uint32_t ld_voff[LPW];
 #pragma unroll
   for (int j = 0; j < LPW; ++j) {
@@ -187,10 +175,7 @@ __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t*
   // this wave's loads of slice s are done when at most (slices issued after it) * LPW remain
   auto wait_slice = [&](int s) __attribute__((always_inline)) {
     const int later = pt - s - 1;
-    if (NSTAGE > 6 && later >= 5) SPD_WAIT_VMCNT(5 * LPW);
-    else if (NSTAGE > 5 && later >= 4) SPD_WAIT_VMCNT(4 * LPW);
-    else if (NSTAGE > 4 && later == 3) SPD_WAIT_VMCNT(3 * LPW);
-    else if (later >= 2) SPD_WAIT_VMCNT(2 * LPW);
+    if (later >= 2) SPD_WAIT_VMCNT(2 * LPW);
     else if (later == 1) SPD_WAIT_VMCNT(LPW);
     else SPD_WAIT_VMCNT(0);
   };
@@ -242,6 +227,132 @@ __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t*
     }
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2)));   // `out` is only promised to be aligned to its entries
+
+// Up to 128 tokens: bound by reading the weights once, i.e. by how many of their bytes are on the way at a time.
+// The weights go straight from global memory into operand registers (a load is 1 KiB of consecutive bytes, 16 joint rows x 32
+// entries in 16x16x32 operand order) and every wave streams rows of its own through a ring of RING slices in
+// registers, which no barrier touches.  A wave has 16 gate rows and the 16 up rows that belong to them, against all 16 NB
+// tokens.  The x rows, which all waves share, go through LDS, 256 hidden entries at a time in two stages, loaded
+// one stage ahead: one barrier per 8 slices.
+// The product is taken transposed (weights are the A operand): a lane then has four consecutive outputs of one token.
+// <NB, 8, 8>: 256 joint rows per workgroup, 128 KiB of weights on the way per CU; <NB, 4, 16>: 128 rows, the same bytes on the
+// way from four waves.  With the weights staged through LDS (at most 96 KiB on the way, a third to a fifth of the stages taken
+// by x, a barrier per slice) 64 tokens of hidden 4096, inter 14336 took 68 us on 128 CUs and 48 on 256; now 55 and 42 us (4.3 and
+// 5.7 TB/s).  A ring of 16 slices with eight waves is slower (56 us; 75 against 62 at 128 tokens), and so are loads
+// without the non-temporal mark (61 us).
+template <int NB, int WAVES, int RING>
+__global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
+                                                                           bf16_t* __restrict__ out, int T, int K, int I, StepMark mark) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
+  constexpr int XS = 8;                           // slices per x stage
+  constexpr int ROWS = 16 * NB, CHUNKS = 4 * XS;  // 16-byte chunks of a row per stage
+  constexpr int PITCH = (ROWS + 1) * 16;          // bytes per chunk column [chunk][row]: the odd row spreads the writes over the banks
+  constexpr int XL = ROWS * CHUNKS / (64 * WAVES);   // 16-byte pieces of a stage per thread
+  static_assert(RING % XS == 0 && ROWS * CHUNKS % (64 * WAVES) == 0, "whole stages per ring, whole pieces per thread");
+  __shared__ __attribute__((aligned(1024))) char smem[2 * CHUNKS * PITCH];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n16 = lane & 15, c4 = lane >> 4;
+  const int n_slices = K / BK, last = n_slices - 1;
+  // this wave's rows: half `hf` of joint block `jb` (64 rows)
+  const int u = (int)blockIdx.x * WAVES + wave, jb = u >> 1, hf = u & 1;
+  const char* wb = (const char*)w + (size_t)(jb >> 2) * n_slices * 16384 + (size_t)((jb & 3) * 64 + hf * 16) * 64;
+  const uint32_t w_off = (uint32_t)(n16 * 64 + ((c4 ^ ((n16 >> 2) & 3)) * 16));
+  auto load_w = [&](int s, int half) __attribute__((always_inline)) -> u32x4 {   // half 0: gate, 1: up rows of slice s
+    return __builtin_nontemporal_load((const u32x4*)(wb + (size_t)min(s, last) * 16384 + half * 2048 + w_off));
+  };
+  // x pieces: piece i of a stage is chunk i % CHUNKS of row i / CHUNKS; rows past T re-read row T - 1, entries past K the row's last ones
+  u32x4 xr[XL];
+  auto load_x = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < XL; ++j) {
+      const int i = tid + 64 * WAVES * j, row = min(i / CHUNKS, T - 1), ch = min(st * CHUNKS + i % CHUNKS, K / 8 - 1);
+      xr[j] = *(const u32x4*)((const char*)x + (size_t)row * K * 2 + (size_t)ch * 16);
+    }
+  };
+  auto store_x = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < XL; ++j) {
+      const int i = tid + 64 * WAVES * j;
+      *(u32x4*)(smem + buf * (CHUNKS * PITCH) + (i % CHUNKS) * PITCH + (i / CHUNKS) * 16) = xr[j];
+    }
+  };
+  f32x4 acc[2][NB];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 wr[RING][2];
+  load_x(0);
+  store_x(0);
+  // the next x pieces before the weights, as inside the loop: the compiler then waits for them with the weights still on their way
+  load_x(1);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < RING; ++s) {
+    wr[s][0] = load_w(s, 0);
+    wr[s][1] = load_w(s, 1);
+  }
+  int buf = 0;
+  const int x_off = c4 * PITCH + n16 * 16;
+  bf16x8 xv[2][NB];
+  auto read_x = [&](bf16x8* o, const char* xs) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) o[b] = *(const bf16x8*)(xs + b * 256);
+  };
+  // RING slices from s0 on; with `tail` only those that there are
+  auto round = [&](int s0, auto tail) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < RING; ++r) {
+      if (r % XS == 0) {
+        // everyone's pieces of this stage are there, and everyone is done with the one before, which the next pieces replace
+        __syncthreads();
+        store_x(buf ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load_x((s0 + r) / XS + 2);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // the stage's x operands are read a slice ahead of the MFMAs
+      const char* xs = smem + buf * (CHUNKS * PITCH) + x_off;
+      if (r % XS == 0) read_x(xv[0], xs);
+      if (r % XS + 1 < XS) read_x(xv[(r + 1) & 1], xs + (r % XS + 1) * (4 * PITCH));
+      __builtin_amdgcn_sched_barrier(0);
+      if (!tail || s0 + r < n_slices) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          acc[0][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[r][0]), xv[r & 1][b], acc[0][b], 0, 0, 0);
+          acc[1][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[r][1]), xv[r & 1][b], acc[1][b], 0, 0, 0);
+        }
+      }
+      if (!tail) {
+        wr[r][0] = load_w(s0 + r + RING, 0);
+        wr[r][1] = load_w(s0 + r + RING, 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (r % XS == XS - 1) buf ^= 1;
+    }
+  };
+  int s0 = 0;
+  for (; s0 + RING <= n_slices; s0 += RING) round(s0, std::false_type{});
+  if (s0 < n_slices) round(s0, std::true_type{});
+  // element i of lane (n16, c4) is output 4 c4 + i of token n16 of its block
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int t = 16 * b + n16;
+    float y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float g = acc[0][b][i];
+      y[i] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * acc[1][b][i];
+    }
+    if (t < T)
+      *(u32x2_any*)(out + (size_t)t * I + 32 * jb + 16 * hf + 4 * c4) = u32x2_any{cvt_bf16(y[0]) | cvt_bf16(y[1]) << 16, cvt_bf16(y[2]) | cvt_bf16(y[3]) << 16};
+  }
+}
+
 // The packed weights from the two weight matrices, one 16-byte piece per thread and step: piece
 // number i of the output lies in tile i / 1024 = (tn, ks), row r = (i % 1024) / 4, slot s = i % 4, and
 // holds the hidden entries 32 ks + 8 (s ^ ((r >> 2) & 3)) .. + 7 of joint row 256 tn + r.
@@ -262,31 +373,41 @@ __global__ __launch_bounds__(256) void ffn_pack_kernel(const uint4* __restrict__
 
 }  // namespace
 
-template <int MB, int WNW, int NSTAGE>
+template <int MB, int WNW>
 static hipError_t launch_tiles(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, const StepMark& mark, hipStream_t stream) {
   constexpr int BM = 64 * MB, BNP = 64 * WNW;
   const int tiles_m = (T + BM - 1) / BM, tiles_n = 2 * I / BNP;
   if (tiles_n < xcds) xcds = 1;
   const int per = xcds > 1 ? ((tiles_n + xcds - 1) / xcds) * tiles_m : tiles_m * tiles_n;
-  hipLaunchKernelGGL((ffn_gate_up_kernel<MB, WNW, NSTAGE>), dim3((unsigned)(per * xcds)), dim3(128 * WNW), 0, stream, (const bf16_t*)x,
+  hipLaunchKernelGGL((ffn_gate_up_kernel<MB, WNW>), dim3((unsigned)(per * xcds)), dim3(128 * WNW), 0, stream, (const bf16_t*)x,
                      (const bf16_t*)w_gu, (bf16_t*)out, T, K, I, tiles_m, tiles_n, xcds, mark);
+  return hipGetLastError();
+}
+
+template <int NB>
+static hipError_t launch_stream(const void* x, const void* w_gu, void* out, int T, int K, int I, int cus, const StepMark& mark, hipStream_t stream) {
+  const bf16_t *xx = (const bf16_t*)x, *ww = (const bf16_t*)w_gu;
+  // eight waves where 256-row workgroups still occupy nearly every compute unit of the share; half as many rows otherwise (64 tokens
+  // of hidden 8192, inter 7168 on 128 CUs, which gives 56 wide workgroups: 59 us with 112 narrow ones)
+  if (8 * (2 * I / 256) >= 7 * cus)
+    hipLaunchKernelGGL((ffn_gate_up_stream_kernel<NB, 8, 8>), dim3((unsigned)(2 * I / 256)), dim3(512), 0, stream, xx, ww, (bf16_t*)out, T, K, I, mark);
+  else
+    hipLaunchKernelGGL((ffn_gate_up_stream_kernel<NB, 4, 16>), dim3((unsigned)(2 * I / 128)), dim3(256), 0, stream, xx, ww, (bf16_t*)out, T, K, I, mark);
   return hipGetLastError();
 }
 
 hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int cus,
                               const StepMark& mark, hipStream_t stream) {
-  // small batches are bound by reading the weights: the small tile where the large one would leave
-  // half of the share's compute units without a workgroup
+  // up to 128 tokens: the weights streamed through registers, all tokens in one workgroup (measured at 100 and 128 tokens of
+  // hidden 4096, inter 14336 on 128 CUs: 61 and 63 us, 96 and 105 us for 128 x 128 tiles)
+  if (T <= 16) return launch_stream<1>(x, w_gu, out, T, K, I, cus, mark, stream);
+  if (T <= 32) return launch_stream<2>(x, w_gu, out, T, K, I, cus, mark, stream);
+  if (T <= 64) return launch_stream<4>(x, w_gu, out, T, K, I, cus, mark, stream);
+  if (T <= 128) return launch_stream<8>(x, w_gu, out, T, K, I, cus, mark, stream);
+  // the small tile where the large one would leave half of the share's compute units without a workgroup
   const int large_tiles = ((T + 255) / 256) * (2 * I / 256);
-  if (T <= 64) {
-    // 64 x 256 tiles (one workgroup per CU, 96 KiB of weights in flight) where they give nearly every compute
-    // unit of the share a workgroup; 64 x 128 tiles (two per CU, 80 KiB in flight) otherwise
-    const int wide_tiles = 2 * I / 256;
-    if (8 * wide_tiles >= 7 * cus) return launch_tiles<1, 4, 7>(x, w_gu, out, T, K, I, xcds, mark, stream);
-    return launch_tiles<1, 2, 6>(x, w_gu, out, T, K, I, xcds, mark, stream);
-  }
-  if (T <= 128 || (T <= 256 && 2 * large_tiles <= cus)) return launch_tiles<2, 2, 4>(x, w_gu, out, T, K, I, xcds, mark, stream);
-  return launch_tiles<4, 4, 4>(x, w_gu, out, T, K, I, xcds, mark, stream);
+  if (T <= 256 && 2 * large_tiles <= cus) return launch_tiles<2, 2>(x, w_gu, out, T, K, I, xcds, mark, stream);
+  return launch_tiles<4, 4>(x, w_gu, out, T, K, I, xcds, mark, stream);
 }
 
 hipError_t launch_ffn_pack(const void* w_gate, const void* w_up, void* w_gu, int K, int I, hipStream_t stream) {

@@ -59,10 +59,33 @@ def test_gate_up_matches_oracle(T, K, I):
     ctx.close()
 
 
+@pytest.mark.parametrize("T", [1, 16, 17, 32, 33, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("K,I,cus", [(32, 128, 0), (288, 128, 0), (512, 256, 0), (544, 384, 0), (800, 3584, 32), (4096, 3584, 32)])
+def test_gate_up_streamed_weights(T, K, I, cus):
+    """Up to 128 tokens the weights stream through a register ring of 8 slices (eight waves: inter fills the share) or
+    16 (four waves): token counts at the edges of the 16-token blocks, slice counts below, at and beyond the rings (1, 9, 16, 17, 25,
+    128), an output tensor that is aligned to its entries only, and no row past the batch written."""
+    ctx = S.Context(0)
+    if cus:
+        ctx.set_partition(ctx.device_info()[0] - cus, cus)
+    xb, wgb, wub = W.ffn_inputs(T, K, I, seed=1300 + T)
+    x, wg, wu = dev_bf16(xb), dev_bf16(wgb), dev_bf16(wub)
+    w_gu = torch.empty((2 * I, K), dtype=torch.bfloat16, device=DEV)
+    flat = torch.full(((T + 2) * I + 1,), 7.0, dtype=torch.bfloat16, device=DEV)
+    out = flat[1:].view(T + 2, I)
+    ctx.ffn_pack_gate_up(DEC, wg, wu, w_gu, K, I)
+    ctx.ffn_gate_up(DEC, x, w_gu, out, T, K, I)
+    ctx.phase_sync(DEC)
+    got = host_f64(flat)
+    assert got[0] == 7.0 and (got[1 + T * I:] == 7.0).all()
+    _assert_ffn(got[1:1 + T * I].reshape(T, I), F.gate_up(f64(xb), f64(wgb), f64(wub)), f"ffn streamed weights T={T} K={K} I={I}")
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,K,I", [(1, 256, 128), (7, 512, 384), (31, 256, 640), (32, 1024, 128), (33, 256, 128), (48, 768, 256),
                                    (63, 512, 128), (64, 256, 384), (16, 4096, 256), (64, 4096, 128)])
 def test_gate_up_batches_of_up_to_64_tokens(T, K, I):
-    """At most 64 tokens: the small-tile instances (which one depends on the phase's share of compute units and on
+    """At most 64 tokens: the instances for few tokens (which one depends on the phase's share of compute units and on
     inter), ragged token counts, 8 to 128 slices."""
     ctx = S.Context(0)
     xb, wgb, wub = W.ffn_inputs(T, K, I, seed=500 + T)
@@ -74,8 +97,8 @@ def test_gate_up_batches_of_up_to_64_tokens(T, K, I):
 
 @pytest.mark.parametrize("T,K", [(5, 256), (33, 512), (64, 1024)])
 def test_gate_up_small_batch_on_a_small_share_takes_the_wide_tile(T, K):
-    """inter = 3584 gives 28 tiles of 256 joint columns: on a 32-CU decode share that is enough for the 64 x 256
-    instance (eight waves, one piece of x per wave), which the shapes above never reach on larger shares."""
+    """inter = 3584 gives 28 workgroups of 256 joint rows: on a 32-CU decode share that is enough for the eight-wave
+    instance, which the shapes above never reach on larger shares."""
     ctx = S.Context(0)
     total, _, gran = ctx.device_info()
     ctx.set_partition(total - gran, gran)
