@@ -68,7 +68,7 @@ struct TileDesc {
   int32_t sub;       // tile index inside the page
   int32_t t_begin;   // first token slot (0..15) touched
   int32_t t_end;     // one past the last token slot touched
-  int32_t pad[3];    // pad[0]: logical position of the tile's token slot 0 in its request
+  int32_t pad[3];    // [0]: logical position of the tile's token slot 0 in its request; [1]: row of KvRows::k_all that t_begin maps to
 };
 
 // A step's first kernel stores `seq`, the number of the phase's step before it, at `flag`: that step has finished.
@@ -257,13 +257,26 @@ int rope_table(spd_ctx* ctx, int phase, const spd_rope_config* c, char* host, co
 // where it is the first one behind a step (flag null: it is not)
 // d_tiles may be device-readable pinned host memory.  With copy_dst non-null the same launch also
 // copies copy_bytes (rounded up to 16) from copy_src to copy_dst.
-// With rope_w non-null (device or device-readable pinned: rot / 2 frequencies) the key rows are rotated on the way
-// (position = TileDesc.pad[0] + token slot), into the pages and in place in k; only where kv_write_can_rotate.
 hipError_t launch_kv_write(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles,
                            const void* k, const void* v, const StepMark& mark, hipStream_t stream, void* copy_dst = nullptr,
-                           const void* copy_src = nullptr, uint64_t copy_bytes = 0, const double* rope_w = nullptr,
-                           int rot = 0, int rot_off = 0, bool interleaved = false);
-bool kv_write_can_rotate(const PoolGeom& g);
+                           const void* copy_src = nullptr, uint64_t copy_bytes = 0);
+// What a prefill step does besides the page write, in the same launch (only where kv_rows_supported).
+struct KvRows {
+  void* copy_dst = nullptr;             // metadata copy, as above
+  const void* copy_src = nullptr;
+  uint64_t copy_bytes = 0;
+  const double* rope_w = nullptr;       // non-null: key rows are rotated, in the pages and in k (position = TileDesc.pad[0] + token slot)
+  int rot = 0, off = 0;
+  bool interleaved = false;
+  void* q = nullptr;                    // with rope_w: the tiles' query rows [rows, n_q_heads, dk], rotated in place
+  int n_q_heads = 0;
+  const TileDesc* d_cached = nullptr;   // tiles of cached rows that go to k_all, v_all, as do the new rows (at TileDesc.pad[1])
+  int n_cached = 0;
+  void *k_all = nullptr, *v_all = nullptr;
+};
+bool kv_rows_supported(const PoolGeom& g);
+hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k, const void* v,
+                          const KvRows& x, const StepMark& mark, hipStream_t stream);
 hipError_t launch_kv_gather(const PoolGeom& g, const char* pool_base, const TileDesc* d_tiles, int n_tiles,
                             void* k_out, void* v_out, const StepMark& mark, hipStream_t stream);
 // FP8 latent pools (kernels_kv_fp8.hip): quantising page write of dense [rows, 576] bf16 latent rows (with the same

@@ -5,6 +5,7 @@
 // kernels move rows between dense [rows, heads, dim] tensors and the library's page layout
 // (internal.h); they are pure copies, bit-exact.
 #include "internal.h"
+#include "rope_device.h"
 
 #include <algorithm>
 
@@ -112,153 +113,248 @@ __global__ __launch_bounds__(256) void kv_write_kernel(char* __restrict__ base, 
   }
 }
 
-// The same page write for GQA pools with dk, dv <= 128, one workgroup per 16-token tile and group of
-// up to HG KV heads: the descriptor (possibly in pinned host memory) is fetched once per group
-// instead of once per head, and the row reads of all the group's heads are in flight together
-// before the first head goes through LDS.  grid (n_tiles + copy_cols, ceil(Hkv / HG)), block 256.
-// With ROPE the key rows are rotated on the way (rotary position embedding, token position = pos0 of the tile's
-// descriptor + token slot; same arithmetic as rope_kernel: fp64 angle reduced to [-pi, pi], fp32 rotation, one
-// rounding to bf16): the rotated piece goes to the page and back to the caller's k row, which the attention
-// kernel of the same step reads.  A piece's partner (the other half of its pairs, in the half layout) is found
-// in the LDS copy of the raw row.
-struct RopeFuse {
-  const double* w;        // [rot / 2] frequencies
-  bf16_t* k_rw;           // the k tensor again, writable
-  int rot, off;           // rotating entries per head, first rotating entry (multiples of 16 and 8)
+// Everything a prefill step does to rows before its attention kernel, in one launch, for GQA pools with dk, dv <= 128:
+//   - the page write of the new rows, one workgroup per 16-token tile and group of up to HG KV heads: the descriptor
+//     (possibly in pinned host memory) is fetched once per group, and the row reads of all the group's heads are in
+//     flight together before the first head goes through LDS;
+//   - with ROPE the rotation of the key rows on that way (rotary position embedding, token position = pos0 of the tile's
+//     descriptor + token slot; same arithmetic as rope_kernel: fp64 angle reduced to [-pi, pi], fp32 rotation, one
+//     rounding to bf16; the rotated piece goes to the page and back to the caller's k row) and, in workgroups of their
+//     own, of the query rows of the same tiles;
+//   - of a chunked step the dense K, V rows that its attention kernel reads: the cached rows out of their pages, the new
+//     ones beside the page write;
+//   - the copy of the step's metadata to its device twin.
+// None of these reads what another writes (the cached and the new tokens of a page are different bytes of it), all are
+// bound by memory, and each is short: as launches of their own (page write, query rotation, gather of all rows, one
+// workgroup per tile and head) they waited for one another's tails and read the new rows back from the pages.
+// One MI355X, Llama-3-8B layer with RoPE, 4 pieces of 201 .. 1024 tokens behind 0 .. 7680 cached ones, 256 CUs: whole step
+// 171 -> 158 us; 3 prompts of 82 .. 633 tokens on 96 CUs beside a decode iteration: 58 -> 38 us.
+// Workgroups in order: n_copy copying metadata, the page write, the cached rows, the queries (the one part that nothing
+// but memory bounds comes last and fills what the others leave).
+struct RowsArgs {
+  char* base;
+  uint64_t page_bytes;
+  uint32_t head_bytes, tile_bytes, tile_k_bytes;
+  const TileDesc* descs;
+  const bf16_t *k, *v;
+  int Hkv, dk, dv, n_tiles, groups;
+  int n_copy;
+  uint4* copy_dst;
+  const uint4* copy_src;
+  uint64_t copy_n16;
+  const TileDesc* pre_descs;    // tiles of cached rows; src_row counts rows of k_all, v_all
+  int n_pre;
+  bf16_t *k_all, *v_all;        // null: not a chunked step
+  const double* w;              // [rot / 2] frequencies
+  bf16_t *k_rw, *q;             // k again, writable; q null: queries stay as they are
+  int H, q_groups;              // query heads, workgroups per tile (eight heads each)
+  int rot, off;                 // rotating entries per head, first rotating entry (multiples of 16 and 8)
   int interleaved;
+  StepMark mark;
 };
 
-__device__ inline float kv_bf_lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
-__device__ inline float kv_bf_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
-__device__ inline uint32_t kv_pack_bf16(float a, float b) {
-  typedef float f32x2_ __attribute__((ext_vector_type(2)));
-  typedef __bf16 bf16x2_ __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_{a, b}, bf16x2_));
-}
-
 template <int HG, bool ROPE>
-__global__ __launch_bounds__(256) void kv_write_heads_kernel(char* __restrict__ base, uint64_t page_bytes, uint32_t head_bytes,
-                                                             uint32_t tile_bytes, uint32_t tile_k_bytes,
-                                                             const TileDesc* __restrict__ descs, const bf16_t* __restrict__ k,
-                                                             const bf16_t* __restrict__ v, int Hkv, int dk, int dv, int n_tiles,
-                                                             uint4* __restrict__ copy_dst, const uint4* __restrict__ copy_src,
-                                                             uint64_t copy_n16, RopeFuse rp, StepMark mark) {
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) store_mark(mark);
-  if ((int)blockIdx.x >= n_tiles) {
-    const uint64_t blk = (uint64_t)(blockIdx.x - n_tiles) * gridDim.y + blockIdx.y;
-    const uint64_t stride = (uint64_t)(gridDim.x - n_tiles) * gridDim.y * blockDim.x;
-    for (uint64_t i = blk * blockDim.x + threadIdx.x; i < copy_n16; i += stride) copy_dst[i] = copy_src[i];
+__global__ __launch_bounds__(256) void kv_rows_kernel(RowsArgs a) {
+  const int i = threadIdx.x;
+  int blk = blockIdx.x;
+  if (blk < a.n_copy) {
+    for (uint64_t j = (uint64_t)blk * 256 + i; j < a.copy_n16; j += (uint64_t)a.n_copy * 256) a.copy_dst[j] = a.copy_src[j];
+    if (blk == 0 && i == 0) store_mark(a.mark);
     return;
   }
+  blk -= a.n_copy;
   __shared__ uint4 ks[TILE_T][16 + 1];              // dk <= 128: 16 pieces per token, one of padding
   __shared__ bf16_t vs[TILE_T][128 + 8];            // dv <= 128; 8 elements of padding per row
-  const TileDesc d = descs[blockIdx.x];
-  const int g0 = blockIdx.y * HG, ng = min(HG, Hkv - g0);
-  const int i = threadIdx.x;
-  const int ck_n = dk >> 3, cv_n = dv >> 3;         // 16-byte pieces per K row, per V row
+  const int ck_n = a.dk >> 3, cv_n = a.dv >> 3;     // 16-byte pieces per K row, per V row
+  const int v_items = (a.dv >> 5) * 64;             // 16-byte pieces of a tile's V part: (d / 32, token quad, d % 16)
+  // a piece in row order: token slot, piece of the row; in page order K has the token slots of a piece together
   const int tk = i / ck_n, ck = i % ck_n, tv = i / cv_n, cv = i % cv_n;
-  const bool k_ok = i < ck_n * TILE_T && tk >= d.t_begin && tk < d.t_end;
-  const bool v_ok = i < cv_n * TILE_T && tv >= d.t_begin && tv < d.t_end;
-  uint4 kr[HG], vr[HG];
-#pragma unroll
-  for (int g = 0; g < HG; ++g) {
-    kr[g] = vr[g] = uint4{0, 0, 0, 0};
-    if (g < ng && k_ok) kr[g] = load_once(k + ((size_t)(d.src_row + tk - d.t_begin) * Hkv + g0 + g) * dk + ck * 8);
-    if (g < ng && v_ok) vr[g] = load_once(v + ((size_t)(d.src_row + tv - d.t_begin) * Hkv + g0 + g) * dv + cv * 8);
-  }
-  const int v_items = (dv >> 5) * 64;
-  // the piece this thread carries to the page: token slot t_out, piece c_out of the row
   const int t_out = i & 15, c_out = i >> 4;
-  const bool out_ok = i < ck_n * TILE_T && t_out >= d.t_begin && t_out < d.t_end;
-  float cs[8], sn[8];
-  int partner = -1;                                  // half layout: the piece that holds the other entry of each pair
-  bool rotates = false, second = false;
-  if constexpr (ROPE) {
-    const int e0 = 8 * c_out - rp.off;               // the piece's first entry, counted from the rotating range's start
-    rotates = out_ok && e0 >= 0 && e0 < rp.rot;
-    if (rotates) {
-      const int half = rp.rot >> 1;
-      second = !rp.interleaved && e0 >= half;
-      partner = rp.interleaved ? c_out : (second ? c_out - (half >> 3) : c_out + (half >> 3));
-      const int pair0 = rp.interleaved ? (e0 >> 1) : (second ? e0 - half : e0);
-      const double p = (double)(d.pad[0] + t_out);
+  const int vm = i & 15, vc4 = (i >> 4) & 3, vblk = i >> 6;
+
+  if (blk < a.n_tiles * a.groups) {
+    const TileDesc d = a.descs[blk / a.groups];
+    const int g0 = blk % a.groups * HG, ng = min(HG, a.Hkv - g0);
+    const bool k_ok = i < ck_n * TILE_T && tk >= d.t_begin && tk < d.t_end;
+    const bool v_ok = i < cv_n * TILE_T && tv >= d.t_begin && tv < d.t_end;
+    uint4 kr[HG], vr[HG];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (rp.interleaved && j >= 4) break;
-        const double turns = p * rp.w[pair0 + j] * 0.15915494309189535;   // angle / 2 pi
-        const float r = (float)((turns - __builtin_rint(turns)) * 6.283185307179586);
-        sincosf(r, &sn[j], &cs[j]);
+    for (int g = 0; g < HG; ++g) {
+      kr[g] = vr[g] = uint4{0, 0, 0, 0};
+      if (g < ng && k_ok) kr[g] = load_once(a.k + ((size_t)(d.src_row + tk - d.t_begin) * a.Hkv + g0 + g) * a.dk + ck * 8);
+      if (g < ng && v_ok) vr[g] = load_once(a.v + ((size_t)(d.src_row + tv - d.t_begin) * a.Hkv + g0 + g) * a.dv + cv * 8);
+    }
+    if (blockIdx.x == 0 && i == 0) store_mark(a.mark);   // (no metadata to copy)
+    // the piece this thread carries to the page: token slot t_out, piece c_out of the row
+    const bool out_ok = i < ck_n * TILE_T && t_out >= d.t_begin && t_out < d.t_end;
+    float cs[8], sn[8];
+    int partner = -1;                                // half layout: the piece that holds the other entry of each pair
+    bool rotates = false, second = false;
+    if constexpr (ROPE) {
+      const int e0 = 8 * c_out - a.off;              // the piece's first entry, counted from the rotating range's start
+      rotates = out_ok && e0 >= 0 && e0 < a.rot;
+      if (rotates) {
+        const int half = a.rot >> 1;
+        second = !a.interleaved && e0 >= half;
+        partner = a.interleaved ? c_out : (second ? c_out - (half >> 3) : c_out + (half >> 3));
+        const int pair0 = a.interleaved ? (e0 >> 1) : (second ? e0 - half : e0);
+        const double p = (double)(d.pad[0] + t_out);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (a.interleaved && j >= 4) break;
+          const double turns = p * a.w[pair0 + j] * 0.15915494309189535;   // angle / 2 pi
+          const float r = (float)((turns - __builtin_rint(turns)) * 6.283185307179586);
+          sincosf(r, &sn[j], &cs[j]);
+        }
       }
     }
-  }
 #pragma unroll
-  for (int g = 0; g < HG; ++g) {
-    if (g >= ng) break;
-    char* tile = base + (uint64_t)d.page * page_bytes + (uint64_t)(g0 + g) * head_bytes + (uint64_t)d.sub * tile_bytes;
-    if (k_ok) ks[tk][ck] = kr[g];
-    if (v_ok) *(uint4*)&vs[tv][cv * 8] = vr[g];
-    __syncthreads();
-    // K part [chunk][token][8 dims]
-    if (out_ok) {
-      uint4 piece = ks[t_out][c_out];
-      if constexpr (ROPE) {
-        if (rotates) {
-          uint32_t x[4] = {piece.x, piece.y, piece.z, piece.w};
-          if (rp.interleaved) {                       // word j holds pair j: low half a, high half b
+    for (int g = 0; g < HG; ++g) {
+      if (g >= ng) break;
+      char* tile = a.base + (uint64_t)d.page * a.page_bytes + (uint64_t)(g0 + g) * a.head_bytes + (uint64_t)d.sub * a.tile_bytes;
+      if (k_ok) ks[tk][ck] = kr[g];
+      if (v_ok) *(uint4*)&vs[tv][cv * 8] = vr[g];
+      if (a.v_all && v_ok)
+        *(uint4*)(a.v_all + ((size_t)(d.pad[1] + tv - d.t_begin) * a.Hkv + g0 + g) * a.dv + cv * 8) = vr[g];
+      __syncthreads();
+      // K part [chunk][token][8 dims]
+      if (out_ok) {
+        uint4 piece = ks[t_out][c_out];
+        if constexpr (ROPE) {
+          if (rotates) {
+            uint32_t x[4] = {piece.x, piece.y, piece.z, piece.w};
+            if (a.interleaved) {                      // word j holds pair j: low half a, high half b
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const float xa = kv_bf_lo(x[j]), xb = kv_bf_hi(x[j]);
-              x[j] = kv_pack_bf16(xa * cs[j] - xb * sn[j], xb * cs[j] + xa * sn[j]);
+              for (int j = 0; j < 4; ++j) {
+                const float xa = rope_bf_lo(x[j]), xb = rope_bf_hi(x[j]);
+                x[j] = rope_pack(rope_a(xa, xb, cs[j], sn[j]), rope_b(xa, xb, cs[j], sn[j]));
+              }
+            } else {
+              const uint4 other = ks[t_out][partner];
+              const uint32_t y[4] = {other.x, other.y, other.z, other.w};
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                const float m0 = rope_bf_lo(x[j]), m1 = rope_bf_hi(x[j]), o0 = rope_bf_lo(y[j]), o1 = rope_bf_hi(y[j]);
+                // first half: mine is a (a cos - b sin); second half: mine is b (b cos + a sin)
+                x[j] = second ? rope_pack(rope_b(o0, m0, cs[2 * j], sn[2 * j]), rope_b(o1, m1, cs[2 * j + 1], sn[2 * j + 1]))
+                              : rope_pack(rope_a(m0, o0, cs[2 * j], sn[2 * j]), rope_a(m1, o1, cs[2 * j + 1], sn[2 * j + 1]));
+              }
             }
-          } else {
-            const uint4 other = ks[t_out][partner];
-            const uint32_t y[4] = {other.x, other.y, other.z, other.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const float m0 = kv_bf_lo(x[j]), m1 = kv_bf_hi(x[j]), o0 = kv_bf_lo(y[j]), o1 = kv_bf_hi(y[j]);
-              // first half: mine is a (a cos - b sin); second half: mine is b (b cos + a sin)
-              x[j] = second ? kv_pack_bf16(m0 * cs[2 * j] + o0 * sn[2 * j], m1 * cs[2 * j + 1] + o1 * sn[2 * j + 1])
-                            : kv_pack_bf16(m0 * cs[2 * j] - o0 * sn[2 * j], m1 * cs[2 * j + 1] - o1 * sn[2 * j + 1]);
-            }
+            piece = uint4{x[0], x[1], x[2], x[3]};
+            *(uint4*)(a.k_rw + ((size_t)(d.src_row + t_out - d.t_begin) * a.Hkv + g0 + g) * a.dk + c_out * 8) = piece;
           }
-          piece = uint4{x[0], x[1], x[2], x[3]};
-          *(uint4*)(rp.k_rw + ((size_t)(d.src_row + t_out - d.t_begin) * Hkv + g0 + g) * dk + c_out * 8) = piece;
+        }
+        store_once(tile + ((size_t)(c_out * 16 + t_out) << 4), piece);
+        if (a.k_all) *(uint4*)(a.k_all + ((size_t)(d.pad[1] + t_out - d.t_begin) * a.Hkv + g0 + g) * a.dk + c_out * 8) = piece;
+      }
+      // V part [d/32][token quad][d%16][(d/16)%2][4 tokens]
+      if (i < v_items) {
+        bf16_t* vt = (bf16_t*)(tile + a.tile_k_bytes);
+        bf16_t vals[8];
+        bool all = true;
+#pragma unroll
+        for (int par = 0; par < 2; ++par)
+#pragma unroll
+          for (int tt = 0; tt < 4; ++tt) {
+            const int t = 4 * vc4 + tt, dd = 32 * vblk + 16 * par + vm;
+            const bool ok = t >= d.t_begin && t < d.t_end;
+            all = all && ok;
+            vals[par * 4 + tt] = ok ? vs[t][dd] : (bf16_t)0;
+          }
+        bf16_t* dst = vt + ((size_t)((vblk * 4 + vc4) * 16 + vm) << 3);
+        if (all) {
+          uint4 pk;
+          pk.x = vals[0] | ((uint32_t)vals[1] << 16);
+          pk.y = vals[2] | ((uint32_t)vals[3] << 16);
+          pk.z = vals[4] | ((uint32_t)vals[5] << 16);
+          pk.w = vals[6] | ((uint32_t)vals[7] << 16);
+          store_once(dst, pk);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int t = 4 * vc4 + (e & 3);
+            if (t >= d.t_begin && t < d.t_end) dst[e] = vals[e];
+          }
         }
       }
-      store_once(tile + ((size_t)(c_out * 16 + t_out) << 4), piece);
+      __syncthreads();
     }
-    // V part [d/32][token quad][d%16][(d/16)%2][4 tokens]
-    if (i < v_items) {
-      bf16_t* vt = (bf16_t*)(tile + tile_k_bytes);
-      const int m = i & 15, c4 = (i >> 4) & 3, blk2 = i >> 6;
-      bf16_t vals[8];
-      bool all = true;
+    return;
+  }
+  blk -= a.n_tiles * a.groups;
+
+  if (blk < a.n_pre * a.groups) {
+    // cached rows: the tile's pieces of all the group's heads at once, each head turned round in LDS and stored as rows
+    const TileDesc d = a.pre_descs[blk / a.groups];
+    const int g0 = blk % a.groups * HG, ng = min(HG, a.Hkv - g0);
+    const bool k_in = i < ck_n * TILE_T, v_in = i < v_items;
+    uint4 kr[HG], vr[HG];
 #pragma unroll
-      for (int par = 0; par < 2; ++par)
+    for (int g = 0; g < HG; ++g) {
+      const char* tile = a.base + (uint64_t)d.page * a.page_bytes + (uint64_t)(g0 + g) * a.head_bytes + (uint64_t)d.sub * a.tile_bytes;
+      kr[g] = vr[g] = uint4{0, 0, 0, 0};
+      if (g < ng && k_in) kr[g] = load_once(tile + ((size_t)i << 4));
+      if (g < ng && v_in) vr[g] = load_once(tile + a.tile_k_bytes + ((size_t)i << 4));
+    }
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-          const int t = 4 * c4 + tt, dd = 32 * blk2 + 16 * par + m;
-          const bool ok = t >= d.t_begin && t < d.t_end;
-          all = all && ok;
-          vals[par * 4 + tt] = ok ? vs[t][dd] : (bf16_t)0;
-        }
-      bf16_t* dst = vt + ((size_t)((blk2 * 4 + c4) * 16 + m) << 3);
-      if (all) {
-        uint4 pk;
-        pk.x = vals[0] | ((uint32_t)vals[1] << 16);
-        pk.y = vals[2] | ((uint32_t)vals[3] << 16);
-        pk.z = vals[4] | ((uint32_t)vals[5] << 16);
-        pk.w = vals[6] | ((uint32_t)vals[7] << 16);
-        store_once(dst, pk);
-      } else {
+    for (int g = 0; g < HG; ++g) {
+      if (g >= ng) break;
+      if (k_in) ks[t_out][c_out] = kr[g];
+      if (v_in) {
+        const uint32_t x[4] = {vr[g].x, vr[g].y, vr[g].z, vr[g].w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int t = 4 * c4 + (e & 3);
-          if (t >= d.t_begin && t < d.t_end) dst[e] = vals[e];
-        }
+        for (int e = 0; e < 8; ++e)                   // element e = (d / 16) % 2 * 4 + token % 4
+          vs[4 * vc4 + (e & 3)][32 * vblk + 16 * (e >> 2) + vm] = (bf16_t)(x[e >> 1] >> (16 * (e & 1)));
+      }
+      __syncthreads();
+      if (k_in && tk >= d.t_begin && tk < d.t_end)
+        *(uint4*)(a.k_all + ((size_t)(d.src_row + tk - d.t_begin) * a.Hkv + g0 + g) * a.dk + ck * 8) = ks[tk][ck];
+      if (i < cv_n * TILE_T && tv >= d.t_begin && tv < d.t_end)
+        *(uint4*)(a.v_all + ((size_t)(d.src_row + tv - d.t_begin) * a.Hkv + g0 + g) * a.dv + cv * 8) = *(const uint4*)&vs[tv][cv * 8];
+      __syncthreads();
+    }
+    return;
+  }
+  blk -= a.n_pre * a.groups;
+
+  if constexpr (ROPE) {
+    // queries, eight heads per workgroup: a thread owns 8 pairs (two pieces) of one token in up to four heads, all on
+    // their way before it computes the angles
+    constexpr int QB = 8, MAXIT = 4;                  // dk <= 128: at most 128 threads per head, so at least two heads at once
+    const TileDesc d = a.descs[blk / a.q_groups];
+    const int pg = a.rot >> 4, par = 256 / (pg * TILE_T), half = a.rot >> 1;
+    const int pr = i % pg, t = i / pg % TILE_T, hs = i / (pg * TILE_T);
+    if (hs >= par || t < d.t_begin || t >= d.t_end) return;
+    const int h0 = blk % a.q_groups * QB, nh = min(QB, a.H - h0);
+    const int e0 = a.interleaved ? 16 * pr : 8 * pr;  // first entry of the pieces, counted from the rotating range's start
+    const int step = a.interleaved ? 8 : half;        // ... of the second one, from the first
+    bf16_t* row = a.q + ((size_t)(d.src_row + t - d.t_begin) * a.H + h0) * a.dk + a.off + e0;
+    uint4 A[MAXIT], B[MAXIT];
+#pragma unroll
+    for (int n = 0; n < MAXIT; ++n) {
+      const int h = hs + n * par;
+      if (h < nh) {
+        A[n] = *(const uint4*)(row + h * a.dk);
+        B[n] = *(const uint4*)(row + h * a.dk + step);
       }
     }
-    __syncthreads();
+    float cs[8], sn[8];
+    const double p = (double)(d.pad[0] + t);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const double turns = p * a.w[8 * pr + j] * 0.15915494309189535;   // angle / 2 pi
+      const float r = (float)((turns - __builtin_rint(turns)) * 6.283185307179586);
+      sincosf(r, &sn[j], &cs[j]);
+    }
+#pragma unroll
+    for (int n = 0; n < MAXIT; ++n) {
+      const int h = hs + n * par;
+      if (h < nh) {
+        rope_rotate_pieces(A[n], B[n], a.interleaved != 0, cs, sn);
+        *(uint4*)(row + h * a.dk) = A[n];
+        *(uint4*)(row + h * a.dk + step) = B[n];
+      }
+    }
   }
 }
 
@@ -497,33 +593,43 @@ hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const St
   return hipGetLastError();
 }
 
-bool kv_write_can_rotate(const PoolGeom& g) {
-  return g.kind == SPD_KV_GQA && g.dk <= 128 && g.dv <= 128 && g.Hkv >= 2;
+bool kv_rows_supported(const PoolGeom& g) { return g.kind == SPD_KV_GQA && g.dk <= 128 && g.dv <= 128 && g.Hkv >= 2; }
+
+hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k, const void* v,
+                          const KvRows& x, const StepMark& mark, hipStream_t stream) {
+  constexpr int HG = 8;
+  RowsArgs a{};
+  a.base = pool_base;
+  a.page_bytes = g.page_bytes; a.head_bytes = g.head_bytes; a.tile_bytes = g.tile_bytes; a.tile_k_bytes = g.tile_k_bytes;
+  a.descs = d_tiles; a.k = (const bf16_t*)k; a.v = (const bf16_t*)v;
+  a.Hkv = g.Hkv; a.dk = g.dk; a.dv = g.dv; a.n_tiles = n_tiles; a.groups = (g.Hkv + HG - 1) / HG;
+  a.copy_dst = (uint4*)x.copy_dst; a.copy_src = (const uint4*)x.copy_src;
+  a.copy_n16 = x.copy_dst ? (x.copy_bytes + 15) / 16 : 0;
+  a.n_copy = (int)std::min<uint64_t>(16ull * g.Hkv, (a.copy_n16 + 255) / 256);
+  a.pre_descs = x.d_cached; a.n_pre = x.n_cached; a.k_all = (bf16_t*)x.k_all; a.v_all = (bf16_t*)x.v_all;
+  a.w = x.rope_w; a.k_rw = (bf16_t*)const_cast<void*>(k); a.rot = x.rot; a.off = x.off; a.interleaved = x.interleaved ? 1 : 0;
+  a.mark = mark;
+  if (x.rope_w && x.q) {
+    a.q = (bf16_t*)x.q; a.H = x.n_q_heads; a.q_groups = (a.H + 7) / 8;
+  }
+  const int64_t blocks = a.n_copy + ((int64_t)n_tiles + a.n_pre) * a.groups + (int64_t)n_tiles * a.q_groups;
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > INT32_MAX) return hipErrorInvalidValue;
+  if (x.rope_w) hipLaunchKernelGGL((kv_rows_kernel<HG, true>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL((kv_rows_kernel<HG, false>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_kv_write(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k,
-                           const void* v, const StepMark& mark, hipStream_t stream, void* copy_dst, const void* copy_src, uint64_t copy_bytes,
-                           const double* rope_w, int rot, int rot_off, bool interleaved) {
+                           const void* v, const StepMark& mark, hipStream_t stream, void* copy_dst, const void* copy_src, uint64_t copy_bytes) {
+  if (kv_rows_supported(g) && v != nullptr) {
+    KvRows x;
+    x.copy_dst = copy_dst; x.copy_src = copy_src; x.copy_bytes = copy_bytes;
+    return launch_kv_rows(g, pool_base, d_tiles, n_tiles, k, v, x, mark, stream);
+  }
   const uint64_t n16 = copy_dst ? (copy_bytes + 15) / 16 : 0;
   const int copy_cols = n16 ? (int)std::min<uint64_t>(16, (n16 + 256ull * g.Hkv - 1) / (256ull * g.Hkv)) : 0;
   if (n_tiles <= 0 && copy_cols == 0) return hipSuccess;
-  if (g.kind == SPD_KV_GQA && v != nullptr && g.dk <= 128 && g.dv <= 128 && g.Hkv >= 2) {
-    constexpr int HG = 8;
-    const int groups = (g.Hkv + HG - 1) / HG;
-    // the metadata copy keeps its share of workgroups: copy_cols x Hkv of them before, the same number now
-    const int cols = copy_cols ? (copy_cols * g.Hkv + groups - 1) / groups : 0;
-    RopeFuse rp{rope_w, (bf16_t*)const_cast<void*>(k), rot, rot_off, interleaved ? 1 : 0};
-    if (rope_w)
-      hipLaunchKernelGGL((kv_write_heads_kernel<HG, true>), dim3(n_tiles + cols, groups), dim3(256), 0, stream, pool_base,
-                         g.page_bytes, g.head_bytes, g.tile_bytes, g.tile_k_bytes, d_tiles, (const bf16_t*)k, (const bf16_t*)v,
-                         g.Hkv, g.dk, g.dv, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, rp, mark);
-    else
-      hipLaunchKernelGGL((kv_write_heads_kernel<HG, false>), dim3(n_tiles + cols, groups), dim3(256), 0, stream, pool_base,
-                         g.page_bytes, g.head_bytes, g.tile_bytes, g.tile_k_bytes, d_tiles, (const bf16_t*)k, (const bf16_t*)v,
-                         g.Hkv, g.dk, g.dv, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, rp, mark);
-    return hipGetLastError();
-  }
-  if (rope_w) return hipErrorInvalidValue;          // callers ask kv_write_can_rotate first
   hipLaunchKernelGGL(kv_write_kernel, dim3(n_tiles + copy_cols, g.Hkv), dim3(256), 0, stream, pool_base, g.page_bytes,
                      g.head_bytes, g.tile_bytes, g.tile_k_bytes, d_tiles, (const bf16_t*)k, (const bf16_t*)v, g.Hkv, g.dk,
                      g.dv, g.kind == SPD_KV_MLA_LATENT ? 1 : 0, n_tiles, (uint4*)copy_dst, (const uint4*)copy_src, n16, mark);

@@ -13,17 +13,9 @@
 // angle in fp64 (p * w reaches 1e5 rad, fp32 would lose the low bits that matter), reduced to
 // [-pi, pi], then the fp32 library sine / cosine.
 #include "internal.h"
+#include "rope_device.h"
 
 namespace spd {
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-__device__ inline float bf_lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
-__device__ inline float bf_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
-__device__ inline uint32_t pack_bf16(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
-}
 
 struct RopeArgs {
   unsigned short* x[2];   // q, k (k may be null)
@@ -67,27 +59,9 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
   unsigned short* row = a.x[which] + ((size_t)t * a.heads[which] + h0) * a.dim;
   for (int h = h0; h < h1; ++h, row += a.dim) {
     uint4 A = *(const uint4*)(row + ea), B = *(const uint4*)(row + eb);
-    uint32_t aw[4] = {A.x, A.y, A.z, A.w}, bw[4] = {B.x, B.y, B.z, B.w};
-    if (INTERLEAVED) {
-      // word j of A holds pair j (low half = a, high half = b); word j of B holds pair 4 + j
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float xa = bf_lo(aw[j]), xb = bf_hi(aw[j]);
-        aw[j] = pack_bf16(xa * cs[j] - xb * sn[j], xb * cs[j] + xa * sn[j]);
-        const float ya = bf_lo(bw[j]), yb = bf_hi(bw[j]);
-        bw[j] = pack_bf16(ya * cs[4 + j] - yb * sn[4 + j], yb * cs[4 + j] + ya * sn[4 + j]);
-      }
-    } else {
-      // entry e of A pairs with entry e of B
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float a0 = bf_lo(aw[j]), a1 = bf_hi(aw[j]), b0 = bf_lo(bw[j]), b1 = bf_hi(bw[j]);
-        aw[j] = pack_bf16(a0 * cs[2 * j] - b0 * sn[2 * j], a1 * cs[2 * j + 1] - b1 * sn[2 * j + 1]);
-        bw[j] = pack_bf16(b0 * cs[2 * j] + a0 * sn[2 * j], b1 * cs[2 * j + 1] + a1 * sn[2 * j + 1]);
-      }
-    }
-    *(uint4*)(row + ea) = uint4{aw[0], aw[1], aw[2], aw[3]};
-    *(uint4*)(row + eb) = uint4{bw[0], bw[1], bw[2], bw[3]};
+    rope_rotate_pieces(A, B, INTERLEAVED, cs, sn);
+    *(uint4*)(row + ea) = A;
+    *(uint4*)(row + eb) = B;
   }
 }
 
