@@ -56,7 +56,6 @@ template <int MB, int WNW>
 __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                                    bf16_t* __restrict__ out, int T, int K, int I, int tiles_m,
                                                                    int tiles_n, int xcds, StepMark mark) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
   constexpr int NSTAGE = 4, WAVES = 2 * WNW, BM = 64 * MB, BNP = 64 * WNW, PD = NSTAGE - 1;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BNP * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
   constexpr int A_LOADS = A_BYTES / 1024, B_LOADS = B_BYTES / 1024, LPW = (A_LOADS + B_LOADS) / WAVES;   // 1 KiB load instructions (per wave)
@@ -213,6 +212,10 @@ __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t*
     step(ct, o0, o1);
     if (ct + 1 < n_slices) step(ct + 1, o1, o0);
   }
+
+  // (ahead of the loop this branch shifts the loop by four bytes against the lines its instructions are fetched in: 2402 us
+  // instead of 2384 at 8192 tokens of hidden 4096, inter 14336 on 128 CUs; workgroup 0 is among the first to get here)
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
 
   // ---- activation and store: lanes 0..31 of a store hold 32 consecutive outputs of one token
   const int col = tn * (BNP / 2) + wn * 32 + n32;
