@@ -243,9 +243,8 @@ int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_batch* batc
  * must be positive and finite.
  * With `rope` non-NULL (declared further down; paper, Evaluation "Implementation based on
  * DistServe": the RoPE kernel) q and k_new are the vectors BEFORE the rotary embedding: the step
- * rotates request b's query and new key by position ctx_lens[b] - 1, the query into a library
- * workspace (the caller's q, k_new are left as they are), the key straight into the page, in the one
- * launch that appends; the attention then reads the rotated query.  The rotating range must fit the
+ * rotates request b's query and new key by position ctx_lens[b] - 1 in the attention launch, the key
+ * on its way into the page (the caller's q, k_new are left as they are).  The rotating range must fit the
  * head (rotary_offset + rotary_dim <= dim_k; multiples of 8 and 16) or the call is SPD_EINVAL. */
 typedef struct {
   int32_t n_req;
@@ -266,7 +265,7 @@ int spd_decode_step(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch* batch)
  * results as spd_decode_step, but the call allocates and frees nothing on the device or in pinned
  * memory (no hipMalloc / hipHostMalloc / hipFree, no event or stream creation): the device twin of
  * the step's metadata (context lengths, block tables, work items, append descriptors, RoPE
- * frequencies) and the workspace (split-K partials, rotated queries) lie in a static device array of
+ * frequencies) and the workspace (split-K partials) lie in a static device array of
  * 33 MiB that every GPU the library runs on holds from the library's load to the end of the process
  * (its address is resolved once per device in spd_ctx_create), and the pinned staging ring is the one
  * spd_ctx_create made.  Limits (spd_noalloc_limits): 256 KiB of metadata per step, i.e.

@@ -124,7 +124,7 @@ struct PrefillWork {
 
 // The entry point that allocates nothing keeps its device-side working memory in one static device
 // array (noalloc.hip): four metadata twins (one per slot of the decode phase's staging ring), then the
-// split-K partials and the rotated queries.
+// split-K partials.
 constexpr size_t NOALLOC_STAGE_BYTES = 256u << 10;
 constexpr size_t NOALLOC_WS_BYTES = 32u << 20;
 // pinned bytes of a staging slot of the decode phase: the metadata of any batch within NOALLOC_STAGE_BYTES (which

@@ -16,7 +16,7 @@
 //   S^T[key, query] = K_tile[16 x d] . Q^T[d x 16]       v_mfma_f32_16x16x32_bf16, d/32 steps
 //   O^T[dim, query] += V_tile^T[16 x 16] . P^T[16 x 16]  v_mfma_f32_16x16x16_bf16, d/16 blocks
 // Long contexts are split into chunks (split-K); partial (max, sum, O) triples go to a
-// workspace and a small second kernel merges them.
+// workspace and are merged by the launch itself or by a small second kernel (split_merge.h).
 #include "internal.h"
 #include "rope_device.h"
 #include "split_merge.h"
