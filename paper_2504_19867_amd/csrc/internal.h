@@ -289,7 +289,10 @@ hipError_t launch_kv_gather_fp8(const PoolGeom& g, const char* pool_base, const 
 hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const StepMark& mark, hipStream_t stream);
 hipError_t launch_decode_gqa(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream);
 hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream);
-constexpr int MLA_CHUNK_PAGES = 252;      // pages a chunk of the latent decode may touch (the workgroup keeps their ids in LDS)
+// The latent decode's workgroup fetches a record one word per thread and keeps it in LDS: as many pages as that leaves a chunk
+// may touch, and no record may be longer (checked again at the launch).
+constexpr int MLA_THREADS = 256;
+constexpr int MLA_CHUNK_PAGES = MLA_THREADS - DECODE_ITEM_WORDS;
 // one workgroup per chain: workgroup b computes the items d_work[d_chain[b]] .. d_work[d_chain[b + 1] - 1]
 hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillWork* d_work,
                           const int32_t* d_chain, int n_blocks, int H, int Hkv, int dqk, int dv, float scale,

@@ -54,7 +54,7 @@ constexpr int DV = 512;               // leading dims that act as values
 constexpr int ROW_BYTES = DL * 2;     // 1152
 constexpr int CH = DL / 8;            // 72 16-byte chunks per row
 constexpr int TILE = 16;              // tokens per tile
-constexpr int WAVES = 4;
+constexpr int WAVES = MLA_THREADS / 64;
 constexpr int KS = DL / 32;           // 18 k-steps of the score product
 constexpr int VB = DV / 16;           // 32 value blocks of 16 dims
 constexpr int HALF_PITCH = DV / 2 + 4;   // floats per (wave, head) of a half of O in the merge, padded
@@ -107,7 +107,7 @@ template <bool HI> __device__ inline uint32_t mla_codes_to_bf16(uint32_t w) {
   return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, HI));
 }
 
-// grid (n_items), block 256: one workgroup per work item = (request, chunk of chunk_tiles tiles).
+// grid (n_wgs), block 256: workgroup i computes the chunk of record i, then those its record's `next` leads to.
 template <bool FP8>
 __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs a) {
   using namespace mla;
@@ -116,10 +116,11 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
   __shared__ float sm_m[WAVES + 1][16], sm_l[WAVES][16];
   __shared__ float sm_cs[128], sm_sn[128];         // rotary_dim <= 256
-  __shared__ int32_t sm_rec[DECODE_ITEM_WORDS + MLA_CHUNK_PAGES];
+  __shared__ int32_t sm_rec[64 * WAVES];           // header and page ids, a word per thread
   __shared__ __attribute__((aligned(16))) char sm_new[ROW_BYTES];
   __shared__ uint32_t sm_last;
   if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(a.mark);
+  static_assert(DECODE_ITEM_WORDS + MLA_CHUNK_PAGES <= 64 * WAVES, "one thread per word of a record");
   const int words = a.item_stride >> 2;
   // Two workgroups per compute unit share the batch's tiles evenly, so a workgroup may go from one request's last tiles to
   // the next one's first: its chain of chunks
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, c4 = lane >> 4;       // col: head (B operand / accumulator column) or token (A operand row)
   // the record (header, page ids) once per workgroup: it may lie in pinned host memory
-  const bool has_word = tid < min(words, DECODE_ITEM_WORDS + MLA_CHUNK_PAGES);
+  const bool has_word = tid < words;
   if (first && has_word) rec_word = ((const int32_t*)(a.items + (size_t)idx * a.item_stride))[tid];
   if (has_word) sm_rec[tid] = rec_word;
   __syncthreads();
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   const int page0 = tile0 / a.tiles_per_page;
   auto tile_addr = [&](int t) -> char* {           // t: tile of the chunk
     const int gt = tile0 + t, pg = gt / a.tiles_per_page;
-    const int page = __builtin_amdgcn_readfirstlane(sm_rec[pg - page0 + DECODE_ITEM_WORDS]);      // (MLA_CHUNK_PAGES fit the record's copy)
+    const int page = __builtin_amdgcn_readfirstlane(sm_rec[pg - page0 + DECODE_ITEM_WORDS]);
     return a.pool + (uint64_t)(uint32_t)page * a.page_bytes + (uint32_t)(gt - pg * a.tiles_per_page) * (uint32_t)TB;
   };
 
@@ -503,6 +504,7 @@ hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLau
   a.pool = pool_base; a.page_bytes = g.page_bytes; a.tiles_per_page = g.P / mla::TILE;
   a.q = (const bf16_t*)d.q; a.k_new = (const bf16_t*)d.k_new; a.out = (bf16_t*)d.out;
   a.items = d.items; a.item_stride = d.item_stride; a.H = d.H;
+  if (d.item_stride > 4 * MLA_THREADS) return hipErrorInvalidValue;    // words that the workgroup would not fetch
   a.c = d.scale * 1.4426950408889634f;
   a.max_chunks = d.max_chunks;
   a.w = d.w; a.rot = d.rot; a.off = d.off; a.interleaved = d.interleaved;

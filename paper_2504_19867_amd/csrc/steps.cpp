@@ -2,6 +2,7 @@
 // reservation, block-table staging, launch geometry.  All arithmetic of the method runs in
 // the kernels (kernels_*.hip).
 #include "internal.h"
+#include "decode_split.h"
 #include "prefill_work.h"
 #include "split_merge.h"
 
@@ -10,7 +11,6 @@
 
 #include <algorithm>
 #include <atomic>
-#include <functional>
 #include <new>
 #include <thread>
 #include <cmath>
@@ -322,111 +322,6 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
 }
 
 // ------------------------------------------------------------------------------------------ decode
-// How the step's contexts are split over workgroups, in units of 16 tokens.
-struct DecodeSplit {
-  int n_wgs = 0, max_chunks = 1;
-  int32_t chunk_units = 0;       // largest chunk
-};
-
-static inline void push_chunk(std::vector<DecodeItem>& items, int r, int32_t chunk, int32_t n, int32_t u0, int32_t nu) {
-  items.push_back(DecodeItem{r, chunk, 0, n, u0, nu, -1, 0});
-}
-
-// Chunks of c units, handed out longest first: the full chunks, request by request, then the requests' remainders by length.
-static void cut_chunks(spd_phase_state& ps, const int32_t* ctx_lens, int B, int max_units, int64_t c, int32_t* n_chunks, DecodeSplit& out) {
-  out.chunk_units = (int32_t)c;
-  out.max_chunks = (int)((max_units + c - 1) / c);
-  std::vector<DecodeItem>& items = ps.tmp_items;
-  std::vector<uint64_t>& rest = ps.tmp_set;                      // (units << 32 | request)
-  items.clear();
-  rest.clear();
-  for (int r = 0; r < B; ++r) {
-    const int32_t units = (ctx_lens[r] + TILE_T - 1) / TILE_T, full = units / (int32_t)c;
-    n_chunks[r] = (int32_t)((units + c - 1) / c);
-    for (int32_t ck = 0; ck < full; ++ck) push_chunk(items, r, ck, ctx_lens[r], ck * (int32_t)c, (int32_t)c);
-    if (units % c) rest.push_back((uint64_t)(units % c) << 32 | (uint32_t)(B - 1 - r));   // equal lengths: request order
-  }
-  std::sort(rest.begin(), rest.end(), std::greater<uint64_t>());
-  for (uint64_t k : rest) {
-    const int r = B - 1 - (int)(uint32_t)k;
-    push_chunk(items, r, n_chunks[r] - 1, ctx_lens[r], (n_chunks[r] - 1) * (int32_t)c, (int32_t)(k >> 32));
-  }
-  out.n_wgs = (int)items.size();
-}
-
-// GQA: about 6 workgroups per CU of the decode share: enough to balance unequal contexts, few enough to keep the split-K
-// partials small.
-static void split_gqa(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t sum_units, int max_units, int Hkv, int cus, int override_tiles,
-                      int32_t* n_chunks, DecodeSplit& out) {
-  const int64_t round = 8;                       // 4 waves x 2 tiles per step
-  int64_t c;
-  if (override_tiles > 0) {                      // tuning override
-    c = (override_tiles + round - 1) / round * round;
-  } else {
-    const int64_t per_head_chunks = std::max<int64_t>(1, (int64_t)cus * 6 / std::max(1, Hkv));
-    c = (sum_units + per_head_chunks - 1) / per_head_chunks;
-    c = std::min<int64_t>(std::max<int64_t>((c + round - 1) / round * round, 16), 1 << 20);
-  }
-  cut_chunks(ps, ctx_lens, B, max_units, std::min<int64_t>(c, (max_units + round - 1) / round * round), n_chunks, out);
-}
-
-// Latent decode: two workgroups per CU are resident, and the batch's units are dealt to them evenly, in request order, a
-// workgroup going on from one request's end to the next one's beginning.  (Chunks of one length, handed out longest first, left
-// a quarter of the slots idle at the end.)  A chunk costs its pipeline fill and its merge beside its tiles, about as
-// much as CHUNK_COST tiles; chunks are whole rounds of the four waves, except at a request's end.
-static void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t sum_units, int cus, int units_per_page, int override_units,
-                         int32_t* n_chunks, DecodeSplit& out) {
-  constexpr int64_t CHUNK_COST = 20, ROUND = 4;
-  const int64_t slots = std::max(1, 2 * cus), most = (int64_t)(MLA_CHUNK_PAGES - 1) * units_per_page / ROUND * ROUND;
-  std::vector<DecodeItem>& items = ps.tmp_items;
-  std::vector<int32_t>& owner = ps.tmp_sizes;                    // workgroup of each chunk
-  // at least two tiles per wave
-  int64_t quota = CHUNK_COST + (override_units > 0 ? override_units : std::max<int64_t>(2 * ROUND, (sum_units + B * CHUNK_COST) / slots));
-  for (;; quota += std::max<int64_t>(1, quota / 64)) {
-    const int64_t sliver = std::min<int64_t>((quota - CHUNK_COST) / 4, 4);
-    items.clear();
-    owner.clear();
-    int wg = 0;
-    int64_t room = quota;
-    out.chunk_units = 0;
-    out.max_chunks = 1;
-    for (int r = 0; r < B; ++r) {
-      const int32_t units = (ctx_lens[r] + TILE_T - 1) / TILE_T;
-      int32_t u0 = 0, chunk = 0;
-      while (u0 < units) {
-        const int64_t left = units - u0;
-        if (room < quota && room - CHUNK_COST <= sliver && left > room - CHUNK_COST) { ++wg; room = quota; }   // too little room to start here
-        int64_t take = std::min<int64_t>(left, std::max<int64_t>(ROUND, (room - CHUNK_COST) / ROUND * ROUND));
-        if (left > take && left - take <= sliver) take = left;                  // too little left to start elsewhere
-        take = std::min(take, most);
-        push_chunk(items, r, chunk++, ctx_lens[r], u0, (int32_t)take);
-        owner.push_back(wg);
-        out.chunk_units = std::max(out.chunk_units, (int32_t)take);
-        u0 += (int32_t)take;
-        room -= CHUNK_COST + take;
-        if (room < CHUNK_COST + ROUND) { ++wg; room = quota; }
-      }
-      n_chunks[r] = chunk;
-      out.max_chunks = std::max(out.max_chunks, (int)chunk);
-    }
-    out.n_wgs = owner.back() + 1;
-    if (out.n_wgs <= slots || override_units > 0) break;
-  }
-  // workgroup i starts with record i: first chunks to the front, the others behind them, linked
-  const int n = (int)items.size();
-  std::vector<DecodeItem>& sorted = ps.tmp_items2;
-  sorted.resize((size_t)n);
-  int behind = out.n_wgs, prev = 0;
-  for (int i = 0; i < n; ++i) {
-    const bool first = i == 0 || owner[(size_t)i] != owner[(size_t)i - 1];
-    const int at = first ? owner[(size_t)i] : behind++;
-    sorted[(size_t)at] = items[(size_t)i];
-    if (!first) sorted[(size_t)prev].next = at;
-    prev = at;
-  }
-  items.swap(sorted);
-}
-
 // noalloc: the variant that allocates nothing.  The metadata's device twin and the workspace lie in the static scratch
 // array, the staging ring is used as spd_ctx_create made it, no timing events are recorded.
 static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch* b, bool noalloc) {
