@@ -264,16 +264,19 @@ int spd_decode_step(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch* batch)
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical
  * results as spd_decode_step, but the call allocates and frees nothing on the device or in pinned
  * memory (no hipMalloc / hipHostMalloc / hipFree, no event or stream creation): the device twin of
- * the step's metadata (context lengths, block tables, work items, append descriptors, RoPE
- * frequencies) and the workspace (split-K partials) lie in a static device array of
+ * the step's metadata (work items with their page ids) and the workspace (split-K partials) lie in a
+ * static device array of
  * 33 MiB that every GPU the library runs on holds from the library's load to the end of the process
  * (its address is resolved once per device in spd_ctx_create), and the pinned staging ring is the one
- * spd_ctx_create made.  Limits (spd_noalloc_limits): 256 KiB of metadata per step, i.e.
- * 4 n_req (1 + pages of the longest context) + 8 work items + 32 n_req (append) bytes, and 32 MiB of
- * workspace, i.e. 4 n_req n_q_heads chunks (dim_v + 2) + 2 n_req n_q_heads dim_k (rope) bytes, where
- * chunks is the split-K count the library picks (about 6 workgroups per compute unit of the decode
- * share).  A batch beyond either limit is refused with SPD_ETOOBIG and nothing is enqueued.  Kernel
- * timing (spd_set_kernel_timing) is not recorded for these steps.
+ * spd_ctx_create made.  Limits (spd_noalloc_limits): 256 KiB of metadata per step, counted as
+ * 4 n_req (1 + pages of the longest context) + 8 work items + 32 n_req (append) + 4 rotary_dim (rope)
+ * bytes, and 32 MiB of workspace, i.e. 4 n_req n_q_heads chunks (dim_v + 2) bytes where a context is
+ * split at all.  Work items are the chunks of all contexts, `chunks` those of the longest one.  On GQA
+ * pools the library aims at six workgroups per compute unit of the decode share; on latent pools
+ * two workgroups per compute unit share the batch evenly, and where that would break a limit this
+ * call makes the chunks longer, up to 247 pages (the result then equals spd_decode_step's within
+ * rounding, not bit for bit).  A batch beyond either limit is refused with SPD_ETOOBIG and nothing is
+ * enqueued.  Kernel timing (spd_set_kernel_timing) is not recorded for these steps.
  * The array is shared by every context and every call on that GPU and keeps the last call's contents
  * (nothing in it has to start at zero: each step writes every partial it later reads).  Steps of one
  * decode phase run in stream order and may follow one another freely, also mixed with spd_decode_step;

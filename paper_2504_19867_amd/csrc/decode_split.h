@@ -12,7 +12,34 @@ namespace spd {
 struct DecodeSplit {
   int n_wgs = 0, max_chunks = 1;
   int32_t chunk_units = 0;       // largest chunk
+  int64_t dealt = 0;             // latent: units that a workgroup was dealt, its chunks' cost included
 };
+
+// The step's metadata as the kernels read it: a record per item (header and page ids; a chunk that starts inside a page
+// touches one more than it holds), then the requests' chunk counts.
+struct DecodeRecords {
+  size_t stride = 0, off_chunks = 0, bytes = 0;
+};
+inline DecodeRecords decode_records(const DecodeSplit& sp, int n_items, int B, int max_pages, int units_per_page) {
+  DecodeRecords d;
+  const size_t chunk_pages = (size_t)std::min<int64_t>(max_pages, ((int64_t)sp.chunk_units + units_per_page - 2) / units_per_page + 1);
+  d.stride = (sizeof(DecodeItem) + sizeof(int32_t) * chunk_pages + 63) & ~(size_t)63;
+  d.off_chunks = d.stride * (size_t)n_items;
+  d.bytes = (d.off_chunks + sizeof(int32_t) * (size_t)B + 15) & ~(size_t)15;
+  return d;
+}
+// What the metadata limit of the entry point that allocates nothing counts: one block table row per request, the items, the
+// appends, the RoPE frequencies.  Any batch within it fits a staging slot of NOALLOC_RING_BYTES in the form above.
+inline size_t noalloc_metadata(int n_items, int B, int max_pages, bool append, size_t w_bytes) {
+  return sizeof(int32_t) * (size_t)B * (1 + (size_t)max_pages) + 8 * (size_t)n_items + (append ? sizeof(TileDesc) * (size_t)B : 0) + w_bytes;
+}
+// Split-K partials: O of every (request, head, chunk), then its maximum and sum.
+inline size_t partial_o_bytes(int B, int H, int max_chunks, int dv) {
+  return max_chunks > 1 ? (sizeof(float) * (size_t)B * H * max_chunks * dv + 15) & ~(size_t)15 : 0;
+}
+inline size_t partial_ml_bytes(int B, int H, int max_chunks) {
+  return max_chunks > 1 ? (sizeof(float) * (size_t)B * H * max_chunks * 2 + 15) & ~(size_t)15 : 0;
+}
 
 inline void push_chunk(std::vector<DecodeItem>& items, int r, int32_t chunk, int32_t n, int32_t u0, int32_t nu) {
   items.push_back(DecodeItem{r, chunk, 0, n, u0, nu, -1, 0});
@@ -59,15 +86,17 @@ inline void split_gqa(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64
 // Latent decode: two workgroups per CU are resident, and the batch's units are dealt to them evenly, in request order, a
 // workgroup going on from one request's end to the next one's beginning.  (Chunks of one length, handed out longest first, left
 // a quarter of the slots idle at the end.)  A chunk costs its pipeline fill and its merge beside its tiles, about as
-// much as CHUNK_COST tiles; chunks are whole rounds of the four waves, except at a request's end.
+// much as CHUNK_COST tiles; chunks are whole rounds of the four waves, except at a request's end.  `least`: deal a workgroup no
+// fewer units than this.
+constexpr int64_t CHUNK_COST = 20;
 inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t sum_units, int cus, int units_per_page, int override_units,
-                         int32_t* n_chunks, DecodeSplit& out) {
-  constexpr int64_t CHUNK_COST = 20, ROUND = 4;
+                         int64_t least, int32_t* n_chunks, DecodeSplit& out) {
+  constexpr int64_t ROUND = 4;
   const int64_t slots = std::max(1, 2 * cus), most = (int64_t)(MLA_CHUNK_PAGES - 1) * units_per_page / ROUND * ROUND;
   std::vector<DecodeItem>& items = ps.tmp_items;
   std::vector<int32_t>& owner = ps.tmp_sizes;                    // workgroup of each chunk
   // at least two tiles per wave
-  int64_t quota = CHUNK_COST + (override_units > 0 ? override_units : std::max<int64_t>(2 * ROUND, (sum_units + B * CHUNK_COST) / slots));
+  int64_t quota = CHUNK_COST + std::max(least, override_units > 0 ? override_units : std::max<int64_t>(2 * ROUND, (sum_units + B * CHUNK_COST) / slots));
   for (;; quota += std::max<int64_t>(1, quota / 64)) {
     const int64_t sliver = std::min<int64_t>((quota - CHUNK_COST) / 4, 4);
     items.clear();
@@ -98,6 +127,7 @@ inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, in
     out.n_wgs = owner.back() + 1;
     if (out.n_wgs <= slots || override_units > 0) break;
   }
+  out.dealt = quota;
   // workgroup i starts with record i: first chunks to the front, the others behind them, linked
   const int n = (int)items.size();
   std::vector<DecodeItem>& sorted = ps.tmp_items2;
@@ -111,6 +141,19 @@ inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, in
     prev = at;
   }
   items.swap(sorted);
+}
+
+// The same for the entry point that allocates nothing: where the even deal's records or partials would not fit, workgroups
+// are dealt more, in fewer and longer chunks, until they do (or until there is nothing left to lengthen).
+inline void split_latent_within_limits(spd_phase_state& ps, const int32_t* ctx_lens, int B, int H, int dv, int64_t sum_units, int max_pages, int cus,
+                                       int units_per_page, int override_units, bool append, size_t w_bytes, int32_t* n_chunks, DecodeSplit& out) {
+  for (int64_t least = 0;; least = out.dealt + out.dealt / 4) {
+    split_latent(ps, ctx_lens, B, sum_units, cus, units_per_page, override_units, least, n_chunks, out);
+    if (noalloc_metadata((int)ps.tmp_items.size(), B, max_pages, append, w_bytes) <= NOALLOC_STAGE_BYTES &&
+        partial_o_bytes(B, H, out.max_chunks, dv) + partial_ml_bytes(B, H, out.max_chunks) <= NOALLOC_WS_BYTES)
+      return;
+    if (out.dealt >= sum_units + B * CHUNK_COST) return;
+  }
 }
 
 }  // namespace spd

@@ -123,16 +123,18 @@ struct PrefillWork {
 };
 
 // The entry point that allocates nothing keeps its device-side working memory in one static device
-// array (noalloc.hip): four metadata twins (one per slot of the decode phase's staging ring), then the
+// array (noalloc.hip): the metadata's device twin (one, written and read in stream order), then the
 // split-K partials.
-constexpr size_t NOALLOC_STAGE_BYTES = 256u << 10;
+constexpr size_t NOALLOC_STAGE_BYTES = 256u << 10;   // limit of a step's metadata as noalloc_metadata counts it
 constexpr size_t NOALLOC_WS_BYTES = 32u << 20;
-// pinned bytes of a staging slot of the decode phase: the metadata of any batch within NOALLOC_STAGE_BYTES (which
-// counts one block table row per request) in the form the kernels read, one record per work item
-constexpr size_t NOALLOC_RING_BYTES = 1u << 20;
+constexpr size_t NOALLOC_TWIN_BYTES = 4 * NOALLOC_STAGE_BYTES;   // a longer batch's records are read from pinned memory
+// Pinned bytes of a staging slot of the decode phase: any batch within NOALLOC_STAGE_BYTES in the form the kernels read.
+// A record is at least 64 bytes, where the limit counts 16 (one page, nothing appended: 16384 requests, 1.06 MiB) or, of a
+// long context cut into many items, 8 (32768 of them, 2 MiB; only with SPD_DECODE_CHUNK_TILES).
+constexpr size_t NOALLOC_RING_BYTES = 9 * NOALLOC_STAGE_BYTES;
 constexpr size_t MERGE_COUNTERS = 4096;
 constexpr int STAGE_SLOTS = 8;             // steps of a phase in flight before a new one waits for the oldest
-constexpr size_t SCRATCH_BYTES = 4 * NOALLOC_STAGE_BYTES + NOALLOC_WS_BYTES;
+constexpr size_t SCRATCH_BYTES = NOALLOC_TWIN_BYTES + NOALLOC_WS_BYTES;
 
 extern thread_local int g_last_hip_error;
 inline int hip_fail(hipError_t e) { g_last_hip_error = (int)e; return SPD_EHIP; }

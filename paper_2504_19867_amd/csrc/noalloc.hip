@@ -1,7 +1,7 @@
 // Scratch memory of the entry point that allocates nothing (spd_decode_step_noalloc).
 //
 // Callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
-// harnesses that forbid it) get a decode step whose device-side working memory - the device twins of
+// harnesses that forbid it) get a decode step whose device-side working memory - the device twin of
 // the step's metadata and the split-K partials - lies in one file-scope device array instead of
 // buffers from hipMalloc.  Every GPU on which the library runs holds the array (SCRATCH_BYTES) from
 // the moment the code object is loaded until the process ends.

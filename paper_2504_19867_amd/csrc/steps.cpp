@@ -24,7 +24,6 @@ uint64_t reserve_entry_locked(spd_pool* pool, spd_req_table& table, int64_t n_to
 }  // namespace spd
 
 static inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
-static inline size_t align64(size_t x) { return (x + 63) & ~(size_t)63; }
 static inline size_t align4k(size_t x) { return (x + 4095) & ~(size_t)4095; }
 
 // Tile descriptors covering logical positions [start, start + n) of a request whose block
@@ -371,22 +370,19 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   std::vector<int32_t>& n_chunks = ds.tmp_chunks;
   n_chunks.resize((size_t)B);
   DecodeSplit sp;
-  if (mla) split_latent(ds, b->ctx_lens, B, sum_units, share, units_per_page, ctx->env_decode_chunk_tiles, n_chunks.data(), sp);
-  else split_gqa(ds, b->ctx_lens, B, sum_units, max_units, g.Hkv, share, ctx->env_decode_chunk_tiles, n_chunks.data(), sp);
+  const size_t w_bytes = b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0;
+  const int cut = ctx->env_decode_chunk_tiles;
+  if (!mla) split_gqa(ds, b->ctx_lens, B, sum_units, max_units, g.Hkv, share, cut, n_chunks.data(), sp);
+  else if (!noalloc) split_latent(ds, b->ctx_lens, B, sum_units, share, units_per_page, cut, 0, n_chunks.data(), sp);
+  else
+    split_latent_within_limits(ds, b->ctx_lens, B, b->n_q_heads, g.dv, sum_units, max_pages, share, units_per_page, cut, append, w_bytes,
+                               n_chunks.data(), sp);
   const std::vector<DecodeItem>& items = ds.tmp_items;
   const int n_items = (int)items.size(), max_chunks = sp.max_chunks;
-
-  // a record per item: header and page ids (a chunk that starts inside a page touches one more than it holds)
-  const int chunk_pages = (int)std::min<int64_t>(max_pages, ((int64_t)sp.chunk_units + units_per_page - 2) / units_per_page + 1);
-  const size_t stride = (sizeof(DecodeItem) + sizeof(int32_t) * (size_t)chunk_pages + 63) & ~(size_t)63;
+  const DecodeRecords rec_layout = decode_records(sp, n_items, B, max_pages, units_per_page);
+  const size_t stride = rec_layout.stride, off_chunks = rec_layout.off_chunks, bytes = rec_layout.bytes;
   if (stride > INT32_MAX) return SPD_EINVAL;
-  const size_t off_chunks = align64(stride * (size_t)n_items);
-  const size_t bytes = align16(off_chunks + sizeof(int32_t) * (size_t)B);
-  const size_t w_bytes = b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0;
-  // what the limit of the entry point that allocates nothing counts: one block table row per request, the items, the appends
-  if (noalloc && sizeof(int32_t) * (size_t)B * (1 + (size_t)max_pages) + 8 * (size_t)n_items + (append ? sizeof(TileDesc) * (size_t)B : 0) + w_bytes >
-                     NOALLOC_STAGE_BYTES)
-    return SPD_ETOOBIG;
+  if (noalloc && noalloc_metadata(n_items, B, max_pages, append, w_bytes) > NOALLOC_STAGE_BYTES) return SPD_ETOOBIG;
   spd_stage* st;
   if ((rc = stage_acquire(ctx, SPD_PHASE_DECODE, bytes + w_bytes, &st, !noalloc)) != SPD_OK) return rc;
   const bool timing = ctx->kernel_timing && !noalloc;
@@ -398,12 +394,11 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   // (each pays for going past the L2), else by a launch of its own
   const bool inline_merge = n_wgs <= (mla ? 128 : 512) && max_chunks <= MERGE_IN_LAUNCH_CHUNKS && (size_t)B * g.Hkv <= MERGE_COUNTERS;
   char* ws = nullptr;
-  const size_t ws_o_bytes = max_chunks > 1 ? align16(sizeof(float) * (size_t)B * b->n_q_heads * max_chunks * g.dv) : 0;
-  const size_t ws_ml_bytes = max_chunks > 1 ? align16(sizeof(float) * (size_t)B * b->n_q_heads * max_chunks * 2) : 0;
+  const size_t ws_o_bytes = partial_o_bytes(B, b->n_q_heads, max_chunks, g.dv), ws_ml_bytes = partial_ml_bytes(B, b->n_q_heads, max_chunks);
   const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + (twin && !noalloc ? bytes : 0);
   if (noalloc) {
     if (ws_bytes > NOALLOC_WS_BYTES) return SPD_ETOOBIG;
-    ws = ctx->scratch + 4 * NOALLOC_STAGE_BYTES;
+    ws = ctx->scratch + NOALLOC_TWIN_BYTES;
   } else if (ws_bytes > 0 && (rc = workspace_reserve(ctx, SPD_PHASE_DECODE, ws_bytes, &ws)) != SPD_OK) {
     return rc;
   }
@@ -455,7 +450,7 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   DecodeLaunch d{};
   if (b->rope && (rc = rope_table(ctx, SPD_PHASE_DECODE, b->rope, st->host + bytes, st->dev + bytes, stream, &mark, &d.w)) != SPD_OK) return rc;
   const char* meta = st->dev;
-  if (twin && (!noalloc || bytes <= 4 * NOALLOC_STAGE_BYTES)) {
+  if (twin && (!noalloc || bytes <= NOALLOC_TWIN_BYTES)) {
     char* to = noalloc ? ctx->scratch : ws + ws_o_bytes + ws_ml_bytes;
     SPD_HIP(launch_meta_copy(to, st->dev, bytes, mark, stream));
     mark.flag = nullptr;

@@ -23,14 +23,23 @@ def build(tmp_path):
     return exe
 
 
+class Split:
+    """One batch's answer: workgroups, most chunks of a request, largest chunk, items (req, chunk, unit0, n_units, next), and the
+    bytes of its records, of its metadata as the limit of the entry point that allocates nothing counts it, of its partials."""
+
+    def __init__(self, head, items):
+        self.n_wgs, self.max_chunks, self.chunk_units, _, self.record_bytes, self.metadata, self.partials = head
+        self.items = items
+
+
 def split(exe, batches):
-    """[(kind, page tokens, cus, kv heads, override, lengths)] -> (page ids, header words, [(n_wgs, max_chunks, chunk_units, items)])"""
-    text = "".join(f"{k} {P} {cus} {hkv} {o} {len(lens)} {' '.join(map(str, lens))}\n" for k, P, cus, hkv, o, lens in batches)
+    """[(kind, page tokens, cus, kv heads, q heads, append, override, lengths)] -> (page ids of a record, its header's words, bytes of
+    a staging slot), [Split]"""
+    text = "".join(" ".join(map(str, (*b[:-1], len(b[-1]), *b[-1]))) + "\n" for b in batches)
     out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=300).stdout.split("\n")
-    pages, words = map(int, out[0].split())
     at, answers = 1, []
     for _ in batches:
-        n_wgs, max_chunks, chunk_units, n = map(int, out[at].split())
-        answers.append((n_wgs, max_chunks, chunk_units, [tuple(map(int, l.split())) for l in out[at + 1:at + 1 + n]]))
-        at += 1 + n
-    return pages, words, answers
+        head = tuple(map(int, out[at].split()))
+        answers.append(Split(head, [tuple(map(int, l.split())) for l in out[at + 1:at + 1 + head[3]]]))
+        at += 1 + head[3]
+    return tuple(map(int, out[0].split())), answers

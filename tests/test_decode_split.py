@@ -47,36 +47,74 @@ def _check_cover(items, lens):
 
 
 def test_latent_chunks_fit_the_kernel(exe):
-    batches = [("latent", P, cus, 1, 0, [n] * B) for B, n, P, cus in LONG]
-    batches += [("latent", P, cus, 1, o, lens) for lens, P, cus, o in _random_batches()]
-    room, words, answers = DS.split(exe, batches)
+    batches = [("latent", P, cus, 1, 16, 1, 0, [n] * B) for B, n, P, cus in LONG]
+    batches += [("latent", P, cus, 1, 16, 1, o, lens) for lens, P, cus, o in _random_batches()]
+    (room, words, _), answers = DS.split(exe, batches)
     assert room + words <= KERNEL_THREADS
     longest = 0
-    for (_, P, cus, _, override, lens), (n_wgs, max_chunks, chunk_units, items) in zip(batches, answers):
+    for (_, P, cus, _, _, _, override, lens), s in zip(batches, answers):
         per_page = P // TILE
-        most = max(_pages(u0, n, per_page) for _, _, u0, n, _ in items)
+        most = max(_pages(u0, n, per_page) for _, _, u0, n, _ in s.items)
         longest = max(longest, most)
         assert most <= room, (P, cus, len(lens), most)
-        # the record as the host lays it out
-        assert min(-(-max(lens) // P), (chunk_units + per_page - 2) // per_page + 1) <= room
-        _check_cover(items, lens)
-        assert max_chunks == max(c for _, c, _, _, _ in items) + 1 and chunk_units == max(n for _, _, _, n, _ in items)
-        assert override or n_wgs <= 2 * cus
+        # the record as the host lays it out, rounded up to 64 bytes
+        assert s.record_bytes >= len(s.items) * 4 * (words + most)
+        assert s.record_bytes <= len(s.items) * 4 * KERNEL_THREADS + 4 * len(lens) + 16
+        _check_cover(s.items, lens)
+        assert s.max_chunks == max(i[1] for i in s.items) + 1 and s.chunk_units == max(i[3] for i in s.items)
+        assert override or s.n_wgs <= 2 * cus
         # the chains that workgroups 0 .. n_wgs - 1 walk pass through every item once
         seen = []
-        for start in range(n_wgs):
+        for start in range(s.n_wgs):
             i = start
-            while i >= 0 and len(seen) <= len(items):
+            while i >= 0 and len(seen) <= len(s.items):
                 seen.append(i)
-                i = items[i][4]
-        assert sorted(seen) == list(range(len(items)))
+                i = s.items[i][4]
+        assert sorted(seen) == list(range(len(s.items)))
     assert longest == room                  # (FULL_CHUNK: the test has seen the kernel's room used to the last word)
 
 
 def test_gqa_chunks_cover_the_batch(exe):
-    batches = [("gqa", 16, cus, hkv, o, lens) for (lens, _, cus, o), hkv in zip(_random_batches(), [1, 2, 8, 64] * 40)]
-    _, _, answers = DS.split(exe, batches)
-    for (_, _, cus, hkv, override, lens), (n_wgs, max_chunks, chunk_units, items) in zip(batches, answers):
-        _check_cover(items, lens)
-        assert n_wgs == len(items) and all(i[4] == -1 for i in items)
-        assert max_chunks == max(c for _, c, _, _, _ in items) + 1 and max(n for _, _, _, n, _ in items) <= chunk_units
+    batches = [("gqa", 16, cus, hkv, 64, 1, o, lens) for (lens, _, cus, o), hkv in zip(_random_batches(), [1, 2, 8, 64] * 40)]
+    _, answers = DS.split(exe, batches)
+    for (*_, lens), s in zip(batches, answers):
+        _check_cover(s.items, lens)
+        assert s.n_wgs == len(s.items) and all(i[4] == -1 for i in s.items)
+        assert s.max_chunks == max(i[1] for i in s.items) + 1 and max(i[3] for i in s.items) <= s.chunk_units
+
+
+LIMIT, WORKSPACE = 256 << 10, 32 << 20
+
+
+def test_metadata_within_the_noalloc_limit_fits_a_staging_slot(exe):
+    """The limit counts a block table row per request, the slot holds a record per work item."""
+    batches = [("gqa", 16, 256, 8, 8, 0, 0, [16] * 16384),          # as many requests as the limit takes
+               ("gqa", 16, 256, 8, 8, 0, 0, [9 * 16] * 5461),
+               ("gqa", 16, 256, 1, 1, 0, 0, [16 * 60000]),
+               ("gqa", 1024, 32, 64, 64, 0, 0, [1024 * 31] + [1] * 1900),
+               ("gqa", 1024, 256, 1, 1, 0, 8, [1024 * 3800])]       # as many items as it takes, with the chunk length overridden
+    batches += [("gqa", P, cus, hkv, 64, 0, o, lens) for (lens, P, cus, o), hkv in zip(_random_batches(), [1, 2, 8, 64] * 40)]
+    batches += [("noalloc", P, cus, 1, 16, 0, o, lens) for lens, P, cus, o in _random_batches()]
+    batches += [("noalloc", 32, 64, 1, 16, 0, 0, [32] * 16384), ("noalloc", 64, 256, 1, 16, 1, 0, [100] * 5000)]
+    (_, _, slot), answers = DS.split(exe, batches)
+    within = [s for s in answers if s.metadata <= LIMIT]
+    assert len(within) > 200 and all(s.metadata <= LIMIT for s in answers[:5])
+    assert all(s.record_bytes + 4 * 256 <= slot for s in within)    # with the largest frequency table
+    assert answers[0].record_bytes > 1 << 20
+
+
+# Latent batches that fit the fixed workspace with chunks of one length (of 62 pages at most), but do not as they are dealt to
+# the workgroups, which cuts requests at the workgroups' borders: requests, context, page tokens, decode CUs, query heads
+TIGHT = [(2187, 286, 64, 96, 7), (1179, 364, 128, 32, 14), (2598, 1339, 96, 96, 10)]
+
+
+def test_latent_chunks_are_lengthened_until_the_noalloc_limits_hold(exe):
+    _, even = DS.split(exe, [("latent", P, cus, 1, H, 0, 0, [n] * B) for B, n, P, cus, H in TIGHT])
+    _, fit = DS.split(exe, [("noalloc", P, cus, 1, H, 0, 0, [n] * B) for B, n, P, cus, H in TIGHT])
+    for (B, n, *_), e, f in zip(TIGHT, even, fit):
+        assert e.partials > WORKSPACE
+        assert f.partials <= WORKSPACE and f.metadata <= LIMIT
+        _check_cover(f.items, [n] * B)
+    # a batch within the limits is split as spd_decode_step splits it
+    same = [(64, 16, 1, 16, 1, 0, [1500, 65, 640, 2047])]
+    assert DS.split(exe, [("noalloc", *s) for s in same])[1][0].items == DS.split(exe, [("latent", *s) for s in same])[1][0].items

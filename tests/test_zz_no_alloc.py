@@ -10,6 +10,7 @@ import torch
 import workloads as W
 from oracle import attention as OA
 from paper_2504_19867_amd import semipd as S
+from test_decode_split import TIGHT
 from gpu_util import DEV, GpuPool, assert_parity, dev_bf16, f64, host_bits, host_f64
 
 pytestmark = pytest.mark.gpu
@@ -97,4 +98,64 @@ def test_noalloc_limits_are_enforced_and_change_nothing():
         gp.pool.decode_step_noalloc_batch(gp.pool.make_decode_batch([1], [n], q, out, 8, 0.125))
     assert e.value.status == S.SPD_ETOOBIG
     assert gp.pool.stats() == before
+    gp.close()
+
+
+def test_noalloc_takes_as_many_requests_as_its_limit_says():
+    """16000 requests of one page, nothing appended: 16 bytes each as the limit counts them, a record of 64 each in the ring."""
+    layer = W.LayerShape("gqa", 8, 8, 64, 64, 16)
+    B = 16000
+    gp = GpuPool(layer, B + 8)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    gp.mem.view(torch.bfloat16).normal_(generator=gen)               # any page contents are rows
+    lens = [1 + i % 16 for i in range(B)]
+    ids = list(range(1, B + 1))
+    for i, n in zip(ids, lens):
+        gp.pool.kv_reserve(i, n)
+    q = torch.randn((B, 8, 64), generator=gen, device=DEV).to(torch.bfloat16)
+    out = [torch.full_like(q, float("nan")) for _ in range(2)]
+    torch.cuda.synchronize()
+    assert 4 * B * 2 + 8 * B <= S.noalloc_limits()[0]
+    gp.pool.decode_step_noalloc_batch(gp.pool.make_decode_batch(ids, lens, q, out[0], 8, 0.125))
+    gp.pool.decode_step_batch(gp.pool.make_decode_batch(ids, lens, q, out[1], 8, 0.125))
+    gp.ctx.phase_sync(DEC)
+    assert torch.isfinite(out[0]).all() and np.array_equal(host_bits(out[0]), host_bits(out[1]))
+    k, v = (torch.empty((1, 8, 64), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    gp.pool.kv_gather(DEC, 1, 1, k, v)                               # one token: attention is its value
+    gp.ctx.phase_sync(DEC)
+    assert np.array_equal(host_bits(out[0][0]), host_bits(v[0]))
+    gp.close()
+
+
+def test_noalloc_latent_decode_with_chunks_lengthened_to_fit():
+    """A latent batch whose even deal over the workgroups would not fit the workspace (tests/test_decode_split.py): taken, and equal
+    to spd_decode_step's within rounding."""
+    B, n, P, cus, H = TIGHT[0]
+    layer = W.LayerShape("mla", H, 1, 192, 128, P, latent_dim=576, latent_v_dim=512)
+    gp = GpuPool(layer, B * -(-n // P) + 8)
+    total, _, _ = gp.ctx.device_info()
+    gp.ctx.set_partition(total, cus)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(6)
+    gp.mem.view(torch.bfloat16).normal_(generator=gen)
+    ids = list(range(1, B + 1))
+    for i in ids:
+        gp.pool.kv_reserve(i, n)
+    q = torch.randn((B, H, 576), generator=gen, device=DEV).mul_(0.2).to(torch.bfloat16)
+    out = [torch.full((B, H, 512), float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    torch.cuda.synchronize()
+    scale = 1.0 / math.sqrt(192)
+    gp.pool.decode_step_noalloc_batch(gp.pool.make_decode_batch(ids, [n] * B, q, out[0], H, scale))
+    gp.pool.decode_step_batch(gp.pool.make_decode_batch(ids, [n] * B, q, out[1], H, scale))
+    gp.ctx.phase_sync(DEC)
+    rows = torch.empty((n, 576), dtype=torch.bfloat16, device=DEV)
+    for i in (0, B // 2, B - 1):
+        gp.pool.kv_gather(DEC, ids[i], n, rows)
+        gp.ctx.phase_sync(DEC)
+        want = OA.mla_decode_latent(host_f64(q[i]), host_f64(rows), scale, 512)[None]
+        for o in out:
+            assert_parity(host_f64(o[i:i + 1]), want, f"request {i}")
+    # two bf16 roundings of sums whose bf16 weights differ by their rounding: 2^-8 of the largest output, which is below 1
+    assert (out[0].float() - out[1].float()).abs().max() < 2 ** -7
     gp.close()
