@@ -385,10 +385,11 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(S[i] * a.c - mc);
     const float psum = (p[0] + p[1]) + (p[2] + p[3]);
     if constexpr (FP8) {
-      if (!have_ref) {                             // (a scale below 2^-64 is no reference: its reciprocal could overflow)
+      // (the reference stays near 1: relative to a scale at one end of fp32's range the others' would leave it at the other end)
+      if (!have_ref) {
 #pragma unroll
         for (int sb = 0; sb < 4; ++sb) {
-          ref[sb] = uniform(fmaxf(sc[0][sb], 0x1p-64f));
+          ref[sb] = uniform(fminf(fmaxf(sc[0][sb], 0x1p-16f), 0x1p16f));
           inv_ref[sb] = uniform(1.f / ref[sb]);
         }
         have_ref = true;

@@ -160,3 +160,33 @@ def test_fp8_append_and_prefill_write_the_same_pages():
         gp.pool.decode_step(ids, cur, dev_bf16(qn), out, 16, scale, rope=S.rope_config(rotary_dim=64, rotary_offset=512))
     assert e.value.status == S.SPD_EINVAL
     gp.close()
+
+
+@pytest.mark.parametrize("first, rest", [(1e-25, 1e20), (1e20, 1e-25), (1e-25, 1.0), (0.0, 1e-20)])
+def test_decode_over_rows_of_very_different_magnitude(first, rest):
+    """The value product is taken relative to one token's scales: neither those nor the others' may leave fp32's range."""
+    layer = W.LayerShape("mla", 16, 1, 192, 128, 64, latent_dim=576, latent_v_dim=512)
+    n = 700
+    gp = GpuPool(layer, 16, kind=S.SPD_KV_MLA_LATENT_FP8)
+    rng = np.random.default_rng(13)
+    c = rng.standard_normal((n, 576)).astype(np.float32)
+    c[:64, :512] *= first                                # the first tile of each of the four waves
+    c[64:, :512] *= rest
+    c[:64, 512:] = 3.0                                   # ... which the scores all but leave out
+    c[64:, 512:] *= 0.1
+    q = np.zeros((1, 16, 576), dtype=np.float32)
+    q[..., :512] = rng.standard_normal((1, 16, 512)) * (0.1 / max(first, rest))
+    q[..., 512:] = -4.0
+    rows, tq = W.to_bf16_bits(c), W.to_bf16_bits(q)
+    dev, dq = dev_bf16(rows), dev_bf16(tq)
+    gp.pool.kv_reserve(1, n)
+    gp.pool.kv_write(S.SPD_PHASE_DECODE, 1, 0, n, dev)
+    out = torch.full((1, 16, 512), float("nan"), dtype=torch.bfloat16, device=DEV)
+    scale = 1.0 / math.sqrt(192)
+    gp.pool.decode_step([1], [n], dq, out, 16, scale)
+    gp.ctx.phase_sync(S.SPD_PHASE_DECODE)
+    want = OA.mla_decode_latent(f64(tq[0]), F8.dequantise_latent(*F8.quantise_latent(W.bf16_bits_to_f32(rows))), scale, 512)
+    got = host_f64(out[0])
+    # one bf16 rounding of the weights and one of the output: 2^-9 / sqrt(3) each, relative, and up to 2^-9 where one token rules
+    assert np.isfinite(got).all() and np.linalg.norm(got - want) <= 2 ** -7 * np.linalg.norm(want), np.linalg.norm(got - want) / np.linalg.norm(want)
+    gp.close()
