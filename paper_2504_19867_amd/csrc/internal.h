@@ -133,6 +133,7 @@ constexpr size_t NOALLOC_TWIN_BYTES = 4 * NOALLOC_STAGE_BYTES;   // a longer bat
 // long context cut into many items, 8 (32768 of them, 2 MiB; only with SPD_DECODE_CHUNK_TILES).
 constexpr size_t NOALLOC_RING_BYTES = 9 * NOALLOC_STAGE_BYTES;
 constexpr size_t MERGE_COUNTERS = 4096;
+constexpr int MERGE_IN_LAUNCH_CHUNKS = 16; // most chunks of a request that a workgroup of the attention launch merges on the side
 constexpr int STAGE_SLOTS = 8;             // steps of a phase in flight before a new one waits for the oldest
 constexpr size_t SCRATCH_BYTES = NOALLOC_TWIN_BYTES + NOALLOC_WS_BYTES;
 

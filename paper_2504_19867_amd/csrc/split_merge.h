@@ -11,8 +11,6 @@
 
 namespace spd {
 
-constexpr int MERGE_IN_LAUNCH_CHUNKS = 16;       // most chunks of a request that a workgroup merges on the side
-
 // two consecutive floats of a partial; `shared`: another workgroup of this launch reads them
 __device__ inline void store_partial(float* p, float x, float y, bool shared) {
   typedef float f32x2_ __attribute__((ext_vector_type(2)));

@@ -4,7 +4,6 @@
 #include "internal.h"
 #include "decode_split.h"
 #include "prefill_work.h"
-#include "split_merge.h"
 
 #include <stdlib.h>
 #include <string.h>
@@ -43,7 +42,7 @@ static int build_tile_descs(const PoolGeom& g, const int32_t* bt, int32_t start,
   }
   return count;
 }
-static size_t tile_desc_count(int32_t start, int32_t n) { return (size_t)((start % TILE_T) + n + TILE_T - 1) / TILE_T; }
+static size_t tile_desc_count(int32_t start, int32_t n) { return ((size_t)(start % TILE_T) + (size_t)n + TILE_T - 1) / TILE_T; }
 
 // Does a request id occur twice?  Small batches pair by pair, larger ones through an open-addressing table.
 static bool has_duplicates(const uint64_t* ids, int n, std::vector<uint64_t>& set) {
@@ -84,17 +83,30 @@ static int kv_copy(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t req_id, int
   if ((g.kind == SPD_KV_GQA) != (v != nullptr)) return SPD_EINVAL;
   if (misaligned16(k, v)) return SPD_EINVAL;
   if (ctx->device < 0) return SPD_ESTATE;
-  spd_stage* st;
-  int rc, n_descs;
-  if ((rc = stage_acquire(ctx, phase, tile_desc_count(start_pos, n_tokens) * sizeof(TileDesc), &st)) != SPD_OK) return rc;
-  {
-    std::lock_guard<std::mutex> lk(pool->mu);
+  // the request's table, if it holds the positions named (caller holds pool->mu)
+  auto find_locked = [&](spd_req_table** out) -> int {
     auto it = pool->tables.find(req_id);
     if (it == pool->tables.end()) return SPD_ENOENT;
     const int64_t need = ((int64_t)start_pos + n_tokens + g.P - 1) / g.P;
     if ((int64_t)it->second.size() < need) return SPD_EINVAL;
-    n_descs = build_tile_descs(g, it->second.data(), start_pos, n_tokens, 0, (TileDesc*)st->host);
-    it->second.last_use[phase] = next_step_number(ctx, phase);
+    *out = &it->second;
+    return SPD_OK;
+  };
+  // asked before anything is allocated for n_tokens, and again once there is a slot to write to (the wait for it is not under
+  // the lock)
+  spd_req_table* table = nullptr;
+  spd_stage* st;
+  int rc, n_descs;
+  {
+    std::lock_guard<std::mutex> lk(pool->mu);
+    if ((rc = find_locked(&table)) != SPD_OK) return rc;
+  }
+  if ((rc = stage_acquire(ctx, phase, tile_desc_count(start_pos, n_tokens) * sizeof(TileDesc), &st)) != SPD_OK) return rc;
+  {
+    std::lock_guard<std::mutex> lk(pool->mu);
+    if ((rc = find_locked(&table)) != SPD_OK) return rc;
+    n_descs = build_tile_descs(g, table->data(), start_pos, n_tokens, 0, (TileDesc*)st->host);
+    table->last_use[phase] = next_step_number(ctx, phase);
   }
   hipStream_t stream;
   if ((rc = phase_enter(ctx, phase, &stream)) != SPD_OK) return rc;

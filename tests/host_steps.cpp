@@ -1,0 +1,199 @@
+// The steps' host side (ctx.cpp, steps.cpp, pool.cpp, rope.cpp) over a stand-in for the HIP runtime, on the CPU: memory is
+// host memory, a stream is a queue of closures that run when the test lets them, and a launch stores the step mark it was
+// given and logs what it reads.  host_steps NAME runs one scenario.
+#include <hip/hip_runtime.h>
+
+#include <climits>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <deque>
+#include <functional>
+#include <string>
+#include <vector>
+
+#include "internal.h"
+
+#define CHECK(x) do { if (!(x)) { fprintf(stderr, "check failed: %s (line %d)\n", #x, __LINE__); exit(1); } } while (0)
+
+// ------------------------------------------------------------------------------------------ the runtime's stand-in
+struct Stream {
+  std::deque<std::function<void()>> queue;      // not yet run
+  std::vector<std::function<void()>>* graph = nullptr;   // being captured
+};
+struct Event {
+  bool recorded = false, done = false, captured = false;
+};
+static std::vector<Stream*> streams;
+static long n_pinned = 0, pinned_bytes = 0, n_device = 0;   // allocations so far
+static int fail_launch = -1;                    // the launch of this number fails
+static int n_launches = 0;
+static std::vector<double> seen_w;              // last RoPE frequency that each decode launch found when it ran (0: none)
+
+static void put(hipStream_t s, std::function<void()> f) {
+  Stream* st = (Stream*)s;
+  if (st->graph) st->graph->push_back(f);
+  else st->queue.push_back(f);
+}
+static void run(Stream* s, size_t n = SIZE_MAX) {
+  for (; n && !s->queue.empty(); --n) {
+    auto f = s->queue.front();
+    s->queue.pop_front();
+    f();
+  }
+}
+extern "C" {
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
+  memset(p, 0, sizeof *p);
+  strcpy(p->gcnArchName, "gfx950");
+  p->multiProcessorCount = 256;
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) { ++n_device; *p = calloc(1, n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  ++n_pinned;
+  pinned_bytes += (long)n;
+  *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+  return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
+hipError_t hipExtStreamCreateWithCUMask(hipStream_t* s, uint32_t, const uint32_t*) {
+  streams.push_back(new Stream);
+  *s = (hipStream_t)streams.back();
+  return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  if (((Stream*)s)->graph) return hipErrorStreamCaptureUnsupported;
+  run((Stream*)s);
+  return hipSuccess;
+}
+hipError_t hipStreamQuery(hipStream_t s) {      // whoever asks lets the stream go on by one
+  if (((Stream*)s)->graph) return hipErrorStreamCaptureUnsupported;
+  run((Stream*)s, 1);
+  return ((Stream*)s)->queue.empty() ? hipSuccess : hipErrorNotReady;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+  *st = ((Stream*)s)->graph ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)new Event; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { delete (Event*)e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  Event* ev = (Event*)e;
+  ev->recorded = true;
+  ev->done = false;
+  ev->captured = ((Stream*)s)->graph != nullptr;
+  put(s, [ev] { ev->done = true; });
+  return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) {
+  Event* ev = (Event*)e;
+  if (ev->captured) return hipErrorCapturedEvent;
+  return !ev->recorded || ev->done ? hipSuccess : hipErrorNotReady;
+}
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipErrorUnknown; }
+}
+
+// ------------------------------------------------------------------------------------------ the launchers' stand-ins
+namespace spd {
+static hipError_t launch(hipStream_t s, const StepMark& m, std::function<void()> f = [] {}) {
+  if (n_launches++ == fail_launch) return hipErrorLaunchFailure;
+  put(s, [m, f] {
+    if (m.flag) *m.flag = m.seq;
+    f();
+  });
+  return hipSuccess;
+}
+hipError_t launch_kv_write(const PoolGeom&, char*, const TileDesc*, int, const void*, const void*, const StepMark& m, hipStream_t s, void*,
+                           const void*, uint64_t) { return launch(s, m); }
+bool kv_rows_supported(const PoolGeom& g) { return g.kind == SPD_KV_GQA && g.Hkv >= 2; }
+hipError_t launch_kv_rows(const PoolGeom&, char*, const TileDesc*, int, const void*, const void*, const KvRows&, const StepMark& m,
+                          hipStream_t s) { return launch(s, m); }
+hipError_t launch_kv_gather(const PoolGeom&, const char*, const TileDesc*, int, void*, void*, const StepMark& m, hipStream_t s) { return launch(s, m); }
+hipError_t launch_kv_write_fp8(const PoolGeom&, char*, const TileDesc*, int, const void*, const StepMark& m, hipStream_t s, void*, const void*,
+                               uint64_t) { return launch(s, m); }
+hipError_t launch_kv_gather_fp8(const PoolGeom&, const char*, const TileDesc*, int, void*, const StepMark& m, hipStream_t s) { return launch(s, m); }
+hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const StepMark& m, hipStream_t s) {
+  return launch(s, m, [=] { memcpy(dst, src, bytes); });
+}
+hipError_t launch_decode_gqa(const PoolGeom&, char*, const DecodeLaunch& d, hipStream_t s) {
+  return launch(s, d.mark, [d] { seen_w.push_back(d.w ? d.w[d.rot / 2 - 1] : 0.0); });
+}
+hipError_t launch_decode_mla(const PoolGeom& g, char* b, const DecodeLaunch& d, hipStream_t s) { return launch_decode_gqa(g, b, d, s); }
+hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillWork*, const int32_t*, int, int, int, int, int, float,
+                          hipStream_t s) { return launch(s, StepMark{}); }
+hipError_t launch_rope(void*, int, void*, int, int, int, int, bool, int, const int32_t*, const double*, const StepMark& m, hipStream_t s) { return launch(s, m); }
+hipError_t launch_probe(int32_t*, int, hipStream_t) { return hipErrorUnknown; }
+hipError_t launch_copy(void*, const void*, uint64_t, int, hipStream_t) { return hipErrorUnknown; }
+hipError_t launch_read(const void*, uint64_t, int, uint32_t*, hipStream_t) { return hipErrorUnknown; }
+hipError_t launch_read_lds(const void*, uint64_t, int, uint32_t*, hipStream_t) { return hipErrorUnknown; }
+hipError_t launch_clock_probe(uint64_t, uint64_t*, hipStream_t) { return hipErrorUnknown; }
+hipError_t launch_issue_probe(uint64_t*, hipStream_t) { return hipErrorUnknown; }
+bool prefill_shape_supported(int dqk, int dv) { return dqk == dv; }
+int prefill_heads_per_block(int group) { return group; }
+int prefill_block_m(int) { return 128; }
+int scratch_resolve(int, char** out) {
+  *out = (char*)aligned_alloc(4096, SCRATCH_BYTES);
+  return SPD_OK;
+}
+}  // namespace spd
+
+// ------------------------------------------------------------------------------------------ what the scenarios share
+static spd_ctx* ctx;
+static spd_pool* pool;
+alignas(16) static char tensor[1 << 16];
+
+static spd_rope_config rope(double theta) { return spd_rope_config{theta, 1.0, 1.0, 4.0, 8192, 128, 0, 0}; }
+
+static void setup() {
+  CHECK(spd_ctx_create(0, &ctx) == SPD_OK);
+  const spd_pool_desc desc = {SPD_KV_GQA, 16, 2, 128, 128, 64};
+  uint64_t bytes;
+  CHECK(spd_pool_bytes(&desc, &bytes) == SPD_OK);
+  CHECK(spd_pool_create(ctx, aligned_alloc(4096, bytes), bytes, &desc, &pool) == SPD_OK);
+  for (uint64_t r = 1; r <= 4; ++r) CHECK(spd_kv_reserve(pool, r, 40, nullptr) == SPD_OK);
+}
+static Stream* decode_stream() { return (Stream*)ctx->phase[SPD_PHASE_DECODE].stream; }
+
+static int decode(uint64_t req, const spd_rope_config* r = nullptr, bool noalloc = false) {
+  const int32_t len = 40;
+  const spd_decode_batch b = {1, &req, &len, tensor, nullptr, nullptr, tensor, 8, 0.1f, r};
+  return noalloc ? spd_decode_step_noalloc(ctx, pool, &b) : spd_decode_step(ctx, pool, &b);
+}
+
+// ------------------------------------------------------------------------------------------ scenarios
+// A page write or gather that is refused allocates nothing, however many tokens it names.
+static void refused_copies() {
+  spd_ctx* c = ctx;
+  const int P = SPD_PHASE_PREFILL;
+  const long pinned = n_pinned;
+  for (const int32_t n : {INT32_MAX, INT32_MAX - 7, 100000000, 49}) {
+    CHECK(spd_kv_write(c, pool, P, 1, 0, n, tensor, tensor) == SPD_EINVAL);       // longer than the request's pages
+    CHECK(spd_kv_write(c, pool, P, 1, 8, n, tensor, tensor) == SPD_EINVAL);
+    CHECK(spd_kv_gather(c, pool, P, 1, n, tensor, tensor) == SPD_EINVAL);
+    CHECK(spd_kv_write(c, pool, P, 99, 0, n, tensor, tensor) == SPD_ENOENT);
+    CHECK(spd_kv_gather(c, pool, P, 99, n, tensor, tensor) == SPD_ENOENT);
+  }
+  CHECK(n_pinned == pinned && n_launches == 0);
+  CHECK(spd_kv_write(c, pool, P, 1, 8, 40, tensor, tensor) == SPD_OK && n_launches == 1);
+}
+
+int main(int argc, char** argv) {
+  CHECK(argc == 2);
+  const std::string name = argv[1];
+  setup();
+  if (name == "refused_copies") refused_copies();
+  else CHECK(!"a scenario of that name");
+  puts("ok");
+}
