@@ -238,6 +238,27 @@ int phase_enter(spd_ctx* ctx, int phase, hipStream_t* stream_out);   // adopt pe
 int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool may_alloc = true);
 int scratch_resolve(int device, char** out);   // noalloc.hip: address of `device`'s copy of the scratch array
 int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, hipStream_t stream);   // behind the step's last launch: the step has its number
+// A step from its first launch on.  One that returns before its commit may have launches in the queue that read the staging slot,
+// and its batch's requests carry its number: it counts as issued all the same, and what it left on the device (the
+// RoPE table) as unknown.
+struct StepScope {
+  spd_ctx* ctx;
+  int phase;
+  spd_stage* st;
+  hipStream_t stream;
+  bool open = true;
+  int commit() {
+    open = false;
+    return stage_commit(ctx, phase, st, stream);
+  }
+  ~StepScope() {
+    if (!open) return;
+    const int error = g_last_hip_error;
+    ctx->phase[phase].rope_valid = false;
+    (void)stage_commit(ctx, phase, st, stream);
+    g_last_hip_error = error;
+  }
+};
 // what the first kernel enqueued behind the phase's last step stores (see spd_phase_state::flag)
 StepMark step_mark(spd_ctx* ctx, int phase);
 // Before anything but a step's first kernel goes onto the phase's stream: an event behind the last step, unless that

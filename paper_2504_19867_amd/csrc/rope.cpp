@@ -92,6 +92,7 @@ extern "C" int spd_rope_qk(spd_ctx* ctx, int phase, const spd_rope_config* cfg, 
   spd_stage* st = nullptr;
   st_rc = stage_acquire(ctx, phase, w_bytes + p_bytes, &st);
   if (st_rc != SPD_OK) return st_rc;
+  StepScope step{ctx, phase, st, stream};
   rope_frequencies(cfg, (double*)st->host);
   std::memcpy(st->host + w_bytes, positions, p_bytes);
   // the kernel reads the table and the positions straight out of the pinned buffer
@@ -103,5 +104,5 @@ extern "C" int spd_rope_qk(spd_ctx* ctx, int phase, const spd_rope_config* cfg, 
                       n_tokens, (const int32_t*)(st->dev + w_bytes), (const double*)st->dev, step_mark(ctx, phase), stream));
   st_rc = kernel_timing_mark(ctx, phase, 1, stream);
   if (st_rc != SPD_OK) return st_rc;
-  return stage_commit(ctx, phase, st, stream);
+  return step.commit();
 }

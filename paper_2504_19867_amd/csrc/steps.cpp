@@ -110,6 +110,7 @@ static int kv_copy(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t req_id, int
   }
   hipStream_t stream;
   if ((rc = phase_enter(ctx, phase, &stream)) != SPD_OK) return rc;
+  StepScope step{ctx, phase, st, stream};
   const TileDesc* descs = (const TileDesc*)st->dev;              // read over PCIe, once per workgroup
   const StepMark mark = step_mark(ctx, phase);
   const bool fp8 = g.kind == SPD_KV_MLA_LATENT_FP8;
@@ -117,7 +118,7 @@ static int kv_copy(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t req_id, int
   else if (write) SPD_HIP(launch_kv_write(g, pool->base, descs, n_descs, k, v, mark, stream));
   else if (fp8) SPD_HIP(launch_kv_gather_fp8(g, pool->base, descs, n_descs, (void*)k, mark, stream));
   else SPD_HIP(launch_kv_gather(g, pool->base, descs, n_descs, (void*)k, (void*)v, mark, stream));
-  return stage_commit(ctx, phase, st, stream);
+  return step.commit();
 }
 
 extern "C" int spd_kv_write(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t req_id, int32_t start_pos,
@@ -270,6 +271,7 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   }
   hipStream_t stream;
   if ((rc = phase_enter(ctx, SPD_PHASE_PREFILL, &stream)) != SPD_OK) return rc;
+  StepScope step{ctx, SPD_PHASE_PREFILL, st, stream};
   memcpy(st->host, work.data(), work.size() * sizeof(PrefillWork));
   memcpy(st->host + off_chain, chain.data(), chain.size() * sizeof(int32_t));
   StepMark mark = step_mark(ctx, SPD_PHASE_PREFILL);
@@ -324,7 +326,7 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   SPD_HIP(launch_prefill(b->q, att_k, att_v, b->out, (const PrefillWork*)ws, (const int32_t*)(ws + off_chain),
                          n_blocks, b->n_q_heads, b->n_kv_heads, b->dim_qk, b->dim_v, b->scale, stream));
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 1, stream)) != SPD_OK) return rc;
-  if ((rc = stage_commit(ctx, SPD_PHASE_PREFILL, st, stream)) != SPD_OK) return rc;
+  if ((rc = step.commit()) != SPD_OK) return rc;
   if (ctx->kernel_timing) {
     SPD_HIP(hipEventRecord(ps.ev_end, stream));
     ps.timed = true;
@@ -457,6 +459,7 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   }
   hipStream_t stream;
   if ((rc = phase_enter(ctx, SPD_PHASE_DECODE, &stream)) != SPD_OK) return rc;
+  StepScope step{ctx, SPD_PHASE_DECODE, st, stream};
   if (timing) SPD_HIP(hipEventRecord(ds.ev_start, stream));
   StepMark mark = step_mark(ctx, SPD_PHASE_DECODE);
   DecodeLaunch d{};
@@ -480,7 +483,7 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   if (mla) SPD_HIP(launch_decode_mla(g, pool->base, d, stream));
   else SPD_HIP(launch_decode_gqa(g, pool->base, d, stream));
   if (timing && (rc = kernel_timing_mark(ctx, SPD_PHASE_DECODE, 1, stream)) != SPD_OK) return rc;
-  if ((rc = stage_commit(ctx, SPD_PHASE_DECODE, st, stream)) != SPD_OK) return rc;
+  if ((rc = step.commit()) != SPD_OK) return rc;
   if (timing) {
     SPD_HIP(hipEventRecord(ds.ev_end, stream));
     ds.timed = true;

@@ -28,7 +28,7 @@ static std::vector<Stream*> streams;
 static long n_pinned = 0, pinned_bytes = 0, n_device = 0;   // allocations so far
 static int fail_launch = -1;                    // the launch of this number fails
 static int n_launches = 0;
-static std::vector<double> seen_w;              // last RoPE frequency that each decode launch found when it ran (0: none)
+static std::vector<double> seen_w;              // sum of the RoPE frequencies that each decode launch found when it ran
 
 static void put(hipStream_t s, std::function<void()> f) {
   Stream* st = (Stream*)s;
@@ -128,7 +128,11 @@ hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const St
   return launch(s, m, [=] { memcpy(dst, src, bytes); });
 }
 hipError_t launch_decode_gqa(const PoolGeom&, char*, const DecodeLaunch& d, hipStream_t s) {
-  return launch(s, d.mark, [d] { seen_w.push_back(d.w ? d.w[d.rot / 2 - 1] : 0.0); });
+  return launch(s, d.mark, [d] {
+    double sum = 0;
+    for (int i = 0; i < d.rot / 2; ++i) sum += d.w[i];
+    seen_w.push_back(sum);
+  });
 }
 hipError_t launch_decode_mla(const PoolGeom& g, char* b, const DecodeLaunch& d, hipStream_t s) { return launch_decode_gqa(g, b, d, s); }
 hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillWork*, const int32_t*, int, int, int, int, int, float,
@@ -172,6 +176,13 @@ static int decode(uint64_t req, const spd_rope_config* r = nullptr, bool noalloc
   return noalloc ? spd_decode_step_noalloc(ctx, pool, &b) : spd_decode_step(ctx, pool, &b);
 }
 
+static double sum_w(const spd_rope_config& c) {
+  double w[64], sum = 0;
+  CHECK(spd_rope_inv_freq(&c, w, 64) == SPD_OK);
+  for (double x : w) sum += x;
+  return sum;
+}
+
 // ------------------------------------------------------------------------------------------ scenarios
 // A page write or gather that is refused allocates nothing, however many tokens it names.
 static void refused_copies() {
@@ -189,11 +200,31 @@ static void refused_copies() {
   CHECK(spd_kv_write(c, pool, P, 1, 8, 40, tensor, tensor) == SPD_OK && n_launches == 1);
 }
 
+// A step whose attention launch fails: its staging slot, which the launch before it reads, stays untouched until that has run,
+// the frequency table that was on its way is not taken for granted, and nothing of it keeps its request's pages.
+static void failed_launch() {
+  const spd_rope_config a = rope(10000.0), b = rope(500000.0);
+  CHECK(decode(1, &a) == SPD_OK);
+  run(decode_stream());
+  fail_launch = n_launches + 1;                      // the frequencies' copy goes out, the attention does not
+  CHECK(decode(2, &b) == SPD_EHIP);
+  CHECK(spd_kv_write(ctx, pool, SPD_PHASE_DECODE, 3, 0, 40, tensor, tensor) == SPD_OK);      // the next user of a slot
+  CHECK(decode(4, &b) == SPD_OK);
+  CHECK(decode(1, &a) == SPD_OK);
+  fail_launch = n_launches;                          // nothing goes out
+  CHECK(decode(2, &b) == SPD_EHIP);
+  CHECK(decode(4, &b) == SPD_OK);
+  run(decode_stream());
+  CHECK(seen_w.size() == 4 && seen_w[0] == sum_w(a) && seen_w[1] == sum_w(b) && seen_w[2] == sum_w(a) && seen_w[3] == sum_w(b));
+  for (uint64_t r = 1; r <= 4; ++r) CHECK(spd_kv_free(pool, r, nullptr) == SPD_OK);
+}
+
 int main(int argc, char** argv) {
   CHECK(argc == 2);
   const std::string name = argv[1];
   setup();
   if (name == "refused_copies") refused_copies();
+  else if (name == "failed_launch") failed_launch();
   else CHECK(!"a scenario of that name");
   puts("ok");
 }
