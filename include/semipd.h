@@ -277,6 +277,11 @@ int spd_decode_step(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch* batch)
  * call makes the chunks longer, up to 247 pages (the result then equals spd_decode_step's within
  * rounding, not bit for bit).  A batch beyond either limit is refused with SPD_ETOOBIG and nothing is
  * enqueued.  Kernel timing (spd_set_kernel_timing) is not recorded for these steps.
+ * Under graph capture on the phase's stream (spd_phase_stream) the call is recorded with the batch as it is
+ * now: contexts, page ids, positions and RoPE frequencies are the captured call's at every replay, whatever
+ * steps run in between.  A captured call keeps its staging slot for good; as many calls can be captured as there are
+ * staging slots in the phase's ring (8), and with all of them captured this call returns SPD_ESTATE.  Replays are not
+ * seen by spd_kv_free: the pages of a captured batch must stay with their requests while the graph is in use.
  * The array is shared by every context and every call on that GPU and keeps the last call's contents
  * (nothing in it has to start at zero: each step writes every partial it later reads).  Steps of one
  * decode phase run in stream order and may follow one another freely, also mixed with spd_decode_step;

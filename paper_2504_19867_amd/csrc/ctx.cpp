@@ -149,6 +149,7 @@ extern "C" int spd_ctx_destroy(spd_ctx* ctx) {
       spd_phase_state& s = ctx->phase[ph];
       for (spd_stage& st : s.ring)
         if (st.host) (void)hipHostFree(st.host);
+      for (char* h : s.kept) (void)hipHostFree(h);
       for (spd_seal& seal : s.seals)
         if (seal.ev) (void)hipEventDestroy(seal.ev);
       if (s.flag) (void)hipHostFree(s.flag);
@@ -260,9 +261,21 @@ static bool flag_says_done(spd_phase_state& s, uint64_t seq) {
   return true;
 }
 
+bool stream_capturing(spd_ctx* ctx, hipStream_t stream) {
+  if (!ctx->phase[0].stream_lent.load(std::memory_order_relaxed) && !ctx->phase[1].stream_lent.load(std::memory_order_relaxed)) return false;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(stream, &status) == hipSuccess && status == hipStreamCaptureStatusActive;
+}
+
 int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool may_alloc) {
   spd_phase_state& s = ctx->phase[phase];
+  for (int i = 0; i < STAGE_SLOTS && s.ring[s.ring_pos].captured; ++i) s.ring_pos = (s.ring_pos + 1) % STAGE_SLOTS;
   spd_stage& st = s.ring[s.ring_pos];
+  if (st.captured) {                                     // all of them
+    if (!may_alloc) return SPD_ESTATE;
+    s.kept.push_back(st.host);
+    st = spd_stage();
+  }
   // The slot's last step is STAGE_SLOTS steps back: the step after it reports its end.  The word is polled, first in a
   // spin, then with pauses; the runtime is asked now and then only, because its calls keep the other phase's thread
   // from launching (and to notice a device error).
@@ -272,7 +285,9 @@ int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool m
       continue;
     }
     std::this_thread::sleep_for(std::chrono::microseconds(20));
-    if (spins % 64 == 0) {
+    if (spins % 64 == 0 && stream_capturing(ctx, s.stream)) {
+      (void)phase_step_done(ctx, phase, st.seq);         // (asks the step's event: this stream may not be asked now)
+    } else if (spins % 64 == 0) {
       const hipError_t e = hipStreamQuery(s.stream);
       if (e == hipSuccess) raise_done_seq(s, s.issue_seq.load(std::memory_order_relaxed));
       else if (e != hipErrorNotReady) return hip_fail(e);
@@ -290,23 +305,24 @@ int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool m
   return SPD_OK;
 }
 
-int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, hipStream_t stream) {
+int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, hipStream_t stream, bool capturing) {
   spd_phase_state& s = ctx->phase[phase];
+  st->captured = capturing;
   st->seq = s.issue_seq.fetch_add(1, std::memory_order_release) + 1;
   s.ring_pos = (s.ring_pos + 1) % STAGE_SLOTS;
-  return s.stream_lent.load(std::memory_order_relaxed) ? phase_seal(ctx, phase, stream) : SPD_OK;
+  return !capturing && s.stream_lent.load(std::memory_order_relaxed) ? phase_seal(ctx, phase, stream) : SPD_OK;
 }
 
-StepMark step_mark(spd_ctx* ctx, int phase) {
+StepMark step_mark(spd_ctx* ctx, int phase, bool capturing) {
   spd_phase_state& s = ctx->phase[phase];
-  return StepMark{s.flag_dev, s.issue_seq.load(std::memory_order_relaxed)};
+  return StepMark{capturing ? nullptr : s.flag_dev, s.issue_seq.load(std::memory_order_relaxed)};
 }
 
 int phase_seal(spd_ctx* ctx, int phase, hipStream_t stream) {
   spd_phase_state& s = ctx->phase[phase];
   std::lock_guard<std::mutex> lk(s.seal_mu);            // spd_phase_stream may be asked from any thread
   const uint64_t seq = s.issue_seq.load(std::memory_order_acquire);
-  if (seq == 0 || s.sealed_seq >= seq || flag_says_done(s, seq)) return SPD_OK;
+  if (seq == 0 || s.sealed_seq >= seq || flag_says_done(s, seq) || stream_capturing(ctx, stream)) return SPD_OK;
   spd_seal& seal = s.seals[s.seal_pos];
   SPD_HIP(hipEventRecord(seal.ev, stream));
   seal.seq.store(seq, std::memory_order_release);       // after the record
@@ -334,7 +350,7 @@ bool phase_step_done(spd_ctx* ctx, int phase, uint64_t seq) {
   const uint64_t issued = s.issue_seq.load(std::memory_order_acquire);
   hipStream_t stream;
   { std::lock_guard<std::mutex> lk(ctx->part_mu); stream = s.stream; }
-  if (issued >= seq && hipStreamQuery(stream) == hipSuccess) {
+  if (issued >= seq && !stream_capturing(ctx, stream) && hipStreamQuery(stream) == hipSuccess) {
     raise_done_seq(s, issued);
     return true;
   }

@@ -40,6 +40,6 @@ extern "C" int spd_ffn_gate_up(spd_ctx* ctx, int phase, const void* x, const voi
   if ((rc = phase_enter(ctx, phase, &stream)) != SPD_OK) return rc;
   if ((rc = kernel_timing_mark(ctx, phase, 0, stream)) != SPD_OK) return rc;
   SPD_HIP(launch_ffn_gate_up(x, w_gu, out, n_tokens, hidden, inter, ctx->xcds, std::max(1, ctx->phase[phase].active_cus),
-                             step_mark(ctx, phase), stream));
+                             step_mark(ctx, phase, stream_capturing(ctx, stream)), stream));
   return kernel_timing_mark(ctx, phase, 1, stream);
 }

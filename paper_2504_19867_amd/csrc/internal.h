@@ -168,6 +168,7 @@ struct spd_stage {          // pinned host buffer a step's metadata is read from
   char* dev = nullptr;      // the same buffer as the device addresses it
   size_t cap = 0;
   uint64_t seq = 0;         // number of the last step that used the slot (0: none)
+  bool captured = false;    // a graph's replays read the buffer: not handed round any more
 };
 
 // An event recorded behind a step, for the steps whose end no later step of the phase reports (see phase_seal).
@@ -185,6 +186,7 @@ struct spd_phase_state {
   std::vector<uint32_t> active_mask, pending_mask;
   spd_stage ring[spd::STAGE_SLOTS];
   int ring_pos = 0;
+  std::vector<char*> kept;             // buffers of captured steps whose slots have got new ones
   // One word of pinned memory per phase: the first kernel of every step stores the number of the step before it, which
   // the stream has finished by then.  Steps cost no event this way (an event record is 2 us of host time and 4 to 6 us
   // of the stream's).
@@ -237,30 +239,36 @@ int phase_enter(spd_ctx* ctx, int phase, hipStream_t* stream_out);   // adopt pe
 // may_alloc = false: SPD_ETOOBIG instead of growing the slot's buffers
 int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool may_alloc = true);
 int scratch_resolve(int device, char** out);   // noalloc.hip: address of `device`'s copy of the scratch array
-int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, hipStream_t stream);   // behind the step's last launch: the step has its number
+// behind the step's last launch: the step has its number
+int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, hipStream_t stream, bool capturing);
+// Is a graph being captured on the phase's stream?  (Only where the caller has been given a phase's stream.)
+bool stream_capturing(spd_ctx* ctx, hipStream_t stream);
 // A step from its first launch on.  One that returns before its commit may have launches in the queue that read the staging slot,
 // and its batch's requests carry its number: it counts as issued all the same, and what it left on the device (the
 // RoPE table) as unknown.
+// While a graph is captured on the stream the step's launches are only noted, to run at every replay: they then store no mark
+// and take nothing from the device that a later step may overwrite.
 struct StepScope {
   spd_ctx* ctx;
   int phase;
   spd_stage* st;
   hipStream_t stream;
-  bool open = true;
+  bool capturing, open = true;
+  StepScope(spd_ctx* c, int ph, spd_stage* s, hipStream_t str) : ctx(c), phase(ph), st(s), stream(str), capturing(stream_capturing(c, str)) {}
   int commit() {
     open = false;
-    return stage_commit(ctx, phase, st, stream);
+    return stage_commit(ctx, phase, st, stream, capturing);
   }
   ~StepScope() {
     if (!open) return;
     const int error = g_last_hip_error;
     ctx->phase[phase].rope_valid = false;
-    (void)stage_commit(ctx, phase, st, stream);
+    (void)commit();
     g_last_hip_error = error;
   }
 };
 // what the first kernel enqueued behind the phase's last step stores (see spd_phase_state::flag)
-StepMark step_mark(spd_ctx* ctx, int phase);
+StepMark step_mark(spd_ctx* ctx, int phase, bool capturing);
 // Before anything but a step's first kernel goes onto the phase's stream: an event behind the last step, unless that
 // step is known to have finished or has one.
 int phase_seal(spd_ctx* ctx, int phase, hipStream_t stream);
@@ -272,10 +280,10 @@ int kernel_timing_mark(spd_ctx* ctx, int phase, int which, hipStream_t stream); 
 int rope_config_check(const spd_rope_config* c);
 void rope_frequencies(const spd_rope_config* c, double* out);
 // The frequency table of `c` in device memory, valid for the phase's work enqueued from here on.  A configuration the
-// phase has not just used is written to a staging slot and copied by a launch of its own (rotary_dim <= ROPE_TABLE_DIM).
+// phase has not just used is written to a staging slot and copied by a launch of its own (rotary_dim <= ROPE_TABLE_DIM);
+// a captured step reads it there.
 constexpr int ROPE_TABLE_DIM = 1024;
-int rope_table(spd_ctx* ctx, int phase, const spd_rope_config* c, char* host, const char* host_dev, hipStream_t stream, StepMark* mark,
-               const double** out);
+int rope_table(const StepScope& step, const spd_rope_config* c, char* host, const char* host_dev, StepMark* mark, const double** out);
 
 // kernel launchers (kernels_*.hip); all enqueue on `stream` and return the launch status; `mark` is stored by the launch
 // where it is the first one behind a step (flag null: it is not)

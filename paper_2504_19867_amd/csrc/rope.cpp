@@ -44,15 +44,19 @@ void rope_frequencies(const spd_rope_config* c, double* out) {
 
 // `host` (device address `host_dev`): room for the table in the step's staging slot.  `mark` goes with the copy where
 // there is one, and is cleared then.
-int rope_table(spd_ctx* ctx, int phase, const spd_rope_config* c, char* host, const char* host_dev, hipStream_t stream, StepMark* mark,
-               const double** out) {
-  spd_phase_state& s = ctx->phase[phase];
+int rope_table(const StepScope& step, const spd_rope_config* c, char* host, const char* host_dev, StepMark* mark, const double** out) {
+  spd_phase_state& s = step.ctx->phase[step.phase];
+  if (step.capturing) {                // replays may come behind steps with other configurations, and this copy is not made now
+    rope_frequencies(c, (double*)host);
+    *out = (const double*)host_dev;
+    return SPD_OK;
+  }
   *out = s.rope_dev;
   static_assert(sizeof(spd_rope_config) == 4 * sizeof(double) + 4 * sizeof(int32_t), "compared byte by byte");
   if (s.rope_valid && std::memcmp(&s.rope_key, c, sizeof *c) == 0) return SPD_OK;
   s.rope_valid = false;
   rope_frequencies(c, (double*)host);
-  SPD_HIP(launch_meta_copy(s.rope_dev, host_dev, sizeof(double) * (size_t)(c->rotary_dim / 2), *mark, stream));
+  SPD_HIP(launch_meta_copy(s.rope_dev, host_dev, sizeof(double) * (size_t)(c->rotary_dim / 2), *mark, step.stream));
   mark->flag = nullptr;
   s.rope_key = *c;
   s.rope_valid = true;
@@ -101,7 +105,7 @@ extern "C" int spd_rope_qk(spd_ctx* ctx, int phase, const spd_rope_config* cfg, 
   st_rc = kernel_timing_mark(ctx, phase, 0, stream);
   if (st_rc != SPD_OK) return st_rc;
   SPD_HIP(launch_rope((void*)qq, hq, q ? k : nullptr, n_kv_heads, dim, cfg->rotary_dim, cfg->rotary_offset, cfg->interleaved != 0,
-                      n_tokens, (const int32_t*)(st->dev + w_bytes), (const double*)st->dev, step_mark(ctx, phase), stream));
+                      n_tokens, (const int32_t*)(st->dev + w_bytes), (const double*)st->dev, step_mark(ctx, phase, step.capturing), stream));
   st_rc = kernel_timing_mark(ctx, phase, 1, stream);
   if (st_rc != SPD_OK) return st_rc;
   return step.commit();

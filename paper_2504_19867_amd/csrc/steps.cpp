@@ -112,7 +112,7 @@ static int kv_copy(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t req_id, int
   if ((rc = phase_enter(ctx, phase, &stream)) != SPD_OK) return rc;
   StepScope step{ctx, phase, st, stream};
   const TileDesc* descs = (const TileDesc*)st->dev;              // read over PCIe, once per workgroup
-  const StepMark mark = step_mark(ctx, phase);
+  const StepMark mark = step_mark(ctx, phase, step.capturing);
   const bool fp8 = g.kind == SPD_KV_MLA_LATENT_FP8;
   if (write && fp8) SPD_HIP(launch_kv_write_fp8(g, pool->base, descs, n_descs, k, mark, stream));
   else if (write) SPD_HIP(launch_kv_write(g, pool->base, descs, n_descs, k, v, mark, stream));
@@ -274,7 +274,7 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   StepScope step{ctx, SPD_PHASE_PREFILL, st, stream};
   memcpy(st->host, work.data(), work.size() * sizeof(PrefillWork));
   memcpy(st->host + off_chain, chain.data(), chain.size() * sizeof(int32_t));
-  StepMark mark = step_mark(ctx, SPD_PHASE_PREFILL);
+  StepMark mark = step_mark(ctx, SPD_PHASE_PREFILL, step.capturing);
   const double* rope_w = nullptr;
   if (ctx->kernel_timing) SPD_HIP(hipEventRecord(ps.ev_start, stream));
   if (b->rope) {
@@ -284,7 +284,7 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
         for (int32_t i = b->cu_seqlens[r]; i < b->cu_seqlens[r + 1]; ++i)
           pos[i] = (chunked ? b->prefix_lens[r] : 0) + (i - b->cu_seqlens[r]);
     }
-    if ((rc = rope_table(ctx, SPD_PHASE_PREFILL, b->rope, st->host + off_w, st->dev + off_w, stream, &mark, &rope_w)) != SPD_OK) return rc;
+    if ((rc = rope_table(step, b->rope, st->host + off_w, st->dev + off_w, &mark, &rope_w)) != SPD_OK) return rc;
   }
   const void* page_src_k = g.kind == SPD_KV_GQA ? b->k : b->latent;
   const void* page_src_v = g.kind == SPD_KV_GQA ? b->v : nullptr;
@@ -461,9 +461,9 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   if ((rc = phase_enter(ctx, SPD_PHASE_DECODE, &stream)) != SPD_OK) return rc;
   StepScope step{ctx, SPD_PHASE_DECODE, st, stream};
   if (timing) SPD_HIP(hipEventRecord(ds.ev_start, stream));
-  StepMark mark = step_mark(ctx, SPD_PHASE_DECODE);
+  StepMark mark = step_mark(ctx, SPD_PHASE_DECODE, step.capturing);
   DecodeLaunch d{};
-  if (b->rope && (rc = rope_table(ctx, SPD_PHASE_DECODE, b->rope, st->host + bytes, st->dev + bytes, stream, &mark, &d.w)) != SPD_OK) return rc;
+  if (b->rope && (rc = rope_table(step, b->rope, st->host + bytes, st->dev + bytes, &mark, &d.w)) != SPD_OK) return rc;
   const char* meta = st->dev;
   if (twin && (!noalloc || bytes <= NOALLOC_TWIN_BYTES)) {
     char* to = noalloc ? ctx->scratch : ws + ws_o_bytes + ws_ml_bytes;

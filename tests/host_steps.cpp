@@ -14,6 +14,8 @@
 
 #include "internal.h"
 
+using namespace spd;
+
 #define CHECK(x) do { if (!(x)) { fprintf(stderr, "check failed: %s (line %d)\n", #x, __LINE__); exit(1); } } while (0)
 
 // ------------------------------------------------------------------------------------------ the runtime's stand-in
@@ -219,12 +221,54 @@ static void failed_launch() {
   for (uint64_t r = 1; r <= 4; ++r) CHECK(spd_kv_free(pool, r, nullptr) == SPD_OK);
 }
 
+// The step that allocates nothing, under graph capture on the phase's stream, which the caller has asked for: a replay reads what
+// the captured call was given, whatever steps and configurations have come in between, and reports no step's end.
+static void captured() {
+  const spd_rope_config a = rope(10000.0), b = rope(500000.0), c = rope(20000.0);
+  spd_phase_state& ps = ctx->phase[SPD_PHASE_DECODE];
+  void* handle;
+  CHECK(spd_phase_stream(ctx, SPD_PHASE_DECODE, &handle) == SPD_OK && handle == decode_stream());
+  std::vector<std::function<void()>> graph, graph2;
+  auto capture = [&](std::vector<std::function<void()>>* g, const spd_rope_config* r) -> int {
+    decode_stream()->graph = g;
+    const int rc = decode(2, r, true);
+    decode_stream()->graph = nullptr;
+    return rc;
+  };
+  auto last = [&](const spd_rope_config& r) { run(decode_stream()); return seen_w.back() == sum_w(r); };
+  CHECK(decode(1, &a) == SPD_OK && last(a));
+  CHECK(capture(&graph, &b) == SPD_OK);              // the first call with this configuration: nothing has run yet
+  CHECK(decode(3, &b) == SPD_OK && last(b));
+  CHECK(capture(&graph2, &b) == SPD_OK);             // and one whose frequencies are on the device
+  for (int round = 0; round < 3; ++round) {
+    for (int i = 0; i < 20; ++i) CHECK(decode(4, i % 2 ? &a : &c) == SPD_OK);
+    CHECK(last(a));
+    const uint64_t flag = *ps.flag;
+    for (auto* g : {&graph, &graph2}) {
+      for (auto& node : *g) put((hipStream_t)decode_stream(), node);
+      CHECK(last(b));
+    }
+    CHECK(*ps.flag == flag);
+  }
+  // as many captured calls as there are staging slots; then steps that may allocate go on, the others are refused
+  int more = 0, rc;
+  std::vector<std::function<void()>> rest;
+  while ((rc = capture(&rest, &a)) == SPD_OK) CHECK(++more < STAGE_SLOTS);
+  CHECK(rc == SPD_ESTATE && more + 2 == STAGE_SLOTS);
+  for (int i = 0; i < 20; ++i) CHECK(decode(4, &c) == SPD_OK && last(c));
+  CHECK(decode(4, &c, true) == SPD_OK);              // (the slots that the steps in between have brought)
+  for (auto& node : graph) put((hipStream_t)decode_stream(), node);
+  CHECK(last(b));
+  for (uint64_t r = 1; r <= 4; ++r) CHECK(spd_kv_free(pool, r, nullptr) == SPD_OK);
+}
+
 int main(int argc, char** argv) {
   CHECK(argc == 2);
   const std::string name = argv[1];
   setup();
   if (name == "refused_copies") refused_copies();
   else if (name == "failed_launch") failed_launch();
+  else if (name == "captured") captured();
   else CHECK(!"a scenario of that name");
   puts("ok");
 }

@@ -1,6 +1,7 @@
 """The decode step that allocates nothing (spd_decode_step_noalloc), through the C ABI: its output against
 spd_decode_step's on the same inputs (same kernels: bit for bit, which is inside the parity bar) and
 against the fp64 oracle, on two calls in a row, the second with a smaller batch; the limits are enforced."""
+import ctypes as C
 import math
 
 import numpy as np
@@ -158,4 +159,50 @@ def test_noalloc_latent_decode_with_chunks_lengthened_to_fit():
             assert_parity(host_f64(o[i:i + 1]), want, f"request {i}")
     # two bf16 roundings of sums whose bf16 weights differ by their rounding: 2^-8 of the largest output, which is below 1
     assert (out[0].float() - out[1].float()).abs().max() < 2 ** -7
+    gp.close()
+
+
+@pytest.mark.parametrize("lens", [(700, 33, 1), tuple(300 + 37 * (i % 29) for i in range(90))], ids=["few", "many"])
+def test_noalloc_decode_in_a_graph(lens):
+    """Captured on the phase's stream, then replayed with other steps, other batches and other RoPE configurations in between: every
+    replay gives what the eager call gives for the query that is there at the time."""
+    hip = S.lib                                          # (the runtime that the library is linked to)
+    layer = W.LayerShape("gqa", 8, 8, 128, 128, 16)
+    gp = GpuPool(layer, sum(-(-n // 16) for n in lens) + 8)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(8)
+    gp.mem.view(torch.bfloat16).normal_(generator=gen)   # any page contents are rows
+    ids = list(range(1, len(lens) + 1))
+    for i, n in zip(ids, lens):
+        gp.pool.kv_reserve(i, n)
+    cfg, other = S.rope_config(theta=500000.0, factor=8.0), S.rope_config(theta=10000.0)
+    q = torch.empty((len(lens), 8, 128), dtype=torch.bfloat16, device=DEV).normal_(generator=gen)
+    out, eager, scrap = (torch.full_like(q, float("nan")) for _ in range(3))
+    batch = gp.pool.make_decode_batch(ids, lens, q, out, 8, 0.09, rope=cfg)
+    torch.cuda.synchronize()
+    stream = C.c_void_p(gp.ctx.phase_stream(DEC))
+    gp.pool.decode_step(ids, lens, q, scrap, 8, 0.09, rope=other)
+    gp.ctx.phase_sync(DEC)
+    graph, run = C.c_void_p(), C.c_void_p()
+    assert hip.hipStreamBeginCapture(stream, 1) == 0     # thread local
+    gp.pool.decode_step_noalloc_batch(batch)
+    assert hip.hipStreamEndCapture(stream, C.byref(graph)) == 0
+    assert hip.hipGraphInstantiate(C.byref(run), graph, None, None, C.c_uint64(0)) == 0
+    for round in range(4):
+        gp.pool.decode_step(ids, lens, q, eager, 8, 0.09, rope=cfg)
+        for i in range(12):                              # more than there are staging slots
+            gp.pool.decode_step(ids[:1 + i % 3], lens[:1 + i % 3], q, scrap, 8, 0.05, rope=other)
+        if round % 2:
+            gp.ctx.phase_sync(DEC)
+        assert hip.hipGraphLaunch(run, stream) == 0
+        gp.pool.decode_step(ids, lens, q, scrap, 8, 0.09, rope=other)
+        gp.ctx.phase_sync(DEC)
+        assert torch.isfinite(eager).all() and np.array_equal(host_bits(out), host_bits(eager)), f"replay {round}"
+        q.normal_(generator=gen)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+    gp.ctx.phase_sync(DEC)
+    assert hip.hipGraphExecDestroy(run) == 0 and hip.hipGraphDestroy(graph) == 0
+    for i in ids:
+        gp.pool.kv_free(i)
     gp.close()
