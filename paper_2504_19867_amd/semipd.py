@@ -176,12 +176,12 @@ _prefill_entry, _decode_entry = _entry("spd_prefill_step"), _entry("spd_decode_s
 
 
 def _numbers(code: str, values) -> array:
-    """A C array of `values` (array typecode Q or i)."""
+    """A C array of `values`: request ids (typecode Q) or token counts (i), as make_prefill_batch and make_decode_batch take them."""
     try:
         return array(code, values)
-    except (TypeError, OverflowError):  # floats and the like, as int() takes them; out of range, as ctypes wraps them
-        kind = C.c_uint64 if code == "Q" else C.c_int32
-        return array(code, bytes((kind * len(values))(*[int(x) for x in values])))
+    except (TypeError, OverflowError):  # out of range: as ctypes wraps them; counts that are floats and the like: as int() takes them
+        kind, values = (C.c_uint64, values) if code == "Q" else (C.c_int32, [int(x) for x in values])
+        return array(code, bytes((kind * len(values))(*values)))
 
 
 def strerror(status: int) -> str:
@@ -206,6 +206,14 @@ def _ptr(x) -> Optional[int]:
     if hasattr(x, "data_ptr"):
         return x.data_ptr()
     return int(x)
+
+
+def _rope_address(rope) -> int:
+    if rope is None:
+        return 0
+    if not isinstance(rope, spd_rope_config):
+        raise TypeError
+    return C.addressof(rope)
 
 
 def rope_config(theta: float = 500000.0, factor: float = 1.0, low_freq_factor: float = 1.0, high_freq_factor: float = 4.0,
@@ -492,14 +500,17 @@ class Pool:
                      n_kv_heads: int, dim_qk: int, dim_v: int, scale: float, latent=None, prefix_lens=None,
                      rope: Optional[spd_rope_config] = None) -> None:
         ids, cu = _numbers("Q", req_ids), _numbers("i", cu_seqlens)
+        pre = _numbers("i", prefix_lens) if prefix_lens is not None else None
         n = len(ids)
-        if len(cu) != n + 1 or (prefix_lens is not None and len(prefix_lens) != n):
+        try:
+            if len(cu) != n + 1 or (pre is not None and len(pre) != n):
+                raise ValueError
+            args = _pack_prefill(n, ids.buffer_info()[0], cu.buffer_info()[0], _ptr(q) or 0, _ptr(k) or 0, _ptr(v) or 0, _ptr(latent) or 0,
+                                 _ptr(out) or 0, n_q_heads, n_kv_heads, dim_qk, dim_v, scale, pre.buffer_info()[0] if pre is not None else 0,
+                                 _rope_address(rope))
+        except (ValueError, TypeError, OverflowError, struct.error):      # what the packing does not take: as ctypes takes or refuses it
             return self.prefill_step_batch(self.make_prefill_batch(req_ids, cu_seqlens, q, k, v, out, n_q_heads, n_kv_heads,
                                                                    dim_qk, dim_v, scale, latent, prefix_lens, rope))
-        pre = _numbers("i", prefix_lens) if prefix_lens is not None else None
-        args = _pack_prefill(n, ids.buffer_info()[0], cu.buffer_info()[0], _ptr(q) or 0, _ptr(k) or 0, _ptr(v) or 0, _ptr(latent) or 0,
-                             _ptr(out) or 0, n_q_heads, n_kv_heads, dim_qk, dim_v, scale, pre.buffer_info()[0] if pre is not None else 0,
-                             C.addressof(rope) if rope is not None else 0)
         status = _prefill_entry(self.ctx.h, self.h, args)
         if status != SPD_OK:
             _check(status, "spd_prefill_step")
@@ -561,10 +572,13 @@ class Pool:
 
     def decode_step(self, req_ids, ctx_lens, q, out, n_q_heads: int, scale: float, k_new=None, v_new=None, rope=None) -> None:
         ids, lens = _numbers("Q", req_ids), _numbers("i", ctx_lens)
-        if len(ids) != len(lens):
+        try:
+            if len(ids) != len(lens):
+                raise ValueError
+            args = _pack_decode(len(ids), ids.buffer_info()[0], lens.buffer_info()[0], _ptr(q) or 0, _ptr(k_new) or 0, _ptr(v_new) or 0,
+                                _ptr(out) or 0, n_q_heads, scale, _rope_address(rope))
+        except (ValueError, TypeError, OverflowError, struct.error):
             return self.decode_step_batch(self.make_decode_batch(req_ids, ctx_lens, q, out, n_q_heads, scale, k_new, v_new, rope))
-        args = _pack_decode(len(ids), ids.buffer_info()[0], lens.buffer_info()[0], _ptr(q) or 0, _ptr(k_new) or 0, _ptr(v_new) or 0,
-                            _ptr(out) or 0, n_q_heads, scale, C.addressof(rope) if rope is not None else 0)
         status = _decode_entry(self.ctx.h, self.h, args)
         if status != SPD_OK:
             _check(status, "spd_decode_step")

@@ -466,3 +466,34 @@ def test_ffn_argument_checks_on_a_host_only_context():
     # well-formed, but this context has no device
     assert lib.spd_ffn_gate_up(ctx.h, 0, 4096, 4096, 4096, 4, 64, 128) == S.SPD_ESTATE
     assert lib.spd_ffn_pack_gate_up(ctx.h, 1, 4096, 4096, 4096, 64, 128) == S.SPD_ESTATE
+
+
+def _outcome(call):
+    try:
+        call()
+        return None
+    except S.SpdError as e:
+        return e.status
+    except Exception as e:
+        return type(e)
+
+
+def test_packed_step_arguments_are_taken_and_refused_as_the_structures_are():
+    """prefill_step and decode_step pack their arguments into bytes, make_*_batch fills ctypes structures: the same calls go through
+    to the library (which answers on a host-only context), the same ones raise."""
+    ctx, pool = host_pool()
+    cfg, wrong = S.rope_config(rotary_dim=64), S.spd_pool_desc()
+    decode = dict(req_ids=[1, 2], ctx_lens=[3, 4], q=64, out=64, n_q_heads=4, scale=0.1)
+    prefill = dict(req_ids=[1, 2], cu_seqlens=[0, 3, 7], q=64, k=64, v=64, out=64, n_q_heads=4, n_kv_heads=2, dim_qk=64, dim_v=64, scale=0.1)
+    common = [{}, dict(rope=cfg), dict(rope=wrong), dict(rope=5), dict(scale=1e300), dict(scale=float("nan")), dict(scale="x"), dict(n_q_heads=4.0),
+              dict(n_q_heads=2 ** 31), dict(n_q_heads=2 ** 40 + 4), dict(n_q_heads=np.int64(4)), dict(req_ids=[1.0, 2.0]),
+              dict(req_ids=[-1, 2 ** 70]), dict(req_ids=np.array([1, 2])), dict(req_ids=(1, 2)), dict(req_ids=[1]), dict(req_ids=["1", "2"]),
+              dict(q=None), dict(q=-64), dict(q=2 ** 64 + 64), dict(q="x"), dict(scale=np.float32(0.1))]
+    for changes in common + [dict(ctx_lens=x) for x in ([3.0, 4.5], [3], [3, 4, 5], [2 ** 32 + 3, 4], [-1, 4], np.array([3, 4]), ["3", "4"])]:
+        args = {**decode, **changes}
+        assert _outcome(lambda: pool.decode_step(**args)) == _outcome(lambda: pool.decode_step_batch(pool.make_decode_batch(**args))), changes
+    for changes in common + [dict(cu_seqlens=x) for x in ([0, 3.5, 7.0], [0, 3], [0, 3, 7, 9], [0, 2 ** 32 + 3, 7])] + \
+            [dict(prefix_lens=x) for x in ([0, 5], [0], [0, 5, 6], [0.0, 5.0], [-1, 5])] + [dict(dim_v=64.0), dict(latent=64)]:
+        args = {**prefill, **changes}
+        assert _outcome(lambda: pool.prefill_step(**args)) == _outcome(lambda: pool.prefill_step_batch(pool.make_prefill_batch(**args))), changes
+    assert _outcome(lambda: pool.decode_step(**decode)) == S.SPD_ESTATE and _outcome(lambda: pool.prefill_step(**prefill)) == S.SPD_ESTATE
