@@ -276,17 +276,19 @@ int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool m
     s.kept.push_back(st.host);
     st = spd_stage();
   }
-  // The slot's last step is STAGE_SLOTS steps back: the step after it reports its end.  The word is polled, first in a
+  // The slot's last step has to be over, and the one STEPS_IN_FLIGHT steps back: what is queued still runs on the share it was
+  // issued for, and a new partition is behind it.  The step after that one reports its end.  The word is polled, first in a
   // spin, then with pauses; the runtime is asked now and then only, because its calls keep the other phase's thread
   // from launching (and to notice a device error).
-  for (int spins = 0; st.seq && !flag_says_done(s, st.seq); ++spins) {
+  const uint64_t over = std::max(st.seq, s.recent[s.recent_pos]);
+  for (int spins = 0; over && !flag_says_done(s, over); ++spins) {
     if (spins < 4096) {
       __builtin_ia32_pause();
       continue;
     }
     std::this_thread::sleep_for(std::chrono::microseconds(20));
     if (spins % 64 == 0 && stream_capturing(ctx, s.stream)) {
-      (void)phase_step_done(ctx, phase, st.seq);         // (asks the step's event: this stream may not be asked now)
+      (void)phase_step_done(ctx, phase, over);           // (asks the step's event: this stream may not be asked now)
     } else if (spins % 64 == 0) {
       const hipError_t e = hipStreamQuery(s.stream);
       if (e == hipSuccess) raise_done_seq(s, s.issue_seq.load(std::memory_order_relaxed));
@@ -309,6 +311,10 @@ int stage_commit(spd_ctx* ctx, int phase, spd_stage* st, hipStream_t stream, boo
   spd_phase_state& s = ctx->phase[phase];
   st->captured = capturing;
   st->seq = s.issue_seq.fetch_add(1, std::memory_order_release) + 1;
+  if (!capturing) {
+    s.recent[s.recent_pos] = st->seq;
+    s.recent_pos = (s.recent_pos + 1) % STEPS_IN_FLIGHT;
+  }
   s.ring_pos = (s.ring_pos + 1) % STAGE_SLOTS;
   return !capturing && s.stream_lent.load(std::memory_order_relaxed) ? phase_seal(ctx, phase, stream) : SPD_OK;
 }

@@ -134,7 +134,8 @@ constexpr size_t NOALLOC_TWIN_BYTES = 4 * NOALLOC_STAGE_BYTES;   // a longer bat
 constexpr size_t NOALLOC_RING_BYTES = 9 * NOALLOC_STAGE_BYTES;
 constexpr size_t MERGE_COUNTERS = 4096;
 constexpr int MERGE_IN_LAUNCH_CHUNKS = 16; // most chunks of a request that a workgroup of the attention launch merges on the side
-constexpr int STAGE_SLOTS = 8;             // steps of a phase in flight before a new one waits for the oldest
+constexpr int STAGE_SLOTS = 8;             // staging slots of a phase (captured steps keep theirs)
+constexpr int STEPS_IN_FLIGHT = 4;         // steps of a phase in flight before a new one waits for the oldest
 constexpr size_t SCRATCH_BYTES = NOALLOC_TWIN_BYTES + NOALLOC_WS_BYTES;
 
 extern thread_local int g_last_hip_error;
@@ -186,6 +187,8 @@ struct spd_phase_state {
   std::vector<uint32_t> active_mask, pending_mask;
   spd_stage ring[spd::STAGE_SLOTS];
   int ring_pos = 0;
+  uint64_t recent[spd::STEPS_IN_FLIGHT] = {};   // numbers of the last steps that were issued, not captured; oldest at recent_pos
+  int recent_pos = 0;
   std::vector<char*> kept;             // buffers of captured steps whose slots have got new ones
   // One word of pinned memory per phase: the first kernel of every step stores the number of the step before it, which
   // the stream has finished by then.  Steps cost no event this way (an event record is 2 us of host time and 4 to 6 us

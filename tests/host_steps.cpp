@@ -262,6 +262,19 @@ static void captured() {
   for (uint64_t r = 1; r <= 4; ++r) CHECK(spd_kv_free(pool, r, nullptr) == SPD_OK);
 }
 
+// A call blocks while four steps of its phase are in flight: what has been issued runs on the share of its time, and a new
+// partition waits for no more than that.
+static void in_flight() {
+  for (int i = 0; i < 4; ++i) {
+    CHECK(decode(1) == SPD_OK);
+    CHECK((int)decode_stream()->queue.size() == i + 1);
+  }
+  for (int i = 0; i < 20; ++i) {
+    CHECK(decode(1) == SPD_OK);
+    CHECK(decode_stream()->queue.size() <= 4);       // (the wait lets the stream go on)
+  }
+}
+
 int main(int argc, char** argv) {
   CHECK(argc == 2);
   const std::string name = argv[1];
@@ -269,6 +282,7 @@ int main(int argc, char** argv) {
   if (name == "refused_copies") refused_copies();
   else if (name == "failed_launch") failed_launch();
   else if (name == "captured") captured();
+  else if (name == "in_flight") in_flight();
   else CHECK(!"a scenario of that name");
   puts("ok");
 }
