@@ -107,7 +107,7 @@ struct DecodeLaunch {
   int max_chunks;
   int rot, off, interleaved;          // rot = 0: no rotation
   float *ws_o, *ws_ml;
-  uint32_t* counters;                 // [B * Hkv] zeros: the chunks are merged by the last workgroup; null: by a launch of its own
+  uint32_t* counters;                 // [B * Hkv] zeros: the chunks are merged by the last workgroup (GQA); null: by a launch of its own
   StepMark mark;
 };
 

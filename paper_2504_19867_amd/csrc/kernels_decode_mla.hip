@@ -76,7 +76,6 @@ struct MlaArgs {
   const double* w;
   int rot, off, interleaved;
   float *ws_o, *ws_ml;
-  uint32_t* counters;
   StepMark mark;
 };
 
@@ -118,7 +117,6 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   __shared__ float sm_cs[128], sm_sn[128];         // rotary_dim <= 256
   __shared__ int32_t sm_rec[64 * WAVES];           // header and page ids, a word per thread
   __shared__ __attribute__((aligned(16))) char sm_new[ROW_BYTES];
-  __shared__ uint32_t sm_last;
   if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(a.mark);
   static_assert(DECODE_ITEM_WORDS + MLA_CHUNK_PAGES <= 64 * WAVES, "one thread per word of a record");
   const int words = a.item_stride >> 2;
@@ -451,7 +449,6 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     if (wave == 0) sm_m[WAVES][col] = m_tot * a.c;
   }
   float* so = (float*)smem;                        // [wave][head][half of the dims]
-  const bool shared = a.counters != nullptr;
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     if (half) __syncthreads();
@@ -479,21 +476,10 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
         *(uint2*)(a.out + head * DV + half * (DV / 2) + d) = uint2{mla_pack_bf16(o[0] * inv, o[1] * inv), mla_pack_bf16(o[2] * inv, o[3] * inv)};
       } else {
         const size_t slot = head * a.max_chunks + chunk;
-        float* po = a.ws_o + slot * DV + half * (DV / 2) + d;
-        if (shared) {
-          store_partial(po, o[0], o[1], true);
-          store_partial(po + 2, o[2], o[3], true);
-        } else {
-          *(f32x4*)po = o;
-        }
-        if (half == 0 && lane == 0) store_partial(a.ws_ml + slot * 2, sm_m[WAVES][h], lt, shared);
+        *(f32x4*)(a.ws_o + slot * DV + half * (DV / 2) + d) = o;
+        if (half == 0 && lane == 0) store_partial(a.ws_ml + slot * 2, sm_m[WAVES][h], lt, false);
       }
     }
-  }
-  // ---- few chunks: the workgroup that finds itself to be the request's last one merges them
-  if (n_chunks > 1 && shared && last_of(a.counters + b, (uint32_t)n_chunks, &sm_last)) {
-    const size_t slot0 = (size_t)b * a.H * a.max_chunks;
-    merge_in_launch<DV, 64 * WAVES>(a.ws_o + slot0 * DV, a.ws_ml + slot0 * 2, a.H, a.max_chunks, n_chunks, so, a.out + (size_t)b * a.H * DV);
   }
   if (idx < 0) break;
   __syncthreads();                                 // LDS belongs to the next chunk
@@ -509,12 +495,12 @@ hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLau
   a.c = d.scale * 1.4426950408889634f;
   a.max_chunks = d.max_chunks;
   a.w = d.w; a.rot = d.rot; a.off = d.off; a.interleaved = d.interleaved;
-  a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.counters = d.counters; a.mark = d.mark;
+  a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.mark = d.mark;
   const dim3 grid((unsigned)d.n_wgs), block(64 * mla::WAVES);
   if (g.kind == SPD_KV_MLA_LATENT_FP8) hipLaunchKernelGGL(decode_mla_kernel<true>, grid, block, 0, stream, a);
   else hipLaunchKernelGGL(decode_mla_kernel<false>, grid, block, 0, stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || d.max_chunks <= 1 || d.counters) return e;
+  if (e != hipSuccess || d.max_chunks <= 1) return e;
   return launch_merge_chunks<mla::DV>(d, stream);
 }
 

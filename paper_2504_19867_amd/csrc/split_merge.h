@@ -1,7 +1,7 @@
 // Split-K partials of the decode kernels: how they are stored, and the two ways of merging them.
 //
 // A launch of its own for the merge costs 2.6 us of host time and a gap on the stream beside its own 4 to 5 us.  So where a
-// request has few chunks (the host says so by handing out counters) the workgroup that a counter finds to be the last
+// request has few chunks (the host says so by handing out counters; GQA pools only) the workgroup that a counter finds to be the last
 // of its group merges the group's chunks.  The eight XCDs' L2s are not coherent with each other inside a launch: partials
 // and counters are stored and loaded at agent scope, past the L2, and no fence (a write-back and invalidation of the whole
 // L2) is needed.
@@ -42,7 +42,7 @@ __device__ inline void merge_in_launch(const float* o, const float* ml, int rows
   auto load2 = [](const float* p) -> f32x2_ {
     return __builtin_bit_cast(f32x2_, __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   };
-  constexpr int NC = MERGE_IN_LAUNCH_CHUNKS, PAIRS = D / 2, BATCH = 4, RB = D > 256 ? 4 : 2;
+  constexpr int NC = MERGE_IN_LAUNCH_CHUNKS, PAIRS = D / 2, BATCH = 4, RB = 2;
   float *sm = lds, *sl = lds + 16 * NC;
   const int tid = threadIdx.x;
   __syncthreads();
@@ -53,7 +53,7 @@ __device__ inline void merge_in_launch(const float* o, const float* ml, int rows
   }
   __syncthreads();
   // a thread keeps its pair of dims and walks over the rows, RB rows by BATCH chunks of loads in flight
-  constexpr int STEP = THREADS / PAIRS < 1 ? 1 : THREADS / PAIRS;     // rows side by side
+  constexpr int STEP = THREADS / PAIRS;            // rows side by side
   static_assert(THREADS % PAIRS == 0, "whole rows");
   const int pr = 2 * (tid % PAIRS);
   for (int r0 = tid / PAIRS; r0 < rows; r0 += RB * STEP) {

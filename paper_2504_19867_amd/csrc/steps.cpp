@@ -404,9 +404,13 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   // Few workgroups read their records straight out of the pinned staging buffer: a launch less.  Above 1024 records of
   // 64 bytes that takes longer than the launch that copies them to the device (PCIe, 1.3 us per round trip).
   const bool twin = (size_t)n_items * g.Hkv * stride > 131072;
-  // Split-K partials are merged by the attention launch itself where a request has few chunks and the launch few workgroups
-  // (each pays for going past the L2), else by a launch of its own
-  const bool inline_merge = n_wgs <= (mla ? 128 : 512) && max_chunks <= MERGE_IN_LAUNCH_CHUNKS && (size_t)B * g.Hkv <= MERGE_COUNTERS;
+  // Split-K partials of a GQA launch of few workgroups are merged by that launch, where a request has few chunks; else by a
+  // launch of its own.  Whole step over 128-dim heads, in the launch / on its own: 24 workgroups, 3 chunks 9.1 / 10.9 us; 192, 9
+  // chunks 11.4 / 12.2 on 128 CUs; 400, 9 chunks 14.1 / 15.1 on 256; level from 500 to 1100 workgroups; 1392, 16 chunks 51.0 / 48.0
+  // (each workgroup pays for going past the L2).  Never for latent pools: their partials are four times as long, and the one
+  // workgroup that merges a request's 16 heads was 7 to 19 us at it (1 request of 4000 tokens in 16 chunks 39.6 / 20.4 us, 16 of 300
+  // tokens 22.7 / 19.4).
+  const bool inline_merge = !mla && n_wgs <= 512 && max_chunks <= MERGE_IN_LAUNCH_CHUNKS && (size_t)B * g.Hkv <= MERGE_COUNTERS;
   char* ws = nullptr;
   const size_t ws_o_bytes = partial_o_bytes(B, b->n_q_heads, max_chunks, g.dv), ws_ml_bytes = partial_ml_bytes(B, b->n_q_heads, max_chunks);
   const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + (twin && !noalloc ? bytes : 0);

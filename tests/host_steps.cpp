@@ -30,6 +30,7 @@ static std::vector<Stream*> streams;
 static long n_pinned = 0, pinned_bytes = 0, n_device = 0;   // allocations so far
 static int fail_launch = -1;                    // the launch of this number fails
 static int n_launches = 0;
+static std::vector<bool> seen_counters;         // may the decode launch merge its own chunks?
 static std::vector<double> seen_w;              // sum of the RoPE frequencies that each decode launch found when it ran
 
 static void put(hipStream_t s, std::function<void()> f) {
@@ -130,6 +131,7 @@ hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const St
   return launch(s, m, [=] { memcpy(dst, src, bytes); });
 }
 hipError_t launch_decode_gqa(const PoolGeom&, char*, const DecodeLaunch& d, hipStream_t s) {
+  seen_counters.push_back(d.counters != nullptr);
   return launch(s, d.mark, [d] {
     double sum = 0;
     for (int i = 0; i < d.rot / 2; ++i) sum += d.w[i];
@@ -275,6 +277,24 @@ static void in_flight() {
   }
 }
 
+// A few chunks of a GQA launch are merged by the launch, those of a latent one (16 heads, one merging workgroup per request) never.
+static void merges() {
+  const spd_pool_desc desc = {SPD_KV_MLA_LATENT, 64, 1, 576, 512, 64};
+  spd_pool* latent;
+  uint64_t bytes, req = 9;
+  CHECK(spd_pool_bytes(&desc, &bytes) == SPD_OK);
+  CHECK(spd_pool_create(ctx, aligned_alloc(4096, bytes), bytes, &desc, &latent) == SPD_OK);
+  CHECK(spd_kv_reserve(latent, req, 4000, nullptr) == SPD_OK && spd_kv_reserve(pool, req, 700, nullptr) == SPD_OK);
+  for (const int32_t n : {100, 600, 1500, 4000}) {
+    const spd_decode_batch b = {1, &req, &n, tensor, nullptr, nullptr, tensor, 16, 0.1f, nullptr};
+    CHECK(spd_decode_step(ctx, latent, &b) == SPD_OK && !seen_counters.back());
+    CHECK(spd_decode_step_noalloc(ctx, latent, &b) == SPD_OK && !seen_counters.back());
+  }
+  const int32_t n = 700;
+  const spd_decode_batch b = {1, &req, &n, tensor, nullptr, nullptr, tensor, 16, 0.1f, nullptr};
+  CHECK(spd_decode_step(ctx, pool, &b) == SPD_OK && seen_counters.back());
+}
+
 int main(int argc, char** argv) {
   CHECK(argc == 2);
   const std::string name = argv[1];
@@ -283,6 +303,7 @@ int main(int argc, char** argv) {
   else if (name == "failed_launch") failed_launch();
   else if (name == "captured") captured();
   else if (name == "in_flight") in_flight();
+  else if (name == "merges") merges();
   else CHECK(!"a scenario of that name");
   puts("ok");
 }
