@@ -107,6 +107,7 @@ struct DecodeLaunch {
   int max_chunks;
   int rot, off, interleaved;          // rot = 0: no rotation
   float *ws_o, *ws_ml;
+  bool prepared;                      // GQA: launch_decode_prepare has rotated and appended
   uint32_t* counters;                 // [B * Hkv] zeros: the chunks are merged by the last workgroup (GQA); null: by a launch of its own
   StepMark mark;
 };
@@ -322,6 +323,9 @@ hipError_t launch_kv_write_fp8(const PoolGeom& g, char* pool_base, const TileDes
 hipError_t launch_kv_gather_fp8(const PoolGeom& g, const char* pool_base, const TileDesc* d_tiles, int n_tiles, void* out,
                                 const StepMark& mark, hipStream_t stream);
 hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const StepMark& mark, hipStream_t stream);
+// What `d` rotates and appends, ahead of the attention launch: its queries are rotated to q_rot (with d.rot), the new tokens go into
+// their pages (with d.k_new).  d.items: n_items records in device memory.
+hipError_t launch_decode_prepare(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, int n_items, void* q_rot, hipStream_t stream);
 hipError_t launch_decode_gqa(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream);
 hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream);
 // The latent decode's workgroup fetches a record one word per thread and keeps it in LDS: as many pages as that leaves a chunk

@@ -35,7 +35,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t pack_bf16_rne(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
-__device__ inline bf16_t to_bf16_rne(float a) { return (bf16_t)(pack_bf16_rne(a, 0.f) & 0xffffu); }
 
 template <int D>
 struct TileFrag {          // two 16-token tiles, K and V parts, in operand order
@@ -165,10 +164,11 @@ __device__ inline void compute_step(const TileFrag<D>& f, const bf16x8 (&qf)[D /
   }
 }
 
-// The attention launch is the whole step: it rotates its query heads (RoPE), rotates the new token's key and puts key
-// and value into their page (the workgroup of the request's last chunk, per KV head), and attends to the context with
-// that token included.  As launches of their own the append and the rotation cost 5.6 us per step, and more than the
-// attention itself in a batch of a few short contexts.
+// Where a share has few workgroups the attention launch is the whole step: it rotates its query heads (RoPE), rotates the new
+// token's key and puts key and value into their page (the workgroup of the request's last chunk, per KV head), and attends
+// to the context with that token included.  As launches of their own the append and the rotation cost 5.6 us per step,
+// and more than the attention itself in a batch of a few short contexts.  Where a compute unit has many workgroups
+// they pay for that in turn, and decode_prepare_kernel does it for all of them.
 struct GqaArgs {
   char* pool;
   uint64_t page_bytes;
@@ -190,8 +190,15 @@ struct GqaArgs {
 // grid (n_items * n_kv_heads), block 256; workgroup i serves KV head i % n_kv_heads of work item
 // i / n_kv_heads.  Heads vary fastest so that the round-robin placement of
 // workgroups on the 8 XCDs gives every XCD the same mix of long and short chunks.
-template <int D>
+// WHOLE: the launch rotates and appends too; otherwise decode_prepare_kernel has, and this kernel's workgroups, of which a compute
+// unit then has many in turn, start without that code.
+template <int D, bool WHOLE>
 __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
+  if constexpr (!WHOLE) {
+    a.rot = 0;
+    a.k_new = nullptr;
+    a.mark.flag = nullptr;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(a.mark);
   const int g = blockIdx.x % a.Hkv;
   const char* rec = a.items + (size_t)(blockIdx.x / a.Hkv) * a.item_stride;
@@ -380,8 +387,79 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
   merge_in_launch<D, 256>(a.ws_o + slot0 * D, a.ws_ml + slot0 * 2, a.G, a.max_chunks, n_chunks, &sm_o[0][0][0], a.out + head0 * D);
 }
 
+// What the attention launch would otherwise do in every workgroup, done once per request: the queries are rotated into q_rot, the
+// new token's key (rotated) and value go into their page.  Same arithmetic as in the attention launch, so the step's results do
+// not depend on which of the two does it.  The records are read in device memory: read in pinned memory by a workgroup
+// each they take 9 to 16 us (the more compute units ask, the longer), copied by a few workgroups beforehand 3.4.
+// grid (n_items), block 256: the workgroup of a request's last chunk does the request.  Bound by latency: record, then rows.
+// 256 requests of 15 .. 45 tokens, 32 query and 8 KV heads with RoPE, whole step: with everything in the attention launch 140 us on
+// 64 CUs and 72 on 128, now 67 and 40.
 template <int D>
-static hipError_t launch_decode_gqa_t(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream) {
+__global__ __launch_bounds__(256) void decode_prepare_kernel(GqaArgs a, bf16_t* __restrict__ q_rot) {
+  const int tid = threadIdx.x;
+  const int32_t* head = (const int32_t*)(a.items + (size_t)blockIdx.x * a.item_stride);
+  __shared__ float cs[D / 2], sn[D / 2];
+  const double w = tid < (a.rot >> 1) ? a.w[tid] : 0.0;
+  const int last_page = head[(a.item_stride >> 2) - 1];          // (a record's end repeats the chunk's last page)
+  const int b = head[0], n = head[3], n_tiles = (n + TILE_T - 1) / TILE_T;
+  if (head[4] + head[5] != n_tiles) return;        // not the request's last chunk
+  const bool interleaved = a.interleaved != 0;
+  constexpr int PCS = D / 8, BATCH = 4;            // 16-byte pieces of a head; loads on their way per thread
+  const int n_q = a.rot ? a.H * PCS : 0, n_k = a.k_new ? a.Hkv * PCS : 0, n_v = a.k_new ? a.Hkv * D : 0;
+  const bf16_t *q = a.q + (size_t)b * a.H * D, *k_new = a.k_new + (size_t)b * a.Hkv * D, *v_new = a.v_new + (size_t)b * a.Hkv * D;
+  auto load = [&](const bf16_t* rows, int i, uint4& own, uint4& oth) {
+    own = *(const uint4*)(rows + 8 * i);
+    if (a.rot) oth = *(const uint4*)(rows + i / PCS * D + rope_partner(8 * (i % PCS), a.off, a.rot, interleaved));
+  };
+  auto rotated = [&](int i, const uint4& own, const uint4& oth) -> uint4 {
+    return a.rot ? rope_rotate(own, oth, 8 * (i % PCS), a.off, a.rot, interleaved, cs, sn) : own;
+  };
+  // the first rows are on their way while the angles are formed
+  uint4 own[BATCH], oth[BATCH], k = uint4{0, 0, 0, 0}, k_oth = k;
+  bf16_t v[BATCH] = {};
+  if (n_q) {
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) load(q, min(tid + 256 * j, n_q - 1), own[j], oth[j]);
+  }
+  if (n_k) {
+    load(k_new, min(tid, n_k - 1), k, k_oth);
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) v[j] = v_new[min(tid + 256 * j, n_v - 1)];
+  }
+  if (a.rot) {
+    if (tid < (a.rot >> 1)) {
+      const double turns = (double)(n - 1) * w * 0.15915494309189535;
+      const float ang = (float)((turns - __builtin_rint(turns)) * 6.283185307179586);
+      sincosf(ang, &sn[tid], &cs[tid]);
+    }
+    __syncthreads();
+  }
+  bf16_t* to = q_rot + (size_t)b * a.H * D;
+  for (int i0 = tid; i0 < n_q; i0 += 256 * BATCH) {
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      const int i = i0 + 256 * j;
+      if (i < n_q) *(uint4*)(to + 8 * i) = rotated(i, own[j], oth[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) load(q, min(i0 + 256 * (BATCH + j), n_q - 1), own[j], oth[j]);
+  }
+  const int t = (n - 1) % TILE_T;
+  char* tile = a.pool + (uint64_t)(uint32_t)last_page * a.page_bytes + (uint64_t)((n_tiles - 1) % a.tiles_per_page) * a.tile_bytes;
+  for (int i = tid; i < n_k; i += 256) {
+    if (i != tid) load(k_new, i, k, k_oth);
+    *(uint4*)(tile + (uint64_t)(i / PCS) * a.head_bytes + ((size_t)(i % PCS * TILE_T + t) << 4)) = rotated(i, k, k_oth);
+  }
+  for (int i0 = tid; i0 < n_v; i0 += 256 * BATCH) {
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      const int i = i0 + 256 * j;
+      if (i < n_v) ((bf16_t*)(tile + (uint64_t)(i / D) * a.head_bytes + TILE_T * D * 2))[v_elem_offset(t, i % D)] = i0 == tid ? v[j] : v_new[i];
+    }
+  }
+}
+
+static GqaArgs gqa_args(const PoolGeom& g, char* pool_base, const DecodeLaunch& d) {
   GqaArgs a;
   a.pool = pool_base;
   a.page_bytes = g.page_bytes; a.head_bytes = g.head_bytes; a.tile_bytes = g.tile_bytes; a.tiles_per_page = g.tiles_per_page;
@@ -392,7 +470,14 @@ static hipError_t launch_decode_gqa_t(const PoolGeom& g, char* pool_base, const 
   a.max_chunks = d.max_chunks;
   a.w = d.w; a.rot = d.rot; a.off = d.off; a.interleaved = d.interleaved;
   a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.counters = d.counters; a.mark = d.mark;
-  hipLaunchKernelGGL(decode_gqa_kernel<D>, dim3((unsigned)d.n_wgs * g.Hkv), dim3(256), 0, stream, a);
+  return a;
+}
+
+template <int D>
+static hipError_t launch_decode_gqa_t(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, hipStream_t stream) {
+  const dim3 grid((unsigned)d.n_wgs * g.Hkv);
+  if (d.prepared) hipLaunchKernelGGL((decode_gqa_kernel<D, false>), grid, dim3(256), 0, stream, gqa_args(g, pool_base, d));
+  else hipLaunchKernelGGL((decode_gqa_kernel<D, true>), grid, dim3(256), 0, stream, gqa_args(g, pool_base, d));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || d.max_chunks <= 1 || d.counters) return e;
   return launch_merge_chunks<D>(d, stream);
@@ -402,6 +487,14 @@ hipError_t launch_decode_gqa(const PoolGeom& g, char* pool_base, const DecodeLau
   if (g.dk == 128) return launch_decode_gqa_t<128>(g, pool_base, d, stream);
   if (g.dk == 64) return launch_decode_gqa_t<64>(g, pool_base, d, stream);
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_decode_prepare(const PoolGeom& g, char* pool_base, const DecodeLaunch& d, int n_items, void* q_rot, hipStream_t stream) {
+  const GqaArgs a = gqa_args(g, pool_base, d);
+  if (g.dk == 128) hipLaunchKernelGGL(decode_prepare_kernel<128>, dim3((unsigned)n_items), dim3(256), 0, stream, a, (bf16_t*)q_rot);
+  else if (g.dk == 64) hipLaunchKernelGGL(decode_prepare_kernel<64>, dim3((unsigned)n_items), dim3(256), 0, stream, a, (bf16_t*)q_rot);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 }  // namespace spd

@@ -335,6 +335,18 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
 }
 
 // ------------------------------------------------------------------------------------------ decode
+// A compute unit holds two workgroups of the GQA kernel (64-dim heads: three).  From the third (fifth) on, what each of them does
+// before its first tile is waited for in turn.
+// Then the records are copied to the device first: with 30-token contexts on 64 .. 256 CUs reading them there takes 0.81 .. 0.98 of
+// the step's time with the reads over the host link, 3 to 24 workgroups per compute unit; 1.02 .. 1.15 below 3.
+static bool gqa_many(int n_wgs, int share, int dim) { return dim > 64 ? n_wgs >= 3 * share : n_wgs > 4 * share; }
+// And where HBM does not hide it, a launch rotates and appends for all of them.  It does where the workgroups' rows, at the rate
+// of all the share's compute units, take longer: line at 32 MiB (no rotation: 24) of mean bytes per workgroup times compute units.
+// Step without the launch ahead / with it, 8 KV heads of 128 dims with RoPE, tokens per workgroup: 64 CUs 200 1.35 .. 1.51,
+// 590 1.12, 1000 1.05, 1729 1.01; 128 CUs 200 1.23, 365 1.09, 600 1.02, 914 0.99; 256 CUs 164 1.03 .. 1.05, 274 0.99, 579 0.96.  Append
+// alone: 64 CUs 590 1.03, 914 0.99; 128 CUs 300 1.00 .. 1.02, 450 0.96; 256 CUs 200 0.99.
+static bool gqa_prepares(int64_t bytes, int n_wgs, int share, bool rope) { return bytes / n_wgs * share <= (rope ? 32 << 20 : 24 << 20); }
+
 // noalloc: the variant that allocates nothing.  The metadata's device twin and the workspace lie in the static scratch
 // array, the staging ring is used as spd_ctx_create made it, no timing events are recorded.
 static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch* b, bool noalloc) {
@@ -401,9 +413,14 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   if ((rc = stage_acquire(ctx, SPD_PHASE_DECODE, bytes + w_bytes, &st, !noalloc)) != SPD_OK) return rc;
   const bool timing = ctx->kernel_timing && !noalloc;
   const int n_wgs = sp.n_wgs * g.Hkv;
-  // Few workgroups read their records straight out of the pinned staging buffer: a launch less.  Above 1024 records of
-  // 64 bytes that takes longer than the launch that copies them to the device (PCIe, 1.3 us per round trip).
-  const bool twin = (size_t)n_items * g.Hkv * stride > 131072;
+  // Few workgroups read their records straight out of the pinned staging buffer: a launch less.  Above 128 KiB, as the
+  // workgroups read them, they are copied too (a latent pool's workgroups, at most two per compute unit, are served as well from
+  // pinned memory up to there: 2048 records on 128 CUs 155 us, 159 copied).
+  const bool many = !mla && gqa_many(n_wgs, share, g.dk);
+  bool twin = many || (size_t)n_items * g.Hkv * stride > 131072;
+  bool prepare = many && (append || b->rope) &&
+                 gqa_prepares(sum_units * TILE_T * g.Hkv * (g.dk + g.dv) * (int64_t)sizeof(uint16_t), n_wgs, share, b->rope != nullptr);
+  if (noalloc && bytes > NOALLOC_TWIN_BYTES) twin = prepare = false;
   // Split-K partials of a GQA launch of few workgroups are merged by that launch, where a request has few chunks; else by a
   // launch of its own.  Whole step over 128-dim heads, in the launch / on its own: 24 workgroups, 3 chunks 9.1 / 10.9 us; 192, 9
   // chunks 11.4 / 12.2 on 128 CUs; 400, 9 chunks 14.1 / 15.1 on 256; level from 500 to 1100 workgroups; 1392, 16 chunks 51.0 / 48.0
@@ -413,7 +430,12 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   const bool inline_merge = !mla && n_wgs <= 512 && max_chunks <= MERGE_IN_LAUNCH_CHUNKS && (size_t)B * g.Hkv <= MERGE_COUNTERS;
   char* ws = nullptr;
   const size_t ws_o_bytes = partial_o_bytes(B, b->n_q_heads, max_chunks, g.dv), ws_ml_bytes = partial_ml_bytes(B, b->n_q_heads, max_chunks);
-  const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + (twin && !noalloc ? bytes : 0);
+  size_t ws_q_bytes = prepare && b->rope ? sizeof(uint16_t) * (size_t)B * b->n_q_heads * g.dk : 0;   // rotated queries
+  if (noalloc && ws_q_bytes && ws_o_bytes + ws_ml_bytes + ws_q_bytes > NOALLOC_WS_BYTES) {
+    prepare = false;
+    ws_q_bytes = 0;
+  }
+  const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + ws_q_bytes + (twin && !noalloc ? bytes : 0);
   if (noalloc) {
     if (ws_bytes > NOALLOC_WS_BYTES) return SPD_ETOOBIG;
     ws = ctx->scratch + NOALLOC_TWIN_BYTES;
@@ -468,21 +490,27 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   StepMark mark = step_mark(ctx, SPD_PHASE_DECODE, step.capturing);
   DecodeLaunch d{};
   if (b->rope && (rc = rope_table(step, b->rope, st->host + bytes, st->dev + bytes, &mark, &d.w)) != SPD_OK) return rc;
-  const char* meta = st->dev;
-  if (twin && (!noalloc || bytes <= NOALLOC_TWIN_BYTES)) {
-    char* to = noalloc ? ctx->scratch : ws + ws_o_bytes + ws_ml_bytes;
-    SPD_HIP(launch_meta_copy(to, st->dev, bytes, mark, stream));
-    mark.flag = nullptr;
-    meta = to;
-  }
   d.q = b->q; d.k_new = b->k_new; d.v_new = b->v_new; d.out = b->out;
-  d.items = meta; d.n_chunks = (const int32_t*)(meta + off_chunks);
+  d.items = st->dev; d.n_chunks = (const int32_t*)(st->dev + off_chunks);
   d.item_stride = (int)stride; d.n_wgs = sp.n_wgs; d.B = B; d.H = b->n_q_heads; d.scale = b->scale;
   d.max_chunks = max_chunks;
   if (b->rope) { d.rot = b->rope->rotary_dim; d.off = b->rope->rotary_offset; d.interleaved = b->rope->interleaved != 0; }
   d.ws_o = (float*)ws; d.ws_ml = (float*)(ws + ws_o_bytes);
   d.counters = inline_merge ? ds.merge_counters : nullptr;
   d.mark = mark;
+  if (twin) {
+    char* q_rot = ws + ws_o_bytes + ws_ml_bytes;
+    char* to = noalloc ? ctx->scratch : q_rot + ws_q_bytes;
+    SPD_HIP(launch_meta_copy(to, st->dev, bytes, mark, stream));
+    d.mark.flag = nullptr;
+    d.items = to;
+    d.n_chunks = (const int32_t*)(to + off_chunks);
+    if (prepare) {
+      SPD_HIP(launch_decode_prepare(g, pool->base, d, n_items, q_rot, stream));
+      if (b->rope) d.q = q_rot;
+      d.prepared = true;
+    }
+  }
   if (timing && (rc = kernel_timing_mark(ctx, SPD_PHASE_DECODE, 0, stream)) != SPD_OK) return rc;
   if (mla) SPD_HIP(launch_decode_mla(g, pool->base, d, stream));
   else SPD_HIP(launch_decode_gqa(g, pool->base, d, stream));

@@ -138,6 +138,7 @@ hipError_t launch_decode_gqa(const PoolGeom&, char*, const DecodeLaunch& d, hipS
     seen_w.push_back(sum);
   });
 }
+hipError_t launch_decode_prepare(const PoolGeom&, char*, const DecodeLaunch& d, int, void*, hipStream_t s) { return launch(s, d.mark); }
 hipError_t launch_decode_mla(const PoolGeom& g, char* b, const DecodeLaunch& d, hipStream_t s) { return launch_decode_gqa(g, b, d, s); }
 hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillWork*, const int32_t*, int, int, int, int, int, float,
                           hipStream_t s) { return launch(s, StepMark{}); }
@@ -295,6 +296,31 @@ static void merges() {
   CHECK(spd_decode_step(ctx, pool, &b) == SPD_OK && seen_counters.back());
 }
 
+// One launch where a compute unit has few workgroups; records copied, rows prepared and attention where it has many with short
+// contexts; without the preparation where the contexts are long or there is nothing to prepare.
+static void launches() {
+  const spd_rope_config r = rope(10000.0);
+  uint64_t req = 9;
+  CHECK(spd_kv_reserve(pool, req, 800, nullptr) == SPD_OK);
+  auto count = [&](int B, int32_t n, const spd_rope_config* rp, bool noalloc = false) -> int {
+    std::vector<uint64_t> ids((size_t)B, req);
+    std::vector<int32_t> lens((size_t)B, n);
+    const spd_decode_batch b = {B, ids.data(), lens.data(), tensor, nullptr, nullptr, tensor, 8, 0.1f, rp};
+    run(decode_stream());
+    const int before = n_launches;
+    CHECK((noalloc ? spd_decode_step_noalloc(ctx, pool, &b) : spd_decode_step(ctx, pool, &b)) == SPD_OK);
+    run(decode_stream());
+    return n_launches - before;
+  };
+  CHECK(count(1, 30, &r) == 2);                      // (the frequency table's copy)
+  for (bool noalloc : {false, true}) {
+    CHECK(count(1, 30, &r, noalloc) == 1 && count(380, 30, &r, noalloc) == 1);     // two KV heads, 256 compute units: 760 workgroups
+    CHECK(count(390, 30, &r, noalloc) == 3);
+    CHECK(count(390, 30, nullptr, noalloc) == 2);    // nothing to rotate or append
+    CHECK(count(800, 800, &r, noalloc) == 2);
+  }
+}
+
 int main(int argc, char** argv) {
   CHECK(argc == 2);
   const std::string name = argv[1];
@@ -304,6 +330,7 @@ int main(int argc, char** argv) {
   else if (name == "captured") captured();
   else if (name == "in_flight") in_flight();
   else if (name == "merges") merges();
+  else if (name == "launches") launches();
   else CHECK(!"a scenario of that name");
   puts("ok");
 }

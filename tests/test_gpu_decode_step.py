@@ -1,6 +1,6 @@
-"""GPU tests of the decode step that does everything in its attention launch (rotation, append, attention, merge of the
-context's chunks), at the sizes where its parts meet: tile, page, chunk and page-id-window borders, both ways the
-metadata reaches the kernel and both ways the chunks are merged."""
+"""GPU tests of the decode step (rotation, append, attention, merge of the context's chunks), everything in one launch or
+rotation and append in a launch ahead, at the sizes where its parts meet: tile, page, chunk and page-id-window borders, both ways
+the metadata reaches the kernel and both ways the chunks are merged."""
 import math
 
 import numpy as np
@@ -29,6 +29,12 @@ CASES = [
     ("one query head per KV head, no rope", 4, 4, 64, 16, 128, (1, 130, 700), 0, False),
     ("sixteen query heads per KV head", 16, 1, 128, 64, 256, (33, 900, 1), 64, False),
     ("page ids beyond one window, large pages", 8, 8, 128, 1024, 32, (9001,) * 12, 128, False),
+    # at least three workgroups per compute unit, short contexts: records copied, rotation and append by a launch ahead
+    ("prepared: tile and page borders", 8, 2, 128, 16, 32, tuple(1 + 31 * i % 68 for i in range(48)), 128, False),
+    ("prepared: pages of three tiles, part of the head interleaved", 8, 4, 64, 48, 32, tuple(1 + 29 * i % 131 for i in range(40)), 32, True),
+    ("prepared: part of the head, chunks", 4, 4, 128, 32, 32, (1100, 700, 257, 17) * 8, 48, False),
+    ("prepared: many query heads", 72, 8, 128, 16, 32, tuple(1 + 7 * i % 40 for i in range(14)), 128, False),
+    ("prepared: many KV heads, no rope", 20, 20, 64, 16, 32, tuple(15 + i for i in range(9)), 0, False),
     ("metadata copied, merge launch", 8, 8, 128, 16, 256, tuple(300 + 37 * (i % 29) for i in range(90)), 128, False),
 ]
 
