@@ -83,12 +83,53 @@ inline void split_gqa(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64
   cut_chunks(ps, ctx_lens, B, max_units, std::min<int64_t>(c, (max_units + round - 1) / round * round), n_chunks, out);
 }
 
+constexpr int64_t CHUNK_COST = 20;
+// Whole requests dealt to `slots` workgroups (B >= slots): true, with the batch so split, if none gets `worst` units or more and
+// no request has more than `most`.
+inline bool deal_whole(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t slots, int64_t most, int64_t worst, int32_t* n_chunks, DecodeSplit& out) {
+  std::vector<uint64_t>&by_length = ps.tmp_set, &loads = ps.tmp_heap;     // (units << 32 | request, counted from the end), (load << 32 | workgroup)
+  by_length.clear();
+  for (int r = 0; r < B; ++r) {
+    const uint64_t units = (uint64_t)(((int64_t)ctx_lens[r] + TILE_T - 1) / TILE_T);
+    if ((int64_t)units > most || (int64_t)units + CHUNK_COST >= worst) return false;
+    by_length.push_back(units << 32 | (uint32_t)(B - 1 - r));
+  }
+  std::sort(by_length.begin(), by_length.end(), std::greater<uint64_t>());
+  loads.clear();
+  for (int64_t w = 0; w < slots; ++w) loads.push_back((uint64_t)w);       // (in order: a heap already)
+  std::vector<int32_t>& owner = ps.tmp_owner;
+  owner.clear();
+  for (uint64_t k : by_length) {
+    std::pop_heap(loads.begin(), loads.end(), std::greater<uint64_t>());
+    owner.push_back((int32_t)(uint32_t)loads.back());
+    loads.back() += ((k >> 32) + CHUNK_COST) << 32;
+    if ((int64_t)(loads.back() >> 32) >= worst) return false;
+    std::push_heap(loads.begin(), loads.end(), std::greater<uint64_t>());
+  }
+  // the first `slots` items, one per workgroup in order, are where the workgroups start
+  std::vector<DecodeItem>& items = ps.tmp_items;
+  std::vector<int32_t>& last = ps.tmp_last;
+  items.clear();
+  last.assign((size_t)slots, -1);
+  for (int i = 0; i < B; ++i) {
+    const uint64_t k = by_length[(size_t)i];
+    const int r = B - 1 - (int)(uint32_t)k, wg = owner[(size_t)i];
+    push_chunk(items, r, 0, ctx_lens[r], 0, (int32_t)(k >> 32));
+    if (last[(size_t)wg] >= 0) items[(size_t)last[(size_t)wg]].next = i;
+    last[(size_t)wg] = i;
+    n_chunks[r] = 1;
+  }
+  out.n_wgs = (int)slots;
+  out.max_chunks = 1;
+  out.chunk_units = (int32_t)(by_length[0] >> 32);
+  return true;
+}
+
 // Latent decode: two workgroups per CU are resident, and the batch's units are dealt to them evenly, in request order, a
 // workgroup going on from one request's end to the next one's beginning.  (Chunks of one length, handed out longest first, left
 // a quarter of the slots idle at the end.)  A chunk costs its pipeline fill and its merge beside its tiles, about as
 // much as CHUNK_COST tiles; chunks are whole rounds of the four waves, except at a request's end.  `least`: deal a workgroup no
 // fewer units than this.
-constexpr int64_t CHUNK_COST = 20;
 inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t sum_units, int cus, int units_per_page, int override_units,
                          int64_t least, int32_t* n_chunks, DecodeSplit& out) {
   constexpr int64_t ROUND = 4;
@@ -128,6 +169,18 @@ inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, in
     if (out.n_wgs <= slots || override_units > 0) break;
   }
   out.dealt = quota;
+  // With at least a request per workgroup, dealt whole instead, the longest first to whoever has least, where the most that a
+  // workgroup then has is less: nothing is cut, and no workgroup stands idle.  (256 requests of 150 .. 450 tokens on 64 CUs: 100 -> 79
+  // units at most; the step 74 -> 58 us.)
+  if (B >= slots && least == 0 && override_units <= 0) {
+    int64_t load = 0, worst = 0;
+    for (size_t i = 0; i < items.size(); ++i) {
+      if (i > 0 && owner[i] != owner[i - 1]) load = 0;
+      load += CHUNK_COST + items[i].n_units;
+      worst = std::max(worst, load);
+    }
+    if (deal_whole(ps, ctx_lens, B, slots, most, worst, n_chunks, out)) return;
+  }
   // workgroup i starts with record i: first chunks to the front, the others behind them, linked
   const int n = (int)items.size();
   std::vector<DecodeItem>& sorted = ps.tmp_items2;

@@ -211,10 +211,10 @@ struct spd_phase_state {
   bool rope_valid = false;
   uint32_t* merge_counters = nullptr;  // decode phase: MERGE_COUNTERS zeros (split_merge.h), zero again after every step
   // a step's working lists, kept from step to step (one thread drives a phase)
-  std::vector<uint64_t> tmp_set;
+  std::vector<uint64_t> tmp_set, tmp_heap;
   std::vector<spd::DecodeItem> tmp_items, tmp_items2;
   std::vector<spd_req_table*> tmp_tables;
-  std::vector<int32_t> tmp_sizes, tmp_chunks;
+  std::vector<int32_t> tmp_sizes, tmp_chunks, tmp_owner, tmp_last;
   char* workspace = nullptr;           // split-K partials (decode)
   size_t ws_cap = 0;
   // workspaces outgrown, with the number of the last step that may still read them: freed once that step has

@@ -1,5 +1,6 @@
 """Host logic, no GPU: every tile of a decode batch belongs to one chunk, chains of chunks are walks through all of them, and
 no chunk of the latent decode touches more pages than its kernel has room for."""
+import heapq
 import random
 
 import pytest
@@ -72,6 +73,38 @@ def test_latent_chunks_fit_the_kernel(exe):
                 i = s.items[i][4]
         assert sorted(seen) == list(range(len(s.items)))
     assert longest == room                  # (FULL_CHUNK: the test has seen the kernel's room used to the last word)
+
+
+def _loads(s, cost):
+    loads = []
+    for i in range(s.n_wgs):
+        loads.append(0)
+        while i >= 0:
+            loads[-1] += cost + s.items[i][3]
+            i = s.items[i][4]
+    return loads
+
+
+def test_latent_requests_that_need_no_cutting_are_dealt_whole(exe):
+    """At least a request per workgroup: the most that one gets is no more than with whole requests dealt longest first, where
+    a request may be that long."""
+    cost, rng, batches = 20, random.Random(4), []
+    for n in (30, 100, 300, 1000):
+        batches += [("latent", 64, cus, 1, 16, 1, 0, [int(n * (0.5 + i / (B - 1))) for i in range(B)])
+                    for cus, B in ((32, 64), (32, 128), (32, 256), (64, 128), (64, 256), (128, 256))]
+    batches += [("latent", P, cus, 1, 16, 1, 0, [rng.randint(1, rng.choice((20, 300, 5000))) for _ in range(rng.randint(2 * cus, 700))])
+                for P in (32, 64) for cus in (32, 96) for _ in range(6)]
+    _, answers = DS.split(exe, batches)
+    whole_ones = 0
+    for (_, P, cus, _, _, _, _, lens), s in zip(batches, answers):
+        _check_cover(s.items, lens)
+        heap = [0] * (2 * cus)
+        for units in sorted((-(-n // TILE) for n in lens), reverse=True):
+            heapq.heappush(heap, heapq.heappop(heap) + units + cost)
+        whole_ones += len(s.items) == len(lens)
+        assert max(_loads(s, cost)) <= max(heap) and s.n_wgs <= 2 * cus
+        assert sum(_loads(s, cost)) == sum(cost + i[3] for i in s.items)          # every item in one chain
+    assert 20 < whole_ones < len(batches)
 
 
 def test_gqa_chunks_cover_the_batch(exe):

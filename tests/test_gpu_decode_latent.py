@@ -22,6 +22,7 @@ CASES = [
     ("tile and wave borders", 16, 64, 256, (1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 192)),
     ("few heads, small pages, merged in the launch", 3, 32, 256, (1000, 33, 4097)),
     ("chains of chunks, merge launch", 16, 64, 32, tuple(40 + 97 * (i % 31) for i in range(70))),
+    ("chains of whole requests", 16, 64, 32, tuple(1 + 53 * i % 400 for i in range(150))),
     ("one long request: many chunks", 16, 64, 128, (20001,)),
 ]
 
