@@ -390,9 +390,11 @@ static hipError_t launch_tiles(const void* x, const void* w_gu, void* out, int T
 template <int NB>
 static hipError_t launch_stream(const void* x, const void* w_gu, void* out, int T, int K, int I, int cus, const StepMark& mark, hipStream_t stream) {
   const bf16_t *xx = (const bf16_t*)x, *ww = (const bf16_t*)w_gu;
-  // eight waves where 256-row workgroups still occupy nearly every compute unit of the share; half as many rows otherwise (64 tokens
-  // of hidden 8192, inter 7168 on 128 CUs, which gives 56 wide workgroups: 59 us with 112 narrow ones)
-  if (8 * (2 * I / 256) >= 7 * cus)
+  // A compute unit runs one workgroup at a time.  A narrow one (four waves, half the rows) takes 0.6 of a wide one's time, so
+  // narrow ones pay where the share runs all of them at once, and wide ones otherwise; 64 tokens, wide / narrow: hidden 4096, inter
+  // 14336 on 256 CUs (112 / 224 workgroups) 55 / 41 us, on 128 55 / 65; 8192, 7168 on 128 (56 / 112) 97 / 59, on 64 98 / 109; 2048,
+  // 5632 on 128 (44 / 88) 28 / 19, on 64 28 / 34.
+  if (2 * I / 128 > cus)
     hipLaunchKernelGGL((ffn_gate_up_stream_kernel<NB, 8, 8>), dim3((unsigned)(2 * I / 256)), dim3(512), 0, stream, xx, ww, (bf16_t*)out, T, K, I, mark);
   else
     hipLaunchKernelGGL((ffn_gate_up_stream_kernel<NB, 4, 16>), dim3((unsigned)(2 * I / 128)), dim3(256), 0, stream, xx, ww, (bf16_t*)out, T, K, I, mark);
