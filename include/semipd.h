@@ -85,7 +85,8 @@ int spd_device_info(spd_ctx* ctx, int* total_cus, int* xcds, int* cu_granularity
  * and scale in fp32) and its 64 rope entries in bf16: 656 bytes per token instead of 1152.  Every call
  * takes and returns the same bf16 tensors as for a bf16 latent pool: rows are quantised on their way
  * into the pages, spd_kv_gather hands back decode(code) * scale rounded to bf16, and the decode step
- * attends over exactly those dequantised rows.  RoPE inside the decode step is not offered on such a
+ * attends over decode(code) * scale as it is, without that rounding (closer to the cached values than
+ * the gathered rows, by less than bf16 resolves).  RoPE inside the decode step is not offered on such a
  * pool (SPD_EINVAL).
  * The byte layout inside a page is private to the library (it is arranged for the
  * decode kernel's matrix-core operand order); read or write pages only through
@@ -243,8 +244,8 @@ int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_batch* batc
  * must be positive and finite.
  * With `rope` non-NULL (declared further down; paper, Evaluation "Implementation based on
  * DistServe": the RoPE kernel) q and k_new are the vectors BEFORE the rotary embedding: the step
- * rotates request b's query and new key by position ctx_lens[b] - 1 in the attention launch, the key
- * on its way into the page (the caller's q, k_new are left as they are).  The rotating range must fit the
+ * rotates request b's query and new key by position ctx_lens[b] - 1, the key on its way into the page
+ * (the caller's q, k_new are left as they are).  The rotating range must fit the
  * head (rotary_offset + rotary_dim <= dim_k; multiples of 8 and 16) or the call is SPD_EINVAL. */
 typedef struct {
   int32_t n_req;
@@ -273,7 +274,8 @@ int spd_decode_step(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch* batch)
  * bytes, and 32 MiB of workspace, i.e. 4 n_req n_q_heads chunks (dim_v + 2) bytes where a context is
  * split at all.  Work items are the chunks of all contexts, `chunks` those of the longest one.  On GQA
  * pools the library aims at six workgroups per compute unit of the decode share; on latent pools
- * two workgroups per compute unit share the batch evenly, and where that would break a limit this
+ * two workgroups per compute unit share the batch evenly (in whole requests where that is the shorter
+ * for many of them), and where that would break a limit this
  * call makes the chunks longer, up to 247 pages (the result then equals spd_decode_step's within
  * rounding, not bit for bit).  A batch beyond either limit is refused with SPD_ETOOBIG and nothing is
  * enqueued.  Kernel timing (spd_set_kernel_timing) is not recorded for these steps.
@@ -380,7 +382,9 @@ int spd_phase_query(spd_ctx* ctx, int phase, int* done);
 /* Make `phase`'s future work wait (on the GPU, not the host) for everything `other` has
  * enqueued so far - e.g. a decode step that reads pages a prefill step has just written. */
 int spd_phase_wait_for(spd_ctx* ctx, int phase, int other);
-/* The phase's current hipStream_t, for callers that enqueue their own work or events. */
+/* The phase's current hipStream_t, for callers that enqueue their own work or events.  From this call
+ * on, for the context's life, every step of the phase records an event behind itself, since the caller's
+ * work may follow any of them: about 2 us of host time and 4 to 6 us of the stream's per step. */
 int spd_phase_stream(spd_ctx* ctx, int phase, void** hip_stream_out);
 
 /* ------------------------------------------------------------------ partition

@@ -7,8 +7,8 @@
 //     scale_b = amax_b / 448  (1 if the block is all zero),    code_i = E4M3(clamp(x_i / scale_b, -448, 448)),
 // rounded to nearest even; the division and the scale in fp32.  A row takes 656 bytes instead of 1152:
 //     [512 codes][4 scales, fp32][64 rope entries, bf16]
-// and a page is page_tokens such rows in token order.  The decode kernel reads these rows and multiplies with
-// decode(code) * scale rounded to bf16.
+// and a page is page_tokens such rows in token order.  The decode kernel computes with the codes (exact in
+// bf16) and puts the scales, in fp32, onto score sums and softmax weights; the gather rounds decode(code) * scale to bf16.
 //
 // Both kernels: one workgroup per 16-token tile, 16 lanes per token; a lane owns 32 consecutive ckv entries (a
 // quarter of a scale block: the block's maximum is formed over 4 neighbouring lanes).

@@ -226,9 +226,10 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   size_t off_desc = align16(off_chain + chain.size() * sizeof(int32_t));
   size_t off_gather = align16(off_desc + n_descs * sizeof(TileDesc));
   // RoPE inside the step: every row's position where the queries have a launch of their own, and room for the frequency
-  // table.  A launch of its own rotates long batches faster (eight waves per SIMD instead of the four that the page
-  // write leaves: 20 thousand rows of 64 heads on 96 CUs, step 1117 us, in one launch 1139); short ones gain what a launch
-  // and its gap cost.
+  // table.  A launch of its own has eight waves per SIMD instead of the four that the page write leaves; short batches gain what
+  // a launch and its gap cost.  Step with the queries in the same launch / in their own, 256-token prompts of 64 heads: 8 MiB of
+  // queries 28 / 35 us on 128 CUs, 16 MiB 42 / 50, 32 MiB 65 / 70, 64 MiB 118 / 119, 128 MiB 239 / 230; on 96 CUs level at 64 MiB
+  // too (147 / 144), 320 MiB 785 / 762.  On 256 CUs one launch stays 3 to 6 % ahead up to 320 MiB, which this line leaves.
   const int32_t n_rows = b->cu_seqlens[b->n_req];
   const bool own_rope = b->rope && (!one_launch || (int64_t)n_rows * b->n_q_heads * b->dim_qk * 2 > Q_IN_ONE_LAUNCH);
   size_t off_pos = align16(off_gather + n_gather * sizeof(TileDesc));
