@@ -246,6 +246,25 @@ int phase_enter(spd_ctx* ctx, int phase, hipStream_t* stream_out) {
   return SPD_OK;
 }
 
+// One workgroup per compute unit gets one compute unit each only where every XCD contributes a multiple of 4 of them: an XCD deals
+// its workgroups to its four shader arrays in turn (the partition granularity sees to that; with 10 per XCD some workgroups
+// wait for others to finish, and a prefill step takes up to twice as long).  And not where the two phases' masks overlap: such a
+// workgroup keeps its compute unit for the whole kernel, and the other phase's workgroups that are allowed nowhere else would
+// wait that long.
+bool phase_exclusive(spd_ctx* ctx, int phase, int* share) {
+  std::lock_guard<std::mutex> lk(ctx->part_mu);
+  const spd_phase_state &s = ctx->phase[phase], &o = ctx->phase[1 - phase];
+  *share = std::max(1, s.has_pending ? s.pending_cus : s.active_cus);
+  if (*share % ctx->xcds != 0 || (*share / ctx->xcds) % 4 != 0) return false;
+  const std::vector<uint32_t>& m = s.has_pending ? s.pending_mask : s.active_mask;
+  auto meets = [&](const std::vector<uint32_t>& other) {
+    for (size_t i = 0; i < m.size() && i < other.size(); ++i)
+      if (m[i] & other[i]) return true;
+    return false;
+  };
+  return !meets(o.active_mask) && !(o.has_pending && meets(o.pending_mask));
+}
+
 static void raise_done_seq(spd_phase_state& s, uint64_t seq) {
   uint64_t cur = s.done_seq.load(std::memory_order_relaxed);
   while (cur < seq && !s.done_seq.compare_exchange_weak(cur, seq, std::memory_order_release)) {

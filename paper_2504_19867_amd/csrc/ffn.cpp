@@ -1,5 +1,4 @@
 // Entry points of the gated FFN's first step (gate and up projection as one GEMM).
-#include <algorithm>
 #include <cstdint>
 
 #include "internal.h"
@@ -36,10 +35,12 @@ extern "C" int spd_ffn_gate_up(spd_ctx* ctx, int phase, const void* x, const voi
   if (n_tokens > 0 && (!x || !w_gu || !out || (((uintptr_t)x | (uintptr_t)w_gu) & 15) || ((uintptr_t)out & 1))) return SPD_EINVAL;
   if (ctx->device < 0) return SPD_ESTATE;
   if (n_tokens == 0) return SPD_OK;
+  int share;
+  const bool exclusive = phase_exclusive(ctx, phase, &share);
   hipStream_t stream;
   if ((rc = phase_enter(ctx, phase, &stream)) != SPD_OK) return rc;
   if ((rc = kernel_timing_mark(ctx, phase, 0, stream)) != SPD_OK) return rc;
-  SPD_HIP(launch_ffn_gate_up(x, w_gu, out, n_tokens, hidden, inter, ctx->xcds, std::max(1, ctx->phase[phase].active_cus),
+  SPD_HIP(launch_ffn_gate_up(x, w_gu, out, n_tokens, hidden, inter, ctx->xcds, share, exclusive,
                              step_mark(ctx, phase, stream_capturing(ctx, stream)), stream));
   return kernel_timing_mark(ctx, phase, 1, stream);
 }

@@ -240,6 +240,8 @@ struct spd_ctx {
 namespace spd {
 // host helpers (ctx.cpp)
 int phase_enter(spd_ctx* ctx, int phase, hipStream_t* stream_out);   // adopt pending stream
+// May the phase's next launch be one workgroup per compute unit of its share (the staged one, where one is)?  `share`: its size.
+bool phase_exclusive(spd_ctx* ctx, int phase, int* share);
 // may_alloc = false: SPD_ETOOBIG instead of growing the slot's buffers
 int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool may_alloc = true);
 int scratch_resolve(int device, char** out);   // noalloc.hip: address of `device`'s copy of the scratch array
@@ -338,7 +340,8 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out
                           hipStream_t stream);
 // x [T, K], w_gu [2 I, K] (joint gate/up rows in blocks of 32 + 32), out [T, I], all bf16 in device memory;
 // K a multiple of 32, I a multiple of 128
-hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int cus,
+// exclusive: as phase_exclusive says
+hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int cus, bool exclusive,
                               const StepMark& mark, hipStream_t stream);
 hipError_t launch_ffn_pack(const void* w_gate, const void* w_up, void* w_gu, int K, int I, hipStream_t stream);
 // d_pos, d_w may be device-readable pinned host memory

@@ -10,19 +10,17 @@
 //
 // A dense contraction: v_mfma_f32_32x32x16_bf16.
 //
-// Prompt batches (ffn_gate_up_kernel): one workgroup = 8 waves computes a tile of 256 tokens x 256
+// Prompt batches (ffn_gate_up_large_kernel): one workgroup = 8 waves computes a tile of 256 tokens x 256
 // joint columns (= 128 outputs); the waves form a 2 x 4 grid, each with 128 tokens x 64 joint
 // columns: one block of 32 gate columns and the 32 up columns that belong to them, so the
 // activation needs nothing but the wave's own accumulators.  Both operands are contiguous along
-// hidden; 32-wide slices of them stream from global memory straight into a ring of four LDS stages
-// (global_load_lds_dwordx4, one s_barrier per slice) and are read back with 16-byte reads in operand
-// order, one slice ahead of the MFMAs, into a second set of operand registers.  Rows are 64 bytes in
-// LDS; the four 16-byte chunks of a row are XOR-swizzled with bits 2..3 of the row number, which
-// spreads 16 consecutive rows over all banks.
+// hidden; 32-wide slices of them stream from global memory straight into LDS rings
+// (global_load_lds_dwordx4) and are read back with 16-byte reads in operand order.  The 16-byte chunks of
+// a row in LDS are XOR-swizzled with bits of the row number, which spreads 16 consecutive rows over all banks.
 //
 // Decode batches of up to 128 tokens are bound by reading the weights once and have a kernel of their own
-// (ffn_gate_up_stream_kernel); between 128 and 256 tokens the tile kernel runs with 128 x 128 tiles (four waves, two workgroups
-// per compute unit), so that every compute unit of the share has a workgroup.
+// (ffn_gate_up_stream_kernel); between 128 and 256 tokens there are 128 x 128 tiles (ffn_gate_up_small_kernel: four waves, two
+// workgroups per compute unit), where 256 x 256 ones would leave half of the share's compute units without a workgroup.
 #include "internal.h"
 
 #include <type_traits>
@@ -49,14 +47,34 @@ __device__ inline void dma16s(const void* sbase, uint32_t voff, uint32_t lds_byt
 }
 #define SPD_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))
 
-// MB: 32-token blocks per wave; WNW: waves along the joint columns.  The waves form a 2 x WNW grid, each with
-// 32 MB tokens x 64 joint columns; the workgroup's tile is 64 MB tokens x 64 WNW joint columns: <4, 4>: 256 x 256 for
-// prompt batches, <2, 2>: 128 x 128, four waves, two workgroups per CU.
-template <int MB, int WNW>
-__global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
+// Which tile the workgroups of an XCD take, in the order in which they take them.  Workgroup b runs on XCD b % xcds, and the
+// workgroups of an XCD start in the order of b.  Every XCD takes a contiguous range of weight tiles (columns) and all token tiles;
+// inside it the tiles are ordered so that the 16 or so workgroups running together form a block of about 4 x 4 tiles:
+// each slice of x and of the weights that misses the XCD's L2 then feeds four workgroups.
+struct TileOrder {
+  int tiles_m, start, cnt;                        // this XCD's weight tiles: cnt from `start` on
+  __device__ TileOrder(int tiles_m_, int tiles_n, int xcds) : tiles_m(tiles_m_) {
+    const int xcd = (int)blockIdx.x % xcds, base = tiles_n / xcds, rem = tiles_n % xcds;
+    cnt = base + (xcd < rem ? 1 : 0);
+    start = xcd * base + min(xcd, rem);
+  }
+  __device__ int slots() const { return cnt * tiles_m; }
+  __device__ void tile(int slot, int& tm, int& tn) const {
+    const int full = cnt / 4;                     // column blocks of four weight tiles; the last one narrower
+    const bool in_full = slot < full * 4 * tiles_m;
+    const int cb = in_full ? slot / (4 * tiles_m) : full, wb = in_full ? 4 : cnt - 4 * full;
+    const int q = slot - cb * 4 * tiles_m;
+    tm = q / wb;
+    tn = start + 4 * cb + q % wb;
+  }
+};
+
+// 128 tokens x 128 joint columns, 2 x 2 waves with 64 tokens x 64 joint columns each, two workgroups per compute unit; a ring of
+// four stages with one s_barrier per slice, operands read a slice ahead of the MFMAs into a second set of registers.
+__global__ __launch_bounds__(256, 2) void ffn_gate_up_small_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                                    bf16_t* __restrict__ out, int T, int K, int I, int tiles_m,
                                                                    int tiles_n, int xcds, StepMark mark) {
-  constexpr int NSTAGE = 4, WAVES = 2 * WNW, BM = 64 * MB, BNP = 64 * WNW, PD = NSTAGE - 1;
+  constexpr int MB = 2, WNW = 2, NSTAGE = 4, WAVES = 2 * WNW, BM = 64 * MB, BNP = 64 * WNW, PD = NSTAGE - 1;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BNP * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
   constexpr int A_LOADS = A_BYTES / 1024, B_LOADS = B_BYTES / 1024, LPW = (A_LOADS + B_LOADS) / WAVES;   // 1 KiB load instructions (per wave)
   static_assert(B_LOADS % WAVES == 0 && A_LOADS % WAVES == 0, "loads divide evenly over the waves");
@@ -65,34 +83,11 @@ __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t*
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n32 = lane & 31, hh = lane >> 5;
   const int wm = wave / WNW, wn = wave % WNW;
-  // Workgroup b runs on XCD b % xcds, and the workgroups of an XCD start in the order of b.  Every
-  // XCD takes a contiguous range of weight tiles (columns) and all token tiles; inside it the tiles
-  // are ordered so that the 16 or so workgroups running together form a block of about 4 x 4 tiles:
-  // each slice of x and of the weights that misses the XCD's L2 then feeds four workgroups.
+  const TileOrder order(tiles_m, tiles_n, xcds);
+  const int slot = (int)blockIdx.x / xcds;
+  if (slot >= order.slots()) return;
   int tm, tn;
-  if (xcds > 1) {
-    const int xcd = (int)blockIdx.x % xcds, slot = (int)blockIdx.x / xcds;
-    const int base = tiles_n / xcds, rem = tiles_n % xcds;
-    const int cnt = base + (xcd < rem ? 1 : 0), start = xcd * base + min(xcd, rem);
-    if (slot >= cnt * tiles_m) return;
-    const int full = cnt / 4;                   // column blocks of four weight tiles; the last one narrower
-    int cb, q, wb;
-    if (slot < full * 4 * tiles_m) {
-      cb = slot / (4 * tiles_m);
-      q = slot % (4 * tiles_m);
-      wb = 4;
-    } else {
-      cb = full;
-      q = slot - full * 4 * tiles_m;
-      wb = cnt - 4 * full;
-    }
-    tm = q / wb;
-    tn = start + 4 * cb + q % wb;
-  } else {
-    if ((int)blockIdx.x >= tiles_m * tiles_n) return;
-    tm = (int)blockIdx.x % tiles_m;
-    tn = (int)blockIdx.x / tiles_m;
-  }
+  order.tile(slot, tm, tn);
   const int m0 = tm * BM, n0p = tn * BNP;
   const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
   const uint32_t pitch = (uint32_t)K * 2;
@@ -213,8 +208,6 @@ __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t*
     if (ct + 1 < n_slices) step(ct + 1, o1, o0);
   }
 
-  // (ahead of the loop this branch shifts the loop by four bytes against the lines its instructions are fetched in: 2402 us
-  // instead of 2384 at 8192 tokens of hidden 4096, inter 14336 on 128 CUs; workgroup 0 is among the first to get here)
   if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
 
   // ---- activation and store: lanes 0..31 of a store hold 32 consecutive outputs of one token
@@ -228,6 +221,253 @@ __global__ __launch_bounds__(128 * WNW, 2) void ffn_gate_up_kernel(const bf16_t*
       const float s = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
       if (t < T) out[(size_t)t * I + col] = (bf16_t)cvt_bf16(s * u);
     }
+}
+
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // `out` is only promised to be aligned to its entries
+
+// 256 tokens x 256 joint columns.  Waves w and w + 4 sit on one SIMD, and the two groups of four waves run half a slice apart: while
+// one group's MFMAs of a slice are issued, the other group starts the loads of a later slice and reads its operands of its slice out of
+// LDS, then they change places; an s_barrier at every change.  So the matrix cores of a SIMD always have one wave that does
+// nothing but feed them, and operand reads, tile loads, waits and the barriers' own latency fall beside the other wave's MFMAs.
+//   slice u, group 0:  [loads, reads u | MFMAs u         | loads, reads u + 1 ..
+//            group 1:  [MFMAs u - 1    | loads, reads u  | MFMAs u ..
+// With both waves of a SIMD reading, loading and multiplying in one stream and one barrier per slice, a slice of both took 1600 cycles,
+// 1024 of them MFMAs; now 1170.  8192 tokens of hidden 4096, inter 14336 on 128 CUs: 2388 -> 1930 us (1 PFLOP/s); the clock falls from 2.4
+// to 2.2 .. 2.3 GHz there (256 CUs: 1.45), so power bounds what is left.  512 tokens: 183 -> 151 us.
+// Loads ahead of the reads: 5 % faster than behind them, 12 % than among the MFMAs.  16x16x32 MFMAs draw less power and
+// take 15 % more cycles: 2100 us.  A fifth stage, or another order of the slices on every XCD: no change.
+//
+// x comes in pairs of slices: a load instruction takes 8 rows x 128 bytes, whole cache lines.  (A slice at a time, 16 rows x 64
+// bytes, every line is asked for twice: 256 tokens of hidden 4096, inter 14336 102 instead of 86 us on 128 CUs, 8192 tokens 1870
+// instead of 1770.)  The ring holds three pairs of x and four slices of the weights, all 160 KiB; a step loads the weights of the
+// slice three later and half the rows of the x pair that begins three or four later.
+//
+// A workgroup walks the tiles slot, slot + gridDim / xcds, ..: with one workgroup per compute unit the loads run ahead across tiles, so
+// that a tile's first slices arrive while the one before is finished (2 % over one workgroup per tile).  The product is taken
+// transposed (weights are the A operand), so that a lane has four consecutive outputs of one token.
+__global__ __launch_bounds__(512, 2) void ffn_gate_up_large_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
+                                                                   bf16_t* __restrict__ out, int T, int K, int I, int tiles_m,
+                                                                   int tiles_n, int xcds, StepMark mark) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
+  constexpr int BM = 256, X_PAIR = BM * 128, W_SLICE = BM * BK * 2, XP = 3, WS = 4;   // bytes of a pair / slice, stages of either ring
+  constexpr int W_LDS = XP * X_PAIR;              // where the weights' stages begin
+  __shared__ __attribute__((aligned(1024))) char smem[XP * X_PAIR + WS * W_SLICE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n32 = lane & 31, hh = lane >> 5;
+  const int wm = wave >> 2, wn = wave & 3;        // wm: also the wave's group
+  const TileOrder order(tiles_m, tiles_n, xcds);
+  const int n_slots = order.slots(), slot_step = (int)gridDim.x / xcds;
+  int slot = (int)blockIdx.x / xcds;
+  if (slot >= n_slots) return;
+  const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  const uint32_t pitch = (uint32_t)K * 2;
+  // steps per tile: whole pairs of slices; with an odd number of slices the last step multiplies nothing
+  const int n_slices = K / BK, n_steps = (n_slices + 1) & ~1;
+  const bool odd = n_slices & 1;
+  int left = ((n_slots - 1 - slot) / slot_step + 1) * n_steps;   // steps of all tiles of this workgroup from the current one on
+
+  // ---- loads.  x: instruction ii = wave + 8 j (j < 2) of half `hf` of a pair fills the 64 consecutive 16-byte slots of rows
+  // 128 hf + 8 ii .. + 7 of the stage (rows of 128 bytes); slot s of a row holds the row's chunk s ^ ((row >> 1) & 7).  Token rows
+  // past T re-read row T - 1; where the pair's second slice lies past the end of the row the first one's chunks are read again.
+  // Weights: the slice's 16 KiB in the order in which they are stored: slot s of a row of 64 bytes holds chunk s ^ ((row >> 2) & 3).
+  const int x_chunk = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7);
+  uint32_t x_voff[2][2];                          // [half][j]
+  const uint32_t w_voff = (uint32_t)lane * 16;
+  const char *x_ptr, *w_ptr;                      // the pair, the slice to be loaded next
+  int x_slot = slot, x_left = n_steps, w_slot = slot, w_left = n_steps;   // their tiles, and steps until those tiles' end
+  auto x_tile = [&]() __attribute__((always_inline)) {
+    int tm, tn;
+    order.tile(x_slot, tm, tn);
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        x_voff[hf][j] = (uint32_t)min(128 * hf + 8 * (wave + 8 * j) + (lane >> 3), T - 1 - tm * BM) * pitch + (uint32_t)x_chunk * 16;
+    x_ptr = (const char*)(x + (size_t)(tm * BM) * K);
+  };
+  auto w_tile = [&]() __attribute__((always_inline)) {
+    int tm, tn;
+    order.tile(w_slot, tm, tn);
+    w_ptr = (const char*)w + (size_t)tn * n_slices * W_SLICE + wave * 1024;
+  };
+  x_tile();
+  w_tile();
+  auto load_x = [&](int stage, int hf) __attribute__((always_inline)) {
+    const uint32_t lds = smem_base + stage * X_PAIR + hf * (X_PAIR / 2) + wave * 1024;
+    if (odd && x_left <= 2) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) dma16s(x_ptr, x_voff[hf][j] - (uint32_t)(x_chunk & 4) * 16, lds + j * 8192);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) dma16s(x_ptr, x_voff[hf][j], lds + j * 8192);
+    }
+    if (hf) x_ptr += 128;
+    if (--x_left == 0) {
+      x_left = n_steps;
+      x_slot += slot_step;
+      if (x_slot < n_slots) x_tile();
+    }
+  };
+  auto load_w = [&](int stage) __attribute__((always_inline)) {
+    const uint32_t lds = smem_base + W_LDS + stage * W_SLICE + wave * 1024;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) dma16s(w_ptr + j * 8192, w_voff, lds + j * 8192);
+    if (--w_left == 0) {
+      w_left = n_steps;
+      w_slot += slot_step;
+      if (w_slot < n_slots) w_tile();
+    } else if (!(odd && w_left == 1)) {
+      w_ptr += W_SLICE;
+    }
+  };
+
+  // ---- LDS operand addresses: k-step ks (16 hidden entries), lane half hh reads chunk 2 ks + hh of the slice's four (x: of the
+  // pair's eight).  The loop is unrolled over the rings, so that the stage is part of a read's 16-bit immediate; the third pair of x
+  // lies beyond its reach and gets lane addresses of its own.  (Vector instructions in the loop would wait for the other wave's MFMAs.)
+  int x_off[2][2][2], w_off[2];                   // x: [third stage][slice of the pair][ks]
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    w_off[ks] = W_LDS + (wn * 64 + n32) * 64 + ((2 * ks + hh) ^ ((n32 >> 2) & 3)) * 16;
+#pragma unroll
+    for (int sl = 0; sl < 2; ++sl) {
+      x_off[0][sl][ks] = (wm * 128 + n32) * 128 + ((4 * sl + 2 * ks + hh) ^ ((n32 >> 1) & 7)) * 16;
+      x_off[1][sl][ks] = x_off[0][sl][ks] + 2 * X_PAIR;
+      asm volatile("" : "+v"(x_off[1][sl][ks]));   // a value of its own, not "x_off + constant" to be recomputed
+    }
+  }
+  uint4 ox[2][4], ow[2][2];
+  // acc[mb][0] = gate, acc[mb][1] = up: element i of lane (n32, hh) is output 8 (i / 4) + 4 hh + i % 4 of token 32 mb + n32
+  f32x16 acc[4][2];
+  auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[mb][nb][e] = 0.f;
+  };
+  clear();
+  auto barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // ahead of the first step: the x pairs of slices 0, 1 and 2, 3, the weights of slices 0, 1, 2, as the steps -4 .. -1 would load them
+  load_x(0, 0);
+  load_x(0, 1);
+  load_w(0);
+  if (left > 2) load_x(1, 0);
+  load_w(1);
+  if (left > 2) {
+    load_x(1, 1);
+    load_w(2);
+    SPD_WAIT_VMCNT(8);
+  } else {
+    SPD_WAIT_VMCNT(0);
+  }
+  barrier();                                      // slice 0 is there
+  if (wm) barrier();                              // the second group starts half a slice later
+
+  int ct = 0;                                     // slice of the tile
+  int ready = 0;                                  // steps that need not wait: the end of a tile has awaited all loads up to it
+  auto step = [&](auto stc) __attribute__((always_inline)) {
+    constexpr int ST = stc, SL = ST & 1;          // step modulo the rings' common period; slice of the pair
+    // Loading and reading half of step u.  The stages being loaded held slice u - 1 and pair u / 2 - 1, whose reads both groups had
+    // behind them at the last barrier.  At this half's end the wave's own reads are done (the other group's next half
+    // may load their stage), and so is what it loaded up to step u - 2, its part of slice u + 1 (which the other group
+    // reads half a slice earlier than this wave).
+    if (left > 4) load_x((ST / 2 + 2) % XP, SL);
+    if (left > 3) load_w((ST + 3) % WS);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int r = 0; r < 2; ++r) ow[ks][r] = *(const uint4*)(smem + w_off[ks] + (ST % WS) * W_SLICE + r * (32 * 64));
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        ox[ks][r] = *(const uint4*)(smem + x_off[ST / 2 % XP == 2][SL][ks] + (ST / 2 % XP == 1 ? X_PAIR : 0) + r * (32 * 128));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (ready > 0) --ready;
+    else if (left >= 5) SPD_WAIT_VMCNT(8);        // four loads of this step, four of the one before
+    else if (left == 4) SPD_WAIT_VMCNT(6);
+    else if (left == 3) SPD_WAIT_VMCNT(2);
+    else SPD_WAIT_VMCNT(0);
+    __builtin_amdgcn_s_waitcnt(0xc07f);           // lgkmcnt(0)
+    barrier();
+    if (SL == 0 || ct < n_slices) {
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb)
+            acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ow[ks][nb]),
+                                                                  __builtin_bit_cast(bf16x8, ox[ks][mb]), acc[mb][nb], 0, 0, 0);
+      __builtin_amdgcn_s_setprio(0);
+    }
+    barrier();
+    --left;
+    ++ct;
+  };
+  // ---- the tile's end: activation and store.  The halves of the wave exchange four outputs each, so that a lane stores eight
+  // consecutive ones.  All loads so far are awaited ahead of the first store: the next two steps then have nothing to wait
+  // for, and do not wait for the stores either.
+  auto finish_tile = [&]() __attribute__((always_inline)) {
+    int tm, tn;
+    order.tile(slot, tm, tn);
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb) {
+      uint32_t y[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float v[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const float g = acc[mb][0][2 * i + e], u = acc[mb][1][2 * i + e];
+          v[e] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
+        }
+        y[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v[0], v[1]}, bf16x2));
+      }
+      if (mb == 0) SPD_WAIT_VMCNT(0);
+      const int t = tm * BM + wm * 128 + mb * 32 + n32;
+      bf16_t* o = out + (size_t)t * I + tn * 128 + wn * 32 + 8 * hh;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        // (machine code: the compiler's builtin for the swap loses the second result)
+        asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3\n\ts_nop 1"
+                     : "+v"(y[4 * p]), "+v"(y[4 * p + 2]), "+v"(y[4 * p + 1]), "+v"(y[4 * p + 3]));
+        if (t < T) *(u32x4_any*)(o + 16 * p) = u32x4_any{y[4 * p], y[4 * p + 1], y[4 * p + 2], y[4 * p + 3]};
+      }
+    }
+  };
+  // a pair of slices and, behind a tile's last one, its end; false behind the last tile
+  auto pair = [&](auto pc) __attribute__((always_inline)) -> bool {
+    constexpr int P = pc;
+    step(std::integral_constant<int, 2 * P>{});
+    step(std::integral_constant<int, 2 * P + 1>{});
+    if (ct == n_steps) {
+      finish_tile();
+      if (left == 0) return false;
+      slot += slot_step;
+      clear();
+      ct = 0;
+      ready = 2;
+    }
+    return true;
+  };
+  for (;;) {
+    if (!pair(std::integral_constant<int, 0>{})) break;
+    if (!pair(std::integral_constant<int, 1>{})) break;
+    if (!pair(std::integral_constant<int, 2>{})) break;
+    if (!pair(std::integral_constant<int, 3>{})) break;
+    if (!pair(std::integral_constant<int, 4>{})) break;
+    if (!pair(std::integral_constant<int, 5>{})) break;
+  }
+  if (!wm) barrier();                             // as many as the second group
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -376,14 +616,16 @@ __global__ __launch_bounds__(256) void ffn_pack_kernel(const uint4* __restrict__
 
 }  // namespace
 
-template <int MB, int WNW>
-static hipError_t launch_tiles(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, const StepMark& mark, hipStream_t stream) {
-  constexpr int BM = 64 * MB, BNP = 64 * WNW;
-  const int tiles_m = (T + BM - 1) / BM, tiles_n = 2 * I / BNP;
-  if (tiles_n < xcds) xcds = 1;
-  const int per = xcds > 1 ? ((tiles_n + xcds - 1) / xcds) * tiles_m : tiles_m * tiles_n;
-  hipLaunchKernelGGL((ffn_gate_up_kernel<MB, WNW>), dim3((unsigned)(per * xcds)), dim3(128 * WNW), 0, stream, (const bf16_t*)x,
-                     (const bf16_t*)w_gu, (bf16_t*)out, T, K, I, tiles_m, tiles_n, xcds, mark);
+// `persistent`: at most so many workgroups, one per compute unit of a share that has them to itself; 0: one per tile
+template <int BM, typename Kernel>
+static hipError_t launch_tiles(Kernel kernel, const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int persistent,
+                               const StepMark& mark, hipStream_t stream) {
+  const int tiles_m = (T + BM - 1) / BM, tiles_n = 2 * I / BM;   // square tiles
+  if (tiles_n < xcds || persistent % xcds) xcds = 1;
+  int n = xcds > 1 ? ((tiles_n + xcds - 1) / xcds) * tiles_m * xcds : tiles_m * tiles_n;
+  if (persistent) n = std::min(n, persistent);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(2 * BM), 0, stream, (const bf16_t*)x, (const bf16_t*)w_gu, (bf16_t*)out, T, K, I,
+                     tiles_m, tiles_n, xcds, mark);
   return hipGetLastError();
 }
 
@@ -401,7 +643,7 @@ static hipError_t launch_stream(const void* x, const void* w_gu, void* out, int 
   return hipGetLastError();
 }
 
-hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int cus,
+hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int cus, bool exclusive,
                               const StepMark& mark, hipStream_t stream) {
   // up to 128 tokens: the weights streamed through registers, all tokens in one workgroup (measured at 100 and 128 tokens of
   // hidden 4096, inter 14336 on 128 CUs: 61 and 63 us, 96 and 105 us for 128 x 128 tiles)
@@ -411,8 +653,8 @@ hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T,
   if (T <= 128) return launch_stream<8>(x, w_gu, out, T, K, I, cus, mark, stream);
   // the small tile where the large one would leave half of the share's compute units without a workgroup
   const int large_tiles = ((T + 255) / 256) * (2 * I / 256);
-  if (T <= 256 && 2 * large_tiles <= cus) return launch_tiles<2, 2>(x, w_gu, out, T, K, I, xcds, mark, stream);
-  return launch_tiles<4, 4>(x, w_gu, out, T, K, I, xcds, mark, stream);
+  if (T <= 256 && 2 * large_tiles <= cus) return launch_tiles<128>(ffn_gate_up_small_kernel, x, w_gu, out, T, K, I, xcds, 0, mark, stream);
+  return launch_tiles<256>(ffn_gate_up_large_kernel, x, w_gu, out, T, K, I, xcds, exclusive ? cus : 0, mark, stream);
 }
 
 hipError_t launch_ffn_pack(const void* w_gate, const void* w_up, void* w_gu, int K, int I, hipStream_t stream) {

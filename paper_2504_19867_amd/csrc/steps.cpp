@@ -181,32 +181,12 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   }
 
   int rc;
-  // One persistent workgroup per compute unit of the prefill share, each with its chain of work
-  // items, where such a launch gets one compute unit per workgroup: an XCD deals its workgroups to
-  // its four shader arrays in turn, so every XCD must contribute a multiple of 4 compute units (the
-  // partition granularity sees to that; with 10 per XCD some workgroups wait for others to finish,
-  // and the step takes up to twice as long).  Elsewhere: one workgroup per item, handed out by the
-  // hardware as compute units free up.
-  // Nor where the two phases' masks overlap: a persistent workgroup keeps its compute unit for the
-  // whole kernel, and decode workgroups that are allowed nowhere else would wait that long.
+  // One persistent workgroup per compute unit of the prefill share, each with its chain of work items, where phase_exclusive says
+  // so; elsewhere one workgroup per item, handed out by the hardware as compute units free up.
   // The share is the one this step will run on: a staged partition is adopted below, once nothing but a HIP
   // call can fail any more, so a step that returns an error of its own leaves the partition as it was.
   int share;
-  bool persistent;
-  {
-    std::lock_guard<std::mutex> lk(ctx->part_mu);
-    const spd_phase_state& psx = ctx->phase[SPD_PHASE_PREFILL];
-    share = std::max(1, psx.has_pending ? psx.pending_cus : psx.active_cus);
-    persistent = share % ctx->xcds == 0 && (share / ctx->xcds) % 4 == 0;
-    const std::vector<uint32_t>& pm = psx.has_pending ? psx.pending_mask : psx.active_mask;
-    const spd_phase_state& dsx = ctx->phase[SPD_PHASE_DECODE];
-    const std::vector<uint32_t>& dm = dsx.has_pending ? dsx.pending_mask : dsx.active_mask;
-    for (size_t i = 0; i < pm.size() && i < dm.size(); ++i)
-      if (pm[i] & dm[i]) persistent = false;
-    if (dsx.has_pending)
-      for (size_t i = 0; i < pm.size() && i < dsx.active_mask.size(); ++i)
-        if (pm[i] & dsx.active_mask[i]) persistent = false;
-  }
+  bool persistent = phase_exclusive(ctx, SPD_PHASE_PREFILL, &share);
   if (ctx->env_prefill_persistent >= 0) persistent = ctx->env_prefill_persistent != 0;   // experiment switch
   std::vector<PrefillWork> work;
   std::vector<int32_t> chain;

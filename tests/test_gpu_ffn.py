@@ -82,6 +82,30 @@ def test_gate_up_streamed_weights(T, K, I, cus):
     ctx.close()
 
 
+@pytest.mark.parametrize("K", [32, 64, 96, 128, 160, 512])
+@pytest.mark.parametrize("T,I,cus", [(1537, 1024, 32), (300, 4224, 32), (257, 1152, 64), (1025, 256, 0)])
+def test_gate_up_several_tiles_per_workgroup(T, I, cus, K):
+    """Prompt batches on a share of their own: a workgroup takes one to three 256 x 256 tiles (56, 66, 18 of them on 32 or 64 CUs;
+    cus = 0: both phases on all of them, one workgroup per tile), the loads three slices ahead of the reads cross from tile to tile
+    (1 to 16 slices per tile), token and column counts leave ragged tiles and blocks, the output is aligned to its
+    entries only, and nothing is written past the batch."""
+    ctx = S.Context(0)
+    if cus:
+        ctx.set_partition(cus, ctx.device_info()[0] - cus)
+    xb, wgb, wub = W.ffn_inputs(T, K, I, seed=1700 + T + K)
+    x, wg, wu = dev_bf16(xb), dev_bf16(wgb), dev_bf16(wub)
+    w_gu = torch.empty((2 * I, K), dtype=torch.bfloat16, device=DEV)
+    flat = torch.full(((T + 2) * I + 1,), 7.0, dtype=torch.bfloat16, device=DEV)
+    out = flat[1:].view(T + 2, I)
+    ctx.ffn_pack_gate_up(PRE, wg, wu, w_gu, K, I)
+    ctx.ffn_gate_up(PRE, x, w_gu, out, T, K, I)
+    ctx.phase_sync(PRE)
+    got = host_f64(flat)
+    assert got[0] == 7.0 and (got[1 + T * I:] == 7.0).all()
+    _assert_ffn(got[1:1 + T * I].reshape(T, I), F.gate_up(f64(xb), f64(wgb), f64(wub)), f"ffn tiles T={T} K={K} I={I} cus={cus}")
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,K,I", [(1, 256, 128), (7, 512, 384), (31, 256, 640), (32, 1024, 128), (33, 256, 128), (48, 768, 256),
                                    (63, 512, 128), (64, 256, 384), (16, 4096, 256), (64, 4096, 128)])
 def test_gate_up_batches_of_up_to_64_tokens(T, K, I):
