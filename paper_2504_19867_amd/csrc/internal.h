@@ -336,7 +336,7 @@ constexpr int MLA_THREADS = 256;
 constexpr int MLA_CHUNK_PAGES = MLA_THREADS - DECODE_ITEM_WORDS;
 // one workgroup per chain: workgroup b computes the items d_work[d_chain[b]] .. d_work[d_chain[b + 1] - 1]
 hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillWork* d_work,
-                          const int32_t* d_chain, int n_blocks, int H, int Hkv, int dqk, int dv, float scale,
+                          const int32_t* d_chain, int n_blocks, int longest, int H, int Hkv, int dqk, int dv, float scale,
                           hipStream_t stream);
 // x [T, K], w_gu [2 I, K] (joint gate/up rows in blocks of 32 + 32), out [T, I], all bf16 in device memory;
 // K a multiple of 32, I a multiple of 128

@@ -27,7 +27,7 @@
 //
 // K and V tiles of 64 keys stream from global memory straight into a ring of LDS stages with
 // global_load_lds_dwordx4 (no register staging, no LDS stores), ahead of the compute; one
-// s_barrier per pair of tiles where the ring has four stages (one per tile with three).  K rows
+// s_barrier per pair of tiles where the ring has four stages (one per tile with three; two in prefill_192_kernel).  K rows
 // are read back with 16-byte reads in A-operand order; V stays in its natural [key][dim] order
 // and the transposition that the second product needs is done by the LDS transpose read
 // ds_read_b64_tr_b16.  Both tiles are XOR-swizzled at 16-byte granularity against bank conflicts.
@@ -41,6 +41,7 @@ namespace spd {
 
 typedef unsigned short bf16_t;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -53,12 +54,8 @@ __device__ inline uint32_t cvt_pk_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
-// 16 bytes per lane from global memory to LDS: lane i's data lands at lds_byte_addr + 16 * i.
-// The compiler does not see this write; completion is tracked by hand with vmcnt (below).
-__device__ inline void dma16(const void* gptr, uint32_t lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_byte_addr), "v"(gptr) : "memory");
-}
-// The same with the address split in a wave-uniform base and a 32-bit per-lane offset.
+// 16 bytes per lane from global memory (a wave-uniform base and a 32-bit per-lane offset) to LDS: lane i's data lands at
+// lds_byte_addr + 16 * i.  The compiler does not see this write; completion is tracked by hand with vmcnt (below).
 __device__ inline void dma16s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte_addr), "v"(voff), "s"(sbase) : "memory");
 }
@@ -503,6 +500,418 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   }
 }
 
+// ---- 192 / 128 dims (the un-absorbed heads of an MLA layer), prompts of more than six tiles.
+//
+// The same contraction, tiles, operand orders and chains; what differs is how the two waves of a SIMD share it.  Waves w and
+// w + 4 sit on one SIMD, and the two groups of four waves run half a tile apart, with an s_barrier at every change:
+//   group 0:  | P.V of tile t - 1, K.Q of tile t | softmax of tile t, loads | P.V of tile t, ..
+//   group 1:  | softmax of tile t - 1, loads     | P.V of t - 1, K.Q of t   | softmax of tile t, ..
+// so that one wave of a SIMD feeds the matrix cores while the other one has the vector units.  With both waves taking a tile from
+// end to end behind one barrier (prefill_kernel: three stages, registers for four K operands on the way) 4 prompts of 4096 tokens of
+// 16 heads take 557 us on 128 CUs, here 490 (whole step on inputs of larger scores 658 / 532).  A matrix half takes about 1450 cycles (1280 of them 32x32x16 MFMAs), a vector half 1100 to 1300, an item's
+// end about 3 us of both.  For 128 dims, whose tiles have a fifth fewer MFMAs for the same softmax, the order above it is
+// the better one (2560 cycles per tile of both waves in either, but 5 instead of 7 us per item: 4 x 4096 tokens of 64 heads 1400 / 1460 us).
+//
+// v_dot2_f32_bf16 takes its turn in the matrix pipe: beside another wave's MFMAs one takes 72 cycles instead of 8, and a softmax
+// with its row sum in dot products stands still.  The row sums are 4x4x4 MFMAs here, issued in the wave's own matrix half: with a first operand
+// of ones every lane gets the sum of its own four bf16 values of p.
+//
+// The reference of the softmax lies 8 (in powers of two) above the largest score seen, so that p stays below 2 until a score exceeds
+// that one by 9; the top exponent bit of any p tells (no sum, no maximum is formed to find out).
+template <int HB>
+__global__ __launch_bounds__(512, 2) void prefill_192_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                                             const bf16_t* __restrict__ v, bf16_t* __restrict__ out,
+                                                             const PrefillWork* __restrict__ work,
+                                                             const int32_t* __restrict__ chain, int H, int Hkv,
+                                                             float c /* scale * log2(e) */) {
+  constexpr int DQK = 192, DV = 128;
+  constexpr int QS = WAVES / HB;                // 32-row sub-tiles per workgroup
+  constexpr int CHK = DQK / 8, CHV = DV / 8;    // 16-byte chunks per K / V row
+  constexpr int K_BYTES = BN * DQK * 2, V_BYTES = BN * DV * 2;
+  constexpr int NST = 3;                        // stages of the K ring and of the V ring
+  constexpr int LK = CHK / WAVES, LV = CHV / WAVES;   // 1 KiB load instructions per wave for a K / V tile
+  constexpr int KS = DQK / 16, VB = DV / 32;
+  constexpr int NS = 2 * KS, NV = (BN / 16) * VB;     // MFMAs of either product
+  constexpr int RING = 4, VAH = 2, VQ = VAH + 1;      // K operands, V operands on the way
+  constexpr int OPITCH = 32 * 2 + 16;           // bytes per staged output row piece (32 dims, padded)
+  constexpr int V_LDS = NST * K_BYTES, EPI_LDS = V_LDS + NST * V_BYTES, TOUCH_LDS = EPI_LDS + WAVES * 32 * OPITCH;
+  constexpr float ABOVE = 8.f;
+  __shared__ __attribute__((aligned(1024))) char smem[TOUCH_LDS + WAVES * 256];
+
+  const int G = H / Hkv;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n32 = lane & 31, hh = lane >> 5;
+  const uint32_t k_pitch = (uint32_t)Hkv * DQK * 2, v_pitch = (uint32_t)Hkv * DV * 2;
+  const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  int it = __builtin_amdgcn_readfirstlane(chain[blockIdx.x]);   // this workgroup's chain of work items
+  const int it_end = __builtin_amdgcn_readfirstlane(chain[blockIdx.x + 1]);
+  if (it >= it_end) return;
+
+  // ---- tile loads: instruction wave + 8 j of a K (V) tile fills the 64 consecutive 16-byte slots from 64 (wave + 8 j) on; slot s
+  // of a row holds the row's chunk s ^ swz(row).  K runs one tile ahead of V, which is needed one matrix half later.
+  auto k_slot = [&](int j, int& row, int& coff) {
+    const int slot = (wave + WAVES * j) * 64 + lane;
+    row = slot / CHK;
+    coff = ((slot % CHK) ^ k_swz<DQK>(row)) * 16;
+  };
+  auto v_slot = [&](int j, int& row, int& coff) {
+    const int slot = (wave + WAVES * j) * 64 + lane;
+    row = slot / CHV;
+    coff = ((slot % CHV) ^ v_swz<DV>(row)) * 16;
+  };
+  uint32_t k_voff[LK], v_voff[LV];
+#pragma unroll
+  for (int j = 0; j < LK; ++j) {
+    int row, coff;
+    k_slot(j, row, coff);
+    k_voff[j] = (uint32_t)row * k_pitch + (uint32_t)coff;
+  }
+#pragma unroll
+  for (int j = 0; j < LV; ++j) {
+    int row, coff;
+    v_slot(j, row, coff);
+    v_voff[j] = (uint32_t)row * v_pitch + (uint32_t)coff;
+  }
+  auto tiles_of = [&](const PrefillWork& pw) __attribute__((always_inline)) -> int {
+    return (min(pw.q_off + pw.len, pw.q_off + pw.q_tile * (32 * QS) + 32 * QS) + BN - 1) / BN;
+  };
+  struct Producer { int it, kt, n, kv_len; const char* base; };   // the tile to be loaded next: kt of the n of item `it`
+  Producer pk{it, 0, 0, 0, nullptr}, pv{it, 0, 0, 0, nullptr};
+  auto producer_item = [&](Producer& p, bool is_k) __attribute__((always_inline)) {
+    const PrefillWork pw = work[p.it];
+    const size_t row = (size_t)pw.kv_row0 * Hkv + pw.head0 / G;
+    p.kv_len = pw.q_off + pw.len;
+    p.n = tiles_of(pw);
+    p.base = is_k ? (const char*)(k + row * DQK) : (const char*)(v + row * DV);
+    p.kt = 0;
+  };
+  producer_item(pk, true);
+  producer_item(pv, false);
+  auto advance = [&](Producer& p, bool is_k, uint32_t pitch) __attribute__((always_inline)) {
+    p.base += (size_t)BN * pitch;
+    if (__builtin_expect(++p.kt == p.n, 0)) {
+      ++p.it;
+      if (p.it < it_end) producer_item(p, is_k);
+    }
+  };
+  auto load_k = [&](int stage) __attribute__((always_inline)) {
+    if (__builtin_expect(pk.it >= it_end, 0)) return;
+    const uint32_t lds = smem_base + stage * K_BYTES + wave * 1024;
+    const int last = pk.kv_len - 1 - pk.kt * BN;
+#pragma unroll
+    for (int j = 0; j < LK; ++j) {
+      if (__builtin_expect(last >= BN - 1, 1)) {
+        dma16s(pk.base, k_voff[j], lds + j * (WAVES * 1024));
+      } else {                                  // rows past the prompt re-read its last row
+        int row, coff;
+        k_slot(j, row, coff);
+        dma16s(pk.base, (uint32_t)min(row, last) * k_pitch + (uint32_t)coff, lds + j * (WAVES * 1024));
+      }
+    }
+    advance(pk, true, k_pitch);
+  };
+  auto load_v = [&](int stage) __attribute__((always_inline)) {
+    if (__builtin_expect(pv.it >= it_end, 0)) return;
+    const uint32_t lds = smem_base + V_LDS + stage * V_BYTES + wave * 1024;
+    const int last = pv.kv_len - 1 - pv.kt * BN;
+#pragma unroll
+    for (int j = 0; j < LV; ++j) {
+      if (__builtin_expect(last >= BN - 1, 1)) {
+        dma16s(pv.base, v_voff[j], lds + j * (WAVES * 1024));
+      } else {
+        int row, coff;
+        v_slot(j, row, coff);
+        dma16s(pv.base, (uint32_t)min(row, last) * v_pitch + (uint32_t)coff, lds + j * (WAVES * 1024));
+      }
+    }
+    advance(pv, false, v_pitch);
+  };
+
+  // ---- LDS operand addresses inside a stage, as in prefill_kernel; the stage is part of a read's immediate.  The swizzle touches
+  // the low three bits of the chunk number only, so K steps four apart differ by 128 bytes and share a lane address.
+  int k_off[4], v_off[VB];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) k_off[ks] = n32 * (CHK * 16) + (((2 * ks + hh) ^ k_swz<DQK>(n32)) * 16);
+  const int r16 = lane & 15, v_row = 4 * hh + (r16 >> 2);
+#pragma unroll
+  for (int blk = 0; blk < VB; ++blk) {
+    const int dim = 32 * blk + 16 * ((lane >> 4) & 1) + 4 * (r16 & 3);
+    v_off[blk] = V_LDS + v_row * (CHV * 16) + (((dim >> 3) ^ v_swz<DV>(v_row)) * 16) + (dim & 7) * 2;
+  }
+
+  // ---- state of the item whose first product comes next, and of the tile between the halves
+  PrefillWork w;
+  int h = 0, wave_q0 = 0, pos0 = 0, pos = 0, n_kv_tiles = 0, kt = 0;
+  bool wave_active = false, act = false, act_prev = false;   // has the wave keys in this tile, in the one before?
+  bf16x8 qf[KS];
+  f32x16 O[VB], S[2];
+  uint32_t pb[2][8];
+  f32x4 L;                                      // row sums: four times the same value
+  float m;
+  s16x4 vq[VQ][2];
+  auto item_begin = [&]() __attribute__((always_inline)) {
+    w = work[it];
+    h = w.head0 + wave % HB;
+    const int q_start = w.q_tile * (32 * QS);
+    wave_q0 = q_start + 32 * (wave / HB);
+    wave_active = wave_q0 < w.len;              // waves past the prompt's end only help loading
+    const int qi = wave_q0 + n32, qi_c = qi < w.len ? qi : w.len - 1;
+    pos0 = w.q_off + wave_q0;
+    pos = w.q_off + qi;
+    const bf16_t* qp = q + ((size_t)(w.row0 + qi_c) * H + h) * DQK + 8 * hh;
+    // (loads and wait in one piece: loads that the compiler knows of it counts, and waits for, in the middle of every tile)
+    asm volatile("global_load_dwordx4 %0, %12, off\n\tglobal_load_dwordx4 %1, %12, off offset:32\n\tglobal_load_dwordx4 %2, %12, off offset:64\n\t"
+                 "global_load_dwordx4 %3, %12, off offset:96\n\tglobal_load_dwordx4 %4, %12, off offset:128\n\tglobal_load_dwordx4 %5, %12, off offset:160\n\t"
+                 "global_load_dwordx4 %6, %12, off offset:192\n\tglobal_load_dwordx4 %7, %12, off offset:224\n\tglobal_load_dwordx4 %8, %12, off offset:256\n\t"
+                 "global_load_dwordx4 %9, %12, off offset:288\n\tglobal_load_dwordx4 %10, %12, off offset:320\n\tglobal_load_dwordx4 %11, %12, off offset:352\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(qf[0]), "=&v"(qf[1]), "=&v"(qf[2]), "=&v"(qf[3]), "=&v"(qf[4]), "=&v"(qf[5]), "=&v"(qf[6]), "=&v"(qf[7]), "=&v"(qf[8]),
+                   "=&v"(qf[9]), "=&v"(qf[10]), "=&v"(qf[11])
+                 : "v"(qp)
+                 : "memory");
+    n_kv_tiles = tiles_of(w);
+    kt = 0;
+  };
+  // the next item's query rows, one 128-byte line per lane, into LDS that nobody reads: the fragment loads then find them in the L2
+  auto touch_next_q = [&]() __attribute__((always_inline)) {
+    const PrefillWork w2 = work[it + 1];
+    constexpr int LINES = DQK / 64;
+    int r2 = w2.q_tile * (32 * QS) + 32 * (wave / HB) + lane / LINES;
+    r2 = r2 < w2.len ? r2 : w2.len - 1;
+    const char* p2 = (const char*)(q + ((size_t)(w2.row0 + r2) * H + w2.head0 + wave % HB) * DQK) + (lane % LINES) * 128;
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(smem_base + TOUCH_LDS + wave * 256), "v"(p2) : "memory");
+  };
+  auto reset_sums = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < VB; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) O[i][e] = 0.f;
+    m = -INFINITY;
+    L = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  bf16_t* o_base = nullptr;                     // the item that O belongs to: its first row of this wave, and how many there are
+  int o_rows = 0;
+  auto finish_item = [&]() __attribute__((always_inline)) {
+    float l = L[0];
+    l += __shfl_xor(l, 32);
+    if (o_rows > 0) {
+      char* ost = smem + EPI_LDS + wave * (32 * OPITCH);
+      const float inv = 1.f / l;
+#pragma unroll
+      for (int blk = 0; blk < VB; ++blk) {
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          uint2 y;
+          y.x = cvt_pk_bf16(O[blk][4 * i4] * inv, O[blk][4 * i4 + 1] * inv);
+          y.y = cvt_pk_bf16(O[blk][4 * i4 + 2] * inv, O[blk][4 * i4 + 3] * inv);
+          *(uint2*)(ost + n32 * OPITCH + (8 * i4 + 4 * hh) * 2) = y;
+        }
+#pragma unroll
+        for (int itr = 0; itr < 2; ++itr) {     // 32 rows x 4 pieces of 16 bytes
+          const int i = lane + 64 * itr;
+          const int r = i >> 2, cc = i & 3;
+          if (r < o_rows) *(uint4*)(o_base + (size_t)r * H * DV + 32 * blk + cc * 8) = *(const uint4*)(ost + r * OPITCH + cc * 16);
+        }
+      }
+    }
+  };
+  auto barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Oᵀ += Vᵀ.Pᵀ of the tile in V stage `stage`; operand j + VAH is read while operand j multiplies, `beside(j)` after each of them
+  auto second_product = [&](int stage, auto beside) __attribute__((always_inline)) {
+    auto read_v = [&](int j, int half) __attribute__((always_inline)) -> s16x4 {
+      return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(
+          smem + v_off[j % VB] + stage * V_BYTES + (16 * (j / VB) + 8 * half) * (CHV * 16)));
+    };
+    const s16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+#pragma unroll
+    for (int j = 0; j < VAH; ++j) {
+      vq[j][0] = read_v(j, 0);
+      vq[j][1] = read_v(j, 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int kk = j / VB, blk = j % VB;
+      const uint4 p = uint4{pb[kk >> 1][4 * (kk & 1)], pb[kk >> 1][4 * (kk & 1) + 1], pb[kk >> 1][4 * (kk & 1) + 2], pb[kk >> 1][4 * (kk & 1) + 3]};
+      if (blk < 2) L = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, blk ? uint2{p.z, p.w} : uint2{p.x, p.y}), L, 0, 0, 0);
+      const uint2 lo = __builtin_bit_cast(uint2, vq[j % VQ][0]), hi = __builtin_bit_cast(uint2, vq[j % VQ][1]);
+      O[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, uint4{lo.x, lo.y, hi.x, hi.y}), __builtin_bit_cast(bf16x8, p),
+                                                       O[blk], 0, 0, 0);
+      if (j + VAH < NV) {
+        vq[(j + VAH) % VQ][0] = read_v(j + VAH, 0);
+        vq[(j + VAH) % VQ][1] = read_v(j + VAH, 1);
+      }
+      beside(j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // K of tiles 0, 1 and V of tile 0, as the vector halves before the first one would load them
+  load_k(0);
+  load_k(1);
+  load_v(0);
+  item_begin();                                 // (waits for all of it)
+  reset_sums();
+  const bool second_group = wave >= WAVES / 2;
+  barrier();
+  if (second_group) barrier();                  // half a tile behind
+
+  // tile number g of the chain, stage g % 3; false behind the last one
+  auto step = [&](auto stc) __attribute__((always_inline)) -> bool {
+    constexpr int ST = stc, PREV = (ST + NST - 1) % NST;
+    auto read_k = [&](int i) __attribute__((always_inline)) -> uint4 {   // operand i: block i % 2 (32 keys), k-step i / 2
+      return *(const uint4*)(smem + k_off[(i / 2) % 4] + ST * K_BYTES + ((i / 2) / 4) * 128 + (i % 2) * (32 * CHK * 16));
+    };
+    const int kv0 = kt * BN;
+    uint4 ring[RING];
+    act = wave_active && kv0 <= pos0 + 31;      // else every key of the tile is in this wave's future
+
+    // ---- matrix half: the second product of the tile before, the first product of this one
+    __builtin_amdgcn_s_setprio(1);
+    if (__builtin_expect(act_prev, 1)) {
+      second_product(PREV, [&](int j) __attribute__((always_inline)) {
+        if (j >= NV - RING) ring[j - (NV - RING)] = read_k(j - (NV - RING));
+      });
+    } else {
+#pragma unroll
+      for (int i = 0; i < RING; ++i) ring[i] = read_k(i);
+    }
+    if (__builtin_expect(act, 1)) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) S[b][e] = 0.f;
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        S[i % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[i % RING]), qf[i / 2], S[i % 2], 0, 0, 0);
+        if (i + RING < NS) ring[i % RING] = read_k(i + RING);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
+    // What the vector half before loaded, K of tile g + 1 and V of tile g, has landed (the other group's next matrix half but
+    // one and this wave's next one read it).
+    SPD_WAIT_VMCNT(0);
+    barrier();
+
+    // ---- vector half
+    const bool first = kt == 0, last = kt + 1 == n_kv_tiles, more = it + 1 < it_end;
+    if (__builtin_expect(first, 0)) {           // the second product of the item before is complete
+      if (o_base) {
+        finish_item();
+        reset_sums();
+      }
+      o_base = out + ((size_t)(w.row0 + wave_q0) * H + h) * DV;
+      o_rows = wave_active ? min(32, w.len - wave_q0) : 0;
+    }
+    const int tile_pos0 = pos0, tile_pos = pos;
+    ++kt;
+    if (__builtin_expect(last && more, 0)) {    // the next first product is the next item's
+      ++it;
+      item_begin();
+    }
+    // K of tile g + 2 into the stage of tile g - 1, V of tile g + 1 into the stage of tile g - 2: both groups are done with those.
+    // Inside an item the loads go between the groups of the softmax, so that the four waves' do not queue up in the address unit.
+    const bool spread = act && !first && pk.it < it_end && pv.it < it_end && pk.kt + 1 < pk.n && pv.kt + 1 < pv.n;
+    constexpr int K_ST = (ST + 2) % NST, V_ST = (ST + 1) % NST;
+    if (__builtin_expect(!spread, 0)) {
+      load_k(K_ST);
+      load_v(V_ST);
+    }
+    auto load_piece = [&](int n) __attribute__((always_inline)) {   // n of 4: whole tiles, not their items' last ones
+      if (!spread) return;
+      const uint32_t lk = smem_base + K_ST * K_BYTES + wave * 1024, lv = smem_base + V_LDS + V_ST * V_BYTES + wave * 1024;
+#pragma unroll
+      for (int j = 0; j < LK; ++j)
+        if (j * 2 / LK == n) dma16s(pk.base, k_voff[j], lk + j * (WAVES * 1024));
+#pragma unroll
+      for (int j = 0; j < LV; ++j)
+        if (2 + j * 2 / LV == n) dma16s(pv.base, v_voff[j], lv + j * (WAVES * 1024));
+      if (n == 3) {
+        pk.base += (size_t)BN * k_pitch;
+        pv.base += (size_t)BN * v_pitch;
+        ++pk.kt;
+        ++pv.kt;
+      }
+    };
+    if (__builtin_expect(act, 1)) {
+      // lane holds, for the query at position tile_pos, keys kv0 + 32b + 8*(i/4) + 4*hh + i%4
+      if (__builtin_expect(kv0 + BN - 1 > tile_pos0, 0)) {   // tile crosses this wave's diagonal (or the prompt's end)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (kv0 + 32 * b + 8 * (i >> 2) + 4 * hh + (i & 3) > tile_pos) S[b][i] = -INFINITY;
+      }
+      // p = exp2(S c - mc) in pb; is any of them 2 or more, infinite or NaN?
+      auto softmax_p = [&](float mc, bool loads) __attribute__((always_inline)) -> bool {
+        uint32_t any = 0;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int i = 0; i < 16; i += 4) {
+#pragma unroll
+            for (int e = i; e < i + 4; e += 2)
+              pb[b][e >> 1] = cvt_pk_bf16(__builtin_amdgcn_exp2f(S[b][e] * c - mc), __builtin_amdgcn_exp2f(S[b][e + 1] * c - mc));
+            any = any | pb[b][i >> 1] | pb[b][(i >> 1) + 1];
+            const int u = b * 4 + i / 4;
+            if (loads && (u & 1)) {
+              __builtin_amdgcn_sched_barrier(0);
+              load_piece(u >> 1);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        return (any & 0x40004000u) != 0;        // the top exponent bits
+      };
+      // an item's first tile has no reference yet; else the reference moves where a p is too large
+      bool move = true;
+      if (__builtin_expect(!first, 1)) move = softmax_p(m * c + ABOVE, true);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(move) != 0, 0)) {
+        float mx = S[0][0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[0][i]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[1][i]);
+        {
+          float mx2 = mx;                       // the other half's 32 keys of the same query (see prefill_kernel)
+          asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(mx), "+v"(mx2));
+          mx = fmaxf(mx, mx2);
+        }
+        const float m_new = fmaxf(m, mx);
+        const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) L[e] *= alpha;
+#pragma unroll
+        for (int blk = 0; blk < VB; ++blk)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) O[blk][e] *= alpha;
+        m = m_new;
+        softmax_p(m * c + ABOVE, false);
+      }
+    }
+    act_prev = act;
+    if (__builtin_expect(first, 0) && !last && more) touch_next_q();
+    barrier();
+    if (__builtin_expect(last && !more, 0)) {
+      if (act_prev) second_product(ST, [](int) {});
+      return false;
+    }
+    return true;
+  };
+  for (;;) {
+    if (!step(std::integral_constant<int, 0>{})) break;
+    if (!step(std::integral_constant<int, 1>{})) break;
+    if (!step(std::integral_constant<int, 2>{})) break;
+  }
+  if (!second_group) barrier();                 // as many as the second group
+  finish_item();
+}
+
 bool prefill_shape_supported(int dqk, int dv) {
   return (dqk == 64 && dv == 64) || (dqk == 128 && dv == 128) || (dqk == 192 && dv == 128);
 }
@@ -518,21 +927,22 @@ int prefill_block_m(int group) { return 32 * (WAVES / prefill_heads_per_block(gr
 template <int DQK, int DV>
 static void launch_hb(int hb, dim3 grid, hipStream_t stream, const bf16_t* q, const bf16_t* k, const bf16_t* v,
                       bf16_t* out, const PrefillWork* work, const int32_t* chain, int H, int Hkv, float c) {
-  const dim3 block(64 * WAVES);
-  if (hb == 8) hipLaunchKernelGGL((prefill_kernel<DQK, DV, 8>), grid, block, 0, stream, q, k, v, out, work, chain, H, Hkv, c);
-  else if (hb == 4) hipLaunchKernelGGL((prefill_kernel<DQK, DV, 4>), grid, block, 0, stream, q, k, v, out, work, chain, H, Hkv, c);
-  else if (hb == 2) hipLaunchKernelGGL((prefill_kernel<DQK, DV, 2>), grid, block, 0, stream, q, k, v, out, work, chain, H, Hkv, c);
-  else hipLaunchKernelGGL((prefill_kernel<DQK, DV, 1>), grid, block, 0, stream, q, k, v, out, work, chain, H, Hkv, c);
+  hipLaunchKernelGGL((hb == 8 ? prefill_kernel<DQK, DV, 8> : hb == 4 ? prefill_kernel<DQK, DV, 4> : hb == 2 ? prefill_kernel<DQK, DV, 2> : prefill_kernel<DQK, DV, 1>),
+                     grid, dim3(64 * WAVES), 0, stream, q, k, v, out, work, chain, H, Hkv, c);
 }
 
 hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillWork* d_work,
-                          const int32_t* d_chain, int n_blocks, int H, int Hkv, int dqk, int dv, float scale, hipStream_t stream) {
+                          const int32_t* d_chain, int n_blocks, int longest, int H, int Hkv, int dqk, int dv, float scale,
+                          hipStream_t stream) {
   const float c = scale * 1.4426950408889634f;
   const int hb = prefill_heads_per_block(H / Hkv);
   const dim3 grid((unsigned)n_blocks);
   const bf16_t *qq = (const bf16_t*)q, *kk = (const bf16_t*)k, *vv = (const bf16_t*)v;
   if (dqk == 64 && dv == 64) launch_hb<64, 64>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d_work, d_chain, H, Hkv, c);
   else if (dqk == 128 && dv == 128) launch_hb<128, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d_work, d_chain, H, Hkv, c);
+  else if (dqk == 192 && dv == 128 && longest > 6)
+    hipLaunchKernelGGL((hb == 8 ? prefill_192_kernel<8> : hb == 4 ? prefill_192_kernel<4> : hb == 2 ? prefill_192_kernel<2> : prefill_192_kernel<1>),
+                       grid, dim3(64 * WAVES), 0, stream, qq, kk, vv, (bf16_t*)out, d_work, d_chain, H, Hkv, c);
   else if (dqk == 192 && dv == 128) launch_hb<192, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d_work, d_chain, H, Hkv, c);
   else return hipErrorInvalidValue;
   return hipGetLastError();

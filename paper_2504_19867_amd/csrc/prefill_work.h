@@ -125,4 +125,11 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
   chain[(size_t)n_blocks] = (int32_t)work.size();
 }
 
+// Tiles of 64 keys that the longest item visits.
+inline int longest_item(const int32_t* cu_seqlens, const int32_t* prefix_lens, int n_req) {
+  int most = 0;
+  for (int r = 0; r < n_req; ++r) most = std::max(most, (cu_seqlens[r + 1] - cu_seqlens[r] - 1 + (prefix_lens ? prefix_lens[r] : 0)) / 64 + 1);
+  return most;
+}
+
 }  // namespace spd

@@ -305,7 +305,8 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   }
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 0, stream)) != SPD_OK) return rc;
   SPD_HIP(launch_prefill(b->q, att_k, att_v, b->out, (const PrefillWork*)ws, (const int32_t*)(ws + off_chain),
-                         n_blocks, b->n_q_heads, b->n_kv_heads, b->dim_qk, b->dim_v, b->scale, stream));
+                         n_blocks, longest_item(b->cu_seqlens, chunked ? b->prefix_lens : nullptr, b->n_req), b->n_q_heads, b->n_kv_heads,
+                         b->dim_qk, b->dim_v, b->scale, stream));
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 1, stream)) != SPD_OK) return rc;
   if ((rc = step.commit()) != SPD_OK) return rc;
   if (ctx->kernel_timing) {
