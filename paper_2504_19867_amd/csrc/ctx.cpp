@@ -156,6 +156,7 @@ extern "C" int spd_ctx_destroy(spd_ctx* ctx) {
       if (s.rope_dev) (void)hipFree(s.rope_dev);
       if (s.merge_counters) (void)hipFree(s.merge_counters);
       if (s.workspace) (void)hipFree(s.workspace);
+      if (s.parts) (void)hipFree(s.parts);
       for (auto& r : s.ws_retired) (void)hipFree(r.first);
       for (hipEvent_t e : {s.ev_start, s.ev_end, s.ev_switch, s.ev_cross})
         if (e) (void)hipEventDestroy(e);
@@ -394,25 +395,49 @@ static void workspace_release_retired(spd_ctx* ctx, int phase) {
   s.ws_retired.resize(keep);
 }
 
-int workspace_reserve(spd_ctx* ctx, int phase, size_t bytes, char** out) {
+// At least `bytes` of device memory in `buf`.
+static int buffer_reserve(spd_ctx* ctx, int phase, size_t bytes, char*& buf, size_t& buf_cap) {
   spd_phase_state& s = ctx->phase[phase];
-  if (s.ws_cap < bytes) {
-    size_t cap = std::max<size_t>(16u << 20, s.ws_cap);
+  if (buf_cap < bytes) {
+    size_t cap = std::max<size_t>(16u << 20, buf_cap);
     while (cap < bytes) cap *= 2;
     char* d = nullptr;
     SPD_HIP(hipMalloc((void**)&d, cap));
     // Earlier steps of this phase may still read the old buffer: it is kept until the last of them (the step
     // issued most recently; the one being built takes the new buffer) is known to have finished.  No wait here.
-    if (s.workspace) {
+    if (buf) {
       std::lock_guard<std::mutex> lk(s.ws_mu);
-      s.ws_retired.emplace_back(s.workspace, s.issue_seq.load(std::memory_order_acquire));
+      s.ws_retired.emplace_back(buf, s.issue_seq.load(std::memory_order_acquire));
     }
-    s.workspace = d;
-    s.ws_cap = cap;
+    buf = d;
+    buf_cap = cap;
     workspace_release_retired(ctx, phase);
   }
-  *out = s.workspace;
   return SPD_OK;
+}
+
+int workspace_reserve(spd_ctx* ctx, int phase, size_t bytes, char** out) {
+  spd_phase_state& s = ctx->phase[phase];
+  const int rc = buffer_reserve(ctx, phase, bytes, s.workspace, s.ws_cap);
+  *out = s.workspace;
+  return rc;
+}
+
+float* parts_reserve(spd_ctx* ctx, size_t bytes) {
+  spd_phase_state& s = ctx->phase[SPD_PHASE_PREFILL];
+  hipStream_t stream;
+  {
+    std::lock_guard<std::mutex> lk(ctx->part_mu);
+    stream = s.has_pending ? s.pending_stream : s.stream;
+  }
+  if (stream_capturing(ctx, stream)) return nullptr;
+  const int error = g_last_hip_error;
+  if (buffer_reserve(ctx, SPD_PHASE_PREFILL, bytes, s.parts, s.parts_cap) != SPD_OK) {
+    (void)hipGetLastError();
+    g_last_hip_error = error;
+    return nullptr;
+  }
+  return (float*)s.parts;
 }
 
 int kernel_timing_mark(spd_ctx* ctx, int phase, int which, hipStream_t stream) {

@@ -121,6 +121,23 @@ struct PrefillWork {
   int32_t head0;     // first query head of the workgroup's head group
   int32_t kv_row0;   // first row of the request's keys / values in the K, V tensors the kernel reads
   int32_t q_off;     // position of query row 0 in the request = number of cached tokens before it
+  int32_t kt0, kt1;  // the tiles of 64 keys to visit: all that the rows can see, or a part of them
+  int32_t part;      // number of the part, where its sums go; -1: the item is whole
+};
+// An item that was shared out: its parts are part0 .. part0 + n_parts - 1.
+struct PrefillMerge {
+  int32_t row0, len, q_tile, head0, part0, n_parts;
+};
+// floats that a part leaves: 8 waves x (32 rows x dv sums, reference and row sum of 32 rows)
+constexpr __host__ __device__ inline size_t prefill_part_floats(int dv) { return 8 * (size_t)(dv * 32 + 64); }
+// what launch_prefill reads on the device
+struct PrefillLists {
+  const PrefillWork* work;
+  const int32_t* chain;
+  int n_blocks;
+  const PrefillMerge* merge;
+  int n_merge;
+  float* parts;
 };
 
 // The entry point that allocates nothing keeps its device-side working memory in one static device
@@ -217,6 +234,8 @@ struct spd_phase_state {
   std::vector<int32_t> tmp_sizes, tmp_chunks, tmp_owner, tmp_last;
   char* workspace = nullptr;           // split-K partials (decode)
   size_t ws_cap = 0;
+  char* parts = nullptr;               // sums of items that were shared out (prefill)
+  size_t parts_cap = 0;
   // workspaces outgrown, with the number of the last step that may still read them: freed once that step has
   // finished (looked at when the workspace grows again, in spd_phase_sync and when the context goes)
   std::vector<std::pair<char*, uint64_t>> ws_retired;
@@ -281,6 +300,9 @@ int phase_seal(spd_ctx* ctx, int phase, hipStream_t stream);
 // true if step number `seq` of `phase` has finished on the GPU (any thread may ask)
 bool phase_step_done(spd_ctx* ctx, int phase, uint64_t seq);
 int workspace_reserve(spd_ctx* ctx, int phase, size_t bytes, char** out);
+// Memory for the parts of a prefill step's items, of its own, so that the workspace grows as ever; null: there is none, or the
+// phase's stream is being captured (the captured launches would outlive the buffer).
+float* parts_reserve(spd_ctx* ctx, size_t bytes);
 int kernel_timing_mark(spd_ctx* ctx, int phase, int which, hipStream_t stream);   // which: 0 begin, 1 end
 // rope.cpp: SPD_OK if the configuration is well-formed; the frequency table (rotary_dim / 2 doubles)
 int rope_config_check(const spd_rope_config* c);
@@ -335,9 +357,8 @@ hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLau
 constexpr int MLA_THREADS = 256;
 constexpr int MLA_CHUNK_PAGES = MLA_THREADS - DECODE_ITEM_WORDS;
 // one workgroup per chain: workgroup b computes the items d_work[d_chain[b]] .. d_work[d_chain[b + 1] - 1]
-hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillWork* d_work,
-                          const int32_t* d_chain, int n_blocks, int longest, int H, int Hkv, int dqk, int dv, float scale,
-                          hipStream_t stream);
+hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillLists& lists, int longest, int H, int Hkv, int dqk, int dv,
+                          float scale, hipStream_t stream);
 // x [T, K], w_gu [2 I, K] (joint gate/up rows in blocks of 32 + 32), out [T, I], all bf16 in device memory;
 // K a multiple of 32, I a multiple of 128
 // exclusive: as phase_exclusive says

@@ -66,12 +66,13 @@ __device__ inline void dma16s(const void* sbase, uint32_t voff, uint32_t lds_byt
 template <int DQK> __device__ inline int k_swz(int row) { return DQK == 128 ? (row & 15) : ((row >> 1) & 7); }
 template <int DV> __device__ inline int v_swz(int row) { return DV == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 
-template <int DQK, int DV, int HB>
+// PARTS: items may be parts of items (an instance of its own: the code for it costs the other steps up to 1 %)
+template <int DQK, int DV, int HB, bool PARTS>
 __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                          const bf16_t* __restrict__ v, bf16_t* __restrict__ out,
                                                          const PrefillWork* __restrict__ work,
                                                          const int32_t* __restrict__ chain, int H, int Hkv,
-                                                         float c /* scale * log2(e) */) {
+                                                         float c /* scale * log2(e) */, float* __restrict__ parts) {
   constexpr int QS = WAVES / HB;                // 32-row sub-tiles per workgroup
   constexpr int CHK = DQK / 8, CHV = DV / 8;    // 16-byte chunks per K / V row
   constexpr int K_BYTES = BN * DQK * 2, V_BYTES = BN * DV * 2, STAGE_BYTES = K_BYTES + V_BYTES;
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   // slots [64 ii, 64 ii + 64) of the stage: K slots first (row = slot / CHK), then V slots.
   // Slot s of a row holds the row's chunk s ^ swz(row).
   // The per-lane part of the address does not depend on the tile (except past the prompt's end).
-  auto slot_of = [&](int j, int& row, int& coff, uint32_t& pitch) {
+  auto slot_of = [&](int j, int& row, int& coff, uint32_t& pitch) __attribute__((always_inline)) {
     const int ii = wave + WAVES * j;
     if (ii < CHK) {
       const int slot = ii * 64 + lane, sl = slot % CHK;
@@ -132,19 +133,22 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   // moves the window when it is half way through it.  (Not with 192 dims: the touch below needs the full wait that
   // only the paired tiles have.)
   constexpr bool ITEM_LANES = DQK <= 128;
+  static_assert(ITEM_LANES || !PARTS, "parts come by lanes");
   int dsc_base = it;
-  int d_row0 = 0, d_len = 0, d_qtile = 0, d_head0 = 0, d_kvrow0 = 0, d_qoff = 0;
+  int d_row0 = 0, d_len = 0, d_qtile = 0, d_head0 = 0, d_kvrow0 = 0, d_qoff = 0, d_kt0 = 0, d_kt1 = 0, d_part = 0;
   auto load_items = [&](int base) __attribute__((always_inline)) {
     const PrefillWork pw = work[min(base + lane, it_end - 1)];
     d_row0 = pw.row0; d_len = pw.len; d_qtile = pw.q_tile; d_head0 = pw.head0; d_kvrow0 = pw.kv_row0; d_qoff = pw.q_off;
+    if constexpr (PARTS) { d_kt0 = pw.kt0; d_kt1 = pw.kt1; d_part = pw.part; }
     dsc_base = base;
   };
-  auto item_of = [&](int i) __attribute__((always_inline)) -> PrefillWork {
-    if constexpr (!ITEM_LANES) return work[i];
+  struct Rows { int row0, len, q_tile, head0, kv_row0, q_off; };
+  auto item_of = [&](int i) __attribute__((always_inline)) -> Rows {
+    if constexpr (!ITEM_LANES) return Rows{work[i].row0, work[i].len, work[i].q_tile, work[i].head0, work[i].kv_row0, work[i].q_off};
     const int l = i - dsc_base;
-    return PrefillWork{__builtin_amdgcn_readlane(d_row0, l), __builtin_amdgcn_readlane(d_len, l),
-                       __builtin_amdgcn_readlane(d_qtile, l), __builtin_amdgcn_readlane(d_head0, l),
-                       __builtin_amdgcn_readlane(d_kvrow0, l), __builtin_amdgcn_readlane(d_qoff, l)};
+    return Rows{__builtin_amdgcn_readlane(d_row0, l), __builtin_amdgcn_readlane(d_len, l),
+                __builtin_amdgcn_readlane(d_qtile, l), __builtin_amdgcn_readlane(d_head0, l),
+                __builtin_amdgcn_readlane(d_kvrow0, l), __builtin_amdgcn_readlane(d_qoff, l)};
   };
   if constexpr (ITEM_LANES) load_items(it);
   // ---- producer: the tile loads run ahead of the compute (a pair of tiles, or PD tiles where the
@@ -152,18 +156,17 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   // pt counts the tiles issued so far (tile number pt goes to stage pt % NSTAGE).
   int p_it = it, p_kt = 0, p_n = 0, p_kv_len = 0, pt = 0;
   const char *p_kb = nullptr, *p_vb = nullptr;
-  auto producer_item = [&]() {                  // producer state for item p_it
-    const PrefillWork pw = item_of(p_it);
+  auto producer_item = [&]() __attribute__((always_inline)) {                  // producer state for item p_it
+    const Rows pw = item_of(p_it);
     const int pg = pw.head0 / G;
     p_kv_len = pw.q_off + pw.len;
-    const int kv_end = min(p_kv_len, pw.q_off + pw.q_tile * (32 * QS) + 32 * QS);
-    p_n = (kv_end + BN - 1) / BN;
+    p_n = PARTS ? __builtin_amdgcn_readlane(d_kt1, p_it - dsc_base) : (min(p_kv_len, pw.q_off + pw.q_tile * (32 * QS) + 32 * QS) + BN - 1) / BN;
     p_kb = (const char*)(k + ((size_t)pw.kv_row0 * Hkv + pg) * DQK);
     p_vb = (const char*)(v + ((size_t)pw.kv_row0 * Hkv + pg) * DV);
-    p_kt = 0;
+    p_kt = PARTS ? __builtin_amdgcn_readlane(d_kt0, p_it - dsc_base) : 0;
   };
   producer_item();
-  auto produce_one = [&]() {
+  auto produce_one = [&]() __attribute__((always_inline)) {
     if (p_it >= it_end) return;
     const int kv0 = p_kt * BN;
     const uint32_t stage = smem_base + (uint32_t)(pt % NSTAGE) * STAGE_BYTES;
@@ -236,8 +239,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   for (int t = 0; t < (PAIRS ? 2 : PD); ++t) produce_one();
 
   // ---- state of the item being computed
-  PrefillWork w;
-  int h = 0, wave_q0 = 0, qi = 0, pos0 = 0, pos = 0, n_kv_tiles = 0, kt = 0;
+  Rows w;
+  int kt_first = 0, kt_end = 0, part = -1;
+  int h = 0, wave_q0 = 0, qi = 0, pos0 = 0, pos = 0, kt = 0;
   bool wave_active = false;
   bf16x8 qf[KS];                                // Q^T fragments (B operand: column = query, 8 consecutive dims per lane and k-step)
   f32x16 O[VB];
@@ -249,7 +253,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   uint32_t q_touch = 0;
   bool touch_next = false;
   auto touch_next_q = [&]() __attribute__((always_inline)) {
-    const PrefillWork w2 = item_of(it + 1);
+    const Rows w2 = item_of(it + 1);
     constexpr int LINES = DQK / 64;               // 128-byte lines per query row
     int r2 = w2.q_tile * (32 * QS) + 32 * (wave / HB) + lane / LINES;
     r2 = r2 < w2.len ? r2 : w2.len - 1;
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
     asm volatile("global_load_dword %0, %1, off" : "=v"(q_touch) : "v"(p2) : "memory");
     touch_next = false;
   };
-  auto item_begin = [&]() {
+  auto item_begin = [&]() __attribute__((always_inline)) {
     if (ITEM_LANES && it - dsc_base >= 32) load_items(it);      // (the producer is past `it` and less than 32 items ahead)
     w = item_of(it);
     h = w.head0 + wave % HB;
@@ -266,15 +270,19 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
     wave_active = wave_q0 < w.len;              // waves past the prompt's end only help loading
     qi = wave_q0 + n32;                         // this lane's query (row inside the request)
     const int qi_c = qi < w.len ? qi : w.len - 1;
-    const int kv_len = w.q_off + w.len;         // cached prefix + this step's rows
     pos0 = w.q_off + wave_q0;                   // position of this wave's first query in the request
     pos = w.q_off + qi;                         // ... of this lane's query
     const bf16_t* qp = q + ((size_t)(w.row0 + qi_c) * H + h) * DQK + 8 * hh;
 #pragma unroll
     for (int s = 0; s < KS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *(const uint4*)(qp + 16 * s));
-    const int kv_end = min(kv_len, w.q_off + q_start + 32 * QS);
-    n_kv_tiles = (kv_end + BN - 1) / BN;
-    kt = 0;
+    if constexpr (PARTS) {
+      kt = kt_first = __builtin_amdgcn_readlane(d_kt0, it - dsc_base);
+      kt_end = __builtin_amdgcn_readlane(d_kt1, it - dsc_base);
+      part = __builtin_amdgcn_readlane(d_part, it - dsc_base);
+    } else {
+      kt_end = (min(w.q_off + w.len, w.q_off + q_start + 32 * QS) + BN - 1) / BN;
+      kt = 0;
+    }
 #pragma unroll
     for (int i = 0; i < VB; ++i)
 #pragma unroll
@@ -287,8 +295,21 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
     for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(__builtin_bit_cast(uint4, qf[s]).x));
     touch_next = ITEM_LANES && it + 1 < it_end;
   };
-  auto item_end = [&]() {
+  auto item_end = [&]() __attribute__((always_inline)) {
     l += __shfl_xor(l, 32);
+    if (PARTS && part >= 0) {
+      // A part of an item: the sums as they are, register by register (1 KiB of consecutive bytes a time), and the softmax's
+      // reference and row sums behind them, for prefill_merge_kernel.
+      if (wave_active) {
+        float* base = parts + (size_t)part * prefill_part_floats(DV) + wave * (DV * 32 + 64);
+#pragma unroll
+        for (int blk = 0; blk < VB; ++blk)
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4)
+            *(f32x4*)(base + ((blk * 4 + i4) * 64 + lane) * 4) = f32x4{O[blk][4 * i4], O[blk][4 * i4 + 1], O[blk][4 * i4 + 2], O[blk][4 * i4 + 3]};
+        if (hh == 0) *(f32x2*)(base + DV * 32 + 2 * n32) = f32x2{m, l};
+      }
+    } else
     // Output: a lane holds one query row in 8-byte bits, 8 KiB apart from its neighbour's.  Each wave
     // turns its block round, 32 dims at a time, in its own piece of LDS and writes 64-byte row pieces.
     if (wave_active) {
@@ -315,7 +336,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
     }
   };
 
-  auto tile = [&](auto stc) {
+  auto tile = [&](auto stc) __attribute__((always_inline)) {
     const int ST = stc;                         // ring stage of tile kt: a constant when the loop is unrolled
     const int kv0 = kt * BN;
     if constexpr (PAIRS) {
@@ -422,7 +443,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
     };
     // (an item's first tile has no reference yet: the pass against it would be thrown away, so it is not made)
     float psum = INFINITY;
-    if (kt != 0) psum = softmax_p(m * c);
+    if (kt != kt_first) psum = softmax_p(m * c);
     if (__builtin_amdgcn_ballot_w64(!(psum < 0x1p60f)) != 0) {
       float mx = S[0][0];
 #pragma unroll
@@ -475,9 +496,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
 
 
   // one tile of the chain; false when the chain is finished
-  auto step = [&](auto stc) -> bool {
+  auto step = [&](auto stc) __attribute__((always_inline)) -> bool {
     tile(stc);
-    if (++kt == n_kv_tiles) {
+    if (++kt == kt_end) {
       item_end();
       if (++it >= it_end) return false;
       item_begin();
@@ -497,6 +518,50 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   } else {
     while (step(ct % NSTAGE)) {
     }
+  }
+}
+
+// Items whose keys were shared out over several workgroups: one wave per (item, wave of the item, 32 dims) adds the parts up,
+// each weighted with exp2((its reference - the largest one) c), and writes the rows as prefill_kernel does.
+template <int DV, int HB>
+__global__ __launch_bounds__(256) void prefill_merge_kernel(bf16_t* __restrict__ out, const PrefillMerge* __restrict__ items, const float* __restrict__ parts,
+                                                            int H, float c) {
+  constexpr int QS = WAVES / HB, VB = DV / 32, OPITCH = 32 * 2 + 16;
+  __shared__ __attribute__((aligned(16))) char smem[4 * 32 * OPITCH];
+  const int tid = threadIdx.x, lane = tid & 63, n32 = lane & 31, hh = lane >> 5;
+  const int unit = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (tid >> 6));   // grid: exactly a wave per unit
+  const int blk = unit % VB, wave = unit / VB % WAVES;
+  const PrefillMerge it = items[unit / (VB * WAVES)];
+  const int wave_q0 = it.q_tile * (32 * QS) + 32 * (wave / HB), rows = min(32, it.len - wave_q0);
+  if (rows <= 0) return;
+  const float* base = parts + (size_t)it.part0 * prefill_part_floats(DV) + wave * (DV * 32 + 64);
+  float m = -INFINITY, l = 0.f;
+  for (int p = 0; p < it.n_parts; ++p) m = fmaxf(m, base[p * prefill_part_floats(DV) + DV * 32 + 2 * n32]);
+  float o[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) o[e] = 0.f;
+  for (int p = 0; p < it.n_parts; ++p) {
+    const float* part = base + p * prefill_part_floats(DV);
+    const f32x2 ml = *(const f32x2*)(part + DV * 32 + 2 * n32);
+    const float f = __builtin_amdgcn_exp2f((ml.x - m) * c);
+    l += ml.y * f;
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 v = *(const f32x4*)(part + ((blk * 4 + i4) * 64 + lane) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[4 * i4 + e] += v[e] * f;
+    }
+  }
+  char* ost = smem + (tid >> 6) * (32 * OPITCH);   // a piece of its own per wave
+  const float inv = 1.f / l;
+#pragma unroll
+  for (int i4 = 0; i4 < 4; ++i4)
+    *(uint2*)(ost + n32 * OPITCH + (8 * i4 + 4 * hh) * 2) = uint2{cvt_pk_bf16(o[4 * i4] * inv, o[4 * i4 + 1] * inv), cvt_pk_bf16(o[4 * i4 + 2] * inv, o[4 * i4 + 3] * inv)};
+  bf16_t* obase = out + ((size_t)(it.row0 + wave_q0) * H + it.head0 + wave % HB) * DV + 32 * blk;
+#pragma unroll
+  for (int itr = 0; itr < 2; ++itr) {
+    const int i = lane + 64 * itr, r = i >> 2, cc = i & 3;
+    if (r < rows) *(uint4*)(obase + (size_t)r * H * DV + cc * 8) = *(const uint4*)(ost + r * OPITCH + cc * 16);
   }
 }
 
@@ -924,26 +989,41 @@ int prefill_heads_per_block(int group) {
 }
 int prefill_block_m(int group) { return 32 * (WAVES / prefill_heads_per_block(group)); }
 
-template <int DQK, int DV>
-static void launch_hb(int hb, dim3 grid, hipStream_t stream, const bf16_t* q, const bf16_t* k, const bf16_t* v,
-                      bf16_t* out, const PrefillWork* work, const int32_t* chain, int H, int Hkv, float c) {
-  hipLaunchKernelGGL((hb == 8 ? prefill_kernel<DQK, DV, 8> : hb == 4 ? prefill_kernel<DQK, DV, 4> : hb == 2 ? prefill_kernel<DQK, DV, 2> : prefill_kernel<DQK, DV, 1>),
-                     grid, dim3(64 * WAVES), 0, stream, q, k, v, out, work, chain, H, Hkv, c);
+template <int DQK, int DV, int HB>
+static void launch_items(dim3 grid, hipStream_t stream, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const PrefillLists& d, int H,
+                         int Hkv, float c) {
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES), 0, stream, q, k, v, out, d.work, d.chain, H, Hkv, c, d.parts); };
+  if constexpr (DQK <= 128) {
+    if (d.n_merge) {
+      launch(prefill_kernel<DQK, DV, HB, true>);
+      hipLaunchKernelGGL((prefill_merge_kernel<DV, HB>), dim3((unsigned)(d.n_merge * WAVES * (DV / 32) / 4)), dim3(256), 0, stream, out, d.merge, d.parts, H, c);
+      return;
+    }
+  }
+  launch(prefill_kernel<DQK, DV, HB, false>);
 }
 
-hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillWork* d_work,
-                          const int32_t* d_chain, int n_blocks, int longest, int H, int Hkv, int dqk, int dv, float scale,
-                          hipStream_t stream) {
+template <int DQK, int DV>
+static void launch_hb(int hb, dim3 grid, hipStream_t stream, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const PrefillLists& d, int H,
+                      int Hkv, float c) {
+  if (hb == 8) launch_items<DQK, DV, 8>(grid, stream, q, k, v, out, d, H, Hkv, c);
+  else if (hb == 4) launch_items<DQK, DV, 4>(grid, stream, q, k, v, out, d, H, Hkv, c);
+  else if (hb == 2) launch_items<DQK, DV, 2>(grid, stream, q, k, v, out, d, H, Hkv, c);
+  else launch_items<DQK, DV, 1>(grid, stream, q, k, v, out, d, H, Hkv, c);
+}
+
+hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillLists& d, int longest, int H, int Hkv, int dqk, int dv,
+                          float scale, hipStream_t stream) {
   const float c = scale * 1.4426950408889634f;
   const int hb = prefill_heads_per_block(H / Hkv);
-  const dim3 grid((unsigned)n_blocks);
+  const dim3 grid((unsigned)d.n_blocks);
   const bf16_t *qq = (const bf16_t*)q, *kk = (const bf16_t*)k, *vv = (const bf16_t*)v;
-  if (dqk == 64 && dv == 64) launch_hb<64, 64>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d_work, d_chain, H, Hkv, c);
-  else if (dqk == 128 && dv == 128) launch_hb<128, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d_work, d_chain, H, Hkv, c);
+  if (dqk == 64 && dv == 64) launch_hb<64, 64>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
+  else if (dqk == 128 && dv == 128) launch_hb<128, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
   else if (dqk == 192 && dv == 128 && longest > 6)
     hipLaunchKernelGGL((hb == 8 ? prefill_192_kernel<8> : hb == 4 ? prefill_192_kernel<4> : hb == 2 ? prefill_192_kernel<2> : prefill_192_kernel<1>),
-                       grid, dim3(64 * WAVES), 0, stream, qq, kk, vv, (bf16_t*)out, d_work, d_chain, H, Hkv, c);
-  else if (dqk == 192 && dv == 128) launch_hb<192, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d_work, d_chain, H, Hkv, c);
+                       grid, dim3(64 * WAVES), 0, stream, qq, kk, vv, (bf16_t*)out, d.work, d.chain, H, Hkv, c);
+  else if (dqk == 192 && dv == 128) launch_hb<192, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -140,7 +140,7 @@ hipError_t launch_decode_gqa(const PoolGeom&, char*, const DecodeLaunch& d, hipS
 }
 hipError_t launch_decode_prepare(const PoolGeom&, char*, const DecodeLaunch& d, int, void*, hipStream_t s) { return launch(s, d.mark); }
 hipError_t launch_decode_mla(const PoolGeom& g, char* b, const DecodeLaunch& d, hipStream_t s) { return launch_decode_gqa(g, b, d, s); }
-hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillWork*, const int32_t*, int, int, int, int, int, int, float,
+hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillLists&, int, int, int, int, int, float,
                           hipStream_t s) { return launch(s, StepMark{}); }
 hipError_t launch_rope(void*, int, void*, int, int, int, int, bool, int, const int32_t*, const double*, const StepMark& m, hipStream_t s) { return launch(s, m); }
 hipError_t launch_probe(int32_t*, int, hipStream_t) { return hipErrorUnknown; }

@@ -1,0 +1,47 @@
+// Prints how a prefill batch is dealt to chains (csrc/prefill_work.h), one batch per input line:
+//   share persistent whole_items n_q_heads n_kv_heads n_req (len prefix)...
+// Answer: "n_chains n_work n_merge", the chains' bounds, a line "row0 len q_tile head0 kv_row0 q_off kt0 kt1 part" per item and a line
+// "row0 len q_tile head0 part0 n_parts" per merged one.
+#include <iostream>
+#include <sstream>
+#include <string>
+
+#include "prefill_work.h"
+
+namespace spd {
+// (as the kernels' file has them: eight waves, HB query heads of a KV head each)
+int prefill_heads_per_block(int group) {
+  for (int hb = 8; hb > 1; hb >>= 1)
+    if (group % hb == 0) return hb;
+  return 1;
+}
+int prefill_block_m(int group) { return 32 * (8 / prefill_heads_per_block(group)); }
+}  // namespace spd
+
+int main() {
+  using namespace spd;
+  std::string line;
+  while (std::getline(std::cin, line)) {
+    std::istringstream in(line);
+    int share, persistent, whole, H, Hkv, n;
+    in >> share >> persistent >> whole >> H >> Hkv >> n;
+    std::vector<int32_t> cu(1, 0), pre, kv(1, 0);
+    for (int i = 0; i < n; ++i) {
+      int len, p;
+      in >> len >> p;
+      cu.push_back(cu.back() + len);
+      pre.push_back(p);
+      kv.push_back(kv.back() + len + p);
+    }
+    std::vector<PrefillWork> work;
+    std::vector<int32_t> chain;
+    std::vector<PrefillMerge> merge;
+    build_prefill_chains(cu.data(), pre.data(), kv.data(), n, H, Hkv, 8, share, persistent != 0, work, chain, whole ? nullptr : &merge);
+    std::printf("%zu %zu %zu\n", chain.size() - 1, work.size(), merge.size());
+    for (int32_t c : chain) std::printf("%d ", c);
+    std::printf("\n");
+    for (const PrefillWork& w : work)
+      std::printf("%d %d %d %d %d %d %d %d %d\n", w.row0, w.len, w.q_tile, w.head0, w.kv_row0, w.q_off, w.kt0, w.kt1, w.part);
+    for (const PrefillMerge& m : merge) std::printf("%d %d %d %d %d %d\n", m.row0, m.len, m.q_tile, m.head0, m.part0, m.n_parts);
+  }
+}

@@ -147,3 +147,37 @@ def test_workspace_grows_between_steps_in_flight():
     assert_parity(host_f64(out_s), want_s, "step that read the workspace before it grew")
     assert_parity(host_f64(out_b), want_b, "step that made it grow")
     gp.close()
+
+
+# heads, dims, (prefix, piece) per request, CUs of a share of its own (0: all of them, with the other phase), drift of the scores in nats
+@pytest.mark.parametrize("H,Hkv,d,reqs,cus,rise", [
+    (8, 2, 128, ((2805, 14), (1500, 7)), 0, 0.0),                  # parts of one length, rows past the piece
+    (16, 2, 128, ((3000, 1),), 64, 0.0),                           # one token
+    (8, 2, 128, ((2048, 129), (2111, 64), (0, 40)), 32, 0.0),      # a prefix that ends on a tile, pieces of several items
+    (3, 3, 64, ((1984, 300), (100, 33)), 32, 0.0),                 # 64 dims, 256 rows per item, waves whose rows begin behind a part's tiles
+    (5, 1, 128, ((2500, 70),), 96, 0.0),
+    (8, 2, 128, ((2000, 50),), 0, 300.0),                          # references far apart
+    (8, 2, 128, ((2000, 50),), 0, -300.0),
+])
+def test_items_shared_out_by_keys(H, Hkv, d, reqs, cus, rise):
+    """Few items behind long prefixes: their keys go to several workgroups, whose sums a second launch adds up."""
+    layer = W.LayerShape("gqa", H, Hkv, d, d, 16)
+    lens = tuple(p + n for p, n in reqs)
+    scale = 1.0 / math.sqrt(d)
+    q, k, v, cu = W.prefill_inputs_drifting(layer, lens, seed=7 + H, rise=rise, scale=scale) if rise else W.prefill_inputs(layer, lens, seed=7 + H)
+    gp = GpuPool(layer, sum(-(-n // 16) for n in lens) + 4, poison=True)
+    if cus:
+        gp.ctx.set_partition(cus, gp.ctx.device_info()[0] - cus)
+    cuts = [[0, p, p + n] if p else [0, n] for p, n in reqs]
+    outs = []
+    for _ in range(2):
+        out = run_chunks(gp, q, k, v, cu, cuts, [1 + i for i in range(len(reqs))], scale)
+        outs.append(host_bits(out))
+        for i in range(len(reqs)):
+            gp.pool.kv_free(1 + i)
+    np.testing.assert_array_equal(outs[0], outs[1])
+    got = host_f64(out)
+    for r, (p, n) in enumerate(reqs):
+        want = OA.chunk_attention(f64(q[cu[r] + p:cu[r + 1]]), f64(k[cu[r]:cu[r + 1]]), f64(v[cu[r]:cu[r + 1]]), scale)
+        assert_parity(got[cu[r] + p:cu[r + 1]], want, f"request {r}: {n} tokens behind {p}")
+    gp.close()

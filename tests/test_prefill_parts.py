@@ -1,0 +1,94 @@
+"""The host's dealing of prefill items to chains, parts of items among them, asked through a small program compiled for the CPU: every
+tile of every item is visited once whichever way the batch is dealt, and the parts keep the conditions their kernel relies on."""
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2504_19867_amd", "csrc")
+# share, persistent, q heads, KV heads, (len, prefix) per request
+FEW = [(256, 0, 32, 8, ((14, 2805), (7, 2805))), (64, 1, 64, 8, ((1, 8000),)), (128, 1, 32, 8, ((512, 8000),)),
+       (256, 0, 32, 8, ((532, 0), (355, 5023), (605, 3058), (867, 2188))), (32, 1, 5, 1, ((300, 4000),)), (96, 1, 8, 8, ((1, 0), (257, 6000)))]
+MANY = [(128, 1, 64, 8, ((4096, 0),) * 4), (256, 0, 32, 8, ((2048, 0),) * 4), (128, 1, 32, 8, ((30, 0),) * 50), (128, 1, 8, 8, ((128, 0),) * 2)]
+
+
+def _deal(tmp_path, batches):
+    gxx = shutil.which("g++")
+    if gxx is None or not os.path.isdir("/opt/rocm/include"):
+        pytest.skip("needs g++ and the HIP headers")
+    exe = str(tmp_path / "dump")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(ROOT, "tests", "prefill_parts_dump.cpp"), "-o", exe], check=True)
+    text = ""
+    for whole in (0, 1):
+        for share, persistent, H, Hkv, reqs in batches:
+            text += " ".join(map(str, (share, persistent, whole, H, Hkv, len(reqs), *(x for r in reqs for x in r)))) + "\n"
+    out = iter(subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=300).stdout.split("\n"))
+    answers = []
+    for _ in range(2 * len(batches)):
+        n_chains, n_work, n_merge = map(int, next(out).split())
+        bounds = list(map(int, next(out).split()))
+        assert len(bounds) == n_chains + 1 and bounds[0] == 0 and bounds[-1] == n_work and bounds == sorted(bounds)
+        work = [tuple(map(int, next(out).split())) for _ in range(n_work)]
+        answers.append((bounds, work, [tuple(map(int, next(out).split())) for _ in range(n_merge)]))
+    return answers[:len(batches)], answers[len(batches):]
+
+
+def _check(batch, got, plain):
+    share, persistent, H, Hkv, _ = batch
+    G = H // Hkv
+    hb = next(h for h in (8, 4, 2, 1) if G % h == 0)
+    bm = 32 * (8 // hb)
+    bounds, work, merge = got
+    whole = {(w[:6]): w[7] for w in plain[1]}                     # item -> its tiles
+    assert len(whole) == len(plain[1]) and all(w[6] == 0 and w[8] == -1 for w in plain[1]) and not plain[2]
+    seen = {}
+    for w in work:
+        seen.setdefault(w[:6], []).append(w[6:])
+    assert set(seen) == set(whole)
+    parts_of = {}
+    for m in merge:
+        parts_of[m[:4]] = m[4:]
+    n_parts = 0
+    for item, ranges in seen.items():
+        ranges.sort()
+        assert ranges[0][0] == 0 and ranges[-1][1] == whole[item]
+        assert all(a[1] == b[0] for a, b in zip(ranges, ranges[1:])) and all(a < b for a, b, _ in ranges)
+        if len(ranges) == 1:
+            assert ranges[0][2] == -1
+            continue
+        n_parts += len(ranges)
+        first_row_tile = (item[5] + item[2] * bm) // 64
+        assert all(a <= first_row_tile for a, _, _ in ranges)     # every row has keys in every part
+        assert all(b - a >= 8 for a, b, _ in ranges)
+        part0, n = parts_of.pop(item[:4])
+        assert n == len(ranges) and [p for _, _, p in ranges] == list(range(part0, part0 + n))
+    assert not parts_of                                           # nothing is merged that was not cut
+    if merge:
+        assert len(bounds) - 1 == share
+        loads = [sum(w[7] - w[6] + 4 + (w[8] >= 0) for w in work[a:b]) for a, b in zip(bounds, bounds[1:])]
+        assert max(loads) <= max(t + 4 for t in whole.values()) * 2 and n_parts <= 2 * share + len(merge)
+        numbers = sorted(w[8] for w in work if w[8] >= 0)
+        assert numbers == list(range(n_parts))
+    return len(merge)
+
+
+def test_items_are_shared_out_where_a_few_long_ones_would_hold_up_the_step(tmp_path):
+    got, plain = _deal(tmp_path, FEW + MANY)
+    n = [_check(b, g, p) for b, g, p in zip(FEW + MANY, got, plain)]
+    assert all(n[:len(FEW)]) and not any(n[len(FEW):]), n
+
+
+def test_random_batches(tmp_path):
+    rng = random.Random(3)
+    batches = []
+    for _ in range(150):
+        H, Hkv = rng.choice(((32, 8), (64, 8), (8, 8), (5, 1), (6, 2), (16, 2)))
+        top, deep = 2 ** rng.randint(0, 11), 2 ** rng.randint(0, 14)
+        reqs = tuple((rng.randint(1, top), rng.choice((0, rng.randint(0, deep)))) for _ in range(rng.randint(1, 12)))
+        batches.append((rng.choice((32, 64, 96, 128, 160, 192, 224, 256, 40)), rng.randint(0, 1), H, Hkv, reqs))
+    got, plain = _deal(tmp_path, batches)
+    assert sum(bool(_check(b, g, p)) for b, g, p in zip(batches, got, plain)) > 20
