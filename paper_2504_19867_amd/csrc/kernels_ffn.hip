@@ -482,7 +482,7 @@ typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2))); 
 // one stage ahead: one barrier per 8 slices.
 // The product is taken transposed (weights are the A operand): a lane then has four consecutive outputs of one token.
 // <NB, 8, 8>: 256 joint rows per workgroup, 128 KiB of weights on the way per CU; <NB, 4, 16>: 128 rows, the same bytes on the
-// way from four waves.  With the weights staged through LDS (at most 96 KiB on the way, a third to a fifth of the stages taken
+// way from four waves; five to seven waves where those fill the share's compute units better (launch_stream).  With the weights staged through LDS (at most 96 KiB on the way, a third to a fifth of the stages taken
 // by x, a barrier per slice) 64 tokens of hidden 4096, inter 14336 took 68 us on 128 CUs and 48 on 256; now 55 and 42 us (4.3 and
 // 5.7 TB/s).  A ring of 16 slices with eight waves is slower (56 us; 75 against 62 at 128 tokens), and so are loads
 // without the non-temporal mark (61 us).
@@ -493,15 +493,16 @@ __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const
   constexpr int XS = 8;                           // slices per x stage
   constexpr int ROWS = 16 * NB, CHUNKS = 4 * XS;  // 16-byte chunks of a row per stage
   constexpr int PITCH = (ROWS + 1) * 16;          // bytes per chunk column [chunk][row]: the odd row spreads the writes over the banks
-  constexpr int XL = ROWS * CHUNKS / (64 * WAVES);   // 16-byte pieces of a stage per thread
-  static_assert(RING % XS == 0 && ROWS * CHUNKS % (64 * WAVES) == 0, "whole stages per ring, whole pieces per thread");
+  constexpr int PIECES = ROWS * CHUNKS, XL = (PIECES + 64 * WAVES - 1) / (64 * WAVES);   // 16-byte pieces of a stage, per thread
+  static_assert(RING % XS == 0, "whole stages per ring");
   __shared__ __attribute__((aligned(1024))) char smem[2 * CHUNKS * PITCH];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n16 = lane & 15, c4 = lane >> 4;
   const int n_slices = K / BK, last = n_slices - 1;
   // this wave's rows: half `hf` of joint block `jb` (64 rows)
-  const int u = (int)blockIdx.x * WAVES + wave, jb = u >> 1, hf = u & 1;
+  // (where the waves of the last workgroup are more than there are rows left, the rest of them repeat the last rows and store nothing)
+  const int n_units = I / 16, u = min((int)blockIdx.x * WAVES + wave, n_units - 1), jb = u >> 1, hf = u & 1;
   const char* wb = (const char*)w + (size_t)(jb >> 2) * n_slices * 16384 + (size_t)((jb & 3) * 64 + hf * 16) * 64;
   const uint32_t w_off = (uint32_t)(n16 * 64 + ((c4 ^ ((n16 >> 2) & 3)) * 16));
   auto load_w = [&](int s, int half) __attribute__((always_inline)) -> u32x4 {   // half 0: gate, 1: up rows of slice s
@@ -520,7 +521,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const
 #pragma unroll
     for (int j = 0; j < XL; ++j) {
       const int i = tid + 64 * WAVES * j;
-      *(u32x4*)(smem + buf * (CHUNKS * PITCH) + (i % CHUNKS) * PITCH + (i / CHUNKS) * 16) = xr[j];
+      if (PIECES % (64 * WAVES) == 0 || i < PIECES) *(u32x4*)(smem + buf * (CHUNKS * PITCH) + (i % CHUNKS) * PITCH + (i / CHUNKS) * 16) = xr[j];
     }
   };
   f32x4 acc[2][NB];
@@ -591,7 +592,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const
       const float g = acc[0][b][i];
       y[i] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * acc[1][b][i];
     }
-    if (t < T)
+    if (t < T && (int)blockIdx.x * WAVES + wave < n_units)
       *(u32x2_any*)(out + (size_t)t * I + 32 * jb + 16 * hf + 4 * c4) = u32x2_any{cvt_bf16(y[0]) | cvt_bf16(y[1]) << 16, cvt_bf16(y[2]) | cvt_bf16(y[3]) << 16};
   }
 }
@@ -631,15 +632,34 @@ static hipError_t launch_tiles(Kernel kernel, const void* x, const void* w_gu, v
 
 template <int NB>
 static hipError_t launch_stream(const void* x, const void* w_gu, void* out, int T, int K, int I, int cus, const StepMark& mark, hipStream_t stream) {
-  const bf16_t *xx = (const bf16_t*)x, *ww = (const bf16_t*)w_gu;
-  // A compute unit runs one workgroup at a time.  A narrow one (four waves, half the rows) takes 0.6 of a wide one's time, so
-  // narrow ones pay where the share runs all of them at once, and wide ones otherwise; 64 tokens, wide / narrow: hidden 4096, inter
-  // 14336 on 256 CUs (112 / 224 workgroups) 55 / 41 us, on 128 55 / 65; 8192, 7168 on 128 (56 / 112) 97 / 59, on 64 98 / 109; 2048,
-  // 5632 on 128 (44 / 88) 28 / 19, on 64 28 / 34.
-  if (2 * I / 128 > cus)
-    hipLaunchKernelGGL((ffn_gate_up_stream_kernel<NB, 8, 8>), dim3((unsigned)(2 * I / 256)), dim3(512), 0, stream, xx, ww, (bf16_t*)out, T, K, I, mark);
-  else
-    hipLaunchKernelGGL((ffn_gate_up_stream_kernel<NB, 4, 16>), dim3((unsigned)(2 * I / 128)), dim3(256), 0, stream, xx, ww, (bf16_t*)out, T, K, I, mark);
+  const int units = I / 16;                       // rows that one wave takes
+  auto launch = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((units + waves - 1) / waves)), dim3((unsigned)(64 * waves)), 0, stream, (const bf16_t*)x, (const bf16_t*)w_gu,
+                       (bf16_t*)out, T, K, I, mark);
+  };
+  // A compute unit runs one workgroup at a time, and one of few waves takes longer per wave (few loads on the way): 64 tokens of hidden
+  // 4096, inter 7168, all workgroups at once, eight to four waves 53, 50.5, 45.7, 40.4, 35.8 us; 128 tokens 60 and 42.7 with eight and
+  // four (the x pieces of other counts do not fit their registers: 78 .. 86).  So the number of rounds decides.  64 tokens of
+  // inter 14336 (896 units), eight waves / the ones taken: 64 CUs 102 / 98 (7), 96 101 / 77 (5), 128 57 / 55.6 (7), 160 57 / 50 (6), 192 57 / 45.5
+  // (5), 256 57 / 43 (4); with only eight and four to choose from the first five took eight.
+  static const int cost[] = {NB <= 4 ? 68 : 71, 77, 87, 96, 100};   // of a workgroup of 4 .. 8 waves
+  int waves = 8;
+  long least = 0;
+  for (int n = 8; n >= 4; --n) {
+    if (NB > 4 && n != 8 && n != 4) continue;
+    const long wgs = (units + n - 1) / n, t = ((wgs + cus - 1) / cus) * cost[n - 4];
+    if (n == 8 || t < least) {
+      least = t;
+      waves = n;
+    }
+  }
+  if constexpr (NB <= 4) {
+    if (waves == 7) launch(ffn_gate_up_stream_kernel<NB, 7, 8>, 7);
+    if (waves == 6) launch(ffn_gate_up_stream_kernel<NB, 6, 8>, 6);
+    if (waves == 5) launch(ffn_gate_up_stream_kernel<NB, 5, 8>, 5);
+  }
+  if (waves == 8) launch(ffn_gate_up_stream_kernel<NB, 8, 8>, 8);
+  if (waves == 4) launch(ffn_gate_up_stream_kernel<NB, 4, 16>, 4);
   return hipGetLastError();
 }
 

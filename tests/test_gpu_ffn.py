@@ -82,6 +82,25 @@ def test_gate_up_streamed_weights(T, K, I, cus):
     ctx.close()
 
 
+@pytest.mark.parametrize("T", [1, 17, 33, 64, 65])
+@pytest.mark.parametrize("K,I,cus,waves", [(288, 3584, 32, 7), (512, 2944, 32, 6), (96, 2432, 32, 5), (544, 2176, 32, 5), (320, 4736, 64, 5)])
+def test_gate_up_streamed_weights_by_five_to_seven_waves(T, K, I, cus, waves):
+    """Shares that 16-row units fill best with workgroups of five to seven waves (up to 64 tokens): the last workgroup's spare waves
+    (2944 / 16 = 184 = 30 x 6 + 4 units, 152 = 30 x 5 + 2, 136 = 27 x 5 + 1, 296 = 59 x 5 + 1) store nothing, and no row past the batch is written."""
+    ctx = S.Context(0)
+    ctx.set_partition(ctx.device_info()[0] - cus, cus)
+    xb, wgb, wub = W.ffn_inputs(T, K, I, seed=2300 + T + I)
+    x, wg, wu = dev_bf16(xb), dev_bf16(wgb), dev_bf16(wub)
+    w_gu = torch.empty((2 * I, K), dtype=torch.bfloat16, device=DEV)
+    out = torch.full((T + 2, I), 7.0, dtype=torch.bfloat16, device=DEV)
+    ctx.ffn_pack_gate_up(DEC, wg, wu, w_gu, K, I)
+    ctx.ffn_gate_up(DEC, x, w_gu, out, T, K, I)
+    ctx.phase_sync(DEC)
+    assert (out[T:] == 7.0).all()
+    _assert_ffn(host_f64(out[:T]), F.gate_up(f64(xb), f64(wgb), f64(wub)), f"ffn streamed weights, {waves} waves, T={T} K={K} I={I}")
+    ctx.close()
+
+
 @pytest.mark.parametrize("K", [32, 64, 96, 128, 160, 512])
 @pytest.mark.parametrize("T,I,cus", [(1537, 1024, 32), (300, 4224, 32), (257, 1152, 64), (1025, 256, 0)])
 def test_gate_up_several_tiles_per_workgroup(T, I, cus, K):
