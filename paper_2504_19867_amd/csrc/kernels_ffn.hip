@@ -20,7 +20,7 @@
 //
 // Decode batches of up to 128 tokens are bound by reading the weights once and have a kernel of their own
 // (ffn_gate_up_stream_kernel); between 128 and 256 tokens there are 128 x 128 tiles (ffn_gate_up_small_kernel: four waves, two
-// workgroups per compute unit), where 256 x 256 ones would leave half of the share's compute units without a workgroup.
+// workgroups per compute unit), where a share has a compute unit for each of them.
 #include "internal.h"
 
 #include <type_traits>
@@ -671,9 +671,12 @@ hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T,
   if (T <= 32) return launch_stream<2>(x, w_gu, out, T, K, I, cus, mark, stream);
   if (T <= 64) return launch_stream<4>(x, w_gu, out, T, K, I, cus, mark, stream);
   if (T <= 128) return launch_stream<8>(x, w_gu, out, T, K, I, cus, mark, stream);
-  // the small tile where the large one would leave half of the share's compute units without a workgroup
+  // the small tile where each of its workgroups then has a compute unit to itself; two of them on one take longer than one of the large
+  // tile's.  Small / large, hidden 8192, inter 7168 (56 large tiles): 256 CUs 112 / 147 us at 256 tokens, 192 152 / 147, 128 171 / 147 (137 /
+  // 135 at 129); hidden 4096, inter 14336 (112): 256 CUs 101 / 84 at 256 tokens, 80 / 75 at 129.  (129 tokens of the former on 160 CUs are the
+  // exception measured: 130 / 136.)
   const int large_tiles = ((T + 255) / 256) * (2 * I / 256);
-  if (T <= 256 && 2 * large_tiles <= cus) return launch_tiles<128>(ffn_gate_up_small_kernel, x, w_gu, out, T, K, I, xcds, 0, mark, stream);
+  if (T <= 256 && 4 * large_tiles <= cus) return launch_tiles<128>(ffn_gate_up_small_kernel, x, w_gu, out, T, K, I, xcds, 0, mark, stream);
   return launch_tiles<256>(ffn_gate_up_large_kernel, x, w_gu, out, T, K, I, xcds, exclusive ? cus : 0, mark, stream);
 }
 
