@@ -435,7 +435,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
           const float p1 = __builtin_amdgcn_exp2f(S[b][i + 1] * c - mc);
           pb[b][i >> 1] = cvt_pk_bf16(p0, p1);
           // the row sum runs over the rounded values, the ones the second product multiplies: two per
-          // instruction (the compiler places the wait states that a dot product's result needs)
+          // instruction (the compiler places the wait states that a dot product's result needs).  As 4x4x4 MFMAs in the second
+          // product, as in prefill_192_kernel: 8 x 4096 tokens of 64 heads on 128 CUs 3079 -> 3348 us.
           ls[(i >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pb[b][i >> 1]),
                                                              __builtin_bit_cast(bf16x2, ones2), ls[(i >> 1) & 3], false);
         }

@@ -33,9 +33,10 @@ struct PrefillItem {
 
 // ---- Sharing items out by keys.  A step with few items, or with a few long ones (short pieces of prompts behind long cached
 // prefixes), leaves most compute units idle while the longest item runs.  Then the chains get about the same weight, and an
-// item that none of them has room for is cut: each part leaves its sums in memory, and a second launch adds them up.  Whole step, 32 heads: 2 pieces of up to 14 tokens behind 2805 on 256 CUs 63.9 -> 38 us; 512 tokens behind
-// 8000 on 128 CUs 193 -> 121; one token behind 8000, 64 heads on 64 CUs 186 -> 61; 4 pieces of 355 .. 867 behind up to 5023 on 256 CUs (312
-// items of up to 89 tiles, mean load 57, now at most 61; with all compute units busy the clock is lower) 159 -> 139.
+// item that none of them has room for is cut: each part leaves its sums in memory, and a second launch adds them up.  Whole step, 32
+// heads: 2 pieces of up to 14 tokens behind 2805 on 256 CUs 63.9 -> 38 us; 512 tokens behind 8000 on 128 CUs 193 -> 121; one token behind
+// 8000, 64 heads on 64 CUs 186 -> 61; 4 pieces of 355 .. 867 behind up to 5023 on 256 CUs (312 items of up to 89 tiles, mean load 57, now
+// at most 61; with all compute units busy the clock is lower) 159 -> 139.
 // A part pays its item's fixed cost again and one tile for writing its sums; the second launch costs what six tiles do.  Parts are no
 // shorter than eight tiles.  No part begins behind the item's first row, so that every row has keys in every part.
 constexpr long PART_COST_TILES = 1, MERGE_COST_TILES = 6, LEAST_PART_TILES = 8;
