@@ -460,14 +460,16 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
         mx = fmaxf(mx, mx2);
       }
       const float m_new = fmaxf(m, mx);
-      const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c);
+      // (a part of an item may begin with tiles whose scores are all -inf: they leave the sums at 0 and the reference where it is)
+      const bool none = PARTS && m_new == -INFINITY;
+      const float alpha = none ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * c);
       l *= alpha;
 #pragma unroll
       for (int blk = 0; blk < VB; ++blk)
 #pragma unroll
         for (int e = 0; e < 16; ++e) O[blk][e] *= alpha;
       m = m_new;
-      psum = softmax_p(m * c);
+      psum = softmax_p(none ? 0.f : m * c);
     }
     l += psum;
     __builtin_amdgcn_s_setprio(1);

@@ -181,3 +181,27 @@ def test_items_shared_out_by_keys(H, Hkv, d, reqs, cus, rise):
         want = OA.chunk_attention(f64(q[cu[r] + p:cu[r + 1]]), f64(k[cu[r]:cu[r + 1]]), f64(v[cu[r]:cu[r + 1]]), scale)
         assert_parity(got[cu[r] + p:cu[r + 1]], want, f"request {r}: {n} tokens behind {p}")
     gp.close()
+
+
+@pytest.mark.parametrize("H,Hkv,d,bits", [(16, 2, 128, 0xFF80), (16, 2, 128, 0xFF7F), (8, 8, 64, 0xFF80)])     # -inf, the lowest finite value
+def test_items_shared_out_whose_parts_see_only_masked_keys(H, Hkv, d, bits):
+    """Keys that no query can choose (scores of -inf, or so low that fp32 takes them there) from the second tile of the prefix to its
+    end: whole parts of the item hold nothing else, and they weigh nothing."""
+    prefix, n = 3000, 5
+    layer = W.LayerShape("gqa", H, Hkv, d, d, 16)
+    scale = 1.0 / math.sqrt(d)
+    q, k, v, cu = W.prefill_inputs(layer, (prefix + n,), seed=5)
+    q, k = q.copy(), k.copy()
+    q[prefix:, :, 0] = 0x4080                                        # 4.0
+    k[64:prefix, :, 0] = bits
+    gp = GpuPool(layer, -(-(prefix + n) // 16) + 4, poison=True)
+    gp.ctx.set_partition(64, gp.ctx.device_info()[0] - 64)
+    # the prefix is written as pages, not computed: its own rows see only masked keys
+    gp.pool.kv_reserve(1, prefix)
+    gp.pool.kv_write(PRE, 1, 0, prefix, dev_bf16(k[:prefix]), dev_bf16(v[:prefix]))
+    out = torch.empty((n, H, d), dtype=torch.bfloat16, device=DEV)
+    gp.pool.prefill_step([1], [0, n], dev_bf16(q[prefix:]), dev_bf16(k[prefix:]), dev_bf16(v[prefix:]), out, H, Hkv, d, d, scale, prefix_lens=[prefix])
+    gp.ctx.phase_sync(PRE)
+    want = OA.chunk_attention(f64(q[prefix:]), f64(k), f64(v), scale)
+    assert_parity(host_f64(out), want, f"{n} tokens behind {prefix}, keys 64 .. {prefix - 1} masked")
+    gp.close()
