@@ -17,7 +17,7 @@ namespace spd {
 // reference), and every chain is
 // ordered by unit, so that the chains of an XCD work on the same unit at about the same time.
 // With fewer units than XCDs the items themselves are dealt round-robin.
-// Without `persistent` there is one workgroup per item instead (chains of length one, handed out by the
+// Without `persistent` there is one workgroup per item (or part of one, below) instead (chains of length one, handed out by the
 // hardware in launch order: the XCDs' queues interleaved, each queue heaviest unit first): for
 // partitions on which a launch of exactly one workgroup per compute unit does not get one compute
 // unit each.
@@ -76,9 +76,14 @@ inline bool deal_parts(const std::vector<PrefillItem>& items, int n_chains, long
   return true;
 }
 
-// The chains (workgroup c xcds + x takes chain c of XCD x) and the merge list, if every chain can be that much shorter than the
-// longest load `longest` of whole items; else nothing.  xq: every XCD's items.
-inline bool share_out(std::vector<std::vector<PrefillItem>>& xq, int per_xcd, long longest, int block_m, std::vector<PrefillWork>& work,
+// The work list and the merge list, if every chain can be that much shorter than the longest load `longest` of whole items; else nothing.
+// xq: every XCD's items.  `persistent`: workgroup c xcds + x takes chain c of XCD x.  Without, the chains only say where to cut, and every
+// item and part is a workgroup of its own, each XCD's longest first: where the phases' masks overlap, the other phase's
+// workgroups then get a compute unit whenever a part ends, not with the kernel.  (The four pieces above on 256 CUs, both phases there: as
+// chains 136 us, as workgroups 137, in the order of the chains 147.  A decode step of 16 requests of 1000 tokens that comes in the
+// middle of it ends 111 us later beside chains, 105 beside workgroups, and 79 beside whole items, which leave it compute units of
+// their own; pairs of both steps, queued, 148, 146 and 159 us.)
+inline bool share_out(std::vector<std::vector<PrefillItem>>& xq, int per_xcd, bool persistent, long longest, int block_m, std::vector<PrefillWork>& work,
                       std::vector<int32_t>& chain, std::vector<PrefillMerge>& merge) {
   const long most = longest * 9 / 10 - MERGE_COST_TILES;   // a tenth ahead, or it is not worth another launch
   long cap = LEAST_PART_TILES + ITEM_COST_TILES + PART_COST_TILES;
@@ -101,21 +106,39 @@ inline bool share_out(std::vector<std::vector<PrefillItem>>& xq, int per_xcd, lo
   }
   merge.clear();
   std::vector<std::vector<PrefillPlace>> places(xcds);
-  chain.assign(xcds * (size_t)per_xcd + 1, 0);
   int32_t n_parts = 0;
+  size_t most_places = 0, n_places = 0;
   for (size_t x = 0; x < xcds; ++x) {
     (void)deal_parts(xq[x], per_xcd, cap, block_m, &places[x]);
     for (PrefillPlace& p : places[x]) {
-      ++chain[(size_t)p.chain * xcds + x + 1];
       if (p.w.part == -1) continue;
       if (p.w.kt0 == 0) merge.push_back(PrefillMerge{p.w.row0, p.w.len, p.w.q_tile, p.w.head0, n_parts, 0});
       p.w.part = n_parts++;
       ++merge.back().n_parts;
     }
+    n_places += places[x].size();
+    most_places = std::max(most_places, places[x].size());
   }
+  if (!persistent) {
+    for (auto& of_xcd : places)
+      std::stable_sort(of_xcd.begin(), of_xcd.end(), [](const PrefillPlace& a, const PrefillPlace& b) { return a.w.kt1 - a.w.kt0 > b.w.kt1 - b.w.kt0; });
+    work.clear();
+    work.reserve(n_places);
+    chain.clear();
+    for (size_t i = 0; i < most_places; ++i)
+      for (size_t x = 0; x < xcds; ++x) {
+        chain.push_back((int32_t)work.size());
+        if (i < places[x].size()) work.push_back(places[x][i].w);
+      }
+    chain.push_back((int32_t)work.size());
+    return true;
+  }
+  chain.assign(xcds * (size_t)per_xcd + 1, 0);
+  for (size_t x = 0; x < xcds; ++x)
+    for (const PrefillPlace& p : places[x]) ++chain[(size_t)p.chain * xcds + x + 1];
   for (size_t c = 0; c + 1 < chain.size(); ++c) chain[c + 1] += chain[c];
   std::vector<int32_t> at(chain.begin(), chain.end() - 1);
-  work.resize((size_t)chain.back());
+  work.resize(n_places);
   for (size_t x = 0; x < xcds; ++x)
     for (const PrefillPlace& p : places[x]) work[(size_t)at[(size_t)p.chain * xcds + x]++] = p.w;
   return true;
@@ -184,7 +207,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
     std::vector<std::vector<PrefillItem>> lists((size_t)xcds);
     for (int x = 0; x < xcds; ++x)
       for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) lists[(size_t)x].push_back(items[xq[i]]);
-    return share_out(lists, per_xcd, longest, bm, work, chain, *merge);
+    return share_out(lists, per_xcd, persistent, longest, bm, work, chain, *merge);
   };
   // (at most the heaviest item's weight is to be gained, and with many items per compute unit whole ones balance well enough)
   const bool may_share = merge && even && n_items <= 8 * (size_t)share && heaviest > 2 * LEAST_PART_TILES;

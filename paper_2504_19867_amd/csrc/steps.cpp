@@ -182,7 +182,7 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
 
   int rc;
   // One persistent workgroup per compute unit of the prefill share, each with its chain of work items, where phase_exclusive says
-  // so; elsewhere one workgroup per item, handed out by the hardware as compute units free up.
+  // so; elsewhere one workgroup per item or part of one, handed out by the hardware as compute units free up.
   // The share is the one this step will run on: a staged partition is adopted below, once nothing but a HIP
   // call can fail any more, so a step that returns an error of its own leaves the partition as it was.
   int share;

@@ -205,3 +205,42 @@ def test_items_shared_out_whose_parts_see_only_masked_keys(H, Hkv, d, bits):
     want = OA.chunk_attention(f64(q[prefix:]), f64(k), f64(v), scale)
     assert_parity(host_f64(out), want, f"{n} tokens behind {prefix}, keys 64 .. {prefix - 1} masked")
     gp.close()
+
+
+@pytest.mark.parametrize("pre,dec", [(256, 256), (192, 192)])
+def test_decode_steps_beside_items_shared_out_on_the_same_compute_units(pre, dec):
+    """Parts are workgroups of their own where the phases' masks overlap: both phases' steps, issued in turn, end and are right."""
+    H, Hkv, d, reqs, n_dec, n_ctx = 8, 2, 128, ((2805, 70), (1500, 7)), 6, 300
+    layer = W.LayerShape("gqa", H, Hkv, d, d, 16)
+    scale = 1.0 / math.sqrt(d)
+    lens = tuple(p + n for p, n in reqs)
+    q, k, v, cu = W.prefill_inputs(layer, lens, seed=23)
+    qd, ks, vs = W.decode_inputs(layer, (n_ctx,) * n_dec, 24)
+    gp = GpuPool(layer, sum(-(-n // 16) for n in lens) + n_dec * -(-n_ctx // 16) + 4, poison=True)
+    gp.ctx.set_partition(pre, dec)
+    for i, (kb, vb) in enumerate(zip(ks, vs)):
+        gp.pool.kv_reserve(50 + i, n_ctx)
+        gp.pool.kv_write(DEC, 50 + i, 0, n_ctx, dev_bf16(kb), dev_bf16(vb))
+    for r, (p, _) in enumerate(reqs):
+        gp.pool.kv_reserve(1 + r, p)
+        gp.pool.kv_write(PRE, 1 + r, 0, p, dev_bf16(k[cu[r]:cu[r] + p]), dev_bf16(v[cu[r]:cu[r] + p]))
+    gp.ctx.phase_sync(PRE)
+    gp.ctx.phase_sync(DEC)
+    rows = np.concatenate([np.arange(cu[r] + p, cu[r + 1]) for r, (p, _) in enumerate(reqs)])
+    step = [dev_bf16(x[rows]) for x in (q, k, v)]
+    cu_step = [0, reqs[0][1], reqs[0][1] + reqs[1][1]]
+    out_p = torch.empty((len(rows), H, d), dtype=torch.bfloat16, device=DEV)
+    tqd, out_d = dev_bf16(qd), torch.empty((n_dec, H, d), dtype=torch.bfloat16, device=DEV)
+    torch.cuda.synchronize()
+    for _ in range(4):
+        gp.pool.prefill_step([1, 2], cu_step, *step, out_p, H, Hkv, d, d, scale, prefix_lens=[p for p, _ in reqs])
+        gp.pool.decode_step([50 + i for i in range(n_dec)], [n_ctx] * n_dec, tqd, out_d, H, scale)
+    gp.ctx.phase_sync(PRE)
+    gp.ctx.phase_sync(DEC)
+    got = host_f64(out_p)
+    for r, (p, n) in enumerate(reqs):
+        want = OA.chunk_attention(f64(q[cu[r] + p:cu[r + 1]]), f64(k[cu[r]:cu[r + 1]]), f64(v[cu[r]:cu[r + 1]]), scale)
+        assert_parity(got[cu_step[r]:cu_step[r + 1]], want, f"request {r}")
+    want_d = np.stack([OA.decode_attention(f64(qd[i]), f64(ks[i]), f64(vs[i]), scale) for i in range(n_dec)])
+    assert_parity(host_f64(out_d), want_d, "decode")
+    gp.close()

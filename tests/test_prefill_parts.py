@@ -67,10 +67,14 @@ def _check(batch, got, plain):
         part0, n = parts_of.pop(item[:4])
         assert n == len(ranges) and [p for _, _, p in ranges] == list(range(part0, part0 + n))
     assert not parts_of                                           # nothing is merged that was not cut
+    if not persistent:                                            # no workgroup keeps a compute unit that it was not given alone
+        assert all(b - a <= 1 for a, b in zip(bounds, bounds[1:]))
     if merge:
-        assert len(bounds) - 1 == share
-        loads = [sum(w[7] - w[6] + 4 + (w[8] >= 0) for w in work[a:b]) for a, b in zip(bounds, bounds[1:])]
-        assert max(loads) <= max(t + 4 for t in whole.values()) * 2 and n_parts <= 2 * share + len(merge)
+        if persistent:
+            assert len(bounds) - 1 == share
+            loads = [sum(w[7] - w[6] + 4 + (w[8] >= 0) for w in work[a:b]) for a, b in zip(bounds, bounds[1:])]
+            assert max(loads) <= max(t + 4 for t in whole.values()) * 2
+        assert n_parts <= 2 * share + len(merge)
         numbers = sorted(w[8] for w in work if w[8] >= 0)
         assert numbers == list(range(n_parts))
     return len(merge)
