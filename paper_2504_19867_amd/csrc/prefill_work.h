@@ -36,119 +36,249 @@ struct PrefillItem {
 // item that none of them has room for is cut: each part leaves its sums in memory, and a second launch adds them up.  Whole step, 32
 // heads: 2 pieces of up to 14 tokens behind 2805 on 256 CUs 63.9 -> 38 us; 512 tokens behind 8000 on 128 CUs 193 -> 121; one token behind
 // 8000, 64 heads on 64 CUs 186 -> 61; 4 pieces of 355 .. 867 behind up to 5023 on 256 CUs (312 items of up to 89 tiles, mean load 57, now
-// at most 61; with all compute units busy the clock is lower) 159 -> 139.
+// at most 67; with all compute units busy the clock is lower) 159 -> 140.
 // A part pays its item's fixed cost again and one tile for writing its sums; the second launch costs what six tiles do.  Parts are no
 // shorter than eight tiles.  No part begins behind the item's first row, so that every row has keys in every part.
 constexpr long PART_COST_TILES = 1, MERGE_COST_TILES = 6, LEAST_PART_TILES = 8;
+// Where the parts have to end for whole items that end at `longest`: a tenth ahead, or it is not worth another launch.
+inline long shared_end(long longest) { return longest * 9 / 10 - MERGE_COST_TILES; }
 
-struct PrefillPlace { PrefillWork w; int chain; };
+struct PrefillPiece { uint32_t item; int32_t kt0, kt1; uint32_t chain; };
 
-// Deals the items of one XCD, longest first, to n_chains chains of weight `cap`: whole into the chain whose room they fill best, else in
-// parts, from the chain with most room on.  `places` (in the order of the items and of their parts, which are not numbered yet: -2) null:
-// only asks.  false: they do not fit.
-inline bool deal_parts(const std::vector<PrefillItem>& items, int n_chains, long cap, int block_m, std::vector<PrefillPlace>* places) {
-  std::vector<long> room((size_t)n_chains, cap);
-  for (const PrefillItem& item : items) {
-    const int32_t last_cut = (item.q_off + item.q_tile * block_m) / 64;   // the tile of the item's first row
-    int32_t k0 = 0;
-    while (k0 < item.tiles) {
-      const long rest = item.tiles - k0 + ITEM_COST_TILES + (k0 > 0 ? PART_COST_TILES : 0);
-      int best = -1, widest = 0;
-      for (int c = 0; c < n_chains; ++c) {
-        if (room[(size_t)c] >= rest && (best < 0 || room[(size_t)c] < room[(size_t)best])) best = c;
-        if (room[(size_t)c] > room[(size_t)widest]) widest = c;
-      }
-      int32_t k1 = item.tiles;
-      if (best >= 0) {
-        room[(size_t)best] -= rest;
-      } else {
-        best = widest;
-        long take = std::min<long>(room[(size_t)best] - ITEM_COST_TILES - PART_COST_TILES, item.tiles - k0 - LEAST_PART_TILES);
-        take = std::min<long>(take, last_cut - k0);
-        if (take < LEAST_PART_TILES) return false;
-        k1 = k0 + (int32_t)take;
-        room[(size_t)best] -= take + ITEM_COST_TILES + PART_COST_TILES;
-      }
-      if (places) places->push_back(PrefillPlace{item.part(k0, k1, k0 > 0 || k1 < item.tiles ? -2 : -1), best});
-      k0 = k1;
+// The whole items as they were dealt (`load` of every chain, XCD after XCD) and what has to move for no chain to exceed a `cap`: a chain
+// with too much cuts its longest item so that it ends at the cap, and what is left over goes where it fits best, in further parts
+// where it fits nowhere.  So the search looks at the chains with too much and at what they give away, not at every item.  Host time of
+// dealing a batch, against dealing all items anew for every cap that is tried: 4 pieces of 355 .. 867 behind up to 5023 on 256 CUs
+// 23 -> 10 us (dealt whole: 3); of random batches of 6 to 16 pieces, nearly none of which is cut, 31 -> 13 on average, 127 -> 38
+// at most.  A step that is waited for has it ahead of everything else: those 4 pieces 168 -> 159 us.
+class PrefillShares {
+ public:
+  PrefillShares(const std::vector<PrefillItem>& items, const std::vector<uint32_t>& chain_of, const std::vector<long>& load, int per_xcd, int block_m)
+      : items_(items), chain_of_(chain_of), load_(load), per_xcd_((size_t)per_xcd), block_m_(block_m) {}
+  // The pieces that take the place of some whole items, ordered by item and keys, if every chain can be that much shorter than the longest.
+  bool find(std::vector<PrefillPiece>& pieces) {
+    const long longest = *std::max_element(load_.begin(), load_.end());
+    long hi = shared_end(longest);
+    long lo = LEAST_PART_TILES + ITEM_COST_TILES + PART_COST_TILES;
+    for (size_t x = 0; x < load_.size(); x += per_xcd_) {
+      long sum = 0;
+      for (size_t c = x; c < x + per_xcd_; ++c) sum += load_[c];
+      lo = std::max(lo, (sum + (long)per_xcd_ - 1) / (long)per_xcd_);
     }
+    if (lo > hi) return false;
+    first_.assign(load_.size() + 1, 0);
+    for (uint32_t c : chain_of_) ++first_[c + 1];
+    for (size_t c = 0; c < load_.size(); ++c) first_[c + 1] += first_[c];
+    std::vector<uint32_t> at(first_.begin(), first_.end() - 1);
+    of_chain_.resize(items_.size());
+    for (size_t i = 0; i < items_.size(); ++i) {  // (each in its place by length: chains are short here)
+      const uint32_t c = chain_of_[i];
+      uint32_t to = at[c]++;
+      for (; to > first_[c] && items_[of_chain_[to - 1]].tiles < items_[i].tiles; --to) of_chain_[to] = of_chain_[to - 1];
+      of_chain_[to] = (uint32_t)i;
+    }
+    by_load_.resize(load_.size());
+    for (size_t c = 0; c < load_.size(); ++c) by_load_[c] = (uint32_t)c;
+    for (size_t x = 0; x < load_.size(); x += per_xcd_)
+      std::sort(by_load_.begin() + (long)x, by_load_.begin() + (long)(x + per_xcd_),
+                [&](uint32_t a, uint32_t b) { return load_[a] != load_[b] ? load_[a] < load_[b] : a < b; });
+    // About the least cap that they fit into: mostly near the mean with what the parts themselves cost; else halfway between what does
+    // not fit and what does.
+    long near = lo;
+    for (size_t x = 0; x < load_.size(); x += per_xcd_) {
+      long sum = 0;
+      for (size_t c = x; c < x + per_xcd_; ++c) {
+        const long over = load_[c] - lo, part = lo - ITEM_COST_TILES - PART_COST_TILES;
+        sum += load_[c] + (over > 0 ? PART_COST_TILES + (over + part - 1) / part * (ITEM_COST_TILES + PART_COST_TILES) : 0);
+      }
+      near = std::max(near, sum / (long)per_xcd_);
+    }
+    near += near / 32 + 1;
+    if (near > hi || !fits(near, pieces)) {
+      if (!fits(hi, pieces)) return false;
+      std::vector<PrefillPiece> fewer;
+      for (lo = std::min(near, hi); hi - lo > hi / 16;) {
+        const long mid = (lo + hi) / 2;
+        if (fits(mid, fewer)) {
+          hi = mid;
+          pieces.swap(fewer);
+        } else {
+          lo = mid;
+        }
+        if (hi - lo == 1) break;
+      }
+    }
+    std::sort(pieces.begin(), pieces.end(), [](const PrefillPiece& a, const PrefillPiece& b) { return a.item != b.item ? a.item < b.item : a.kt0 < b.kt0; });
+    return true;
   }
-  return true;
-}
+  long looked_at() const { return looked_at_; }   // items, parts and chains, over the whole search
 
-// The work list and the merge list, if every chain can be that much shorter than the longest load `longest` of whole items; else nothing.
-// xq: every XCD's items.  `persistent`: workgroup c xcds + x takes chain c of XCD x.  Without, the chains only say where to cut, and every
+ private:
+  const std::vector<PrefillItem>& items_;
+  const std::vector<uint32_t>& chain_of_;
+  const std::vector<long>& load_;
+  const size_t per_xcd_;
+  const int block_m_;
+  std::vector<uint32_t> first_, of_chain_;        // every chain's items, the longest first
+  std::vector<uint32_t> by_load_;                 // every XCD's chains, the least loaded first
+  struct Room { long room; uint32_t chain; };
+  std::vector<Room> rooms_;                       // of one XCD, the widest first
+  struct Rest { int32_t tiles; uint32_t item; };  // the last `tiles` of an item, which its chain gives away
+  std::vector<Rest> rest_;
+  size_t doubtful_ = 0;                           // the XCD that did not fit the last time is asked first
+  long looked_at_ = 0;
+
+  bool fits(long cap, std::vector<PrefillPiece>& pieces) {
+    pieces.clear();
+    const size_t xcds = load_.size() / per_xcd_, start = doubtful_;
+    for (size_t i = 0; i < xcds; ++i) {
+      const size_t x = (start + i) % xcds;
+      if (!fits_xcd(x * per_xcd_, cap, pieces)) {
+        doubtful_ = x;
+        return false;
+      }
+    }
+    return true;
+  }
+  int32_t last_cut(uint32_t i) const { return (items_[i].q_off + items_[i].q_tile * block_m_) / 64; }   // the tile of the item's first row
+  bool fits_xcd(size_t c0, long cap, std::vector<PrefillPiece>& pieces) {
+    rooms_.clear();
+    rest_.clear();
+    ++looked_at_;
+    if (load_[by_load_[c0 + per_xcd_ - 1]] <= cap) return true;
+    looked_at_ += (long)per_xcd_;
+    size_t n_within = per_xcd_;
+    while (n_within > 0 && load_[by_load_[c0 + n_within - 1]] > cap) --n_within;
+    for (size_t i = 0; i < n_within; ++i) rooms_.push_back(Room{cap - load_[by_load_[c0 + i]], by_load_[c0 + i]});
+    for (size_t i = per_xcd_; i > n_within; --i) {  // the most loaded first: what they give away is about in order then
+      const uint32_t c = by_load_[c0 + i - 1];
+      long room = cap - load_[c];
+      for (uint32_t n = first_[c]; room < 0; ++n) {
+        const uint32_t item = of_chain_[n];
+        ++looked_at_;
+        room += items_[item].weight();
+        int32_t keep = (int32_t)std::min<long>(room - ITEM_COST_TILES - PART_COST_TILES, items_[item].tiles - LEAST_PART_TILES);
+        keep = std::min(keep, last_cut(item));
+        if (keep < LEAST_PART_TILES) keep = 0;    // all of it goes
+        if (keep) {
+          pieces.push_back(PrefillPiece{item, 0, keep, c});
+          room -= keep + ITEM_COST_TILES + PART_COST_TILES;
+        }
+        const Rest r{items_[item].tiles - keep, item};
+        rest_.push_back(r);
+        size_t to = rest_.size() - 1;
+        for (; to > 0 && rest_[to - 1].tiles < r.tiles; --to) rest_[to] = rest_[to - 1];
+        rest_[to] = r;
+      }
+      const Room r{room, c};
+      rooms_.push_back(r);
+      size_t to = rooms_.size() - 1;
+      for (; to > 0 && rooms_[to - 1].room < room; --to) rooms_[to] = rooms_[to - 1];
+      rooms_[to] = r;
+    }
+    for (const Rest& r : rest_) {
+      const int32_t tiles = items_[r.item].tiles;
+      for (int32_t kt0 = tiles - r.tiles; kt0 < tiles;) {
+        ++looked_at_;
+        long need = tiles - kt0 + ITEM_COST_TILES + (kt0 > 0 ? PART_COST_TILES : 0);
+        int32_t kt1 = tiles;
+        // the narrowest that takes all of it, else a part into the widest
+        auto at = std::partition_point(rooms_.begin(), rooms_.end(), [&](const Room& a) { return a.room >= need; });
+        if (at != rooms_.begin()) {
+          --at;
+        } else {
+          const long rest = tiles - kt0, most = std::max<long>(1, at->room - ITEM_COST_TILES - PART_COST_TILES), n = (rest + most - 1) / most;
+          const long even = (rest + n - 1) / n;   // n parts of a length, where there are n chains for them
+          long take = std::min(most, rest - LEAST_PART_TILES);
+          if ((size_t)n <= rooms_.size() && rooms_[(size_t)n - 1].room >= even + ITEM_COST_TILES + PART_COST_TILES) take = even;
+          take = std::min({take, rest - LEAST_PART_TILES, (long)last_cut(r.item) - kt0});
+          if (take < LEAST_PART_TILES) return false;
+          kt1 = kt0 + (int32_t)take;
+          need = take + ITEM_COST_TILES + PART_COST_TILES;
+        }
+        pieces.push_back(PrefillPiece{r.item, kt0, kt1, at->chain});
+        kt0 = kt1;
+        const Room left{at->room - need, at->chain};
+        for (; at + 1 != rooms_.end() && at[1].room > left.room; ++at) *at = at[1];
+        *at = left;
+      }
+    }
+    return true;
+  }
+};
+
+// The work list and the merge list of items some of which are shared out.  `persistent`: workgroup c xcds + x takes chain c of XCD x, each in
+// the order of its items.  Without, the chains only say where to cut, and every
 // item and part is a workgroup of its own, each XCD's longest first: where the phases' masks overlap, the other phase's
 // workgroups then get a compute unit whenever a part ends, not with the kernel.  (The four pieces above on 256 CUs, both phases there: as
 // chains 136 us, as workgroups 137, in the order of the chains 147.  A decode step of 16 requests of 1000 tokens that comes in the
 // middle of it ends 111 us later beside chains, 105 beside workgroups, and 79 beside whole items, which leave it compute units of
 // their own; pairs of both steps, queued, 148, 146 and 159 us.)
-inline bool share_out(std::vector<std::vector<PrefillItem>>& xq, int per_xcd, bool persistent, long longest, int block_m, std::vector<PrefillWork>& work,
-                      std::vector<int32_t>& chain, std::vector<PrefillMerge>& merge) {
-  const long most = longest * 9 / 10 - MERGE_COST_TILES;   // a tenth ahead, or it is not worth another launch
-  long cap = LEAST_PART_TILES + ITEM_COST_TILES + PART_COST_TILES;
-  for (const auto& items : xq) {
-    long sum = 0;
-    for (const PrefillItem& item : items) sum += item.weight();
-    cap = std::max(cap, (sum + per_xcd - 1) / per_xcd);
-  }
-  if (cap > most) return false;
-  const size_t xcds = xq.size();
-  for (auto& items : xq) std::stable_sort(items.begin(), items.end(), [](const PrefillItem& a, const PrefillItem& b) { return a.tiles > b.tiles; });
-  for (size_t x = 0; x < xcds;) {                 // the least that the items of all XCDs fit into
-    if (deal_parts(xq[x], per_xcd, cap, block_m, nullptr)) {
-      ++x;
-    } else {
-      cap += 1 + cap / 24;
-      if (cap > most) return false;
-      x = 0;                                      // (what fitted into less need not fit into more)
-    }
-  }
+inline void write_shares(const std::vector<PrefillItem>& items, const std::vector<uint32_t>& chain_of, const std::vector<PrefillPiece>& pieces, size_t xcds,
+                         size_t per_xcd, bool persistent, std::vector<PrefillWork>& work, std::vector<int32_t>& chain, std::vector<PrefillMerge>& merge) {
   merge.clear();
-  std::vector<std::vector<PrefillPlace>> places(xcds);
+  // what goes where, in the order of the items: a piece (its number), or the whole item
+  struct Entry { uint32_t item, chain; int32_t tiles, piece; };
+  std::vector<Entry> all;
+  all.reserve(items.size() + pieces.size());
+  std::vector<int32_t> part(pieces.size(), -1);   // numbers of the pieces that are not whole
   int32_t n_parts = 0;
-  size_t most_places = 0, n_places = 0;
-  for (size_t x = 0; x < xcds; ++x) {
-    (void)deal_parts(xq[x], per_xcd, cap, block_m, &places[x]);
-    for (PrefillPlace& p : places[x]) {
-      if (p.w.part == -1) continue;
-      if (p.w.kt0 == 0) merge.push_back(PrefillMerge{p.w.row0, p.w.len, p.w.q_tile, p.w.head0, n_parts, 0});
-      p.w.part = n_parts++;
+  for (size_t i = 0, p = 0; i < items.size(); ++i) {
+    if (p == pieces.size() || pieces[p].item != i) {
+      all.push_back(Entry{(uint32_t)i, chain_of[i], items[i].tiles, -1});
+      continue;
+    }
+    const bool cut = pieces[p].kt1 < items[i].tiles;
+    if (cut) merge.push_back(PrefillMerge{items[i].row0, items[i].len, items[i].q_tile, items[i].head0, n_parts, 0});
+    for (; p < pieces.size() && pieces[p].item == i; ++p) {
+      all.push_back(Entry{(uint32_t)i, pieces[p].chain, pieces[p].kt1 - pieces[p].kt0, (int32_t)p});
+      if (!cut) continue;
+      part[p] = n_parts++;
       ++merge.back().n_parts;
     }
-    n_places += places[x].size();
-    most_places = std::max(most_places, places[x].size());
   }
-  if (!persistent) {
-    for (auto& of_xcd : places)
-      std::stable_sort(of_xcd.begin(), of_xcd.end(), [](const PrefillPlace& a, const PrefillPlace& b) { return a.w.kt1 - a.w.kt0 > b.w.kt1 - b.w.kt0; });
-    work.clear();
-    work.reserve(n_places);
-    chain.clear();
-    for (size_t i = 0; i < most_places; ++i)
-      for (size_t x = 0; x < xcds; ++x) {
-        chain.push_back((int32_t)work.size());
-        if (i < places[x].size()) work.push_back(places[x][i].w);
-      }
-    chain.push_back((int32_t)work.size());
-    return true;
+  auto work_of = [&](const Entry& e) -> PrefillWork {
+    return e.piece < 0 ? items[e.item].whole() : items[e.item].part(pieces[(size_t)e.piece].kt0, pieces[(size_t)e.piece].kt1, part[(size_t)e.piece]);
+  };
+  const size_t n = all.size();
+  work.resize(n);
+  if (persistent) {
+    auto slot = [&](uint32_t c) -> size_t { return c % (uint32_t)per_xcd * (uint32_t)xcds + c / (uint32_t)per_xcd; };
+    chain.assign(xcds * per_xcd + 1, 0);
+    for (const Entry& e : all) ++chain[slot(e.chain) + 1];
+    for (size_t c = 0; c + 1 < chain.size(); ++c) chain[c + 1] += chain[c];
+    std::vector<int32_t> at(chain.begin(), chain.end() - 1);
+    for (const Entry& e : all) work[(size_t)at[slot(e.chain)]++] = work_of(e);
+    return;
   }
-  chain.assign(xcds * (size_t)per_xcd + 1, 0);
-  for (size_t x = 0; x < xcds; ++x)
-    for (const PrefillPlace& p : places[x]) ++chain[(size_t)p.chain * xcds + x + 1];
-  for (size_t c = 0; c + 1 < chain.size(); ++c) chain[c + 1] += chain[c];
-  std::vector<int32_t> at(chain.begin(), chain.end() - 1);
-  work.resize(n_places);
-  for (size_t x = 0; x < xcds; ++x)
-    for (const PrefillPlace& p : places[x]) work[(size_t)at[(size_t)p.chain * xcds + x]++] = p.w;
-  return true;
+  std::vector<uint64_t> order(n);                 // XCD, longest first (an item has fewer than 2^26 tiles of 64 keys), place
+  std::vector<size_t> first(xcds + 1, 0);
+  for (size_t i = 0; i < n; ++i) {
+    const uint64_t x = all[i].chain / (uint32_t)per_xcd;
+    order[i] = x << 58 | (uint64_t)((1 << 26) - all[i].tiles) << 32 | i;
+    ++first[x + 1];
+  }
+  std::sort(order.begin(), order.end());
+  size_t most = 0, at = 0;
+  for (size_t x = 0; x < xcds; ++x) {
+    most = std::max(most, first[x + 1]);
+    first[x + 1] += first[x];
+  }
+  chain.clear();
+  chain.reserve(most * xcds + 1);
+  for (size_t i = 0; i < most; ++i)
+    for (size_t x = 0; x < xcds; ++x) {           // workgroup i * xcds + x runs on XCD x
+      chain.push_back((int32_t)at);
+      if (first[x] + i < first[x + 1]) work[at++] = work_of(all[(uint32_t)order[first[x] + i]]);
+    }
+  chain.push_back((int32_t)at);
 }
 
 // `persistent`: a chain per compute unit; `merge` null: no item is shared out.
 // (Lists in a few flat arrays: with a vector per unit, per XCD and per chain this took 13 of the 20 us of a step of 8 short prompts.)
 inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefix_lens, const int32_t* kv_cu, int n_req,
                                  int H, int Hkv, int xcds, int share, bool persistent, std::vector<PrefillWork>& work,
-                                 std::vector<int32_t>& chain, std::vector<PrefillMerge>* merge) {
+                                 std::vector<int32_t>& chain, std::vector<PrefillMerge>* merge, long* looked_at = nullptr) {
   const int G = H / Hkv, hb = prefill_heads_per_block(G), bm = prefill_block_m(G), groups = G / hb;
   // items, unit after unit, each unit's longest first
   const size_t n_units = (size_t)n_req * (size_t)Hkv;
@@ -203,25 +333,59 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
     for (int x = 0; x < xcds; ++x) xq_first[(size_t)x + 1] = xq_first[(size_t)x] + (uint32_t)((n_items + (size_t)(xcds - 1 - x)) / (size_t)xcds);
     for (size_t i = 0; i < n_items; ++i) xq[xq_first[i % (size_t)xcds] + i / (size_t)xcds] = (uint32_t)i;
   }
-  auto share_items = [&](long longest) -> bool {
-    std::vector<std::vector<PrefillItem>> lists((size_t)xcds);
-    for (int x = 0; x < xcds; ++x)
-      for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) lists[(size_t)x].push_back(items[xq[i]]);
-    return share_out(lists, per_xcd, persistent, longest, bm, work, chain, *merge);
-  };
-  // (at most the heaviest item's weight is to be gained, and with many items per compute unit whole ones balance well enough)
-  const bool may_share = merge && even && n_items <= 8 * (size_t)share && heaviest > 2 * LEAST_PART_TILES;
-  std::vector<long> load((size_t)per_xcd);
-  long longest = 0;                               // load of the chain, or of the compute unit, that is done last
-  if (!persistent) {
-    if (may_share) {
-      for (int x = 0; x < xcds; ++x) {
-        std::fill(load.begin(), load.end(), 0);
-        for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) *std::min_element(load.begin(), load.end()) += items[xq[i]].weight();
-        longest = std::max(longest, *std::max_element(load.begin(), load.end()));
+  // At most the heaviest item's weight is to be gained, and with many items per compute unit whole ones balance well enough: of random
+  // batches with more than three per compute unit one in twelve can be a sixth shorter, and all of them would pay for the search.
+  bool may_share = merge && even && n_items <= 3 * (size_t)share && heaviest > 2 * LEAST_PART_TILES;
+  if (may_share && !persistent) {
+    // Before the items are dealt only for the search: one begins no later than when those ahead of it fill all compute units, and those
+    // that have to be cut cost more.  (Near the border the search finds nothing, mostly: one prompt of 2500 tokens on 256 CUs.)
+    long end = 0;
+    for (int x = 0; x < xcds; ++x) {
+      long ahead = 0;
+      for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) {
+        const long w = items[xq[i]].weight();
+        end = std::max(end, (i - xq_first[(size_t)x] < (uint32_t)per_xcd ? 0 : ahead / per_xcd) + w);
+        ahead += w;
       }
-      if (share_items(longest)) return;
     }
+    const long cap = shared_end(end);
+    for (int x = 0; x < xcds; ++x) {
+      long sum = 0;
+      for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) {
+        const long w = items[xq[i]].weight();
+        sum += w + (w > cap ? ITEM_COST_TILES + 2 * PART_COST_TILES : 0);
+      }
+      may_share = may_share && sum * 16 <= cap * per_xcd * 15;
+    }
+  }
+  std::vector<uint32_t> chain_of(n_items);        // chain c of XCD x: x * per_xcd + c
+  std::vector<long> load((size_t)xcds * (size_t)per_xcd, 0);
+  // Unit after unit (in the order the XCD took them), each unit's items longest-first onto the chain
+  // with the least load so far: every chain then holds about the same weight of EVERY unit, so the
+  // chains of an XCD pass from one unit to the next at about the same time and the XCD's L2 has to
+  // hold one or two units' K, V, not all of them.  (Dealt over all units at once the chains were as
+  // well balanced in total, but drifted apart unit by unit, and K, V crossed HBM four times.)
+  // Workgroups of one item each land on the compute units in the same way.
+  if (persistent || may_share)
+    for (int x = 0; x < xcds; ++x) {
+      const auto of_xcd = load.begin() + (long)x * per_xcd;
+      for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) {
+        const auto least = std::min_element(of_xcd, of_xcd + per_xcd);
+        *least += items[xq[i]].weight();
+        chain_of[xq[i]] = (uint32_t)(least - load.begin());
+      }
+    }
+  if (may_share) {
+    PrefillShares shares(items, chain_of, load, per_xcd, bm);
+    std::vector<PrefillPiece> pieces;
+    const bool found = shares.find(pieces);
+    if (looked_at) *looked_at = shares.looked_at();
+    if (found) {
+      write_shares(items, chain_of, pieces, (size_t)xcds, (size_t)per_xcd, persistent, work, chain, *merge);
+      return;
+    }
+  }
+  if (!persistent) {
     uint32_t most = 0;
     for (int x = 0; x < xcds; ++x) most = std::max(most, xq_first[(size_t)x + 1] - xq_first[(size_t)x]);
     work.clear();
@@ -236,29 +400,14 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
     chain.push_back((int32_t)work.size());
     return;
   }
-  // Unit after unit (in the order the XCD took them), each unit's items longest-first onto the chain
-  // with the least load so far: every chain then holds about the same weight of EVERY unit, so the
-  // chains of an XCD pass from one unit to the next at about the same time and the XCD's L2 has to
-  // hold one or two units' K, V, not all of them.  (Dealt over all units at once the chains were as
-  // well balanced in total, but drifted apart unit by unit, and K, V crossed HBM four times.)
-  std::vector<uint32_t> chain_of(n_items);
-  chain.assign((size_t)share + 1, 0);
-  for (int x = 0; x < xcds; ++x) {
-    std::fill(load.begin(), load.end(), 0);
-    for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) {
-      const size_t c = (size_t)(std::min_element(load.begin(), load.end()) - load.begin());
-      load[c] += items[xq[i]].weight();
-      chain_of[xq[i]] = (uint32_t)(c * (size_t)xcds) + (uint32_t)x;   // workgroup id = chain slot * xcds + xcd
-      ++chain[c * (size_t)xcds + (size_t)x + 1];
-    }
-    longest = std::max(longest, *std::max_element(load.begin(), load.end()));
-  }
-  if (may_share && share_items(longest)) return;
   // every chain in the order of the units
+  auto slot = [&](uint32_t c) -> size_t { return (size_t)(c % (uint32_t)per_xcd) * (size_t)xcds + c / (uint32_t)per_xcd; };   // workgroup id = chain slot * xcds + xcd
+  chain.assign((size_t)share + 1, 0);
+  for (uint32_t c : chain_of) ++chain[slot(c) + 1];
   for (int c = 0; c < share; ++c) chain[(size_t)c + 1] += chain[(size_t)c];
   std::vector<int32_t> at(chain.begin(), chain.end() - 1);
   work.resize(n_items);
-  for (size_t i = 0; i < n_items; ++i) work[(size_t)at[chain_of[i]]++] = items[i].whole();
+  for (size_t i = 0; i < n_items; ++i) work[(size_t)at[slot(chain_of[i])]++] = items[i].whole();
 }
 
 // Tiles of 64 keys that the longest item visits.

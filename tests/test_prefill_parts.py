@@ -29,12 +29,23 @@ def _deal(tmp_path, batches):
     out = iter(subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=300).stdout.split("\n"))
     answers = []
     for _ in range(2 * len(batches)):
-        n_chains, n_work, n_merge = map(int, next(out).split())
+        n_chains, n_work, n_merge, looked_at = map(int, next(out).split())
         bounds = list(map(int, next(out).split()))
         assert len(bounds) == n_chains + 1 and bounds[0] == 0 and bounds[-1] == n_work and bounds == sorted(bounds)
         work = [tuple(map(int, next(out).split())) for _ in range(n_work)]
-        answers.append((bounds, work, [tuple(map(int, next(out).split())) for _ in range(n_merge)]))
+        answers.append((bounds, work, [tuple(map(int, next(out).split())) for _ in range(n_merge)], looked_at))
     return answers[:len(batches)], answers[len(batches):]
+
+
+def _end(share, bounds, work):
+    """When the last compute unit is done, in tiles: an XCD's workgroups go to its compute units as these come free."""
+    per_xcd, end = share // 8, 0
+    for x in range(8):
+        load = [0] * per_xcd
+        for c in range(x, len(bounds) - 1, 8):
+            load[load.index(min(load))] += sum(w[7] - w[6] + 4 + (w[8] >= 0) for w in work[bounds[c]:bounds[c + 1]])
+        end = max(end, *load)
+    return end
 
 
 def _check(batch, got, plain):
@@ -42,7 +53,7 @@ def _check(batch, got, plain):
     G = H // Hkv
     hb = next(h for h in (8, 4, 2, 1) if G % h == 0)
     bm = 32 * (8 // hb)
-    bounds, work, merge = got
+    bounds, work, merge, looked_at = got
     whole = {(w[:6]): w[7] for w in plain[1]}                     # item -> its tiles
     assert len(whole) == len(plain[1]) and all(w[6] == 0 and w[8] == -1 for w in plain[1]) and not plain[2]
     seen = {}
@@ -67,13 +78,16 @@ def _check(batch, got, plain):
         part0, n = parts_of.pop(item[:4])
         assert n == len(ranges) and [p for _, _, p in ranges] == list(range(part0, part0 + n))
     assert not parts_of                                           # nothing is merged that was not cut
+    # the host's search: a handful of tries, each over a part of the items and the chains (a step that nothing overtakes waits for it)
+    assert looked_at <= 8 * (len(whole) + share)
     if not persistent:                                            # no workgroup keeps a compute unit that it was not given alone
         assert all(b - a <= 1 for a, b in zip(bounds, bounds[1:]))
     if merge:
-        if persistent:
-            assert len(bounds) - 1 == share
-            loads = [sum(w[7] - w[6] + 4 + (w[8] >= 0) for w in work[a:b]) for a, b in zip(bounds, bounds[1:])]
-            assert max(loads) <= max(t + 4 for t in whole.values()) * 2
+        assert not persistent or len(bounds) - 1 == share
+        # predicted end of the step: a tenth and the second launch ahead of the whole items, as the search has it for its chains (dealt
+        # longest first the parts may end a little later than the chains that they were cut for)
+        most = _end(share, bounds, work), _end(share, plain[0], plain[1])
+        assert most[0] <= most[1] * 9 // 10 - 6 if persistent else most[0] + 6 < most[1], most
         assert n_parts <= 2 * share + len(merge)
         numbers = sorted(w[8] for w in work if w[8] >= 0)
         assert numbers == list(range(n_parts))
@@ -89,7 +103,7 @@ def test_items_are_shared_out_where_a_few_long_ones_would_hold_up_the_step(tmp_p
 def test_random_batches(tmp_path):
     rng = random.Random(3)
     batches = []
-    for _ in range(150):
+    for _ in range(400):
         H, Hkv = rng.choice(((32, 8), (64, 8), (8, 8), (5, 1), (6, 2), (16, 2)))
         top, deep = 2 ** rng.randint(0, 11), 2 ** rng.randint(0, 14)
         reqs = tuple((rng.randint(1, top), rng.choice((0, rng.randint(0, deep)))) for _ in range(rng.randint(1, 12)))
