@@ -320,6 +320,7 @@ int stage_acquire(spd_ctx* ctx, int phase, size_t bytes, spd_stage** out, bool m
     if (!may_alloc) return SPD_ETOOBIG;
     size_t cap = std::max<size_t>(256 * 1024, st.cap);
     while (cap < bytes) cap *= 2;
+    SPD_HIP(hipSetDevice(ctx->device));                  // (the calling thread's last call may have been for another GPU)
     int rc = stage_alloc(&st, cap);
     if (rc != SPD_OK) return rc;
   }
@@ -402,6 +403,7 @@ static int buffer_reserve(spd_ctx* ctx, int phase, size_t bytes, char*& buf, siz
     size_t cap = std::max<size_t>(16u << 20, buf_cap);
     while (cap < bytes) cap *= 2;
     char* d = nullptr;
+    SPD_HIP(hipSetDevice(ctx->device));                  // (the calling thread's last call may have been for another GPU)
     SPD_HIP(hipMalloc((void**)&d, cap));
     // Earlier steps of this phase may still read the old buffer: it is kept until the last of them (the step
     // issued most recently; the one being built takes the new buffer) is known to have finished.  No wait here.

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <deque>
 #include <functional>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -28,8 +29,11 @@ struct Event {
 };
 static std::vector<Stream*> streams;
 static long n_pinned = 0, pinned_bytes = 0, n_device = 0;   // allocations so far
+static int device = 0;                          // the calling thread's current one
+static std::set<int> allocated_on;
 static int fail_launch = -1;                    // the launch of this number fails
 static int n_launches = 0;
+static std::vector<PrefillLists> seen_lists;     // what every attention launch of a prefill step was given
 static std::vector<bool> seen_counters;         // may the decode launch merge its own chunks?
 static std::vector<double> seen_w;              // sum of the RoPE frequencies that each decode launch found when it ran
 
@@ -52,14 +56,15 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   p->multiProcessorCount = 256;
   return hipSuccess;
 }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipSetDevice(int d) { device = d; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
-hipError_t hipMalloc(void** p, size_t n) { ++n_device; *p = calloc(1, n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipMalloc(void** p, size_t n) { ++n_device; allocated_on.insert(device); *p = calloc(1, n); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
   ++n_pinned;
+  allocated_on.insert(device);
   pinned_bytes += (long)n;
   *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
   return *p ? hipSuccess : hipErrorOutOfMemory;
@@ -140,8 +145,10 @@ hipError_t launch_decode_gqa(const PoolGeom&, char*, const DecodeLaunch& d, hipS
 }
 hipError_t launch_decode_prepare(const PoolGeom&, char*, const DecodeLaunch& d, int, void*, hipStream_t s) { return launch(s, d.mark); }
 hipError_t launch_decode_mla(const PoolGeom& g, char* b, const DecodeLaunch& d, hipStream_t s) { return launch_decode_gqa(g, b, d, s); }
-hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillLists&, int, int, int, int, int, float,
-                          hipStream_t s) { return launch(s, StepMark{}); }
+hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillLists& d, int, int, int, int, int, float, hipStream_t s) {
+  seen_lists.push_back(d);
+  return launch(s, StepMark{});
+}
 hipError_t launch_rope(void*, int, void*, int, int, int, int, bool, int, const int32_t*, const double*, const StepMark& m, hipStream_t s) { return launch(s, m); }
 hipError_t launch_probe(int32_t*, int, hipStream_t) { return hipErrorUnknown; }
 hipError_t launch_copy(void*, const void*, uint64_t, int, hipStream_t) { return hipErrorUnknown; }
@@ -179,6 +186,23 @@ static int decode(uint64_t req, const spd_rope_config* r = nullptr, bool noalloc
   const int32_t len = 40;
   const spd_decode_batch b = {1, &req, &len, tensor, nullptr, nullptr, tensor, 8, 0.1f, r};
   return noalloc ? spd_decode_step_noalloc(ctx, pool, &b) : spd_decode_step(ctx, pool, &b);
+}
+
+// A pool of its own with a request that has `n_tokens` cached tokens, and the prefill step of the next five of them: two items, whose
+// keys are shared out.
+static spd_pool* long_pool(uint64_t req, int32_t n_tokens) {
+  spd_pool* p;
+  uint64_t bytes;
+  const spd_pool_desc desc = {SPD_KV_GQA, 16, 2, 128, 128, (n_tokens + 5) / 16 + 1};
+  CHECK(spd_pool_bytes(&desc, &bytes) == SPD_OK);
+  CHECK(spd_pool_create(ctx, aligned_alloc(4096, bytes), bytes, &desc, &p) == SPD_OK);
+  CHECK(spd_kv_reserve(p, req, n_tokens, nullptr) == SPD_OK);
+  return p;
+}
+static int prefill(spd_pool* p, uint64_t req, int32_t n_cached) {
+  const int32_t cu[] = {0, 5};
+  const spd_prefill_batch b = {1, &req, cu, tensor, tensor, tensor, nullptr, tensor, 8, 2, 128, 128, 0.1f, &n_cached, nullptr};
+  return spd_prefill_step(ctx, p, &b);
 }
 
 static double sum_w(const spd_rope_config& c) {
@@ -321,6 +345,19 @@ static void launches() {
   }
 }
 
+// Whatever GPU the calling thread's last call was for, a step's buffers lie on the context's own.
+static void devices() {
+  spd_pool* p = long_pool(9, 3000);
+  allocated_on.clear();
+  const long pinned = n_pinned, before = n_device;
+  CHECK(hipSetDevice(1) == hipSuccess);
+  CHECK(prefill(p, 9, 3000) == SPD_OK && seen_lists.back().n_merge == 2 && seen_lists.back().parts);
+  CHECK(n_pinned > pinned && n_device == before + 2);      // the staging slot; the workspace and the parts' sums
+  CHECK(hipSetDevice(1) == hipSuccess);
+  CHECK(spd_kv_write(ctx, p, SPD_PHASE_DECODE, 9, 0, 3000, tensor, tensor) == SPD_OK);
+  CHECK(allocated_on == std::set<int>{0});
+}
+
 int main(int argc, char** argv) {
   CHECK(argc == 2);
   const std::string name = argv[1];
@@ -331,6 +368,7 @@ int main(int argc, char** argv) {
   else if (name == "in_flight") in_flight();
   else if (name == "merges") merges();
   else if (name == "launches") launches();
+  else if (name == "devices") devices();
   else CHECK(!"a scenario of that name");
   puts("ok");
 }
