@@ -427,12 +427,14 @@ int workspace_reserve(spd_ctx* ctx, int phase, size_t bytes, char** out) {
 
 float* parts_reserve(spd_ctx* ctx, size_t bytes) {
   spd_phase_state& s = ctx->phase[SPD_PHASE_PREFILL];
-  hipStream_t stream;
+  // (a staged partition's stream waits for the current one when the step adopts it, and with that joins its capture)
+  hipStream_t stream, staged;
   {
     std::lock_guard<std::mutex> lk(ctx->part_mu);
-    stream = s.has_pending ? s.pending_stream : s.stream;
+    stream = s.stream;
+    staged = s.has_pending ? s.pending_stream : s.stream;
   }
-  if (stream_capturing(ctx, stream)) return nullptr;
+  if (stream_capturing(ctx, stream) || (staged != stream && stream_capturing(ctx, staged))) return nullptr;
   const int error = g_last_hip_error;
   if (buffer_reserve(ctx, SPD_PHASE_PREFILL, bytes, s.parts, s.parts_cap) != SPD_OK) {
     (void)hipGetLastError();

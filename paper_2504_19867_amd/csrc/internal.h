@@ -301,7 +301,7 @@ int phase_seal(spd_ctx* ctx, int phase, hipStream_t stream);
 bool phase_step_done(spd_ctx* ctx, int phase, uint64_t seq);
 int workspace_reserve(spd_ctx* ctx, int phase, size_t bytes, char** out);
 // Memory for the parts of a prefill step's items, of its own, so that the workspace grows as ever; null: there is none, or the
-// phase's stream is being captured (the captured launches would outlive the buffer).
+// phase's stream, or the staged one, is being captured (the captured launches would outlive the buffer).
 float* parts_reserve(spd_ctx* ctx, size_t bytes);
 int kernel_timing_mark(spd_ctx* ctx, int phase, int which, hipStream_t stream);   // which: 0 begin, 1 end
 // rope.cpp: SPD_OK if the configuration is well-formed; the frequency table (rotary_dim / 2 doubles)

@@ -25,7 +25,8 @@ struct Stream {
   std::vector<std::function<void()>>* graph = nullptr;   // being captured
 };
 struct Event {
-  bool recorded = false, done = false, captured = false;
+  bool recorded = false, done = false;
+  std::vector<std::function<void()>>* graph = nullptr;   // recorded into a graph: who waits for it joins the capture
 };
 static std::vector<Stream*> streams;
 static long n_pinned = 0, pinned_bytes = 0, n_device = 0;   // allocations so far
@@ -98,18 +99,21 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   Event* ev = (Event*)e;
   ev->recorded = true;
   ev->done = false;
-  ev->captured = ((Stream*)s)->graph != nullptr;
+  ev->graph = ((Stream*)s)->graph;
   put(s, [ev] { ev->done = true; });
   return hipSuccess;
 }
 hipError_t hipEventQuery(hipEvent_t e) {
   Event* ev = (Event*)e;
-  if (ev->captured) return hipErrorCapturedEvent;
+  if (ev->graph) return hipErrorCapturedEvent;
   return !ev->recorded || ev->done ? hipSuccess : hipErrorNotReady;
 }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+  if (((Event*)e)->graph) ((Stream*)s)->graph = ((Event*)e)->graph;
+  return hipSuccess;
+}
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipErrorUnknown; }
 }
 
@@ -345,6 +349,26 @@ static void launches() {
   }
 }
 
+// Under graph capture a prefill step takes whole items: the launches would outlive the buffer of the parts' sums.  Also where the step adopts
+// a staged partition, whose stream joins the capture only then.
+static void captured_prefill() {
+  spd_pool* p = long_pool(9, 3000);
+  CHECK(prefill(p, 9, 3000) == SPD_OK && seen_lists.back().n_merge == 2 && seen_lists.back().parts);
+  void* handle;
+  CHECK(spd_phase_stream(ctx, SPD_PHASE_PREFILL, &handle) == SPD_OK);
+  run((Stream*)handle);
+  std::vector<std::function<void()>> graph;
+  auto whole = [] { return seen_lists.back().n_merge == 0 && !seen_lists.back().parts; };
+  ((Stream*)handle)->graph = &graph;
+  CHECK(prefill(p, 9, 3000) == SPD_OK && whole());
+  CHECK(spd_set_partition(ctx, 128, 128) == SPD_OK);
+  CHECK(prefill(p, 9, 3000) == SPD_OK && whole());
+  Stream* staged = (Stream*)ctx->phase[SPD_PHASE_PREFILL].stream;
+  CHECK(staged != handle && staged->graph == &graph);
+  staged->graph = ((Stream*)handle)->graph = nullptr;
+  CHECK(prefill(p, 9, 3000) == SPD_OK && seen_lists.back().n_merge == 2 && seen_lists.back().parts);
+}
+
 // Whatever GPU the calling thread's last call was for, a step's buffers lie on the context's own.
 static void devices() {
   spd_pool* p = long_pool(9, 3000);
@@ -368,6 +392,7 @@ int main(int argc, char** argv) {
   else if (name == "in_flight") in_flight();
   else if (name == "merges") merges();
   else if (name == "launches") launches();
+  else if (name == "captured_prefill") captured_prefill();
   else if (name == "devices") devices();
   else CHECK(!"a scenario of that name");
   puts("ok");
