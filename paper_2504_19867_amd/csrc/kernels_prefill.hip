@@ -586,14 +586,13 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(bf16_t* __restrict__
 //
 // The reference of the softmax lies 8 (in powers of two) above the largest score seen, so that p stays below 2 until a score exceeds
 // that one by 9; the top exponent bit of any p tells (no sum, no maximum is formed to find out).
-template <int HB>
 __global__ __launch_bounds__(512, 2) void prefill_192_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                              const bf16_t* __restrict__ v, bf16_t* __restrict__ out,
                                                              const PrefillWork* __restrict__ work,
                                                              const int32_t* __restrict__ chain, int H, int Hkv,
                                                              float c /* scale * log2(e) */) {
   constexpr int DQK = 192, DV = 128;
-  constexpr int QS = WAVES / HB;                // 32-row sub-tiles per workgroup
+  constexpr int QS = WAVES;                     // 32-row sub-tiles per workgroup: every query head has keys of its own, a workgroup takes one
   constexpr int CHK = DQK / 8, CHV = DV / 8;    // 16-byte chunks per K / V row
   constexpr int K_BYTES = BN * DQK * 2, V_BYTES = BN * DV * 2;
   constexpr int NST = 3;                        // stages of the K ring and of the V ring
@@ -720,9 +719,9 @@ __global__ __launch_bounds__(512, 2) void prefill_192_kernel(const bf16_t* __res
   s16x4 vq[VQ][2];
   auto item_begin = [&]() __attribute__((always_inline)) {
     w = work[it];
-    h = w.head0 + wave % HB;
+    h = w.head0;
     const int q_start = w.q_tile * (32 * QS);
-    wave_q0 = q_start + 32 * (wave / HB);
+    wave_q0 = q_start + 32 * wave;
     wave_active = wave_q0 < w.len;              // waves past the prompt's end only help loading
     const int qi = wave_q0 + n32, qi_c = qi < w.len ? qi : w.len - 1;
     pos0 = w.q_off + wave_q0;
@@ -745,9 +744,9 @@ __global__ __launch_bounds__(512, 2) void prefill_192_kernel(const bf16_t* __res
   auto touch_next_q = [&]() __attribute__((always_inline)) {
     const PrefillWork w2 = work[it + 1];
     constexpr int LINES = DQK / 64;
-    int r2 = w2.q_tile * (32 * QS) + 32 * (wave / HB) + lane / LINES;
+    int r2 = w2.q_tile * (32 * QS) + 32 * wave + lane / LINES;
     r2 = r2 < w2.len ? r2 : w2.len - 1;
-    const char* p2 = (const char*)(q + ((size_t)(w2.row0 + r2) * H + w2.head0 + wave % HB) * DQK) + (lane % LINES) * 128;
+    const char* p2 = (const char*)(q + ((size_t)(w2.row0 + r2) * H + w2.head0) * DQK) + (lane % LINES) * 128;
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(smem_base + TOUCH_LDS + wave * 256), "v"(p2) : "memory");
   };
   auto reset_sums = [&]() __attribute__((always_inline)) {
@@ -1023,11 +1022,10 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out
   const bf16_t *qq = (const bf16_t*)q, *kk = (const bf16_t*)k, *vv = (const bf16_t*)v;
   if (dqk == 64 && dv == 64) launch_hb<64, 64>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
   else if (dqk == 128 && dv == 128) launch_hb<128, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
-  else if (dqk == 192 && dv == 128 && longest > 6)
-    hipLaunchKernelGGL((hb == 8 ? prefill_192_kernel<8> : hb == 4 ? prefill_192_kernel<4> : hb == 2 ? prefill_192_kernel<2> : prefill_192_kernel<1>),
-                       grid, dim3(64 * WAVES), 0, stream, qq, kk, vv, (bf16_t*)out, d.work, d.chain, H, Hkv, c);
-  else if (dqk == 192 && dv == 128) launch_hb<192, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
-  else return hipErrorInvalidValue;
+  else if (dqk != 192 || dv != 128 || hb != 1) return hipErrorInvalidValue;   // (192 / 128: a latent layer's heads, each with keys of its own)
+  else if (longest > 6)
+    hipLaunchKernelGGL(prefill_192_kernel, grid, dim3(64 * WAVES), 0, stream, qq, kk, vv, (bf16_t*)out, d.work, d.chain, H, Hkv, c);
+  else launch_items<192, 128, 1>(grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
   return hipGetLastError();
 }
 
