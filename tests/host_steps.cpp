@@ -32,6 +32,8 @@ static std::vector<Stream*> streams;
 static long n_pinned = 0, pinned_bytes = 0, n_device = 0;   // allocations so far
 static int device = 0;                          // the calling thread's current one
 static std::set<int> allocated_on;
+static bool fail_malloc = false;                // the next allocation of device memory fails
+static std::set<void*> freed;                   // device memory that was given back
 static int fail_launch = -1;                    // the launch of this number fails
 static int n_launches = 0;
 static std::vector<PrefillLists> seen_lists;     // what every attention launch of a prefill step was given
@@ -60,8 +62,17 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
 hipError_t hipSetDevice(int d) { device = d; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
-hipError_t hipMalloc(void** p, size_t n) { ++n_device; allocated_on.insert(device); *p = calloc(1, n); return *p ? hipSuccess : hipErrorOutOfMemory; }
-hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) {
+  if (fail_malloc) {
+    fail_malloc = false;
+    return hipErrorOutOfMemory;
+  }
+  ++n_device;
+  allocated_on.insert(device);
+  *p = calloc(1, n);
+  return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipFree(void* p) { freed.insert(p); return hipSuccess; }   // (kept, so that no address comes twice)
 hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
   ++n_pinned;
@@ -192,20 +203,25 @@ static int decode(uint64_t req, const spd_rope_config* r = nullptr, bool noalloc
   return noalloc ? spd_decode_step_noalloc(ctx, pool, &b) : spd_decode_step(ctx, pool, &b);
 }
 
-// A pool of its own with a request that has `n_tokens` cached tokens, and the prefill step of the next five of them: two items, whose
+// A pool of its own with requests that have `n_tokens` cached tokens, and the prefill step of the next five of each: two items a request, whose
 // keys are shared out.
-static spd_pool* long_pool(uint64_t req, int32_t n_tokens) {
+static spd_pool* long_pool(uint64_t req, int32_t n_tokens, int n_req = 1) {
   spd_pool* p;
   uint64_t bytes;
-  const spd_pool_desc desc = {SPD_KV_GQA, 16, 2, 128, 128, (n_tokens + 5) / 16 + 1};
+  const spd_pool_desc desc = {SPD_KV_GQA, 16, 2, 128, 128, ((n_tokens + 5) / 16 + 1) * n_req};
   CHECK(spd_pool_bytes(&desc, &bytes) == SPD_OK);
   CHECK(spd_pool_create(ctx, aligned_alloc(4096, bytes), bytes, &desc, &p) == SPD_OK);
-  CHECK(spd_kv_reserve(p, req, n_tokens, nullptr) == SPD_OK);
+  for (int r = 0; r < n_req; ++r) CHECK(spd_kv_reserve(p, req + (uint64_t)r, n_tokens, nullptr) == SPD_OK);
   return p;
 }
-static int prefill(spd_pool* p, uint64_t req, int32_t n_cached) {
-  const int32_t cu[] = {0, 5};
-  const spd_prefill_batch b = {1, &req, cu, tensor, tensor, tensor, nullptr, tensor, 8, 2, 128, 128, 0.1f, &n_cached, nullptr};
+static int prefill(spd_pool* p, uint64_t req, int32_t n_cached, int n_req = 1) {
+  std::vector<uint64_t> ids;
+  std::vector<int32_t> cu(1, 0), cached((size_t)n_req, n_cached);
+  for (int r = 0; r < n_req; ++r) {
+    ids.push_back(req + (uint64_t)r);
+    cu.push_back(cu.back() + 5);
+  }
+  const spd_prefill_batch b = {n_req, ids.data(), cu.data(), tensor, tensor, tensor, nullptr, tensor, 8, 2, 128, 128, 0.1f, cached.data(), nullptr};
   return spd_prefill_step(ctx, p, &b);
 }
 
@@ -369,6 +385,25 @@ static void captured_prefill() {
   CHECK(prefill(p, 9, 3000) == SPD_OK && seen_lists.back().n_merge == 2 && seen_lists.back().parts);
 }
 
+// The buffer of the parts' sums: where there is no memory for it the step takes whole items; one that is outgrown stays until the steps
+// that were given it have finished.
+static void parts() {
+  spd_pool *p = long_pool(9, 3000), *many = long_pool(20, 6000, 8);
+  CHECK(prefill(p, 9, 3000) == SPD_OK && seen_lists.back().n_merge == 2);
+  char* const first = (char*)seen_lists.back().parts;
+  CHECK(first && first == ctx->phase[SPD_PHASE_PREFILL].parts);
+  fail_malloc = true;
+  CHECK(prefill(many, 20, 6000, 8) == SPD_OK && !fail_malloc && spd_last_hip_error() == 0);
+  CHECK(seen_lists.back().n_merge == 0 && !seen_lists.back().parts);
+  CHECK(prefill(many, 20, 6000, 8) == SPD_OK && seen_lists.back().n_merge == 16);
+  char* const second = (char*)seen_lists.back().parts;
+  CHECK(second && second != first);
+  CHECK(prefill(p, 9, 3000) == SPD_OK && (char*)seen_lists.back().parts == second);
+  CHECK(!freed.count(first));                        // the first step has not run yet
+  CHECK(spd_phase_sync(ctx, SPD_PHASE_PREFILL) == SPD_OK);
+  CHECK(freed.count(first) && !freed.count(second));
+}
+
 // Whatever GPU the calling thread's last call was for, a step's buffers lie on the context's own.
 static void devices() {
   spd_pool* p = long_pool(9, 3000);
@@ -393,6 +428,7 @@ int main(int argc, char** argv) {
   else if (name == "merges") merges();
   else if (name == "launches") launches();
   else if (name == "captured_prefill") captured_prefill();
+  else if (name == "parts") parts();
   else if (name == "devices") devices();
   else CHECK(!"a scenario of that name");
   puts("ok");

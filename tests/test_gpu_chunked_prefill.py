@@ -150,7 +150,8 @@ def test_workspace_grows_between_steps_in_flight():
 
 
 # heads, dims, (prefix, piece) per request, CUs of a share of its own (0: all of them, with the other phase), drift of the scores in nats
-@pytest.mark.parametrize("H,Hkv,d,reqs,cus,rise", [
+# (test_prefill_parts.py asks the host's dealing that items of every one of them are cut)
+SHARED_OUT = [
     (8, 2, 128, ((2805, 14), (1500, 7)), 0, 0.0),                  # parts of one length, rows past the piece
     (16, 2, 128, ((3000, 1),), 64, 0.0),                           # one token
     (8, 2, 128, ((2048, 129), (2111, 64), (0, 40)), 32, 0.0),      # a prefix that ends on a tile, pieces of several items
@@ -158,7 +159,11 @@ def test_workspace_grows_between_steps_in_flight():
     (5, 1, 128, ((2500, 70),), 96, 0.0),
     (8, 2, 128, ((2000, 50),), 0, 300.0),                          # references far apart
     (8, 2, 128, ((2000, 50),), 0, -300.0),
-])
+]
+MANY_PARTS = (8, 8, 128, ((4000, 1),) * 4, 0)                      # more parts than the buffer of their sums holds at first (16 MiB)
+
+
+@pytest.mark.parametrize("H,Hkv,d,reqs,cus,rise", SHARED_OUT)
 def test_items_shared_out_by_keys(H, Hkv, d, reqs, cus, rise):
     """Few items behind long prefixes: their keys go to several workgroups, whose sums a second launch adds up."""
     layer = W.LayerShape("gqa", H, Hkv, d, d, 16)
@@ -180,6 +185,33 @@ def test_items_shared_out_by_keys(H, Hkv, d, reqs, cus, rise):
     for r, (p, n) in enumerate(reqs):
         want = OA.chunk_attention(f64(q[cu[r] + p:cu[r + 1]]), f64(k[cu[r]:cu[r + 1]]), f64(v[cu[r]:cu[r + 1]]), scale)
         assert_parity(got[cu[r] + p:cu[r + 1]], want, f"request {r}: {n} tokens behind {p}")
+    gp.close()
+
+
+def test_buffer_of_the_parts_sums_grows_between_steps_in_flight():
+    """Two steps with shared-out items issued back to back, the second with more parts than the buffer holds that the first one's sums
+    went to: the first still writes and reads it when the second takes a new one."""
+    H, Hkv, d, reqs, _ = MANY_PARTS
+    layer = W.LayerShape("gqa", H, Hkv, d, d, 16)
+    scale = 1.0 / math.sqrt(d)
+    lens = tuple(p + n for p, n in reqs)
+    q, k, v, cu = W.prefill_inputs(layer, lens, seed=61)
+    gp = GpuPool(layer, sum(-(-n // 16) for n in lens) + 4, poison=True)
+    for r, (p, _) in enumerate(reqs):
+        gp.pool.kv_reserve(1 + r, p)
+        gp.pool.kv_write(PRE, 1 + r, 0, p, dev_bf16(k[cu[r]:cu[r] + p]), dev_bf16(v[cu[r]:cu[r] + p]))
+    gp.ctx.phase_sync(PRE)
+    outs = []
+    for first, last in ((0, 1), (0, len(reqs)), (0, 1)):              # one request, all of them, one again (its pieces written anew)
+        rows = np.concatenate([np.arange(cu[r] + reqs[r][0], cu[r + 1]) for r in range(first, last)])
+        outs.append(([dev_bf16(x[rows]) for x in (q, k, v)], torch.empty((len(rows), H, d), dtype=torch.bfloat16, device=DEV), last))
+    torch.cuda.synchronize()
+    for step, out, last in outs:
+        gp.pool.prefill_step([1 + r for r in range(last)], list(range(last + 1)), *step, out, H, Hkv, d, d, scale, prefix_lens=[p for p, _ in reqs[:last]])
+    gp.ctx.phase_sync(PRE)
+    want = np.concatenate([OA.chunk_attention(f64(q[cu[r] + p:cu[r + 1]]), f64(k[cu[r]:cu[r + 1]]), f64(v[cu[r]:cu[r + 1]]), scale) for r, (p, _) in enumerate(reqs)])
+    for i, (_, out, last) in enumerate(outs):
+        assert_parity(host_f64(out), want[:last], f"step {i}")
     gp.close()
 
 

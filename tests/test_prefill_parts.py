@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_chunked_prefill import MANY_PARTS, SHARED_OUT
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2504_19867_amd", "csrc")
 # share, persistent, q heads, KV heads, (len, prefix) per request
@@ -98,6 +100,17 @@ def test_items_are_shared_out_where_a_few_long_ones_would_hold_up_the_step(tmp_p
     got, plain = _deal(tmp_path, FEW + MANY)
     n = [_check(b, g, p) for b, g, p in zip(FEW + MANY, got, plain)]
     assert all(n[:len(FEW)]) and not any(n[len(FEW):]), n
+
+
+def test_batches_of_the_gpu_tests_are_shared_out(tmp_path):
+    """The tests of parts on the GPU are tests of parts."""
+    batches = [(cus or 256, int(cus > 0), H, Hkv, tuple((n, p) for p, n in reqs if p)) for H, Hkv, _, reqs, cus, *_ in [*SHARED_OUT, MANY_PARTS]]
+    got, plain = _deal(tmp_path, batches)
+    assert all(_check(b, g, p) for b, g, p in zip(batches, got, plain))
+    floats = 8 * (128 * 32 + 64)                                     # that a part of 128 dims leaves
+    assert sum(w[8] >= 0 for w in got[-1][1]) * floats * 4 > 16 << 20
+    one, _ = _deal(tmp_path, [(*batches[-1][:4], batches[-1][4][:1])])
+    assert 0 < sum(w[8] >= 0 for w in one[0][1]) * floats * 4 <= 16 << 20
 
 
 def test_random_batches(tmp_path):
