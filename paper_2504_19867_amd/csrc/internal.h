@@ -121,7 +121,10 @@ struct PrefillWork {
   int32_t head0;     // first query head of the workgroup's head group
   int32_t kv_row0;   // first row of the request's keys / values in the K, V tensors the kernel reads
   int32_t q_off;     // position of query row 0 in the request = number of cached tokens before it
-  int32_t kt0, kt1;  // the tiles of 64 keys to visit: all that the rows can see, or a part of them
+};
+// What an item of a step with shared-out items visits (a list beside the items': the others, of more items, have nothing to stage for it).
+struct PrefillRange {
+  int32_t kt0, kt1;  // the tiles of 64 keys: all that the rows can see, or a part of them
   int32_t part;      // number of the part, where its sums go; -1: the item is whole
 };
 // An item that was shared out: its parts are part0 .. part0 + n_parts - 1.
@@ -135,6 +138,7 @@ struct PrefillLists {
   const PrefillWork* work;
   const int32_t* chain;
   int n_blocks;
+  const PrefillRange* range;   // null: all items are whole
   const PrefillMerge* merge;
   int n_merge;
   float* parts;

@@ -72,7 +72,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
                                                          const bf16_t* __restrict__ v, bf16_t* __restrict__ out,
                                                          const PrefillWork* __restrict__ work,
                                                          const int32_t* __restrict__ chain, int H, int Hkv,
-                                                         float c /* scale * log2(e) */, float* __restrict__ parts) {
+                                                         float c /* scale * log2(e) */, const PrefillRange* __restrict__ range, float* __restrict__ parts) {
   constexpr int QS = WAVES / HB;                // 32-row sub-tiles per workgroup
   constexpr int CHK = DQK / 8, CHV = DV / 8;    // 16-byte chunks per K / V row
   constexpr int K_BYTES = BN * DQK * 2, V_BYTES = BN * DV * 2, STAGE_BYTES = K_BYTES + V_BYTES;
@@ -139,16 +139,18 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   auto load_items = [&](int base) __attribute__((always_inline)) {
     const PrefillWork pw = work[min(base + lane, it_end - 1)];
     d_row0 = pw.row0; d_len = pw.len; d_qtile = pw.q_tile; d_head0 = pw.head0; d_kvrow0 = pw.kv_row0; d_qoff = pw.q_off;
-    if constexpr (PARTS) { d_kt0 = pw.kt0; d_kt1 = pw.kt1; d_part = pw.part; }
+    if constexpr (PARTS) {
+      const PrefillRange pr = range[min(base + lane, it_end - 1)];
+      d_kt0 = pr.kt0; d_kt1 = pr.kt1; d_part = pr.part;
+    }
     dsc_base = base;
   };
-  struct Rows { int row0, len, q_tile, head0, kv_row0, q_off; };
-  auto item_of = [&](int i) __attribute__((always_inline)) -> Rows {
-    if constexpr (!ITEM_LANES) return Rows{work[i].row0, work[i].len, work[i].q_tile, work[i].head0, work[i].kv_row0, work[i].q_off};
+  auto item_of = [&](int i) __attribute__((always_inline)) -> PrefillWork {
+    if constexpr (!ITEM_LANES) return work[i];
     const int l = i - dsc_base;
-    return Rows{__builtin_amdgcn_readlane(d_row0, l), __builtin_amdgcn_readlane(d_len, l),
-                __builtin_amdgcn_readlane(d_qtile, l), __builtin_amdgcn_readlane(d_head0, l),
-                __builtin_amdgcn_readlane(d_kvrow0, l), __builtin_amdgcn_readlane(d_qoff, l)};
+    return PrefillWork{__builtin_amdgcn_readlane(d_row0, l), __builtin_amdgcn_readlane(d_len, l),
+                       __builtin_amdgcn_readlane(d_qtile, l), __builtin_amdgcn_readlane(d_head0, l),
+                       __builtin_amdgcn_readlane(d_kvrow0, l), __builtin_amdgcn_readlane(d_qoff, l)};
   };
   if constexpr (ITEM_LANES) load_items(it);
   // ---- producer: the tile loads run ahead of the compute (a pair of tiles, or PD tiles where the
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   int p_it = it, p_kt = 0, p_n = 0, p_kv_len = 0, pt = 0;
   const char *p_kb = nullptr, *p_vb = nullptr;
   auto producer_item = [&]() __attribute__((always_inline)) {                  // producer state for item p_it
-    const Rows pw = item_of(p_it);
+    const PrefillWork pw = item_of(p_it);
     const int pg = pw.head0 / G;
     p_kv_len = pw.q_off + pw.len;
     p_n = PARTS ? __builtin_amdgcn_readlane(d_kt1, p_it - dsc_base) : (min(p_kv_len, pw.q_off + pw.q_tile * (32 * QS) + 32 * QS) + BN - 1) / BN;
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   for (int t = 0; t < (PAIRS ? 2 : PD); ++t) produce_one();
 
   // ---- state of the item being computed
-  Rows w;
+  PrefillWork w;
   int kt_first = 0, kt_end = 0, part = -1;
   int h = 0, wave_q0 = 0, qi = 0, pos0 = 0, pos = 0, kt = 0;
   bool wave_active = false;
@@ -253,7 +255,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   uint32_t q_touch = 0;
   bool touch_next = false;
   auto touch_next_q = [&]() __attribute__((always_inline)) {
-    const Rows w2 = item_of(it + 1);
+    const PrefillWork w2 = item_of(it + 1);
     constexpr int LINES = DQK / 64;               // 128-byte lines per query row
     int r2 = w2.q_tile * (32 * QS) + 32 * (wave / HB) + lane / LINES;
     r2 = r2 < w2.len ? r2 : w2.len - 1;
@@ -994,7 +996,7 @@ int prefill_block_m(int group) { return 32 * (WAVES / prefill_heads_per_block(gr
 template <int DQK, int DV, int HB>
 static void launch_items(dim3 grid, hipStream_t stream, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const PrefillLists& d, int H,
                          int Hkv, float c) {
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES), 0, stream, q, k, v, out, d.work, d.chain, H, Hkv, c, d.parts); };
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES), 0, stream, q, k, v, out, d.work, d.chain, H, Hkv, c, d.range, d.parts); };
   if constexpr (DQK <= 128) {
     if (d.n_merge) {
       launch(prefill_kernel<DQK, DV, HB, true>);

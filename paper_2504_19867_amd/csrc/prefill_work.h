@@ -27,8 +27,7 @@ constexpr long ITEM_COST_TILES = 4;
 struct PrefillItem {
   int32_t row0, len, q_tile, head0, kv_row0, q_off, tiles, unit;
   int32_t weight() const { return tiles + (int32_t)ITEM_COST_TILES; }
-  PrefillWork part(int32_t kt0, int32_t kt1, int32_t number) const { return PrefillWork{row0, len, q_tile, head0, kv_row0, q_off, kt0, kt1, number}; }
-  PrefillWork whole() const { return part(0, tiles, -1); }
+  PrefillWork work() const { return PrefillWork{row0, len, q_tile, head0, kv_row0, q_off}; }
 };
 
 // ---- Sharing items out by keys.  A step with few items, or with a few long ones (short pieces of prompts behind long cached
@@ -215,8 +214,8 @@ class PrefillShares {
 // middle of it ends 111 us later beside chains, 105 beside workgroups, and 79 beside whole items, which leave it compute units of
 // their own; pairs of both steps, queued, 148, 146 and 159 us.)
 inline void write_shares(const std::vector<PrefillItem>& items, const std::vector<uint32_t>& chain_of, const std::vector<PrefillPiece>& pieces, size_t xcds,
-                         size_t per_xcd, bool persistent, std::vector<PrefillWork>& work, std::vector<int32_t>& chain, std::vector<PrefillMerge>& merge) {
-  merge.clear();
+                         size_t per_xcd, bool persistent, std::vector<PrefillWork>& work, std::vector<PrefillRange>& range, std::vector<int32_t>& chain,
+                         std::vector<PrefillMerge>& merge) {
   // what goes where, in the order of the items: a piece (its number), or the whole item
   struct Entry { uint32_t item, chain; int32_t tiles, piece; };
   std::vector<Entry> all;
@@ -237,18 +236,20 @@ inline void write_shares(const std::vector<PrefillItem>& items, const std::vecto
       ++merge.back().n_parts;
     }
   }
-  auto work_of = [&](const Entry& e) -> PrefillWork {
-    return e.piece < 0 ? items[e.item].whole() : items[e.item].part(pieces[(size_t)e.piece].kt0, pieces[(size_t)e.piece].kt1, part[(size_t)e.piece]);
-  };
   const size_t n = all.size();
   work.resize(n);
+  range.resize(n);
+  auto write = [&](size_t to, const Entry& e) {
+    work[to] = items[e.item].work();
+    range[to] = e.piece < 0 ? PrefillRange{0, e.tiles, -1} : PrefillRange{pieces[(size_t)e.piece].kt0, pieces[(size_t)e.piece].kt1, part[(size_t)e.piece]};
+  };
   if (persistent) {
     auto slot = [&](uint32_t c) -> size_t { return c % (uint32_t)per_xcd * (uint32_t)xcds + c / (uint32_t)per_xcd; };
     chain.assign(xcds * per_xcd + 1, 0);
     for (const Entry& e : all) ++chain[slot(e.chain) + 1];
     for (size_t c = 0; c + 1 < chain.size(); ++c) chain[c + 1] += chain[c];
     std::vector<int32_t> at(chain.begin(), chain.end() - 1);
-    for (const Entry& e : all) work[(size_t)at[slot(e.chain)]++] = work_of(e);
+    for (const Entry& e : all) write((size_t)at[slot(e.chain)]++, e);
     return;
   }
   std::vector<uint64_t> order(n);                 // XCD, longest first (an item has fewer than 2^26 tiles of 64 keys), place
@@ -269,16 +270,22 @@ inline void write_shares(const std::vector<PrefillItem>& items, const std::vecto
   for (size_t i = 0; i < most; ++i)
     for (size_t x = 0; x < xcds; ++x) {           // workgroup i * xcds + x runs on XCD x
       chain.push_back((int32_t)at);
-      if (first[x] + i < first[x + 1]) work[at++] = work_of(all[(uint32_t)order[first[x] + i]]);
+      if (first[x] + i < first[x + 1]) write(at++, all[(uint32_t)order[first[x] + i]]);
     }
   chain.push_back((int32_t)at);
 }
 
-// `persistent`: a chain per compute unit; `merge` null: no item is shared out.
+// What a step's items that were shared out need besides `work` and `chain`; both empty where all items are whole.
+struct PrefillParts {
+  std::vector<PrefillRange> range;                // one per item of `work`
+  std::vector<PrefillMerge> merge;
+};
+
+// `persistent`: a chain per compute unit; `parts` null: no item is shared out.
 // (Lists in a few flat arrays: with a vector per unit, per XCD and per chain this took 13 of the 20 us of a step of 8 short prompts.)
 inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefix_lens, const int32_t* kv_cu, int n_req,
                                  int H, int Hkv, int xcds, int share, bool persistent, std::vector<PrefillWork>& work,
-                                 std::vector<int32_t>& chain, std::vector<PrefillMerge>* merge, long* looked_at = nullptr) {
+                                 std::vector<int32_t>& chain, PrefillParts* parts, long* looked_at = nullptr) {
   const int G = H / Hkv, hb = prefill_heads_per_block(G), bm = prefill_block_m(G), groups = G / hb;
   // items, unit after unit, each unit's longest first
   const size_t n_units = (size_t)n_req * (size_t)Hkv;
@@ -308,7 +315,10 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
     }
   }
   unit_first[n_units] = (uint32_t)items.size();
-  if (merge) merge->clear();
+  if (parts) {
+    parts->range.clear();
+    parts->merge.clear();
+  }
   const bool even = share >= xcds && share % xcds == 0;
   if (persistent && !even) xcds = 1;
   const int per_xcd = std::max(1, share / xcds);  // chains per XCD, or workgroups that run there at a time
@@ -335,7 +345,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
   }
   // At most the heaviest item's weight is to be gained, and with many items per compute unit whole ones balance well enough: of random
   // batches with more than three per compute unit one in twelve can be a sixth shorter, and all of them would pay for the search.
-  bool may_share = merge && even && n_items <= 3 * (size_t)share && heaviest > 2 * LEAST_PART_TILES;
+  bool may_share = parts && even && n_items <= 3 * (size_t)share && heaviest > 2 * LEAST_PART_TILES;
   if (may_share && !persistent) {
     // Before the items are dealt only for the search: one begins no later than when those ahead of it fill all compute units, and those
     // that have to be cut cost more.  (Near the border the search finds nothing, mostly: one prompt of 2500 tokens on 256 CUs.)
@@ -381,7 +391,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
     const bool found = shares.find(pieces);
     if (looked_at) *looked_at = shares.looked_at();
     if (found) {
-      write_shares(items, chain_of, pieces, (size_t)xcds, (size_t)per_xcd, persistent, work, chain, *merge);
+      write_shares(items, chain_of, pieces, (size_t)xcds, (size_t)per_xcd, persistent, work, parts->range, chain, parts->merge);
       return;
     }
   }
@@ -395,7 +405,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
     for (uint32_t i = 0; i < most; ++i)
       for (int x = 0; x < xcds; ++x) {            // workgroup i * xcds + x runs on XCD x
         chain.push_back((int32_t)work.size());
-        if (xq_first[(size_t)x] + i < xq_first[(size_t)x + 1]) work.push_back(items[xq[xq_first[(size_t)x] + i]].whole());
+        if (xq_first[(size_t)x] + i < xq_first[(size_t)x + 1]) work.push_back(items[xq[xq_first[(size_t)x] + i]].work());
       }
     chain.push_back((int32_t)work.size());
     return;
@@ -407,7 +417,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
   for (int c = 0; c < share; ++c) chain[(size_t)c + 1] += chain[(size_t)c];
   std::vector<int32_t> at(chain.begin(), chain.end() - 1);
   work.resize(n_items);
-  for (size_t i = 0; i < n_items; ++i) work[(size_t)at[slot(chain_of[i])]++] = items[i].whole();
+  for (size_t i = 0; i < n_items; ++i) work[(size_t)at[slot(chain_of[i])]++] = items[i].work();
 }
 
 // Tiles of 64 keys that the longest item visits.

@@ -190,19 +190,20 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   if (ctx->env_prefill_persistent >= 0) persistent = ctx->env_prefill_persistent != 0;   // experiment switch
   std::vector<PrefillWork> work;
   std::vector<int32_t> chain;
-  std::vector<PrefillMerge> merge;
+  PrefillParts shared;
+  const std::vector<PrefillMerge>& merge = shared.merge;
   float* parts = nullptr;
-  auto deal = [&](std::vector<PrefillMerge>* m) {
+  auto deal = [&](PrefillParts* p) {
     build_prefill_chains(b->cu_seqlens, chunked ? b->prefix_lens : nullptr, chunked ? kv_cu.data() : nullptr, b->n_req,
-                         b->n_q_heads, b->n_kv_heads, ctx->xcds, share, persistent, work, chain, m);
+                         b->n_q_heads, b->n_kv_heads, ctx->xcds, share, persistent, work, chain, p);
   };
-  deal(b->dim_qk <= 128 ? &merge : nullptr);     // (the kernel for 192 dims takes whole items)
+  deal(b->dim_qk <= 128 ? &shared : nullptr);     // (the kernel for 192 dims takes whole items)
   if (!merge.empty()) {
     size_t n_parts = 0;
     for (const PrefillMerge& m : merge) n_parts += (size_t)m.n_parts;
     parts = parts_reserve(ctx, n_parts * prefill_part_floats(b->dim_v) * sizeof(float));
     if (!parts) {
-      merge.clear();
+      shared = PrefillParts();
       deal(nullptr);
     }
   }
@@ -216,7 +217,8 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
     if (chunked) n_gather += tile_desc_count(0, one_launch ? pre : pre + len);
   }
   size_t off_chain = align16(work.size() * sizeof(PrefillWork));
-  size_t off_merge = align16(off_chain + chain.size() * sizeof(int32_t));
+  size_t off_range = align16(off_chain + chain.size() * sizeof(int32_t));
+  size_t off_merge = align16(off_range + shared.range.size() * sizeof(PrefillRange));
   size_t off_desc = align16(off_merge + merge.size() * sizeof(PrefillMerge));
   size_t off_gather = align16(off_desc + n_descs * sizeof(TileDesc));
   // RoPE inside the step: every row's position where the queries have a launch of their own, and room for the frequency
@@ -269,7 +271,10 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   StepScope step{ctx, SPD_PHASE_PREFILL, st, stream};
   memcpy(st->host, work.data(), work.size() * sizeof(PrefillWork));
   memcpy(st->host + off_chain, chain.data(), chain.size() * sizeof(int32_t));
-  if (!merge.empty()) memcpy(st->host + off_merge, merge.data(), merge.size() * sizeof(PrefillMerge));
+  if (!merge.empty()) {
+    memcpy(st->host + off_range, shared.range.data(), shared.range.size() * sizeof(PrefillRange));
+    memcpy(st->host + off_merge, merge.data(), merge.size() * sizeof(PrefillMerge));
+  }
   StepMark mark = step_mark(ctx, SPD_PHASE_PREFILL, step.capturing);
   const double* rope_w = nullptr;
   if (ctx->kernel_timing) SPD_HIP(hipEventRecord(ps.ev_start, stream));
@@ -319,8 +324,8 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
       SPD_HIP(launch_kv_gather(g, pool->base, (const TileDesc*)(ws + off_gather), (int)n_gather, ws + ws_k, ws + ws_v, StepMark{}, stream));
   }
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 0, stream)) != SPD_OK) return rc;
-  const PrefillLists lists{(const PrefillWork*)ws, (const int32_t*)(ws + off_chain), (int)chain.size() - 1, (const PrefillMerge*)(ws + off_merge),
-                           (int)merge.size(), parts};
+  const PrefillLists lists{(const PrefillWork*)ws, (const int32_t*)(ws + off_chain), (int)chain.size() - 1,
+                           merge.empty() ? nullptr : (const PrefillRange*)(ws + off_range), (const PrefillMerge*)(ws + off_merge), (int)merge.size(), parts};
   SPD_HIP(launch_prefill(b->q, att_k, att_v, b->out, lists, longest_item(b->cu_seqlens, chunked ? b->prefix_lens : nullptr, b->n_req),
                          b->n_q_heads, b->n_kv_heads, b->dim_qk, b->dim_v, b->scale, stream));
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 1, stream)) != SPD_OK) return rc;

@@ -37,6 +37,7 @@ static std::set<void*> freed;                   // device memory that was given 
 static int fail_launch = -1;                    // the launch of this number fails
 static int n_launches = 0;
 static std::vector<PrefillLists> seen_lists;     // what every attention launch of a prefill step was given
+static uint64_t staged_bytes = 0;                // of the last prefill step: what its launch copies to the device
 static std::vector<bool> seen_counters;         // may the decode launch merge its own chunks?
 static std::vector<double> seen_w;              // sum of the RoPE frequencies that each decode launch found when it ran
 
@@ -141,8 +142,10 @@ static hipError_t launch(hipStream_t s, const StepMark& m, std::function<void()>
 hipError_t launch_kv_write(const PoolGeom&, char*, const TileDesc*, int, const void*, const void*, const StepMark& m, hipStream_t s, void*,
                            const void*, uint64_t) { return launch(s, m); }
 bool kv_rows_supported(const PoolGeom& g) { return g.kind == SPD_KV_GQA && g.Hkv >= 2; }
-hipError_t launch_kv_rows(const PoolGeom&, char*, const TileDesc*, int, const void*, const void*, const KvRows&, const StepMark& m,
-                          hipStream_t s) { return launch(s, m); }
+hipError_t launch_kv_rows(const PoolGeom&, char*, const TileDesc*, int, const void*, const void*, const KvRows& x, const StepMark& m, hipStream_t s) {
+  staged_bytes = x.copy_bytes;
+  return launch(s, m);
+}
 hipError_t launch_kv_gather(const PoolGeom&, const char*, const TileDesc*, int, void*, void*, const StepMark& m, hipStream_t s) { return launch(s, m); }
 hipError_t launch_kv_write_fp8(const PoolGeom&, char*, const TileDesc*, int, const void*, const StepMark& m, hipStream_t s, void*, const void*,
                                uint64_t) { return launch(s, m); }
@@ -404,6 +407,15 @@ static void parts() {
   CHECK(freed.count(first) && !freed.count(second));
 }
 
+// Lists cross the host link ahead of the attention: a step of whole items stages 24 bytes for each, and no ranges of keys.
+static void staged() {
+  constexpr int N = 64;
+  spd_pool* p = long_pool(100, 1, N);
+  CHECK(prefill(p, 100, 0, N) == SPD_OK && seen_lists.back().n_merge == 0 && !seen_lists.back().range);
+  const uint64_t items = 2 * N, chains = (uint64_t)seen_lists.back().n_blocks + 1;
+  CHECK(staged_bytes >= items * 24 && staged_bytes < items * 24 + chains * 4 + N * sizeof(TileDesc) + 5 * 16);
+}
+
 // Whatever GPU the calling thread's last call was for, a step's buffers lie on the context's own.
 static void devices() {
   spd_pool* p = long_pool(9, 3000);
@@ -429,6 +441,7 @@ int main(int argc, char** argv) {
   else if (name == "launches") launches();
   else if (name == "captured_prefill") captured_prefill();
   else if (name == "parts") parts();
+  else if (name == "staged") staged();
   else if (name == "devices") devices();
   else CHECK(!"a scenario of that name");
   puts("ok");

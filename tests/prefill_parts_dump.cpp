@@ -35,14 +35,20 @@ int main() {
     }
     std::vector<PrefillWork> work;
     std::vector<int32_t> chain;
-    std::vector<PrefillMerge> merge;
+    PrefillParts parts;
+    const std::vector<PrefillMerge>& merge = parts.merge;
     long looked_at = 0;
-    build_prefill_chains(cu.data(), pre.data(), kv.data(), n, H, Hkv, 8, share, persistent != 0, work, chain, whole ? nullptr : &merge, &looked_at);
+    build_prefill_chains(cu.data(), pre.data(), kv.data(), n, H, Hkv, 8, share, persistent != 0, work, chain, whole ? nullptr : &parts, &looked_at);
     std::printf("%zu %zu %zu %ld\n", chain.size() - 1, work.size(), merge.size(), looked_at);
     for (int32_t c : chain) std::printf("%d ", c);
     std::printf("\n");
-    for (const PrefillWork& w : work)
-      std::printf("%d %d %d %d %d %d %d %d %d\n", w.row0, w.len, w.q_tile, w.head0, w.kv_row0, w.q_off, w.kt0, w.kt1, w.part);
+    const int bm = prefill_block_m(H / Hkv);
+    for (size_t i = 0; i < work.size(); ++i) {
+      const PrefillWork& w = work[i];
+      const int end = w.q_off + std::min(w.len, (w.q_tile + 1) * bm);   // behind the last key that a whole item visits
+      const PrefillRange r = parts.range.empty() ? PrefillRange{0, (end + 63) / 64, -1} : parts.range[i];
+      std::printf("%d %d %d %d %d %d %d %d %d\n", w.row0, w.len, w.q_tile, w.head0, w.kv_row0, w.q_off, r.kt0, r.kt1, r.part);
+    }
     for (const PrefillMerge& m : merge) std::printf("%d %d %d %d %d %d\n", m.row0, m.len, m.q_tile, m.head0, m.part0, m.n_parts);
   }
 }
