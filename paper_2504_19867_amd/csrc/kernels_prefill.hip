@@ -603,9 +603,9 @@ __global__ __launch_bounds__(512, 2) void prefill_192_kernel(const bf16_t* __res
   constexpr int NS = 2 * KS, NV = (BN / 16) * VB;     // MFMAs of either product
   constexpr int RING = 4, VAH = 2, VQ = VAH + 1;      // K operands, V operands on the way
   constexpr int OPITCH = 32 * 2 + 16;           // bytes per staged output row piece (32 dims, padded)
-  constexpr int V_LDS = NST * K_BYTES, EPI_LDS = V_LDS + NST * V_BYTES, TOUCH_LDS = EPI_LDS + WAVES * 32 * OPITCH;
+  constexpr int V_LDS = NST * K_BYTES, EPI_LDS = V_LDS + NST * V_BYTES;
   constexpr float ABOVE = 8.f;
-  __shared__ __attribute__((aligned(1024))) char smem[TOUCH_LDS + WAVES * 256];
+  __shared__ __attribute__((aligned(1024))) char smem[EPI_LDS + WAVES * 32 * OPITCH];
 
   const int G = H / Hkv;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -741,15 +741,6 @@ __global__ __launch_bounds__(512, 2) void prefill_192_kernel(const bf16_t* __res
                  : "memory");
     n_kv_tiles = tiles_of(w);
     kt = 0;
-  };
-  // the next item's query rows, one 128-byte line per lane, into LDS that nobody reads: the fragment loads then find them in the L2
-  auto touch_next_q = [&]() __attribute__((always_inline)) {
-    const PrefillWork w2 = work[it + 1];
-    constexpr int LINES = DQK / 64;
-    int r2 = w2.q_tile * (32 * QS) + 32 * wave + lane / LINES;
-    r2 = r2 < w2.len ? r2 : w2.len - 1;
-    const char* p2 = (const char*)(q + ((size_t)(w2.row0 + r2) * H + w2.head0) * DQK) + (lane % LINES) * 128;
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(smem_base + TOUCH_LDS + wave * 256), "v"(p2) : "memory");
   };
   auto reset_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -964,7 +955,6 @@ __global__ __launch_bounds__(512, 2) void prefill_192_kernel(const bf16_t* __res
       }
     }
     act_prev = act;
-    if (__builtin_expect(first, 0) && !last && more) touch_next_q();
     barrier();
     if (__builtin_expect(last && !more, 0)) {
       if (act_prev) second_product(ST, [](int) {});
