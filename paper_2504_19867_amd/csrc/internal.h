@@ -360,8 +360,9 @@ hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLau
 // may touch, and no record may be longer (checked again at the launch).
 constexpr int MLA_THREADS = 256;
 constexpr int MLA_CHUNK_PAGES = MLA_THREADS - DECODE_ITEM_WORDS;
-// one workgroup per chain: workgroup b computes the items d_work[d_chain[b]] .. d_work[d_chain[b + 1] - 1]
-hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillLists& lists, int longest, int H, int Hkv, int dqk, int dv,
+// one workgroup per chain: workgroup b computes the items work[chain[b]] .. work[chain[b + 1] - 1].  two_groups: 192 / 128 dims only, as
+// two_groups_pay says
+hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillLists& lists, bool two_groups, int H, int Hkv, int dqk, int dv,
                           float scale, hipStream_t stream);
 // x [T, K], w_gu [2 I, K] (joint gate/up rows in blocks of 32 + 32), out [T, I], all bf16 in device memory;
 // K a multiple of 32, I a multiple of 128

@@ -570,7 +570,7 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(bf16_t* __restrict__
   }
 }
 
-// ---- 192 / 128 dims (the un-absorbed heads of an MLA layer), prompts of more than six tiles.
+// ---- 192 / 128 dims (the un-absorbed heads of an MLA layer), where two_groups_pay (prefill_work.h) says that it is the faster one.
 //
 // The same contraction, tiles, operand orders and chains; what differs is how the two waves of a SIMD share it.  Waves w and
 // w + 4 sit on one SIMD, and the two groups of four waves run half a tile apart, with an s_barrier at every change:
@@ -1006,7 +1006,7 @@ static void launch_hb(int hb, dim3 grid, hipStream_t stream, const bf16_t* q, co
   else launch_items<DQK, DV, 1>(grid, stream, q, k, v, out, d, H, Hkv, c);
 }
 
-hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillLists& d, int longest, int H, int Hkv, int dqk, int dv,
+hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillLists& d, bool two_groups, int H, int Hkv, int dqk, int dv,
                           float scale, hipStream_t stream) {
   const float c = scale * 1.4426950408889634f;
   const int hb = prefill_heads_per_block(H / Hkv);
@@ -1015,7 +1015,7 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out
   if (dqk == 64 && dv == 64) launch_hb<64, 64>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
   else if (dqk == 128 && dv == 128) launch_hb<128, 128>(hb, grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
   else if (dqk != 192 || dv != 128 || hb != 1) return hipErrorInvalidValue;   // (192 / 128: a latent layer's heads, each with keys of its own)
-  else if (longest > 6)
+  else if (two_groups)
     hipLaunchKernelGGL(prefill_192_kernel, grid, dim3(64 * WAVES), 0, stream, qq, kk, vv, (bf16_t*)out, d.work, d.chain, H, Hkv, c);
   else launch_items<192, 128, 1>(grid, stream, qq, kk, vv, (bf16_t*)out, d, H, Hkv, c);
   return hipGetLastError();

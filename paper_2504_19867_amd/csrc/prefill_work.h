@@ -420,11 +420,20 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
   for (size_t i = 0; i < n_items; ++i) work[(size_t)at[slot(chain_of[i])]++] = items[i].work();
 }
 
-// Tiles of 64 keys that the longest item visits.
-inline int longest_item(const int32_t* cu_seqlens, const int32_t* prefix_lens, int n_req) {
-  int most = 0;
-  for (int r = 0; r < n_req; ++r) most = std::max(most, (cu_seqlens[r + 1] - cu_seqlens[r] - 1 + (prefix_lens ? prefix_lens[r] : 0)) / 64 + 1);
-  return most;
+// 192 / 128 dims: is prefill_192_kernel the faster one for the step?  It gains about three times per tile ahead of an item's diagonal what it
+// loses per item, and nothing where only one group of waves has rows (up to 128), so the sum over the step's items decides.  (Not the share:
+// a batch has the same bits on all of them.)  One prompt of 400 .. 4000 tokens of 16 heads with 8 .. 60 of 1 .. 300, equal prompts of 1 .. 1024 and
+// random ones of up to 200 .. 1500, on 64, 128 and 256 CUs (549 steps, kernel alone): 0.16, 0.26 and 0.33 % over the better one of the two on average,
+// at most 7 % over prefill_kernel (24 -> 26 us); with "longest prompt over six tiles" as the rule 0.71, 0.77 and 0.26 %.  prefill_kernel /
+// prefill_192_kernel on 64 CUs: a prompt of 400 tokens and 60 of 64 tokens 91 / 96 us, of 1000 and 24 of 64 70 / 67, of 4000 and 8 of 64 333 / 263;
+// 32 of 384 tokens 217 / 220, of 448 303 / 279.
+inline bool two_groups_pay(const int32_t* cu_seqlens, int n_req) {
+  int64_t gain = 0;
+  for (int r = 0; r < n_req; ++r) {
+    const int64_t len = cu_seqlens[r + 1] - cu_seqlens[r], items = (len + 255) / 256, full = len - 256 * (items - 1) > 128 ? items : items - 1;
+    gain += 6 * full * (full - 1) - items;        // 3 x (0 + 4 + 8 ..) tiles ahead of the full items' diagonals
+  }
+  return gain > 0;
 }
 
 }  // namespace spd

@@ -326,8 +326,8 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 0, stream)) != SPD_OK) return rc;
   const PrefillLists lists{(const PrefillWork*)ws, (const int32_t*)(ws + off_chain), (int)chain.size() - 1,
                            merge.empty() ? nullptr : (const PrefillRange*)(ws + off_range), (const PrefillMerge*)(ws + off_merge), (int)merge.size(), parts};
-  SPD_HIP(launch_prefill(b->q, att_k, att_v, b->out, lists, longest_item(b->cu_seqlens, chunked ? b->prefix_lens : nullptr, b->n_req),
-                         b->n_q_heads, b->n_kv_heads, b->dim_qk, b->dim_v, b->scale, stream));
+  const bool two_groups = b->dim_qk == 192 && two_groups_pay(b->cu_seqlens, b->n_req);
+  SPD_HIP(launch_prefill(b->q, att_k, att_v, b->out, lists, two_groups, b->n_q_heads, b->n_kv_heads, b->dim_qk, b->dim_v, b->scale, stream));
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 1, stream)) != SPD_OK) return rc;
   if ((rc = step.commit()) != SPD_OK) return rc;
   if (ctx->kernel_timing) {

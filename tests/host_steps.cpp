@@ -163,7 +163,7 @@ hipError_t launch_decode_gqa(const PoolGeom&, char*, const DecodeLaunch& d, hipS
 }
 hipError_t launch_decode_prepare(const PoolGeom&, char*, const DecodeLaunch& d, int, void*, hipStream_t s) { return launch(s, d.mark); }
 hipError_t launch_decode_mla(const PoolGeom& g, char* b, const DecodeLaunch& d, hipStream_t s) { return launch_decode_gqa(g, b, d, s); }
-hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillLists& d, int, int, int, int, int, float, hipStream_t s) {
+hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillLists& d, bool, int, int, int, int, float, hipStream_t s) {
   seen_lists.push_back(d);
   return launch(s, StepMark{});
 }

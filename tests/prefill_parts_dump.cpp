@@ -1,6 +1,6 @@
 // Prints how a prefill batch is dealt to chains (csrc/prefill_work.h), one batch per input line:
 //   share persistent whole_items n_q_heads n_kv_heads n_req (len prefix)...
-// Answer: "n_chains n_work n_merge looked_at" (what the search for the cuts looked at), the chains' bounds, a line "row0 len q_tile head0 kv_row0 q_off kt0 kt1 part" per item and a line
+// Answer: "n_chains n_work n_merge looked_at two_groups" (what the search for the cuts looked at; which kernel 192 / 128 dims take), the chains' bounds, a line "row0 len q_tile head0 kv_row0 q_off kt0 kt1 part" per item and a line
 // "row0 len q_tile head0 part0 n_parts" per merged one.
 #include <iostream>
 #include <sstream>
@@ -39,7 +39,7 @@ int main() {
     const std::vector<PrefillMerge>& merge = parts.merge;
     long looked_at = 0;
     build_prefill_chains(cu.data(), pre.data(), kv.data(), n, H, Hkv, 8, share, persistent != 0, work, chain, whole ? nullptr : &parts, &looked_at);
-    std::printf("%zu %zu %zu %ld\n", chain.size() - 1, work.size(), merge.size(), looked_at);
+    std::printf("%zu %zu %zu %ld %d\n", chain.size() - 1, work.size(), merge.size(), looked_at, (int)two_groups_pay(cu.data(), n));
     for (int32_t c : chain) std::printf("%d ", c);
     std::printf("\n");
     const int bm = prefill_block_m(H / Hkv);

@@ -1,5 +1,5 @@
 """GPU parity of the prefill kernel for 192 / 128 dims (two groups of waves half a tile apart) against the fp64 oracle, through
-spd_prefill_step over a latent pool.  A prompt of more than 384 tokens takes the whole batch to that kernel."""
+spd_prefill_step over a latent pool."""
 import math
 
 import numpy as np
@@ -34,8 +34,14 @@ def _run(H, lens, cus, make):
     return got[:-1], OA.prefill_attention(f64(q), f64(k), f64(v), cu, SCALE), host_bits(out)
 
 
-# chains of one-tile items, item ends on every stage of the rings of three, waves without rows, tiles that only some waves have
-@pytest.mark.parametrize("H,lens", [(3, (385,) + (1,) * 30 + (64, 65, 63)), (16, (1, 31, 32, 33, 63, 64, 65, 400)), (2, (255, 256, 257, 320, 700)), (1, (1300, 1)), (2, (384, 383))])
+# Chains of one-tile items, item ends on every stage of the rings of three, waves without rows, tiles that only some waves have
+# (test_prefill_parts.py asks the host that the whole batch goes to this kernel)
+BORDERS = [(3, (1500,) + (1,) * 30 + (64, 65, 63)), (16, (1, 31, 32, 33, 63, 64, 65, 400)), (2, (255, 256, 257, 320, 700)), (1, (1300, 1))]
+# batches of the same kind for which prefill_kernel is the faster one
+ONE_GROUP = [(3, (385,) + (1,) * 30 + (64, 65, 63)), (2, (384, 383))]
+
+
+@pytest.mark.parametrize("H,lens", BORDERS + ONE_GROUP)
 def test_item_and_tile_borders(H, lens):
     ref = None
     for cus in (32, 0):            # one chain per compute unit; one workgroup per item

@@ -8,6 +8,7 @@ import subprocess
 import pytest
 
 from test_gpu_chunked_prefill import MANY_PARTS, SHARED_OUT
+from test_gpu_prefill_192 import BORDERS, ONE_GROUP
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2504_19867_amd", "csrc")
@@ -31,11 +32,11 @@ def _deal(tmp_path, batches):
     out = iter(subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=300).stdout.split("\n"))
     answers = []
     for _ in range(2 * len(batches)):
-        n_chains, n_work, n_merge, looked_at = map(int, next(out).split())
+        n_chains, n_work, n_merge, looked_at, two_groups = map(int, next(out).split())
         bounds = list(map(int, next(out).split()))
         assert len(bounds) == n_chains + 1 and bounds[0] == 0 and bounds[-1] == n_work and bounds == sorted(bounds)
         work = [tuple(map(int, next(out).split())) for _ in range(n_work)]
-        answers.append((bounds, work, [tuple(map(int, next(out).split())) for _ in range(n_merge)], looked_at))
+        answers.append((bounds, work, [tuple(map(int, next(out).split())) for _ in range(n_merge)], looked_at, two_groups))
     return answers[:len(batches)], answers[len(batches):]
 
 
@@ -55,7 +56,7 @@ def _check(batch, got, plain):
     G = H // Hkv
     hb = next(h for h in (8, 4, 2, 1) if G % h == 0)
     bm = 32 * (8 // hb)
-    bounds, work, merge, looked_at = got
+    bounds, work, merge, looked_at, _ = got
     whole = {(w[:6]): w[7] for w in plain[1]}                     # item -> its tiles
     assert len(whole) == len(plain[1]) and all(w[6] == 0 and w[8] == -1 for w in plain[1]) and not plain[2]
     seen = {}
@@ -111,6 +112,26 @@ def test_batches_of_the_gpu_tests_are_shared_out(tmp_path):
     assert sum(w[8] >= 0 for w in got[-1][1]) * floats * 4 > 16 << 20
     one, _ = _deal(tmp_path, [(*batches[-1][:4], batches[-1][4][:1])])
     assert 0 < sum(w[8] >= 0 for w in one[0][1]) * floats * 4 <= 16 << 20
+
+
+def _two_groups(lens):
+    """Item by item: three times the tiles ahead of the diagonal where both groups of waves have rows, against one per item."""
+    gain = 0
+    for n in lens:
+        for row0 in range(0, n, 256):
+            gain += 3 * (row0 // 64) * (min(256, n - row0) > 128) - 1
+    return gain > 0
+
+
+def test_which_kernel_192_dims_take(tmp_path):
+    rng = random.Random(4)
+    cases = [lens for _, lens in BORDERS + ONE_GROUP]
+    assert [_two_groups(lens) for lens in cases] == [True] * len(BORDERS) + [False] * len(ONE_GROUP)
+    for _ in range(300):
+        top = rng.choice((64, 300, 500, 1500, 8192))
+        cases.append(tuple(rng.randint(1, top) for _ in range(rng.randint(1, 60))))
+    got, _ = _deal(tmp_path, [(64, 1, 2, 2, tuple((n, 0) for n in lens)) for lens in cases])
+    assert [bool(g[4]) for g in got] == [_two_groups(lens) for lens in cases]
 
 
 def test_random_batches(tmp_path):
