@@ -92,11 +92,11 @@ class PrefillShares {
       }
       near = std::max(near, sum / (long)per_xcd_);
     }
-    near += near / 32 + 1;
-    if (near > hi || !fits(near, pieces)) {
-      if (!fits(hi, pieces)) return false;
+    near = std::min(hi, near + near / 32 + 1);
+    if (!fits(near, pieces)) {
+      if (near == hi || !fits(hi, pieces)) return false;
       std::vector<PrefillPiece> fewer;
-      for (lo = std::min(near, hi); hi - lo > hi / 16;) {
+      for (lo = near; hi - lo > hi / 16;) {
         const long mid = (lo + hi) / 2;
         if (fits(mid, fewer)) {
           hi = mid;
@@ -206,15 +206,34 @@ class PrefillShares {
   }
 };
 
+// When the last of an XCD's workgroups ends, of these weights in the order in which they are launched, one per compute unit.  The XCD deals
+// them to its four shader arrays in turn, each as soon as its array has a compute unit free, and not before the one ahead of it has begun.
+inline long dealt_end(const std::vector<int32_t>& weights, int per_xcd) {
+  const size_t arrays = per_xcd % 4 == 0 ? 4 : 1, cus = (size_t)per_xcd / arrays;
+  std::vector<long> free(arrays * cus, 0);        // when every compute unit is free, array after array
+  long begun = 0, end = 0;
+  for (size_t i = 0; i < weights.size(); ++i) {
+    const auto array = free.begin() + (long)(i % arrays * cus), cu = std::min_element(array, array + (long)cus);
+    begun = std::max(begun, *cu);
+    *cu = begun + weights[i];
+    end = std::max(end, *cu);
+  }
+  return end;
+}
+
 // The work list and the merge list of items some of which are shared out.  `persistent`: workgroup c xcds + x takes chain c of XCD x, each in
 // the order of its items.  Without, the chains only say where to cut, and every
 // item and part is a workgroup of its own, each XCD's longest first: where the phases' masks overlap, the other phase's
-// workgroups then get a compute unit whenever a part ends, not with the kernel.  (The four pieces above on 256 CUs, both phases there: as
+// workgroups then get a compute unit whenever a part ends, not with the kernel.  Of every four, one per shader array, the shortest goes
+// first, so that the array whose turn it is when all compute units have one is the one that comes free.  (Longest first throughout
+// leaves the next one waiting behind the longest: 300 tokens behind 4000, 5 items a head on 8 compute units, cut into 46 + 21 tiles: the
+// last parts began when the first ones ended, 97.5 us, whole 88.9.)  `whole_end`: when the whole items would end; false, and nothing
+// written, if the parts do not end early enough after all.  (The four pieces above on 256 CUs, both phases there: as
 // chains 136 us, as workgroups 137, in the order of the chains 147.  A decode step of 16 requests of 1000 tokens that comes in the
 // middle of it ends 111 us later beside chains, 105 beside workgroups, and 79 beside whole items, which leave it compute units of
 // their own; pairs of both steps, queued, 148, 146 and 159 us.)
-inline void write_shares(const std::vector<PrefillItem>& items, const std::vector<uint32_t>& chain_of, const std::vector<PrefillPiece>& pieces, size_t xcds,
-                         size_t per_xcd, bool persistent, std::vector<PrefillWork>& work, std::vector<PrefillRange>& range, std::vector<int32_t>& chain,
+inline bool write_shares(const std::vector<PrefillItem>& items, const std::vector<uint32_t>& chain_of, const std::vector<PrefillPiece>& pieces, size_t xcds,
+                         size_t per_xcd, bool persistent, long whole_end, std::vector<PrefillWork>& work, std::vector<PrefillRange>& range, std::vector<int32_t>& chain,
                          std::vector<PrefillMerge>& merge) {
   // what goes where, in the order of the items: a piece (its number), or the whole item
   struct Entry { uint32_t item, chain; int32_t tiles, piece; };
@@ -237,20 +256,29 @@ inline void write_shares(const std::vector<PrefillItem>& items, const std::vecto
     }
   }
   const size_t n = all.size();
-  work.resize(n);
-  range.resize(n);
   auto write = [&](size_t to, const Entry& e) {
     work[to] = items[e.item].work();
     range[to] = e.piece < 0 ? PrefillRange{0, e.tiles, -1} : PrefillRange{pieces[(size_t)e.piece].kt0, pieces[(size_t)e.piece].kt1, part[(size_t)e.piece]};
   };
+  auto weight = [&](const Entry& e) -> int32_t { return e.tiles + (int32_t)(ITEM_COST_TILES + (e.piece >= 0 && part[(size_t)e.piece] >= 0 ? PART_COST_TILES : 0)); };
+  const long latest = shared_end(whole_end);
+  long end = 0;
   if (persistent) {
+    std::vector<long> load(xcds * per_xcd, 0);
+    for (const Entry& e : all) end = std::max(end, load[e.chain] += weight(e));
+    if (end > latest) {
+      merge.clear();
+      return false;
+    }
+    work.resize(n);
+    range.resize(n);
     auto slot = [&](uint32_t c) -> size_t { return c % (uint32_t)per_xcd * (uint32_t)xcds + c / (uint32_t)per_xcd; };
     chain.assign(xcds * per_xcd + 1, 0);
     for (const Entry& e : all) ++chain[slot(e.chain) + 1];
     for (size_t c = 0; c + 1 < chain.size(); ++c) chain[c + 1] += chain[c];
     std::vector<int32_t> at(chain.begin(), chain.end() - 1);
     for (const Entry& e : all) write((size_t)at[slot(e.chain)]++, e);
-    return;
+    return true;
   }
   std::vector<uint64_t> order(n);                 // XCD, longest first (an item has fewer than 2^26 tiles of 64 keys), place
   std::vector<size_t> first(xcds + 1, 0);
@@ -261,10 +289,23 @@ inline void write_shares(const std::vector<PrefillItem>& items, const std::vecto
   }
   std::sort(order.begin(), order.end());
   size_t most = 0, at = 0;
+  std::vector<int32_t> weights;
   for (size_t x = 0; x < xcds; ++x) {
     most = std::max(most, first[x + 1]);
     first[x + 1] += first[x];
+    weights.clear();
+    for (size_t i = first[x]; i < first[x + 1]; ++i) {
+      if (i % 4 == first[x] % 4 && i + 4 <= first[x + 1]) std::reverse(order.begin() + (long)i, order.begin() + (long)i + 4);
+      weights.push_back(weight(all[(uint32_t)order[i]]));
+    }
+    end = std::max(end, dealt_end(weights, (int)per_xcd));
   }
+  if (end > latest) {
+    merge.clear();
+    return false;
+  }
+  work.resize(n);
+  range.resize(n);
   chain.clear();
   chain.reserve(most * xcds + 1);
   for (size_t i = 0; i < most; ++i)
@@ -273,6 +314,7 @@ inline void write_shares(const std::vector<PrefillItem>& items, const std::vecto
       if (first[x] + i < first[x + 1]) write(at++, all[(uint32_t)order[first[x] + i]]);
     }
   chain.push_back((int32_t)at);
+  return true;
 }
 
 // What a step's items that were shared out need besides `work` and `chain`; both empty where all items are whole.
@@ -390,10 +432,16 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
     std::vector<PrefillPiece> pieces;
     const bool found = shares.find(pieces);
     if (looked_at) *looked_at = shares.looked_at();
-    if (found) {
-      write_shares(items, chain_of, pieces, (size_t)xcds, (size_t)per_xcd, persistent, work, parts->range, chain, parts->merge);
-      return;
+    long end = persistent ? *std::max_element(load.begin(), load.end()) : 0;
+    if (found && !persistent) {
+      std::vector<int32_t> weights;
+      for (int x = 0; x < xcds; ++x) {
+        weights.clear();
+        for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) weights.push_back(items[xq[i]].weight());
+        end = std::max(end, dealt_end(weights, per_xcd));
+      }
     }
+    if (found && write_shares(items, chain_of, pieces, (size_t)xcds, (size_t)per_xcd, persistent, end, work, parts->range, chain, parts->merge)) return;
   }
   if (!persistent) {
     uint32_t most = 0;

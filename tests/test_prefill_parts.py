@@ -41,13 +41,18 @@ def _deal(tmp_path, batches):
 
 
 def _end(share, bounds, work):
-    """When the last compute unit is done, in tiles: an XCD's workgroups go to its compute units as these come free."""
+    """When the last compute unit is done, in tiles: an XCD's workgroups go to its four shader arrays in turn, each to the compute unit
+    there that is free first, and none begins ahead of the one before it."""
     per_xcd, end = share // 8, 0
+    arrays = 4 if per_xcd % 4 == 0 else 1
     for x in range(8):
-        load = [0] * per_xcd
-        for c in range(x, len(bounds) - 1, 8):
-            load[load.index(min(load))] += sum(w[7] - w[6] + 4 + (w[8] >= 0) for w in work[bounds[c]:bounds[c + 1]])
-        end = max(end, *load)
+        free, begun = [[0] * (per_xcd // arrays) for _ in range(arrays)], 0
+        for i, c in enumerate(range(x, len(bounds) - 1, 8)):
+            units = free[i % arrays]
+            cu = units.index(min(units))
+            begun = max(begun, units[cu])
+            units[cu] = begun + sum(w[7] - w[6] + 4 + (w[8] >= 0) for w in work[bounds[c]:bounds[c + 1]])
+        end = max(end, *(t for units in free for t in units))
     return end
 
 
@@ -87,10 +92,9 @@ def _check(batch, got, plain):
         assert all(b - a <= 1 for a, b in zip(bounds, bounds[1:]))
     if merge:
         assert not persistent or len(bounds) - 1 == share
-        # predicted end of the step: a tenth and the second launch ahead of the whole items, as the search has it for its chains (dealt
-        # longest first the parts may end a little later than the chains that they were cut for)
+        # predicted end of the step: a tenth and the second launch ahead of the whole items
         most = _end(share, bounds, work), _end(share, plain[0], plain[1])
-        assert most[0] <= most[1] * 9 // 10 - 6 if persistent else most[0] + 6 < most[1], most
+        assert most[0] <= most[1] * 9 // 10 - 6, most
         assert n_parts <= 2 * share + len(merge)
         numbers = sorted(w[8] for w in work if w[8] >= 0)
         assert numbers == list(range(n_parts))
