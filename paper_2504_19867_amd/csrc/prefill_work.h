@@ -39,8 +39,21 @@ struct PrefillItem {
 // A part pays its item's fixed cost again and one tile for writing its sums; the second launch costs what six tiles do.  Parts are no
 // shorter than eight tiles.  No part begins behind the item's first row, so that every row has keys in every part.
 constexpr long PART_COST_TILES = 1, MERGE_COST_TILES = 6, LEAST_PART_TILES = 8;
+// With more than MANY_PIECES items and parts the host takes so much longer to deal and stage them that MANY_PIECES_TILES more have to be
+// won: 1500 tokens on 256 CUs (192 items of up to 28 tiles, 264 pieces of up to 19) 45.7 -> 47.3 us, waited for 58 -> 68, 1659 behind 519 (39 tiles,
+// 28) 66.3 -> 63.6 and 78.5 -> 87.3; where more is won both fall (100 tokens behind 2000, four times: 256 pieces, 37 -> 14 tiles, 68 -> 51
+// and 80 -> 73).
+constexpr size_t MANY_PIECES = 192;
+constexpr long MANY_PIECES_TILES = 5;
 // Where the parts have to end for whole items that end at `longest`: a tenth ahead, or it is not worth another launch.
-inline long shared_end(long longest) { return longest * 9 / 10 - MERGE_COST_TILES; }
+inline long shared_end(long longest, size_t n_pieces) { return longest * 9 / 10 - MERGE_COST_TILES - (n_pieces > MANY_PIECES ? MANY_PIECES_TILES : 0); }
+// The same ahead of the search: every item that is longer than that will be two pieces at least.
+inline long shared_end(long longest, const std::vector<PrefillItem>& items) {
+  const long end = shared_end(longest, 0);
+  size_t n = items.size();
+  for (const PrefillItem& item : items) n += item.weight() > end;
+  return shared_end(longest, n);
+}
 
 struct PrefillPiece { uint32_t item; int32_t kt0, kt1; uint32_t chain; };
 
@@ -57,14 +70,14 @@ class PrefillShares {
   // The pieces that take the place of some whole items, ordered by item and keys, if every chain can be that much shorter than the longest.
   bool find(std::vector<PrefillPiece>& pieces) {
     const long longest = *std::max_element(load_.begin(), load_.end());
-    long hi = shared_end(longest);
+    long hi = shared_end(longest, 0);             // (what MANY_PIECES asks for is looked at when the pieces are known)
     long lo = LEAST_PART_TILES + ITEM_COST_TILES + PART_COST_TILES;
     for (size_t x = 0; x < load_.size(); x += per_xcd_) {
       long sum = 0;
       for (size_t c = x; c < x + per_xcd_; ++c) sum += load_[c];
       lo = std::max(lo, (sum + (long)per_xcd_ - 1) / (long)per_xcd_);
     }
-    if (lo > hi) return false;
+    if (lo > shared_end(longest, items_)) return false;
     first_.assign(load_.size() + 1, 0);
     for (uint32_t c : chain_of_) ++first_[c + 1];
     for (size_t c = 0; c < load_.size(); ++c) first_[c + 1] += first_[c];
@@ -261,7 +274,7 @@ inline bool write_shares(const std::vector<PrefillItem>& items, const std::vecto
     range[to] = e.piece < 0 ? PrefillRange{0, e.tiles, -1} : PrefillRange{pieces[(size_t)e.piece].kt0, pieces[(size_t)e.piece].kt1, part[(size_t)e.piece]};
   };
   auto weight = [&](const Entry& e) -> int32_t { return e.tiles + (int32_t)(ITEM_COST_TILES + (e.piece >= 0 && part[(size_t)e.piece] >= 0 ? PART_COST_TILES : 0)); };
-  const long latest = shared_end(whole_end);
+  const long latest = shared_end(whole_end, n);
   long end = 0;
   if (persistent) {
     std::vector<long> load(xcds * per_xcd, 0);
@@ -400,7 +413,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
         ahead += w;
       }
     }
-    const long cap = shared_end(end);
+    const long cap = shared_end(end, items);
     for (int x = 0; x < xcds; ++x) {
       long sum = 0;
       for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) {

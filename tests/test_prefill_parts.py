@@ -15,7 +15,7 @@ CSRC = os.path.join(ROOT, "paper_2504_19867_amd", "csrc")
 # share, persistent, q heads, KV heads, (len, prefix) per request
 FEW = [(256, 0, 32, 8, ((14, 2805), (7, 2805))), (64, 1, 64, 8, ((1, 8000),)), (128, 1, 32, 8, ((512, 8000),)),
        (256, 0, 32, 8, ((532, 0), (355, 5023), (605, 3058), (867, 2188))), (32, 1, 5, 1, ((300, 4000),)), (96, 1, 8, 8, ((1, 0), (257, 6000)))]
-MANY = [(128, 1, 64, 8, ((4096, 0),) * 4), (256, 0, 32, 8, ((2048, 0),) * 4), (128, 1, 32, 8, ((30, 0),) * 50), (128, 1, 8, 8, ((128, 0),) * 2)]
+MANY = [(256, 0, 32, 8, ((1500, 0),)), (256, 0, 32, 8, ((1659, 519),)), (128, 1, 64, 8, ((4096, 0),) * 4), (256, 0, 32, 8, ((2048, 0),) * 4), (128, 1, 32, 8, ((30, 0),) * 50), (128, 1, 8, 8, ((128, 0),) * 2)]
 
 
 def _deal(tmp_path, batches):
