@@ -663,6 +663,22 @@ static hipError_t launch_stream(const void* x, const void* w_gu, void* out, int 
   return hipGetLastError();
 }
 
+// 129 to 256 tokens: are the small tiles faster?  With each on a compute unit of its own they are (hidden 8192, inter 7168 on 224 CUs, 256
+// tokens: 114 / 147 us).  An XCD deals its workgroups to its four shader arrays in turn; what counts is how many compute units of an array
+// get two.  A large tile costs about 6 us and 0.56 a slice, small ones 1 and, with one such unit per array, about as much a slice, with two
+// 0.7 (up to 160 tokens, most of whose second tile is one row again and again, 0.55 too).  Small / large, hidden x inter, tokens, CUs (units with two):
+// 2048 x 5632, 256, 160 (1) 38.9 / 44.3 us; 4096 x 4096, 256, 96 (1) 69.7 / 78.2; 4096 x 8192, 256, 224 (1) 71.7 / 80.0, 192 (2) 97.4 / 79.7, at 160 tokens
+// 0.97, at 176 1.04 of the large tiles' time; 8192 x 7168, 192, 192 (1) 149 / 139, 160 (2) 153 / 138; 4096 x 14336, 256, 256 (6) 104 / 86.  With two on every
+// unit: 1024 x 2048, 256, 32 (1) 20.6 / 24.6; 4096 x 1792 86.3 / 76.6.  (8192 x 3584 on 96 CUs is the exception measured: 128 / 146.)
+static bool small_tiles_pay(int T, int K, int I, int xcds, int cus) {
+  const int columns = 2 * I / 128, per_xcd = (columns + xcds - 1) / xcds * 2;
+  const int with_two = (per_xcd + 3) / 4 - cus / (4 * xcds);   // per shader array
+  if (with_two <= 0) return true;
+  if (K > 4096) return false;
+  if (T <= 160) return with_two <= 2;
+  return with_two == 1 && (K <= 2048 || 2 * columns * 2 <= 3 * cus);
+}
+
 hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T, int K, int I, int xcds, int cus, bool exclusive,
                               const StepMark& mark, hipStream_t stream) {
   // up to 128 tokens: the weights streamed through registers, all tokens in one workgroup (measured at 100 and 128 tokens of
@@ -671,12 +687,7 @@ hipError_t launch_ffn_gate_up(const void* x, const void* w_gu, void* out, int T,
   if (T <= 32) return launch_stream<2>(x, w_gu, out, T, K, I, cus, mark, stream);
   if (T <= 64) return launch_stream<4>(x, w_gu, out, T, K, I, cus, mark, stream);
   if (T <= 128) return launch_stream<8>(x, w_gu, out, T, K, I, cus, mark, stream);
-  // the small tile where each of its workgroups then has a compute unit to itself; two of them on one take longer than one of the large
-  // tile's.  Small / large, hidden 8192, inter 7168 (56 large tiles): 256 CUs 112 / 147 us at 256 tokens, 192 152 / 147, 128 171 / 147 (137 /
-  // 135 at 129); hidden 4096, inter 14336 (112): 256 CUs 101 / 84 at 256 tokens, 80 / 75 at 129.  (129 tokens of the former on 160 CUs are the
-  // exception measured: 130 / 136.)
-  const int large_tiles = ((T + 255) / 256) * (2 * I / 256);
-  if (T <= 256 && 4 * large_tiles <= cus) return launch_tiles<128>(ffn_gate_up_small_kernel, x, w_gu, out, T, K, I, xcds, 0, mark, stream);
+  if (T <= 256 && small_tiles_pay(T, K, I, xcds, cus)) return launch_tiles<128>(ffn_gate_up_small_kernel, x, w_gu, out, T, K, I, xcds, 0, mark, stream);
   return launch_tiles<256>(ffn_gate_up_large_kernel, x, w_gu, out, T, K, I, xcds, exclusive ? cus : 0, mark, stream);
 }
 

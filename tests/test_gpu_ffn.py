@@ -125,6 +125,25 @@ def test_gate_up_several_tiles_per_workgroup(T, I, cus, K):
     ctx.close()
 
 
+@pytest.mark.parametrize("T", [129, 160, 161, 256])
+@pytest.mark.parametrize("K,I", [(96, 2048), (544, 3072)])
+def test_gate_up_two_small_tiles_on_some_compute_units(T, K, I):
+    """129 to 256 tokens on 32 CUs: 8 and 12 small tiles per XCD, so that one and two compute units more than there are would be needed per
+    shader array (the latter up to 160 tokens; above, the large tiles)."""
+    ctx = S.Context(0)
+    ctx.set_partition(ctx.device_info()[0] - 32, 32)
+    xb, wgb, wub = W.ffn_inputs(T, K, I, seed=2900 + T + I)
+    x, wg, wu = dev_bf16(xb), dev_bf16(wgb), dev_bf16(wub)
+    w_gu = torch.empty((2 * I, K), dtype=torch.bfloat16, device=DEV)
+    out = torch.full((T + 2, I), 7.0, dtype=torch.bfloat16, device=DEV)
+    ctx.ffn_pack_gate_up(DEC, wg, wu, w_gu, K, I)
+    ctx.ffn_gate_up(DEC, x, w_gu, out, T, K, I)
+    ctx.phase_sync(DEC)
+    assert (out[T:] == 7.0).all()
+    _assert_ffn(host_f64(out[:T]), F.gate_up(f64(xb), f64(wgb), f64(wub)), f"ffn small tiles T={T} K={K} I={I}")
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,K,I", [(1, 256, 128), (7, 512, 384), (31, 256, 640), (32, 1024, 128), (33, 256, 128), (48, 768, 256),
                                    (63, 512, 128), (64, 256, 384), (16, 4096, 256), (64, 4096, 128)])
 def test_gate_up_batches_of_up_to_64_tokens(T, K, I):
