@@ -35,7 +35,7 @@ struct PrefillItem {
 // item that none of them has room for is cut: each part leaves its sums in memory, and a second launch adds them up.  Whole step, 32
 // heads: 2 pieces of up to 14 tokens behind 2805 on 256 CUs 63.9 -> 38 us; 512 tokens behind 8000 on 128 CUs 193 -> 121; one token behind
 // 8000, 64 heads on 64 CUs 186 -> 61; 4 pieces of 355 .. 867 behind up to 5023 on 256 CUs (312 items of up to 89 tiles, mean load 57, now
-// at most 67; with all compute units busy the clock is lower) 159 -> 140.
+// at most 65; with all compute units busy the clock is lower) 155 -> 137.
 // A part pays its item's fixed cost again and one tile for writing its sums; the second launch costs what six tiles do.  Parts are no
 // shorter than eight tiles.  No part begins behind the item's first row, so that every row has keys in every part.
 constexpr long PART_COST_TILES = 1, MERGE_COST_TILES = 6, LEAST_PART_TILES = 8;
@@ -45,14 +45,20 @@ constexpr long PART_COST_TILES = 1, MERGE_COST_TILES = 6, LEAST_PART_TILES = 8;
 // and 80 -> 73).
 constexpr size_t MANY_PIECES = 192;
 constexpr long MANY_PIECES_TILES = 5;
-// Where the parts have to end for whole items that end at `longest`: a tenth ahead, or it is not worth another launch.
-inline long shared_end(long longest, size_t n_pieces) { return longest * 9 / 10 - MERGE_COST_TILES - (n_pieces > MANY_PIECES ? MANY_PIECES_TILES : 0); }
+// Where the parts have to end for whole items that end at `longest`: a tenth ahead, or it is not worth another launch; with a chain per compute
+// unit ten tiles do (pieces of 893, 207 and 547 tokens behind 4118, 3798 and 7358 on 128 CUs, 188 tiles -> 167: 266.6 -> 246.9 us, waited for 303 ->
+// 284; 20 batches of 119 to 315 tiles won 5 to 10 % queued and 2 to 9 waited for; as workgroups of their own 3 to 6, and waited for up to 4
+// were lost).
+inline long shared_end(long longest, size_t n_pieces, bool persistent) {
+  const long ahead = persistent ? std::min((longest + 9) / 10, 10l) : (longest + 9) / 10;
+  return longest - ahead - MERGE_COST_TILES - (n_pieces > MANY_PIECES ? MANY_PIECES_TILES : 0);
+}
 // The same ahead of the search: every item that is longer than that will be two pieces at least.
-inline long shared_end(long longest, const std::vector<PrefillItem>& items) {
-  const long end = shared_end(longest, 0);
+inline long shared_end(long longest, const std::vector<PrefillItem>& items, bool persistent) {
+  const long end = shared_end(longest, 0, persistent);
   size_t n = items.size();
   for (const PrefillItem& item : items) n += item.weight() > end;
-  return shared_end(longest, n);
+  return shared_end(longest, n, persistent);
 }
 
 struct PrefillPiece { uint32_t item; int32_t kt0, kt1; uint32_t chain; };
@@ -65,19 +71,20 @@ struct PrefillPiece { uint32_t item; int32_t kt0, kt1; uint32_t chain; };
 // at most.  A step that is waited for has it ahead of everything else: those 4 pieces 168 -> 159 us.
 class PrefillShares {
  public:
-  PrefillShares(const std::vector<PrefillItem>& items, const std::vector<uint32_t>& chain_of, const std::vector<long>& load, int per_xcd, int block_m)
-      : items_(items), chain_of_(chain_of), load_(load), per_xcd_((size_t)per_xcd), block_m_(block_m) {}
+  PrefillShares(const std::vector<PrefillItem>& items, const std::vector<uint32_t>& chain_of, const std::vector<long>& load, int per_xcd, int block_m,
+                bool persistent)
+      : items_(items), chain_of_(chain_of), load_(load), per_xcd_((size_t)per_xcd), block_m_(block_m), persistent_(persistent) {}
   // The pieces that take the place of some whole items, ordered by item and keys, if every chain can be that much shorter than the longest.
   bool find(std::vector<PrefillPiece>& pieces) {
     const long longest = *std::max_element(load_.begin(), load_.end());
-    long hi = shared_end(longest, 0);             // (what MANY_PIECES asks for is looked at when the pieces are known)
+    long hi = shared_end(longest, items_, persistent_);
     long lo = LEAST_PART_TILES + ITEM_COST_TILES + PART_COST_TILES;
     for (size_t x = 0; x < load_.size(); x += per_xcd_) {
       long sum = 0;
       for (size_t c = x; c < x + per_xcd_; ++c) sum += load_[c];
       lo = std::max(lo, (sum + (long)per_xcd_ - 1) / (long)per_xcd_);
     }
-    if (lo > shared_end(longest, items_)) return false;
+    if (lo > hi) return false;
     first_.assign(load_.size() + 1, 0);
     for (uint32_t c : chain_of_) ++first_[c + 1];
     for (size_t c = 0; c < load_.size(); ++c) first_[c + 1] += first_[c];
@@ -131,6 +138,7 @@ class PrefillShares {
   const std::vector<long>& load_;
   const size_t per_xcd_;
   const int block_m_;
+  const bool persistent_;
   std::vector<uint32_t> first_, of_chain_;        // every chain's items, the longest first
   std::vector<uint32_t> by_load_;                 // every XCD's chains, the least loaded first
   struct Room { long room; uint32_t chain; };
@@ -274,7 +282,7 @@ inline bool write_shares(const std::vector<PrefillItem>& items, const std::vecto
     range[to] = e.piece < 0 ? PrefillRange{0, e.tiles, -1} : PrefillRange{pieces[(size_t)e.piece].kt0, pieces[(size_t)e.piece].kt1, part[(size_t)e.piece]};
   };
   auto weight = [&](const Entry& e) -> int32_t { return e.tiles + (int32_t)(ITEM_COST_TILES + (e.piece >= 0 && part[(size_t)e.piece] >= 0 ? PART_COST_TILES : 0)); };
-  const long latest = shared_end(whole_end, n);
+  const long latest = shared_end(whole_end, n, persistent);
   long end = 0;
   if (persistent) {
     std::vector<long> load(xcds * per_xcd, 0);
@@ -413,7 +421,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
         ahead += w;
       }
     }
-    const long cap = shared_end(end, items);
+    const long cap = shared_end(end, items, false);
     for (int x = 0; x < xcds; ++x) {
       long sum = 0;
       for (uint32_t i = xq_first[(size_t)x]; i < xq_first[(size_t)x + 1]; ++i) {
@@ -441,7 +449,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
       }
     }
   if (may_share) {
-    PrefillShares shares(items, chain_of, load, per_xcd, bm);
+    PrefillShares shares(items, chain_of, load, per_xcd, bm, persistent);
     std::vector<PrefillPiece> pieces;
     const bool found = shares.find(pieces);
     if (looked_at) *looked_at = shares.looked_at();
