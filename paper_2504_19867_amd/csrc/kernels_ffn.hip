@@ -20,7 +20,7 @@
 //
 // Decode batches of up to 128 tokens are bound by reading the weights once and have a kernel of their own
 // (ffn_gate_up_stream_kernel); between 128 and 256 tokens there are 128 x 128 tiles (ffn_gate_up_small_kernel: four waves, two
-// workgroups per compute unit), where a share has a compute unit for each of them.
+// workgroups per compute unit), where those are the faster ones (small_tiles_pay).
 #include "internal.h"
 
 #include <type_traits>
@@ -482,10 +482,11 @@ typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2))); 
 // one stage ahead: one barrier per 8 slices.
 // The product is taken transposed (weights are the A operand): a lane then has four consecutive outputs of one token.
 // <NB, 8, 8>: 256 joint rows per workgroup, 128 KiB of weights on the way per CU; <NB, 4, 16>: 128 rows, the same bytes on the
-// way from four waves; five to seven waves where those fill the share's compute units better (launch_stream).  With the weights staged through LDS (at most 96 KiB on the way, a third to a fifth of the stages taken
-// by x, a barrier per slice) 64 tokens of hidden 4096, inter 14336 took 68 us on 128 CUs and 48 on 256; now 55 and 42 us (4.3 and
-// 5.7 TB/s).  A ring of 16 slices with eight waves is slower (56 us; 75 against 62 at 128 tokens), and so are loads
-// without the non-temporal mark (61 us).
+// way from four waves; five to seven waves where those fill the share's compute units better (launch_stream).  With the weights staged
+// through LDS (at most 96 KiB on the way, a third to a fifth of the stages taken by x, a barrier per slice) 64 tokens of hidden 4096, inter
+// 14336 took 68 us on 128 CUs and 48 on 256; now 54.8 and 42.7 us (4.3 and 5.5 TB/s) with the weights from HBM, copies of them cycled, and
+// 52.8 on 128 CUs from one copy, most of which the memory-side cache then holds.  With eight waves a ring of 16 slices was slower (56 us
+// instead of 55; 75 against 62 at 128 tokens), and so were loads without the non-temporal mark (61 us).
 template <int NB, int WAVES, int RING>
 __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                                            bf16_t* __restrict__ out, int T, int K, int I, StepMark mark) {
