@@ -195,10 +195,9 @@ int spd_shm_kv_free_list(spd_shm_pool* pool, int32_t* out, int64_t cap, int64_t*
  * pages and the rows given are the next piece of its prompt, at positions prefix .. prefix+len-1:
  *     out[i, h, :] = sum_{j <= prefix + i} softmax_j(scale * q[i, h, :] . K_r[j, g, :]) * V_r[j, g, :]
  * where K_r, V_r are the cached rows followed by the piece's own.  The step reserves blocks for
- * prefix + len tokens, writes the new rows to the pages, gathers each request's rows
- * 0 .. prefix+len-1 through its block table into a library workspace and attends over that.  A
- * request with prefix > 0 must exist with at least prefix tokens reserved (else SPD_ENOENT /
- * SPD_EINVAL).
+ * prefix + len tokens, writes the new rows to the pages and attends over each request's rows
+ * 0 .. prefix+len-1 where they lie, through its block table.  A request with prefix > 0 must exist
+ * with at least prefix tokens reserved (else SPD_ENOENT / SPD_EINVAL).
  *
  * With `rope` non-NULL (GQA pools only; spd_rope_config is declared further down; paper, Evaluation
  * "Implementation based on DistServe": the RoPE kernel) q and k are the vectors BEFORE the rotary

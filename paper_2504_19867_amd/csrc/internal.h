@@ -68,7 +68,7 @@ struct TileDesc {
   int32_t sub;       // tile index inside the page
   int32_t t_begin;   // first token slot (0..15) touched
   int32_t t_end;     // one past the last token slot touched
-  int32_t pad[3];    // [0]: logical position of the tile's token slot 0 in its request; [1]: row of KvRows::k_all that t_begin maps to
+  int32_t pad[3];    // [0]: logical position of the tile's token slot 0 in its request
 };
 
 // A step's first kernel stores `seq`, the number of the phase's step before it, at `flag`: that step has finished.
@@ -119,7 +119,7 @@ struct PrefillWork {
   int32_t len;       // number of query rows of the request in this step
   int32_t q_tile;    // tile index inside those rows (tile height depends on the head grouping)
   int32_t head0;     // first query head of the workgroup's head group
-  int32_t kv_row0;   // first row of the request's keys / values in the K, V tensors the kernel reads
+  int32_t kv_row0;   // where the request's keys and values begin in what the kernel reads: its first unit in PrefillLists::units, or row of k, v
   int32_t q_off;     // position of query row 0 in the request = number of cached tokens before it
 };
 // What an item of a step with shared-out items visits (a list beside the items': the others, of more items, have nothing to stage for it).
@@ -133,7 +133,10 @@ struct PrefillMerge {
 };
 // floats that a part leaves: 8 waves x (32 rows x dv sums, reference and row sum of 32 rows)
 constexpr __host__ __device__ inline size_t prefill_part_floats(int dv) { return 8 * (size_t)(dv * 32 + 64); }
-// what launch_prefill reads on the device
+// What launch_prefill reads on the device.
+// A step with cached tokens has all its keys and values out of the pages, its own rows, written ahead, among them:
+// `units` holds for each request the numbers of its units (16 tokens of one head: K part, V part, consecutive in a page) for KV head 0,
+// in the order of the tokens; head g's are g * head_units further.
 struct PrefillLists {
   const PrefillWork* work;
   const int32_t* chain;
@@ -142,6 +145,9 @@ struct PrefillLists {
   const PrefillMerge* merge;
   int n_merge;
   float* parts;
+  const char* pages;           // null: k, v are dense rows
+  const int32_t* units;
+  int head_units;
 };
 
 // The entry point that allocates nothing keeps its device-side working memory in one static device
@@ -334,9 +340,6 @@ struct KvRows {
   bool interleaved = false;
   void* q = nullptr;                    // with rope_w: the tiles' query rows [rows, n_q_heads, dk], rotated in place
   int n_q_heads = 0;
-  const TileDesc* d_cached = nullptr;   // tiles of cached rows that go to k_all, v_all, as do the new rows (at TileDesc.pad[1])
-  int n_cached = 0;
-  void *k_all = nullptr, *v_all = nullptr;
 };
 bool kv_rows_supported(const PoolGeom& g);
 hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k, const void* v,
@@ -362,6 +365,7 @@ constexpr int MLA_THREADS = 256;
 constexpr int MLA_CHUNK_PAGES = MLA_THREADS - DECODE_ITEM_WORDS;
 // one workgroup per chain: workgroup b computes the items work[chain[b]] .. work[chain[b + 1] - 1].  two_groups: 192 / 128 dims only, as
 // two_groups_pay says
+// (k, v are not read where lists.pages is there)
 hipError_t launch_prefill(const void* q, const void* k, const void* v, void* out, const PrefillLists& lists, bool two_groups, int H, int Hkv, int dqk, int dv,
                           float scale, hipStream_t stream);
 // x [T, K], w_gu [2 I, K] (joint gate/up rows in blocks of 32 + 32), out [T, I], all bf16 in device memory;

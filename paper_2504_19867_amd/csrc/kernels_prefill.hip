@@ -4,8 +4,8 @@
 // context.  For request r, query head h (KV head g = h / (H / Hkv)), row i:
 //     out[i,h,:] = sum_{j<=i} softmax_j(scale * q[i,h,:] . k[j,g,:]) * v[j,g,:]
 // (The page write of K, V that belongs to the same step is kv_write_kernel.)
-// With a cached prefix of p tokens (chunked prefill) the request's K, V hold p + len rows and
-// query row i sits at position p + i: the sum runs over j <= p + i.
+// With a cached prefix of p tokens (chunked prefill) the request's K, V hold p + len rows, all of them in its
+// pages, and query row i sits at position p + i: the sum runs over j <= p + i.
 //
 // A dense contraction, so it runs on the matrix cores.  One workgroup = 8 waves = one CU's worth
 // of work; every wave owns 32 query rows of one head.  The 8 waves are HB query heads of ONE
@@ -31,6 +31,10 @@
 // are read back with 16-byte reads in A-operand order; V stays in its natural [key][dim] order
 // and the transposition that the second product needs is done by the LDS transpose read
 // ds_read_b64_tr_b16.  Both tiles are XOR-swizzled at 16-byte granularity against bank conflicts.
+// A step with cached tokens has its tiles out of the pages, four units of 16 tokens each, in the order in which the pages (laid
+// out for the decode kernel) have them, which is an operand order here too.  With the rows brought together in dense tensors first
+// (by the page write's launch, once through HBM and back) 4 pieces of 201 .. 1024 tokens behind up to 7680 cached ones of the
+// Llama-3-8B layer took 139 us on 256 CUs, now 128: the page write's launch 32 -> 17 us, this kernel 101 -> 103.
 //
 // The softmax keeps a reference per query that is moved to the running maximum only when a row sum
 // shows that it must be (an item's first tile, or scores that have outgrown it by 2^60).
@@ -62,14 +66,30 @@ __device__ inline void dma16s(const void* sbase, uint32_t voff, uint32_t lds_byt
 // s_waitcnt vmcnt(N) only (expcnt and lgkmcnt fields left at their maxima)
 #define SPD_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))
 
-// XOR swizzles (in units of 16-byte chunks) of a K row and a V row
+// XOR swizzles (in units of 16-byte chunks) of a dense K row and a dense V row
 template <int DQK> __device__ inline int k_swz(int row) { return DQK == 128 ? (row & 15) : ((row >> 1) & 7); }
 template <int DV> __device__ inline int v_swz(int row) { return DV == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 
-// PARTS: items may be parts of items (an instance of its own: the code for it costs the other steps up to 1 %)
-template <int DQK, int DV, int HB, bool PARTS>
+// Rows i .. i + 3 of a block of 32 rows of O^T into a staged row of the output, as out_pairs has them in bf16.  Out of pages row i is
+// dim i / 2 + 16 (i % 2).
+template <bool PAGED> __device__ inline uint2 out_pairs(float a, float b, float c, float d) {
+  return PAGED ? uint2{cvt_pk_bf16(a, c), cvt_pk_bf16(b, d)} : uint2{cvt_pk_bf16(a, b), cvt_pk_bf16(c, d)};
+}
+template <bool PAGED> __device__ inline void stage_out(char* row, int i, uint2 pairs) {
+  if constexpr (PAGED) {
+    *(uint32_t*)(row + i) = pairs.x;
+    *(uint32_t*)(row + i + 32) = pairs.y;
+  } else {
+    *(uint2*)(row + i * 2) = pairs;
+  }
+}
+
+// PARTS: items may be parts of items (an instance of its own: the code for it costs the other steps up to 1 %).
+// PAGED: K, V out of the pages (pages, units, head_units; see PrefillLists) instead of the dense rows k, v.
+template <int DQK, int DV, int HB, bool PARTS, bool PAGED>
 __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                         const bf16_t* __restrict__ v, bf16_t* __restrict__ out,
+                                                         const bf16_t* __restrict__ v, const char* __restrict__ pages,
+                                                         const int32_t* __restrict__ units, int head_units, bf16_t* __restrict__ out,
                                                          const PrefillWork* __restrict__ work,
                                                          const int32_t* __restrict__ chain, int H, int Hkv,
                                                          float c /* scale * log2(e) */, const PrefillRange* __restrict__ range, float* __restrict__ parts) {
@@ -85,6 +105,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   constexpr int NS = 2 * KS;                    // MFMAs of S^T
   constexpr int RING = DQK > 128 ? 4 : 8;       // K operands in flight (fewer where registers are short)
   static_assert(NS >= RING, "operand ring longer than the first product");
+  // a unit of 16 tokens as it lies in a page: K part, then V part
+  constexpr int UNIT_K = TILE_T * DQK * 2, UNIT_BYTES = UNIT_K + TILE_T * DV * 2, UNIT_LOADS = UNIT_BYTES / 1024;
   constexpr int OPITCH = 32 * 2 + 16;           // bytes per staged output row piece (32 dims, padded)
   constexpr int EPI_BYTES = WAVES * 32 * OPITCH;  // output staging, apart from the K/V stages
   __shared__ __attribute__((aligned(1024))) char smem[NSTAGE * STAGE_BYTES + EPI_BYTES];
@@ -93,17 +115,19 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n32 = lane & 31, hh = lane >> 5;
-  const uint32_t k_pitch = (uint32_t)Hkv * DQK * 2, v_pitch = (uint32_t)Hkv * DV * 2;
+  const uint32_t k_pitch = (uint32_t)Hkv * DQK * 2, v_pitch = (uint32_t)Hkv * DV * 2;   // (dense rows)
   const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
   // this workgroup's chain of work items
   int it = __builtin_amdgcn_readfirstlane(chain[blockIdx.x]);
   const int it_end = __builtin_amdgcn_readfirstlane(chain[blockIdx.x + 1]);
   if (it >= it_end) return;
 
-  // ---- tile loads.  Load instruction ii = wave + 8 j (j < LPW) fills the 64 consecutive 16-byte
-  // slots [64 ii, 64 ii + 64) of the stage: K slots first (row = slot / CHK), then V slots.
-  // Slot s of a row holds the row's chunk s ^ swz(row).
-  // The per-lane part of the address does not depend on the tile (except past the prompt's end).
+  // ---- tile loads.  Load instruction ii = wave + 8 j (j < LPW) fills 1 KiB of the stage.
+  // Paged: a stage is the tile's four units one after the other, each as it lies in its page, so an instruction reads 1 KiB of
+  // consecutive bytes, from an address that is the wave's but for the lane's 16 bytes.
+  // Dense rows (192 dims): the 64 consecutive 16-byte slots [64 ii, 64 ii + 64), K slots first (row = slot / CHK), then V slots;
+  // slot s of a row holds the row's chunk s ^ swz(row).  The per-lane part of the address does not depend on the tile
+  // (except past the prompt's end).
   auto slot_of = [&](int j, int& row, int& coff, uint32_t& pitch) __attribute__((always_inline)) {
     const int ii = wave + WAVES * j;
     if (ii < CHK) {
@@ -118,13 +142,17 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
       pitch = v_pitch;
     }
   };
-  uint32_t ld_voff[LPW];
+  uint32_t ld_voff[PAGED ? 1 : LPW];
+  if constexpr (PAGED) {
+    ld_voff[0] = (uint32_t)(wave % UNIT_LOADS * 1024 + lane * 16);
+  } else {
 #pragma unroll
-  for (int j = 0; j < LPW; ++j) {
-    int row, coff;
-    uint32_t pitch;
-    slot_of(j, row, coff, pitch);
-    ld_voff[j] = (uint32_t)row * pitch + (uint32_t)coff;
+    for (int j = 0; j < LPW; ++j) {
+      int row, coff;
+      uint32_t pitch;
+      slot_of(j, row, coff, pitch);
+      ld_voff[j] = (uint32_t)row * pitch + (uint32_t)coff;
+    }
   }
   // ---- the chain's work items, 64 at a time, one per lane: item i sits in lane i - dsc_base.  An item is then had
   // with six lane reads, where a load from memory at every item boundary (one by the producer, one by the
@@ -140,7 +168,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
     const PrefillWork pw = work[min(base + lane, it_end - 1)];
     d_row0 = pw.row0; d_len = pw.len; d_qtile = pw.q_tile; d_head0 = pw.head0; d_kvrow0 = pw.kv_row0; d_qoff = pw.q_off;
     if constexpr (PARTS) {
-      const PrefillRange pr = range[min(base + lane, it_end - 1)];
+      PrefillRange pr = {0, (pw.q_off + min(pw.len, (pw.q_tile + 1) * (32 * QS)) + BN - 1) / BN, -1};
+      if (range) pr = range[min(base + lane, it_end - 1)];
       d_kt0 = pr.kt0; d_kt1 = pr.kt1; d_part = pr.part;
     }
     dsc_base = base;
@@ -157,80 +186,118 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   // ring has three stages), across the items of the chain.
   // pt counts the tiles issued so far (tile number pt goes to stage pt % NSTAGE).
   int p_it = it, p_kt = 0, p_n = 0, p_kv_len = 0, pt = 0;
-  const char *p_kb = nullptr, *p_vb = nullptr;
+  const char *p_kb = nullptr, *p_vb = nullptr;  // dense rows
+  // Paged: the numbers of the units that the item's next tiles lie in, 64 of them, one per lane; tile p_kt's are in the lanes from p_win
+  // on.  They are had with one load per 16 tiles, which is not waited for before the next tile's loads go out.
+  const int32_t* p_units = nullptr;
+  int p_head = 0, p_win = 0, win = 0;
+  bool win_new = false;
+  auto load_window = [&]() __attribute__((always_inline)) {
+    win = p_units[min(4 * p_kt + lane, (p_kv_len - 1) / TILE_T)];   // (units past the last one: that one again)
+    p_win = 0;
+    win_new = true;
+  };
   auto producer_item = [&]() __attribute__((always_inline)) {                  // producer state for item p_it
     const PrefillWork pw = item_of(p_it);
     const int pg = pw.head0 / G;
     p_kv_len = pw.q_off + pw.len;
     p_n = PARTS ? __builtin_amdgcn_readlane(d_kt1, p_it - dsc_base) : (min(p_kv_len, pw.q_off + pw.q_tile * (32 * QS) + 32 * QS) + BN - 1) / BN;
-    p_kb = (const char*)(k + ((size_t)pw.kv_row0 * Hkv + pg) * DQK);
-    p_vb = (const char*)(v + ((size_t)pw.kv_row0 * Hkv + pg) * DV);
     p_kt = PARTS ? __builtin_amdgcn_readlane(d_kt0, p_it - dsc_base) : 0;
+    if constexpr (PAGED) {
+      p_units = units + pw.kv_row0;
+      p_head = pg * head_units;
+      load_window();
+    } else {
+      p_kb = (const char*)(k + ((size_t)pw.kv_row0 * Hkv + pg) * DQK);
+      p_vb = (const char*)(v + ((size_t)pw.kv_row0 * Hkv + pg) * DV);
+    }
   };
   producer_item();
   auto produce_one = [&]() __attribute__((always_inline)) {
     if (p_it >= it_end) return;
-    const int kv0 = p_kt * BN;
     const uint32_t stage = smem_base + (uint32_t)(pt % NSTAGE) * STAGE_BYTES;
-    const char* kb = p_kb + (size_t)kv0 * k_pitch;
-    const char* vb = p_vb + (size_t)kv0 * v_pitch;
-    if (kv0 + BN <= p_kv_len) {
+    if constexpr (PAGED) {
+      // A full wait: loads into LDS and loads into registers are not known to return in one order.  (Behind a pair's barrier there
+      // is nothing to wait for, and between a pair's tiles little.)
+      if (win_new) SPD_WAIT_VMCNT(0);
+      win_new = false;
 #pragma unroll
       for (int j = 0; j < LPW; ++j) {
-        const int ii = wave + WAVES * j;
-        dma16s(ii < CHK ? kb : vb, ld_voff[j], stage + (uint32_t)ii * 1024);
+        const int u = (wave + WAVES * j) / UNIT_LOADS;
+        const size_t unit = (size_t)(uint32_t)(__builtin_amdgcn_readlane(win, p_win + u) + p_head);
+        dma16s(pages + unit * UNIT_BYTES, ld_voff[0], stage + (uint32_t)(wave + WAVES * j) * 1024);
       }
-    } else {                                    // rows past the prompt re-read its last row
-      const int last = p_kv_len - 1 - kv0;
+    } else {
+      const int kv0 = p_kt * BN;
+      const char* kb = p_kb + (size_t)kv0 * k_pitch;
+      const char* vb = p_vb + (size_t)kv0 * v_pitch;
+      if (kv0 + BN <= p_kv_len) {
 #pragma unroll
-      for (int j = 0; j < LPW; ++j) {
-        const int ii = wave + WAVES * j;
-        int row, coff;
-        uint32_t pitch;
-        slot_of(j, row, coff, pitch);
-        dma16s(ii < CHK ? kb : vb, (uint32_t)min(row, last) * pitch + (uint32_t)coff, stage + (uint32_t)ii * 1024);
+        for (int j = 0; j < LPW; ++j) {
+          const int ii = wave + WAVES * j;
+          dma16s(ii < CHK ? kb : vb, ld_voff[j], stage + (uint32_t)ii * 1024);
+        }
+      } else {                                    // rows past the prompt re-read its last row
+        const int last = p_kv_len - 1 - kv0;
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) {
+          const int ii = wave + WAVES * j;
+          int row, coff;
+          uint32_t pitch;
+          slot_of(j, row, coff, pitch);
+          dma16s(ii < CHK ? kb : vb, (uint32_t)min(row, last) * pitch + (uint32_t)coff, stage + (uint32_t)ii * 1024);
+        }
       }
     }
     ++pt;
     if (++p_kt == p_n) {
       ++p_it;
       if (p_it < it_end) producer_item();
+    } else if (PAGED && (p_win += BN / TILE_T) == 64) {
+      load_window();
     }
   };
 
   // ---- LDS operand addresses (byte offsets inside a stage)
-  // K operand (S^T block b, k-step ks): row 32 b + n32, chunk 2 ks + hh
-  // (192 dims: the swizzle touches the low three bits of the chunk number only, so k-steps four apart differ by
-  // 128 bytes and share a lane address; that frees eight registers)
-  constexpr int KOFFS = DQK == 192 ? 4 : KS;
-  int k_off[KOFFS];
-#pragma unroll
-  for (int ks = 0; ks < KOFFS; ++ks) k_off[ks] = n32 * (CHK * 16) + (((2 * ks + hh) ^ k_swz<DQK>(n32)) * 16);
-  auto k_addr = [&](int ks) -> int { return k_off[ks % KOFFS] + (ks / KOFFS) * 128; };
-  // V operand (16-key step kk, value block blk): two transpose reads.  In each group of 16 lanes
-  // lane r supplies row (key) 4 hh + r / 4 and dims 4 (r % 4) .. + 3 of the group's 16 dims; the
-  // hardware hands lane i of the group dim i of those 4 keys.
-  const int r16 = lane & 15;
-  const int v_row = 4 * hh + (r16 >> 2);                         // plus 16 kk + 8 half
-  int v_off[VB];
-#pragma unroll
-  for (int blk = 0; blk < VB; ++blk) {
-    const int dim = 32 * blk + 16 * ((lane >> 4) & 1) + 4 * (r16 & 3);
-    v_off[blk] = K_BYTES + v_row * (CHV * 16) + (((dim >> 3) ^ v_swz<DV>(v_row)) * 16) + (dim & 7) * 2;
-  }
-
   // The tile loop is unrolled over the ring's stages so that the stage offset is part of each LDS
   // read's 16-bit immediate; stages 2 and 3 lie beyond its reach and get a second set of lane addresses.
   constexpr bool UNROLL = NSTAGE == 4 && 2 * STAGE_BYTES <= 65536;
   constexpr bool PAIRS = UNROLL;                // a ring of four holds the pair in use and the pair in flight
-  int k_off2[KS], v_off2[VB];
+  static_assert(UNROLL || !PAGED, "pages are read a pair of tiles at a time");
+  // K operand (S^T block b, k-step ks): row 32 b + n32, chunk 2 ks + hh.
+  // (192 dims: the swizzle touches the low three bits of the chunk number only, so k-steps four apart differ by
+  // 128 bytes and share a lane address; that frees eight registers)
+  // V operand (16-key step kk, value block blk): two halves, 4 keys each.  Two transpose reads: in each group of 16 lanes
+  // lane r supplies row (key) 4 hh + r / 4 and dims 4 (r % 4) .. + 3 of the group's 16 dims; the
+  // hardware hands lane i of the group dim i of those 4 keys.
+  // Out of pages both lie as the operands want them, chunk by chunk and in quads of tokens, and operands differ by constants: a lane
+  // address each.  K: the token's 16 bytes.  V: consecutive 8 bytes per lane, so that row i of a block of 32 is its dim i / 2 + 16 (i % 2)
+  // (with row i its dim i the reads have 2-way bank conflicts, 8 x 4096 tokens 9 % longer).  8-byte reads take the LDS twice as long as
+  // transpose reads do, and the whole kernel 2 to 6 % longer than over dense rows, which a step without cached tokens has anyway.
+  constexpr int KOFFS = PAGED ? 1 : DQK == 192 ? 4 : KS, VOFFS = PAGED ? 1 : VB;
+  int k_off[KOFFS], v_off[VOFFS];
+  if constexpr (PAGED) {
+    k_off[0] = (n32 >> 4) * UNIT_BYTES + hh * (TILE_T * 16) + (n32 & 15) * 16;
+    v_off[0] = UNIT_K + lane * 8;
+  } else {
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    k_off2[ks] = k_addr(ks) + 2 * STAGE_BYTES;
+    for (int ks = 0; ks < KOFFS; ++ks) k_off[ks] = n32 * (CHK * 16) + (((2 * ks + hh) ^ k_swz<DQK>(n32)) * 16);
+    const int r16 = lane & 15;
+    const int v_row = 4 * hh + (r16 >> 2);                       // plus 16 kk + 8 half
+#pragma unroll
+    for (int blk = 0; blk < VB; ++blk) {
+      const int dim = 32 * blk + 16 * ((lane >> 4) & 1) + 4 * (r16 & 3);
+      v_off[blk] = K_BYTES + v_row * (CHV * 16) + (((dim >> 3) ^ v_swz<DV>(v_row)) * 16) + (dim & 7) * 2;
+    }
+  }
+  int k_off2[KOFFS], v_off2[VOFFS];
+#pragma unroll
+  for (int ks = 0; ks < KOFFS; ++ks) {
+    k_off2[ks] = k_off[ks] + 2 * STAGE_BYTES;
     asm volatile("" : "+v"(k_off2[ks]));        // a value of its own, not "k_off + constant" to be recomputed
   }
 #pragma unroll
-  for (int blk = 0; blk < VB; ++blk) {
+  for (int blk = 0; blk < VOFFS; ++blk) {
     v_off2[blk] = v_off[blk] + 2 * STAGE_BYTES;
     asm volatile("" : "+v"(v_off2[blk]));
   }
@@ -273,7 +340,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
     qi = wave_q0 + n32;                         // this lane's query (row inside the request)
     const int qi_c = qi < w.len ? qi : w.len - 1;
     pos0 = w.q_off + wave_q0;                   // position of this wave's first query in the request
-    pos = w.q_off + qi;                         // ... of this lane's query
+    // ... of this lane's query.  Out of pages lanes past the last row do as that row does (the keys behind it may be anything, and
+    // one lane out of range moves the whole wave's references)
+    pos = w.q_off + (PAGED ? qi_c : qi);
     const bf16_t* qp = q + ((size_t)(w.row0 + qi_c) * H + h) * DQK + 8 * hh;
 #pragma unroll
     for (int s = 0; s < KS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *(const uint4*)(qp + 16 * s));
@@ -323,10 +392,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
       for (int blk = 0; blk < VB; ++blk) {
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
-          uint2 pk;
-          pk.x = cvt_pk_bf16(O[blk][4 * i4] * inv, O[blk][4 * i4 + 1] * inv);
-          pk.y = cvt_pk_bf16(O[blk][4 * i4 + 2] * inv, O[blk][4 * i4 + 3] * inv);
-          *(uint2*)(ost + n32 * OPITCH + (8 * i4 + 4 * hh) * 2) = pk;
+          const uint2 pk = out_pairs<PAGED>(O[blk][4 * i4] * inv, O[blk][4 * i4 + 1] * inv, O[blk][4 * i4 + 2] * inv, O[blk][4 * i4 + 3] * inv);
+          stage_out<PAGED>(ost + n32 * OPITCH, 8 * i4 + 4 * hh, pk);
         }
 #pragma unroll
         for (int itr = 0; itr < 2; ++itr) {       // 32 rows x 4 pieces of 16 bytes
@@ -370,13 +437,42 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
 
     const char* sbase = UNROLL ? smem + (ST & 1) * STAGE_BYTES : smem + ST * STAGE_BYTES;
     auto read_k = [&](int i) -> uint4 {
-      return *(const uint4*)(sbase + (UNROLL && ST >= 2 ? k_off2[i / 2] : k_addr(i / 2)) + (i % 2) * (32 * CHK * 16));
+      const int ks = i / 2, b = i % 2;
+      const int off = UNROLL && ST >= 2 ? k_off2[ks % KOFFS] : k_off[ks % KOFFS];
+      if constexpr (PAGED) return *(const uint4*)(sbase + off + 2 * b * UNIT_BYTES + ks * (2 * TILE_T * 16));
+      else return *(const uint4*)(sbase + off + (ks / KOFFS) * 128 + b * (32 * CHK * 16));
     };
     auto read_v = [&](int i, int half) -> s16x4 {
       const int kk = i / VB, blk = i % VB;
-      return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(
-          sbase + (UNROLL && ST >= 2 ? v_off2[blk] : v_off[blk]) + (16 * kk + 8 * half) * (CHV * 16)));
+      const int off = UNROLL && ST >= 2 ? v_off2[blk % VOFFS] : v_off[blk % VOFFS];
+      if constexpr (PAGED) return *(const s16x4*)(sbase + off + kk * UNIT_BYTES + blk * 1024 + half * 512);
+      else return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(sbase + off + (16 * kk + 8 * half) * (CHV * 16)));
     };
+    if constexpr (PAGED) {
+      // Behind the request's last token the pages hold anything; p is 0 there, and so must V be.  Every wave sees to it itself, all to
+      // the same effect, a lane for the 4 tokens of a dim that it reads itself.
+      const int n = w.q_off + w.len - kv0;
+      if (n < BN) {
+        for (int g = n / 8; g < BN / 8; ++g) {        // 8 tokens, the first 4 in the lower half of the lanes
+          char* p = smem + ST * STAGE_BYTES + v_off[0] + g / 2 * UNIT_BYTES + g % 2 * 512;
+          uint2 x[VB];
+          if (n > 8 * g) {
+            const int keep = n - 8 * g - 4 * hh;
+            const uint2 mask = {keep >= 2 ? ~0u : keep == 1 ? 0xffffu : 0u, keep >= 4 ? ~0u : keep == 3 ? 0xffffu : 0u};
+#pragma unroll
+            for (int blk = 0; blk < VB; ++blk) x[blk] = *(const uint2*)(p + blk * 1024);
+#pragma unroll
+            for (int blk = 0; blk < VB; ++blk) x[blk] = uint2{x[blk].x & mask.x, x[blk].y & mask.y};
+          } else {
+#pragma unroll
+            for (int blk = 0; blk < VB; ++blk) x[blk] = uint2{0u, 0u};
+          }
+#pragma unroll
+          for (int blk = 0; blk < VB; ++blk) *(uint2*)(p + blk * 1024) = x[blk];
+        }
+        asm volatile("" ::: "memory");
+      }
+    }
 
     // ---- S^T = K . Q^T.  Operand i: block b = i % 2 (32 keys), k-step ks = i / 2; LDS reads run
     // RING operands ahead of the MFMAs that consume them.
@@ -528,7 +624,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
 
 // Items whose keys were shared out over several workgroups: one wave per (item, wave of the item, 32 dims) adds the parts up,
 // each weighted with exp2((its reference - the largest one) c), and writes the rows as prefill_kernel does.
-template <int DV, int HB>
+template <int DV, int HB, bool PAGED>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(bf16_t* __restrict__ out, const PrefillMerge* __restrict__ items, const float* __restrict__ parts,
                                                             int H, float c) {
   constexpr int QS = WAVES / HB, VB = DV / 32, OPITCH = 32 * 2 + 16;
@@ -561,7 +657,7 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(bf16_t* __restrict__
   const float inv = 1.f / l;
 #pragma unroll
   for (int i4 = 0; i4 < 4; ++i4)
-    *(uint2*)(ost + n32 * OPITCH + (8 * i4 + 4 * hh) * 2) = uint2{cvt_pk_bf16(o[4 * i4] * inv, o[4 * i4 + 1] * inv), cvt_pk_bf16(o[4 * i4 + 2] * inv, o[4 * i4 + 3] * inv)};
+    stage_out<PAGED>(ost + n32 * OPITCH, 8 * i4 + 4 * hh, out_pairs<PAGED>(o[4 * i4] * inv, o[4 * i4 + 1] * inv, o[4 * i4 + 2] * inv, o[4 * i4 + 3] * inv));
   bf16_t* obase = out + ((size_t)(it.row0 + wave_q0) * H + it.head0 + wave % HB) * DV + 32 * blk;
 #pragma unroll
   for (int itr = 0; itr < 2; ++itr) {
@@ -983,18 +1079,29 @@ int prefill_heads_per_block(int group) {
 }
 int prefill_block_m(int group) { return 32 * (WAVES / prefill_heads_per_block(group)); }
 
+// (Steps with cached tokens: the instance that takes parts also where there are none.)
 template <int DQK, int DV, int HB>
 static void launch_items(dim3 grid, hipStream_t stream, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const PrefillLists& d, int H,
                          int Hkv, float c) {
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES), 0, stream, q, k, v, out, d.work, d.chain, H, Hkv, c, d.range, d.parts); };
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES), 0, stream, q, k, v, d.pages, d.units, d.head_units, out, d.work, d.chain, H, Hkv, c, d.range, d.parts);
+  };
+  auto merge = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(d.n_merge * WAVES * (DV / 32) / 4)), dim3(256), 0, stream, out, d.merge, d.parts, H, c);
+  };
   if constexpr (DQK <= 128) {
+    if (d.pages) {
+      launch(prefill_kernel<DQK, DV, HB, true, true>);
+      if (d.n_merge) merge(prefill_merge_kernel<DV, HB, true>);
+      return;
+    }
     if (d.n_merge) {
-      launch(prefill_kernel<DQK, DV, HB, true>);
-      hipLaunchKernelGGL((prefill_merge_kernel<DV, HB>), dim3((unsigned)(d.n_merge * WAVES * (DV / 32) / 4)), dim3(256), 0, stream, out, d.merge, d.parts, H, c);
+      launch(prefill_kernel<DQK, DV, HB, true, false>);
+      merge(prefill_merge_kernel<DV, HB, false>);
       return;
     }
   }
-  launch(prefill_kernel<DQK, DV, HB, false>);
+  launch(prefill_kernel<DQK, DV, HB, false, false>);
 }
 
 template <int DQK, int DV>

@@ -361,7 +361,7 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
   long heaviest = 0;
   for (int r = 0; r < n_req; ++r) {
     const int32_t row0 = cu_seqlens[r], len = cu_seqlens[r + 1] - row0;
-    const int32_t q_off = prefix_lens ? prefix_lens[r] : 0, kv_row0 = prefix_lens ? kv_cu[r] : row0;
+    const int32_t q_off = prefix_lens ? prefix_lens[r] : 0, kv_row0 = kv_cu ? kv_cu[r] : row0;
     const int tiles = (len + bm - 1) / bm;
     heaviest = std::max(heaviest, (long)((int64_t)q_off + len + 63) / 64 + ITEM_COST_TILES);
     for (int g = 0; g < Hkv; ++g) {

@@ -276,3 +276,34 @@ def test_decode_steps_beside_items_shared_out_on_the_same_compute_units(pre, dec
     want_d = np.stack([OA.decode_attention(f64(qd[i]), f64(ks[i]), f64(vs[i]), scale) for i in range(n_dec)])
     assert_parity(host_f64(out_d), want_d, "decode")
     gp.close()
+
+
+@pytest.mark.parametrize("H,Hkv,d,page,rope", [(8, 2, 128, 16, False), (16, 2, 128, 64, True), (4, 1, 64, 32, False), (6, 3, 64, 48, True)])
+def test_pieces_read_from_scattered_pages(H, Hkv, d, page, rope):
+    """Keys and values come out of the pages: pages of one and of several units of 16 tokens in no order, prefixes around the 1024 tokens whose units
+    a workgroup has at hand, ends in every part of a unit, and NaN behind them."""
+    reqs = ((1023, 1), (1024, 33), (1025, 64), (2050, 13), (0, 70), (15, 2), (64, 129))
+    layer = W.LayerShape("gqa", H, Hkv, d, d, page)
+    scale = 1.0 / math.sqrt(d)
+    lens = tuple(p + n for p, n in reqs)
+    q, k, v, cu = W.prefill_inputs(layer, lens, seed=29 + H)
+    gp = GpuPool(layer, sum(-(-n // page) for n in lens) + 70, poison=True)
+    for op, r, n in W.scramble_ops(60, page, seed=7):
+        (gp.pool.kv_reserve if op == "reserve" else lambda r, _: gp.pool.kv_free(r))(r, n)
+    for r, (p, _) in enumerate(reqs):
+        if p:
+            gp.pool.kv_reserve(1 + r, p)
+            gp.pool.kv_write(PRE, 1 + r, 0, p, dev_bf16(k[cu[r]:cu[r] + p]), dev_bf16(v[cu[r]:cu[r] + p]))
+    rows = np.concatenate([np.arange(cu[r] + p, cu[r + 1]) for r, (p, _) in enumerate(reqs)])
+    cu_step = np.concatenate([[0], np.cumsum([n for _, n in reqs])]).astype(np.int64)
+    tq, tk, tv = [dev_bf16(x[rows]) for x in (q, k, v)]
+    out = torch.empty((len(rows), H, d), dtype=torch.bfloat16, device=DEV)
+    cfg = S.rope_config(theta=10000.0, rotary_dim=d) if rope else None
+    gp.pool.prefill_step([1 + r for r in range(len(reqs))], cu_step, tq, tk, tv, out, H, Hkv, d, d, scale, prefix_lens=[p for p, _ in reqs], rope=cfg)
+    gp.ctx.phase_sync(PRE)
+    got, q_used, k_used = host_f64(out), host_f64(tq), host_f64(tk)      # (rotated in place with rope)
+    for r, (p, n) in enumerate(reqs):
+        a, b = cu_step[r], cu_step[r + 1]
+        keys = np.concatenate([f64(k[cu[r]:cu[r] + p]), k_used[a:b]])
+        assert_parity(got[a:b], OA.chunk_attention(q_used[a:b], keys, f64(v[cu[r]:cu[r + 1]]), scale), f"request {r}: {n} tokens behind {p}")
+    gp.close()
