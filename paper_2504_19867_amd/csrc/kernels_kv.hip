@@ -550,9 +550,21 @@ hipError_t launch_meta_copy(void* dst, const void* src, uint64_t bytes, const St
 
 bool kv_rows_supported(const PoolGeom& g) { return g.kind == SPD_KV_GQA && g.dk <= 128 && g.dv <= 128 && g.Hkv >= 2; }
 
+// KV heads per workgroup.  A workgroup takes its heads one after the other, in code that it runs once, so where there are compute units to
+// spare each head more in it is time: 0.9 us with rotation, 0.6 without.  Where there are not, more workgroups mean more reads of the
+// descriptors over the host link and, with rotation, the angles formed as often.  This launch in us, 8 KV heads of 128 dims (with rotation: 32
+// query heads), 8 / 4 / 2 / 1 heads per workgroup: 8 tiles on 128 CUs 8.9 / 5.5 / 4.8 / 4.3, with rotation 11.6 / 7.5 / 7.0 / 6.5; 32
+// tiles on 64 8.9 / 6.1 / 6.6 / 4.5 and 14.0 / 10.1 / 10.2 / 12.2; 64 on 64 8.5 / 6.5 / 5.9 / 6.5 and 17.0 / 16.6 / 17.0 / 20.5; 128 on
+// 128 9.9 / 7.8 / 7.1 / 7.0 and 16.5 / 16.5 / 17.7 / 21.3; 256 on 64 13.2 / 14.0 / 14.1 / 16.7 and 42.4 / 41.8 / 50.2 / 73.1.
+static int heads_per_workgroup(int n_tiles, int Hkv, int cus, bool rope) {
+  const int64_t wgs = (int64_t)n_tiles * ((Hkv + 7) / 8);     // with 8 heads in each
+  if (rope) return 2 * wgs <= cus ? 2 : wgs < cus ? 4 : 8;
+  return 2 * wgs <= cus ? 1 : wgs <= 2 * cus ? 2 : 8;
+}
+
 hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k, const void* v,
                           const KvRows& x, const StepMark& mark, hipStream_t stream) {
-  constexpr int HG = 8;
+  const int HG = heads_per_workgroup(n_tiles, g.Hkv, x.cus, x.rope_w != nullptr);
   RowsArgs a{};
   a.base = pool_base;
   a.page_bytes = g.page_bytes; a.head_bytes = g.head_bytes; a.tile_bytes = g.tile_bytes; a.tile_k_bytes = g.tile_k_bytes;
@@ -569,8 +581,16 @@ hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_
   const int64_t blocks = a.n_copy + (int64_t)n_tiles * a.groups + (int64_t)n_tiles * a.q_groups;
   if (blocks <= 0) return hipSuccess;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  if (x.rope_w) hipLaunchKernelGGL((kv_rows_kernel<HG, true>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL((kv_rows_kernel<HG, false>), dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  const dim3 grid((unsigned)blocks);
+  if (x.rope_w) {
+    if (HG == 8) hipLaunchKernelGGL((kv_rows_kernel<8, true>), grid, dim3(256), 0, stream, a);
+    else if (HG == 4) hipLaunchKernelGGL((kv_rows_kernel<4, true>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((kv_rows_kernel<2, true>), grid, dim3(256), 0, stream, a);
+  } else {
+    if (HG == 8) hipLaunchKernelGGL((kv_rows_kernel<8, false>), grid, dim3(256), 0, stream, a);
+    else if (HG == 2) hipLaunchKernelGGL((kv_rows_kernel<2, false>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((kv_rows_kernel<1, false>), grid, dim3(256), 0, stream, a);
+  }
   return hipGetLastError();
 }
 

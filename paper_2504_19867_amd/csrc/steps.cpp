@@ -293,6 +293,7 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   const TileDesc *d_desc = (const TileDesc*)(st->dev + off_desc);
   if (one_launch) {
     KvRows x;
+    x.cus = share;
     x.copy_dst = ws; x.copy_src = st->dev; x.copy_bytes = bytes;
     if (rc_) {
       x.rope_w = rope_w; x.rot = rc_->rotary_dim; x.off = rc_->rotary_offset; x.interleaved = rc_->interleaved != 0;
