@@ -83,15 +83,17 @@ inline void split_gqa(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64
   cut_chunks(ps, ctx_lens, B, max_units, std::min<int64_t>(c, (max_units + round - 1) / round * round), n_chunks, out);
 }
 
-constexpr int64_t CHUNK_COST = 20;
+// What a latent chunk costs beside its tiles, in tiles.  FP8 tiles take less time and the cost is the same: 128 requests of
+// 1024 .. 8192 tokens on 128 CUs 97.6 us with 20, 96.0 with 30 (bf16 148.8, 151.0; with 12 both are 2 to 3 us slower).
+constexpr int64_t CHUNK_COST = 20, CHUNK_COST_FP8 = 30;
 // Whole requests dealt to `slots` workgroups (B >= slots): true, with the batch so split, if none gets `worst` units or more and
 // no request has more than `most`.
-inline bool deal_whole(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t slots, int64_t most, int64_t worst, int32_t* n_chunks, DecodeSplit& out) {
+inline bool deal_whole(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t slots, int64_t most, int64_t worst, int32_t* n_chunks, DecodeSplit& out, int64_t cost) {
   std::vector<uint64_t>&by_length = ps.tmp_set, &loads = ps.tmp_heap;     // (units << 32 | request, counted from the end), (load << 32 | workgroup)
   by_length.clear();
   for (int r = 0; r < B; ++r) {
     const uint64_t units = (uint64_t)(((int64_t)ctx_lens[r] + TILE_T - 1) / TILE_T);
-    if ((int64_t)units > most || (int64_t)units + CHUNK_COST >= worst) return false;
+    if ((int64_t)units > most || (int64_t)units + cost >= worst) return false;
     by_length.push_back(units << 32 | (uint32_t)(B - 1 - r));
   }
   std::sort(by_length.begin(), by_length.end(), std::greater<uint64_t>());
@@ -102,7 +104,7 @@ inline bool deal_whole(spd_phase_state& ps, const int32_t* ctx_lens, int B, int6
   for (uint64_t k : by_length) {
     std::pop_heap(loads.begin(), loads.end(), std::greater<uint64_t>());
     owner.push_back((int32_t)(uint32_t)loads.back());
-    loads.back() += ((k >> 32) + CHUNK_COST) << 32;
+    loads.back() += ((k >> 32) + cost) << 32;
     if ((int64_t)(loads.back() >> 32) >= worst) return false;
     std::push_heap(loads.begin(), loads.end(), std::greater<uint64_t>());
   }
@@ -128,18 +130,18 @@ inline bool deal_whole(spd_phase_state& ps, const int32_t* ctx_lens, int B, int6
 // Latent decode: two workgroups per CU are resident, and the batch's units are dealt to them evenly, in request order, a
 // workgroup going on from one request's end to the next one's beginning.  (Chunks of one length, handed out longest first, left
 // a quarter of the slots idle at the end.)  A chunk costs its pipeline fill and its merge beside its tiles, about as
-// much as CHUNK_COST tiles; chunks are whole rounds of the four waves, except at a request's end.  `least`: deal a workgroup no
+// much as `cost` tiles; chunks are whole rounds of the four waves, except at a request's end.  `least`: deal a workgroup no
 // fewer units than this.
 inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, int64_t sum_units, int cus, int units_per_page, int override_units,
-                         int64_t least, int32_t* n_chunks, DecodeSplit& out) {
+                         int64_t least, int32_t* n_chunks, DecodeSplit& out, int64_t cost = CHUNK_COST) {
   constexpr int64_t ROUND = 4;
   const int64_t slots = std::max(1, 2 * cus), most = (int64_t)(MLA_CHUNK_PAGES - 1) * units_per_page / ROUND * ROUND;
   std::vector<DecodeItem>& items = ps.tmp_items;
   std::vector<int32_t>& owner = ps.tmp_sizes;                    // workgroup of each chunk
   // at least two tiles per wave
-  int64_t quota = CHUNK_COST + std::max(least, override_units > 0 ? override_units : std::max<int64_t>(2 * ROUND, (sum_units + B * CHUNK_COST) / slots));
+  int64_t quota = cost + std::max(least, override_units > 0 ? override_units : std::max<int64_t>(2 * ROUND, (sum_units + B * cost) / slots));
   for (;; quota += std::max<int64_t>(1, quota / 64)) {
-    const int64_t sliver = std::min<int64_t>((quota - CHUNK_COST) / 4, 4);
+    const int64_t sliver = std::min<int64_t>((quota - cost) / 4, 4);
     items.clear();
     owner.clear();
     int wg = 0;
@@ -151,16 +153,16 @@ inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, in
       int32_t u0 = 0, chunk = 0;
       while (u0 < units) {
         const int64_t left = units - u0;
-        if (room < quota && room - CHUNK_COST <= sliver && left > room - CHUNK_COST) { ++wg; room = quota; }   // too little room to start here
-        int64_t take = std::min<int64_t>(left, std::max<int64_t>(ROUND, (room - CHUNK_COST) / ROUND * ROUND));
+        if (room < quota && room - cost <= sliver && left > room - cost) { ++wg; room = quota; }   // too little room to start here
+        int64_t take = std::min<int64_t>(left, std::max<int64_t>(ROUND, (room - cost) / ROUND * ROUND));
         if (left > take && left - take <= sliver) take = left;                  // too little left to start elsewhere
         take = std::min(take, most);
         push_chunk(items, r, chunk++, ctx_lens[r], u0, (int32_t)take);
         owner.push_back(wg);
         out.chunk_units = std::max(out.chunk_units, (int32_t)take);
         u0 += (int32_t)take;
-        room -= CHUNK_COST + take;
-        if (room < CHUNK_COST + ROUND) { ++wg; room = quota; }
+        room -= cost + take;
+        if (room < cost + ROUND) { ++wg; room = quota; }
       }
       n_chunks[r] = chunk;
       out.max_chunks = std::max(out.max_chunks, (int)chunk);
@@ -176,10 +178,10 @@ inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, in
     int64_t load = 0, worst = 0;
     for (size_t i = 0; i < items.size(); ++i) {
       if (i > 0 && owner[i] != owner[i - 1]) load = 0;
-      load += CHUNK_COST + items[i].n_units;
+      load += cost + items[i].n_units;
       worst = std::max(worst, load);
     }
-    if (deal_whole(ps, ctx_lens, B, slots, most, worst, n_chunks, out)) return;
+    if (deal_whole(ps, ctx_lens, B, slots, most, worst, n_chunks, out, cost)) return;
   }
   // workgroup i starts with record i: first chunks to the front, the others behind them, linked
   const int n = (int)items.size();
@@ -199,13 +201,14 @@ inline void split_latent(spd_phase_state& ps, const int32_t* ctx_lens, int B, in
 // The same for the entry point that allocates nothing: where the even deal's records or partials would not fit, workgroups
 // are dealt more, in fewer and longer chunks, until they do (or until there is nothing left to lengthen).
 inline void split_latent_within_limits(spd_phase_state& ps, const int32_t* ctx_lens, int B, int H, int dv, int64_t sum_units, int max_pages, int cus,
-                                       int units_per_page, int override_units, bool append, size_t w_bytes, int32_t* n_chunks, DecodeSplit& out) {
+                                       int units_per_page, int override_units, bool append, size_t w_bytes, int32_t* n_chunks, DecodeSplit& out,
+                                       int64_t cost = CHUNK_COST) {
   for (int64_t least = 0;; least = out.dealt + out.dealt / 4) {
-    split_latent(ps, ctx_lens, B, sum_units, cus, units_per_page, override_units, least, n_chunks, out);
+    split_latent(ps, ctx_lens, B, sum_units, cus, units_per_page, override_units, least, n_chunks, out, cost);
     if (noalloc_metadata((int)ps.tmp_items.size(), B, max_pages, append, w_bytes) <= NOALLOC_STAGE_BYTES &&
         partial_o_bytes(B, H, out.max_chunks, dv) + partial_ml_bytes(B, H, out.max_chunks) <= NOALLOC_WS_BYTES)
       return;
-    if (out.dealt >= sum_units + B * CHUNK_COST) return;
+    if (out.dealt >= sum_units + B * cost) return;
   }
 }
 

@@ -16,7 +16,7 @@
 // score is computed twice, and the waves drift apart: while some wait for their tiles (one stage per wave, 18
 // KiB each, 147 KiB per compute unit), others compute.  A read-only loop of this shape takes 5.5 TB/s out of 128 compute
 // units (half as many waves with two stages each: 4.8).  128 requests of 1024 .. 8192 tokens on 128 compute units, whole step: 149
-// us, 4.7 TB/s (FP8 115 us); with a barrier-coupled ring of four stages, in which every wave computed the scores of all tokens, 169
+// us, 4.7 TB/s (FP8 96 us); with a barrier-coupled ring of four stages, in which every wave computed the scores of all tokens, 169
 // (242).
 // What a chunk costs beyond its tiles (record, queries, first tile: 9 us; merge of the waves: 6 us) is covered by the
 // other workgroup of the compute unit: as one workgroup of eight waves the same loop took 174 us at a batch of 128 requests
@@ -30,7 +30,13 @@
 // are.  Codes become bf16 on their way out of LDS (exact; two per instruction), the scales stay out of the
 // operands: one score accumulator per block of 128 dims, summed with the tokens' scales in fp32, and the softmax weights
 // multiplied with them per block.  ds_read_b64_tr_b8 hands a lane 8 rows of one dim: four tokens of a dim and the
-// same four of the dim 16 further on, the operands of two products.
+// same four of the dim 16 further on, the operands of two products.  An FP8 tile is 10.25 KiB and its conversions keep the vector
+// ALU as long as HBM its loads (the batch above without the in-loop loads 79 us, without the arithmetic 84), so the two have to run side by
+// side: a workgroup's LDS holds seven stages, which its tiles pass round in order, and a wave loads its next tile while it consumes
+// one, into the stage of the tile three before (the next wave's, which says in LDS when it has done with it; a wave only
+// ever waits for an earlier tile).  115 -> 96 us together with fewer rescalings of O (8 us of it).  Loads that bring a tile's codes apart from its
+// scales and rope entries, so that two stages per wave would fit, are pieces of 512 bytes across cache lines: 115 us without any
+// arithmetic.  Scores as FP8 products, the queries as sums of two codes: no conversions, but longer chains, 104 us.
 //
 // The launch is the whole step: it rotates the query heads (RoPE), and the wave that holds the request's last
 // tile rotates or quantises the new token's row, puts it into its page and into the tile in LDS.
@@ -61,7 +67,7 @@ constexpr int VB = DV / 16;           // 32 value blocks of 16 dims
 constexpr int HALF_PITCH = DV / 2 + 4;   // floats per (wave, head) of a half of O in the merge, padded
 constexpr int MERGE_BYTES = WAVES * 16 * HALF_PITCH * 4;
 template <bool FP8> constexpr int tile_bytes() { return FP8 ? TILE * FP8_ROW_BYTES : TILE * ROW_BYTES; }
-template <bool FP8> constexpr int loads() { return (tile_bytes<FP8>() + 1023) / 1024; }    // 1 KiB load instructions: 18, 11
+template <bool FP8> constexpr int loads() { return tile_bytes<FP8>() / 1024; }    // 1 KiB load instructions: 18, 10 (and one of 256 bytes)
 }  // namespace mla
 
 struct MlaArgs {
@@ -88,6 +94,10 @@ __device__ inline uint32_t mla_pack_bf16(float a, float b) {
 __device__ inline void mla_dma16s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_byte_addr), "v"(voff), "s"(sbase) : "memory");
 }
+// the same with 4 bytes per lane
+__device__ inline void mla_dma4s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2 nt" ::"s"(lds_byte_addr), "v"(voff), "s"(sbase) : "memory");
+}
 // max over the four 16-lane rows of a wave, on the vector ALU: the row swaps exchange odd rows of
 // the first register with even rows of the second (rows of 16, then of 32 lanes)
 __device__ inline float mla_max_over_rows(float x) {
@@ -111,13 +121,17 @@ template <bool HI> __device__ inline uint32_t mla_codes_to_bf16(uint32_t w) {
 template <bool FP8>
 __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs a) {
   using namespace mla;
-  constexpr int NL = loads<FP8>(), STAGE = NL * 1024, TB = tile_bytes<FP8>();
-  constexpr int SMEM = WAVES * STAGE > MERGE_BYTES ? WAVES * STAGE : MERGE_BYTES;
+  constexpr int NL = loads<FP8>(), TB = tile_bytes<FP8>(), STAGE = TB;
+  static_assert(TB == NL * 1024 + (FP8 ? 256 : 0), "whole load instructions");
+  constexpr int STAGES = FP8 ? 7 : WAVES;          // (as many as two workgroups' LDS holds)
+  constexpr int SMEM = STAGES * STAGE > MERGE_BYTES ? STAGES * STAGE : MERGE_BYTES;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
   __shared__ float sm_m[WAVES + 1][16], sm_l[WAVES][16];
   __shared__ float sm_cs[128], sm_sn[128];         // rotary_dim <= 256
   __shared__ int32_t sm_rec[64 * WAVES];           // header and page ids, a word per thread
-  __shared__ __attribute__((aligned(16))) char sm_new[ROW_BYTES];
+  __shared__ __attribute__((aligned(16))) char sm_new[FP8 ? FP8_ROW_BYTES : ROW_BYTES];
+  __shared__ uint4 sm_q[FP8 ? 2 : 1][64];          // FP8: the rope entries' query fragments (registers are full)
+  __shared__ int sm_done[WAVES];                   // FP8: tiles that a wave has finished with
   if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(a.mark);
   static_assert(DECODE_ITEM_WORDS + MLA_CHUNK_PAGES <= 64 * WAVES, "one thread per word of a record");
   const int words = a.item_stride >> 2;
@@ -133,6 +147,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   const bool has_word = tid < words;
   if (first && has_word) rec_word = ((const int32_t*)(a.items + (size_t)idx * a.item_stride))[tid];
   if (has_word) sm_rec[tid] = rec_word;
+  if (FP8 && tid < WAVES) sm_done[tid] = 0;
   __syncthreads();
   first = 0;
   const int b = __builtin_amdgcn_readfirstlane(sm_rec[0]), chunk = __builtin_amdgcn_readfirstlane(sm_rec[1]);
@@ -156,19 +171,19 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     const int slot = 64 * j + lane, row = slot / CH, sl = slot % CH;
     ld_off[j] = FP8 ? (uint32_t)lane * 16 : (uint32_t)(row * ROW_BYTES + ((sl ^ (row & 7)) * 16));
   }
-  const uint32_t stage_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + (uint32_t)wave * STAGE;
-  char* const stage = smem + wave * STAGE;
-  auto load_tile = [&](const char* src) __attribute__((always_inline)) {
+  const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  int at = wave;                                   // the tile's stage
+  auto load_tile = [&](const char* src, int to) __attribute__((always_inline)) {
+    const uint32_t stage_base = smem_base + (uint32_t)to * STAGE;
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       if constexpr (FP8) {
-        // the last instruction is a quarter full: its other lanes repeat the tile's last piece, into the stage's padding
-        const uint32_t off = j == NL - 1 ? (uint32_t)min(lane * 16, TB - 16 - j * 1024) : ld_off[0];
-        mla_dma16s(src + j * 1024, off, stage_base + (uint32_t)j * 1024);
+        mla_dma16s(src + j * 1024, ld_off[0], stage_base + (uint32_t)j * 1024);
       } else {
         mla_dma16s(src + (j / 9) * (8 * ROW_BYTES), ld_off[j % 9], stage_base + (uint32_t)j * 1024);
       }
     }
+    if constexpr (FP8) mla_dma4s(src + NL * 1024, ld_off[0] >> 2, stage_base + NL * 1024);
   };
 
   const bool interleaved = a.interleaved != 0;
@@ -176,14 +191,15 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   const bool appends = a.k_new != nullptr && tile0 + n_tiles == n_tiles_all;
   // (the first tile's loads go out behind the queries': loads return in order, and the queries are needed first)
   // absorbed-query fragments: B operand, column = head, dims 8 (4 s + c4) .. + 7 for k-step s
-  bf16x8 qf[KS];
+  constexpr int KR = FP8 ? KS - 2 : KS;            // fragments in registers
+  bf16x8 qf[KR];
   {
     const bf16_t* qrow = a.q + ((size_t)b * a.H + min(col, a.H - 1)) * DL;
     uint4 raw[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) raw[s] = *(const uint4*)(qrow + 8 * (4 * s + c4));
     __builtin_amdgcn_sched_barrier(0);
-    if (wave < n_tiles) load_tile(tile_addr(wave));
+    if (wave < n_tiles) load_tile(tile_addr(wave), wave);
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- rotation angles of the step's position; same arithmetic as the RoPE step
@@ -245,7 +261,8 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
         }
       }
       if (col >= a.H) piece = uint4{0, 0, 0, 0};
-      qf[s] = __builtin_bit_cast(bf16x8, piece);
+      if (s < KR) qf[s] = __builtin_bit_cast(bf16x8, piece);
+      else sm_q[s - KR][lane] = piece;             // (every wave writes, and reads, the same)
     }
   }
 
@@ -255,16 +272,17 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   const int f = (col >> 2) & 1;
   const int k_base = col * ROW_BYTES + ((c4 ^ (col & 3)) * 16);
   const int k_even = k_base + 64 * f, k_odd = k_base + 64 * (1 - f);
-  const int k8 = col * FP8_ROW_BYTES + 8 * c4, k8_rope = col * FP8_ROW_BYTES + 528 + 16 * c4;
+  // (FP8: with the stage's offset, moved on from tile to tile; a copy of each without it would not fit the registers)
+  int k8 = wave * STAGE + col * FP8_ROW_BYTES + 8 * c4, k8_rope = wave * STAGE + col * FP8_ROW_BYTES + 528 + 16 * c4;
   // value operand (16 dims of block blk).  bf16: in each 16-lane group, lane r supplies row 4 c4 + r / 4 and dims
   // 4 (r % 4) .. + 3; the transpose read hands lane i dim i of those 4 tokens.  FP8: lane r supplies row (token)
   // 4 c4 + (r / 2) % 4 and 8 dims of block 2 p + r / 8; lane i gets dim i of the 4 tokens of both blocks.
-  const int sc8 = 4 * c4 * FP8_ROW_BYTES + 512;     // FP8: the scales of token 4 c4 (+ i rows)
+  int sc8 = wave * STAGE + 4 * c4 * FP8_ROW_BYTES + 512;     // FP8: the scales of token 4 c4 (+ i rows)
   const int v_row = 4 * c4 + (col >> 2);
   int v_base[4];                                   // by blk & 3; add 128 * (blk / 4)
 #pragma unroll
   for (int b3 = 0; b3 < 4; ++b3) v_base[b3] = v_row * ROW_BYTES + (((2 * b3 + ((col & 3) >> 1)) ^ (v_row & 7)) * 16) + (col & 1) * 8;
-  const int v8 = (4 * c4 + ((col >> 1) & 3)) * FP8_ROW_BYTES + 16 * (col >> 3) + 8 * (col & 1);
+  int v8 = wave * STAGE + (4 * c4 + ((col >> 1) & 3)) * FP8_ROW_BYTES + 16 * (col >> 3) + 8 * (col & 1);
 
   f32x4 O[VB];
 #pragma unroll
@@ -277,7 +295,15 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   auto uniform = [](float x) -> float { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); };
 
   for (int t = wave; t < n_tiles; t += WAVES) {     // (a fixed share for each wave: the result does not depend on who is faster)
-    char* const next_src = t + WAVES < n_tiles ? tile_addr(t + WAVES) : nullptr;
+    char* const stage = smem + at * STAGE;
+    char* next_src = t + WAVES < n_tiles ? tile_addr(t + WAVES) : nullptr;
+    const int next_at = FP8 ? (at + WAVES < STAGES ? at + WAVES : at + WAVES - STAGES) : at;
+    // FP8: the next tile's stage is free when the tile three before this one, the next wave's, is finished with
+    auto stage_is_free = [&]() -> bool {
+      if (t < STAGES - WAVES) return true;
+      const int owner = (wave + WAVES - (STAGES - WAVES)) % WAVES;
+      return __builtin_amdgcn_readfirstlane(__hip_atomic_load(&sm_done[owner], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > (t - (STAGES - WAVES)) / WAVES;
+    };
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the tile has landed
     const int tok0 = (tile0 + t) * TILE;
     if (tok0 + TILE >= n) {                                      // the request's last tile
@@ -304,15 +330,15 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     if constexpr (FP8) {
       constexpr int AHEAD = 4;
       uint2 ring[AHEAD];
-      auto read_s = [&](int s) -> uint2 { return *(const uint2*)(stage + k8 + 32 * s); };
+      auto read_s = [&](int s) -> uint2 { return *(const uint2*)(smem + k8 + 32 * s); };
 #pragma unroll
       for (int s = 0; s < AHEAD; ++s) ring[s] = read_s(s);
-      const uint4 rope0 = *(const uint4*)(stage + k8_rope), rope1 = *(const uint4*)(stage + k8_rope + 64);
+      const uint4 rope0 = *(const uint4*)(smem + k8_rope), rope1 = *(const uint4*)(smem + k8_rope + 64);
       // a block's sum is multiplied by the tokens' scales while the next block's products run
       f32x4 acc[2], scale;
       S = f32x4{0.f, 0.f, 0.f, 0.f};
-      S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rope0), qf[16], S, 0, 0, 0);
-      S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rope1), qf[17], S, 0, 0, 0);
+      S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rope0), __builtin_bit_cast(bf16x8, sm_q[0][lane]), S, 0, 0, 0);
+      S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rope1), __builtin_bit_cast(bf16x8, sm_q[1][lane]), S, 0, 0, 0);
 #pragma unroll
       for (int sb = 0; sb <= 4; ++sb) {
         if (sb < 4) {
@@ -331,12 +357,10 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
         if (sb > 0) S += acc[(sb - 1) & 1] * scale;
         if (sb < 4) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) scale[i] = *(const float*)(stage + sc8 + i * FP8_ROW_BYTES + 4 * sb);
+          for (int i = 0; i < 4; ++i) scale[i] = *(const float*)(smem + sc8 + i * FP8_ROW_BYTES + 4 * sb);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sc[i] = *(const f32x4*)(stage + sc8 + i * FP8_ROW_BYTES);     // for the value product
     } else {
       constexpr int AHEAD = 4;
       uint4 ring[AHEAD];
@@ -355,12 +379,19 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
       }
       S = acc[0] + acc[1];
     }
+    if constexpr (FP8) {
+      asm volatile("" : "+v"(S));                  // (the compiler would put the products behind the branch)
+      if (next_src && stage_is_free()) {
+        load_tile(next_src, next_at);
+        next_src = nullptr;
+      }
+    }
     // the first value operands: in flight while the vector ALU does the softmax
     constexpr int VAH = FP8 ? 3 : 5, NVR = FP8 ? VB / 2 : VB;
     uint2 vring[VAH];
     auto read_v = [&](int r) -> uint2 {
       if constexpr (FP8)
-        return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2*)(stage + v8 + 32 * r)));
+        return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2*)(smem + v8 + 32 * r)));
       else
         return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
             (__attribute__((address_space(3))) s16x4*)(stage + v_base[r & 3] + 128 * (r >> 2))));
@@ -369,6 +400,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     for (int r = 0; r < VAH; ++r) vring[r] = read_v(r);
     __builtin_amdgcn_sched_barrier(0);
 
+    if constexpr (FP8) __builtin_amdgcn_s_setprio(2);
     // lane holds, for head col, tokens tok0 + 4 c4 + i
     if (tok0 + TILE > n) {
 #pragma unroll
@@ -378,12 +410,18 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3]));
     mx = mla_max_over_rows(mx);
     const float m_new = fmaxf(m, mx);
-    const float mc = m_new * a.c;
+    // O is rescaled only where some running maximum moved; with FP8, whose weights are rounded with their tokens' scales and are
+    // never exact, by more than 2^8 (in six tiles of ten one of 16 heads has a new maximum, and 128 multiplications)
+    const bool moves = __builtin_amdgcn_ballot_w64(FP8 ? (m_new - m) * a.c > 8.f : m_new > m) != 0;
+    const float m_ref = moves ? m_new : m;
+    const float mc = m_ref * a.c;
     float p[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(S[i] * a.c - mc);
     const float psum = (p[0] + p[1]) + (p[2] + p[3]);
     if constexpr (FP8) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sc[i] = *(const f32x4*)(smem + sc8 + i * FP8_ROW_BYTES);     // for the value product
       // (the reference stays near 1: relative to a scale at one end of fp32's range the others' would leave it at the other end)
       if (!have_ref) {
 #pragma unroll
@@ -400,7 +438,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     } else {
       pb[0] = uint2{mla_pack_bf16(p[0], p[1]), mla_pack_bf16(p[2], p[3])};
     }
-    if (__builtin_amdgcn_ballot_w64(m_new > m) != 0) {        // rescale only when some running maximum moved
+    if (moves) {
       const float alpha = __builtin_amdgcn_exp2f((m - m_new) * a.c);
       l *= alpha;
 #pragma unroll
@@ -409,6 +447,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     }
     l += psum;
 
+    if constexpr (FP8) __builtin_amdgcn_s_setprio(1);
     // ---- O^T += C^T . P^T
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -427,10 +466,20 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (next_src) {
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // every read of the stage has returned
-      load_tile(next_src);
+    if constexpr (FP8) __builtin_amdgcn_s_setprio(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // every read of the stage has returned
+    if constexpr (FP8) {
+      if (lane == 0) __hip_atomic_store(&sm_done[wave], t / WAVES + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (next_src)
+        while (!stage_is_free()) __builtin_amdgcn_s_sleep(1);
     }
+    if (next_src) load_tile(next_src, next_at);
+    if constexpr (FP8) {
+      const int by = (next_at - at) * STAGE;
+      k8 += by; k8_rope += by; sc8 += by; v8 += by;
+      asm volatile("" : "+v"(k8), "+v"(k8_rope), "+v"(sc8), "+v"(v8));
+    }
+    at = next_at;
   }
 
   // ---- merge the waves' (m, l, O)

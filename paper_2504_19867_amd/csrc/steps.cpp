@@ -393,11 +393,12 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   DecodeSplit sp;
   const size_t w_bytes = b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0;
   const int cut = ctx->env_decode_chunk_tiles;
+  const int64_t cost = g.kind == SPD_KV_MLA_LATENT_FP8 ? CHUNK_COST_FP8 : CHUNK_COST;
   if (!mla) split_gqa(ds, b->ctx_lens, B, sum_units, max_units, g.Hkv, share, cut, n_chunks.data(), sp);
-  else if (!noalloc) split_latent(ds, b->ctx_lens, B, sum_units, share, units_per_page, cut, 0, n_chunks.data(), sp);
+  else if (!noalloc) split_latent(ds, b->ctx_lens, B, sum_units, share, units_per_page, cut, 0, n_chunks.data(), sp, cost);
   else
     split_latent_within_limits(ds, b->ctx_lens, B, b->n_q_heads, g.dv, sum_units, max_pages, share, units_per_page, cut, append, w_bytes,
-                               n_chunks.data(), sp);
+                               n_chunks.data(), sp, cost);
   const std::vector<DecodeItem>& items = ds.tmp_items;
   const int n_items = (int)items.size(), max_chunks = sp.max_chunks;
   const DecodeRecords rec_layout = decode_records(sp, n_items, B, max_pages, units_per_page);

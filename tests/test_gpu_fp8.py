@@ -190,3 +190,36 @@ def test_decode_over_rows_of_very_different_magnitude(first, rest):
     # one bf16 rounding of the weights and one of the output: 2^-9 / sqrt(3) each, relative, and up to 2^-9 where one token rules
     assert np.isfinite(got).all() and np.linalg.norm(got - want) <= 2 ** -7 * np.linalg.norm(want), np.linalg.norm(got - want) / np.linalg.norm(want)
     gp.close()
+
+
+@pytest.mark.parametrize("rise", [0.0, 1.0, 8.0, -8.0])
+def test_decode_of_many_tiles_per_wave(rise):
+    """Contexts of 1 .. 43 tiles that a workgroup has whole (its four waves pass seven stages round, each loads its next tile while
+    it consumes one), with scores that rise or fall by `rise` nats per tile: O is rescaled when a maximum has moved far, by an
+    amount in between, or never."""
+    lens = [16 * t - r for t in range(1, 44) for r in ((0, 1) if t % 3 else (15,))][-64:]
+    gp = fp8_pool(pages=sum(-(-n // 64) for n in lens))
+    gp.ctx.set_partition(224, 32)                        # 64 workgroups of the decode phase: one per request
+    rng = np.random.default_rng(31)
+    scale = 1.0 / math.sqrt(192)
+    q = rng.standard_normal((len(lens), 16, 576)).astype(np.float32)
+    q[..., :512] *= 0.2
+    q[..., 512:] = 1.0
+    tq = W.to_bf16_bits(q)
+    deqs = []
+    for i, n in enumerate(lens):
+        c = rng.standard_normal((n, 576)).astype(np.float32)
+        c[:, 512:] = (0.2 * c[:, 512:] + (rise / (64 * scale) * (np.arange(n) // 16))[:, None])
+        bits = W.to_bf16_bits(c)
+        gp.pool.kv_reserve(100 + i, n)
+        gp.pool.kv_write(DEC, 100 + i, 0, n, dev_bf16(bits))
+        deqs.append(oracle_rows(bits)[1])
+    out = torch.full((len(lens), 16, 512), float("nan"), dtype=torch.bfloat16, device=DEV)
+    gp.pool.decode_step([100 + i for i in range(len(lens))], lens, dev_bf16(tq), out, 16, scale)
+    gp.ctx.phase_sync(DEC)
+    got = host_f64(out)
+    for i, n in enumerate(lens):
+        want = OA.mla_decode_latent(f64(tq[i]), deqs[i], scale, 512)
+        # bf16 weights (2^-9 each, relative) over values of up to 5, and the output's own rounding
+        assert_parity(got[i], want, f"n={n} rise={rise}")
+    gp.close()
