@@ -100,7 +100,8 @@ struct DecodeLaunch {
   const void *q, *k_new, *v_new;      // k_new: null without append
   void* out;
   const char* items;                  // n_items records of item_stride bytes
-  const int32_t* n_chunks;            // [B]
+  const int32_t* n_chunks;            // [B], for the merge launch
+  int32_t* put_chunks;                // where the attention launch puts them, for a merge launch that would find them in pinned memory; or null
   const double* w;                    // rot / 2 frequencies
   int item_stride, n_wgs, B, H;       // n_wgs: workgroups (GQA: per KV head), each starts with the record of its number
   float scale;

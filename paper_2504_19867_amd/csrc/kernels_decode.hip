@@ -183,6 +183,7 @@ struct GqaArgs {
   const double* w;
   int rot, off, interleaved;
   float *ws_o, *ws_ml;
+  int32_t* put_chunks;
   uint32_t* counters;
   StepMark mark;
 };
@@ -216,6 +217,7 @@ __global__ __launch_bounds__(256, 2) void decode_gqa_kernel(GqaArgs a) {
   __syncthreads();
   const int b = __builtin_amdgcn_readfirstlane(sm_rec[0]), chunk = __builtin_amdgcn_readfirstlane(sm_rec[1]);
   const int n_chunks = __builtin_amdgcn_readfirstlane(sm_rec[2]), n = __builtin_amdgcn_readfirstlane(sm_rec[3]);
+  if (a.put_chunks && chunk == 0 && g == 0 && threadIdx.x == 0) a.put_chunks[b] = n_chunks;
   auto page_id = [&](int i) -> int {               // i-th page of the chunk
     const int wd = min(i + DECODE_ITEM_WORDS, words - 1);
     int id = sm_rec[min(wd, 255)];
@@ -469,7 +471,7 @@ static GqaArgs gqa_args(const PoolGeom& g, char* pool_base, const DecodeLaunch& 
   a.c = d.scale * 1.4426950408889634f;
   a.max_chunks = d.max_chunks;
   a.w = d.w; a.rot = d.rot; a.off = d.off; a.interleaved = d.interleaved;
-  a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.counters = d.counters; a.mark = d.mark;
+  a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.put_chunks = d.put_chunks; a.counters = d.counters; a.mark = d.mark;
   return a;
 }
 

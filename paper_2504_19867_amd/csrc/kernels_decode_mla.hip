@@ -83,6 +83,7 @@ struct MlaArgs {
   const double* w;
   int rot, off, interleaved;
   float *ws_o, *ws_ml;
+  int32_t* put_chunks;
   StepMark mark;
 };
 
@@ -152,6 +153,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   first = 0;
   const int b = __builtin_amdgcn_readfirstlane(sm_rec[0]), chunk = __builtin_amdgcn_readfirstlane(sm_rec[1]);
   const int n_chunks = __builtin_amdgcn_readfirstlane(sm_rec[2]), n = __builtin_amdgcn_readfirstlane(sm_rec[3]);
+  if (a.put_chunks && chunk == 0 && tid == 0) a.put_chunks[b] = n_chunks;
   const int tile0 = __builtin_amdgcn_readfirstlane(sm_rec[4]), n_tiles = __builtin_amdgcn_readfirstlane(sm_rec[5]);
   const int n_tiles_all = (n + TILE - 1) / TILE;
   const int page0 = tile0 / a.tiles_per_page;
@@ -545,7 +547,7 @@ hipError_t launch_decode_mla(const PoolGeom& g, char* pool_base, const DecodeLau
   a.c = d.scale * 1.4426950408889634f;
   a.max_chunks = d.max_chunks;
   a.w = d.w; a.rot = d.rot; a.off = d.off; a.interleaved = d.interleaved;
-  a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.mark = d.mark;
+  a.ws_o = d.ws_o; a.ws_ml = d.ws_ml; a.put_chunks = d.put_chunks; a.mark = d.mark;
   const dim3 grid((unsigned)d.n_wgs), block(64 * mla::WAVES);
   if (g.kind == SPD_KV_MLA_LATENT_FP8) hipLaunchKernelGGL(decode_mla_kernel<true>, grid, block, 0, stream, a);
   else hipLaunchKernelGGL(decode_mla_kernel<false>, grid, block, 0, stream, a);

@@ -431,7 +431,9 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
     prepare = false;
     ws_q_bytes = 0;
   }
-  const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + ws_q_bytes + (twin && !noalloc ? bytes : 0);
+  // A merge launch reads the requests' chunk counts first of all: out of device memory, where the records have them in pinned memory.
+  const bool put_chunks = !twin && !inline_merge && max_chunks > 1;
+  const size_t ws_bytes = ws_o_bytes + ws_ml_bytes + ws_q_bytes + (noalloc ? 0 : twin ? bytes : put_chunks ? sizeof(int32_t) * (size_t)B : 0);
   if (noalloc) {
     if (ws_bytes > NOALLOC_WS_BYTES) return SPD_ETOOBIG;
     ws = ctx->scratch + NOALLOC_TWIN_BYTES;
@@ -494,6 +496,11 @@ static int decode_step_impl(spd_ctx* ctx, spd_pool* pool, const spd_decode_batch
   d.ws_o = (float*)ws; d.ws_ml = (float*)(ws + ws_o_bytes);
   d.counters = inline_merge ? ds.merge_counters : nullptr;
   d.mark = mark;
+  if (put_chunks) {
+    static_assert(NOALLOC_STAGE_BYTES <= NOALLOC_TWIN_BYTES, "room for a count per request");
+    d.put_chunks = (int32_t*)(noalloc ? ctx->scratch : ws + ws_o_bytes + ws_ml_bytes + ws_q_bytes);
+    d.n_chunks = d.put_chunks;
+  }
   if (twin) {
     char* q_rot = ws + ws_o_bytes + ws_ml_bytes;
     char* to = noalloc ? ctx->scratch : q_rot + ws_q_bytes;
