@@ -482,39 +482,45 @@ typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2))); 
 // one stage ahead: one barrier per 8 slices.
 // The product is taken transposed (weights are the A operand): a lane then has four consecutive outputs of one token.
 // <NB, 8, 8>: 256 joint rows per workgroup, 128 KiB of weights on the way per CU; <NB, 4, 16>: 128 rows, the same bytes on the
-// way from four waves; five to seven waves where those fill the share's compute units better (launch_stream).  With the weights staged
+// way from four waves; five to seven waves where those fill the share's compute units better (launch_stream).  <NB, 6, 8, 2>, <NB, 4, 16, 2>:
+// 96 or 64 rows, two waves with half of the slices each, which add up at the end, where the wider ones leave compute units idle.  With the weights staged
 // through LDS (at most 96 KiB on the way, a third to a fifth of the stages taken by x, a barrier per slice) 64 tokens of hidden 4096, inter
 // 14336 took 68 us on 128 CUs and 48 on 256; now 54.8 and 42.7 us (4.3 and 5.5 TB/s) with the weights from HBM, copies of them cycled, and
 // 52.8 on 128 CUs from one copy, most of which the memory-side cache then holds.  With eight waves a ring of 16 slices was slower (56 us
 // instead of 55; 75 against 62 at 128 tokens), and so were loads without the non-temporal mark (61 us).
-template <int NB, int WAVES, int RING>
+template <int NB, int WAVES, int RING, int SPLIT = 1>
 __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w,
                                                                            bf16_t* __restrict__ out, int T, int K, int I, StepMark mark) {
   if (blockIdx.x == 0 && threadIdx.x == 0) store_mark(mark);
-  constexpr int XS = 8;                           // slices per x stage
+  constexpr int UNITS = WAVES / SPLIT;            // waves w, w + UNITS, .. share a unit's rows, each with its part of the slices
+  static_assert(WAVES % SPLIT == 0 && SPLIT <= 2, "the tail is one round");
+  constexpr int XS = SPLIT * NB > 8 ? 4 : 8;      // slices per x stage
   constexpr int ROWS = 16 * NB, CHUNKS = 4 * XS;  // 16-byte chunks of a row per stage
   constexpr int PITCH = (ROWS + 1) * 16;          // bytes per chunk column [chunk][row]: the odd row spreads the writes over the banks
-  constexpr int PIECES = ROWS * CHUNKS, XL = (PIECES + 64 * WAVES - 1) / (64 * WAVES);   // 16-byte pieces of a stage, per thread
+  constexpr int PIECES = ROWS * CHUNKS * SPLIT, XL = (PIECES + 64 * WAVES - 1) / (64 * WAVES);   // 16-byte pieces of a stage, per thread
+  constexpr int STAGE = SPLIT * CHUNKS * PITCH;
   static_assert(RING % XS == 0, "whole stages per ring");
-  __shared__ __attribute__((aligned(1024))) char smem[2 * CHUNKS * PITCH];
+  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n16 = lane & 15, c4 = lane >> 4;
   const int n_slices = K / BK, last = n_slices - 1;
+  const int part = SPLIT > 1 ? wave / UNITS : 0, per_part = (n_slices + SPLIT - 1) / SPLIT, first = part * per_part, mine = min(per_part, n_slices - first);
   // this wave's rows: half `hf` of joint block `jb` (64 rows)
   // (where the waves of the last workgroup are more than there are rows left, the rest of them repeat the last rows and store nothing)
-  const int n_units = I / 16, u = min((int)blockIdx.x * WAVES + wave, n_units - 1), jb = u >> 1, hf = u & 1;
+  const int n_units = I / 16, unit = (int)blockIdx.x * UNITS + (SPLIT > 1 ? wave % UNITS : wave), u = min(unit, n_units - 1), jb = u >> 1, hf = u & 1;
   const char* wb = (const char*)w + (size_t)(jb >> 2) * n_slices * 16384 + (size_t)((jb & 3) * 64 + hf * 16) * 64;
   const uint32_t w_off = (uint32_t)(n16 * 64 + ((c4 ^ ((n16 >> 2) & 3)) * 16));
   auto load_w = [&](int s, int half) __attribute__((always_inline)) -> u32x4 {   // half 0: gate, 1: up rows of slice s
-    return __builtin_nontemporal_load((const u32x4*)(wb + (size_t)min(s, last) * 16384 + half * 2048 + w_off));
+    return __builtin_nontemporal_load((const u32x4*)(wb + (size_t)min(first + s, last) * 16384 + half * 2048 + w_off));
   };
-  // x pieces: piece i of a stage is chunk i % CHUNKS of row i / CHUNKS; rows past T re-read row T - 1, entries past K the row's last ones
+  // x pieces: piece i of a part's stage is chunk i % CHUNKS of row i / CHUNKS; rows past T re-read row T - 1, entries past K the row's last ones
   u32x4 xr[XL];
   auto load_x = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < XL; ++j) {
-      const int i = tid + 64 * WAVES * j, row = min(i / CHUNKS, T - 1), ch = min(st * CHUNKS + i % CHUNKS, K / 8 - 1);
+      const int i = tid + 64 * WAVES * j, of = SPLIT > 1 ? min(i / (ROWS * CHUNKS), SPLIT - 1) : 0;
+      const int row = min(i / CHUNKS - of * ROWS, T - 1), ch = min(of * per_part * (BK / 8) + st * CHUNKS + i % CHUNKS, K / 8 - 1);
       xr[j] = *(const u32x4*)((const char*)x + (size_t)row * K * 2 + (size_t)ch * 16);
     }
   };
@@ -522,7 +528,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const
 #pragma unroll
     for (int j = 0; j < XL; ++j) {
       const int i = tid + 64 * WAVES * j;
-      if (PIECES % (64 * WAVES) == 0 || i < PIECES) *(u32x4*)(smem + buf * (CHUNKS * PITCH) + (i % CHUNKS) * PITCH + (i / CHUNKS) * 16) = xr[j];
+      const int of = SPLIT > 1 ? i / (ROWS * CHUNKS) : 0;
+      if (PIECES % (64 * WAVES) == 0 || i < PIECES)
+        *(u32x4*)(smem + buf * STAGE + (of * CHUNKS + i % CHUNKS) * PITCH + (i / CHUNKS - of * ROWS) * 16) = xr[j];
     }
   };
   f32x4 acc[2][NB];
@@ -542,7 +550,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const
     wr[s][1] = load_w(s, 1);
   }
   int buf = 0;
-  const int x_off = c4 * PITCH + n16 * 16;
+  const int x_off = (part * CHUNKS + c4) * PITCH + n16 * 16;
   bf16x8 xv[2][NB];
   auto read_x = [&](bf16x8* o, const char* xs) __attribute__((always_inline)) {
 #pragma unroll
@@ -561,11 +569,11 @@ __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const
         __builtin_amdgcn_sched_barrier(0);
       }
       // the stage's x operands are read a slice ahead of the MFMAs
-      const char* xs = smem + buf * (CHUNKS * PITCH) + x_off;
+      const char* xs = smem + buf * STAGE + x_off;
       if (r % XS == 0) read_x(xv[0], xs);
       if (r % XS + 1 < XS) read_x(xv[(r + 1) & 1], xs + (r % XS + 1) * (4 * PITCH));
       __builtin_amdgcn_sched_barrier(0);
-      if (!tail || s0 + r < n_slices) {
+      if (!tail || s0 + r < mine) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
           acc[0][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[r][0]), xv[r & 1][b], acc[0][b], 0, 0, 0);
@@ -581,8 +589,22 @@ __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const
     }
   };
   int s0 = 0;
-  for (; s0 + RING <= n_slices; s0 += RING) round(s0, std::false_type{});
-  if (s0 < n_slices) round(s0, std::true_type{});
+  const int whole = n_slices - (SPLIT - 1) * per_part;            // slices that every part has: at most one less than some
+  for (; s0 + RING <= whole; s0 += RING) round(s0, std::false_type{});
+  if (s0 < per_part) round(s0, std::true_type{});
+  if constexpr (SPLIT > 1) {                      // the second part's sums, through LDS, to the first
+    static_assert(UNITS * 2 * NB * 1024 <= 2 * STAGE, "room for the sums");
+    __syncthreads();
+    f32x4* const sums = (f32x4*)smem + wave % UNITS * (2 * NB * 64) + lane;
+    if (part == 1) {
+#pragma unroll
+      for (int i = 0; i < 2 * NB; ++i) sums[64 * i] = acc[i / NB][i % NB];
+    }
+    __syncthreads();
+    if (part == 1) return;
+#pragma unroll
+    for (int i = 0; i < 2 * NB; ++i) acc[i / NB][i % NB] += sums[64 * i];
+  }
   // element i of lane (n16, c4) is output 4 c4 + i of token n16 of its block
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
@@ -593,7 +615,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void ffn_gate_up_stream_kernel(const
       const float g = acc[0][b][i];
       y[i] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * acc[1][b][i];
     }
-    if (t < T && (int)blockIdx.x * WAVES + wave < n_units)
+    if (t < T && unit < n_units)
       *(u32x2_any*)(out + (size_t)t * I + 32 * jb + 16 * hf + 4 * c4) = u32x2_any{cvt_bf16(y[0]) | cvt_bf16(y[1]) << 16, cvt_bf16(y[2]) | cvt_bf16(y[3]) << 16};
   }
 }
@@ -633,9 +655,9 @@ static hipError_t launch_tiles(Kernel kernel, const void* x, const void* w_gu, v
 
 template <int NB>
 static hipError_t launch_stream(const void* x, const void* w_gu, void* out, int T, int K, int I, int cus, const StepMark& mark, hipStream_t stream) {
-  const int units = I / 16;                       // rows that one wave takes
-  auto launch = [&](auto kernel, int waves) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((units + waves - 1) / waves)), dim3((unsigned)(64 * waves)), 0, stream, (const bf16_t*)x, (const bf16_t*)w_gu,
+  const int units = I / 16;                       // of 16 gate and 16 up rows, a wave's
+  auto launch = [&](auto kernel, int waves, int per_wg) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((units + per_wg - 1) / per_wg)), dim3((unsigned)(64 * waves)), 0, stream, (const bf16_t*)x, (const bf16_t*)w_gu,
                        (bf16_t*)out, T, K, I, mark);
   };
   // A compute unit runs one workgroup at a time, and one of few waves takes longer per wave (few loads on the way): 64 tokens of hidden
@@ -643,24 +665,29 @@ static hipError_t launch_stream(const void* x, const void* w_gu, void* out, int 
   // four (the x pieces of other counts do not fit their registers: 78 .. 86).  So the number of rounds decides.  64 tokens of
   // inter 14336 (896 units), eight waves / the ones taken: 64 CUs 102 / 98 (7), 96 101 / 77 (5), 128 57 / 55.6 (7), 160 57 / 50 (6), 192 57 / 45.5
   // (5), 256 57 / 43 (4); with only eight and four to choose from the first five took eight.
-  static const int cost[] = {NB <= 4 ? 68 : 71, 77, 87, 96, 100};   // of a workgroup of 4 .. 8 waves
-  int waves = 8;
+  // Three or two units, each with two waves that halve the slices: for shares with more compute units than four units leave
+  // workgroups.  Hidden 8192, inter 7168 (448 units), 64 tokens, four units / the ones taken: 160 and 192 CUs 58 / 51 us (3), 256 58 / 42 (2); 1 token
+  // 46 / 40, 46 / 37; 128 tokens on 256 CUs 73 / 57 (2).  Where they take more rounds they lose (128 CUs, 64 tokens: 58 / 93, 70).
+  static const int cost[] = {NB <= 4 ? 52 : 57, 60, NB <= 4 ? 68 : 71, 77, 87, 96, 100};   // of a workgroup of 2 .. 8 units
+  int per_wg = 8;
   long least = 0;
-  for (int n = 8; n >= 4; --n) {
-    if (NB > 4 && n != 8 && n != 4) continue;
-    const long wgs = (units + n - 1) / n, t = ((wgs + cus - 1) / cus) * cost[n - 4];
+  for (int n = 8; n >= 2; --n) {
+    if (NB > 4 && n != 8 && n != 4 && n != 2) continue;
+    const long wgs = (units + n - 1) / n, t = ((wgs + cus - 1) / cus) * cost[n - 2];
     if (n == 8 || t < least) {
       least = t;
-      waves = n;
+      per_wg = n;
     }
   }
   if constexpr (NB <= 4) {
-    if (waves == 7) launch(ffn_gate_up_stream_kernel<NB, 7, 8>, 7);
-    if (waves == 6) launch(ffn_gate_up_stream_kernel<NB, 6, 8>, 6);
-    if (waves == 5) launch(ffn_gate_up_stream_kernel<NB, 5, 8>, 5);
+    if (per_wg == 7) launch(ffn_gate_up_stream_kernel<NB, 7, 8>, 7, 7);
+    if (per_wg == 6) launch(ffn_gate_up_stream_kernel<NB, 6, 8>, 6, 6);
+    if (per_wg == 5) launch(ffn_gate_up_stream_kernel<NB, 5, 8>, 5, 5);
+    if (per_wg == 3) launch(ffn_gate_up_stream_kernel<NB, 6, 8, 2>, 6, 3);
   }
-  if (waves == 8) launch(ffn_gate_up_stream_kernel<NB, 8, 8>, 8);
-  if (waves == 4) launch(ffn_gate_up_stream_kernel<NB, 4, 16>, 4);
+  if (per_wg == 8) launch(ffn_gate_up_stream_kernel<NB, 8, 8>, 8, 8);
+  if (per_wg == 4) launch(ffn_gate_up_stream_kernel<NB, 4, 16>, 4, 4);
+  if (per_wg == 2) launch(ffn_gate_up_stream_kernel<NB, 4, 16, 2>, 4, 2);
   return hipGetLastError();
 }
 

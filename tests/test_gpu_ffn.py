@@ -101,6 +101,27 @@ def test_gate_up_streamed_weights_by_five_to_seven_waves(T, K, I, cus, waves):
     ctx.close()
 
 
+@pytest.mark.parametrize("T", [1, 16, 33, 64, 65, 128])
+@pytest.mark.parametrize("K", [32, 64, 288, 992, 1024, 1056, 2080])
+@pytest.mark.parametrize("I", [896, 1408])
+def test_gate_up_streamed_weights_in_two_parts(T, K, I):
+    """Shares of more compute units than workgroups of four units would be (32 for 56 and 88 units): workgroups of two or, up to 64
+    tokens, three units whose slices two waves share: one slice (nothing for the second wave), parts of equal and of unequal length below,
+    at and beyond a ring (1, 4 | 5, 15 | 16, 16, 17 | 16, 33 | 32 slices), spare waves of the last workgroup (88 = 29 x 3 + 1)."""
+    ctx = S.Context(0)
+    ctx.set_partition(ctx.device_info()[0] - 32, 32)
+    xb, wgb, wub = W.ffn_inputs(T, K, I, seed=3300 + T + I)
+    x, wg, wu = dev_bf16(xb), dev_bf16(wgb), dev_bf16(wub)
+    w_gu = torch.empty((2 * I, K), dtype=torch.bfloat16, device=DEV)
+    out = torch.full((T + 2, I), 7.0, dtype=torch.bfloat16, device=DEV)
+    ctx.ffn_pack_gate_up(DEC, wg, wu, w_gu, K, I)
+    ctx.ffn_gate_up(DEC, x, w_gu, out, T, K, I)
+    ctx.phase_sync(DEC)
+    assert (out[T:] == 7.0).all()
+    _assert_ffn(host_f64(out[:T]), F.gate_up(f64(xb), f64(wgb), f64(wub)), f"ffn in two parts, T={T} K={K} I={I}")
+    ctx.close()
+
+
 @pytest.mark.parametrize("K", [32, 64, 96, 128, 160, 512])
 @pytest.mark.parametrize("T,I,cus", [(1537, 1024, 32), (300, 4224, 32), (257, 1152, 64), (1025, 256, 0)])
 def test_gate_up_several_tiles_per_workgroup(T, I, cus, K):
