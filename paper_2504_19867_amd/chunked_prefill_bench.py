@@ -57,7 +57,7 @@ def main():
         km = kms[len(kms) // 2]
         flops = R * L.n_q_heads * 2 * (L.dim_qk + L.dim_v) * (chunk * prefix + chunk * (chunk + 1) / 2)
         print(f"prefix {prefix:5d} chunk {chunk:5d} x {R}: step wall {wall:.3f} ms, attention kernel {km:.3f} ms "
-              f"({flops / km / 1e9:.0f} TFLOP/s), rest (page write + gather + launches) {wall - km:.3f} ms", flush=True)
+              f"({flops / km / 1e9:.0f} TFLOP/s), rest (page write + launches) {wall - km:.3f} ms", flush=True)
     pool.close()
     ctx.close()
 
