@@ -1,5 +1,5 @@
 """Chunked prefill on the Llama-3-8B layer shape: step time of 4 requests x `chunk` new tokens each over
-`prefix` cached tokens (page write + gather of the context + attention), attention kernel time by HIP events.
+`prefix` cached tokens (page write + attention over the pages), attention kernel time by HIP events.
 Run as `python -m paper_2504_19867_amd.chunked_prefill_bench`."""
 import math
 import os

@@ -16,7 +16,7 @@
 // score is computed twice, and the waves drift apart: while some wait for their tiles (one stage per wave, 18
 // KiB each, 147 KiB per compute unit), others compute.  A read-only loop of this shape takes 5.5 TB/s out of 128 compute
 // units (half as many waves with two stages each: 4.8).  128 requests of 1024 .. 8192 tokens on 128 compute units, whole step: 149
-// us, 4.7 TB/s (FP8 96 us); with a barrier-coupled ring of four stages, in which every wave computed the scores of all tokens, 169
+// us, 4.7 TB/s (FP8 93 us); with a barrier-coupled ring of four stages, in which every wave computed the scores of all tokens, 169
 // (242).
 // What a chunk costs beyond its tiles (record, queries, first tile: 9 us; merge of the waves: 6 us) is covered by the
 // other workgroup of the compute unit: as one workgroup of eight waves the same loop took 174 us at a batch of 128 requests
