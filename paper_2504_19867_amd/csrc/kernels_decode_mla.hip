@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   f32x4 O[VB];
 #pragma unroll
   for (int i = 0; i < VB; ++i) O[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f;                    // running maximum of the scores (FP8: the softmax's reference, as an exponent of 2), row sum
   // FP8: the value product runs on the codes, with softmax weights times scale / (scale of the wave's first token), so that
   // the weights lose nothing to their rounding that they would not lose without scales; O is multiplied at the end.
   float ref[4] = {1.f, 1.f, 1.f, 1.f}, inv_ref[4] = {1.f, 1.f, 1.f, 1.f};
@@ -411,12 +411,13 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
     }
     float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3]));
     mx = mla_max_over_rows(mx);
-    const float m_new = fmaxf(m, mx);
     // O is rescaled only where some running maximum moved; with FP8, whose weights are rounded with their tokens' scales and are
-    // never exact, by more than 2^8 (in six tiles of ten one of 16 heads has a new maximum, and 128 multiplications)
-    const bool moves = __builtin_amdgcn_ballot_w64(FP8 ? (m_new - m) * a.c > 8.f : m_new > m) != 0;
-    const float m_ref = moves ? m_new : m;
-    const float mc = m_ref * a.c;
+    // never exact, where it passed a reference that is put 2^8 above it (in six tiles of ten one of 16 heads has a new maximum, and
+    // 128 multiplications).  (Above: the weights are 1 at most, so that the sums leave fp32's range no earlier than with the maximum itself.)
+    const float top = mx * a.c;
+    const float m_new = FP8 ? (top > m ? top + 8.f : m) : fmaxf(m, mx);
+    const bool moves = __builtin_amdgcn_ballot_w64(m_new > m) != 0;
+    const float mc = FP8 ? m_new : m_new * a.c;
     float p[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(S[i] * a.c - mc);
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
       pb[0] = uint2{mla_pack_bf16(p[0], p[1]), mla_pack_bf16(p[2], p[3])};
     }
     if (moves) {
-      const float alpha = __builtin_amdgcn_exp2f((m - m_new) * a.c);
+      const float alpha = __builtin_amdgcn_exp2f(FP8 ? m - m_new : (m - m_new) * a.c);
       l *= alpha;
 #pragma unroll
       for (int blk = 0; blk < VB; ++blk) O[blk] *= alpha;
@@ -495,10 +496,10 @@ __global__ __launch_bounds__(64 * mla::WAVES, 2) void decode_mla_kernel(MlaArgs 
   float m_tot = sm_m[0][col];
 #pragma unroll
   for (int w = 1; w < WAVES; ++w) m_tot = fmaxf(m_tot, sm_m[w][col]);
-  const float mine = __builtin_amdgcn_exp2f((m - m_tot) * a.c);
+  const float mine = __builtin_amdgcn_exp2f(FP8 ? m - m_tot : (m - m_tot) * a.c);
   if (c4 == 0) {
     sm_l[wave][col] = l * mine;
-    if (wave == 0) sm_m[WAVES][col] = m_tot * a.c;
+    if (wave == 0) sm_m[WAVES][col] = FP8 ? m_tot : m_tot * a.c;
   }
   float* so = (float*)smem;                        // [wave][head][half of the dims]
 #pragma unroll

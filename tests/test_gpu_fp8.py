@@ -192,6 +192,43 @@ def test_decode_over_rows_of_very_different_magnitude(first, rest):
     gp.close()
 
 
+@pytest.mark.parametrize("first, rest", [(2.0 ** 121, 2.0 ** 121), (1e-25, 2.0 ** 106)])
+def test_scores_that_rise_over_values_of_large_magnitude(first, rest):
+    """A maximum that moves too little for O to be rescaled: no weight may exceed 1 for it, or the sums would leave fp32's range where
+    the values (all of one sign here) do not: at the merge of the waves, or in the value product itself, relative to small scales."""
+    lens = list(range(601, 729, 2))
+    gp = fp8_pool(pages=64 * 12)
+    gp.ctx.set_partition(224, 32)                        # 64 workgroups of the decode phase: one per request
+    rng = np.random.default_rng(17)
+    scale = 1.0 / math.sqrt(192)
+    q = np.zeros((64, 16, 576), dtype=np.float32)
+    q[..., 512:] = 1.0
+    tq = W.to_bf16_bits(q)
+    deqs = []
+    for i, n in enumerate(lens):
+        c = np.abs(rng.standard_normal((n, 576))).astype(np.float32)
+        c[:64, :512] *= first                            # the first tile of each of the four waves
+        c[64:, :512] *= rest
+        c[:64, 512:] = 0.0
+        c[64:, 512:] = 0.2
+        c[600:, 512:] = 0.3
+        c[600, 512:] = 1.125                             # 2^7.5 times the first tiles' weight
+        bits = W.to_bf16_bits(c)
+        gp.pool.kv_reserve(100 + i, n)
+        gp.pool.kv_write(DEC, 100 + i, 0, n, dev_bf16(bits))
+        deqs.append(oracle_rows(bits)[1])
+    out = torch.full((64, 16, 512), float("nan"), dtype=torch.bfloat16, device=DEV)
+    gp.pool.decode_step([100 + i for i in range(64)], lens, dev_bf16(tq), out, 16, scale)
+    gp.ctx.phase_sync(DEC)
+    got = host_f64(out)
+    for i, n in enumerate(lens):
+        want = OA.mla_decode_latent(f64(tq[i]), deqs[i], scale, 512)
+        # one bf16 rounding of the weights and one of the output: 2^-9 each, relative, at most
+        assert np.isfinite(got[i]).all(), n
+        assert np.linalg.norm((got[i] - want) / rest) <= 2 ** -7 * np.linalg.norm(want / rest), n
+    gp.close()
+
+
 @pytest.mark.parametrize("rise", [0.0, 1.0, 8.0, -8.0])
 def test_decode_of_many_tiles_per_wave(rise):
     """Contexts of 1 .. 43 tiles that a workgroup has whole (its four waves pass seven stages round, each loads its next tile while
