@@ -249,7 +249,7 @@ inline long dealt_end(const std::vector<int32_t>& weights, int per_xcd) {
 // first, so that the array whose turn it is when all compute units have one is the one that comes free.  (Longest first throughout
 // leaves the next one waiting behind the longest: 300 tokens behind 4000, 5 items a head on 8 compute units, cut into 46 + 21 tiles: the
 // last parts began when the first ones ended, 97.5 us, whole 88.9.)  `whole_end`: when the whole items would end; false, and nothing
-// written, if the parts do not end early enough after all.  (The four pieces above on 256 CUs, both phases there: as
+// written, if no item is cut or the parts do not end early enough after all.  (The four pieces above on 256 CUs, both phases there: as
 // chains 136 us, as workgroups 137, in the order of the chains 147.  A decode step of 16 requests of 1000 tokens that comes in the
 // middle of it ends 111 us later beside chains, 105 beside workgroups, and 79 beside whole items, which leave it compute units of
 // their own; pairs of both steps, queued, 148, 146 and 159 us.)
@@ -276,6 +276,7 @@ inline bool write_shares(const std::vector<PrefillItem>& items, const std::vecto
       ++merge.back().n_parts;
     }
   }
+  if (n_parts == 0) return false;
   const size_t n = all.size();
   auto write = [&](size_t to, const Entry& e) {
     work[to] = items[e.item].work();

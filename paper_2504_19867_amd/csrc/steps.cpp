@@ -269,10 +269,8 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   StepScope step{ctx, SPD_PHASE_PREFILL, st, stream};
   memcpy(st->host, work.data(), work.size() * sizeof(PrefillWork));
   memcpy(st->host + off_chain, chain.data(), chain.size() * sizeof(int32_t));
-  if (!merge.empty()) {
-    memcpy(st->host + off_range, shared.range.data(), shared.range.size() * sizeof(PrefillRange));
-    memcpy(st->host + off_merge, merge.data(), merge.size() * sizeof(PrefillMerge));
-  }
+  if (!shared.range.empty()) memcpy(st->host + off_range, shared.range.data(), shared.range.size() * sizeof(PrefillRange));
+  if (!merge.empty()) memcpy(st->host + off_merge, merge.data(), merge.size() * sizeof(PrefillMerge));
   StepMark mark = step_mark(ctx, SPD_PHASE_PREFILL, step.capturing);
   const double* rope_w = nullptr;
   if (ctx->kernel_timing) SPD_HIP(hipEventRecord(ps.ev_start, stream));

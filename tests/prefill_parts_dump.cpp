@@ -2,6 +2,7 @@
 //   share persistent whole_items n_q_heads n_kv_heads n_req (len prefix)...
 // Answer: "n_chains n_work n_merge looked_at two_groups" (what the search for the cuts looked at; which kernel 192 / 128 dims take), the chains' bounds, a line "row0 len q_tile head0 kv_row0 q_off kt0 kt1 part" per item and a line
 // "row0 len q_tile head0 part0 n_parts" per merged one.
+// Called as "uncut": what comes of sharing out two whole items (write_shares), as chains and as workgroups: "shared_out n_work n_ranges n_merge" each.
 #include <iostream>
 #include <sstream>
 #include <string>
@@ -18,8 +19,19 @@ int prefill_heads_per_block(int group) {
 int prefill_block_m(int group) { return 32 * (8 / prefill_heads_per_block(group)); }
 }  // namespace spd
 
-int main() {
+int main(int argc, char**) {
   using namespace spd;
+  if (argc > 1) {
+    const std::vector<PrefillItem> items(2, PrefillItem{0, 128, 0, 0, 0, 0, 2, 0});
+    for (bool persistent : {false, true}) {
+      std::vector<PrefillWork> work;
+      std::vector<int32_t> chain;
+      PrefillParts parts;
+      const bool shared = write_shares(items, {0, 0}, {PrefillPiece{0, 0, 2, 1}}, 1, 2, persistent, 1000, work, parts.range, chain, parts.merge);
+      std::printf("%d %zu %zu %zu\n", (int)shared, work.size(), parts.range.size(), parts.merge.size());
+    }
+    return 0;
+  }
   std::string line;
   while (std::getline(std::cin, line)) {
     std::istringstream in(line);

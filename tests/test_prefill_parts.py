@@ -18,14 +18,18 @@ FEW = [(128, 1, 32, 8, ((893, 4118), (207, 3798), (547, 7358))), (256, 0, 32, 8,
 MANY = [(256, 0, 32, 8, ((1500, 0),)), (256, 0, 32, 8, ((1659, 519),)), (128, 1, 64, 8, ((4096, 0),) * 4), (256, 0, 32, 8, ((2048, 0),) * 4), (128, 1, 32, 8, ((30, 0),) * 50), (128, 1, 8, 8, ((128, 0),) * 2)]
 
 
-def _deal(tmp_path, batches):
+def _build(tmp_path):
     gxx = shutil.which("g++")
     if gxx is None or not os.path.isdir("/opt/rocm/include"):
         pytest.skip("needs g++ and the HIP headers")
     exe = str(tmp_path / "dump")
     subprocess.run([gxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                     os.path.join(ROOT, "tests", "prefill_parts_dump.cpp"), "-o", exe], check=True)
-    text = ""
+    return exe
+
+
+def _deal(tmp_path, batches):
+    exe, text = _build(tmp_path), ""
     for whole in (0, 1):
         for share, persistent, H, Hkv, reqs in batches:
             text += " ".join(map(str, (share, persistent, whole, H, Hkv, len(reqs), *(x for r in reqs for x in r)))) + "\n"
@@ -105,6 +109,12 @@ def test_items_are_shared_out_where_a_few_long_ones_would_hold_up_the_step(tmp_p
     got, plain = _deal(tmp_path, FEW + MANY)
     n = [_check(b, g, p) for b, g, p in zip(FEW + MANY, got, plain)]
     assert all(n[:len(FEW)]) and not any(n[len(FEW):]), n
+
+
+def test_a_step_in_which_no_item_is_cut_has_whole_items(tmp_path):
+    """Ranges of keys come with parts: the steps' host side and the kernels take either to mean both."""
+    out = subprocess.run([_build(tmp_path), "uncut"], capture_output=True, text=True, check=True, timeout=60).stdout
+    assert out.split("\n")[:2] == ["0 0 0 0"] * 2
 
 
 def test_batches_of_the_gpu_tests_are_shared_out(tmp_path):
