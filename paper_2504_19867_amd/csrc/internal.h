@@ -341,7 +341,7 @@ struct KvRows {
   bool interleaved = false;
   void* q = nullptr;                    // with rope_w: the tiles' query rows [rows, n_q_heads, dk], rotated in place
   int n_q_heads = 0;
-  int cus = 128;                        // compute units that the launch will run on, where the caller knows
+  int cus = 0;                          // compute units that the launch will run on
 };
 bool kv_rows_supported(const PoolGeom& g);
 hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k, const void* v,

@@ -596,11 +596,6 @@ hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_
 
 hipError_t launch_kv_write(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k,
                            const void* v, const StepMark& mark, hipStream_t stream, void* copy_dst, const void* copy_src, uint64_t copy_bytes) {
-  if (kv_rows_supported(g) && v != nullptr) {
-    KvRows x;
-    x.copy_dst = copy_dst; x.copy_src = copy_src; x.copy_bytes = copy_bytes;
-    return launch_kv_rows(g, pool_base, d_tiles, n_tiles, k, v, x, mark, stream);
-  }
   const uint64_t n16 = copy_dst ? (copy_bytes + 15) / 16 : 0;
   const int copy_cols = n16 ? (int)std::min<uint64_t>(16, (n16 + 256ull * g.Hkv - 1) / (256ull * g.Hkv)) : 0;
   if (n_tiles <= 0 && copy_cols == 0) return hipSuccess;

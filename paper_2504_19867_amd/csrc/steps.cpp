@@ -113,7 +113,10 @@ static int kv_copy(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t req_id, int
   const TileDesc* descs = (const TileDesc*)st->dev;              // read over PCIe, once per workgroup
   const StepMark mark = step_mark(ctx, phase, step.capturing);
   const bool fp8 = g.kind == SPD_KV_MLA_LATENT_FP8;
+  KvRows rows;
+  phase_exclusive(ctx, phase, &rows.cus);                         // (its share)
   if (write && fp8) SPD_HIP(launch_kv_write_fp8(g, pool->base, descs, n_descs, k, mark, stream));
+  else if (write && kv_rows_supported(g)) SPD_HIP(launch_kv_rows(g, pool->base, descs, n_descs, k, v, rows, mark, stream));
   else if (write) SPD_HIP(launch_kv_write(g, pool->base, descs, n_descs, k, v, mark, stream));
   else if (fp8) SPD_HIP(launch_kv_gather_fp8(g, pool->base, descs, n_descs, (void*)k, mark, stream));
   else SPD_HIP(launch_kv_gather(g, pool->base, descs, n_descs, (void*)k, (void*)v, mark, stream));

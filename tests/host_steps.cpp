@@ -37,6 +37,7 @@ static std::set<void*> freed;                   // device memory that was given 
 static int fail_launch = -1;                    // the launch of this number fails
 static int n_launches = 0;
 static std::vector<PrefillLists> seen_lists;     // what every attention launch of a prefill step was given
+static std::vector<int> seen_cus;                // compute units that every page write was told of
 static uint64_t staged_bytes = 0;                // of the last prefill step: what its launch copies to the device
 static std::vector<bool> seen_counters;         // may the decode launch merge its own chunks?
 static std::vector<double> seen_w;              // sum of the RoPE frequencies that each decode launch found when it ran
@@ -144,6 +145,7 @@ hipError_t launch_kv_write(const PoolGeom&, char*, const TileDesc*, int, const v
 bool kv_rows_supported(const PoolGeom& g) { return g.kind == SPD_KV_GQA && g.Hkv >= 2; }
 hipError_t launch_kv_rows(const PoolGeom&, char*, const TileDesc*, int, const void*, const void*, const KvRows& x, const StepMark& m, hipStream_t s) {
   staged_bytes = x.copy_bytes;
+  seen_cus.push_back(x.cus);
   return launch(s, m);
 }
 hipError_t launch_kv_gather(const PoolGeom&, const char*, const TileDesc*, int, void*, void*, const StepMark& m, hipStream_t s) { return launch(s, m); }
@@ -416,6 +418,15 @@ static void staged() {
   CHECK(staged_bytes >= items * 24 && staged_bytes < items * 24 + chains * 4 + N * sizeof(TileDesc) + 5 * 16);
 }
 
+// A page write is laid out for the compute units that it runs on: those of its phase's share, a staged one among them.
+static void shares() {
+  CHECK(spd_kv_write(ctx, pool, SPD_PHASE_DECODE, 1, 0, 40, tensor, tensor) == SPD_OK && seen_cus == std::vector<int>{256});
+  CHECK(spd_set_partition(ctx, 192, 64) == SPD_OK);
+  for (const int phase : {SPD_PHASE_PREFILL, SPD_PHASE_DECODE}) CHECK(spd_kv_write(ctx, pool, phase, 1, 0, 40, tensor, tensor) == SPD_OK);
+  CHECK(prefill(long_pool(9, 40), 9, 40) == SPD_OK);
+  CHECK(seen_cus == (std::vector<int>{256, 192, 64, 192}));
+}
+
 // Whatever GPU the calling thread's last call was for, a step's buffers lie on the context's own.
 static void devices() {
   spd_pool* p = long_pool(9, 3000);
@@ -443,6 +454,7 @@ int main(int argc, char** argv) {
   else if (name == "parts") parts();
   else if (name == "staged") staged();
   else if (name == "devices") devices();
+  else if (name == "shares") shares();
   else CHECK(!"a scenario of that name");
   puts("ok");
 }
