@@ -196,7 +196,7 @@ int spd_shm_kv_free_list(spd_shm_pool* pool, int32_t* out, int64_t cap, int64_t*
  *     out[i, h, :] = sum_{j <= prefix + i} softmax_j(scale * q[i, h, :] . K_r[j, g, :]) * V_r[j, g, :]
  * where K_r, V_r are the cached rows followed by the piece's own.  The step reserves blocks for
  * prefix + len tokens, writes the new rows to the pages and attends over each request's rows
- * 0 .. prefix+len-1 where they lie, through its block table.  A request with prefix > 0 must exist
+ * 0 .. prefix+len-1, where they lie, through its block table, or brought together in library memory (up to 1 GiB) where that is faster.  A request with prefix > 0 must exist
  * with at least prefix tokens reserved (else SPD_ENOENT / SPD_EINVAL).
  *
  * With `rope` non-NULL (GQA pools only; spd_rope_config is declared further down; paper, Evaluation

@@ -157,6 +157,7 @@ extern "C" int spd_ctx_destroy(spd_ctx* ctx) {
       if (s.merge_counters) (void)hipFree(s.merge_counters);
       if (s.workspace) (void)hipFree(s.workspace);
       if (s.parts) (void)hipFree(s.parts);
+      if (s.rows) (void)hipFree(s.rows);
       for (auto& r : s.ws_retired) (void)hipFree(r.first);
       for (hipEvent_t e : {s.ev_start, s.ev_end, s.ev_switch, s.ev_cross})
         if (e) (void)hipEventDestroy(e);
@@ -425,7 +426,8 @@ int workspace_reserve(spd_ctx* ctx, int phase, size_t bytes, char** out) {
   return rc;
 }
 
-float* parts_reserve(spd_ctx* ctx, size_t bytes) {
+// Memory that a prefill step can do without, or null.
+static char* spare_reserve(spd_ctx* ctx, size_t bytes, char*& buf, size_t& buf_cap) {
   spd_phase_state& s = ctx->phase[SPD_PHASE_PREFILL];
   // (a staged partition's stream waits for the current one when the step adopts it, and with that joins its capture)
   hipStream_t stream, staged;
@@ -436,12 +438,22 @@ float* parts_reserve(spd_ctx* ctx, size_t bytes) {
   }
   if (stream_capturing(ctx, stream) || (staged != stream && stream_capturing(ctx, staged))) return nullptr;
   const int error = g_last_hip_error;
-  if (buffer_reserve(ctx, SPD_PHASE_PREFILL, bytes, s.parts, s.parts_cap) != SPD_OK) {
+  if (buffer_reserve(ctx, SPD_PHASE_PREFILL, bytes, buf, buf_cap) != SPD_OK) {
     (void)hipGetLastError();
     g_last_hip_error = error;
     return nullptr;
   }
-  return (float*)s.parts;
+  return buf;
+}
+
+float* parts_reserve(spd_ctx* ctx, size_t bytes) {
+  spd_phase_state& s = ctx->phase[SPD_PHASE_PREFILL];
+  return (float*)spare_reserve(ctx, bytes, s.parts, s.parts_cap);
+}
+
+char* rows_reserve(spd_ctx* ctx, size_t bytes) {
+  spd_phase_state& s = ctx->phase[SPD_PHASE_PREFILL];
+  return spare_reserve(ctx, bytes, s.rows, s.rows_cap);
 }
 
 int kernel_timing_mark(spd_ctx* ctx, int phase, int which, hipStream_t stream) {

@@ -68,7 +68,7 @@ struct TileDesc {
   int32_t sub;       // tile index inside the page
   int32_t t_begin;   // first token slot (0..15) touched
   int32_t t_end;     // one past the last token slot touched
-  int32_t pad[3];    // [0]: logical position of the tile's token slot 0 in its request
+  int32_t pad[3];    // [0]: logical position of the tile's token slot 0 in its request; [1]: row of KvRows::k_all that t_begin maps to
 };
 
 // A step's first kernel stores `seq`, the number of the phase's step before it, at `flag`: that step has finished.
@@ -135,7 +135,8 @@ struct PrefillMerge {
 // floats that a part leaves: 8 waves x (32 rows x dv sums, reference and row sum of 32 rows)
 constexpr __host__ __device__ inline size_t prefill_part_floats(int dv) { return 8 * (size_t)(dv * 32 + 64); }
 // What launch_prefill reads on the device.
-// A step with cached tokens has all its keys and values out of the pages, its own rows, written ahead, among them:
+// A step with cached tokens has all its keys and values, its own rows among them, as dense rows, request after request (dense_rows_pay),
+// or out of the pages, where its own are written ahead:
 // `units` holds for each request the numbers of its units (16 tokens of one head: K part, V part, consecutive in a page) for KV head 0,
 // in the order of the tokens; head g's are g * head_units further.
 struct PrefillLists {
@@ -247,6 +248,8 @@ struct spd_phase_state {
   size_t ws_cap = 0;
   char* parts = nullptr;               // sums of items that were shared out (prefill)
   size_t parts_cap = 0;
+  char* rows = nullptr;                // keys and values of a chunked step as dense rows (prefill)
+  size_t rows_cap = 0;
   // workspaces outgrown, with the number of the last step that may still read them: freed once that step has
   // finished (looked at when the workspace grows again, in spd_phase_sync and when the context goes)
   std::vector<std::pair<char*, uint64_t>> ws_retired;
@@ -314,6 +317,8 @@ int workspace_reserve(spd_ctx* ctx, int phase, size_t bytes, char** out);
 // Memory for the parts of a prefill step's items, of its own, so that the workspace grows as ever; null: there is none, or the
 // phase's stream, or the staged one, is being captured (the captured launches would outlive the buffer).
 float* parts_reserve(spd_ctx* ctx, size_t bytes);
+// The same for the dense rows of a chunked step.
+char* rows_reserve(spd_ctx* ctx, size_t bytes);
 int kernel_timing_mark(spd_ctx* ctx, int phase, int which, hipStream_t stream);   // which: 0 begin, 1 end
 // rope.cpp: SPD_OK if the configuration is well-formed; the frequency table (rotary_dim / 2 doubles)
 int rope_config_check(const spd_rope_config* c);
@@ -341,6 +346,9 @@ struct KvRows {
   bool interleaved = false;
   void* q = nullptr;                    // with rope_w: the tiles' query rows [rows, n_q_heads, dk], rotated in place
   int n_q_heads = 0;
+  const TileDesc* d_cached = nullptr;   // tiles of cached rows that go to k_all, v_all, as do the new rows (at TileDesc.pad[1])
+  int n_cached = 0;
+  void *k_all = nullptr, *v_all = nullptr;
   int cus = 0;                          // compute units that the launch will run on
 };
 bool kv_rows_supported(const PoolGeom& g);

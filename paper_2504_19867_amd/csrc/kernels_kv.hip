@@ -121,10 +121,13 @@ __global__ __launch_bounds__(256) void kv_write_kernel(char* __restrict__ base, 
 //     descriptor + token slot; same arithmetic as rope_kernel: fp64 angle reduced to [-pi, pi], fp32 rotation, one
 //     rounding to bf16; the rotated piece goes to the page and back to the caller's k row) and, in workgroups of their
 //     own, of the query rows of the same tiles;
+//   - with DENSE, of a chunked step whose attention kernel reads dense K, V rows (dense_rows_pay), those rows: the cached ones out
+//     of their pages, the new ones beside the page write;
 //   - the copy of the step's metadata to its device twin.
-// None of these reads what another writes, all are bound by memory, and each is short: as launches of their own they waited
+// None of these reads what another writes (the cached and the new tokens of a page are different bytes of it), all are
+// bound by memory, and each is short: as launches of their own they waited
 // for one another's tails (3 prompts of 82 .. 633 tokens on 96 CUs beside a decode iteration: 58 -> 38 us).
-// Workgroups in order: n_copy copying metadata, the page write, the queries (the one part that nothing
+// Workgroups in order: n_copy copying metadata, the page write, the cached rows, the queries (the one part that nothing
 // but memory bounds comes last and fills what the others leave).
 struct RowsArgs {
   char* base;
@@ -137,6 +140,9 @@ struct RowsArgs {
   uint4* copy_dst;
   const uint4* copy_src;
   uint64_t copy_n16;
+  const TileDesc* pre_descs;    // tiles of cached rows; src_row counts rows of k_all, v_all
+  int n_pre;
+  bf16_t *k_all, *v_all;
   const double* w;              // [rot / 2] frequencies
   bf16_t *k_rw, *q;             // k again, writable; q null: queries stay as they are
   int H, q_groups;              // query heads, workgroups per tile (eight heads each)
@@ -145,7 +151,7 @@ struct RowsArgs {
   StepMark mark;
 };
 
-template <int HG, bool ROPE>
+template <int HG, bool ROPE, bool DENSE>
 __global__ __launch_bounds__(256) void kv_rows_kernel(RowsArgs a) {
   const int i = threadIdx.x;
   int blk = blockIdx.x;
@@ -206,6 +212,8 @@ __global__ __launch_bounds__(256) void kv_rows_kernel(RowsArgs a) {
       char* tile = a.base + (uint64_t)d.page * a.page_bytes + (uint64_t)(g0 + g) * a.head_bytes + (uint64_t)d.sub * a.tile_bytes;
       if (k_ok) ks[tk][ck] = kr[g];
       if (v_ok) *(uint4*)&vs[tv][cv * 8] = vr[g];
+      if (DENSE && v_ok)
+        *(uint4*)(a.v_all + ((size_t)(d.pad[1] + tv - d.t_begin) * a.Hkv + g0 + g) * a.dv + cv * 8) = vr[g];
       __syncthreads();
       // K part [chunk][token][8 dims]
       if (out_ok) {
@@ -235,6 +243,7 @@ __global__ __launch_bounds__(256) void kv_rows_kernel(RowsArgs a) {
           }
         }
         store_once(tile + ((size_t)(c_out * 16 + t_out) << 4), piece);
+        if constexpr (DENSE) *(uint4*)(a.k_all + ((size_t)(d.pad[1] + t_out - d.t_begin) * a.Hkv + g0 + g) * a.dk + c_out * 8) = piece;
       }
       // V part [d/32][token quad][d%16][(d/16)%2][4 tokens]
       if (i < v_items) {
@@ -271,6 +280,40 @@ __global__ __launch_bounds__(256) void kv_rows_kernel(RowsArgs a) {
     return;
   }
   blk -= a.n_tiles * a.groups;
+
+  if (DENSE && blk < a.n_pre * a.groups) {
+    // cached rows: the tile's pieces of all the group's heads at once, each head turned round in LDS and stored as rows
+    const TileDesc d = a.pre_descs[blk / a.groups];
+    const int g0 = blk % a.groups * HG, ng = min(HG, a.Hkv - g0);
+    const bool k_in = i < ck_n * TILE_T, v_in = i < v_items;
+    uint4 kr[HG], vr[HG];
+#pragma unroll
+    for (int g = 0; g < HG; ++g) {
+      const char* tile = a.base + (uint64_t)d.page * a.page_bytes + (uint64_t)(g0 + g) * a.head_bytes + (uint64_t)d.sub * a.tile_bytes;
+      kr[g] = vr[g] = uint4{0, 0, 0, 0};
+      if (g < ng && k_in) kr[g] = load_once(tile + ((size_t)i << 4));
+      if (g < ng && v_in) vr[g] = load_once(tile + a.tile_k_bytes + ((size_t)i << 4));
+    }
+#pragma unroll
+    for (int g = 0; g < HG; ++g) {
+      if (g >= ng) break;
+      if (k_in) ks[t_out][c_out] = kr[g];
+      if (v_in) {
+        const uint32_t x[4] = {vr[g].x, vr[g].y, vr[g].z, vr[g].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)                   // element e = (d / 16) % 2 * 4 + token % 4
+          vs[4 * vc4 + (e & 3)][32 * vblk + 16 * (e >> 2) + vm] = (bf16_t)(x[e >> 1] >> (16 * (e & 1)));
+      }
+      __syncthreads();
+      if (k_in && tk >= d.t_begin && tk < d.t_end)
+        *(uint4*)(a.k_all + ((size_t)(d.src_row + tk - d.t_begin) * a.Hkv + g0 + g) * a.dk + ck * 8) = ks[tk][ck];
+      if (i < cv_n * TILE_T && tv >= d.t_begin && tv < d.t_end)
+        *(uint4*)(a.v_all + ((size_t)(d.src_row + tv - d.t_begin) * a.Hkv + g0 + g) * a.dv + cv * 8) = *(const uint4*)&vs[tv][cv * 8];
+      __syncthreads();
+    }
+    return;
+  }
+  if constexpr (DENSE) blk -= a.n_pre * a.groups;
 
   if constexpr (ROPE) {
     // queries, eight heads per workgroup: a thread owns 8 pairs (two pieces) of one token in up to four heads, all on
@@ -564,7 +607,7 @@ static int heads_per_workgroup(int n_tiles, int Hkv, int cus, bool rope) {
 
 hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_tiles, int n_tiles, const void* k, const void* v,
                           const KvRows& x, const StepMark& mark, hipStream_t stream) {
-  const int HG = heads_per_workgroup(n_tiles, g.Hkv, x.cus, x.rope_w != nullptr);
+  const int HG = heads_per_workgroup(n_tiles + x.n_cached, g.Hkv, x.cus, x.rope_w != nullptr);
   RowsArgs a{};
   a.base = pool_base;
   a.page_bytes = g.page_bytes; a.head_bytes = g.head_bytes; a.tile_bytes = g.tile_bytes; a.tile_k_bytes = g.tile_k_bytes;
@@ -573,23 +616,24 @@ hipError_t launch_kv_rows(const PoolGeom& g, char* pool_base, const TileDesc* d_
   a.copy_dst = (uint4*)x.copy_dst; a.copy_src = (const uint4*)x.copy_src;
   a.copy_n16 = x.copy_dst ? (x.copy_bytes + 15) / 16 : 0;
   a.n_copy = (int)std::min<uint64_t>(16ull * g.Hkv, (a.copy_n16 + 255) / 256);
+  a.pre_descs = x.d_cached; a.n_pre = x.n_cached; a.k_all = (bf16_t*)x.k_all; a.v_all = (bf16_t*)x.v_all;
   a.w = x.rope_w; a.k_rw = (bf16_t*)const_cast<void*>(k); a.rot = x.rot; a.off = x.off; a.interleaved = x.interleaved ? 1 : 0;
   a.mark = mark;
   if (x.rope_w && x.q) {
     a.q = (bf16_t*)x.q; a.H = x.n_q_heads; a.q_groups = (a.H + 7) / 8;
   }
-  const int64_t blocks = a.n_copy + (int64_t)n_tiles * a.groups + (int64_t)n_tiles * a.q_groups;
+  const int64_t blocks = a.n_copy + ((int64_t)n_tiles + a.n_pre) * a.groups + (int64_t)n_tiles * a.q_groups;
   if (blocks <= 0) return hipSuccess;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks);
+  auto launch = [&](auto kernel, auto dense) { hipLaunchKernelGGL(x.k_all ? dense : kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a); };
   if (x.rope_w) {
-    if (HG == 8) hipLaunchKernelGGL((kv_rows_kernel<8, true>), grid, dim3(256), 0, stream, a);
-    else if (HG == 4) hipLaunchKernelGGL((kv_rows_kernel<4, true>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((kv_rows_kernel<2, true>), grid, dim3(256), 0, stream, a);
+    if (HG == 8) launch(kv_rows_kernel<8, true, false>, kv_rows_kernel<8, true, true>);
+    else if (HG == 4) launch(kv_rows_kernel<4, true, false>, kv_rows_kernel<4, true, true>);
+    else launch(kv_rows_kernel<2, true, false>, kv_rows_kernel<2, true, true>);
   } else {
-    if (HG == 8) hipLaunchKernelGGL((kv_rows_kernel<8, false>), grid, dim3(256), 0, stream, a);
-    else if (HG == 2) hipLaunchKernelGGL((kv_rows_kernel<2, false>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((kv_rows_kernel<1, false>), grid, dim3(256), 0, stream, a);
+    if (HG == 8) launch(kv_rows_kernel<8, false, false>, kv_rows_kernel<8, false, true>);
+    else if (HG == 2) launch(kv_rows_kernel<2, false, false>, kv_rows_kernel<2, false, true>);
+    else launch(kv_rows_kernel<1, false, false>, kv_rows_kernel<1, false, true>);
   }
   return hipGetLastError();
 }

@@ -5,7 +5,7 @@
 //     out[i,h,:] = sum_{j<=i} softmax_j(scale * q[i,h,:] . k[j,g,:]) * v[j,g,:]
 // (The page write of K, V that belongs to the same step is kv_write_kernel.)
 // With a cached prefix of p tokens (chunked prefill) the request's K, V hold p + len rows, all of them in its
-// pages, and query row i sits at position p + i: the sum runs over j <= p + i.
+// pages or brought together as dense rows, and query row i sits at position p + i: the sum runs over j <= p + i.
 //
 // A dense contraction, so it runs on the matrix cores.  One workgroup = 8 waves = one CU's worth
 // of work; every wave owns 32 query rows of one head.  The 8 waves are HB query heads of ONE
@@ -31,8 +31,8 @@
 // are read back with 16-byte reads in A-operand order; V stays in its natural [key][dim] order
 // and the transposition that the second product needs is done by the LDS transpose read
 // ds_read_b64_tr_b16.  Both tiles are XOR-swizzled at 16-byte granularity against bank conflicts.
-// A step with cached tokens has its tiles out of the pages, four units of 16 tokens each, in the order in which the pages (laid
-// out for the decode kernel) have them, which is an operand order here too.  With the rows brought together in dense tensors first
+// A step with cached tokens has its tiles out of the pages, unless dense_rows_pay (prefill_work.h): four units of 16 tokens each, in the
+// order in which the pages (laid out for the decode kernel) have them, which is an operand order here too.  With the rows brought together in dense tensors first
 // (by the page write's launch, once through HBM and back) 4 pieces of 201 .. 1024 tokens behind up to 7680 cached ones of the
 // Llama-3-8B layer took 139 us on 256 CUs, now 128: the page write's launch 32 -> 17 us, this kernel 101 -> 103.
 //
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   // ---- tile loads.  Load instruction ii = wave + 8 j (j < LPW) fills 1 KiB of the stage.
   // Paged: a stage is the tile's four units one after the other, each as it lies in its page, so an instruction reads 1 KiB of
   // consecutive bytes, from an address that is the wave's but for the lane's 16 bytes.
-  // Dense rows (192 dims): the 64 consecutive 16-byte slots [64 ii, 64 ii + 64), K slots first (row = slot / CHK), then V slots;
+  // Dense rows: the 64 consecutive 16-byte slots [64 ii, 64 ii + 64), K slots first (row = slot / CHK), then V slots;
   // slot s of a row holds the row's chunk s ^ swz(row).  The per-lane part of the address does not depend on the tile
   // (except past the prompt's end).
   auto slot_of = [&](int j, int& row, int& coff, uint32_t& pitch) __attribute__((always_inline)) {
@@ -273,7 +273,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(const bf16_t* __restric
   // Out of pages both lie as the operands want them, chunk by chunk and in quads of tokens, and operands differ by constants: a lane
   // address each.  K: the token's 16 bytes.  V: consecutive 8 bytes per lane, so that row i of a block of 32 is its dim i / 2 + 16 (i % 2)
   // (with row i its dim i the reads have 2-way bank conflicts, 8 x 4096 tokens 9 % longer).  8-byte reads take the LDS twice as long as
-  // transpose reads do, and the whole kernel 2 to 6 % longer than over dense rows, which a step without cached tokens has anyway.
+  // transpose reads do, and the whole kernel up to 4 % longer than over dense rows.  (16-byte reads of a quad's dims m and m + 16, for two blocks at
+  // once: their halves have to be sorted into operands, and long pieces take another 4 to 11 %.)
   constexpr int KOFFS = PAGED ? 1 : DQK == 192 ? 4 : KS, VOFFS = PAGED ? 1 : VB;
   int k_off[KOFFS], v_off[VOFFS];
   if constexpr (PAGED) {
@@ -1079,7 +1080,7 @@ int prefill_heads_per_block(int group) {
 }
 int prefill_block_m(int group) { return 32 * (WAVES / prefill_heads_per_block(group)); }
 
-// (Steps with cached tokens: the instance that takes parts also where there are none.)
+// (Pages: the instance that takes parts also where there are none.)
 template <int DQK, int DV, int HB>
 static void launch_items(dim3 grid, hipStream_t stream, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const PrefillLists& d, int H,
                          int Hkv, float c) {

@@ -23,6 +23,7 @@ uint64_t reserve_entry_locked(spd_pool* pool, spd_req_table& table, int64_t n_to
 }  // namespace spd
 
 static inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
+static inline size_t align4k(size_t x) { return (x + 4095) & ~(size_t)4095; }
 
 // Tile descriptors covering logical positions [start, start + n) of a request whose block
 // table is `bt`, written at `out`; dense row src_row0 maps to position `start`.  Returns how many.
@@ -135,6 +136,7 @@ extern "C" int spd_kv_gather(spd_ctx* ctx, spd_pool* pool, int phase, uint64_t r
 
 // ------------------------------------------------------------------------------------------ prefill
 constexpr int64_t Q_IN_ONE_LAUNCH = 32ll << 20;   // bytes of query rows that are rotated by the page write's launch
+constexpr size_t MOST_DENSE_BYTES = 1ull << 30;   // of a chunked step's dense rows, a buffer that the context keeps
 
 extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_batch* b) {
   if (!ctx || !pool || pool->ctx != ctx || !b || b->n_req <= 0 || !b->req_ids || !b->cu_seqlens) return SPD_EINVAL;
@@ -171,17 +173,10 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
       chunked = chunked || b->prefix_lens[r] > 0;
     }
   }
-  // Chunked: where each request's units of 16 tokens (prefix and this step's rows) begin in the list that the attention kernel finds its
-  // keys and values with
-  std::vector<int32_t> unit_cu;
+  int64_t n_keys = 0;
   if (chunked) {
-    unit_cu.resize((size_t)b->n_req + 1, 0);
-    int64_t rows = 0;
-    for (int r = 0; r < b->n_req; ++r) {
-      const int64_t len = (int64_t)b->prefix_lens[r] + (b->cu_seqlens[r + 1] - b->cu_seqlens[r]);
-      if ((rows += len) > INT32_MAX) return SPD_EINVAL;
-      unit_cu[(size_t)r + 1] = unit_cu[(size_t)r] + (int32_t)((len + TILE_T - 1) / TILE_T);
-    }
+    for (int r = 0; r < b->n_req; ++r) n_keys += (int64_t)b->prefix_lens[r] + (b->cu_seqlens[r + 1] - b->cu_seqlens[r]);
+    if (n_keys > INT32_MAX) return SPD_EINVAL;
   }
 
   int rc;
@@ -192,13 +187,33 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   int share;
   bool persistent = phase_exclusive(ctx, SPD_PHASE_PREFILL, &share);
   if (ctx->env_prefill_persistent >= 0) persistent = ctx->env_prefill_persistent != 0;   // experiment switch
+  // Chunked: the attention kernel's keys and values as dense rows, brought together for it where that pays and there is memory for them
+  // (K whole pages of 4 KiB: the kernel loads rows in 1 KiB pieces, which should not straddle cache lines) ...
+  char *rows_k = nullptr, *rows_v = nullptr;
+  const size_t k_bytes = align4k((size_t)n_keys * g.Hkv * g.dk * 2), v_bytes = (size_t)n_keys * g.Hkv * g.dv * 2;
+  if (chunked && k_bytes + v_bytes <= MOST_DENSE_BYTES &&
+      dense_rows_pay(b->cu_seqlens, b->prefix_lens, b->n_req, b->n_q_heads, b->n_kv_heads, g.dk, share)) {
+    rows_k = rows_reserve(ctx, k_bytes + v_bytes);
+    if (rows_k) rows_v = rows_k + k_bytes;
+  }
+  // ... else out of the pages.  kv_cu: where each request's begin, its first dense row or its first unit of 16 tokens in the list that the
+  // kernel finds them with
+  const bool paged = chunked && !rows_k;
+  std::vector<int32_t> kv_cu;
+  if (chunked) {
+    kv_cu.resize((size_t)b->n_req + 1, 0);
+    for (int r = 0; r < b->n_req; ++r) {
+      const int32_t len = b->prefix_lens[r] + (b->cu_seqlens[r + 1] - b->cu_seqlens[r]);
+      kv_cu[(size_t)r + 1] = kv_cu[(size_t)r] + (paged ? (len + TILE_T - 1) / TILE_T : len);
+    }
+  }
   std::vector<PrefillWork> work;
   std::vector<int32_t> chain;
   PrefillParts shared;
   const std::vector<PrefillMerge>& merge = shared.merge;
   float* parts = nullptr;
   auto deal = [&](PrefillParts* p) {
-    build_prefill_chains(b->cu_seqlens, chunked ? b->prefix_lens : nullptr, chunked ? unit_cu.data() : nullptr, b->n_req,
+    build_prefill_chains(b->cu_seqlens, chunked ? b->prefix_lens : nullptr, chunked ? kv_cu.data() : nullptr, b->n_req,
                          b->n_q_heads, b->n_kv_heads, ctx->xcds, share, persistent, work, chain, p);
   };
   deal(b->dim_qk <= 128 ? &shared : nullptr);     // (the kernel for 192 dims takes whole items)
@@ -212,18 +227,20 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
     }
   }
 
-  // page write and RoPE in one launch, where that kernel takes the pool's shape
+  // page write, RoPE and dense rows in one launch, where that kernel takes the pool's shape (elsewhere the rows, the new ones included, are
+  // gathered out of the pages by a launch of its own)
   const bool one_launch = kv_rows_supported(g);
-  size_t n_descs = 0;
+  size_t n_descs = 0, n_gather = 0;
   for (int r = 0; r < b->n_req; ++r) {
     const int32_t len = b->cu_seqlens[r + 1] - b->cu_seqlens[r], pre = chunked ? b->prefix_lens[r] : 0;
     n_descs += tile_desc_count(pre, len);
+    if (rows_k) n_gather += tile_desc_count(0, one_launch ? pre : pre + len);
   }
   size_t off_chain = align16(work.size() * sizeof(PrefillWork));
   size_t off_range = align16(off_chain + chain.size() * sizeof(int32_t));
   size_t off_merge = align16(off_range + shared.range.size() * sizeof(PrefillRange));
   size_t off_desc = align16(off_merge + merge.size() * sizeof(PrefillMerge));
-  size_t off_units = align16(off_desc + n_descs * sizeof(TileDesc));
+  size_t off_units = align16(off_desc + n_descs * sizeof(TileDesc)), off_gather = off_units;
   // RoPE inside the step: every row's position where the queries have a launch of their own, and room for the frequency
   // table.  A launch of its own has eight waves per SIMD instead of the four that the page write leaves; short batches gain what
   // a launch and its gap cost.  Step with the queries in the same launch / in their own, 256-token prompts of 64 heads: 8 MiB of
@@ -231,14 +248,14 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   // too (147 / 144), 320 MiB 785 / 762.  On 256 CUs one launch stays 3 to 6 % ahead up to 320 MiB, which this line leaves.
   const int32_t n_rows = b->cu_seqlens[b->n_req];
   const bool own_rope = b->rope && (!one_launch || (int64_t)n_rows * b->n_q_heads * b->dim_qk * 2 > Q_IN_ONE_LAUNCH);
-  size_t off_pos = align16(off_units + (chunked ? (size_t)unit_cu.back() * sizeof(int32_t) : 0));
+  size_t off_pos = align16(off_units + (paged ? (size_t)kv_cu.back() * sizeof(int32_t) : n_gather * sizeof(TileDesc)));
   size_t bytes = align16(off_pos + (own_rope ? sizeof(int32_t) * (size_t)n_rows : 0));
   const size_t off_w = bytes, w_bytes = b->rope ? sizeof(double) * (size_t)(b->rope->rotary_dim / 2) : 0;
   spd_stage* st;
   if ((rc = stage_acquire(ctx, SPD_PHASE_PREFILL, bytes + w_bytes, &st)) != SPD_OK) return rc;
   char* ws = nullptr;                                               // the metadata's device twin
   if ((rc = workspace_reserve(ctx, SPD_PHASE_PREFILL, bytes, &ws)) != SPD_OK) return rc;
-  TileDesc* h_desc = (TileDesc*)(st->host + off_desc);
+  TileDesc *h_desc = (TileDesc*)(st->host + off_desc), *h_gather = (TileDesc*)(st->host + off_gather);
   int32_t* h_units = (int32_t*)(st->host + off_units);
   {
     std::lock_guard<std::mutex> lk(pool->mu);                       // atomic: query, get, update
@@ -258,9 +275,14 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
       reserve_locked(pool, b->req_ids[r], pre + len);
       spd_req_table& entry = pool->tables[b->req_ids[r]];
       entry.last_use[SPD_PHASE_PREFILL] = next_step_number(ctx, SPD_PHASE_PREFILL);
-      h_desc += build_tile_descs(g, entry.data(), pre, len, row0, h_desc);
-      if (chunked) {
-        const int n = unit_cu[(size_t)r + 1] - unit_cu[(size_t)r], tpp = g.tiles_per_page;
+      const int n_new = build_tile_descs(g, entry.data(), pre, len, row0, h_desc);
+      if (rows_k) {
+        for (int i = 0; i < n_new; ++i) h_desc[i].pad[1] = kv_cu[(size_t)r] + pre + (h_desc[i].src_row - row0);
+        h_gather += build_tile_descs(g, entry.data(), 0, one_launch ? pre : pre + len, kv_cu[(size_t)r], h_gather);
+      }
+      h_desc += n_new;
+      if (paged) {
+        const int n = kv_cu[(size_t)r + 1] - kv_cu[(size_t)r], tpp = g.tiles_per_page;
         for (int i = 0, page = 0; i < n; ++page)
           for (int sub = 0; sub < tpp && i < n; ++sub) h_units[i++] = entry[(size_t)page] * g.Hkv * tpp + sub;
         h_units += n;
@@ -300,6 +322,10 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
       x.rope_w = rope_w; x.rot = rc_->rotary_dim; x.off = rc_->rotary_offset; x.interleaved = rc_->interleaved != 0;
       if (!own_rope) { x.q = (void*)b->q; x.n_q_heads = b->n_q_heads; }
     }
+    if (rows_k) {
+      x.d_cached = (const TileDesc*)(st->dev + off_gather); x.n_cached = (int)n_gather;
+      x.k_all = rows_k; x.v_all = rows_v;
+    }
     SPD_HIP(launch_kv_rows(g, pool->base, d_desc, (int)n_descs, page_src_k, page_src_v, x, mark, stream));
     if (own_rope)
       SPD_HIP(launch_rope((void*)b->q, b->n_q_heads, nullptr, 0, b->dim_qk, rc_->rotary_dim, rc_->rotary_offset,
@@ -314,13 +340,15 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
       SPD_HIP(launch_kv_write_fp8(g, pool->base, d_desc, (int)n_descs, page_src_k, mark, stream, ws, st->dev, bytes));
     else
       SPD_HIP(launch_kv_write(g, pool->base, d_desc, (int)n_descs, page_src_k, page_src_v, mark, stream, ws, st->dev, bytes));
+    if (rows_k) SPD_HIP(launch_kv_gather(g, pool->base, (const TileDesc*)(ws + off_gather), (int)n_gather, rows_k, rows_v, StepMark{}, stream));
   }
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 0, stream)) != SPD_OK) return rc;
   const PrefillLists lists{(const PrefillWork*)ws, (const int32_t*)(ws + off_chain), (int)chain.size() - 1,
                            shared.range.empty() ? nullptr : (const PrefillRange*)(ws + off_range), (const PrefillMerge*)(ws + off_merge), (int)merge.size(), parts,
-                           chunked ? pool->base : nullptr, (const int32_t*)(ws + off_units), g.tiles_per_page};
+                           paged ? pool->base : nullptr, (const int32_t*)(ws + off_units), g.tiles_per_page};
   const bool two_groups = b->dim_qk == 192 && two_groups_pay(b->cu_seqlens, b->n_req);
-  SPD_HIP(launch_prefill(b->q, b->k, b->v, b->out, lists, two_groups, b->n_q_heads, b->n_kv_heads, b->dim_qk, b->dim_v, b->scale, stream));
+  SPD_HIP(launch_prefill(b->q, rows_k ? rows_k : b->k, rows_k ? rows_v : b->v, b->out, lists, two_groups, b->n_q_heads, b->n_kv_heads, b->dim_qk,
+                         b->dim_v, b->scale, stream));
   if ((rc = kernel_timing_mark(ctx, SPD_PHASE_PREFILL, 1, stream)) != SPD_OK) return rc;
   if ((rc = step.commit()) != SPD_OK) return rc;
   if (ctx->kernel_timing) {

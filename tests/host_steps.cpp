@@ -37,6 +37,7 @@ static std::set<void*> freed;                   // device memory that was given 
 static int fail_launch = -1;                    // the launch of this number fails
 static int n_launches = 0;
 static std::vector<PrefillLists> seen_lists;     // what every attention launch of a prefill step was given
+static std::vector<const void*> seen_keys;       // ... and where it finds its keys, if not in the pages
 static std::vector<int> seen_cus;                // compute units that every page write was told of
 static uint64_t staged_bytes = 0;                // of the last prefill step: what its launch copies to the device
 static std::vector<bool> seen_counters;         // may the decode launch merge its own chunks?
@@ -165,8 +166,9 @@ hipError_t launch_decode_gqa(const PoolGeom&, char*, const DecodeLaunch& d, hipS
 }
 hipError_t launch_decode_prepare(const PoolGeom&, char*, const DecodeLaunch& d, int, void*, hipStream_t s) { return launch(s, d.mark); }
 hipError_t launch_decode_mla(const PoolGeom& g, char* b, const DecodeLaunch& d, hipStream_t s) { return launch_decode_gqa(g, b, d, s); }
-hipError_t launch_prefill(const void*, const void*, const void*, void*, const PrefillLists& d, bool, int, int, int, int, float, hipStream_t s) {
+hipError_t launch_prefill(const void*, const void* k, const void*, void*, const PrefillLists& d, bool, int, int, int, int, float, hipStream_t s) {
   seen_lists.push_back(d);
+  seen_keys.push_back(d.pages ? nullptr : k);
   return launch(s, StepMark{});
 }
 hipError_t launch_rope(void*, int, void*, int, int, int, int, bool, int, const int32_t*, const double*, const StepMark& m, hipStream_t s) { return launch(s, m); }
@@ -409,6 +411,30 @@ static void parts() {
   CHECK(freed.count(first) && !freed.count(second));
 }
 
+// Long pieces behind few cached tokens have their keys as dense rows: not where there is no memory for them, nor under capture; a buffer that
+// is outgrown stays until the steps that were given it have finished.  Short ones behind many read the pages.
+static void dense_rows() {
+  spd_pool *few = long_pool(9, 40), *more = long_pool(20, 40, 32), *many = long_pool(9, 3000);
+  spd_phase_state& ps = ctx->phase[SPD_PHASE_PREFILL];
+  CHECK(prefill(many, 9, 3000) == SPD_OK && !seen_keys.back() && seen_lists.back().units && !ps.rows);
+  void* handle;
+  CHECK(spd_phase_stream(ctx, SPD_PHASE_PREFILL, &handle) == SPD_OK);
+  std::vector<std::function<void()>> graph;
+  run((Stream*)handle);
+  ((Stream*)handle)->graph = &graph;
+  CHECK(prefill(few, 9, 40) == SPD_OK && !seen_keys.back() && !ps.rows);
+  ((Stream*)handle)->graph = nullptr;
+  fail_malloc = true;
+  CHECK(prefill(few, 9, 40) == SPD_OK && !fail_malloc && spd_last_hip_error() == 0 && !seen_keys.back() && !ps.rows);
+  CHECK(prefill(few, 9, 40) == SPD_OK && seen_keys.back() && seen_keys.back() == ps.rows);
+  char* const first = ps.rows;
+  ps.rows_cap = 1 << 10;                             // (as if it were a small one)
+  CHECK(prefill(more, 20, 40, 32) == SPD_OK && seen_keys.back() == ps.rows && ps.rows != first);
+  CHECK(!freed.count(first));
+  CHECK(spd_phase_sync(ctx, SPD_PHASE_PREFILL) == SPD_OK);
+  CHECK(freed.count(first) && !freed.count(ps.rows));
+}
+
 // Lists cross the host link ahead of the attention: a step of whole items stages 24 bytes for each, and no ranges of keys.
 static void staged() {
   constexpr int N = 64;
@@ -455,6 +481,7 @@ int main(int argc, char** argv) {
   else if (name == "staged") staged();
   else if (name == "devices") devices();
   else if (name == "shares") shares();
+  else if (name == "dense_rows") dense_rows();
   else CHECK(!"a scenario of that name");
   puts("ok");
 }

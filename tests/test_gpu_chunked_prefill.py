@@ -278,11 +278,16 @@ def test_decode_steps_beside_items_shared_out_on_the_same_compute_units(pre, dec
     gp.close()
 
 
-@pytest.mark.parametrize("H,Hkv,d,page,rope", [(8, 2, 128, 16, False), (16, 2, 128, 64, True), (4, 1, 64, 32, False), (6, 3, 64, 48, True)])
-def test_pieces_read_from_scattered_pages(H, Hkv, d, page, rope):
-    """Keys and values come out of the pages: pages of one and of several units of 16 tokens in no order, prefixes around the 1024 tokens whose units
-    a workgroup has at hand, ends in every part of a unit, and NaN behind them."""
-    reqs = ((1023, 1), (1024, 33), (1025, 64), (2050, 13), (0, 70), (15, 2), (64, 129))
+# (cached tokens, new ones) per request
+READ_FROM_PAGES = ((1023, 1), (1024, 33), (1025, 64), (2050, 13), (0, 70), (15, 2), (64, 129))
+FEW_CACHED = ((1, 300), (17, 129), (0, 70), (100, 64), (15, 2), (64, 65), (3, 13))
+# q heads, KV heads, dims, page tokens, RoPE, compute units (0: all), requests
+AS_ROWS = [(8, 2, 128, 16, False, 0, FEW_CACHED), (16, 2, 128, 64, True, 0, FEW_CACHED), (6, 3, 64, 48, True, 0, FEW_CACHED), (4, 4, 64, 32, False, 0, FEW_CACHED),
+           (16, 16, 128, 16, True, 0, FEW_CACHED[:3]), (16, 1, 128, 32, True, 32, ((40, 2300), (17, 70)))]
+
+
+def _check_pieces(H, Hkv, d, page, rope, reqs, cus=0):
+    """One step of the requests' pieces, pages in no order and NaN behind the tokens."""
     layer = W.LayerShape("gqa", H, Hkv, d, d, page)
     scale = 1.0 / math.sqrt(d)
     lens = tuple(p + n for p, n in reqs)
@@ -290,6 +295,8 @@ def test_pieces_read_from_scattered_pages(H, Hkv, d, page, rope):
     gp = GpuPool(layer, sum(-(-n // page) for n in lens) + 70, poison=True)
     for op, r, n in W.scramble_ops(60, page, seed=7):
         (gp.pool.kv_reserve if op == "reserve" else lambda r, _: gp.pool.kv_free(r))(r, n)
+    if cus:
+        gp.ctx.set_partition(cus, 256 - cus)
     for r, (p, _) in enumerate(reqs):
         if p:
             gp.pool.kv_reserve(1 + r, p)
@@ -307,3 +314,17 @@ def test_pieces_read_from_scattered_pages(H, Hkv, d, page, rope):
         keys = np.concatenate([f64(k[cu[r]:cu[r] + p]), k_used[a:b]])
         assert_parity(got[a:b], OA.chunk_attention(q_used[a:b], keys, f64(v[cu[r]:cu[r + 1]]), scale), f"request {r}: {n} tokens behind {p}")
     gp.close()
+
+
+@pytest.mark.parametrize("H,Hkv,d,page,rope", [(8, 2, 128, 16, False), (16, 2, 128, 64, True), (4, 1, 64, 32, False), (6, 3, 64, 48, True)])
+def test_pieces_read_from_scattered_pages(H, Hkv, d, page, rope):
+    """Keys and values come out of the pages: pages of one and of several units of 16 tokens in no order, prefixes around the 1024 tokens whose units
+    a workgroup has at hand, ends in every part of a unit, and NaN behind them."""
+    _check_pieces(H, Hkv, d, page, rope, READ_FROM_PAGES)
+
+
+@pytest.mark.parametrize("H,Hkv,d,page,rope,cus,reqs", AS_ROWS)
+def test_pieces_brought_together_as_rows(H, Hkv, d, page, rope, cus, reqs):
+    """The same where the step brings keys and values together as dense rows: prefixes and pieces that end in every part of a unit, and one KV
+    head, whose rows a launch of their own gathers (test_prefill_parts.py has that these are such steps)."""
+    _check_pieces(H, Hkv, d, page, rope, reqs, cus)

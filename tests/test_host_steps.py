@@ -23,7 +23,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["refused_copies", "failed_launch", "captured", "captured_prefill", "parts", "staged", "in_flight", "merges", "launches", "devices", "shares"])
+@pytest.mark.parametrize("scenario", ["refused_copies", "failed_launch", "captured", "captured_prefill", "parts", "staged", "in_flight", "merges", "launches", "devices", "shares", "dense_rows"])
 def test_host_side(exe, scenario):
     run = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=60)
     assert run.returncode == 0 and run.stdout == "ok\n", run.stderr[-2000:]
