@@ -21,6 +21,7 @@
 // Decode batches of up to 128 tokens are bound by reading the weights once and have a kernel of their own
 // (ffn_gate_up_stream_kernel); between 128 and 256 tokens there are 128 x 128 tiles (ffn_gate_up_small_kernel: four waves, two
 // workgroups per compute unit), where those are the faster ones (small_tiles_pay).
+#include "ffn_stream.h"
 #include "internal.h"
 
 #include <type_traits>
@@ -482,7 +483,7 @@ typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2))); 
 // one stage ahead: one barrier per 8 slices.
 // The product is taken transposed (weights are the A operand): a lane then has four consecutive outputs of one token.
 // <NB, 8, 8>: 256 joint rows per workgroup, 128 KiB of weights on the way per CU; <NB, 4, 16>: 128 rows, the same bytes on the
-// way from four waves; five to seven waves where those fill the share's compute units better (launch_stream).  <NB, 6, 8, 2>, <NB, 4, 16, 2>:
+// way from four waves; five to seven waves where those fill the share's compute units better (ffn_stream_units).  <NB, 6, 8, 2>, <NB, 4, 16, 2>:
 // 96 or 64 rows, two waves with half of the slices each, which add up at the end, where the wider ones leave compute units idle.  With the weights staged
 // through LDS (at most 96 KiB on the way, a third to a fifth of the stages taken by x, a barrier per slice) 64 tokens of hidden 4096, inter
 // 14336 took 68 us on 128 CUs and 48 on 256; now 54.8 and 42.7 us (4.3 and 5.5 TB/s) with the weights from HBM, copies of them cycled, and
@@ -660,25 +661,7 @@ static hipError_t launch_stream(const void* x, const void* w_gu, void* out, int 
     hipLaunchKernelGGL(kernel, dim3((unsigned)((units + per_wg - 1) / per_wg)), dim3((unsigned)(64 * waves)), 0, stream, (const bf16_t*)x, (const bf16_t*)w_gu,
                        (bf16_t*)out, T, K, I, mark);
   };
-  // A compute unit runs one workgroup at a time, and one of few waves takes longer per wave (few loads on the way): 64 tokens of hidden
-  // 4096, inter 7168, all workgroups at once, eight to four waves 53, 50.5, 45.7, 40.4, 35.8 us; 128 tokens 60 and 42.7 with eight and
-  // four (the x pieces of other counts do not fit their registers: 78 .. 86).  So the number of rounds decides.  64 tokens of
-  // inter 14336 (896 units), eight waves / the ones taken: 64 CUs 102 / 98 (7), 96 101 / 77 (5), 128 57 / 55.6 (7), 160 57 / 50 (6), 192 57 / 45.5
-  // (5), 256 57 / 43 (4); with only eight and four to choose from the first five took eight.
-  // Three or two units, each with two waves that halve the slices: for shares with more compute units than four units leave
-  // workgroups.  Hidden 8192, inter 7168 (448 units), 64 tokens, four units / the ones taken: 160 and 192 CUs 58 / 51 us (3), 256 58 / 42 (2); 1 token
-  // 46 / 40, 46 / 37; 128 tokens on 256 CUs 73 / 57 (2).  Where they take more rounds they lose (128 CUs, 64 tokens: 58 / 93, 70).
-  static const int cost[] = {NB <= 4 ? 52 : 57, 60, NB <= 4 ? 68 : 71, 77, 87, 96, 100};   // of a workgroup of 2 .. 8 units
-  int per_wg = 8;
-  long least = 0;
-  for (int n = 8; n >= 2; --n) {
-    if (NB > 4 && n != 8 && n != 4 && n != 2) continue;
-    const long wgs = (units + n - 1) / n, t = ((wgs + cus - 1) / cus) * cost[n - 2];
-    if (n == 8 || t < least) {
-      least = t;
-      per_wg = n;
-    }
-  }
+  const int per_wg = ffn_stream_units(NB, units, K, cus);
   if constexpr (NB <= 4) {
     if (per_wg == 7) launch(ffn_gate_up_stream_kernel<NB, 7, 8>, 7, 7);
     if (per_wg == 6) launch(ffn_gate_up_stream_kernel<NB, 6, 8>, 6, 6);

@@ -102,12 +102,12 @@ def test_gate_up_streamed_weights_by_five_to_seven_waves(T, K, I, cus, waves):
 
 
 @pytest.mark.parametrize("T", [1, 16, 33, 64, 65, 128])
-@pytest.mark.parametrize("K", [32, 64, 288, 992, 1024, 1056, 2080])
+@pytest.mark.parametrize("K", [32, 64, 288, 512, 544, 640, 672, 992, 1024, 1056, 2080])
 @pytest.mark.parametrize("I", [896, 1408])
 def test_gate_up_streamed_weights_in_two_parts(T, K, I):
     """Shares of more compute units than workgroups of four units would be (32 for 56 and 88 units): workgroups of two or, up to 64
-    tokens, three units whose slices two waves share: one slice (nothing for the second wave), parts of equal and of unequal length below,
-    at and beyond a ring (1, 4 | 5, 15 | 16, 16, 17 | 16, 33 | 32 slices), spare waves of the last workgroup (88 = 29 x 3 + 1)."""
+    tokens, three units whose slices two waves share (from hidden 512 on up to 32 tokens, else from 544; below it four units): parts of
+    equal and of unequal length at and beyond a ring (8, 9 | 8, 10, 11 | 10, 16 | 15, 16, 17 | 16, 33 | 32 slices), spare waves of the last workgroup (88 = 29 x 3 + 1)."""
     ctx = S.Context(0)
     ctx.set_partition(ctx.device_info()[0] - 32, 32)
     xb, wgb, wub = W.ffn_inputs(T, K, I, seed=3300 + T + I)
