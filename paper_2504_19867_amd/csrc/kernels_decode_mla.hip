@@ -11,10 +11,10 @@
 //
 // Bound: HBM, every cached row is read once.  One workgroup (4 waves, two workgroups per compute unit) owns one
 // (request, chunk of the context); every wave takes tiles of 16 tokens (every fourth tile of the chunk) and does
-// all there is to do with a tile by itself: HBM -> its own LDS stage with global_load_lds_dwordx4, scores, softmax,
-// value product for all 512 dims.  Nothing in the loop is shared between waves, so there is no barrier, no
-// score is computed twice, and the waves drift apart: while some wait for their tiles (one stage per wave, 18
-// KiB each, 147 KiB per compute unit), others compute.  A read-only loop of this shape takes 5.5 TB/s out of 128 compute
+// all there is to do with a tile by itself: HBM -> an LDS stage with global_load_lds_dwordx4, scores, softmax,
+// value product for all 512 dims.  There is no barrier in the loop, no
+// score is computed twice, and the waves drift apart: while some wait for their tiles, others compute.  With bf16 pages they share
+// nothing (one stage per wave, 18 KiB each, 147 KiB per compute unit), with FP8 pages the stages (below).  A read-only loop of this shape takes 5.5 TB/s out of 128 compute
 // units (half as many waves with two stages each: 4.8).  128 requests of 1024 .. 8192 tokens on 128 compute units, whole step: 149
 // us, 4.7 TB/s (FP8 93 us); with a barrier-coupled ring of four stages, in which every wave computed the scores of all tokens, 169
 // (242).

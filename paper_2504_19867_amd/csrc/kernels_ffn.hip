@@ -480,7 +480,7 @@ typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2))); 
 // entries in 16x16x32 operand order) and every wave streams rows of its own through a ring of RING slices in
 // registers, which no barrier touches.  A wave has 16 gate rows and the 16 up rows that belong to them, against all 16 NB
 // tokens.  The x rows, which all waves share, go through LDS, 256 hidden entries at a time in two stages, loaded
-// one stage ahead: one barrier per 8 slices.
+// one stage ahead: one barrier per 8 slices.  (<8, 4, 16, 2>, two halves of 128 rows: 128 entries, 4 slices.)
 // The product is taken transposed (weights are the A operand): a lane then has four consecutive outputs of one token.
 // <NB, 8, 8>: 256 joint rows per workgroup, 128 KiB of weights on the way per CU; <NB, 4, 16>: 128 rows, the same bytes on the
 // way from four waves; five to seven waves where those fill the share's compute units better (ffn_stream_units).  <NB, 6, 8, 2>, <NB, 4, 16, 2>:

@@ -34,7 +34,7 @@ class Split:
 
 def split(exe, batches):
     """[(kind, page tokens, cus, kv heads, q heads, append, override, lengths)] -> (page ids of a record, its header's words, bytes of
-    a staging slot), [Split]"""
+    a staging slot, cost of a chunk over bf16 pages, over FP8 pages), [Split]"""
     text = "".join(" ".join(map(str, (*b[:-1], len(b[-1]), *b[-1]))) + "\n" for b in batches)
     out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=300).stdout.split("\n")
     at, answers = 1, []

@@ -47,10 +47,11 @@ def _check_cover(items, lens):
         assert at == -(-lens[r] // TILE)
 
 
-def test_latent_chunks_fit_the_kernel(exe):
-    batches = [("latent", P, cus, 1, 16, 1, 0, [n] * B) for B, n, P, cus in LONG]
-    batches += [("latent", P, cus, 1, 16, 1, o, lens) for lens, P, cus, o in _random_batches()]
-    (room, words, _), answers = DS.split(exe, batches)
+@pytest.mark.parametrize("kind", ["latent", "latent_fp8"])
+def test_latent_chunks_fit_the_kernel(exe, kind):
+    batches = [(kind, P, cus, 1, 16, 1, 0, [n] * B) for B, n, P, cus in LONG]
+    batches += [(kind, P, cus, 1, 16, 1, o, lens) for lens, P, cus, o in _random_batches()]
+    (room, words, *_), answers = DS.split(exe, batches)
     assert room + words <= KERNEL_THREADS
     longest = 0
     for (_, P, cus, _, _, _, override, lens), s in zip(batches, answers):
@@ -85,14 +86,16 @@ def _loads(s, cost):
     return loads
 
 
-def test_latent_requests_that_need_no_cutting_are_dealt_whole(exe):
+@pytest.mark.parametrize("kind", ["latent", "latent_fp8"])
+def test_latent_requests_that_need_no_cutting_are_dealt_whole(exe, kind):
     """At least a request per workgroup: the most that one gets is no more than with whole requests dealt longest first, where
     a request may be that long."""
-    cost, rng, batches = 20, random.Random(4), []
+    rng, batches = random.Random(4), []
+    cost = DS.split(exe, [])[0][3 if kind == "latent" else 4]
     for n in (30, 100, 300, 1000):
-        batches += [("latent", 64, cus, 1, 16, 1, 0, [int(n * (0.5 + i / (B - 1))) for i in range(B)])
+        batches += [(kind, 64, cus, 1, 16, 1, 0, [int(n * (0.5 + i / (B - 1))) for i in range(B)])
                     for cus, B in ((32, 64), (32, 128), (32, 256), (64, 128), (64, 256), (128, 256))]
-    batches += [("latent", P, cus, 1, 16, 1, 0, [rng.randint(1, rng.choice((20, 300, 5000))) for _ in range(rng.randint(2 * cus, 700))])
+    batches += [(kind, P, cus, 1, 16, 1, 0, [rng.randint(1, rng.choice((20, 300, 5000))) for _ in range(rng.randint(2 * cus, 700))])
                 for P in (32, 64) for cus in (32, 96) for _ in range(6)]
     _, answers = DS.split(exe, batches)
     whole_ones = 0
@@ -127,9 +130,10 @@ def test_metadata_within_the_noalloc_limit_fits_a_staging_slot(exe):
                ("gqa", 1024, 32, 64, 64, 0, 0, [1024 * 31] + [1] * 1900),
                ("gqa", 1024, 256, 1, 1, 0, 8, [1024 * 3800])]       # as many items as it takes, with the chunk length overridden
     batches += [("gqa", P, cus, hkv, 64, 0, o, lens) for (lens, P, cus, o), hkv in zip(_random_batches(), [1, 2, 8, 64] * 40)]
-    batches += [("noalloc", P, cus, 1, 16, 0, o, lens) for lens, P, cus, o in _random_batches()]
-    batches += [("noalloc", 32, 64, 1, 16, 0, 0, [32] * 16384), ("noalloc", 64, 256, 1, 16, 1, 0, [100] * 5000)]
-    (_, _, slot), answers = DS.split(exe, batches)
+    for kind in ("noalloc", "noalloc_fp8"):
+        batches += [(kind, P, cus, 1, 16, 0, o, lens) for lens, P, cus, o in _random_batches()]
+        batches += [(kind, 32, 64, 1, 16, 0, 0, [32] * 16384), (kind, 64, 256, 1, 16, 1, 0, [100] * 5000)]
+    (_, _, slot, *_), answers = DS.split(exe, batches)
     within = [s for s in answers if s.metadata <= LIMIT]
     assert len(within) > 200 and all(s.metadata <= LIMIT for s in answers[:5])
     assert all(s.record_bytes + 4 * 256 <= slot for s in within)    # with the largest frequency table
@@ -139,15 +143,17 @@ def test_metadata_within_the_noalloc_limit_fits_a_staging_slot(exe):
 # Latent batches that fit the fixed workspace with chunks of one length (of 62 pages at most), but do not as they are dealt to
 # the workgroups, which cuts requests at the workgroups' borders: requests, context, page tokens, decode CUs, query heads
 TIGHT = [(2187, 286, 64, 96, 7), (1179, 364, 128, 32, 14), (2598, 1339, 96, 96, 10)]
+TIGHT_FP8 = [(1688, 1449, 128, 192, 11), (3608, 190, 96, 64, 8), (805, 2348, 64, 256, 14)]
 
 
-def test_latent_chunks_are_lengthened_until_the_noalloc_limits_hold(exe):
-    _, even = DS.split(exe, [("latent", P, cus, 1, H, 0, 0, [n] * B) for B, n, P, cus, H in TIGHT])
-    _, fit = DS.split(exe, [("noalloc", P, cus, 1, H, 0, 0, [n] * B) for B, n, P, cus, H in TIGHT])
-    for (B, n, *_), e, f in zip(TIGHT, even, fit):
+@pytest.mark.parametrize("fp8,tight", [("", TIGHT), ("_fp8", TIGHT_FP8)])
+def test_latent_chunks_are_lengthened_until_the_noalloc_limits_hold(exe, fp8, tight):
+    _, even = DS.split(exe, [("latent" + fp8, P, cus, 1, H, 0, 0, [n] * B) for B, n, P, cus, H in tight])
+    _, fit = DS.split(exe, [("noalloc" + fp8, P, cus, 1, H, 0, 0, [n] * B) for B, n, P, cus, H in tight])
+    for (B, n, *_), e, f in zip(tight, even, fit):
         assert e.partials > WORKSPACE
         assert f.partials <= WORKSPACE and f.metadata <= LIMIT
         _check_cover(f.items, [n] * B)
     # a batch within the limits is split as spd_decode_step splits it
     same = [(64, 16, 1, 16, 1, 0, [1500, 65, 640, 2047])]
-    assert DS.split(exe, [("noalloc", *s) for s in same])[1][0].items == DS.split(exe, [("latent", *s) for s in same])[1][0].items
+    assert DS.split(exe, [("noalloc" + fp8, *s) for s in same])[1][0].items == DS.split(exe, [("latent" + fp8, *s) for s in same])[1][0].items

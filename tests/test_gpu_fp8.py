@@ -234,7 +234,8 @@ def test_decode_of_many_tiles_per_wave(rise):
     """Contexts of 1 .. 43 tiles that a workgroup has whole (its four waves pass seven stages round, each loads its next tile while
     it consumes one), with scores that rise or fall by `rise` nats per tile: O is rescaled when a maximum has moved far, by an
     amount in between, or never."""
-    lens = [16 * t - r for t in range(1, 44) for r in ((0, 1) if t % 3 else (15,))][-64:]
+    lens = [16 * t - r for t in range(1, 44) for r in ((15,) if t % 3 == 0 else (0, 1) if t <= 31 else (t % 2,))]
+    assert len(lens) == 64 and {-(-n // 16) for n in lens} == set(range(1, 44))
     gp = fp8_pool(pages=sum(-(-n // 64) for n in lens))
     gp.ctx.set_partition(224, 32)                        # 64 workgroups of the decode phase: one per request
     rng = np.random.default_rng(31)

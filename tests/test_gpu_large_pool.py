@@ -1,7 +1,7 @@
 """GPU parity on a pool larger than 4 GiB: every page the checked requests own lies beyond byte offset 2^32 of the
 pool (a filler request holds the pages below), so page addressing that dropped to 32 bits anywhere on the way
 (page number x page bytes, a block table entry widened too late) reads or writes the wrong page and fails here.
-One case per KV layout: prefill page write, gather, decode over the written pages, decode with append."""
+One case per KV layout: prefill page write, gather, decode over the written pages, decode with append; chunked prefill over GQA pages."""
 import math
 
 import numpy as np
@@ -99,6 +99,24 @@ def test_gqa_pages_beyond_4gib():
     gp.ctx.phase_sync(DEC)
     want = np.stack([OA.decode_attention(f64(qd[i]), f64(kd[i]), f64(vd[i]), scale) for i in range(3)])
     assert_parity(host_f64(od), want, "split-K decode above 4 GiB")
+
+    # the next pieces of those contexts: the attention reads the pages; then of the shortest one alone, whose rows the step brings together
+    cur = dict(zip(dids, ctx_lens))
+    kc, vc = dict(zip(dids, kd)), dict(zip(dids, vd))
+    for rids, new in (((11, 12, 13), (40, 7, 100)), ((13,), (64,))):
+        cu = np.concatenate([[0], np.cumsum(new)]).astype(np.int64)
+        qn, kn, vn = W.normal_bf16(rng, (cu[-1], 32, 128)), W.normal_bf16(rng, (cu[-1], 8, 128)), W.normal_bf16(rng, (cu[-1], 8, 128))
+        oc = torch.empty((cu[-1], 32, 128), dtype=torch.bfloat16, device=DEV)
+        gp.ctx.phase_wait_for(PRE, DEC)
+        gp.pool.prefill_step(rids, cu, dev_bf16(qn), dev_bf16(kn), dev_bf16(vn), oc, 32, 8, 128, 128, scale, prefix_lens=[cur[r] for r in rids])
+        gp.ctx.phase_sync(PRE)
+        got = host_f64(oc)
+        for r, a, b in zip(rids, cu[:-1], cu[1:]):
+            kc[r], vc[r] = np.concatenate([kc[r], kn[a:b]]), np.concatenate([vc[r], vn[a:b]])
+            cur[r] += int(b - a)
+            ora.reserve(r, cur[r])
+            assert_table_above_4gib(gp, ora, r, page_bytes, n_low)
+            assert_parity(got[a:b], OA.chunk_attention(f64(qn[a:b]), f64(kc[r]), f64(vc[r]), scale), f"chunk of request {r} above 4 GiB")
     assert gp.pool.kv_free_list() == ora.free_stack and gp.pool.stats()[3] == ora.op_seq
     gp.close()
 
