@@ -493,13 +493,14 @@ inline void build_prefill_chains(const int32_t* cu_seqlens, const int32_t* prefi
 // A step with cached tokens: are its keys and values as dense rows, brought together ahead of the attention kernel, the faster way, or
 // the pages?  Out of the pages the kernel takes up to 4 % longer (operands of V come in smaller reads) and 1 to 2 us longer to begin (the list of
 // units is one more round trip); dense rows cost a pass over the cached ones and, in the page write's launch, a second store of the new ones.
-// So the pairs of query and key per cached row decide, and the pass is free where it is short.  Whole step, pages / dense rows, 8 KV heads of 128 dims on 128
+// So the pairs of query and key per cached row decide, and the pass is free where it is short, or runs beside the rotation of the step's
+// queries (`rotates`: 64 query heads, 12 pieces of 128 behind 100 on 256 CUs 45 / 41 us, 4 of 256 on 64 69 / 66).  Whole step, pages / dense rows, 8 KV heads of 128 dims on 128
 // CUs: 32 query heads, 4 pieces of 2048 behind 100 tokens 289 / 277 us, 1 of 4096 behind 1500 335 / 325, 4 of 1024 behind 6000 569 / 594, 4 of
 // 256 behind 1500 55 / 65, 1 of 128 behind one 19.3 / 17.7; 64 query heads, 1 of 1024 behind 6000 290 / 286, 4 of 256 behind 6000 278 / 307.  With a query
 // head per KV head the pages cost the kernel 1 % at most: 16 heads, 1 of 4096 behind 1500 180 / 183.  One KV head has a launch of its own for
 // the rows, the new ones among them: 32 query heads, 1 of 4096 behind 100 203 / 199, 4 of 700 behind 400 72 / 74.  Over 1207 steps (32 to 16000 cached tokens, 1
 // to 12 pieces of 40 to 4096, eleven layers, 64 to 256 CUs) 0.2 % over the faster one of the two on average, always pages 1.5 %, always rows 10 %.
-inline bool dense_rows_pay(const int32_t* cu_seqlens, const int32_t* prefix_lens, int n_req, int H, int Hkv, int dim, int share) {
+inline bool dense_rows_pay(const int32_t* cu_seqlens, const int32_t* prefix_lens, int n_req, int H, int Hkv, int dim, int share, bool rotates) {
   double pairs = 0, cached = 0;                   // of query and key, over all heads; rows of all KV heads
   for (int r = 0; r < n_req; ++r) {
     const double len = cu_seqlens[r + 1] - cu_seqlens[r];
@@ -507,6 +508,7 @@ inline bool dense_rows_pay(const int32_t* cu_seqlens, const int32_t* prefix_lens
     cached += (double)prefix_lens[r] * Hkv;
   }
   if (Hkv == 1) return pairs * dim > 1.2e6 * 128 * share;
+  if (rotates) pairs += 400. * cu_seqlens[n_req] * H;
   return pairs * dim + 1e5 * 128 * share > (H > Hkv ? 8e3 : 3e4) * cached * dim;
 }
 

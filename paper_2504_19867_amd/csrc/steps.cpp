@@ -192,7 +192,7 @@ extern "C" int spd_prefill_step(spd_ctx* ctx, spd_pool* pool, const spd_prefill_
   char *rows_k = nullptr, *rows_v = nullptr;
   const size_t k_bytes = align4k((size_t)n_keys * g.Hkv * g.dk * 2), v_bytes = (size_t)n_keys * g.Hkv * g.dv * 2;
   if (chunked && k_bytes + v_bytes <= MOST_DENSE_BYTES &&
-      dense_rows_pay(b->cu_seqlens, b->prefix_lens, b->n_req, b->n_q_heads, b->n_kv_heads, g.dk, share)) {
+      dense_rows_pay(b->cu_seqlens, b->prefix_lens, b->n_req, b->n_q_heads, b->n_kv_heads, g.dk, share, b->rope != nullptr)) {
     rows_k = rows_reserve(ctx, k_bytes + v_bytes);
     if (rows_k) rows_v = rows_k + k_bytes;
   }

@@ -2,7 +2,7 @@
 //   share persistent whole_items n_q_heads n_kv_heads n_req (len prefix)...
 // Answer: "n_chains n_work n_merge looked_at two_groups" (what the search for the cuts looked at; which kernel 192 / 128 dims take), the chains' bounds, a line "row0 len q_tile head0 kv_row0 q_off kt0 kt1 part" per item and a line
 // "row0 len q_tile head0 part0 n_parts" per merged one.
-// Called as "rows": whether a chunked step has its keys as dense rows (dense_rows_pay), 0 or 1 per line "share H Hkv dim n (len prefix)..".
+// Called as "rows": whether a chunked step has its keys as dense rows (dense_rows_pay), 0 or 1 per line "share H Hkv dim rope n (len prefix)..".
 // Called as "uncut": what comes of sharing out two whole items (write_shares), as chains and as workgroups: "shared_out n_work n_ranges n_merge" each.
 #include <iostream>
 #include <sstream>
@@ -23,14 +23,14 @@ int prefill_block_m(int group) { return 32 * (8 / prefill_heads_per_block(group)
 int main(int argc, char** argv) {
   using namespace spd;
   if (argc > 1 && std::string(argv[1]) == "rows") {
-    int share, H, Hkv, dim, n;
-    while (std::cin >> share >> H >> Hkv >> dim >> n) {
+    int share, H, Hkv, dim, rope, n;
+    while (std::cin >> share >> H >> Hkv >> dim >> rope >> n) {
       std::vector<int32_t> cu(1, 0), pre((size_t)n);
       for (int i = 0, len; i < n; ++i) {
         std::cin >> len >> pre[(size_t)i];
         cu.push_back(cu.back() + len);
       }
-      std::printf("%d\n", (int)dense_rows_pay(cu.data(), pre.data(), n, H, Hkv, dim, share));
+      std::printf("%d\n", (int)dense_rows_pay(cu.data(), pre.data(), n, H, Hkv, dim, share, rope != 0));
     }
     return 0;
   }

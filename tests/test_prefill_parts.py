@@ -130,17 +130,22 @@ def test_batches_of_the_gpu_tests_are_shared_out(tmp_path):
 
 def test_which_chunked_steps_have_dense_rows(tmp_path):
     """Long pieces behind few cached tokens, which the attention over the pages would take longer for; the GPU tests of either way are that."""
-    def ask(cases):       # share, q heads, KV heads, dims, ((cached, new), ..)
-        text = "".join(" ".join(map(str, (*c[:4], len(c[4]), *(x for p, n in c[4] for x in (n, p))))) + "\n" for c in cases)
+    def ask(cases):       # share, q heads, KV heads, dims, RoPE, ((cached, new), ..)
+        text = "".join(" ".join(map(str, (*c[:4], int(c[4]), len(c[5]), *(x for p, n in c[5] for x in (n, p))))) + "\n" for c in cases)
         return [int(x) for x in subprocess.run([_build(tmp_path), "rows"], input=text, capture_output=True, text=True, check=True, timeout=60).stdout.split()]
 
-    rows = [(cus or 256, H, Hkv, d, reqs) for H, Hkv, d, _, _, cus, reqs in AS_ROWS]
-    rows += [(128, 32, 8, 128, ((100, 2048),) * 4), (128, 32, 8, 128, ((1500, 4096),)), (128, 32, 8, 128, ((1, 128),)), (128, 64, 8, 128, ((6000, 2048),)),
-             (64, 64, 8, 128, ((64, 2048),) * 8), (256, 64, 8, 128, ((64, 512),) * 4), (128, 32, 1, 128, ((100, 4096),)),
-             (256, 32, 8, 128, ((1 << 20, 1 << 20),) * 64)]           # (sums beyond 2^63)
-    pages = [(256, H, Hkv, d, READ_FROM_PAGES) for H, Hkv, d in ((8, 2, 128), (16, 2, 128), (4, 1, 64), (6, 3, 64))]
-    pages += [(128, 32, 8, 128, ((6000, 1024),) * 4), (128, 32, 8, 128, ((1500, 256),) * 4), (128, 64, 8, 128, ((6000, 256),) * 4), (128, 16, 16, 128, ((1500, 4096),)),
-              (128, 32, 1, 128, ((400, 700),) * 4), (256, 32, 8, 128, ((0, 201), (7680, 1024), (3000, 700), (4000, 600)))]
+    rows = [(cus or 256, H, Hkv, d, rope, reqs) for H, Hkv, d, _, rope, cus, reqs in AS_ROWS]
+    for rope in (False, True):
+        rows += [(128, 32, 8, 128, rope, ((100, 2048),) * 4), (128, 32, 8, 128, rope, ((1500, 4096),)), (128, 32, 8, 128, rope, ((1, 128),)),
+                 (128, 64, 8, 128, rope, ((6000, 2048),)), (64, 64, 8, 128, rope, ((64, 2048),) * 8), (256, 64, 8, 128, rope, ((64, 512),) * 4),
+                 (128, 32, 1, 128, rope, ((100, 4096),)), (256, 32, 8, 128, rope, ((1 << 20, 1 << 20),) * 64)]           # (the last: sums beyond 2^63)
+    rows.append((256, 64, 8, 128, True, ((100, 128),) * 12))
+    pages = [(256, H, Hkv, d, rope, READ_FROM_PAGES) for H, Hkv, d, rope in ((8, 2, 128, False), (16, 2, 128, True), (4, 1, 64, False), (6, 3, 64, True))]
+    for rope in (False, True):
+        pages += [(128, 32, 8, 128, rope, ((6000, 1024),) * 4), (128, 32, 8, 128, rope, ((1500, 256),) * 4), (128, 64, 8, 128, rope, ((6000, 256),) * 4),
+                  (128, 16, 16, 128, rope, ((1500, 4096),)), (128, 32, 1, 128, rope, ((400, 700),) * 4),
+                  (256, 32, 8, 128, rope, ((0, 201), (7680, 1024), (3000, 700), (4000, 600)))]
+    pages.append((256, 64, 8, 128, False, ((100, 128),) * 12))
     assert ask(rows) == [1] * len(rows) and ask(pages) == [0] * len(pages)
 
 
